@@ -11,8 +11,8 @@ namespace vsa {
 // Preprocess.  Per token i of cube c (pad rows produce zeros):
 //   dGc_i = dO_i * Oc[c]      dGf_i = dO_i * Of_i      dOf_i = dO_i * Gf_i  (bf16, feeds the MFMAs)
 //   Delta_i = sum_d dOf_i * Of_i                       dOc[c] = sum_i dO_i * Gc_i
-//   ld_i = (lse_i * log2(e), Delta_i) as one pair per row, lse = +inf on pad rows (makes P = 0
-//          there in the fine backward kernels)
+//   rowd   per 32 rows: 32 values of -lse_i * log2(e) / sl2 (so that P = exp2((S + value) * sl2); -30000 on
+//          pad rows, where P then underflows to 0), then 32 values of -Delta_i
 // One workgroup per (b*h, cube), which walks the cube's m blocks of 64 rows; thread layout as in the
 // pooling kernel.
 template <int D>
@@ -20,8 +20,8 @@ __global__ __launch_bounds__(256) void k_bwd_pre(int Nc, int m_blocks, const uin
                                                  const uint4* __restrict__ gc, const uint4* __restrict__ gf,
                                                  const uint4* __restrict__ of, const float* __restrict__ oc,
                                                  uint4* __restrict__ dgc, uint4* __restrict__ dgf,
-                                                 uint4* __restrict__ dof, float* __restrict__ ld,
-                                                 uint4* __restrict__ ldb, float inv_sl2, float* __restrict__ doc,
+                                                 uint4* __restrict__ dof, float* __restrict__ rowd, float inv_sl2,
+                                                 float* __restrict__ doc,
                                                  const float* __restrict__ lse_f, int H, long long do_head_stride,
                                                  long long do_row_stride) {
   constexpr int CPR = D / 8, RG = 256 / CPR, RPT = kTile / RG;
@@ -80,14 +80,9 @@ __global__ __launch_bounds__(256) void k_bwd_pre(int Nc, int m_blocks, const uin
 #pragma unroll
     for (int o = CPR / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
     if (ch == 0) {
-      const float lse2 = valid ? lse_f[row0 + r] * kLog2e : INFINITY;
-      *(float2*)&ld[2 * (row0 + r)] = make_float2(lse2, dsum);
-      // the same pair as two rows of bf16 MFMA operand slots: -lse2/sl2 and -Delta, each split into
-      // three bf16 parts that add up to the fp32 value, then a constant slot (1 for the first, 0
-      // for the second).  Pad rows carry a large finite negative number instead of -inf.
-      const uint2 a = split3_bf16(valid ? -lse2 * inv_sl2 : -30000.f, 1.f);
-      const uint2 b = split3_bf16(-dsum, 0.f);
-      ldb[row0 + r] = make_uint4(a.x, a.y, b.x, b.y);
+      float* p = rowd + 2 * (row0 + (r & ~31)) + (r & 31);
+      p[0] = valid ? -lse_f[row0 + r] * kLog2e * inv_sl2 : -30000.f;
+      p[32] = -dsum;
     }
   }
   }
@@ -103,7 +98,7 @@ __global__ __launch_bounds__(256) void k_bwd_pre(int Nc, int m_blocks, const uin
 
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
-                          void* dof, float* ld, void* ldb, float scale, float* doc, const float* lse_f, int H,
+                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
                           int dout_token_major, hipStream_t s) {
   const unsigned grid = (unsigned)(BH * Nc);
   const float inv_sl2 = 1.0f / (scale * kLog2e);
@@ -111,12 +106,12 @@ hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* m
   const long long dhs = dout_token_major ? cpr : Np * cpr, drs = dout_token_major ? H * cpr : cpr;
   if (d == 128)
     k_bwd_pre<128><<<grid, 256, 0, s>>>(Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, ld,
-                                        (uint4*)ldb, inv_sl2, doc, lse_f, H, dhs, drs);
+                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
+                                        inv_sl2, doc, lse_f, H, dhs, drs);
   else
     k_bwd_pre<64><<<grid, 256, 0, s>>>(Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                       (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, ld,
-                                       (uint4*)ldb, inv_sl2, doc, lse_f, H, dhs, drs);
+                                       (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
+                                       inv_sl2, doc, lse_f, H, dhs, drs);
   return hipGetLastError();
 }
 

@@ -78,4 +78,40 @@ VSA_RULE int slots_wanted(int deg, int seg) { const int r = split_runs(deg, seg)
 // stay within `cap`.
 VSA_RULE bool split_granted(int runs, int wanted_before, int cap) { return runs > 1 && wanted_before + runs <= cap; }
 
+// dK/dV pass: workgroup -> (b, h) and item of its longest-first order.  Workgroups are dealt to the 8 XCDs round-robin
+// by blockIdx and every XCD has an L2 of its own, so an XCD takes whole heads as long as there are 8 of
+// them left (two heads' tiles in an L2 instead of parts of all the heads in flight), then half heads, quarter
+// heads and an eighth, always dealing a head's items in turn so that the XCDs carry the same load.
+// Against all XCDs on one head after the other (B*H = 16 .. 32): 3 to 14 % (d = 64, 256 blocks, top-32,
+// local lists: 343 -> 295 us).
+VSA_RULE int dkv_share(int heads, int items) { return (heads * items + 7) / 8; }  // per XCD
+VSA_RULE void dkv_item(unsigned b, int BH, int items, int& bh, int& item) {
+  const unsigned x = b & 7u;
+  unsigned i = b >> 3;
+  const unsigned whole = (unsigned)(BH >> 3) * items;
+  if (i < whole) {
+    bh = (int)(x + 8u * (i / items));
+    item = (int)(i % items);
+    return;
+  }
+  i -= whole;
+  int base = BH & ~7, g = 4;  // groups of 4, 2 and 1 heads, in this order
+  while (!(BH & g) || i >= (unsigned)dkv_share(g, items)) {
+    if (BH & g) {
+      i -= dkv_share(g, items);
+      base += g;
+    }
+    g >>= 1;
+  }
+  const unsigned n = x + 8u * i;
+  bh = base + (int)(n & (g - 1));
+  item = (int)(n / g);
+}
+VSA_RULE unsigned dkv_grid(int BH, int items) {
+  int per = (BH >> 3) * items;
+  for (int g = 4; g; g >>= 1)
+    if (BH & g) per += dkv_share(g, items);
+  return 8u * (unsigned)per;
+}
+
 }  // namespace vsa

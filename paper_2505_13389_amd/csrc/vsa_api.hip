@@ -126,8 +126,8 @@ FwdWs carve_fwd(const vsa_params_t* p, const Geo& g, void* ws) {
 struct BwdWs {
   uint64_t* mask;
   int32_t* kcnt;
-  float *qc, *kc, *vc, *ld, *doc, *ac, *dsc, *dqc, *dkc, *dvc;
-  void *dof, *ldb;
+  float *qc, *kc, *vc, *rowd, *doc, *ac, *dsc, *dqc, *dkc, *dvc;
+  void* dof;
   int32_t *row_ptr, *col, *order, *split, *idx_blocks;
   uint32_t* bits;
   float* parts;
@@ -160,8 +160,7 @@ BwdWs carve_bwd(const vsa_params_t* p, const Geo& g, void* ws) {
   w.qc = c.take<float>(bh * g.Nc * p->d);
   w.kc = c.take<float>(bh * nk * p->d);
   w.vc = c.take<float>(bh * nk * p->d);
-  w.ld = c.take<float>(2 * bh * g.Np);
-  w.ldb = c.take<uint32_t>(4 * bh * g.Np);
+  w.rowd = c.take<float>(2 * bh * g.Np);
   w.doc = c.take<float>(bh * g.Nc * p->d);
   w.ac = c.take<float>(bh * g.Nc * nk);
   w.dsc = c.take<float>(bh * g.Nc * nk);
@@ -369,7 +368,7 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
     if (sub) VSA_TRY("pool", vsa::launch_pool_keys16(BH, g.Nc, p->d, w.mask, w.kcnt, k, v, w.kc, w.vc, s));
   }
   VSA_TRY("bwd_pre", vsa::launch_bwd_pre(BH, g.Nc, g.m, p->d, w.mask, dout, gate_c, gate_f, out_fine, out_coarse, dgate_c, dgate_f,
-                              w.dof, w.ld, w.ldb, scale, w.doc, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, s));
+                              w.dof, w.rowd, scale, w.doc, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, s));
   VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, w.ac, w.dsc,
                                  w.dqc, w.dkc, w.dvc, w.kcnt, s));
   const int32_t* lists = block_idx;
@@ -382,10 +381,10 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
     lists = w.idx_blocks;
   }
   VSA_TRY("transpose_map", vsa::launch_transpose_map(BH, g.Nb, kb, lists, w.bits, w.row_ptr, w.col, w.order, w.split, w.seg, w.cap, sub ? 1 : 0, s));
-  VSA_TRY("fine_bwd_dq", vsa::launch_fine_bwd_dq(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.ld,
+  VSA_TRY("fine_bwd_dq", vsa::launch_fine_bwd_dq(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.rowd,
                                   w.dqc, w.mask, dq, g.m, sub ? 1 : 0, s));
   VSA_TRY("fine_bwd_dkv", vsa::launch_fine_bwd_dkv(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, w.col, w.order, w.split, w.parts,
-                                   w.cap, w.ldb, w.dkc, w.dvc, w.mask, dk, dv, g.m, sub ? 1 : 0, s));
+                                   w.cap, w.rowd, w.dkc, w.dvc, w.mask, dk, dv, g.m, sub ? 1 : 0, s));
   return VSA_OK;
 }
 
@@ -493,6 +492,18 @@ int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, 
     if (items > max_items) max_items = items;
     if (slots_hi > max_slots) max_slots = slots_hi;
     if (nsplit > max_split) max_split = nsplit;
+  }
+  {  // every item of every (b, h) belongs to exactly one workgroup of the dK/dV launch
+    const int BH = p->B * p->H, per = Nc + cap;
+    std::vector<unsigned char> taken((size_t)BH * per);
+    const unsigned grid = vsa::dkv_grid(BH, per);
+    for (unsigned b = 0; b < grid; ++b) {
+      int bh, item;
+      vsa::dkv_item(b, BH, per, bh, item);
+      if (bh < 0 || bh >= BH || item < 0) ++bad;
+      else if (item < per && taken[(size_t)bh * per + item]++) ++bad;
+    }
+    for (unsigned char t : taken) bad += t != 1;
   }
   if (report) {
     report[0] = bad; report[1] = max_deg; report[2] = max_items; report[3] = max_slots;

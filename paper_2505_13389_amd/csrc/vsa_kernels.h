@@ -35,7 +35,7 @@ hipError_t launch_expand_lists(int BH, int Nc, int K, int m, const int32_t* idx,
 // backward
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
-                          void* dof, float* ld, void* ldb, float scale, float* doc, const float* lse_f, int H,
+                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
                           int dout_token_major, hipStream_t s);
 hipError_t launch_coarse_bwd(int BH, int Nq, int Nk, int d, float scale, const float* qc, const float* kc,
                              const float* vc, const float* lse_c, const float* doc, float* ac, float* dsc, float* dqc,
@@ -44,12 +44,12 @@ hipError_t launch_transpose_map(int BH, int Nc, int K, const int32_t* idx, uint3
                                 int32_t* col, int32_t* order, int32_t* split, int seg, int cap, int key_cubes_16,
                                 hipStream_t s);
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
-                              const void* dof, const int32_t* idx, const float* ld,
+                              const void* dof, const int32_t* idx, const float* rowd,
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,
                               hipStream_t s);
 hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                                const void* dof, const int32_t* col, const int32_t* order, const int32_t* split,
-                               float* parts, int cap, const void* ldb, const float* dkc, const float* dvc,
+                               float* parts, int cap, const float* rowd, const float* dkc, const float* dvc,
                                const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s);
 
 }  // namespace vsa

@@ -168,3 +168,15 @@ def test_list_index_rules_keep_hostile_lists_in_bounds(lib, shape, topk, cube):
     assert rep["longest_list"] == Nc * m
     if Nc * m > rep["seg"] and 2 * topk * m <= rep["cap"]:  # (more equal long lists than slots: nothing to balance)
         assert rep["split_lists"] == topk * m and rep["items"] > Nc * m  # the sink lists are shared by several workgroups
+
+
+@pytest.mark.parametrize("BH", list(range(1, 18)) + [23, 24, 40])
+def test_dkv_workgroups_cover_every_item_once(lib, BH):
+    """The workgroup -> (b, h), item mapping of the dK/dV launch (whole heads per XCD, then half, quarter and
+    eighth heads) is checked inside the replay: every item exactly once, none outside, for any number of heads."""
+    import numpy as np
+    pb = vsa.Problem(1, BH, 7, 14, 30, 64, 3)
+    _, Nc = vsa.vsa_padded_tokens(pb)
+    lists = np.broadcast_to(np.arange(3, dtype=np.int32), (1, BH, Nc, 3))
+    rc, rep = vsa.vsa_host_replay_lists(pb, lists)
+    assert rc == 0 and rep["violations"] == 0, rep

@@ -11,10 +11,15 @@ SOURCES = ["vsa_api.hip", "permute_pool.hip", "coarse.hip", "fine_fwd.hip", "bwd
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
+# Kernels with more than 256 registers that mix matrix instructions of both kinds: those the compiler emits
+# accumulate in ordinary registers (their results feed vector arithmetic at once), the accumulation registers are
+# filled by instructions written as assembly.
+FILE_FLAGS = {"fine_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
 
 def _compile(src: str, extra) -> str:
     obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-    r = subprocess.run(["hipcc", *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj], capture_output=True, text=True)
+    r = subprocess.run(["hipcc", *FLAGS, *FILE_FLAGS.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj], capture_output=True, text=True)
     # the host pass does not know the packed-fp32 feature and says so on every file: drop that line
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:

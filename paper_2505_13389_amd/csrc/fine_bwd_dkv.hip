@@ -2,7 +2,7 @@
 // block map.
 #include <type_traits>
 
-#include "fine_tile.h"
+#include "unit_stream.h"
 #include "vsa_kernels.h"
 
 namespace vsa {
@@ -17,24 +17,6 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
   const float4 p0 = *(const float4*)p, p1 = *(const float4*)(p + 4);
   out[0] = p0.x * inv; out[1] = p0.y * inv; out[2] = p0.z * inv; out[3] = p0.w * inv;
   out[4] = p1.x * inv; out[5] = p1.y * inv; out[6] = p1.z * inv; out[7] = p1.w * inv;
-}
-
-// The matrix instructions of this kernel are written as assembly so that the register class of every
-// accumulator is fixed: dK and dV of a wavefront fill the 256 accumulation registers, S and dP have to
-// sit in ordinary registers (left to the compiler, all accumulators of a kernel with more than 256
-// registers are accumulation registers, and every vector use of S and dP costs a move).  The compiler
-// does not see matrix instructions here and inserts none of the wait states they need; the kernel's
-// fixed order provides them: a vector result is consumed by a matrix instruction no earlier than one
-// step (two matrix instructions) after it was written, and a matrix result is read by vector
-// instructions no earlier than two matrix instructions after the one that completed it.
-__device__ __forceinline__ void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_v_from(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
-}
-__device__ __forceinline__ void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
 
 // One workgroup of NW = 2 wavefronts per (b, h, key block), two per CU (512 registers per wavefront: one

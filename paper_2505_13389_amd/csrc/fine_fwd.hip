@@ -1,30 +1,44 @@
 // Fine stage forward (Sec. 2.2 fine stage; Sec. 2.1 attention equation under the block mask)
 // fused with the gated combine O = O_c * G_c + O_f * G_f.
 //
-// One workgroup (4 wavefronts) per (b, h, 64-row query block); "cube" below means such a block (a
-// cube of 64*m tokens is m consecutive blocks, and the lists the kernel gets name blocks).  The K
-// selected key blocks are walked through a double-buffered LDS stage (K tile + V tile).  LIST says how
-// list entries turn into streamed 64-key tiles: CubeList, one entry = one block; SubCubeList, four
-// entries that name key cubes of 16 tokens are gathered into one tile (Sec. 3.2, 64 x 16 tiles).  Work split inside the workgroup:
-// wavefront (qh, kh) owns query rows qh*32..+31 and key rows kh*32..+31 of every key tile and
-// keeps its OWN online-softmax state (running max, running sum, unnormalised O); the two
-// key halves of a query row are merged once, after the last tile.  Splitting keys instead of
-// queries halves the LDS traffic per MFMA (each K/V byte is read by two wavefronts, not four).
+// One workgroup per (b, h, 64-row query block); "cube" below means such a block (a cube of 64*m tokens is m
+// consecutive blocks, and the lists the kernel gets name blocks).  A workgroup is two wavefronts (four where the
+// launch is too small to fill the chip), each with a list walk, LDS stages and an online softmax of its own:
+// it multiplies UNITS of 32 keys with all 64 query rows (unit_stream.h), so that every operand it reads from
+// LDS feeds two matrix instructions, and since nobody else reads its rows the loop has no barrier.  The partial
+// results are merged once, through LDS, at the end.
 //
 // Everything is computed transposed so that softmax statistics are per-lane scalars:
-//   S^T[key, q]  = K_tile (A operand, row-major LDS reads) x Q^T (B operand, registers)
-//   O^T[dv,  q] += V_tile^T (A operand, transposing LDS reads) x P^T (B operand = the S^T
-//                  accumulator registers converted to bf16 in place)
+//   S^T[key, q]  = K rows (A operand, row-major LDS reads) x Q^T (B operand, registers)
+//   O^T[dv,  q] += V^T (A operand, transposing LDS reads) x P^T (B operand = the S^T accumulator
+//                  registers converted to bf16 in place)
 // In the 32x32 accumulator layout lane l holds query column l%32 and 16 key (or dv) rows.
+//
+// d = 128: one wavefront per SIMD (Q 64 registers, S of two units 64, O in 128 accumulation registers), so
+// nothing but the wavefront's own order overlaps vector work with matrix work: P(u) is formed while S(u+1) is
+// multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
+// one.  d = 64 takes two wavefronts per SIMD.
+//
+// What bounds it: instruction issue.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma, exp2, sum,
+// half a conversion per value; 24 LDS reads, 16 copies): 1650 cycles at 1.77 GHz where the matrix pipe needs 1024;
+// without waiting for any copy it is as fast, and without the copies 6 to 15 % faster.  About 7 us of a workgroup's
+// 80 are start-up, merge and stores, which nothing overlaps on its SIMD.
+// Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD (every operand fed one
+// matrix instruction; the vector work of one wavefront behind the matrix work of another): 39936 tokens, 12
+// heads, d = 128, top-78 of 624: 1.47 -> 1.28 ms (i.i.d. selections), 1.43 -> 1.22 ms (local ones); 16384 tokens,
+// top-32 of 256: 263 -> 241 us; B = 2, 16 heads, top-128 of 256: 2.38 -> 2.09 ms; d = 64, B = 2, 8 heads, top-32:
+// 193 -> 172 us.
 #include <type_traits>
 
-#include "fine_tile.h"
+#include "unit_stream.h"
 #include "vsa_kernels.h"
 
 namespace vsa {
 
 constexpr float kMaskBias = -30000.f;  // added to the raw logits of pad keys (|q.k| is assumed < 15000)
-constexpr float kTau = 8.f;             // lazy-rescale threshold, log2 units
+constexpr float kTau = 60.f;            // lazy-rescale threshold, log2 units
+constexpr float kMaxSum = 1152921504606846976.f;  // 2^kTau
+constexpr float kNoRef = -1e30f;        // reference before the first valid key: every value then exceeds kMaxSum
 
 // max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
 // round trip through the LDS permute path
@@ -33,283 +47,407 @@ __device__ __forceinline__ float max_across_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-template <int D, class LIST>
-__global__ __launch_bounds__(256, 2) void k_fine_fwd(int Nc, int K, float sl2, const uint4* __restrict__ q,
-                                                     const uint4* __restrict__ k, const uint4* __restrict__ v,
-                                                     const uint4* __restrict__ gc, const uint4* __restrict__ gf,
-                                                     const int32_t* __restrict__ idx, const float* __restrict__ oc,
-                                                     const uint64_t* __restrict__ mask, uint4* __restrict__ out,
-                                                     uint4* __restrict__ out_fine, float* __restrict__ lse_f,
-                                                     int H, long long out_head_stride, long long out_row_stride,
-                                                     int m_blocks) {
+template <int D, int NW, template <class> class UNITS>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
+    int Nc, int K, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
+    const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
+    const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
+    uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
+    int m_blocks) {
   using TL = Tile<D>;
-  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, LPT = TL::LPT;
-  constexpr int OS = D;  // fp32 row stride of the merge buffer
-  constexpr int STAGE = 2 * TL::BYTES;  // K tile + V tile
-  // Two separate LDS objects: the compiler can then tell that the asynchronous fill of one
-  // stage does not alias the reads of the other and keeps the copy in flight during the math.
-  __shared__ __attribute__((aligned(16))) unsigned char stage0[STAGE];
-  __shared__ __attribute__((aligned(16))) unsigned char stage1[STAGE];
-  __shared__ float ml[4 * 32 * 2];
-  static_assert(2 * 32 * OS * 4 <= STAGE, "merge buffer must fit in one stage");
+  using UL = UNITS<TL>;
+  using UC = UnitCopy<TL, UL>;
+  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
+  constexpr int EPR = NW / 2;           // tiles a round of units takes
+  constexpr int HALF = TL::BYTES / 2;   // 32 rows
+  constexpr int NC = UC::NC;            // copy instructions per 32 rows
+  constexpr int NPV = 2 * DVB;          // steps of the PV phase
+  // LDS operands are read in pairs (one wait for both), kAhead steps before the first of them is used
+  constexpr int kAhead = D == 128 ? 4 : 2;
+  constexpr int kEarly = 7;             // of the 16 softmax items of a unit, those behind the PV phase before it
+  constexpr int OS = D;
+  // per wavefront: K of two units, V of two units
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
+  __shared__ float ml[NW * 64 * 2];
+  static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
+  static_assert(KS == NPV && KS > kAhead, "phase interleave");
 
   // With K = Nc every workgroup of a head walks the same list: then all XCDs work on the same head
   // (plain blockIdx order), which keeps that list's tiles shared chip-wide, and the workgroups that
   // run side by side on an XCD (cubes c, c+8, ...) start their walk a few entries apart and wrap
   // around -- otherwise they ask for the same cache lines in the same cycles.
-  // (The walk is in tiles of 64 keys: one list entry, or four entries that name key cubes of 16 tokens.)
-  const int NT = (K + LIST::kEntriesPerTile - 1) / LIST::kEntriesPerTile;
-  const bool same_lists = K == Nc * LIST::kEntriesPerTile;
+  const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
+  const bool same_lists = K == Nc * UL::kEntriesPerTile;
   const unsigned wg = same_lists ? blockIdx.x : xcd_chunked_id(blockIdx.x, gridDim.x);
   const int c = wg % Nc;
   const long long bh = wg / Nc;
-  const int rot = same_lists ? ((c >> 3) & 15) % NT : 0;
-  auto ent = [&](int t) { const int e = t + rot; return e >= NT ? e - NT : e; };
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qh = wave & 1, kh = wave >> 1, l32 = lane & 31, h = lane >> 5;
+  const int rot = same_lists ? ((c >> 3) & 15) % tiles : 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int first = wave >> 1, half = wave & 1;  // this wavefront's tiles: first, first + EPR, ...
+  const int nu = tiles > first ? (tiles - first + EPR - 1) / EPR : 0;
+  auto tile_of = [&](int u) { const int t = first + EPR * u + rot; return t >= tiles ? t - tiles : t; };
   const long long rows0 = bh * (long long)Nc * kTile;  // first row of this (b,h)
-  const int32_t* my_idx = idx + (bh * Nc + c) * (long long)K;
+  const unsigned char* kb = (const unsigned char*)uniform_ptr(k + rows0 * CPR);
+  const unsigned char* vb = (const unsigned char*)uniform_ptr(v + rows0 * CPR);
 
-  // Software pipeline of the K/V stream: two LDS stages (K tile + V tile each), the copy of tile
-  // t+1 runs behind the math of tile t.  Per tile: wait for this wave's share of tile t, one
-  // barrier (tile t complete; every wave is done with tile t-1), start the copy of tile t+1 into
-  // the other stage, do the math with operands read from LDS just ahead of their use.
-  // The barrier is a raw s_barrier (no fence): a fence would drain the copy still in flight.
-  // vmcnt is waited by hand (the compiler cannot see the copies; see Tile::async_load).
-  unsigned goff[TL::IPW];
-  LIST::template offsets<TL>(wave, lane, goff);
-  auto issue = [&](unsigned char* st, int row) {  // `row`: first source row of this wave's share
-    TL::async_load(k, rows0 + row, st, wave, goff);
-    TL::async_load(v, rows0 + row, st + TL::BYTES, wave, goff);
+  // Start-up: the list first (one round trip), then the copies of the first units and of Q (which waits in
+  // the second V stages of the first two wavefronts), then the key masks, all in flight together.
+  // O: accumulation registers where the kernel has them (one wavefront per SIMD)
+  auto mfma_o = [](f32x16& acc, bf16x8 a, bf16x8 b) {
+    if (D == 128) mfma_a(acc, a, b);
+    else mfma_v(acc, a, b);
   };
-  // Start-up order: the list first (one round trip), then the copy of tile 0, and only then the
-  // loads of the key masks and of Q, so that everything the first iteration needs is in flight
-  // together.  The empty asm below consumes the loaded registers: the compiler has to place its
-  // wait for them right there (it also drains the copy), and its own vmcnt bookkeeping has nothing
-  // left to wait for inside the loop.
-  LIST cubes;
-  cubes.init(my_idx, mask, K, kh, wave, lane, Nc);
-  issue(stage0, cubes.first_row(ent(0)));
-  cubes.load_masks();
-  bf16x8 qreg[KS];
-  {
-    const uint4* qrow = q + (rows0 + c * kTile + qh * 32 + l32) * CPR;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) qreg[s] = __builtin_bit_cast(bf16x8, qrow[2 * s + h]);
+  auto pin_o = [](f32x16& acc) {
+    if (D == 128) asm volatile("" : "+a"(acc));
+    else asm volatile("" : "+v"(acc));
+  };
+  f32x16 o[DVB][2];
+  UC copy;
+  copy.init(lane);
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
+  UL list;
+  list.init(idx + (bh * Nc + c) * (long long)K, mask, K, half, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the units after the current one
+  Unit u0 = {0, 0, 0};
+  bool second = false;  // unit 1 is requested already
+  if (nu > 0) {
+    list.rows(tile_of(0), u0);
+    copy.all(kb, u0, lds0);
   }
-#pragma unroll
-  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qreg[s]));
-  asm volatile("" : "+v"(cubes.km_v));
-  uint32_t km_cur;  // valid-key mask (this wave's key half) of the tile of this iteration
-  {
-    int j0;
-    cubes.get_tile(ent(0), j0, km_cur);
+  if (NW == 2 || wave < 2) {  // half w of Q by wavefront w
+    UnitCopy<TL, CubeUnits<TL>> cq;
+    cq.init(lane);
+    const Unit uq = {(unsigned)half * HALF, (unsigned)half * HALF + HALF / 2, 0};
+    cq.all((const unsigned char*)uniform_ptr(q + (rows0 + (long long)c * kTile) * CPR), uq, lds0 + 3 * HALF);
   }
-  const int lane_a = TL::rowmajor_lane(kh * 32, lane);
-  int lane_b0, lane_b1;
-  TL::transposed_lane(kh * 32, lane, lane_b0, lane_b1);
-
-  float mref = -INFINITY, lsum = 0.f;
-  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-  bf16x8 ones_b = zero8;
-  ones_b[0] = (h == 0) ? (__bf16)1.f : (__bf16)0.f;
-  f32x16 o[DVB];
+  if (nu > 0) copy.all(vb, u0, lds0 + 2 * HALF);
+  if (nu > 1 && list.loaded(tile_of(1))) {
+    list.rows(tile_of(1), un[0]);
+    copy.all(kb, un[0], lds0 + HALF);
+    second = true;
+  }
+  list.load_masks();
+  asm volatile("" : "+v"(list.km_v));
 #pragma unroll
   for (int x = 0; x < DVB; ++x)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[x][i] = 0.f;
-
-  auto body = [&](auto copy_tag, const unsigned char* cur, unsigned char* nxt, int t) {
-    constexpr bool COPY = decltype(copy_tag)::value;  // false for the last tile of the list
-    const uint32_t kmask = km_cur;
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    // The copy of the next tile is not issued in one burst here -- eight wavefronts doing that at
-    // the same moment queue up behind one another in the load path and stall -- but one
-    // instruction per S^T step below.
-    int jn = 0;
-    if (COPY) cubes.get_tile(ent(t + 1), jn, km_cur);
-    const void* gk = uniform_ptr(k + (rows0 + jn) * CPR);
-    const void* gv = uniform_ptr(v + (rows0 + jn) * CPR);
-    const unsigned ln = __builtin_amdgcn_readfirstlane(lds_address(nxt) + (unsigned)(wave * TL::IPW) * 1024u);
-    auto copy_piece = [&](int i) {
-      if (!COPY) return;
-      if (i == 0) set_m0(ln);
-      if (i == TL::IPW) set_m0(ln + TL::BYTES);
-      if (i < 2 * TL::IPW) {
-        const void* g = i < TL::IPW ? gk : gv;
-        const int r = i % TL::IPW;
-        if (r == 0) lds_dma16_at<0>(g, goff[0]);
-        if (r == 1) lds_dma16_at<1024>(g, goff[1 % TL::IPW]);
-        if (r == 2) lds_dma16_at<2048>(g, goff[2 % TL::IPW]);
-        if (r == 3) lds_dma16_at<3072>(g, goff[3 % TL::IPW]);
-      }
-    };
-    constexpr int PIECES_PER_STEP = (2 * TL::IPW + KS - 1) / KS;
-    __builtin_amdgcn_sched_barrier(0);
-    const unsigned char* Ks = cur;
-    const unsigned char* Vs = cur + TL::BYTES;
-    // Operand i: K rows (S^T steps), then transposed V (O^T steps).  The K operands are requested a
-    // fixed number of matrix instructions ahead of their use, the V operands during the last S^T
-    // steps and the softmax arithmetic; addresses are rebuilt from three lane values (one XOR each).
-    int la = lane_a, lb0 = lane_b0, lb1 = lane_b1;
-    asm volatile("" : "+v"(la), "+v"(lb0), "+v"(lb1));
-    constexpr int NOP = KS + 2 * DVB, AHEAD = 4;
-    bf16x8 op[NOP];
-    auto read_op = [&](int i) {
-      if (i < KS) return TL::rowmajor_at(Ks, la, i);
-      const int j = i - KS;
-      return TL::transposed_at(Vs, lb0, lb1, j & 1, j >> 1);
-    };
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) op[i] = read_op(i);
-    __builtin_amdgcn_sched_barrier(0);
-
-    f32x16 sacc;
+      for (int i = 0; i < 16; ++i) o[x][b][i] = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+  for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
-    for (int i = 0; i < KS; ++i) {
-      sacc = mfma32(op[i], qreg[i], sacc);
-      op[i + AHEAD] = read_op(i + AHEAD);
-#pragma unroll
-      for (int c2 = 0; c2 < PIECES_PER_STEP; ++c2) copy_piece(i * PIECES_PER_STEP + c2);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = KS + AHEAD; i < NOP; ++i) op[i] = read_op(i);
-
-    // Pad keys of a partially filled cube never take part: one extra MFMA adds a large negative
-    // bias to their rows of S^T (A = bias of key l%32 in contraction slot 0, B = ones in slot 0).
-    const bool partial = kmask != 0xffffffffu;
-    if (partial) {
-      const bool dead = !((kmask >> l32) & 1);
-      bf16x8 ab = zero8;
-      ab[0] = (h == 0 && dead) ? (__bf16)kMaskBias : (__bf16)0.f;
-      sacc = mfma32(ab, ones_b, sacc);
-    }
-
-    // Online softmax with a lazily updated reference maximum: mref only moves when the running
-    // maximum exceeds it by more than kTau (log2 units), so exp2(s - mref) stays below 2^kTau and
-    // the O / l rescale is skipped for almost every tile.  The result is exact either way.
-    float mx = fmaxf(fmaxf(sacc[0], sacc[1]), sacc[2]);
-#pragma unroll
-    for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, sacc[i]), sacc[i + 1]);
-    mx = fmaxf(mx, sacc[15]);
-    mx = max_across_halves(mx);
-    if (partial && mx < 0.5f * kMaskBias) mx = -INFINITY;  // every key of this half is a pad
-    const float mx2 = mx * sl2;
-    if (__any(mx2 > mref + kTau)) {
-      // only the lanes over the threshold move their reference: a lane's arithmetic then never
-      // depends on what other query columns (pad rows included) hold
-      const float mnew = (mx2 > mref + kTau) ? mx2 : mref;
-      // mref = -inf: nothing accumulated yet, the factor is irrelevant but must not be NaN
-      const float alpha = (mnew == -INFINITY) ? 1.f : fast_exp2(mref - mnew);
-      lsum *= alpha;
-#pragma unroll
-      for (int x = 0; x < DVB; ++x)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[x][i] *= alpha;
-      mref = mnew;
-    }
-    const float muse = (mref == -INFINITY) ? 0.f : mref;
-    float p[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      p[i] = fast_exp2(fmaf(sacc[i], sl2, -muse));
-      lsum += p[i];
-    }
-    const bf16x8 pb0 = acc_to_operand(p), pb1 = acc_to_operand(p + 8);
-#pragma unroll
-    for (int x = 0; x < DVB; ++x) {
-      o[x] = mfma32(op[KS + 2 * x], pb0, o[x]);
-      o[x] = mfma32(op[KS + 2 * x + 1], pb1, o[x]);
-    }
-  };
-
+    for (int b = 0; b < 2; ++b) pin_o(o[x][b]);
+  if (nu > 0) list.get(tile_of(0), u0);
+  if (nu > 1) {
+    list.get(tile_of(1), un[0]);
+    if (!second) copy.all(kb, un[0], lds0 + HALF);
+  }
+  if (nu > 2) list.get(tile_of(2), un[1]);
+  wait_vmcnt<0>();
+  __syncthreads();
+  bf16x8 qreg[2][KS];
   {
-    const std::true_type copy;
-    const std::false_type last;
-    int t = 0;
-    for (; t + 2 < NT; t += 2) {
-      body(copy, stage0, stage1, t);
-      body(copy, stage1, stage0, t + 1);
-    }
-    if (t + 1 < NT) {
-      body(copy, stage0, stage1, t);
-      body(last, stage1, stage0, t + 1);
-    } else {
-      body(last, stage0, stage1, t);
+    const int lane_q = TL::rowmajor_lane(0, lane) + 3 * HALF;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      qreg[0][s] = TL::rowmajor_at(smem, lane_q, s);
+      qreg[1][s] = TL::rowmajor_at(smem + 4 * HALF, lane_q, s);
     }
   }
-  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qreg[0][s]), "+v"(qreg[1][s]));
+  __syncthreads();  // every wavefront has Q: the second V stages may be filled
+
+  const int my = wave * (4 * HALF);
+  const int lane_a = TL::rowmajor_lane(0, lane) + my;
+  int lane_b0, lane_b1;
+  TL::transposed_lane(0, lane, lane_b0, lane_b1);
+  lane_b0 += my;
+  lane_b1 += my;
+
+  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  bf16x8 ones_b = zero8;
+  ones_b[0] = (h == 0) ? (__bf16)1.f : (__bf16)0.f;
+  // Pad keys never take part: one extra matrix step adds a large negative bias to their rows of S^T (A = bias
+  // of key l%32 in contraction slot 0, B = ones in slot 0).
+  auto add_bias = [&](f32x16 (&S)[2], uint32_t valid) {
+    bf16x8 ab = zero8;
+    ab[0] = (h == 0 && !((valid >> l32) & 1)) ? (__bf16)kMaskBias : (__bf16)0.f;
+    S[0] = mfma32(ab, ones_b, S[0]);
+    S[1] = mfma32(ab, ones_b, S[1]);
+  };
+
+  float ref[2] = {kNoRef, kNoRef}, lsum[2] = {0.f, 0.f}, tsum[2] = {0.f, 0.f};
+  uint4 pb[2][2];  // P^T of the current unit as operands: [query half][contraction step]
+  auto put = [](uint4& u4, int w, uint32_t x) {
+    if (w == 0) u4.x = x;
+    if (w == 1) u4.y = x;
+    if (w == 2) u4.z = x;
+    if (w == 3) u4.w = x;
+  };
+  // softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0
+  auto p_item = [&](const f32x16 (&S)[2], int it, const float* rf) {
+    const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
+    const float x0 = fast_exp2(fmaf(S[b][e], sl2, -rf[b])), x1 = fast_exp2(fmaf(S[b][e + 1], sl2, -rf[b]));
+    tsum[b] = (it & 11) == 0 ? x0 + x1 : tsum[b] + x0 + x1;
+    const uint32_t pp = pack_bf16(x0, x1);
+    put(pb[b][st], w, pp);
+    asm volatile("" : "+v"(tsum[b]) : "v"(pp));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+  };
+  auto p_items = [&](const f32x16 (&S)[2], int from, int to, const float* rf) {
+#pragma unroll
+    for (int it = from; it < to; ++it) p_item(S, it, rf);
+  };
+  // the reference of a query column moves to the maximum of this unit where that exceeds it by more than
+  // kTau: a lane's arithmetic then never depends on what other query columns (pad rows included) hold
+  auto new_ref = [&](const f32x16& S, float old) {
+    float mx = fmaxf(fmaxf(S[0], S[1]), S[2]);
+#pragma unroll
+    for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, S[i]), S[i + 1]);
+    mx = max_across_halves(fmaxf(mx, S[15]));
+    const float mx2 = mx * sl2;
+    return (mx > 0.5f * kMaskBias && mx2 > old + kTau) ? mx2 : old;  // (below: every key of this unit is a pad)
+  };
+  auto usable = [](float r) { return r == kNoRef ? 0.f : r; };
+
+  f32x16 zero16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero16[i] = 0.f;
+  f32x16 s0[2], s1[2];
+  bf16x8 kcur[kAhead];  // K operands of a unit's first steps, read during the phase before
+  if (nu > 0) {  // S of the first unit, its reference, and the softmax items that precede its PV phase's own
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bf16x8 a = TL::rowmajor_at(smem, lane_a, s);
+      s0[0] = mfma32(a, qreg[0][s], s == 0 ? zero16 : s0[0]);
+      s0[1] = mfma32(a, qreg[1][s], s == 0 ? zero16 : s0[1]);
+    }
+    if (u0.valid != 0xffffffffu) add_bias(s0, u0.valid);
+    __builtin_amdgcn_sched_barrier(0);  // (the matrix instructions above have waited for the reads of this stage)
+    if (nu > 2) copy.all(kb, un[1], lds0);
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) kcur[s] = TL::rowmajor_at(smem + HALF, lane_a, s);
+    ref[0] = new_ref(s0[0], kNoRef);
+    ref[1] = new_ref(s0[1], kNoRef);
+    p_items(s0, 0, kEarly, ref);
+  }
+
+  // One unit u (its S is there, in S): P(u) while S(u+1) is multiplied into T, then PV(u) while P(u+1) begins.
+  // KIND 2: the units up to u + 3 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
+  auto body = [&](auto kind_tag, int par, f32x16 (&S)[2], f32x16 (&T)[2], int u) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool more1 = KIND >= 1;
+    const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu), more3 = KIND == 2 || (KIND == 1 && u + 3 < nu);
+    const unsigned char* kn = smem + (1 - par) * HALF;  // K(u+1)
+    const unsigned char* vc = smem + (2 + par) * HALF;  // V(u)
+    bf16x8 ka[KS + kAhead], va[NPV + kAhead];
+    auto v_op = [&](int i) { return TL::transposed_at(vc, lane_b0, lane_b1, i / DVB, i % DVB); };
+    if (more1) {
+#pragma unroll
+      for (int s = 0; s < kAhead; ++s) ka[s] = kcur[s];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- S(u+1) | the rest of P(u), the copy of V(u+1), the first V operands
+    constexpr int LATE = 16 - kEarly;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int i0 = kEarly + s * LATE / KS, i2 = kEarly + (s + 1) * LATE / KS, i1 = (i0 + i2) / 2;
+      if (more1 && s % 2 == 0) {  // this pair is there; newer: the next one
+        if (kAhead == 2) wait_lgkmcnt<0>();
+        else if (s + 2 < KS) wait_lgkmcnt<2>();
+        else wait_lgkmcnt<4>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (more1) {
+        T[0] = mfma32(ka[s], qreg[0][s], s == 0 ? zero16 : T[0]);
+        if (s < KS - kAhead) {
+#pragma unroll
+          for (int e = s * NC / (KS - kAhead); e < (s + 1) * NC / (KS - kAhead); ++e)
+            copy.piece(vb, un[0], lds0 + (3 - par) * HALF, e);
+        }
+      }
+      p_items(S, i0, i1, ref);
+      if (s == KS - kAhead) {  // V(u) has landed; newer: K(u+2) and V(u+1)
+        if (more2) wait_vmcnt<2 * NC>();
+        else if (more1) wait_vmcnt<NC>();
+        else wait_vmcnt<0>();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (more1) {
+        T[1] = mfma32(ka[s], qreg[1][s], s == 0 ? zero16 : T[1]);
+      }
+      if (s % 2 == 0) {
+#pragma unroll
+        for (int j = s + kAhead; j < s + kAhead + 2; ++j) {
+          if (j >= KS) va[j - KS] = v_op(j - KS);
+          else if (more1) ka[j] = TL::rowmajor_at(kn, lane_a, j);
+        }
+      }
+      p_items(S, i1, i2, ref);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (more1) {
+      if (un[0].valid != 0xffffffffu) add_bias(T, un[0].valid);
+    }
+    // The reference stays as long as no sum of this unit's 16 values exceeds 2^kTau: then no value does, and
+    // the rescaling of O is skipped for almost every unit.  The result is exact either way.
+    if (__builtin_expect(__any(fmaxf(tsum[0], tsum[1]) > kMaxSum), 0)) {
+      mfma_fence();
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const float mnew = new_ref(S[b], ref[b]);
+        const float alpha = fast_exp2(ref[b] - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
+        lsum[b] *= alpha;
+#pragma unroll
+        for (int x = 0; x < DVB; ++x) {
+          pin_o(o[x][b]);  // (moved to ordinary registers from here on and not before the branch)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[x][b][i] *= alpha;
+          pin_o(o[x][b]);
+          __builtin_amdgcn_sched_barrier(0);  // (one block of O in ordinary registers at a time)
+        }
+        ref[b] = mnew;
+      }
+      const float rf[2] = {usable(ref[0]), usable(ref[1])};
+      p_items(S, 0, 16, rf);
+      mfma_fence();
+    }
+    lsum[0] += tsum[0];
+    lsum[1] += tsum[1];
+    // ---- PV(u) | the first of P(u+1), the copy of K(u+3), the first K operands of u+2
+    const uint4 pc[2][2] = {{pb[0][0], pb[0][1]}, {pb[1][0], pb[1][1]}};
+    if (more3) list.get(tile_of(u + 3), un[2]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");  // (two wait states between the moves to pc and the first matrix instruction)
+#pragma unroll
+    for (int i = 0; i < NPV; ++i) {
+      const int i0 = i == 0 ? 0 : (i - 1) * kEarly / (NPV - 1), i2 = i * kEarly / (NPV - 1), i1 = (i0 + i2) / 2;
+      if (i % 2 == 0) {
+        if (kAhead == 2) wait_lgkmcnt<0>();
+        else if (i + 2 < NPV) wait_lgkmcnt<4>();
+        else wait_lgkmcnt<2>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mfma_o(o[i % DVB][0], va[i], __builtin_bit_cast(bf16x8, pc[0][i / DVB]));
+      if (more3 && i < NPV - kAhead) {
+#pragma unroll
+        for (int e = i * NC / (NPV - kAhead); e < (i + 1) * NC / (NPV - kAhead); ++e)
+          copy.piece(kb, un[2], lds0 + (1 - par) * HALF, e);
+      }
+      if (more1) p_items(T, i0, i1, ref);
+      if (more1 && i == NPV - kAhead) {  // K(u+2) has landed; newer: V(u+1) and K(u+3)
+        if (more3) wait_vmcnt<2 * NC>();
+        else if (more2) wait_vmcnt<NC>();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_o(o[i % DVB][1], va[i], __builtin_bit_cast(bf16x8, pc[1][i / DVB]));
+      if (i % 2 == 0) {
+#pragma unroll
+        for (int j = i + kAhead; j < i + kAhead + 2; ++j) {
+          if (j < NPV) va[j] = v_op(j);
+          else if (more1) kcur[j - NPV] = TL::rowmajor_at(smem + par * HALF, lane_a, j - NPV);  // (unused if u + 2 does not exist)
+        }
+      }
+      if (more1) p_items(T, i1, i2, ref);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    un[0] = un[1];
+    un[1] = un[2];
+  };
+  if (nu > 0) {
+    const std::integral_constant<int, 2> steady;
+    const std::integral_constant<int, 1> inner;
+    const std::integral_constant<int, 0> last;
+    int u = 0;
+    for (; u + 4 < nu; u += 2) {
+      body(steady, 0, s0, s1, u);
+      body(steady, 1, s1, s0, u + 1);
+    }
+    for (; u + 1 < nu; ++u) {
+      body(inner, u & 1, s0, s1, u);
+      s0[0] = s1[0];
+      s0[1] = s1[1];
+    }
+    body(last, u & 1, s0, s1, u);
+  }
+  mfma_fence();  // the last matrix results land before they are read
+#pragma unroll
+  for (int x = 0; x < DVB; ++x)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) pin_o(o[x][b]);
+  __builtin_amdgcn_sched_barrier(0);
 
   // `out` may be head-major [B,H,Np,D] or token-major [B,Np,H,D] (same batch stride): chunk ch of
   // tiled row n of head h of batch b sits at b*H*Np*CPR + h*out_head_stride + n*out_row_stride + ch
   const long long out0 = (bh / H) * ((long long)H * Nc * kTile * CPR) + (bh % H) * out_head_stride;
-  // ---- merge the two key halves, normalise, gate, store
+  // ---- merge the wavefronts' partial results, normalise, gate, store
   // The gates and the coarse output of this thread's items are requested first: they arrive while
   // the partial results go through LDS.  Pad rows are loaded too (they exist in memory) and ignored.
+  static_assert(NT % CPR == 0, "a thread keeps its column chunk");
   const uint64_t qmask = mask[c];
+  const int ch = tid % CPR;
   uint4 gc_raw[LPT], gf_raw[LPT];
-  float4 oc_raw[LPT][2];
+  const float* ocr = oc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // O_c is per cube = m_blocks blocks
+  const float4 c0 = *(const float4*)ocr, c1 = *(const float4*)(ocr + 4);
 #pragma unroll
   for (int it = 0; it < LPT; ++it) {
-    const int item = it * 256 + tid, r = item / CPR, ch = item % CPR;
-    const long long g = (rows0 + c * kTile + r) * CPR + ch;
-    const float* ocr = oc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // O_c is per cube = m_blocks blocks
+    const long long g = (rows0 + c * kTile + (it * NT + tid) / CPR) * CPR + ch;
     gc_raw[it] = gc[g];
     gf_raw[it] = gf ? gf[g] : make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);  // bf16 ones
-    oc_raw[it][0] = *(const float4*)ocr;
-    oc_raw[it][1] = *(const float4*)(ocr + 4);
   }
-  // Partial O of wave (qh, kh) goes to rows qh*32.. of stage `kh` (fp32 [64][D] each).
-  lsum += __shfl_xor(lsum, 32);
+  __syncthreads();  // every wavefront is done with its stages
   {
-    float* Op = (float*)(kh == 0 ? stage0 : stage1) + qh * 32 * OS;
+    float* Op = (float*)smem + wave * 64 * OS;
 #pragma unroll
-    for (int x = 0; x < DVB; ++x)
+    for (int b = 0; b < 2; ++b) {
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        float4 val = make_float4(o[x][4 * g4], o[x][4 * g4 + 1], o[x][4 * g4 + 2], o[x][4 * g4 + 3]);
-        *(float4*)&Op[merge_offset(l32, x * 32 + 8 * g4 + 4 * h, OS)] = val;
+      for (int x = 0; x < DVB; ++x)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+          *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
+              make_float4(o[x][b][4 * g4], o[x][b][4 * g4 + 1], o[x][b][4 * g4 + 2], o[x][b][4 * g4 + 3]);
+      const float l = lsum[b] + __shfl_xor(lsum[b], 32);
+      if (h == 0) {
+        ml[(wave * 64 + b * 32 + l32) * 2] = ref[b] == kNoRef ? -INFINITY : ref[b];
+        ml[(wave * 64 + b * 32 + l32) * 2 + 1] = l;
       }
-  }
-  if (h == 0) {
-    ml[(wave * 32 + l32) * 2] = mref;
-    ml[(wave * 32 + l32) * 2 + 1] = lsum;
+    }
   }
   __syncthreads();
 
 #pragma unroll
   for (int it = 0; it < LPT; ++it) {
-    const int item = it * 256 + tid, r = item / CPR, ch = item % CPR;
-    const int wa = r >> 5, wb = wa + 2, ql = r & 31;
-    const float ma = ml[(wa * 32 + ql) * 2], la = ml[(wa * 32 + ql) * 2 + 1];
-    const float mb = ml[(wb * 32 + ql) * 2], lb = ml[(wb * 32 + ql) * 2 + 1];
-    const float M = fmaxf(ma, mb);
+    const int r = (it * NT + tid) / CPR;
+    float M = ml[r * 2], L = 0.f, f[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[(w * 64 + r) * 2]);
     // (M = -inf: the list named no valid key at all -- only a caller-supplied list can, e.g. one made of
     // dead key cubes; the row then gets O_f = 0 and lse = 0 instead of NaN)
     const bool none = M == -INFINITY;
-    float fa = none ? 0.f : fast_exp2(ma - M), fb = none ? 0.f : fast_exp2(mb - M);
-    const float inv = none ? 0.f : 1.0f / (la * fa + lb * fb);
-    fa *= inv; fb *= inv;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      f[w] = none ? 0.f : fast_exp2(ml[(w * 64 + r) * 2] - M);
+      L += ml[(w * 64 + r) * 2 + 1] * f[w];
+    }
+    const float inv = none ? 0.f : 1.0f / L;
     const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-    const float* Oa = (const float*)stage0;
-    const float* Ob = (const float*)stage1;
-    float of[8], res[8];
-    const float4 a0 = *(const float4*)(Oa + m0), a1 = *(const float4*)(Oa + m1);
-    const float4 b0 = *(const float4*)(Ob + m0), b1 = *(const float4*)(Ob + m1);
-    of[0] = a0.x * fa + b0.x * fb; of[1] = a0.y * fa + b0.y * fb; of[2] = a0.z * fa + b0.z * fb; of[3] = a0.w * fa + b0.w * fb;
-    of[4] = a1.x * fa + b1.x * fb; of[5] = a1.y * fa + b1.y * fb; of[6] = a1.z * fa + b1.z * fb; of[7] = a1.w * fa + b1.w * fb;
+    float of[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, res[8];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float* Op = (const float*)smem + w * 64 * OS;
+      const float4 a0 = *(const float4*)(Op + m0), a1 = *(const float4*)(Op + m1);
+      const float fw = f[w] * inv;
+      of[0] = fmaf(a0.x, fw, of[0]); of[1] = fmaf(a0.y, fw, of[1]); of[2] = fmaf(a0.z, fw, of[2]); of[3] = fmaf(a0.w, fw, of[3]);
+      of[4] = fmaf(a1.x, fw, of[4]); of[5] = fmaf(a1.y, fw, of[5]); of[6] = fmaf(a1.z, fw, of[6]); of[7] = fmaf(a1.w, fw, of[7]);
+    }
     const long long g = (rows0 + c * kTile + r) * CPR + ch;
-    const bool valid = (qmask >> r) & 1;
     uint4 ov = make_uint4(0, 0, 0, 0), fv = make_uint4(0, 0, 0, 0);
-    if (valid) {
+    if ((qmask >> r) & 1) {
       float gcv[8], gfv[8];
       unpack8(gc_raw[it], gcv);
       unpack8(gf_raw[it], gfv);
-      const float4 c0 = oc_raw[it][0], c1 = oc_raw[it][1];
       const float ocv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) res[e] = fmaf(ocv[e], gcv[e], of[e] * gfv[e]);
@@ -318,16 +456,14 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd(int Nc, int K, float sl2, c
     }
     out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
     if (out_fine) out_fine[g] = fv;
-  }
-  if (lse_f && tid < kTile) {
-    const int r = tid, wa = r >> 5, wb = wa + 2, ql = r & 31;
-    const float ma = ml[(wa * 32 + ql) * 2], la = ml[(wa * 32 + ql) * 2 + 1];
-    const float mb = ml[(wb * 32 + ql) * 2], lb = ml[(wb * 32 + ql) * 2 + 1];
-    const float M = fmaxf(ma, mb);
-    const float Lt = la * fast_exp2(ma - M) + lb * fast_exp2(mb - M);
-    lse_f[rows0 + c * kTile + r] = (((qmask >> r) & 1) && M != -INFINITY) ? (M + fast_log2(Lt)) * kLn2 : 0.f;
+    if (lse_f && ch == 0) lse_f[rows0 + c * kTile + r] = (((qmask >> r) & 1) && !none) ? (M + fast_log2(L)) * kLn2 : 0.f;
   }
 }
+
+// Up to this many query blocks, four wavefronts per workgroup: the launch does not fill the chip with
+// two-wavefront workgroups, and half as long a list walk counts.  (64 blocks, d = 64, top-8: 10.0
+// against 12.0 us; 256 to 512 blocks: level.)
+constexpr int kFwdFourWaves = 256;
 
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
@@ -337,17 +473,23 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const unsigned grid = (unsigned)(BH * Nc);
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
-#define VSA_FWD(D_, LIST_)                                                                                           \
-  k_fine_fwd<D_, LIST_><<<grid, 256, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,           \
+#define VSA_FWD(D_, NW_, LIST_)                                                                                      \
+  k_fine_fwd<D_, NW_, LIST_><<<grid, 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
                                              (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks)
+#define VSA_FWD_NW(D_, LIST_)                     \
+  do {                                            \
+    if (grid <= kFwdFourWaves) VSA_FWD(D_, 4, LIST_); \
+    else VSA_FWD(D_, 2, LIST_);                   \
+  } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
-    if (d == 128) VSA_FWD(128, SubCubeList);
-    else VSA_FWD(64, SubCubeList);
+    if (d == 128) VSA_FWD_NW(128, SubCubeUnits);
+    else VSA_FWD_NW(64, SubCubeUnits);
   } else {
-    if (d == 128) VSA_FWD(128, CubeList);
-    else VSA_FWD(64, CubeList);
+    if (d == 128) VSA_FWD_NW(128, CubeUnits);
+    else VSA_FWD_NW(64, CubeUnits);
   }
+#undef VSA_FWD_NW
 #undef VSA_FWD
   return hipGetLastError();
 }

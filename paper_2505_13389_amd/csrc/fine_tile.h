@@ -63,6 +63,10 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 // The list of key cubes a workgroup streams, with the valid-key mask of one 32-key half of each

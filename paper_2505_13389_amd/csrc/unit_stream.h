@@ -1,0 +1,161 @@
+// The stream of the forward and the dQ kernel: UNITS of 32 key rows, each copied by the one wavefront that
+// multiplies it, global -> LDS, into stages of that wavefront's own.  A workgroup's list is walked in
+// tiles of 64 keys; wavefront w takes half w & 1 of the tiles w >> 1, (w >> 1) + NW/2, ...
+//
+// A unit is two groups of 16 consecutive LDS rows whose sources may lie apart (lists that name key cubes of
+// 16 tokens gather a tile from four entries).  The list sits in a register, 64 entries at a time (lane e
+// holds entry e of the current chunk) with the valid-key bits of the entries, and is read with v_readlane:
+// no load and no wait on one sits in the loops except where a chunk ends.
+#pragma once
+#include "fine_tile.h"
+
+namespace vsa {
+
+// Byte offsets of a unit's two 16-row groups from the first row of the (b, h), and its 32 valid-key bits.
+struct Unit {
+  unsigned a, b;
+  uint32_t valid;
+};
+
+// Lists that name 64-row blocks: one tile per entry.
+template <class TL>
+struct CubeUnits {
+  const int32_t* list;
+  const uint64_t* mask;
+  int n, half, lane, chunk, idx_v, ncubes;
+  uint32_t km_v;
+  static constexpr int kEntriesPerTile = 1, kTilesPerChunk = 64;
+  static constexpr bool kContiguous = true;  // a unit's 32 rows lie one behind the other
+  __device__ __forceinline__ void load_indices(int c) {
+    chunk = c;
+    idx_v = list[list_slot(c, lane, n)];
+    asm volatile("" : "+v"(idx_v));  // consumed at once: the compiler's wait for the load is placed right here
+    idx_v = clamp_cube(idx_v, ncubes);  // (a caller-supplied list is not trusted)
+  }
+  __device__ __forceinline__ void load_masks() {
+    const uint64_t m = mask[idx_v];
+    km_v = half ? (uint32_t)(m >> 32) : (uint32_t)m;
+  }
+  // (after init the offsets of the units of tile t's chunk are there; the valid-key bits come with load_masks)
+  __device__ __forceinline__ void init(const int32_t* list_, const uint64_t* mask_, int n_, int half_, int lane_,
+                                       int ncubes_, int t) {
+    list = list_, mask = mask_, n = n_, half = half_, lane = lane_, ncubes = ncubes_;
+    load_indices(t / kTilesPerChunk);
+  }
+  __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
+  __device__ __forceinline__ void rows(int t, Unit& u) const {
+    u.a = (unsigned)__builtin_amdgcn_readlane(idx_v, t & 63) * (unsigned)TL::BYTES + (unsigned)half * (TL::BYTES / 2);
+    u.b = u.a + TL::BYTES / 4;
+  }
+  __device__ __forceinline__ void get(int t, Unit& u) {
+    if (!loaded(t)) {
+      load_indices(t / kTilesPerChunk);
+      load_masks();
+      asm volatile("" : "+v"(km_v));
+    }
+    rows(t, u);
+    u.valid = (uint32_t)__builtin_amdgcn_readlane((int)km_v, t & 63);
+  }
+  __device__ static __forceinline__ int source_row(int x) { return x; }
+};
+
+// Lists that name key cubes of 16 tokens (see subcube_* in list_rules.h): a tile is four entries, and row x of
+// a 16-row group is token x of its key cube.  Entries past the end repeat the last one with no valid key.
+template <class TL>
+struct SubCubeUnits {
+  const int32_t* list;
+  const uint64_t* mask;
+  int n, half, lane, chunk, idx_v, ncubes;
+  uint32_t km_v;  // 16 valid-key bits of the lane's entry
+  static constexpr int kEntriesPerTile = 4, kTilesPerChunk = 16;
+  static constexpr bool kContiguous = false;
+  __device__ __forceinline__ void load_indices(int c) {
+    chunk = c;
+    idx_v = list[list_slot(c, lane, n)];
+    asm volatile("" : "+v"(idx_v));
+    idx_v = clamp_cube(idx_v, 4 * ncubes);
+  }
+  __device__ __forceinline__ void load_masks() { km_v = subcube_mask16(mask[idx_v >> 2], idx_v & 3); }
+  __device__ __forceinline__ void init(const int32_t* list_, const uint64_t* mask_, int n_, int half_, int lane_,
+                                       int ncubes_, int t) {
+    list = list_, mask = mask_, n = n_, half = half_, lane = lane_, ncubes = ncubes_;
+    load_indices(t / kTilesPerChunk);
+  }
+  __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
+  __device__ __forceinline__ unsigned entry_offset(int e) const {  // e in the current chunk
+    const int id = __builtin_amdgcn_readlane(idx_v, min(e, n - 1) & 63);
+    return (unsigned)(id >> 2) * (unsigned)TL::BYTES + (unsigned)subcube_first_slot(id & 3) * (unsigned)TL::ROW_BYTES;
+  }
+  __device__ __forceinline__ void rows(int t, Unit& u) const {
+    u.a = entry_offset(4 * t + 2 * half);
+    u.b = entry_offset(4 * t + 2 * half + 1);
+  }
+  __device__ __forceinline__ void get(int t, Unit& u) {
+    if (!loaded(t)) {
+      load_indices(t / kTilesPerChunk);
+      load_masks();
+      asm volatile("" : "+v"(km_v));
+    }
+    rows(t, u);
+    const int ea = 4 * t + 2 * half, eb = ea + 1;
+    const uint32_t ma = (uint32_t)__builtin_amdgcn_readlane((int)km_v, ea & 63);
+    const uint32_t mb = (uint32_t)__builtin_amdgcn_readlane((int)km_v, eb & 63);
+    u.valid = (ea < n ? ma : 0u) | ((eb < n ? mb : 0u) << 16);
+  }
+  __device__ static __forceinline__ int source_row(int x) { return subcube_slot(x); }
+};
+
+// Copies of 32 rows by one wavefront (see Tile::async_load for the instruction and the swizzle): instruction c
+// fills rows c*RPI ..; the swizzle repeats after 16 rows.  Every 16-row group has an M0 value of its own; where
+// the 32 rows are contiguous one base address serves both, the distance is in the second group's lane offsets.
+template <class TL, class UNITS>
+struct UnitCopy {
+  static constexpr int NC = 32 / TL::RPI;  // instructions
+  static constexpr int GROUP = NC / 2;     // per 16-row group
+  unsigned off[UNITS::kContiguous ? NC : GROUP];
+  __device__ __forceinline__ void init(int lane) {
+#pragma unroll
+    for (int i = 0; i < (UNITS::kContiguous ? NC : GROUP); ++i) {
+      const int x = i * TL::RPI + lane / TL::CPR, pc = lane % TL::CPR;
+      off[i] = (unsigned)((UNITS::source_row(x) * TL::CPR + (pc ^ TL::swz(x))) * 16) - (unsigned)(i % GROUP) * 1024u;
+    }
+  }
+  // instruction c (a constant after unrolling); `base` = first row of the (b, h), `lds` = the stage's address
+  __device__ __forceinline__ void piece(const unsigned char* base, const Unit& u, unsigned lds, int c) const {
+    const void* g = base + (UNITS::kContiguous || c < GROUP ? u.a : u.b);
+    const int r = c % GROUP, o = UNITS::kContiguous ? c : r;
+    if (r == 0) set_m0(lds + (unsigned)(c / GROUP) * (16u * TL::ROW_BYTES));
+    if (r == 0) lds_dma16_at<0>(g, off[o]);
+    if (r == 1) lds_dma16_at<1024>(g, off[o]);
+    if (r == 2) lds_dma16_at<2048>(g, off[o]);
+    if (r == 3) lds_dma16_at<3072>(g, off[o]);
+  }
+  __device__ __forceinline__ void all(const unsigned char* base, const Unit& u, unsigned lds) const {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) piece(base, u, lds, c);
+  }
+};
+
+// Matrix instructions written as assembly, so that the register class of every accumulator is fixed: `_v`
+// accumulates in ordinary registers, `_a` in the accumulation registers (left to the compiler, all
+// accumulators of a kernel with more than 256 registers are accumulation registers, and every vector use of
+// one costs a move).  The compiler does not see matrix instructions here and inserts none of the wait states
+// they need; the kernels' fixed order provides them: a vector result is consumed by a matrix instruction
+// no earlier than two instructions after it was written, and a matrix result is read by vector instructions
+// no earlier than two matrix instructions after the one that completed it.
+__device__ __forceinline__ void mfma_v0(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v_from(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
+}
+__device__ __forceinline__ void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+// matrix results land before the vector instructions behind this read them, and the other way round
+__device__ __forceinline__ void mfma_fence() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+}  // namespace vsa

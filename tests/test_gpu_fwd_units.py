@@ -1,0 +1,83 @@
+"""Forward: list walks of every length around the unrolled loop, on both sides of the workgroup-size rule, and the
+reference of the online softmax: first units without a valid key, and logits that outgrow the reference again and
+again along the walk."""
+import numpy as np
+import pytest
+
+from helpers import assert_close, bf16_to_np, grid_of, problem_of, tiled_bits, to_dev, widen
+from oracle import vsa_oracle as orc
+from paper_2505_13389_amd import synth
+from paper_2505_13389_amd.synth import Workload
+
+pytestmark = pytest.mark.gpu
+
+
+def run_and_check(wl, bits, idx):
+    import torch
+    from paper_2505_13389_amd import vsa
+    x, dev, g = widen(bits), to_dev(bits), grid_of(wl)
+    ref = orc.forward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], wl.topk, real="f32", block_idx=idx)
+    buf = vsa.Buffers(problem_of(wl))
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"], indices_given=True)
+    torch.cuda.synchronize()
+    assert_close(bf16_to_np(buf.out), ref["out"], "out")
+    assert_close(bf16_to_np(buf.out_fine), ref["out_fine"], "out_fine")
+    # fp32 sums of up to a few thousand terms, logits of magnitude up to 500 (log2 units): 1e-3 is 8 spacings there
+    assert np.abs(buf.lse_fine.cpu().numpy() - ref["lse_fine"]).max() < 1e-3
+
+
+def random_lists(wl, g, seed):
+    rng = np.random.default_rng(seed)
+    return np.sort(rng.permuted(np.tile(np.arange(g.Nc, dtype=np.int32), (1, wl.H, g.Nc, 1)), axis=-1)[..., :wl.topk])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 3])  # 96 query blocks each: four wavefronts per workgroup, two
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 65])
+def test_walks_of_every_length(K, H, d):
+    wl = Workload("fwd_units", 1, H, 7, 22, 30, d, K)
+    g = grid_of(wl)
+    run_and_check(wl, tiled_bits(wl, seed=K + d + H, pad_garbage=True), random_lists(wl, g, K))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 3])
+def test_walks_that_begin_without_a_valid_key(H, d):
+    """6 frames: in the last layer of cubes slots 32..63 are pads, so the wavefronts of the second key half meet only
+    pads in lists of that layer (even rows) and a valid key late in the others."""
+    wl = Workload("fwd_dead", 1, H, 6, 22, 30, d, 9)
+    g = grid_of(wl)
+    idx = random_lists(wl, g, 5)
+    layer = np.arange(g.Nc // 2, g.Nc)
+    rng = np.random.default_rng(1)
+    for h in range(H):
+        for c in range(g.Nc):
+            pick = rng.permutation(layer)[:wl.topk].astype(np.int32)
+            if c % 2:
+                pick[-1] = c % (g.Nc // 2)  # (the order of a list is free)
+            idx[0, h, c] = pick
+    run_and_check(wl, tiled_bits(wl, seed=3, pad_garbage=True), idx)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 3])
+@pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
+def test_reference_follows_the_logits(order, H, d):
+    """Logits between -290 and 290 (log2 units), constant per key cube up to noise: rising lists grow by
+    about 15 per entry, mixed ones jump by up to 580, more than fp32 holds."""
+    wl = Workload("fwd_ramp", 1, H, 7, 22, 30, d, 40)
+    g = grid_of(wl)
+    bits = tiled_bits(wl, seed=d)
+    rng = np.random.default_rng(d + H)
+    ramp = np.linspace(-200.0, 200.0, g.Nc)
+    if order == "falling":
+        ramp = ramp[::-1]
+    if order == "mixed":
+        ramp = rng.permutation(ramp)
+    u = rng.choice([-1.0, 1.0], size=d)
+    # q.k = d * 8 / sqrt(d) * ramp / 8, times log2(e) / sqrt(d): 1.44 * ramp
+    k = np.repeat(ramp, g.Np // g.Nc)[None, None, :, None] * u / np.sqrt(d) + 0.3 * rng.standard_normal((1, H, g.Np, d))
+    q = u + 0.1 * rng.standard_normal((1, H, g.Np, d))
+    bits["q"], bits["k"] = synth.f32_to_bf16_bits(q.astype(np.float32)), synth.f32_to_bf16_bits(k.astype(np.float32))
+    run_and_check(wl, bits, random_lists(wl, g, 11))

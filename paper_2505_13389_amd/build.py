@@ -14,7 +14,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Xclang", "-tar
 # Kernels with more than 256 registers that mix matrix instructions of both kinds: those the compiler emits
 # accumulate in ordinary registers (their results feed vector arithmetic at once), the accumulation registers are
 # filled by instructions written as assembly.
-FILE_FLAGS = {"fine_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("fine_fwd.hip", "fine_bwd.hip")}
 
 
 def _compile(src: str, extra) -> str:

@@ -1,245 +1,361 @@
 // Fine stage backward (Sec. 2.4 states a backward kernel exists; this is FlashAttention-style
 // recomputation of P from the saved log-sum-exp, on the block-sparse pattern):
 //   P_ij = exp(S_ij - lse_i),  dP_ij = dOf_i . v_j,  dS_ij = P_ij (dP_ij - Delta_i)
-//   dQ_i = scale sum_j dS_ij k_j      (query-tile-major pass over the index list)
-//   dK_j = scale sum_i dS_ij q_i,  dV_j = sum_i P_ij dOf_i   (key-tile-major pass over the
-//                                                             transposed block map)
+//   dQ_i = scale sum_j dS_ij k_j      (query-block-major pass over the index list: this file)
+//   dK_j = scale sum_i dS_ij q_i,  dV_j = sum_i P_ij dOf_i   (key-block-major pass over the transposed
+//                                                             block map: fine_bwd_dkv.hip)
 // Both passes add the pooled-path gradient dXc[cube]/cnt to every valid row in their epilogue
-// and write zeros to pad rows.  Work split and operand layouts follow the forward kernel: the
-// streamed tiles are copied global -> LDS asynchronously (two stages in the dQ pass, four in the
-// dK/dV pass), the resident tile sits in registers, and each wavefront pair owning the same output
-// rows is merged once at the end.  The per-row terms (lse, Delta) and the pad-key mask enter the
-// products through extra MFMA steps rather than per-element vector arithmetic.
+// and write zeros to pad rows.
 #include <type_traits>
 
-#include "fine_tile.h"
+#include "unit_stream.h"
 #include "vsa_kernels.h"
 
 namespace vsa {
 
-// ---------------------------------------------------------------------------------------------
-// dQ pass: one workgroup per (b, h, query cube); streams the K selected (K tile, V tile) pairs.
-// Wavefront (qh, kh): query rows qh*32..+31, key rows kh*32..+31 of each tile.  LIST as in the forward
-// kernel: one list entry per tile, or four key cubes of 16 tokens gathered into one.
-template <int D, class LIST>
-__global__ __launch_bounds__(256, 2) void k_fine_bwd_dq(int Nc, int K, float sl2, float scale, const uint4* __restrict__ q,
-                                                        const uint4* __restrict__ k, const uint4* __restrict__ v,
-                                                        const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
-                                                        const float* __restrict__ rowd,
-                                                        const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
-                                                        uint4* __restrict__ dq, int m_blocks) {
+// One workgroup per (b, h, 64-row query block), split into wavefronts that stream units of 32 keys like the forward's
+// (fine_fwd.hip).  A unit is six groups of d/16 matrix instructions, query half by query half:
+//   S 0 | S 1 | dP 0 | dP 1 | dQ 0 | dQ 1
+// so that the vector work of one half, P = exp2(S sl2 - lse) and dS = P dP', lies behind the matrix work of the other
+// without a second unit in flight; the LDS operands of a product stay in registers for its second half, so
+// each feeds two matrix instructions.  The row terms are per-lane scalars here (a lane owns a query column): lse goes
+// into the exponential's fma, -Delta is the initial value of the dP accumulators.
+//
+// d = 128: one wavefront per SIMD; dQ takes 128 of the accumulation registers and Q and dO_f the other 128 (a
+// matrix instruction reads an operand from either file).  d = 64: two wavefronts per SIMD, whose 256 registers do not
+// hold both halves' S and dP: there S 1 follows dP 0, and -Delta is added in vector arithmetic.
+//
+// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 205 others, all issued by one
+// wavefront; at 1.74 GHz the pipe is busy 67 % of the time, an instruction is issued in 57 % of it and 15 % are spent
+// in waits (start-up, merge and stores among them: about 7 us of a workgroup's 95).
+// Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
+// top-78 of 624: 1.61 -> 1.49 ms (1.23 PFLOP/s executed); 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
+// of 256, local lists: 2.83 -> 2.58 ms; d = 64, B = 2, 8 heads, top-32: 220 -> 210 us.
+template <int D, int NW, template <class> class UNITS>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
+    int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
+    const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
+    const float* __restrict__ rowd, const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
+    uint4* __restrict__ dq, int m_blocks) {
   using TL = Tile<D>;
-  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, LPT = TL::LPT;
+  using UL = UNITS<TL>;
+  using UC = UnitCopy<TL, UL>;
+  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
+  constexpr int EPR = NW / 2;           // tiles a round of units takes
+  constexpr int HALF = TL::BYTES / 2;   // 32 rows
+  constexpr int NC = UC::NC;            // copy instructions per 32 rows
+  constexpr int G = KS;                 // matrix instructions of a group
   constexpr int OS = D;
-  constexpr int STAGE = 2 * TL::BYTES;  // K tile + V tile
-  __shared__ __attribute__((aligned(16))) unsigned char stage0[STAGE];
-  __shared__ __attribute__((aligned(16))) unsigned char stage1[STAGE];
-  static_assert(2 * 32 * OS * 4 <= STAGE, "merge buffer must fit in one stage");
+  // per wavefront: K of two units, V of two units
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
+  static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
+  static_assert(G == 2 * DVB && G == NC && G % 4 == 0, "phase interleave: one copy instruction per matrix instruction");
 
   // (K = Nc: plain blockIdx order and staggered walks, as in the forward kernel)
-  const int NT = (K + LIST::kEntriesPerTile - 1) / LIST::kEntriesPerTile;  // the walk is in tiles of 64 keys
-  const bool same_lists = K == Nc * LIST::kEntriesPerTile;
+  const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
+  const bool same_lists = K == Nc * UL::kEntriesPerTile;
   const unsigned wg = same_lists ? blockIdx.x : xcd_chunked_id(blockIdx.x, gridDim.x);
   const int c = wg % Nc;
   const long long bh = wg / Nc;
-  const int rot = same_lists ? ((c >> 3) & 15) % NT : 0;
-  auto ent = [&](int t) { const int e = t + rot; return e >= NT ? e - NT : e; };
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qh = wave & 1, kh = wave >> 1, l32 = lane & 31, h = lane >> 5;
+  const int rot = same_lists ? ((c >> 3) & 15) % tiles : 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int first = wave >> 1, half = wave & 1;  // this wavefront's tiles: first, first + EPR, ...
+  const int nu = tiles > first ? (tiles - first + EPR - 1) / EPR : 0;
+  auto tile_of = [&](int u) { const int t = first + EPR * u + rot; return t >= tiles ? t - tiles : t; };
   const long long rows0 = bh * (long long)Nc * kTile;
-  const int32_t* my_idx = idx + (bh * Nc + c) * (long long)K;
-  const uint64_t qmask = mask[c];
+  const unsigned char* kb = (const unsigned char*)uniform_ptr(k + rows0 * CPR);
+  const unsigned char* vb = (const unsigned char*)uniform_ptr(v + rows0 * CPR);
 
-  // Start-up order: the list first (one round trip), then the copy of tile 0, and only then the
-  // loads of the key masks, Q, dO_f and the per-row terms, so that everything the first iteration
-  // needs is in flight together.  The empty asm consumes the loaded registers: the compiler has to
-  // place its wait for them right there (it also drains the copy, which it cannot see), and its own
-  // vmcnt bookkeeping has nothing left to wait for inside the loop (see Tile::async_load).
-  unsigned goff[TL::IPW];
-  LIST::template offsets<TL>(wave, lane, goff);
-  LIST cubes;
-  cubes.init(my_idx, mask, K, kh, wave, lane, Nc);
-  {
-    const int jt = cubes.first_row(ent(0));  // first source row of this wave's share
-    TL::async_load(k, rows0 + jt, stage0, wave, goff);
-    TL::async_load(v, rows0 + jt, stage0 + TL::BYTES, wave, goff);
-  }
-  cubes.load_masks();
-  const long long qrow_g = rows0 + c * kTile + qh * 32 + l32;
-  bf16x8 qreg[KS], doreg[KS];
-  {
-    const uint4* qrow = q + qrow_g * CPR;
-    const uint4* dorow = dof + qrow_g * CPR;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      qreg[s] = __builtin_bit_cast(bf16x8, qrow[2 * s + h]);
-      doreg[s] = __builtin_bit_cast(bf16x8, dorow[2 * s + h]);
-    }
-  }
-  // row terms -lse*log2(e)/sl2 (-30000 on pad query rows: then P = 0 and the row contributes nothing) and -Delta
-  const float* qterm = rowd + 2 * (rows0 + c * kTile + qh * 32) + l32;
-  float nlse = qterm[0], ndelta = qterm[32];
-#pragma unroll
-  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qreg[s]), "+v"(doreg[s]));
-  asm volatile("" : "+v"(nlse), "+v"(ndelta), "+v"(cubes.km_v));
-  uint32_t km_cur;  // valid-key mask (this wave's key half) of the tile of this iteration
-  {
-    int jt;
-    cubes.get_tile(ent(0), jt, km_cur);
-  }
+  // dQ and the resident operands: accumulation registers where the kernel has them (one wavefront per SIMD)
+  auto mfma_acc = [](f32x16& acc, bf16x8 a, bf16x8 b) {
+    if (D == 128) mfma_a(acc, a, b);
+    else mfma_v(acc, a, b);
+  };
+  auto pin_acc = [](f32x16& acc) {
+    if (D == 128) asm volatile("" : "+a"(acc));
+    else asm volatile("" : "+v"(acc));
+  };
+  auto pin_op = [](bf16x8& op) {
+    if (D == 128) asm volatile("" : "+a"(op));
+    else asm volatile("" : "+v"(op));
+  };
 
-  f32x16 acc[DVB];
+  // Start-up: the list first (one round trip), then the copies of the first unit, of Q (which waits in the
+  // second V stages of the first two wavefronts) and of dO_f (in their second K stages), then the row terms and
+  // the key masks, all in flight together.
+  UC copy;
+  copy.init(lane);
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
+  UL list;
+  list.init(idx + (bh * Nc + c) * (long long)K, mask, K, half, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the current unit and the two after it
+  if (nu > 0) {
+    list.rows(tile_of(0), un[0]);
+    copy.all(kb, un[0], lds0);
+  }
+  const long long q0 = rows0 + (long long)c * kTile;  // first row of this query block
+  if (NW == 2 || wave < 2) {  // half w of Q and of dO_f by wavefront w
+    UnitCopy<TL, CubeUnits<TL>> cq;
+    cq.init(lane);
+    const Unit uq = {(unsigned)half * HALF, (unsigned)half * HALF + HALF / 2, 0};
+    cq.all((const unsigned char*)uniform_ptr(q + q0 * CPR), uq, lds0 + 3 * HALF);
+    cq.all((const unsigned char*)uniform_ptr(dof + q0 * CPR), uq, lds0 + HALF);
+  }
+  if (nu > 0) copy.all(vb, un[0], lds0 + 2 * HALF);
+  list.load_masks();
+  // row terms of the lane's two query columns: -lse*log2(e)/sl2 (-30000 on pad rows: then P = 0 and the row
+  // contributes nothing) and -Delta
+  const float* qterm = rowd + 2 * q0 + l32;
+  float nlse[2] = {qterm[0], qterm[64]}, ndelta[2] = {qterm[32], qterm[96]};
+  f32x16 acc[DVB][2];
 #pragma unroll
   for (int x = 0; x < DVB; ++x)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[x][i] = 0.f;
-
-  const int lane_a = TL::rowmajor_lane(kh * 32, lane);
-  int lane_b0, lane_b1;
-  TL::transposed_lane(kh * 32, lane, lane_b0, lane_b1);
-
-  // Per-row terms folded into the matrix products (the vector pipe is the scarcer resource here):
-  // one extra MFMA step adds -lse2[q]/sl2 to S^T, so that P = exp2(S' * sl2), plus a large negative
-  // bias on pad keys; one extra step subtracts Delta[q] from dP^T.  Query-side operands (lane = query
-  // column, slots 0..2 = the fp32 value split into three bf16 parts, slot 3 = 1 resp. 0) are fixed for
-  // the workgroup; the key-side operand is (1, 1, 1, bias of key l%32).  Only the lane half h = 0
-  // carries contraction slots 0..7; the other half is zero.
-  constexpr uint32_t kOneBits = 0x3f80u, kBiasBits = 0xc6eau;  // bf16 1.0 and bf16(-29952)
-  bf16x8 bq_s, bq_d, a_d;
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[x][b][i] = 0.f;
+#pragma unroll
+  for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
+  asm volatile("" : "+v"(list.km_v), "+v"(nlse[0]), "+v"(nlse[1]), "+v"(ndelta[0]), "+v"(ndelta[1]));
+  if (nu > 0) list.get(tile_of(0), un[0]);
+  if (nu > 1) list.get(tile_of(1), un[1]);
+  wait_vmcnt<0>();
+  __syncthreads();
+  bf16x8 qreg[2][KS], doreg[2][KS];
   {
-    const uint2 sb = split3_bf16(nlse, 1.f), db = split3_bf16(ndelta, 0.f);
-    bq_s = __builtin_bit_cast(bf16x8, make_uint4(h == 0 ? sb.x : 0u, h == 0 ? sb.y : 0u, 0u, 0u));
-    bq_d = __builtin_bit_cast(bf16x8, make_uint4(h == 0 ? db.x : 0u, h == 0 ? db.y : 0u, 0u, 0u));
-    a_d = __builtin_bit_cast(bf16x8, make_uint4(h == 0 ? kOneBits * 0x10001u : 0u, h == 0 ? kOneBits : 0u, 0u, 0u));
+    const int lane_q = TL::rowmajor_lane(0, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        qreg[b][s] = TL::rowmajor_at(smem + (4 * b + 3) * HALF, lane_q, s);
+        doreg[b][s] = TL::rowmajor_at(smem + (4 * b + 1) * HALF, lane_q, s);
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      pin_op(qreg[b][s]);
+      pin_op(doreg[b][s]);
+    }
+  __syncthreads();  // every wavefront has Q and dO_f: the second stages may be filled
+  if (nu > 1) {
+    copy.all(kb, un[1], lds0 + HALF);
+    copy.all(vb, un[1], lds0 + 3 * HALF);
   }
 
-  // Per tile: wait for this wave's share of tile t, barrier (tile t complete, and every wave is
-  // done with tile t-1), start the copy of tile t+1 into the other stage, do the math on tile t.
-  auto body = [&](auto copy_tag, const unsigned char* cur, unsigned char* nxt, int t) {
-    constexpr bool COPY = decltype(copy_tag)::value;  // false for the last tile of the list
-    const uint32_t mh = km_cur;
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    // The copy of the next tile is not issued in one burst here -- eight wavefronts doing that at
-    // the same moment queue up behind one another in the load path and stall -- but one
-    // instruction per matrix step below.
-    int jt = 0;
-    if (COPY) cubes.get_tile(ent(t + 1), jt, km_cur);
-    const void* gk = uniform_ptr(k + (rows0 + jt) * CPR);
-    const void* gv = uniform_ptr(v + (rows0 + jt) * CPR);
-    const unsigned ln = __builtin_amdgcn_readfirstlane(lds_address(nxt) + (unsigned)(wave * TL::IPW) * 1024u);
-    auto copy_piece = [&](int i) {
-      if (!COPY) return;
-      if (i == 0) set_m0(ln);
-      if (i == TL::IPW) set_m0(ln + TL::BYTES);
-      if (i < 2 * TL::IPW) {
-        const void* g = i < TL::IPW ? gk : gv;
-        const int r = i % TL::IPW;
-        if (r == 0) lds_dma16_at<0>(g, goff[0]);
-        if (r == 1) lds_dma16_at<1024>(g, goff[1 % TL::IPW]);
-        if (r == 2) lds_dma16_at<2048>(g, goff[2 % TL::IPW]);
-        if (r == 3) lds_dma16_at<3072>(g, goff[3 % TL::IPW]);
+  const int my = wave * (4 * HALF);
+  const int lane_a = TL::rowmajor_lane(0, lane) + my;
+  int lane_b0, lane_b1;
+  TL::transposed_lane(0, lane, lane_b0, lane_b1);
+  lane_b0 += my;
+  lane_b1 += my;
+  const float crow[2] = {nlse[0] * sl2, nlse[1] * sl2};
+  // -Delta of the lane's query column: the initial value of dP^T where the registers allow, else added to dP^T
+  constexpr bool kDeltaInit = D == 128;
+  f32x16 dinit[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dinit[b][i] = kDeltaInit ? ndelta[b] : 0.f;
+    if (kDeltaInit) asm volatile("" : "+v"(dinit[b]));
+  }
+  f32x16 zero16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero16[i] = 0.f;
+
+  bf16x8 ka[KS];  // K rows, read during the last group of the unit before
+  if (nu > 0) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) ka[s] = TL::rowmajor_at(smem, lane_a, s);
+  }
+
+  // One unit.  KIND 2: the units up to u + 2 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
+  auto body = [&](auto kind_tag, int par, int u) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool more1 = KIND >= 1;
+    const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu);
+    const unsigned char* kc = smem + par * HALF;        // K(u)
+    const unsigned char* vc = smem + (2 + par) * HALF;  // V(u)
+    bf16x8 va[KS], kt[2 * DVB];
+    f32x16 S[2], P[2];  // S^T and then P^T; dP^T
+    uint4 ds[2][2];     // dS^T as operands: [query half][contraction step]
+    auto put = [](uint4& u4, int w, uint32_t x) {
+      if (w == 0) u4.x = x;
+      if (w == 1) u4.y = x;
+      if (w == 2) u4.z = x;
+      if (w == 3) u4.w = x;
+    };
+    // items 0..7 of a query half: two values each; the first four make up contraction step 0
+    auto p_items = [&](int b, int from, int to) {
+#pragma unroll
+      for (int it = from; it < to; ++it) {
+        float x0 = fast_exp2(fmaf(S[b][2 * it], sl2, crow[b])), x1 = fast_exp2(fmaf(S[b][2 * it + 1], sl2, crow[b]));
+        asm volatile("" : "+v"(x0), "+v"(x1));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+        S[b][2 * it] = x0;
+        S[b][2 * it + 1] = x1;
       }
     };
-    __builtin_amdgcn_sched_barrier(0);
-    const unsigned char* Ks = cur;
-    const unsigned char* Vs = cur + TL::BYTES;
-
-    // The LDS operands are requested a fixed number of matrix instructions ahead of their use, in
-    // a pinned order (left to itself the compiler reads, waits and multiplies one operand at a
-    // time).  Operand i: K rows (S^T steps), then V rows (dP^T steps), then transposed K (dQ^T
-    // steps).  Operand addresses are rebuilt from three lane-dependent values (one XOR per read)
-    // rather than held in registers across the loop: the register file is the scarce resource.
-    int la = lane_a, lb0 = lane_b0, lb1 = lane_b1;
-    asm volatile("" : "+v"(la), "+v"(lb0), "+v"(lb1));
-    constexpr int NOP = 2 * KS + 2 * DVB, AHEAD = 4;
-    bf16x8 op[NOP];
-    auto read_op = [&](int i) {
-      if (i < KS) return TL::rowmajor_at(Ks, la, i);
-      if (i < 2 * KS) return TL::rowmajor_at(Vs, la, i - KS);
-      const int j = i - 2 * KS;
-      return TL::transposed_at(Ks, lb0, lb1, j & 1, j >> 1);
+    auto d_items = [&](int b, int from, int to) {
+#pragma unroll
+      for (int it = from; it < to; ++it) {
+        const float p0 = kDeltaInit ? P[b][2 * it] : P[b][2 * it] + ndelta[b];
+        const float p1 = kDeltaInit ? P[b][2 * it + 1] : P[b][2 * it + 1] + ndelta[b];
+        const uint32_t x = pack_bf16(S[b][2 * it] * p0, S[b][2 * it + 1] * p1);
+        put(ds[b][it >> 2], it & 3, x);
+        asm volatile("" : : "v"(x));
+      }
     };
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i) op[i] = read_op(i);
+    // pad keys never take part: one extra matrix step adds a large negative bias to their rows of S^T
+    auto bias = [&](int b) {
+      if (un[0].valid != 0xffffffffu) {
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));  // (built here, not held in registers across the loop)
+        const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+        bf16x8 ab = zero8, ones_b = zero8;
+        ones_b[0] = ln < 32 ? (__bf16)1.f : (__bf16)0.f;
+        ab[0] = (ln < 32 && !((un[0].valid >> (ln & 31)) & 1)) ? (__bf16)kMaskBias : (__bf16)0.f;
+        S[b] = mfma32(ab, ones_b, S[b]);
+      }
+    };
+    // the share of `n` items that step m of the steps [lo, hi) of a group does: [from, to)
+    auto share = [](int n, int m, int lo, int hi) { return m < lo ? 0 : (m >= hi ? n : n * (m - lo) / (hi - lo)); };
     __builtin_amdgcn_sched_barrier(0);
-    f32x16 sacc, dpacc;
+    // the groups of matrix instructions; `with(m)` is the rest of step m
+    auto s_group = [&](int b, auto with) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = 0.f; }
+      for (int m = 0; m < G; ++m) {
+        if (b == 0 && m == 0) wait_lgkmcnt<G / 2>();      // the first half of the K operands; newer: the second
+        if (b == 0 && m == G / 2) wait_lgkmcnt<G / 2>();  // the second half; newer: the V operands read so far
+        S[b] = mfma32(ka[m], qreg[b][m], m == 0 ? zero16 : S[b]);
+        if (b == 0) va[m] = TL::rowmajor_at(vc, lane_a, m);
+        with(m);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      bias(b);
+    };
+    auto d_group = [&](int b, auto with) {
+      if (b == 0) wait_lgkmcnt<0>();
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i) {
-      if (i < KS) sacc = mfma32(op[i], qreg[i < KS ? i : 0], sacc);
-      else dpacc = mfma32(op[i], doreg[i < KS ? 0 : i - KS], dpacc);
-      if (i + AHEAD < NOP) op[i + AHEAD] = read_op(i + AHEAD);
-      if (!(i & 1)) copy_piece(i >> 1);
+      for (int m = 0; m < G; ++m) {
+        P[b] = mfma32(va[m], doreg[b][m], m == 0 ? dinit[b] : P[b]);
+        if (b == 0) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
+        if (b == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);  // (V(u) is in registers)
+        with(m);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if constexpr (D == 128) {
+      s_group(0, [&](int) {});
+      s_group(1, [&](int m) { p_items(0, share(6, m, 1, G), share(6, m + 1, 1, G)); });
+      d_group(0, [&](int m) {
+        p_items(0, 6 + share(2, m, 0, G / 4), 6 + share(2, m + 1, 0, G / 4));
+        p_items(1, share(4, m, G / 4, G), share(4, m + 1, G / 4, G));
+      });
+      d_group(1, [&](int m) {
+        p_items(1, 4 + share(4, m, 0, G / 2), 4 + share(4, m + 1, 0, G / 2));
+        d_items(0, share(4, m, G / 2, G), share(4, m + 1, G / 2, G));
+      });
+    } else {  // one half after the other: fewer registers, and another wavefront fills the gaps
+      s_group(0, [&](int) {});
+      d_group(0, [&](int m) { p_items(0, share(8, m, 1, G), share(8, m + 1, 1, G)); });
+      s_group(1, [&](int m) { d_items(0, share(4, m, 1, G), share(4, m + 1, 1, G)); });
+      d_group(1, [&](int m) { p_items(1, share(8, m, 1, G), share(8, m + 1, 1, G)); });
+    }
+    // ---- dQ of half 0 | the rest of its dS, the first half of dS of half 1, the copy of K(u+2)
+    wait_lgkmcnt<0>();
+    asm volatile("s_nop 1");  // (two wait states between the last item and the matrix instruction that reads it)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < G; ++m) {
+      mfma_acc(acc[m % DVB][0], kt[m], __builtin_bit_cast(bf16x8, ds[0][m / DVB]));
+      if (more2) copy.piece(kb, un[2], lds0 + par * HALF, m);
+      d_items(0, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+      d_items(1, share(4, m, DVB - 1, G), share(4, m + 1, DVB - 1, G));
       __builtin_amdgcn_sched_barrier(0);
     }
-
-    // one more step on each product brings in the per-row terms and the pad-key bias (see bq_s)
-    {
-      const bool dead = !((mh >> l32) & 1);
-      const uint32_t w1 = kOneBits | ((dead ? kBiasBits : 0u) << 16);
-      const bf16x8 a_s = __builtin_bit_cast(bf16x8, make_uint4(h == 0 ? kOneBits * 0x10001u : 0u, h == 0 ? w1 : 0u, 0u, 0u));
-      sacc = mfma32(a_s, bq_s, sacc);
-      dpacc = mfma32(a_d, bq_d, dpacc);
+    // ---- dQ of half 1 | the rest of its dS, the K operands of the next unit
+    if (more1) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2)
+      if (more2) wait_vmcnt<2 * NC>();
+      else wait_vmcnt<0>();
     }
-    float ds[16];
+    asm volatile("s_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) ds[i] = fast_exp2(sacc[i] * sl2) * dpacc[i];
-    const bf16x8 b0 = acc_to_operand(ds), b1 = acc_to_operand(ds + 8);
-#pragma unroll
-    for (int j = 0; j < 2 * DVB; ++j) {
-      const int i = 2 * KS + j;
-      acc[j >> 1] = mfma32(op[i], (j & 1) ? b1 : b0, acc[j >> 1]);
-      if (i + AHEAD < NOP) op[i + AHEAD] = read_op(i + AHEAD);
+    for (int m = 0; m < G; ++m) {
+      mfma_acc(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
+      d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+      if (more1) ka[m] = TL::rowmajor_at(smem + (1 - par) * HALF, lane_a, m);
       __builtin_amdgcn_sched_barrier(0);
     }
+    un[0] = un[1];
+    un[1] = un[2];
   };
-
-  {
-    const std::true_type copy;
-    const std::false_type last;
-    int t = 0;
-    for (; t + 2 < NT; t += 2) {
-      body(copy, stage0, stage1, t);
-      body(copy, stage1, stage0, t + 1);
+  if (nu > 0) {
+    const std::integral_constant<int, 2> steady;
+    const std::integral_constant<int, 1> inner;
+    const std::integral_constant<int, 0> last;
+    int u = 0;
+    for (; u + 3 < nu; u += 2) {
+      list.get(tile_of(u + 2), un[2]);
+      body(steady, 0, u);
+      list.get(tile_of(u + 3), un[2]);
+      body(steady, 1, u + 1);
     }
-    if (t + 1 < NT) {
-      body(copy, stage0, stage1, t);
-      body(last, stage1, stage0, t + 1);
-    } else {
-      body(last, stage0, stage1, t);
+    for (; u + 1 < nu; ++u) {
+      if (u + 2 < nu) list.get(tile_of(u + 2), un[2]);
+      body(inner, u & 1, u);
     }
+    body(last, u & 1, u);
   }
+  mfma_fence();  // the last matrix results land before they are read
+#pragma unroll
+  for (int x = 0; x < DVB; ++x)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
+  __builtin_amdgcn_sched_barrier(0);
+
   // the pooled-gradient term of this thread's column chunk (the same chunk for all of its items),
   // requested before the partial results go through LDS
-  static_assert(256 % CPR == 0, "a thread keeps its column chunk");
-  const float* dqcr = dqc + ((bh * Nc + c) / m_blocks) * D + (tid % CPR) * 8;  // per cube = m_blocks blocks
+  static_assert(NT % CPR == 0, "a thread keeps its column chunk");
+  const int ch = tid % CPR;
+  const float* dqcr = dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks
   const float4 pc0 = *(const float4*)dqcr, pc1 = *(const float4*)(dqcr + 4);
-  __syncthreads();
-
+  const uint64_t qmask = mask[c];
+  const float inv_cnt = 1.0f / (float)cube_count(mask, c, m_blocks);
+  __syncthreads();  // every wavefront is done with its stages
   {
-    float* Op = (float*)(kh == 0 ? stage0 : stage1) + qh * 32 * OS;
+    float* Op = (float*)smem + wave * 64 * OS;
 #pragma unroll
-    for (int x = 0; x < DVB; ++x)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        float4 val = make_float4(acc[x][4 * g4], acc[x][4 * g4 + 1], acc[x][4 * g4 + 2], acc[x][4 * g4 + 3]);
-        *(float4*)&Op[merge_offset(l32, x * 32 + 8 * g4 + 4 * h, OS)] = val;
-      }
+      for (int x = 0; x < DVB; ++x)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+          *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
+              make_float4(acc[x][b][4 * g4], acc[x][b][4 * g4 + 1], acc[x][b][4 * g4 + 2], acc[x][b][4 * g4 + 3]);
   }
   __syncthreads();
 
-  const float inv_cnt = 1.0f / (float)cube_count(mask, c, m_blocks);
   const float pooled[8] = {pc0.x * inv_cnt, pc0.y * inv_cnt, pc0.z * inv_cnt, pc0.w * inv_cnt,
                            pc1.x * inv_cnt, pc1.y * inv_cnt, pc1.z * inv_cnt, pc1.w * inv_cnt};
 #pragma unroll
   for (int it = 0; it < LPT; ++it) {
-    const int item = it * 256 + tid, r = item / CPR, ch = item % CPR;
+    const int r = (it * NT + tid) / CPR;
     const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-    const float4 a0 = *(const float4*)((const float*)stage0 + m0), a1 = *(const float4*)((const float*)stage0 + m1);
-    const float4 b0 = *(const float4*)((const float*)stage1 + m0), b1 = *(const float4*)((const float*)stage1 + m1);
-    const float sum[8] = {a0.x + b0.x, a0.y + b0.y, a0.z + b0.z, a0.w + b0.w, a1.x + b1.x, a1.y + b1.y, a1.z + b1.z, a1.w + b1.w};
+    float4 a = *(const float4*)((const float*)smem + m0), b = *(const float4*)((const float*)smem + m1);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float4 x = *(const float4*)((const float*)smem + w * 64 * OS + m0);
+      const float4 y = *(const float4*)((const float*)smem + w * 64 * OS + m1);
+      a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
+      b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
+    }
+    const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     uint4 ov = make_uint4(0, 0, 0, 0);
     if ((qmask >> r) & 1) {
       float res[8];
@@ -247,9 +363,12 @@ __global__ __launch_bounds__(256, 2) void k_fine_bwd_dq(int Nc, int K, float sl2
       for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], scale, pooled[e]);
       ov = pack8(res);
     }
-    dq[(rows0 + c * kTile + r) * CPR + ch] = ov;
+    dq[(q0 + r) * CPR + ch] = ov;
   }
 }
+
+// Up to this many query blocks, four wavefronts per workgroup (as in the forward).
+constexpr int kDqFourWaves = 256;
 
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
@@ -257,16 +376,22 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
                               hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
-#define VSA_DQ(D_, LIST_)                                                                                          \
-  k_fine_bwd_dq<D_, LIST_><<<grid, 256, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
+#define VSA_DQ(D_, NW_, LIST_)                                                                                          \
+  k_fine_bwd_dq<D_, NW_, LIST_><<<grid, 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
                                                 (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks)
+#define VSA_DQ_NW(D_, LIST_)                        \
+  do {                                              \
+    if (grid <= kDqFourWaves) VSA_DQ(D_, 4, LIST_); \
+    else VSA_DQ(D_, 2, LIST_);                      \
+  } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
-    if (d == 128) VSA_DQ(128, SubCubeList);
-    else VSA_DQ(64, SubCubeList);
+    if (d == 128) VSA_DQ_NW(128, SubCubeUnits);
+    else VSA_DQ_NW(64, SubCubeUnits);
   } else {
-    if (d == 128) VSA_DQ(128, CubeList);
-    else VSA_DQ(64, CubeList);
+    if (d == 128) VSA_DQ_NW(128, CubeUnits);
+    else VSA_DQ_NW(64, CubeUnits);
   }
+#undef VSA_DQ_NW
 #undef VSA_DQ
   return hipGetLastError();
 }

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
   const unsigned char* rw = (const unsigned char*)uniform_ptr(rowd + 2 * (rows0 + half * 32));  // 32 + 32 floats per 32 rows
   constexpr int ROWD_SHIFT = D == 128 ? 5 : 4;  // bytes of a block's Q rows / bytes of its row terms
 
-  // Copies (see Tile::async_load): instruction c of 32 rows fills rows c*RPI ..; the swizzle repeats after
+  // Copies (see UnitCopy): instruction c of 32 rows fills rows c*RPI ..; the swizzle repeats after
   // 16 rows = 4 KiB (d = 128), so four lane offsets serve and the second group moves both bases by 4 KiB.
   constexpr int NOFF = NC < 4 ? NC : 4;
   unsigned goff[NOFF];

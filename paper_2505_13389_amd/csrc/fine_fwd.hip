@@ -35,7 +35,6 @@
 
 namespace vsa {
 
-constexpr float kMaskBias = -30000.f;  // added to the raw logits of pad keys (|q.k| is assumed < 15000)
 constexpr float kTau = 60.f;            // lazy-rescale threshold, log2 units
 constexpr float kMaxSum = 1152921504606846976.f;  // 2^kTau
 constexpr float kNoRef = -1e30f;        // reference before the first valid key: every value then exceeds kMaxSum

@@ -11,6 +11,8 @@
 
 namespace vsa {
 
+constexpr float kMaskBias = -30000.f;  // added to the raw logits of pad keys (|q.k| is assumed < 15000)
+
 // Byte offsets of a unit's two 16-row groups from the first row of the (b, h), and its 32 valid-key bits.
 struct Unit {
   unsigned a, b;
@@ -105,8 +107,9 @@ struct SubCubeUnits {
   __device__ static __forceinline__ int source_row(int x) { return subcube_slot(x); }
 };
 
-// Copies of 32 rows by one wavefront (see Tile::async_load for the instruction and the swizzle): instruction c
-// fills rows c*RPI ..; the swizzle repeats after 16 rows.  Every 16-row group has an M0 value of its own; where
+// Copies of 32 rows by one wavefront (global_load_lds_dwordx4, see lds_dma16_at): instruction c fills rows c*RPI ..,
+// the swizzle is applied on the SOURCE side (the lane that writes physical chunk pc of row r fetches logical chunk
+// pc ^ swz(r)) and repeats after 16 rows.  Every 16-row group has an M0 value of its own; where
 // the 32 rows are contiguous one base address serves both, the distance is in the second group's lane offsets.
 template <class TL, class UNITS>
 struct UnitCopy {
@@ -143,9 +146,6 @@ struct UnitCopy {
 // they need; the kernels' fixed order provides them: a vector result is consumed by a matrix instruction
 // no earlier than two instructions after it was written, and a matrix result is read by vector instructions
 // no earlier than two matrix instructions after the one that completed it.
-__device__ __forceinline__ void mfma_v0(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
-}
 __device__ __forceinline__ void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }

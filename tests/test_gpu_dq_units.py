@@ -1,0 +1,32 @@
+"""dQ pass: list walks of every length around the unrolled loop, on both sides of the workgroup-size rule, with partial
+cubes and, in the last layer of a 6-frame clip, key halves that are all pads."""
+import numpy as np
+import pytest
+
+from helpers import assert_close, bf16_to_np, grid_of, problem_of, tiled_bits, to_dev, widen
+from oracle import vsa_oracle as orc
+from paper_2505_13389_amd.synth import Workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 3])  # 96 query blocks each: four wavefronts per workgroup, two
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 65])
+def test_dq_walks_of_every_length(K, H, d):
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("dq_units", 1, H, 6, 22, 30, d, K)
+    bits = tiled_bits(wl, seed=100 + K + d + H, pad_garbage=True)
+    x, dev, g = widen(bits), to_dev(bits), grid_of(wl)
+    rng = np.random.default_rng(K)
+    idx = np.sort(rng.permuted(np.tile(np.arange(g.Nc, dtype=np.int32), (1, H, g.Nc, 1)), axis=-1)[..., :K])
+    ref = orc.backward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], x["dout"], idx, K, real="f32")
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(*a, indices_given=True)
+    buf.backward(*a, dev["dout"], workspace_kept=True)
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv"):
+        assert_close(bf16_to_np(getattr(buf, n)), ref[n], n)

@@ -46,13 +46,45 @@ __device__ __forceinline__ float max_across_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Gangs.  The workgroups that run side by side on an XCD fetch their tiles through one 4 MiB L2, and a tile
+// is in it for the second one that wants it only if both are at about the same place of their (ascending) lists.
+// They start together, but every workgroup starts when an earlier one ends, and after many generations their places
+// are spread over the whole walk.  So in long launches the workgroups that fill an XCD once form a gang, and those
+// of every `every`-th gang wait until all of it is there.  A wait is bounded (about 25 us: it only costs time if
+// part of the chip is taken by somebody else) and changes no result.  Workgroups are dealt to the 8 XCDs round-robin
+// by blockIdx.
+template <int D>
+constexpr unsigned kGang = D == 128 ? 64 : 128;  // 32 CUs x the workgroups of two wavefronts a CU holds
+constexpr int kGangSpins = 40;
+
+__global__ void k_gang_clear(unsigned* __restrict__ arrived, unsigned n) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) arrived[i] = 0;
+}
+
+template <unsigned GANG>
+__device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
+  const unsigned x = blockIdx.x & 7u, i = blockIdx.x >> 3, gang = i / GANG;
+  if (gang % every) return;  // (uniform)
+  if (threadIdx.x == 0) {
+    unsigned* mine = arrived + gang * 8 + x;
+    const unsigned of_xcd = (gridDim.x + 7 - x) >> 3, size = min(GANG, of_xcd - gang * GANG);
+    __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int spin = 0; spin < kGangSpins; ++spin) {
+      if (__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= size) break;
+      __builtin_amdgcn_s_sleep(4);
+    }
+  }
+  __syncthreads();
+}
+
 template <int D, int NW, template <class> class UNITS>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     int Nc, int K, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
     const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
     uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
-    int m_blocks) {
+    int m_blocks, unsigned* __restrict__ gang_arrived, unsigned gang_every) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
@@ -75,6 +107,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // (plain blockIdx order), which keeps that list's tiles shared chip-wide, and the workgroups that
   // run side by side on an XCD (cubes c, c+8, ...) start their walk a few entries apart and wrap
   // around -- otherwise they ask for the same cache lines in the same cycles.
+  if (NW == 2 && gang_arrived) gang_start<kGang<D>>(gang_arrived, gang_every);
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
   const unsigned wg = same_lists ? blockIdx.x : xcd_chunked_id(blockIdx.x, gridDim.x);
@@ -467,15 +500,30 @@ constexpr int kFwdFourWaves = 256;
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, hipStream_t s) {
+                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
+  // Gangs where the K and V of a head are many times an L2, the lists differ and there are several generations; one
+  // in about every 256 tiles walked.  16 heads of 1440 blocks (45 MiB), d = 128, i.i.d. lists of 60 / 180 / 480: 4.58 -> 3.97,
+  // 10.0 -> 9.15, 22.9 -> 22.0 ms; 40 heads, 180: 32.9 -> 23.3 ms (L2 hits 0.38 before); 1152 blocks (36 MiB): 5.86 ->
+  // 5.65; 840 blocks (26 MiB), 40: 1.54 -> 1.46; d = 64, 1440 blocks (22.5 MiB): 4.7 to 6.8 -> 4.7.  Below, waiting costs
+  // more than the hits return: 624 blocks (19.5 MiB) 1.23 -> 1.26 ms at one gang in 312 tiles.  Local selections, which hit
+  // anyway: 1440 blocks, lists of 180 / 60: 9.33 -> 8.95, 3.36 -> 3.39 ms.
+  const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
+  const unsigned gang = d == 128 ? kGang<128> : kGang<64>;
+  const bool gangs = (size_t)Nc * kTile * d * 4 >= ((size_t)22 << 20) && tiles < Nc && grid >= 16 * gang;
+  const unsigned every = gangs ? (unsigned)(255 / tiles + 1) : 1u;
+  unsigned* arrived = gangs ? gang_scratch : nullptr;
+  if (gangs) {
+    const unsigned n = 8 * ((grid / 8 + gang) / gang + 1);  // (at most BH*Nc/32 + 24 counters)
+    k_gang_clear<<<(n + 255) / 256, 256, 0, s>>>(arrived, n);
+  }
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
 #define VSA_FWD(D_, NW_, LIST_)                                                                                      \
   k_fine_fwd<D_, NW_, LIST_><<<grid, 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks)
+                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, arrived, every)
 #define VSA_FWD_NW(D_, LIST_)                     \
   do {                                            \
     if (grid <= kFwdFourWaves) VSA_FWD(D_, 4, LIST_); \

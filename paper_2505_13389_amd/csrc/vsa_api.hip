@@ -255,8 +255,9 @@ int enqueue_forward(const vsa_params_t* p, const Geo& g, const void* q, const vo
     VSA_TRY("expand_lists", vsa::launch_expand_lists(BH, g.Nc, p->topk, g.m, idx, w.idx_blocks, s));
     lists = w.idx_blocks;
   }
+  // (the coarse scores have been read by now: [BH, Nc, key rows] floats, more than the counters need by far)
   VSA_TRY("fine_fwd", vsa::launch_fine_fwd(BH, g.Nb, p->d, p->topk * blocks_per_entry(p, g), scale, q, k, v, gate_c, gate_f, lists, oc, w.mask, out,
-                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, s));
+                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, (unsigned*)w.sc, s));
   return VSA_OK;
 }
 

@@ -81,3 +81,40 @@ def test_reference_follows_the_logits(order, H, d):
     q = u + 0.1 * rng.standard_normal((1, H, g.Np, d))
     bits["q"], bits["k"] = synth.f32_to_bf16_bits(q.astype(np.float32)), synth.f32_to_bf16_bits(k.astype(np.float32))
     run_and_check(wl, bits, random_lists(wl, g, 11))
+
+
+@pytest.mark.parametrize("d,K", [(64, 300), (128, 150), (128, 20)])
+def test_gangs_of_large_heads(d, K):
+    """Heads of 1440 blocks: workgroups start in gangs (every one, every second, only the first; the last gang of an
+    XCD is not a whole one).  Sampled query cubes against the oracle; graph replays, with the counters' memory
+    poisoned in between, bit-identical."""
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("fwd_gang", 1, 2, 24, 48, 80, d, K)
+    g = grid_of(wl)
+    bits = tiled_bits(wl, seed=K)
+    x, dev = widen(bits), to_dev(bits)
+    idx = random_lists(wl, g, K)
+    cubes = np.array([0, 1, 511, 512, 777, g.Nc - 1], np.int32)
+    ref = orc.forward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], K, real="f32", block_idx=idx, cubes=cubes)
+    buf = vsa.Buffers(problem_of(wl))
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    args = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.forward(*args, indices_given=True)
+    torch.cuda.synchronize()
+    V = g.Np // g.Nc
+    rows = (cubes[:, None] * V + np.arange(V)).ravel()
+    assert_close(bf16_to_np(buf.out)[:, :, rows], ref["out"][:, :, rows], "out")
+    eager = buf.out.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        buf.forward(*args, indices_given=True)
+    for rep in range(3):
+        buf.out.fill_(float("nan"))
+        buf.workspace.fill_(0xFF)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(buf.out.view(torch.int16), eager.view(torch.int16)), f"replay {rep}"

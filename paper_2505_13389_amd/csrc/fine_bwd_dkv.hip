@@ -46,12 +46,13 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // instruction per key half subtracts a large number from S of the other keys.  The pooled-gradient terms
 // are per key cube.
 //
-// What bounds it: the matrix pipe is busy 64 % of the time at 1.6 GHz (power: the clock falls as the pipe
-// fills), 391 instructions per 64 matrix instructions; 3 us of start-up and 5 us of merge and stores per
+// What bounds it: the matrix pipe is busy 69 % of the time at 1.6 GHz (power: the clock falls as the pipe
+// fills: 12 % fewer instructions, by addresses held in registers and one wait per two steps, 391 -> 346 per 64 matrix
+// instructions, gave 2 %); 3 us of start-up and 5 us of merge and stores per
 // workgroup, which the other workgroup of the CU overlaps.  Before (32 keys x 32 queries per wavefront, 4
 // wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
-// 12 heads, d = 128, top-78 of 624: 2.68 -> 2.01 ms (1.19 PFLOP/s executed); 16384 tokens, top-32: 529 -> 377
-// us, top-8: 228 -> 150 us; d = 64, B = 2, 8 heads, top-32: 485 -> 294 us.  Four wavefronts (one workgroup
+// 12 heads, d = 128, top-78 of 624: 2.68 -> 1.97 ms (1.22 PFLOP/s executed); 16384 tokens, top-32: 529 -> 370
+// us; d = 64, B = 2, 8 heads, top-32: 485 -> 288 us.  Four wavefronts (one workgroup
 // per CU, merging four partial results) instead of two: 2.20 ms, 426 us, 216 us, 349 us.
 template <int D, int NW, bool SUB>
 __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int K, float sl2, float scale, const uint4* __restrict__ q,
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
   constexpr int STAGE = 2 * HALF + 256;    // Q rows, dO_f rows, row terms of one unit
   constexpr int NST = D == 128 ? 2 : 4;    // stages per wavefront
   constexpr int NC = HALF / 1024;          // copy instructions per 32 rows
-  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use
+  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use: a pair of steps reads for the next pair
   constexpr int NCD = 2 * DVB;             // steps of the dV and of the dK phase
   constexpr int OS = D;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[HALF + NW * NST * STAGE];
@@ -240,18 +241,19 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
     sinit = row_init(0, 0);
   }
 
-  int st_off = 0;  // byte offset of the current unit's stage among the wavefront's stages
-  auto body = [&](auto steady_tag, int u) {
+  // One unit, whose rows lie in the wavefront's stage `st` (a constant in the unrolled loop).
+  auto body = [&](auto steady_tag, int u, int st) {
     constexpr bool STEADY = decltype(steady_tag)::value;  // the units up to u + NST exist
     const bool more_q = STEADY || u + NST - 1 < nu;
-    const int next_st = st_off == (NST - 1) * STAGE ? 0 : st_off + STAGE;
-    const int prev_st = st_off == 0 ? (NST - 1) * STAGE : st_off - STAGE;
-    // operand addresses are rebuilt from a few lane values in every iteration (one XOR per read) instead
-    // of being held in registers across the loop
-    int lq = lane_q + st_off, lv = lane_v, lb0 = lane_b0 + st_off, lb1 = lane_b1 + st_off;
-    asm volatile("" : "+v"(lq), "+v"(lv), "+v"(lb0), "+v"(lb1));
-    const unsigned char* Qs = smem;
-    const unsigned char* Ds = smem + HALF;
+    const int st_off = st * STAGE, next_st = st == NST - 1 ? 0 : st_off + STAGE;
+    const int prev_st = st == 0 ? (NST - 1) * STAGE : st_off - STAGE;
+    // (the addresses of V, and with key cubes of 16 all of them, are rebuilt per unit: registers are short)
+    int lv = lane_v, lq = lane_q, lb0 = lane_b0, lb1 = lane_b1;
+    asm volatile("" : "+v"(lv));
+    if (SUB) asm volatile("" : "+v"(lq), "+v"(lb0), "+v"(lb1));
+    const unsigned char* Qs = smem + st_off;
+    const unsigned char* Ds = smem + st_off + HALF;
+    const unsigned char* Qn = smem + next_st;
     bf16x8 qa[KS], da[KS], va[KS], dt[NCD], qt[NCD];
     f32x16 dpinit;
 #pragma unroll
@@ -273,11 +275,21 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
         qt[c] = TL::transposed_at(Qs, lb0, lb1, c / DVB, c % DVB);
       } else {
         const int s = m - 2 * KS - 2 * NCD;
-        if (s == 0) {
-          lq = lane_q + next_st;
-          sinit = row_init(next_st, 0);
-        }
-        qcur[s] = TL::rowmajor_at(smem, lq, s);
+        if (s == 0) sinit = row_init(next_st, 0);
+        qcur[s] = TL::rowmajor_at(Qn, lq, s);
+      }
+    };
+    // at the first step of a pair: its operands are there; those of the next pair are requested
+    auto pair_begins = [&](int m) {
+      if (m % 2 == 0) {
+        wait_lgkmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto pair_reads = [&](int m) {
+      if (m % 2 == 0) {
+        read_step(m + kAhead);
+        read_step(m + kAhead + 1);
       }
     };
     // ---- S
@@ -292,6 +304,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
     const unsigned char* gq = qw + next_off;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
+      pair_begins(s);
       if (s == 0) mfma_v_from(s0, qa[0], kreg[0][0], sinit);
       else mfma_v(s0, qa[s], kreg[0][s]);
       if (more_q) {
@@ -302,10 +315,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
       __builtin_amdgcn_sched_barrier(0);
       if (s == 0) s1 = sinit;
       mfma_v(s1, qa[s], kreg[1][s]);
-      read_step(s + kAhead);
+      pair_reads(s);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (SUB) {
+      asm volatile("s_nop 1");  // (two wait states between the moves to the bias operands and the matrix instruction)
       mfma_v(s0, ones_a, bias0);
       mfma_v(s1, ones_a, bias1);
       __builtin_amdgcn_sched_barrier(0);
@@ -349,9 +363,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
     for (int s = 0; s < KS; ++s) {
       const bool on = s >= 1 && s <= KS - 2;
       const int i0 = (s - 1) * P_DP / (KS - 2), i2 = s * P_DP / (KS - 2), i1 = (i0 + i2) / 2;
+      pair_begins(KS + s);
       if (s == 0) mfma_v_from(p0, da[0], vreg[0], dpinit);
       else mfma_v(p0, da[s], vreg[s]);
-      read_step(KS + s + kAhead);
+      pair_reads(KS + s);
       if (on) p_items(i0, i1);
       __builtin_amdgcn_sched_barrier(0);
       if (s == 0) p1 = dpinit;
@@ -369,10 +384,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
       const int i0 = P_DP + c * (16 - P_DP) / (DVB - 1), i2 = P_DP + (c + 1) * (16 - P_DP) / (DVB - 1), i1 = (i0 + i2) / 2;
       // (those of step 0 are the first eight: done one step before the end)
       const int e0 = (c - DVB + 1) * 8 / DVB, e2 = c == NCD - 1 ? S_DV : (c - DVB + 2) * 8 / DVB, e1 = (e0 + e2) / 2;
+      pair_begins(2 * KS + c);
       mfma_a(dva[c % DVB][0], dt[c], opnd(pb[0][c / DVB]));
       if (pv_on) p_items(i0, i1);
       if (ds_on) s_items(e0, e1);
-      read_step(2 * KS + c + kAhead);
+      pair_reads(2 * KS + c);
       __builtin_amdgcn_sched_barrier(0);
       mfma_a(dva[c % DVB][1], dt[c], opnd(pb[1][c / DVB]));
       if (pv_on) p_items(i1, i2);
@@ -399,6 +415,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
 #pragma unroll
           for (int e = from; e < to; ++e) copy_piece(gd, wbase + st_off + HALF, e);
       };
+      pair_begins(2 * KS + NCD + c);
       mfma_a(dka[c % DVB][0], qt[c], opnd(sb[0][c / DVB]));
       if (ds_on) s_items(i0, i1);
       copies(g0, g1);
@@ -414,14 +431,17 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
         else if (NST > 2 && left == 1) wait_vmcnt<G>();
         else wait_vmcnt<0>();
       }
-      read_step(2 * KS + NCD + c + kAhead);
+      pair_reads(2 * KS + NCD + c);
       __builtin_amdgcn_sched_barrier(0);
     }
-    st_off = next_st;
   };
   int u = 0;
-  for (; u + NST < nu; ++u) body(std::true_type{}, u);
-  for (; u < nu; ++u) body(std::false_type{}, u);
+  for (; u + 2 * NST - 1 < nu; u += NST) {
+#pragma unroll
+    for (int st = 0; st < NST; ++st) body(std::true_type{}, u + st, st);
+  }
+  for (; u + NST < nu; ++u) body(std::true_type{}, u, u % NST);
+  for (; u < nu; ++u) body(std::false_type{}, u, u % NST);
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix results land before they are read
   __builtin_amdgcn_sched_barrier(0);
 

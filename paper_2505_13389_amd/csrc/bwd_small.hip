@@ -8,114 +8,6 @@
 namespace vsa {
 
 // ---------------------------------------------------------------------------------------------
-// Preprocess.  Per token i of cube c (pad rows produce zeros):
-//   dGc_i = dO_i * Oc[c]      dGf_i = dO_i * Of_i      dOf_i = dO_i * Gf_i  (bf16, feeds the MFMAs)
-//   Delta_i = sum_d dOf_i * Of_i                       dOc[c] = sum_i dO_i * Gc_i
-//   rowd   per 32 rows: 32 values of -lse_i * log2(e) / sl2 (so that P = exp2((S + value) * sl2); -30000 on
-//          pad rows, where P then underflows to 0), then 32 values of -Delta_i
-// One workgroup per (b*h, cube), which walks the cube's m blocks of 64 rows; thread layout as in the
-// pooling kernel.
-template <int D>
-__global__ __launch_bounds__(256) void k_bwd_pre(int Nc, int m_blocks, const uint64_t* __restrict__ mask, const uint4* __restrict__ dout,
-                                                 const uint4* __restrict__ gc, const uint4* __restrict__ gf,
-                                                 const uint4* __restrict__ of, const float* __restrict__ oc,
-                                                 uint4* __restrict__ dgc, uint4* __restrict__ dgf,
-                                                 uint4* __restrict__ dof, float* __restrict__ rowd, float inv_sl2,
-                                                 float* __restrict__ doc,
-                                                 const float* __restrict__ lse_f, int H, long long do_head_stride,
-                                                 long long do_row_stride) {
-  constexpr int CPR = D / 8, RG = 256 / CPR, RPT = kTile / RG;
-  __shared__ float part[RG][D + 4];
-  const int c = blockIdx.x % Nc;
-  const long long bh = blockIdx.x / Nc;
-  const int ch = threadIdx.x % CPR, rg = threadIdx.x / CPR;
-  float ocv[8];
-  {
-    const float* p = oc + (bh * Nc + c) * D + ch * 8;
-    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-    ocv[0] = a.x; ocv[1] = a.y; ocv[2] = a.z; ocv[3] = a.w; ocv[4] = b.x; ocv[5] = b.y; ocv[6] = b.z; ocv[7] = b.w;
-  }
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int sb = 0; sb < m_blocks; ++sb) {
-  const long long blk = (bh * Nc + c) * m_blocks + sb;  // block index over all (b, h)
-  const uint64_t m = mask[c * m_blocks + sb];
-  const long long row0 = blk * (long long)kTile;
-  // dout may be head-major [B,H,Np,D] or token-major [B,Np,H,D] (see the forward's `out`)
-  const long long Npad = (long long)Nc * m_blocks * kTile;
-  const long long do0 = (bh / H) * ((long long)H * Npad * CPR) + (bh % H) * do_head_stride +
-                        ((long long)c * m_blocks + sb) * kTile * do_row_stride;
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int r = rg + i * RG;
-    const long long g = (row0 + r) * CPR + ch;
-    const bool valid = (m >> r) & 1;
-    uint4 z = make_uint4(0, 0, 0, 0), o_gc = z, o_gf = z, o_dof = z;
-    float dsum = 0.f;
-    if (valid) {
-      float go[8], gcv[8], gfv[8], ofv[8], t0[8], t1[8], t2[8];
-      unpack8(dout[do0 + r * do_row_stride + ch], go);
-      unpack8(gc[g], gcv);
-      unpack8(of[g], ofv);
-      if (gf) unpack8(gf[g], gfv);
-      else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gfv[e] = 1.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        t0[e] = go[e] * ocv[e];
-        t1[e] = go[e] * ofv[e];
-        t2[e] = go[e] * gfv[e];
-        acc[e] += go[e] * gcv[e];
-      }
-      o_gc = pack8(t0); o_gf = pack8(t1); o_dof = pack8(t2);
-      float t2r[8];
-      unpack8(o_dof, t2r);  // Delta uses the rounded dOf, the value the fine kernels multiply with
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dsum = fmaf(t2r[e], ofv[e], dsum);
-    }
-    dgc[g] = o_gc;
-    if (dgf) dgf[g] = o_gf;
-    dof[g] = o_dof;
-#pragma unroll
-    for (int o = CPR / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-    if (ch == 0) {
-      float* p = rowd + 2 * (row0 + (r & ~31)) + (r & 31);
-      p[0] = valid ? -lse_f[row0 + r] * kLog2e * inv_sl2 : -30000.f;
-      p[32] = -dsum;
-    }
-  }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) part[rg][ch * 8 + e] = acc[e];
-  __syncthreads();
-  if (threadIdx.x < D) {
-    float s = 0;
-    for (int r = 0; r < RG; ++r) s += part[r][threadIdx.x];
-    doc[(bh * Nc + c) * D + threadIdx.x] = s;
-  }
-}
-
-hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
-                          const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
-                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
-                          int dout_token_major, hipStream_t s) {
-  const unsigned grid = (unsigned)(BH * Nc);
-  const float inv_sl2 = 1.0f / (scale * kLog2e);
-  const long long cpr = d / 8, Np = (long long)Nc * m_blocks * kTile;
-  const long long dhs = dout_token_major ? cpr : Np * cpr, drs = dout_token_major ? H * cpr : cpr;
-  if (d == 128)
-    k_bwd_pre<128><<<grid, 256, 0, s>>>(Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                        inv_sl2, doc, lse_f, H, dhs, drs);
-  else
-    k_bwd_pre<64><<<grid, 256, 0, s>>>(Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                       (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                       inv_sl2, doc, lse_f, H, dhs, drs);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
 // Up to three independent problems of the same shape run as one launch (blockIdx.z = problem *
 // batch + batch index): the small coarse-stage products do not fill the chip one at a time.
 struct GemmOperands {
@@ -265,11 +157,14 @@ __global__ __launch_bounds__(256) void k_map_degree(int Nc, int W32, long long r
   if (lane == 0) row_ptr[(row / Nc) * (Nc + 1) + row % Nc] = c;
 }
 
-// Exclusive scan over 4 * 1024 values, 4 consecutive ones per thread of a 1024-thread workgroup:
+// Exclusive scan over PT * NT values, PT consecutive ones per thread of an NT-thread workgroup:
 // v[i] is replaced by the sum of everything before it; returns the grand total.
-__device__ __forceinline__ int block_scan4(int* v, int* wsum, int tid) {
+template <int PT, int NT>
+__device__ __forceinline__ int block_scan(int* v, int* wsum, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
-  const int sum = v[0] + v[1] + v[2] + v[3];
+  int sum = 0;
+#pragma unroll
+  for (int i = 0; i < PT; ++i) sum += v[i];
   int incl = sum;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -280,13 +175,13 @@ __device__ __forceinline__ int block_scan4(int* v, int* wsum, int tid) {
   if (lane == 63) wsum[wave] = incl;
   __syncthreads();
   int base = 0, total = 0;
-  for (int w = 0; w < 16; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     if (w < wave) base += wsum[w];
     total += wsum[w];
   }
   int run = base + incl - sum;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < PT; ++i) {
     const int t = v[i];
     v[i] = run;
     run += t;
@@ -294,7 +189,8 @@ __device__ __forceinline__ int block_scan4(int* v, int* wsum, int tid) {
   return total;
 }
 
-// sum of one value per thread over a 1024-thread workgroup, returned to every thread
+// sum of one value per thread over an NT-thread workgroup, returned to every thread
+template <int NT>
 __device__ __forceinline__ int block_sum(int x, int* wsum, int tid) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
@@ -302,7 +198,7 @@ __device__ __forceinline__ int block_sum(int x, int* wsum, int tid) {
   if ((tid & 63) == 0) wsum[tid >> 6] = x;
   __syncthreads();
   int total = 0;
-  for (int w = 0; w < 16; ++w) total += wsum[w];
+  for (int w = 0; w < NT / 64; ++w) total += wsum[w];
   return total;
 }
 
@@ -319,23 +215,24 @@ __device__ __forceinline__ int block_sum(int x, int* wsum, int tid) {
 //          workgroup, Nc + cap of them per (b, h); unused ones carry key cube -1
 //   split: per (b, h) cap/2 + 1 descriptors: [0] = (number of split lists, 0, 0, 0), then
 //          (key cube, first slot, number of slots, 0) per split list, in cube order
-// (the body, for the 1024 threads of one workgroup: thread `tid` owns cubes 4*tid .. 4*tid+3, whose
-// in-degrees it passes in `deg`; `v` returns where their lists begin.  wsum[16] and hist[kMaxCubes] are
+// (the body, for the NT threads of one workgroup: thread `tid` owns cubes PT*tid .. PT*tid+PT-1, Nc <= PT*NT, whose
+// in-degrees it passes in `deg`; `v` returns where their lists begin.  wsum[NT/64] and hist[PT*NT] are
 // LDS scratch: bucket x of hist counts the items of length Nc - x (the last bucket also takes what
 // lies beyond it), then holds the next free slot of the bucket)
-__device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int bh, int tid, const int (&deg)[4], int (&v)[4],
+template <int PT, int NT>
+__device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int bh, int tid, const int (&deg)[PT], int (&v)[PT],
                                               int32_t* __restrict__ row_ptr, int32_t* __restrict__ order,
                                               int32_t* __restrict__ split, int* wsum, int* hist) {
   int32_t* rp = row_ptr + (long long)bh * (Nc + 1);
-  const int j0 = tid * 4;
+  const int j0 = tid * PT;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < PT; ++i) {
     v[i] = deg[i];
     hist[j0 + i] = 0;
   }
-  const int total = block_scan4(v, wsum, tid);  // (its barriers also cover the clearing of hist)
+  const int total = block_scan<PT, NT>(v, wsum, tid);  // (its barriers also cover the clearing of hist)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < PT; ++i)
     if (j0 + i < Nc) rp[j0 + i] = v[i];
   if (tid == 0) rp[Nc] = total;
 
@@ -343,8 +240,8 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
   auto wanted = [&](int len) {
     int w = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w += slots_wanted(deg[i], len);
-    return block_sum(w, wsum, tid);
+    for (int i = 0; i < PT; ++i) w += slots_wanted(deg[i], len);
+    return block_sum<NT>(w, wsum, tid);
   };
   int seg = seg_min;
   if (wanted(seg) > cap) {
@@ -356,55 +253,55 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
     seg = hi;
   }
   // which lists are split, and into how many runs
-  int nseg[4], slot[4], rank[4];
+  int nseg[PT], slot[PT], rank[PT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < PT; ++i) {
     nseg[i] = split_runs(deg[i], seg);
     slot[i] = nseg[i] > 1 ? nseg[i] : 0;
   }
-  block_scan4(slot, wsum, tid);
+  block_scan<PT, NT>(slot, wsum, tid);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < PT; ++i) {
     if (nseg[i] > 1 && !split_granted(nseg[i], slot[i], cap)) nseg[i] = 1;
     rank[i] = nseg[i] > 1 ? 1 : 0;
   }
-  const int nsplit = block_scan4(rank, wsum, tid);
+  const int nsplit = block_scan<PT, NT>(rank, wsum, tid);
   int4* sp = (int4*)split + (long long)bh * (cap / 2 + 1);
   if (tid == 0) sp[0] = make_int4(nsplit, 0, 0, 0);
-  int extra[4];
+  int extra[PT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < PT; ++i) {
     if (nseg[i] > 1) sp[1 + rank[i]] = make_int4(j0 + i, slot[i], nseg[i], 0);
     extra[i] = nseg[i] - 1;
   }
-  const int items = Nc + block_scan4(extra, wsum, tid);
+  const int items = Nc + block_scan<PT, NT>(extra, wsum, tid);
 
   // counting sort of the items by length, descending
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < PT; ++i)
     if (j0 + i < Nc)
       for (int r = 0; r < nseg[i]; ++r) {
         const int len = run_bound(deg[i], nseg[i], r + 1) - run_bound(deg[i], nseg[i], r);
-        atomicAdd(&hist[min(Nc - len, kMaxCubes - 1)], 1);
+        atomicAdd(&hist[min(Nc - len, PT * NT - 1)], 1);
       }
   __syncthreads();
-  int first[4];
+  int first[PT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) first[i] = hist[j0 + i];
-  block_scan4(first, wsum, tid);
+  for (int i = 0; i < PT; ++i) first[i] = hist[j0 + i];
+  block_scan<PT, NT>(first, wsum, tid);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) hist[j0 + i] = first[i];
+  for (int i = 0; i < PT; ++i) hist[j0 + i] = first[i];
   __syncthreads();
   int4* ord = (int4*)order + (long long)bh * (Nc + cap);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < PT; ++i)
     if (j0 + i < Nc)
       for (int r = 0; r < nseg[i]; ++r) {
         const int lo = run_bound(deg[i], nseg[i], r), hi = run_bound(deg[i], nseg[i], r + 1);
-        ord[atomicAdd(&hist[min(Nc - (hi - lo), kMaxCubes - 1)], 1)] =
+        ord[atomicAdd(&hist[min(Nc - (hi - lo), PT * NT - 1)], 1)] =
             make_int4(j0 + i, v[i] + lo, v[i] + hi, nseg[i] > 1 ? slot[i] + r : -1);
       }
-  for (int e = items + tid; e < Nc + cap; e += 1024) ord[e] = make_int4(-1, 0, 0, -1);
+  for (int e = items + tid; e < Nc + cap; e += NT) ord[e] = make_int4(-1, 0, 0, -1);
 }
 
 __global__ __launch_bounds__(1024) void k_map_scan(int Nc, int seg_min, int cap, int32_t* __restrict__ row_ptr,
@@ -416,7 +313,7 @@ __global__ __launch_bounds__(1024) void k_map_scan(int Nc, int seg_min, int cap,
   int deg[4], v[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) deg[i] = (4 * tid + i < Nc) ? rp[4 * tid + i] : 0;
-  map_scan_body(Nc, seg_min, cap, bh, tid, deg, v, row_ptr, order, split, wsum, hist);
+  map_scan_body<4, 1024>(Nc, seg_min, cap, bh, tid, deg, v, row_ptr, order, split, wsum, hist);
 }
 
 // the list of key cube j: positions of the set bits of its row `r` (W32 words, global memory or LDS),
@@ -501,57 +398,50 @@ __global__ __launch_bounds__(256) void k_map_fill_sub(int Nc, int W32, long long
   }
 }
 
-// The whole map of one (b, h) in ONE launch, for short sequences (the bit matrix of a (b, h) fits in LDS
-// up to kMapOneLaunchMaxCubes key cubes): the four steps above by the 1024 threads of one workgroup --
-// bits OR-ed into LDS, in-degrees, scan and work items, lists -- instead of four launches.
-constexpr int kMapOneLaunchMaxCubes = 384;  // (measured: ahead of the four launches up to here, level at 512)
-__global__ __launch_bounds__(1024) void k_map_one_launch(int Nc, int K, int W32, int seg_min, int cap,
-                                                         const int32_t* __restrict__ idx, int32_t* __restrict__ row_ptr,
-                                                         int32_t* __restrict__ col, long long col_stride,
-                                                         int32_t* __restrict__ order, int32_t* __restrict__ split) {
-  __shared__ uint32_t bits_l[kMapOneLaunchMaxCubes * (kMapOneLaunchMaxCubes / 32 + 1)];
+// The whole map of one (b, h) by ONE workgroup, for short sequences (the bit matrix of a (b, h) fits in LDS up to
+// kMapOneMaxCubes key cubes): the four steps above -- bits OR-ed into LDS, in-degrees, scan and work items, lists --
+// with barriers between them instead of launches.  It needs nothing but the index lists, so it shares the launch
+// of the preprocess pass, whose first B*H workgroups do it.
+constexpr int kMapOneMaxCubes = 384;
+constexpr int kPreThreads = 512;
+struct MapOneLds {
+  uint32_t bits[kMapOneMaxCubes * (kMapOneMaxCubes / 32 + 1)];
+  int start[kPreThreads], hist[kPreThreads];
+  int wsum[kPreThreads / 64];
+};
+static_assert(kMapOneMaxCubes <= kPreThreads, "a cube per thread");
+__device__ __forceinline__ void map_one(MapOneLds& l, const MapArgs& a, int bh, int tid) {
+  const int Nc = a.Nc, K = a.K, W32 = (Nc + 31) / 32;
   const int WS = W32 | 1;  // odd row stride: the rows the OR step and the count step touch together fall into different banks
-  __shared__ int deg_l[kMaxCubes], start_l[kMaxCubes];
-  __shared__ int wsum[16];
-  __shared__ int hist[kMaxCubes];
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  for (int i = tid; i < Nc * WS; i += 1024) bits_l[i] = 0u;
+  for (int i = tid; i < Nc * WS; i += kPreThreads) l.bits[i] = 0u;
   __syncthreads();
-  const int32_t* my = idx + (long long)bh * Nc * K;
-  for (int e0 = tid; e0 < Nc * K; e0 += 8 * 1024) {  // (eight loads in flight per thread, then their bits)
+  const int32_t* my = a.idx + (long long)bh * Nc * K;
+  for (int e0 = tid; e0 < Nc * K; e0 += 8 * kPreThreads) {  // (eight loads in flight per thread, then their bits)
     int c[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) c[u] = e0 + u * 1024 < Nc * K ? my[e0 + u * 1024] : -1;
+    for (int u = 0; u < 8; ++u) c[u] = e0 + u * kPreThreads < Nc * K ? my[e0 + u * kPreThreads] : -1;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int q = (e0 + u * 1024) / K;
-      if (map_takes(c[u], Nc)) atomicOr(&bits_l[c[u] * WS + (q >> 5)], 1u << (q & 31));  // (a caller-supplied list is not trusted)
+      const int q = (e0 + u * kPreThreads) / K;
+      if (map_takes(c[u], Nc)) atomicOr(&l.bits[c[u] * WS + (q >> 5)], 1u << (q & 31));  // (a caller-supplied list is not trusted)
     }
   }
   __syncthreads();
-  for (int j = tid; j < kMaxCubes; j += 1024) {
-    int c = 0;
-    if (j < Nc)
-      for (int w = 0; w < W32; ++w) c += __popc(bits_l[j * WS + w]);
-    deg_l[j] = c;
-  }
-  __syncthreads();
-  int deg[4], v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) deg[i] = deg_l[4 * tid + i];
-  map_scan_body(Nc, seg_min, cap, bh, tid, deg, v, row_ptr, order, split, wsum, hist);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) start_l[4 * tid + i] = v[i];
+  int deg[1] = {0}, v[1];
+  if (tid < Nc)
+    for (int w = 0; w < W32; ++w) deg[0] += __popc(l.bits[tid * WS + w]);
+  map_scan_body<1, kPreThreads>(Nc, a.seg, a.cap, bh, tid, deg, v, a.row_ptr, a.order, a.split, l.wsum, l.hist);
+  l.start[tid] = v[0];
   __syncthreads();
   // lists: one thread per word of the bit matrix (a row has at most 12 words here, so the count of the
   // bits before a word is a short loop over LDS)
-  int32_t* cl = col + bh * col_stride;
-  for (int i = tid; i < Nc * W32; i += 1024) {
+  int32_t* cl = a.col + bh * ((long long)Nc * K);
+  for (int i = tid; i < Nc * W32; i += kPreThreads) {
     const int j = i / W32, w = i - j * W32;
-    uint32_t word = bits_l[j * WS + w];
+    uint32_t word = l.bits[j * WS + w];
     if (!word) continue;
-    int pos = start_l[j];
-    for (int x = 0; x < w; ++x) pos += __popc(bits_l[j * WS + x]);
+    int pos = l.start[j];
+    for (int x = 0; x < w; ++x) pos += __popc(l.bits[j * WS + x]);
     while (word) {
       cl[pos++] = w * 32 + __ffs(word) - 1;
       word &= word - 1;
@@ -559,9 +449,139 @@ __global__ __launch_bounds__(1024) void k_map_one_launch(int Nc, int K, int W32,
   }
 }
 
-hipError_t launch_transpose_map(int BH, int Nc, int K, const int32_t* idx, uint32_t* bits, int32_t* row_ptr,
-                                int32_t* col, int32_t* order, int32_t* split, int seg, int cap, int key_cubes_16,
-                                hipStream_t s) {
+// ---------------------------------------------------------------------------------------------
+// Preprocess.  Per token i of cube c (pad rows produce zeros):
+//   dGc_i = dO_i * Oc[c]      dGf_i = dO_i * Of_i      dOf_i = dO_i * Gf_i  (bf16, feeds the MFMAs)
+//   Delta_i = sum_d dOf_i * Of_i                       dOc[c] = sum_i dO_i * Gc_i
+//   rowd   per 32 rows: 32 values of -lse_i * log2(e) / sl2 (so that P = exp2((S + value) * sl2); -30000 on
+//          pad rows, where P then underflows to 0), then 32 values of -Delta_i
+// 256 threads per (b*h, cube), which walk the cube's m blocks of 64 rows; thread layout as in the
+// pooling kernel.  Bound by its seven tensors' traffic (39936 tokens, 12 heads: 0.86 GB in 137 us).
+// The first `map_blocks` workgroups transpose the block map instead: a serial chain of short steps that keeps B*H
+// CUs busy for 11 to 40 us and used to be a launch of its own.  Train step, own launch -> shared: 32 blocks 65 -> 55 us;
+// 256 blocks, 12 heads 1044 -> 1035, d = 64, 16 heads 795 -> 783; 280 blocks, 5 heads, through the op 562 -> 548.
+// (Workgroups of 256 threads: 57 and, for the last, whose map is then the longer part, 555; of 1024: 57 and 544, but
+// 788 for the one before.)
+template <int D>
+__global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs map_args, unsigned cubes, int Nc, int m_blocks, const uint64_t* __restrict__ mask, const uint4* __restrict__ dout,
+                                                 const uint4* __restrict__ gc, const uint4* __restrict__ gf,
+                                                 const uint4* __restrict__ of, const float* __restrict__ oc,
+                                                 uint4* __restrict__ dgc, uint4* __restrict__ dgf,
+                                                 uint4* __restrict__ dof, float* __restrict__ rowd, float inv_sl2,
+                                                 float* __restrict__ doc,
+                                                 const float* __restrict__ lse_f, int H, long long do_head_stride,
+                                                 long long do_row_stride) {
+  constexpr int CPR = D / 8, RG = 256 / CPR, RPT = kTile / RG;
+  __shared__ union {
+    float part[kPreThreads / 256][RG][D + 4];
+    MapOneLds map;
+  } lds;
+  if ((int)blockIdx.x < map_blocks) {  // (uniform) the transposed map of one (b, h)
+    map_one(lds.map, map_args, blockIdx.x, threadIdx.x);
+    return;
+  }
+  // two cubes a workgroup, 256 threads each
+  const int tid = threadIdx.x & 255;
+  auto& part = lds.part[threadIdx.x >> 8];
+  const unsigned at = (blockIdx.x - map_blocks) * (kPreThreads / 256) + (threadIdx.x >> 8), cube = min(at, cubes - 1);
+  const bool live = at < cubes;  // (the last workgroup's spare threads store nothing)
+  const int c = cube % Nc;
+  const long long bh = cube / Nc;
+  const int ch = tid % CPR, rg = tid / CPR;
+  float ocv[8];
+  {
+    const float* p = oc + (bh * Nc + c) * D + ch * 8;
+    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
+    ocv[0] = a.x; ocv[1] = a.y; ocv[2] = a.z; ocv[3] = a.w; ocv[4] = b.x; ocv[5] = b.y; ocv[6] = b.z; ocv[7] = b.w;
+  }
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int sb = 0; sb < (live ? m_blocks : 0); ++sb) {
+  const long long blk = (bh * Nc + c) * m_blocks + sb;  // block index over all (b, h)
+  const uint64_t m = mask[c * m_blocks + sb];
+  const long long row0 = blk * (long long)kTile;
+  // dout may be head-major [B,H,Np,D] or token-major [B,Np,H,D] (see the forward's `out`)
+  const long long Npad = (long long)Nc * m_blocks * kTile;
+  const long long do0 = (bh / H) * ((long long)H * Npad * CPR) + (bh % H) * do_head_stride +
+                        ((long long)c * m_blocks + sb) * kTile * do_row_stride;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int r = rg + i * RG;
+    const long long g = (row0 + r) * CPR + ch;
+    const bool valid = (m >> r) & 1;
+    uint4 z = make_uint4(0, 0, 0, 0), o_gc = z, o_gf = z, o_dof = z;
+    float dsum = 0.f;
+    if (valid) {
+      float go[8], gcv[8], gfv[8], ofv[8], t0[8], t1[8], t2[8];
+      unpack8(dout[do0 + r * do_row_stride + ch], go);
+      unpack8(gc[g], gcv);
+      unpack8(of[g], ofv);
+      if (gf) unpack8(gf[g], gfv);
+      else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gfv[e] = 1.f;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        t0[e] = go[e] * ocv[e];
+        t1[e] = go[e] * ofv[e];
+        t2[e] = go[e] * gfv[e];
+        acc[e] += go[e] * gcv[e];
+      }
+      o_gc = pack8(t0); o_gf = pack8(t1); o_dof = pack8(t2);
+      float t2r[8];
+      unpack8(o_dof, t2r);  // Delta uses the rounded dOf, the value the fine kernels multiply with
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dsum = fmaf(t2r[e], ofv[e], dsum);
+    }
+    dgc[g] = o_gc;
+    if (dgf) dgf[g] = o_gf;
+    dof[g] = o_dof;
+#pragma unroll
+    for (int o = CPR / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
+    if (ch == 0) {
+      float* p = rowd + 2 * (row0 + (r & ~31)) + (r & 31);
+      p[0] = valid ? -lse_f[row0 + r] * kLog2e * inv_sl2 : -30000.f;
+      p[32] = -dsum;
+    }
+  }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) part[rg][ch * 8 + e] = acc[e];
+  __syncthreads();
+  if (tid < D && live) {
+    float s = 0;
+    for (int r = 0; r < RG; ++r) s += part[r][tid];
+    doc[(bh * Nc + c) * D + tid] = s;
+  }
+}
+
+hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
+                          const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
+                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
+                          int dout_token_major, const MapArgs* map, hipStream_t s) {
+  const MapArgs m = map ? *map : MapArgs{};
+  const int mb = map ? BH : 0;  // workgroups that transpose the map, ahead of the others
+  const unsigned cubes = (unsigned)(BH * Nc), per = kPreThreads / 256, grid = (cubes + per - 1) / per + (unsigned)mb;
+  const float inv_sl2 = 1.0f / (scale * kLog2e);
+  const long long cpr = d / 8, Np = (long long)Nc * m_blocks * kTile;
+  const long long dhs = dout_token_major ? cpr : Np * cpr, drs = dout_token_major ? H * cpr : cpr;
+  if (d == 128)
+    k_bwd_pre<128><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
+                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
+                                        inv_sl2, doc, lse_f, H, dhs, drs);
+  else
+    k_bwd_pre<64><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
+                                       (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
+                                       inv_sl2, doc, lse_f, H, dhs, drs);
+  return hipGetLastError();
+}
+
+bool map_with_bwd_pre(int Nc, int key_cubes_16) { return !key_cubes_16 && Nc <= kMapOneMaxCubes; }
+
+hipError_t launch_transpose_map(int BH, const MapArgs& a, uint32_t* bits, int key_cubes_16, hipStream_t s) {
+  const int Nc = a.Nc, K = a.K, seg = a.seg, cap = a.cap;
+  const int32_t* idx = a.idx;
+  int32_t *row_ptr = a.row_ptr, *col = a.col, *order = a.order, *split = a.split;
   const int W32 = (Nc + 31) / 32;
   const long long rows = (long long)BH * Nc;
   hipError_t e;
@@ -573,10 +593,6 @@ hipError_t launch_transpose_map(int BH, int Nc, int K, const int32_t* idx, uint3
     k_map_scan<<<BH, 1024, 0, s>>>(Nc, seg, cap, row_ptr, order, split);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_map_fill_sub<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(Nc, W32, rows, bits, row_ptr, col, (long long)Nc * K);
-    return hipGetLastError();
-  }
-  if (Nc <= kMapOneLaunchMaxCubes) {
-    k_map_one_launch<<<BH, 1024, 0, s>>>(Nc, K, W32, seg, cap, idx, row_ptr, col, (long long)Nc * K, order, split);
     return hipGetLastError();
   }
   k_map_bits<<<(unsigned)(BH * W32), 256, 0, s>>>(Nc, Nc, K, W32, idx, bits);

@@ -368,10 +368,6 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
     VSA_TRY("pool", vsa::launch_pool(g, BH, p->d, w.mask, q, k, v, w.qc, w.kc, w.vc, sub ? 1 : 3, s));
     if (sub) VSA_TRY("pool", vsa::launch_pool_keys16(BH, g.Nc, p->d, w.mask, w.kcnt, k, v, w.kc, w.vc, s));
   }
-  VSA_TRY("bwd_pre", vsa::launch_bwd_pre(BH, g.Nc, g.m, p->d, w.mask, dout, gate_c, gate_f, out_fine, out_coarse, dgate_c, dgate_f,
-                              w.dof, w.rowd, scale, w.doc, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, s));
-  VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, w.ac, w.dsc,
-                                 w.dqc, w.dkc, w.dvc, w.kcnt, s));
   const int32_t* lists = block_idx;
   const int kb = p->topk * blocks_per_entry(p, g);
   if (pooled_select(p)) {
@@ -381,7 +377,13 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
     VSA_TRY("expand_lists", vsa::launch_expand_lists(BH, g.Nc, p->topk, g.m, block_idx, w.idx_blocks, s));
     lists = w.idx_blocks;
   }
-  VSA_TRY("transpose_map", vsa::launch_transpose_map(BH, g.Nb, kb, lists, w.bits, w.row_ptr, w.col, w.order, w.split, w.seg, w.cap, sub ? 1 : 0, s));
+  const vsa::MapArgs map = {g.Nb, kb, w.seg, w.cap, lists, w.row_ptr, w.col, w.order, w.split};
+  const bool map_aside = vsa::map_with_bwd_pre(g.Nb, sub ? 1 : 0);
+  VSA_TRY("bwd_pre", vsa::launch_bwd_pre(BH, g.Nc, g.m, p->d, w.mask, dout, gate_c, gate_f, out_fine, out_coarse, dgate_c, dgate_f,
+                              w.dof, w.rowd, scale, w.doc, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, map_aside ? &map : nullptr, s));
+  VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, w.ac, w.dsc,
+                                 w.dqc, w.dkc, w.dvc, w.kcnt, s));
+  if (!map_aside) VSA_TRY("transpose_map", vsa::launch_transpose_map(BH, map, w.bits, sub ? 1 : 0, s));
   VSA_TRY("fine_bwd_dq", vsa::launch_fine_bwd_dq(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.rowd,
                                   w.dqc, w.mask, dq, g.m, sub ? 1 : 0, s));
   VSA_TRY("fine_bwd_dkv", vsa::launch_fine_bwd_dkv(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, w.col, w.order, w.split, w.parts,

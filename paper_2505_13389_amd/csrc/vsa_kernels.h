@@ -34,16 +34,23 @@ hipError_t launch_expand_tiles(int BH, int Nt, int Nh, int Nw, int K, const int3
 hipError_t launch_expand_lists(int BH, int Nc, int K, int m, const int32_t* idx, int32_t* idx_blocks, hipStream_t s);
 
 // backward
+// The transposed block map of lists of K blocks (or, with key cubes of 16 tokens, key cubes) per query block:
+// Nc blocks per (b, h); see split_plan for seg and cap.
+struct MapArgs {
+  int Nc, K, seg, cap;
+  const int32_t* idx;
+  int32_t *row_ptr, *col, *order, *split;
+};
+// whether launch_bwd_pre transposes the map on the side (`map` given) or launch_transpose_map has to
+bool map_with_bwd_pre(int Nc, int key_cubes_16);
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
                           void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
-                          int dout_token_major, hipStream_t s);
+                          int dout_token_major, const MapArgs* map, hipStream_t s);
 hipError_t launch_coarse_bwd(int BH, int Nq, int Nk, int d, float scale, const float* qc, const float* kc,
                              const float* vc, const float* lse_c, const float* doc, float* ac, float* dsc, float* dqc,
                              float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s);
-hipError_t launch_transpose_map(int BH, int Nc, int K, const int32_t* idx, uint32_t* bits, int32_t* row_ptr,
-                                int32_t* col, int32_t* order, int32_t* split, int seg, int cap, int key_cubes_16,
-                                hipStream_t s);
+hipError_t launch_transpose_map(int BH, const MapArgs& a, uint32_t* bits, int key_cubes_16, hipStream_t s);
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,

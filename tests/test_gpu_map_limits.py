@@ -1,0 +1,37 @@
+"""The transposed block map on both sides of the limit below which it shares the preprocess launch (384 blocks), with
+lists that name a few key blocks very often (split lists) and some never."""
+import numpy as np
+import pytest
+
+from helpers import assert_close, bf16_to_np, grid_of, problem_of, tiled_bits, to_dev, widen
+from oracle import vsa_oracle as orc
+from paper_2505_13389_amd.synth import Workload
+from test_gpu_dkv_units import lists_of_spread_degrees
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("grid,blocks", [((4, 4, 7), 2), ((23, 32, 30), 384), ((20, 27, 44), 385)])
+def test_map_on_both_sides_of_the_limit(grid, blocks):
+    import torch
+    from paper_2505_13389_amd import vsa
+    K = min(5, blocks)
+    wl = Workload("map_limit", 1, 3, *grid, 64, K)  # an odd number of cubes in all: the last workgroup has a spare half
+    g = grid_of(wl)
+    assert g.Nc == blocks
+    bits = tiled_bits(wl, seed=blocks, pad_garbage=True)
+    x, dev = widen(bits), to_dev(bits)
+    if blocks > 8:
+        idx = lists_of_spread_degrees(np.random.default_rng(blocks), 3, g.Nc, K)
+    else:
+        idx = np.tile(np.arange(K, dtype=np.int32), (1, 3, g.Nc, 1))
+    ref = orc.backward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], x["dout"], idx, K, real="f32")
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(*a, indices_given=True)
+    buf.workspace[vsa.vsa_workspace_bytes(problem_of(wl), False):].fill_(0xFF)  # nothing of the backward's part is kept
+    buf.backward(*a, dev["dout"])
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv", "dgate_c", "dgate_f"):
+        assert_close(bf16_to_np(getattr(buf, n)), ref[n], n)

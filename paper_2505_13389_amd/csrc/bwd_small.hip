@@ -82,11 +82,126 @@ __global__ __launch_bounds__(256) void k_coarse_softmax_bwd(int rows, int Nc, co
   for (int j = lane; j < Nc; j += 64) ds[j] = s[j] * (ds[j] - dot);
 }
 
+// The whole coarse backward in ONE launch.  With dot[q] = dOc[q] . Oc[q] (= sum_j Ac dAc, left by the preprocess pass)
+// nothing couples the columns of a row any more, so every product can be formed where it is used, from either side:
+//   query side, 16 query cubes:  A, dS [16 x Nc] -> dQc = scale dS Kc
+//   key side, 16 key cubes:      A^T, dS^T [16 x Nc] -> dVc = A^T dOc, dKc = scale dS^T Qc
+// with A = exp(scale Qc Kc^T - lse), dS = A (dOc Vc^T - dot): nothing but the gradients goes to memory.  One
+// workgroup of 16 wavefronts per 16 cubes and side walks the other side in chunks of 256 cubes: one 16 x 16 block of both
+// products per wavefront (v_mfma_f32_16x16x4_f32: fp32 products and sums), A and dS into LDS, then their products with
+// the other side's tensors, 16 columns per wavefront, the wavefronts left over splitting the contraction (partial
+// sums added in a fixed order).  Operands come straight from L2 (see k_coarse_fused for the relabelling of k).
+// Bound by latency (two dependent chains of L2 loads and matrix instructions per chunk).  Measured against three
+// launches through [Nc x Nc] matrices in memory, us: 32 cubes, 2 heads, d = 64: 14.8 -> 7.4 (train step 56 -> 49); 64 cubes,
+// 12 heads, d = 128: 19.7 -> 12.1; 280 cubes, 5 heads: 33 -> 26; 256 cubes, 16 heads, d = 64: 31 -> 24; 256 cubes, 12 heads,
+// d = 128: 38 -> 40; 32 heads: 56 -> 79; 480 cubes, 16 heads: 100 -> 150; 624, 12 heads: 117 -> 178 -- the staged
+// 64 x 64 tiles of the launches read every operand four times less often, which is what counts once the chip is full.
+typedef float f32x4c __attribute__((ext_vector_type(4)));
+constexpr long long kCoarseBwdOneMax = 80ll << 20;  // multiply-adds of one product, all heads
+template <int D>
+__global__ __launch_bounds__(1024) void k_coarse_bwd_one(int Nc, float scale, const float* __restrict__ qc,
+                                                         const float* __restrict__ kc, const float* __restrict__ vc,
+                                                         const float* __restrict__ doc, const float* __restrict__ lse_c,
+                                                         const float* __restrict__ dot, float* __restrict__ dqc,
+                                                         float* __restrict__ dkc, float* __restrict__ dvc) {
+  constexpr int R = 16, CH = 256, ROW = CH + 4, OWN = D + 4;  // (rows start 4 banks apart)
+  constexpr int CB = D / 16;  // 16-column blocks of an output
+  __shared__ __attribute__((aligned(16))) float A[R * ROW], G[R * ROW];
+  __shared__ __attribute__((aligned(16))) float X[R * OWN], Y[R * OWN];
+  __shared__ __attribute__((aligned(16))) float part[16][64][4];
+  const int blocks = (Nc + R - 1) / R;
+  const bool keys = blockIdx.x & 1;  // which side
+  const int m0 = (int)((blockIdx.x >> 1) % blocks) * R;
+  const long long bh = (blockIdx.x >> 1) / blocks, first = bh * Nc;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int rows_valid = min(R, Nc - m0);
+  const float *own_x = (keys ? kc : qc) + (first + m0) * D, *own_y = (keys ? vc : doc) + (first + m0) * D;
+  const float *oth_p = (keys ? qc : kc) + first * D, *oth_r = (keys ? doc : vc) + first * D;
+  for (int i = tid; i < R * D; i += 1024) {
+    const int r = i / D, e = i % D;
+    X[r * OWN + e] = r < rows_valid ? own_x[i] : 0.f;
+    Y[r * OWN + e] = r < rows_valid ? own_y[i] : 0.f;
+  }
+  // the outputs' blocks: query side dQc, 16 / CB wavefronts a block; key side the first 8 wavefronts dKc, the last dVc
+  const int per_out = keys ? 8 : 16, ksplit = per_out / CB;
+  const int ow = wave % per_out, cb = ow % CB, ks = ow / CB;
+  const bool second = wave >= per_out;
+  const float* M = second ? A : G;
+  const float* col = (second ? oth_r : oth_p) + cb * 16 + l16;
+  f32x4c out = {0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < Nc; c0 += CH) {
+    __syncthreads();  // own rows are there; A and G of the chunk before have been read
+    const int n = c0 + wave * 16 + l16;
+    if (c0 + wave * 16 < ((Nc + 15) & ~15)) {
+      const long long at = (long long)min(n, Nc - 1) * D + 4 * kq;
+      f32x4c s = {0.f, 0.f, 0.f, 0.f}, da = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k0 = 0; k0 < D; k0 += 16) {
+        const float4 x = *(const float4*)&X[l16 * OWN + k0 + 4 * kq], y = *(const float4*)&Y[l16 * OWN + k0 + 4 * kq];
+        const float4 p = *(const float4*)(oth_p + at + k0), r = *(const float4*)(oth_r + at + k0);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, p.x, s, 0, 0, 0);
+        da = __builtin_amdgcn_mfma_f32_16x16x4f32(y.x, r.x, da, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, p.y, s, 0, 0, 0);
+        da = __builtin_amdgcn_mfma_f32_16x16x4f32(y.y, r.y, da, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, p.z, s, 0, 0, 0);
+        da = __builtin_amdgcn_mfma_f32_16x16x4f32(y.z, r.z, da, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, p.w, s, 0, 0, 0);
+        da = __builtin_amdgcn_mfma_f32_16x16x4f32(y.w, r.w, da, 0, 0, 0);
+      }
+      // lane: rows 4*kq + i, column n; the row terms belong to the query cube
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = 4 * kq + i;
+        const long long qrow = first + (keys ? min(n, Nc - 1) : min(m0 + m, Nc - 1));
+        const float a = n < Nc ? fast_exp2((scale * s[i] - lse_c[qrow]) * kLog2e) : 0.f;
+        A[m * ROW + wave * 16 + l16] = a;
+        G[m * ROW + wave * 16 + l16] = a * (da[i] - dot[qrow]);
+      }
+    }
+    __syncthreads();
+    const int kend = min(CH, ((Nc + 15) & ~15) - c0);
+    for (int k0 = ks * 16; k0 < kend; k0 += 16 * ksplit) {
+      const float4 a = *(const float4*)&M[l16 * ROW + k0 + 4 * kq];
+      const int kk = c0 + k0 + 4 * kq;
+      float b[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = col[(long long)min(kk + j, Nc - 1) * D];  // (past the end: times zero)
+      out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[0], out, 0, 0, 0);
+      out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[1], out, 0, 0, 0);
+      out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[2], out, 0, 0, 0);
+      out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[3], out, 0, 0, 0);
+    }
+  }
+  *(float4*)part[wave][lane] = make_float4(out[0], out[1], out[2], out[3]);
+  __syncthreads();
+  if (ks == 0) {
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < ksplit; ++o) {
+      const float4 x = *(const float4*)part[wave + o * CB][lane];
+      sum[0] += x.x; sum[1] += x.y; sum[2] += x.z; sum[3] += x.w;
+    }
+    float* dst = second ? dvc : (keys ? dkc : dqc);
+    const float mul = second ? 1.f : scale;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = 4 * kq + i;
+      if (m < rows_valid) dst[(first + m0 + m) * D + cb * 16 + l16] = mul * sum[i];
+    }
+  }
+}
+
 // Coarse backward: dVc = Ac^T dOc, dQc = scale dSc Kc, dKc = scale dSc^T Qc, for Nq query cubes and Nk
-// key cubes (see launch_coarse).  `ac` and `dsc` are [BH,Nq,Nk] scratch.
+// key cubes (see launch_coarse).  `ac` and `dsc` are [BH,Nq,Nk] scratch, `dot` as the preprocess pass leaves it.
 hipError_t launch_coarse_bwd(int BH, int Nq, int Nk, int d, float scale, const float* qc, const float* kc,
-                             const float* vc, const float* lse_c, const float* doc, float* ac, float* dsc, float* dqc,
-                             float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s) {
+                             const float* vc, const float* lse_c, const float* doc, const float* dot, float* ac,
+                             float* dsc, float* dqc, float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s) {
+  if (Nq == Nk && !kcnt && (long long)BH * Nq * Nk * d <= kCoarseBwdOneMax) {
+    const unsigned grid = 2u * (unsigned)(BH * ((Nq + 15) / 16));
+    if (d == 128) k_coarse_bwd_one<128><<<grid, 1024, 0, s>>>(Nq, scale, qc, kc, vc, doc, lse_c, dot, dqc, dkc, dvc);
+    else k_coarse_bwd_one<64><<<grid, 1024, 0, s>>>(Nq, scale, qc, kc, vc, doc, lse_c, dot, dqc, dkc, dvc);
+    return hipGetLastError();
+  }
   const long long sq = (long long)Nq * d, sk = (long long)Nk * d, ss = (long long)Nq * Nk;
   hipError_t e;
   GemmSet set;
@@ -452,7 +567,7 @@ __device__ __forceinline__ void map_one(MapOneLds& l, const MapArgs& a, int bh, 
 // ---------------------------------------------------------------------------------------------
 // Preprocess.  Per token i of cube c (pad rows produce zeros):
 //   dGc_i = dO_i * Oc[c]      dGf_i = dO_i * Of_i      dOf_i = dO_i * Gf_i  (bf16, feeds the MFMAs)
-//   Delta_i = sum_d dOf_i * Of_i                       dOc[c] = sum_i dO_i * Gc_i
+//   Delta_i = sum_d dOf_i * Of_i                       dOc[c] = sum_i dO_i * Gc_i   dot[c] = dOc[c] . Oc[c]
 //   rowd   per 32 rows: 32 values of -lse_i * log2(e) / sl2 (so that P = exp2((S + value) * sl2); -30000 on
 //          pad rows, where P then underflows to 0), then 32 values of -Delta_i
 // 256 threads per (b*h, cube), which walk the cube's m blocks of 64 rows; thread layout as in the
@@ -468,7 +583,7 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
                                                  const uint4* __restrict__ of, const float* __restrict__ oc,
                                                  uint4* __restrict__ dgc, uint4* __restrict__ dgf,
                                                  uint4* __restrict__ dof, float* __restrict__ rowd, float inv_sl2,
-                                                 float* __restrict__ doc,
+                                                 float* __restrict__ doc, float* __restrict__ dot,
                                                  const float* __restrict__ lse_f, int H, long long do_head_stride,
                                                  long long do_row_stride) {
   constexpr int CPR = D / 8, RG = 256 / CPR, RPT = kTile / RG;
@@ -548,16 +663,24 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
 #pragma unroll
   for (int e = 0; e < 8; ++e) part[rg][ch * 8 + e] = acc[e];
   __syncthreads();
-  if (tid < D && live) {
-    float s = 0;
-    for (int r = 0; r < RG; ++r) s += part[r][tid];
-    doc[(bh * Nc + c) * D + tid] = s;
+  if (tid < 64 && live) {  // one wavefront: its lanes take columns lane and, at d = 128, lane + 64
+    float dsum = 0.f;
+#pragma unroll
+    for (int e = tid; e < D; e += 64) {
+      float s = 0;
+      for (int r = 0; r < RG; ++r) s += part[r][e];
+      doc[(bh * Nc + c) * D + e] = s;
+      dsum = fmaf(s, oc[(bh * Nc + c) * D + e], dsum);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
+    if (tid == 0) dot[bh * Nc + c] = dsum;
   }
 }
 
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
-                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
+                          void* dof, float* rowd, float scale, float* doc, float* dot, const float* lse_f, int H,
                           int dout_token_major, const MapArgs* map, hipStream_t s) {
   const MapArgs m = map ? *map : MapArgs{};
   const int mb = map ? BH : 0;  // workgroups that transpose the map, ahead of the others
@@ -568,11 +691,11 @@ hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* m
   if (d == 128)
     k_bwd_pre<128><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
                                         (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                        inv_sl2, doc, lse_f, H, dhs, drs);
+                                        inv_sl2, doc, dot, lse_f, H, dhs, drs);
   else
     k_bwd_pre<64><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                       inv_sl2, doc, lse_f, H, dhs, drs);
+                                       inv_sl2, doc, dot, lse_f, H, dhs, drs);
   return hipGetLastError();
 }
 

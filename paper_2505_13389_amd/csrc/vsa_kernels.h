@@ -45,11 +45,11 @@ struct MapArgs {
 bool map_with_bwd_pre(int Nc, int key_cubes_16);
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
-                          void* dof, float* rowd, float scale, float* doc, const float* lse_f, int H,
+                          void* dof, float* rowd, float scale, float* doc, float* dot, const float* lse_f, int H,
                           int dout_token_major, const MapArgs* map, hipStream_t s);
 hipError_t launch_coarse_bwd(int BH, int Nq, int Nk, int d, float scale, const float* qc, const float* kc,
-                             const float* vc, const float* lse_c, const float* doc, float* ac, float* dsc, float* dqc,
-                             float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s);
+                             const float* vc, const float* lse_c, const float* doc, const float* dot, float* ac,
+                             float* dsc, float* dqc, float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s);
 hipError_t launch_transpose_map(int BH, const MapArgs& a, uint32_t* bits, int key_cubes_16, hipStream_t s);
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,

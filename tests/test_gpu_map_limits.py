@@ -1,5 +1,6 @@
 """The transposed block map on both sides of the limit below which it shares the preprocess launch (384 blocks), with
-lists that name a few key blocks very often (split lists) and some never."""
+lists that name a few key blocks very often (split lists) and some never.  These shapes also take the coarse backward
+in one launch, in one chunk of 256 cubes and in two."""
 import numpy as np
 import pytest
 
@@ -11,12 +12,13 @@ from test_gpu_dkv_units import lists_of_spread_degrees
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("grid,blocks", [((4, 4, 7), 2), ((23, 32, 30), 384), ((20, 27, 44), 385)])
-def test_map_on_both_sides_of_the_limit(grid, blocks):
+@pytest.mark.parametrize("grid,blocks,d", [((4, 4, 7), 2, 64), ((4, 4, 7), 2, 128), ((23, 32, 30), 384, 64),
+                                           ((23, 32, 30), 384, 128), ((20, 27, 44), 385, 64)])
+def test_map_on_both_sides_of_the_limit(grid, blocks, d):
     import torch
     from paper_2505_13389_amd import vsa
     K = min(5, blocks)
-    wl = Workload("map_limit", 1, 3, *grid, 64, K)  # an odd number of cubes in all: the last workgroup has a spare half
+    wl = Workload("map_limit", 1, 3, *grid, d, K)  # an odd number of cubes in all: the last workgroup has a spare half
     g = grid_of(wl)
     assert g.Nc == blocks
     bits = tiled_bits(wl, seed=blocks, pad_garbage=True)

@@ -367,8 +367,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
   }
 }
 
-// Up to this many query blocks, four wavefronts per workgroup (as in the forward).
-constexpr int kDqFourWaves = 256;
+// Up to this many query blocks, four wavefronts per workgroup, as in the forward.  (d = 64, top-33: 324 blocks 31.0 against
+// 46.3 us, 432 blocks 31.9 against 46.9; d = 128, 324 blocks 48.6 against 45.0.)
+template <int D>
+constexpr unsigned kDqFourWaves = D == 128 ? 256 : 512;
 
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
@@ -381,7 +383,7 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
                                                 (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks)
 #define VSA_DQ_NW(D_, LIST_)                        \
   do {                                              \
-    if (grid <= kDqFourWaves) VSA_DQ(D_, 4, LIST_); \
+    if (grid <= kDqFourWaves<D_>) VSA_DQ(D_, 4, LIST_); \
     else VSA_DQ(D_, 2, LIST_);                      \
   } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens

@@ -37,7 +37,7 @@ namespace vsa {
 
 constexpr float kTau = 60.f;            // lazy-rescale threshold, log2 units
 constexpr float kMaxSum = 1152921504606846976.f;  // 2^kTau
-constexpr float kNoRef = -1e30f;        // reference before the first valid key: every value then exceeds kMaxSum
+constexpr float kNoRef = -1e30f;        // below every reference
 
 // max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
 // round trip through the LDS permute path
@@ -211,7 +211,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     S[1] = mfma32(ab, ones_b, S[1]);
   };
 
-  float ref[2] = {kNoRef, kNoRef}, lsum[2] = {0.f, 0.f}, tsum[2] = {0.f, 0.f};
+  // references of the lane's two query columns; zero, and `have` false, until the first unit with a valid key
+  float ref[2] = {0.f, 0.f};
+  bool have = false;
+  float lsum[2] = {0.f, 0.f}, tsum[2] = {0.f, 0.f};
   uint4 pb[2][2];  // P^T of the current unit as operands: [query half][contraction step]
   auto put = [](uint4& u4, int w, uint32_t x) {
     if (w == 0) u4.x = x;
@@ -240,9 +243,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, S[i]), S[i + 1]);
     mx = max_across_halves(fmaxf(mx, S[15]));
     const float mx2 = mx * sl2;
-    return (mx > 0.5f * kMaskBias && mx2 > old + kTau) ? mx2 : old;  // (below: every key of this unit is a pad)
+    return mx2 > old + kTau ? mx2 : old;
   };
-  auto usable = [](float r) { return r == kNoRef ? 0.f : r; };
+  uint32_t valid = 0;  // valid keys of the current unit
 
   f32x16 zero16;
 #pragma unroll
@@ -261,8 +264,12 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (nu > 2) copy.all(kb, un[1], lds0);
 #pragma unroll
     for (int s = 0; s < kAhead; ++s) kcur[s] = TL::rowmajor_at(smem + HALF, lane_a, s);
-    ref[0] = new_ref(s0[0], kNoRef);
-    ref[1] = new_ref(s0[1], kNoRef);
+    valid = u0.valid;
+    if (valid) {
+      ref[0] = new_ref(s0[0], kNoRef);
+      ref[1] = new_ref(s0[1], kNoRef);
+      have = true;
+    }
     p_items(s0, 0, kEarly, ref);
   }
 
@@ -325,12 +332,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     }
     // The reference stays as long as no sum of this unit's 16 values exceeds 2^kTau: then no value does, and
     // the rescaling of O is skipped for almost every unit.  The result is exact either way.
-    if (__builtin_expect(__any(fmaxf(tsum[0], tsum[1]) > kMaxSum), 0)) {
+    // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
+    if (__builtin_expect((!have && valid) || __any(fmaxf(tsum[0], tsum[1]) > kMaxSum), 0)) {
       mfma_fence();
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const float mnew = new_ref(S[b], ref[b]);
-        const float alpha = fast_exp2(ref[b] - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
+        const float old = have ? ref[b] : kNoRef, mnew = new_ref(S[b], old);
+        const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
         lsum[b] *= alpha;
 #pragma unroll
         for (int x = 0; x < DVB; ++x) {
@@ -342,8 +350,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         }
         ref[b] = mnew;
       }
-      const float rf[2] = {usable(ref[0]), usable(ref[1])};
-      p_items(S, 0, 16, rf);
+      have = true;
+      p_items(S, 0, 16, ref);
       mfma_fence();
     }
     lsum[0] += tsum[0];
@@ -385,6 +393,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       if (more1) p_items(T, i1, i2, ref);
       __builtin_amdgcn_sched_barrier(0);
     }
+    valid = un[0].valid;
     un[0] = un[1];
     un[1] = un[2];
   };
@@ -442,7 +451,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
               make_float4(o[x][b][4 * g4], o[x][b][4 * g4 + 1], o[x][b][4 * g4 + 2], o[x][b][4 * g4 + 3]);
       const float l = lsum[b] + __shfl_xor(lsum[b], 32);
       if (h == 0) {
-        ml[(wave * 64 + b * 32 + l32) * 2] = ref[b] == kNoRef ? -INFINITY : ref[b];
+        ml[(wave * 64 + b * 32 + l32) * 2] = have ? ref[b] : -INFINITY;
         ml[(wave * 64 + b * 32 + l32) * 2 + 1] = l;
       }
     }
@@ -492,10 +501,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Up to this many query blocks, four wavefronts per workgroup: the launch does not fill the chip with
-// two-wavefront workgroups, and half as long a list walk counts.  (64 blocks, d = 64, top-8: 10.0
-// against 12.0 us; 256 to 512 blocks: level.)
-constexpr int kFwdFourWaves = 256;
+// Up to this many query blocks -- one workgroup of four wavefronts per CU at d = 128, two at d = 64 -- four
+// wavefronts per workgroup: the launch does not fill the chip with two-wavefront workgroups, and half as long a list
+// walk counts.  (d = 64: 64 blocks, top-8 10.0 against 12.0 us; 324 and 432 blocks, top-33 26.7 against 37.6 and 27.5
+// against 38.1, top-6 13.0 against 16.3; 648 blocks 36.6 against 39.9, but top-6 19.0 against 17.0.  d = 128: 324 blocks,
+// top-33 42.5 against 38.5.)
+template <int D>
+constexpr unsigned kFwdFourWaves = D == 128 ? 256 : 512;
 
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
@@ -526,7 +538,7 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
                                              (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, arrived, every)
 #define VSA_FWD_NW(D_, LIST_)                     \
   do {                                            \
-    if (grid <= kFwdFourWaves) VSA_FWD(D_, 4, LIST_); \
+    if (grid <= kFwdFourWaves<D_>) VSA_FWD(D_, 4, LIST_); \
     else VSA_FWD(D_, 2, LIST_);                   \
   } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens

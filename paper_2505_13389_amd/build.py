@@ -6,7 +6,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvsa.so")
-SOURCES = ["vsa_api.hip", "permute_pool.hip", "coarse.hip", "fine_fwd.hip", "bwd_small.hip", "fine_bwd.hip", "fine_bwd_dkv.hip"]
+SOURCES = ["vsa_api.hip", "permute_pool.hip", "coarse.hip", "fine_fwd.hip", "fine_fwd_short.hip", "bwd_small.hip", "fine_bwd.hip", "fine_bwd_dkv.hip"]
 # Packed-fp32 VALU forms are disabled on purpose (hipcc would otherwise emit them from plain float code).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
@@ -30,7 +30,7 @@ def _compile(src: str, extra) -> str:
 
 
 def build(extra_flags=()) -> str:
-    with ThreadPoolExecutor(max_workers=7) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     return LIB

@@ -506,6 +506,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 // walk counts.  (d = 64: 64 blocks, top-8 10.0 against 12.0 us; 324 and 432 blocks, top-33 26.7 against 37.6 and 27.5
 // against 38.1, top-6 13.0 against 16.3; 648 blocks 36.6 against 39.9, but top-6 19.0 against 17.0.  d = 128: 324 blocks,
 // top-33 42.5 against 38.5.)
+constexpr int kShortTiles = 12;
 template <int D>
 constexpr unsigned kFwdFourWaves = D == 128 ? 256 : 512;
 
@@ -515,6 +516,11 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
                            int m_blocks, int key_cubes_16, unsigned* gang_scratch, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
+  // Short walks, once there are enough workgroups for several generations: the kernel whose start-up and wind-down
+  // overlap (its header has both kernels' times).
+  if (grid > kFwdFourWaves<128> * 2 && (key_cubes_16 ? (K + 3) / 4 : K) <= kShortTiles)
+    return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
+                                 out_token_major, m_blocks, key_cubes_16, s);
   // Gangs where the K and V of a head are many times an L2, the lists differ and there are several generations; one
   // in about every 256 tiles walked.  16 heads of 1440 blocks (45 MiB), d = 128, i.i.d. lists of 60 / 180 / 480: 4.58 -> 3.97,
   // 10.0 -> 9.15, 22.9 -> 22.0 ms; 40 heads, 180: 32.9 -> 23.3 ms (L2 hits 0.38 before); 1152 blocks (36 MiB): 5.86 ->

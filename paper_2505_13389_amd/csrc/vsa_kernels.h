@@ -18,6 +18,10 @@ hipError_t launch_pool_keys16(int BH, int Nc, int d, const uint64_t* mask, int32
 hipError_t launch_coarse(int BH, int Nq, int Nk, int d, int K, float scale, const float* qc, const float* kc,
                          const float* vc, float* sc, float* oc, float* lse_c, int32_t* idx, int emit_idx, int fused,
                          const int32_t* kcnt, hipStream_t s);
+hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
+                                 const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
+                                 const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
+                                 int m_blocks, int key_cubes_16, hipStream_t s);
 // gang_scratch: BH*Nc/32 + 24 counters' worth of memory that nothing else uses during the launch
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,

@@ -42,6 +42,15 @@ def test_walks_of_every_length(K, H, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("K", [1, 2, 12, 13])
+def test_short_walks_of_larger_launches(K, d):
+    """576 query blocks: up to 12 tiles the kernel for short lists, then the general one."""
+    wl = Workload("fwd_short", 1, 6, 7, 22, 30, d, K)
+    g = grid_of(wl)
+    run_and_check(wl, tiled_bits(wl, seed=200 + K + d, pad_garbage=True), random_lists(wl, g, K))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H", [1, 3])
 def test_walks_that_begin_without_a_valid_key(H, d):
     """6 frames: in the last layer of cubes slots 32..63 are pads, so the wavefronts of the second key half meet only

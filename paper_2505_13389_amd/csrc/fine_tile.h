@@ -36,10 +36,13 @@ __device__ __forceinline__ void lds_dma16_at(const void* base, unsigned voff) {
 }
 // M0 is written here and read by the copies that follow in program order (volatile asm statements
 // keep their order).  Nothing else in these kernels uses M0: no dynamically indexed register arrays
-// (v_movrel), no GWS or message instructions.
-__device__ __forceinline__ void set_m0(unsigned lds_addr) { asm volatile("s_mov_b32 m0, %0" : : "s"(lds_addr) : "m0", "memory"); }
+// (v_movrel), no GWS or message instructions.  One wait state has to lie between the write and the copy that reads it;
+// the compiler inserts none for inline assembly.
+__device__ __forceinline__ void set_m0(unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "m0", "memory");
+}
 __device__ __forceinline__ void lds_dma4(const void* base, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :
                : "v"(voff), "s"(base), "s"(lds_addr)
                : "memory", "m0");

@@ -1,0 +1,140 @@
+"""Wait states around the instructions that the fine kernels write as inline assembly: the compiler inserts none for
+them, so the emitted code of every kernel instance is checked, over all paths.
+
+  M0 written by a scalar instruction, then read by a copy to LDS            1 wait state
+  scalar register written by a vector instruction, then a copy's address    5
+(the "manually inserted wait states" table of the CDNA3 ISA document)
+"""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2505_13389_amd import build
+
+FILES = ("fine_fwd.hip", "fine_fwd_short.hip", "fine_bwd.hip", "fine_bwd_dkv.hip")
+
+
+def regs(operand):
+    """The registers an operand names, as (kind, number)."""
+    name = operand.split()[0] if operand.split() else ""
+    m = re.fullmatch(r"([vas])\[(\d+):(\d+)\]", name)
+    if m:
+        return {(m[1], i) for i in range(int(m[2]), int(m[3]) + 1)}
+    m = re.fullmatch(r"([vas])(\d+)", name)
+    if m:
+        return {(m[1], int(m[2]))}
+    return {(name, 0)} if name in ("m0", "vcc") else set()
+
+
+class Instruction:
+    def __init__(self, text):
+        self.text = text
+        op, _, rest = text.partition(" ")
+        self.op = op
+        self.operands = [x.strip() for x in rest.split(",")] if rest.strip() else []
+        named = [regs(x) for x in self.operands]
+        self.matrix = op.startswith("v_mfma")
+        self.vector = op.startswith("v_") and not self.matrix
+        self.copy = "load_lds" in op
+        no_result = self.copy or op.startswith(("ds_write", "global_store", "s_cmp", "s_cbranch", "s_waitcnt", "s_barrier"))
+        self.writes = set() if no_result or not named else named[0]
+        self.reads = set().union(*(named if no_result else named[1:]))
+        self.states = int(self.operands[0], 0) + 1 if op == "s_nop" else 1
+
+
+def parse(lines):
+    """Instructions of one kernel with their successors."""
+    code, labels = [], {}
+    for line in lines:
+        m = re.match(r"(\.LBB\w+):", line)
+        if m:
+            labels[m[1]] = len(code)
+            continue
+        text = " ".join(line.split(";")[0].split())
+        if text and not text.startswith(".") and not text.endswith(":"):
+            code.append(Instruction(text))
+    for n, i in enumerate(code):
+        i.next = [n + 1] if n + 1 < len(code) else []
+        if i.op.startswith("s_cbranch"):
+            i.next = i.next + [labels[i.operands[0]]]
+        elif i.op == "s_branch":
+            i.next = [labels[i.operands[0]]]
+        elif i.op == "s_endpgm":
+            i.next = []
+    return code
+
+
+def within(code, start, states, visit):
+    """visit(instruction, wait states since `start`) along every path while fewer than `states` have passed; a path ends
+    where visit returns True."""
+    best, todo = {}, [(n, 0) for n in code[start].next]
+    while todo:
+        n, age = todo.pop()
+        if age >= states or best.get(n, states) <= age:
+            continue
+        best[n] = age
+        if not visit(code[n], age):
+            todo += [(m, age + code[n].states) for m in code[n].next]
+
+
+def faults(code):
+    found = []
+
+    def note(rule, a, b, age):
+        found.append(f"{rule}: '{a.text}' ... {age} ... '{b.text}'")
+
+    for n, a in enumerate(code):
+        if ("m0", 0) in a.writes:
+            within(code, n, 1, lambda b, age: b.copy and note("M0 before a copy", a, b, age))
+        scalars = {r for r in a.writes if r[0] in ("s", "vcc")} if a.vector else set()
+        if scalars:
+            def address(b, age):
+                if b.copy and b.reads & scalars:
+                    note("address from a vector instruction", a, b, age)
+                return bool(b.writes & scalars)  # (written anew by a scalar instruction, which has waited)
+            within(code, n, 5, address)
+    return found
+
+
+def kernels(path):
+    name, lines = None, []
+    for line in open(path):
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            name, lines = m[1], []
+        elif line.startswith(".Lfunc_end"):
+            if name:
+                yield name, parse(lines)
+            name = None
+        elif name:
+            lines.append(line)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no compiler")
+@pytest.mark.parametrize("source", FILES)
+def test_wait_states_of_the_emitted_code(source, tmp_path):
+    out = str(tmp_path / "kernels.s")
+    subprocess.run(["hipcc", *build.FLAGS, *build.FILE_FLAGS.get(source, []), "-S", "--offload-device-only",
+                    os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
+    seen = 0
+    for name, code in kernels(out):
+        seen += sum(i.copy for i in code)
+        found = faults(code)
+        assert not found, f"{name}: {len(found)}, the first: {found[0]}"
+    assert seen  # (the copies are where the test looks for them)
+
+
+def test_the_check_sees_a_missing_wait():
+    """Planted mistakes, and what mends them."""
+    def of(*text):
+        return faults(parse(text + ("s_endpgm",)))
+    assert of("s_mov_b32 m0, s3", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    assert not of("s_mov_b32 m0, s3", "s_nop 0", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    assert of("v_readlane_b32 s4, v1, s2", "s_nop 3", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    assert not of("v_readlane_b32 s4, v1, s2", "s_nop 4", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    assert not of("v_readlane_b32 s4, v1, s2", "s_add_u32 s4, s4, s6", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    # around a loop: the write at its end, the copy at its beginning
+    assert of(".LBB0_1:", "global_load_lds_dwordx4 v1, s[4:5] offset:0", "v_readlane_b32 s4, v1, s2", "s_cbranch_scc1 .LBB0_1")

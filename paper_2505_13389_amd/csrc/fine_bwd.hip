@@ -287,6 +287,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < G; ++m) {
+      // (behind the last unit no operand reads lie between the last item of step 1 and the matrix instruction that reads it)
+      if (!more1 && m == DVB) asm volatile("s_nop 1");
       mfma_acc(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
       d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
       if (more1) ka[m] = TL::rowmajor_at(smem + (1 - par) * HALF, lane_a, m);

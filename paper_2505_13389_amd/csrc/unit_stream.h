@@ -145,7 +145,8 @@ struct UnitCopy {
 // one costs a move).  The compiler does not see matrix instructions here and inserts none of the wait states
 // they need; the kernels' fixed order provides them: a vector result is consumed by a matrix instruction
 // no earlier than two instructions after it was written, and a matrix result is read by vector instructions
-// no earlier than two matrix instructions after the one that completed it.
+// no earlier than two matrix instructions after the one that completed it (tests/test_wait_states.py checks the
+// emitted code of every instance).
 __device__ __forceinline__ void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }

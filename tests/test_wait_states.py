@@ -3,7 +3,12 @@ them, so the emitted code of every kernel instance is checked, over all paths.
 
   M0 written by a scalar instruction, then read by a copy to LDS            1 wait state
   scalar register written by a vector instruction, then a copy's address    5
-(the "manually inserted wait states" table of the CDNA3 ISA document)
+  vector result, then an operand of a matrix instruction                    2
+  matrix result, then anything but the accumulator of the next one         12
+  accumulator input of a matrix instruction, then a vector write over it    8 (where it is not its result)
+(the "manually inserted wait states" table of the CDNA3 ISA document; the last two for matrix instructions of 8 passes,
+v_mfma_f32_32x32x16_bf16, the only ones here, with a pass to spare.  A matrix instruction behind another starts when
+that one's 8 passes are over, which counts in the last two.  The 2 count instructions, whatever lies between.)
 """
 import os
 import re
@@ -42,6 +47,7 @@ class Instruction:
         no_result = self.copy or op.startswith(("ds_write", "global_store", "s_cmp", "s_cbranch", "s_waitcnt", "s_barrier"))
         self.writes = set() if no_result or not named else named[0]
         self.reads = set().union(*(named if no_result else named[1:]))
+        self.accumulator = named[3] if self.matrix and len(named) > 3 else set()
         self.states = int(self.operands[0], 0) + 1 if op == "s_nop" else 1
 
 
@@ -67,9 +73,9 @@ def parse(lines):
     return code
 
 
-def within(code, start, states, visit):
+def within(code, start, states, visit, passes=1):
     """visit(instruction, wait states since `start`) along every path while fewer than `states` have passed; a path ends
-    where visit returns True."""
+    where visit returns True.  `passes`: wait states a matrix instruction counts for."""
     best, todo = {}, [(n, 0) for n in code[start].next]
     while todo:
         n, age = todo.pop()
@@ -77,7 +83,7 @@ def within(code, start, states, visit):
             continue
         best[n] = age
         if not visit(code[n], age):
-            todo += [(m, age + code[n].states) for m in code[n].next]
+            todo += [(m, age + (passes if code[n].matrix else code[n].states)) for m in code[n].next]
 
 
 def faults(code):
@@ -96,6 +102,22 @@ def faults(code):
                     note("address from a vector instruction", a, b, age)
                 return bool(b.writes & scalars)  # (written anew by a scalar instruction, which has waited)
             within(code, n, 5, address)
+        vectors = {r for r in a.writes if r[0] in ("v", "a")} if a.vector else set()
+        if vectors:
+            within(code, n, 2, lambda b, age: b.matrix and b.reads & vectors and note("vector result to matrix operand", a, b, age))
+        if a.matrix:
+            def result(b, age):
+                if b.matrix and b.accumulator == a.writes:
+                    if (b.reads - b.accumulator) & a.writes:
+                        note("matrix result to matrix operand", a, b, age)
+                    return True
+                if (b.reads | b.writes) & a.writes:
+                    note("matrix result used", a, b, age)
+                return False
+            within(code, n, 12, result, passes=8)
+            if a.accumulator - a.writes:
+                within(code, n, 8, lambda b, age: b.vector and b.writes & a.accumulator and
+                       note("accumulator input overwritten", a, b, age), passes=8)
     return found
 
 
@@ -136,5 +158,15 @@ def test_the_check_sees_a_missing_wait():
     assert of("v_readlane_b32 s4, v1, s2", "s_nop 3", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
     assert not of("v_readlane_b32 s4, v1, s2", "s_nop 4", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
     assert not of("v_readlane_b32 s4, v1, s2", "s_add_u32 s4, s4, s6", "global_load_lds_dwordx4 v1, s[4:5] offset:0")
+    product = "v_mfma_f32_32x32x16_bf16 v[0:15], v[20:23], v[24:27], v[0:15]"
+    other = "v_mfma_f32_32x32x16_bf16 v[32:47], v[50:53], v[54:57], v[32:47]"
+    assert of("v_cvt_pk_bf16_f32 v27, v30, v31", other, product)
+    assert not of("v_cvt_pk_bf16_f32 v27, v30, v31", "s_nop 1", product)
+    assert of(product, other, "s_nop 2", "v_add_f32_e32 v60, v3, v61")
+    assert not of(product, other, "s_nop 3", "v_add_f32_e32 v60, v3, v61")
+    assert not of(product, product)
+    assert of(product, other.replace("v[50:53]", "v[12:15]"))
+    from_zero = product.replace("v[24:27], v[0:15]", "v[24:27], v[64:79]")
+    assert of(from_zero, "s_nop 6", "v_mov_b32_e32 v70, 0") and not of(from_zero, "s_nop 7", "v_mov_b32_e32 v70, 0")
     # around a loop: the write at its end, the copy at its beginning
     assert of(".LBB0_1:", "global_load_lds_dwordx4 v1, s[4:5] offset:0", "v_readlane_b32 s4, v1, s2", "s_cbranch_scc1 .LBB0_1")

@@ -237,11 +237,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   };
   // the reference of a query column moves to the maximum of this unit where that exceeds it by more than
   // kTau: a lane's arithmetic then never depends on what other query columns (pad rows included) hold
-  auto new_ref = [&](const f32x16& S, float old) {
+  // (pad keys do not count: a column all of whose logits are -inf keeps kNoRef and ends as one without a valid key)
+  auto new_ref = [&](const f32x16& S, uint32_t keys, float old) {
     float mx = fmaxf(fmaxf(S[0], S[1]), S[2]);
 #pragma unroll
     for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, S[i]), S[i + 1]);
     mx = max_across_halves(fmaxf(mx, S[15]));
+    if (keys != 0xffffffffu && mx < 0.5f * kMaskBias) mx = -INFINITY;
     const float mx2 = mx * sl2;
     return mx2 > old + kTau ? mx2 : old;
   };
@@ -266,8 +268,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     for (int s = 0; s < kAhead; ++s) kcur[s] = TL::rowmajor_at(smem + HALF, lane_a, s);
     valid = u0.valid;
     if (valid) {
-      ref[0] = new_ref(s0[0], kNoRef);
-      ref[1] = new_ref(s0[1], kNoRef);
+      ref[0] = new_ref(s0[0], valid, kNoRef);
+      ref[1] = new_ref(s0[1], valid, kNoRef);
       have = true;
     }
     p_items(s0, 0, kEarly, ref);
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       mfma_fence();
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const float old = have ? ref[b] : kNoRef, mnew = new_ref(S[b], old);
+        const float old = have ? ref[b] : kNoRef, mnew = new_ref(S[b], valid, old);
         const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
         lsum[b] *= alpha;
 #pragma unroll
@@ -351,7 +353,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         ref[b] = mnew;
       }
       have = true;
-      p_items(S, 0, 16, ref);
+      // (no reference yet: -inf in every key, and nothing of the pad keys either)
+      const float use[2] = {ref[0] > kNoRef ? ref[0] : -kNoRef, ref[1] > kNoRef ? ref[1] : -kNoRef};
+      p_items(S, 0, 16, use);
       mfma_fence();
     }
     lsum[0] += tsum[0];
@@ -451,7 +455,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
               make_float4(o[x][b][4 * g4], o[x][b][4 * g4 + 1], o[x][b][4 * g4 + 2], o[x][b][4 * g4 + 3]);
       const float l = lsum[b] + __shfl_xor(lsum[b], 32);
       if (h == 0) {
-        ml[(wave * 64 + b * 32 + l32) * 2] = have ? ref[b] : -INFINITY;
+        // (kNoRef: every logit of the column was -inf)
+        ml[(wave * 64 + b * 32 + l32) * 2] = have && ref[b] > kNoRef ? ref[b] : -INFINITY;
         ml[(wave * 64 + b * 32 + l32) * 2 + 1] = l;
       }
     }

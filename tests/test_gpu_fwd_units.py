@@ -92,6 +92,43 @@ def test_reference_follows_the_logits(order, H, d):
     run_and_check(wl, bits, random_lists(wl, g, 11))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,K", [(1, 9), (6, 5), (6, 20)])  # four wavefronts, the kernel for short lists, two wavefronts
+def test_rows_whose_logits_are_all_minus_infinity(H, K, d):
+    """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys."""
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("fwd_minf", 1, H, 7, 22, 30, d, K)
+    g = grid_of(wl)
+    bits = tiled_bits(wl, seed=K + d)
+    valid, _ = orc.valid_mask(g)
+    V = g.Np // g.Nc
+    bits["q"] = synth.f32_to_bf16_bits(np.abs(widen(bits)["q"]) + np.float32(0.01))
+    k = widen(bits)["k"]
+    n = max(12, K)
+    k[:, :, :n * V, 0] = np.where(valid[:n * V], -np.inf, 0.0)
+    bits["k"] = synth.f32_to_bf16_bits(k)
+    idx = random_lists(wl, g, K)
+    idx[:, :, :4] = np.arange(K)  # the lists of the first cubes name only such keys
+    with np.errstate(invalid="ignore"):
+        x = widen(bits)
+        ref = orc.forward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], K, real="f32", block_idx=idx)
+    dev, buf = to_dev(bits), vsa.Buffers(problem_of(wl))
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.forward(*a, indices_given=True)
+    torch.cuda.synchronize()
+    of, lse = bf16_to_np(buf.out_fine), buf.lse_fine.cpu().numpy()
+    assert (of[:, :, :4 * V] == 0).all() and (lse[:, :, :4 * V] == 0).all()
+    # (elsewhere a list may still name nothing but those cubes: compared where the oracle has a result)
+    rest = np.isfinite(ref["lse_fine"][:, :, 4 * V:])
+    assert rest.mean() > 0.9 and np.isfinite(of).all() and np.isfinite(lse).all()
+    assert_close(of[:, :, 4 * V:][rest], ref["out_fine"][:, :, 4 * V:][rest], "out_fine")
+    buf.backward(*a, dev["dout"], workspace_kept=True)
+    torch.cuda.synchronize()
+    assert np.isfinite(bf16_to_np(buf.dk)).all() and np.isfinite(bf16_to_np(buf.dv)).all()
+
+
 @pytest.mark.parametrize("d,K", [(64, 300), (128, 150), (128, 20)])
 def test_gangs_of_large_heads(d, K):
     """Heads of 1440 blocks: workgroups start in gangs (every one, every second, only the first; the last gang of an

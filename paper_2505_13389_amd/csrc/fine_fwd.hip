@@ -35,8 +35,11 @@
 
 namespace vsa {
 
-constexpr float kTau = 60.f;            // lazy-rescale threshold, log2 units
-constexpr float kMaxSum = 1152921504606846976.f;  // 2^kTau
+// A lane's sum of 16 values of a unit above this moves the reference of its column.  Values far above the reference
+// cost nothing unless V is large: then O may overflow before it is normalised.  A block in which it does is done again
+// with the second bound, under which O stays below 2^8 times the sum of the values of V it is made of.
+constexpr float kMaxSum = 1152921504606846976.f;  // 2^60
+constexpr float kTightSum = 256.f;
 constexpr float kNoRef = -1e30f;        // below every reference
 
 // max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
@@ -80,7 +83,7 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
 
 template <int D, int NW, template <class> class UNITS>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
-    int Nc, int K, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
+    int Nc_, int K_, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
     const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
     uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
@@ -108,13 +111,21 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // run side by side on an XCD (cubes c, c+8, ...) start their walk a few entries apart and wrap
   // around -- otherwise they ask for the same cache lines in the same cycles.
   if (NW == 2 && gang_arrived) gang_start<kGang<D>>(gang_arrived, gang_every);
+  __shared__ int again;  // O of a valid row overflowed under kMaxSum
+  if (threadIdx.x == 0) again = 0;  // (read behind several barriers)
+  for (bool tight = false;; tight = true) {
+  const float limit = tight ? kTightSum : kMaxSum;
+  // (nothing is kept in registers from one round to the next)
+  unsigned block = blockIdx.x;
+  int tid = threadIdx.x, Nc = Nc_, K = K_;
+  asm volatile("" : "+s"(block), "+v"(tid), "+s"(Nc), "+s"(K));
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
-  const unsigned wg = same_lists ? blockIdx.x : xcd_chunked_id(blockIdx.x, gridDim.x);
+  const unsigned wg = same_lists ? block : xcd_chunked_id(block, gridDim.x);
   const int c = wg % Nc;
   const long long bh = wg / Nc;
   const int rot = same_lists ? ((c >> 3) & 15) % tiles : 0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   const int first = wave >> 1, half = wave & 1;  // this wavefront's tiles: first, first + EPR, ...
   const int nu = tiles > first ? (tiles - first + EPR - 1) / EPR : 0;
@@ -235,17 +246,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 #pragma unroll
     for (int it = from; it < to; ++it) p_item(S, it, rf);
   };
-  // the reference of a query column moves to the maximum of this unit where that exceeds it by more than
-  // kTau: a lane's arithmetic then never depends on what other query columns (pad rows included) hold
+  // the larger of `old` and the largest (scaled) logit of the unit in the lane's query column
   // (pad keys do not count: a column all of whose logits are -inf keeps kNoRef and ends as one without a valid key)
-  auto new_ref = [&](const f32x16& S, uint32_t keys, float old) {
+  auto unit_max = [&](const f32x16& S, uint32_t keys, float old) {
     float mx = fmaxf(fmaxf(S[0], S[1]), S[2]);
 #pragma unroll
     for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, S[i]), S[i + 1]);
     mx = max_across_halves(fmaxf(mx, S[15]));
     if (keys != 0xffffffffu && mx < 0.5f * kMaskBias) mx = -INFINITY;
-    const float mx2 = mx * sl2;
-    return mx2 > old + kTau ? mx2 : old;
+    return fmaxf(mx * sl2, old);
   };
   uint32_t valid = 0;  // valid keys of the current unit
 
@@ -268,8 +277,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     for (int s = 0; s < kAhead; ++s) kcur[s] = TL::rowmajor_at(smem + HALF, lane_a, s);
     valid = u0.valid;
     if (valid) {
-      ref[0] = new_ref(s0[0], valid, kNoRef);
-      ref[1] = new_ref(s0[1], valid, kNoRef);
+      ref[0] = unit_max(s0[0], valid, kNoRef);
+      ref[1] = unit_max(s0[1], valid, kNoRef);
       have = true;
     }
     p_items(s0, 0, kEarly, ref);
@@ -332,14 +341,16 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (more1) {
       if (un[0].valid != 0xffffffffu) add_bias(T, un[0].valid);
     }
-    // The reference stays as long as no sum of this unit's 16 values exceeds 2^kTau: then no value does, and
-    // the rescaling of O is skipped for almost every unit.  The result is exact either way.
+    // The reference of a column stays as long as neither lane's sum of 16 values exceeds `limit`: then no value does, and
+    // the rescaling of O is skipped for almost every unit.  The result is exact either way, and a lane's arithmetic
+    // never depends on what other query columns (pad rows included) hold.
     // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
-    if (__builtin_expect((!have && valid) || __any(fmaxf(tsum[0], tsum[1]) > kMaxSum), 0)) {
+    if (__builtin_expect((!have && valid) || __any(fmaxf(tsum[0], tsum[1]) > limit), 0)) {
       mfma_fence();
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const float old = have ? ref[b] : kNoRef, mnew = new_ref(S[b], valid, old);
+        const bool moves = !have || max_across_halves(tsum[b]) > limit;
+        const float old = have ? ref[b] : kNoRef, mnew = moves ? unit_max(S[b], valid, old) : old;
         const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
         lsum[b] *= alpha;
 #pragma unroll
@@ -463,10 +474,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
   __syncthreads();
 
+  bool overflow = false;
 #pragma unroll
   for (int it = 0; it < LPT; ++it) {
     const int r = (it * NT + tid) / CPR;
-    float M = ml[r * 2], L = 0.f, f[NW];
+    float M = ml[r * 2], L = 0.f, most = 0.f, f[NW];
 #pragma unroll
     for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[(w * 64 + r) * 2]);
     // (M = -inf: the list named no valid key at all -- only a caller-supplied list can, e.g. one made of
@@ -476,6 +488,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     for (int w = 0; w < NW; ++w) {
       f[w] = none ? 0.f : fast_exp2(ml[(w * 64 + r) * 2] - M);
       L += ml[(w * 64 + r) * 2 + 1] * f[w];
+      most = fmaxf(most, ml[(w * 64 + r) * 2 + 1]);
     }
     const float inv = none ? 0.f : 1.0f / L;
     const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
@@ -499,10 +512,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       for (int e = 0; e < 8; ++e) res[e] = fmaf(ocv[e], gcv[e], of[e] * gfv[e]);
       ov = pack8(res);
       fv = pack8(of);
+      float nought = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) nought = fmaf(of[e], 0.f, nought);  // NaN unless all of them are finite
+      overflow |= most > kTightSum && nought != 0.f;
     }
     out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
     if (out_fine) out_fine[g] = fv;
     if (lse_f && ch == 0) lse_f[rows0 + c * kTile + r] = (((qmask >> r) & 1) && !none) ? (M + fast_log2(L)) * kLn2 : 0.f;
+  }
+  if (tight) return;
+  if (overflow) again = 1;
+  __syncthreads();
+  if (!again) return;
   }
 }
 

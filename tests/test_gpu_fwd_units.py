@@ -93,6 +93,25 @@ def test_reference_follows_the_logits(order, H, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 6])
+@pytest.mark.parametrize("scale", [2.0 ** 60, 2.0 ** 110])
+def test_values_of_any_magnitude(scale, H, d):
+    """Rising logits, up to 57 (log2 units) above the first unit's: V of magnitude 2^60 still fits beside them before O is
+    normalised, 2^110 does not."""
+    wl = Workload("fwd_big", 1, H, 7, 22, 30, d, 40)
+    g = grid_of(wl)
+    bits = tiled_bits(wl, seed=d + 1, pad_garbage=True)
+    rng = np.random.default_rng(d + H)
+    ramp = np.linspace(-20.0, 20.0, g.Nc)
+    u = rng.choice([-1.0, 1.0], size=d)
+    k = np.repeat(ramp, g.Np // g.Nc)[None, None, :, None] * u / np.sqrt(d) + 0.1 * rng.standard_normal((1, H, g.Np, d))
+    q = u + 0.1 * rng.standard_normal((1, H, g.Np, d))
+    bits["q"], bits["k"] = synth.f32_to_bf16_bits(q.astype(np.float32)), synth.f32_to_bf16_bits(k.astype(np.float32))
+    bits["v"] = synth.f32_to_bf16_bits(widen(bits)["v"] * np.float32(scale))
+    run_and_check(wl, bits, random_lists(wl, g, 11))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,K", [(1, 9), (6, 5), (6, 20)])  # four wavefronts, the kernel for short lists, two wavefronts
 def test_rows_whose_logits_are_all_minus_infinity(H, K, d):
     """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys."""

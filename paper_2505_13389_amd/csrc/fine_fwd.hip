@@ -38,7 +38,12 @@ namespace vsa {
 // A lane's sum of 16 values of a unit above this moves the reference of its column.  Values far above the reference
 // cost nothing unless V is large: then O may overflow before it is normalised.  A block in which it does is done again
 // with the second bound, under which O stays below 2^8 times the sum of the values of V it is made of.
-constexpr float kMaxSum = 1152921504606846976.f;  // 2^60
+// Moving a reference costs about 770 cycles per 32 query columns (O through ordinary registers and back).  2^80: with
+// N(0, s^2) logits, s in nats, top-32 of 256 blocks / top-78 of 624, 12 heads, d = 128: s = 12 244 / 1262 us, 30 264 / 1380,
+// 60 309 / 1500, 100 331 / 1520 (2^60 and both halves of the queries at once: 245 / 1265, 332 / 1665, 374 / 1735, 394 /
+// 1766; the kernel for short lists, whose O is in ordinary registers: 283 / 1516, 263 / 1517, 255 / 1496, 252 / 1495).
+// Not higher: where one wavefront's sum is 2^80 times the number of keys, another's share is scaled by 2^-126 and no less.
+constexpr float kMaxSum = 1208925819614629174706176.f;  // 2^80
 constexpr float kTightSum = 256.f;
 constexpr float kNoRef = -1e30f;        // below every reference
 
@@ -346,10 +351,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     // never depends on what other query columns (pad rows included) hold.
     // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
     if (__builtin_expect((!have && valid) || __any(fmaxf(tsum[0], tsum[1]) > limit), 0)) {
-      mfma_fence();
+      // (the last products that wrote O lie a whole S phase back, so it can be read at once)
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const bool moves = !have || max_across_halves(tsum[b]) > limit;
+        if (!__any(moves)) continue;
         const float old = have ? ref[b] : kNoRef, mnew = moves ? unit_max(S[b], valid, old) : old;
         const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
         lsum[b] *= alpha;
@@ -362,12 +368,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
           __builtin_amdgcn_sched_barrier(0);  // (one block of O in ordinary registers at a time)
         }
         ref[b] = mnew;
+        // (no reference yet: -inf in every key, and nothing of the pad keys either)
+        const float use[2] = {ref[0] > kNoRef ? ref[0] : -kNoRef, ref[1] > kNoRef ? ref[1] : -kNoRef};
+#pragma unroll
+        for (int st = 0; st < 2; ++st) p_items(S, 8 * st + 4 * b, 8 * st + 4 * b + 4, use);
       }
       have = true;
-      // (no reference yet: -inf in every key, and nothing of the pad keys either)
-      const float use[2] = {ref[0] > kNoRef ? ref[0] : -kNoRef, ref[1] > kNoRef ? ref[1] : -kNoRef};
-      p_items(S, 0, 16, use);
-      mfma_fence();
+      asm volatile("s_nop 1");
     }
     lsum[0] += tsum[0];
     lsum[1] += tsum[1];

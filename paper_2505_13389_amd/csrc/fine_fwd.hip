@@ -535,14 +535,36 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Up to this many query blocks -- one workgroup of four wavefronts per CU at d = 128, two at d = 64 -- four
-// wavefronts per workgroup: the launch does not fill the chip with two-wavefront workgroups, and half as long a list
-// walk counts.  (d = 64: 64 blocks, top-8 10.0 against 12.0 us; 324 and 432 blocks, top-33 26.7 against 37.6 and 27.5
-// against 38.1, top-6 13.0 against 16.3; 648 blocks 36.6 against 39.9, but top-6 19.0 against 17.0.  d = 128: 324 blocks,
-// top-33 42.5 against 38.5.)
-constexpr int kShortTiles = 12;
-template <int D>
-constexpr unsigned kFwdFourWaves = D == 128 ? 256 : 512;
+// Which kernel, by the number of query blocks and of 64-key tiles in a list (times in us: one head size, lists of N(0,1)
+// inputs, B*H*Nb from 64 to 7488).  512 workgroups of the d = 128 kernels are on the chip at a time, 1024 of the d = 64
+// kernel with two wavefronts, 512 of the one with four.
+//
+// The kernel for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile:
+//   d = 128  full generations: 384 blocks, 6 tiles 17.7 against 17.4; 512, 8 tiles 21.0 / 22.4, 12 tiles 25.0 / 24.4; 1024, 20 tiles 59.5 / 60.1, 24
+//            tiles 69.5 / 67.2; 3072, 20 tiles 165 / 166, 33 tiles 246 / 237.  A last generation that is at most half
+//            full costs the general kernel more, the less the more generations there are: 576 blocks, 16 tiles 40.3 / 43.9,
+//            56 tiles 104 / 108; 1152, 16 tiles 62.2 / 69.5, 48 tiles 145 / 149; 1600, 28 tiles 127 / 134; 4160, 24 tiles 1.02.
+//   d = 64   up to 14 tiles, unless the blocks just fill the chip with two-wavefront workgroups (1024 blocks, 12 tiles 27.4 /
+//            23.8) or there are generations enough (4160, 12 tiles 0.95).
+//   one or two tiles: 256 blocks 7.3 / 7.8, 9.2 / 9.6.
+inline bool fwd_short(int d, unsigned grid, int tiles) {
+  if (tiles <= 2) return true;
+  if (d == 128) {
+    const unsigned full = grid / 512, last = grid % 512;
+    if (grid <= 256) return false;
+    if (grid <= 512) return tiles <= (grid > 448 ? 12 : 8);
+    return tiles <= (last > 0 && last <= 256 ? 20 + 40 / (int)full : 20);
+  }
+  if (grid <= 512 || (grid > 768 && grid <= 1024) || grid > 4096) return false;
+  return tiles <= (grid <= 2560 ? 14 : 8);
+}
+// The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
+// with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks
+// 0.93 of it, 1536 0.87; 1024 blocks 1.05, 2560 0.95 to 1.01.  d = 128, 256 blocks, 33 tiles 26.2 / 34.8, 384 blocks 44.0 / 37.2.
+inline bool fwd_four_waves(int d, unsigned grid, int tiles) {
+  if (d == 128) return grid <= 256;
+  return grid <= 512 || (tiles > 14 && grid <= 2560 && !(grid > 768 && grid <= 1024));
+}
 
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
@@ -550,9 +572,8 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
                            int m_blocks, int key_cubes_16, unsigned* gang_scratch, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
-  // Short walks, once there are enough workgroups for several generations: the kernel whose start-up and wind-down
-  // overlap (its header has both kernels' times).
-  if (grid > kFwdFourWaves<128> * 2 && (key_cubes_16 ? (K + 3) / 4 : K) <= kShortTiles)
+  const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
+  if (fwd_short(d, grid, tiles))
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
                                  out_token_major, m_blocks, key_cubes_16, s);
   // Gangs where the K and V of a head are many times an L2, the lists differ and there are several generations; one
@@ -561,7 +582,6 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   // 5.65; 840 blocks (26 MiB), 40: 1.54 -> 1.46; d = 64, 1440 blocks (22.5 MiB): 4.7 to 6.8 -> 4.7.  Below, waiting costs
   // more than the hits return: 624 blocks (19.5 MiB) 1.23 -> 1.26 ms at one gang in 312 tiles.  Local selections, which hit
   // anyway: 1440 blocks, lists of 180 / 60: 9.33 -> 8.95, 3.36 -> 3.39 ms.
-  const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
   const unsigned gang = d == 128 ? kGang<128> : kGang<64>;
   const bool gangs = (size_t)Nc * kTile * d * 4 >= ((size_t)22 << 20) && tiles < Nc && grid >= 16 * gang;
   const unsigned every = gangs ? (unsigned)(255 / tiles + 1) : 1u;
@@ -578,7 +598,7 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
                                              (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, arrived, every)
 #define VSA_FWD_NW(D_, LIST_)                     \
   do {                                            \
-    if (grid <= kFwdFourWaves<D_>) VSA_FWD(D_, 4, LIST_); \
+    if (fwd_four_waves(D_, grid, tiles)) VSA_FWD(D_, 4, LIST_); \
     else VSA_FWD(D_, 2, LIST_);                   \
   } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens

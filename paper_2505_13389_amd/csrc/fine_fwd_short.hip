@@ -19,9 +19,8 @@
 //
 // Two workgroups of four wavefronts per CU, two wavefronts per SIMD: less efficient per tile than the general kernel
 // (every LDS operand feeds one matrix instruction), but one wavefront's start-up, merge and stores lie behind another's
-// work on the same SIMD, which is what counts when a walk is a dozen tiles.  Measured, general / this one, us: 108 blocks,
-// 16 heads, d = 128, top-4 51.9 / 46.1, top-12 77.3 / 75.3; 256 blocks, 12 heads, top-6 with all outputs 109 / 100, top-8
-// 103 / 101, top-16 148 / 151; 256 blocks, 8 heads, d = 64, top-6 36.2 / 34.7, top-12 level.
+// work on the same SIMD, which is what counts when a walk is short or the last generation of a launch nearly empty.  The
+// rule (fwd_short in fine_fwd.hip) has both kernels' times.
 #include <type_traits>
 
 #include "unit_stream.h"

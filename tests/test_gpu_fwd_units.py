@@ -1,4 +1,4 @@
-"""Forward: list walks of every length around the unrolled loop, on both sides of the workgroup-size rule, and the
+"""Forward: list walks of every length around the unrolled loop, on both sides of the rules that choose the kernel, and the
 reference of the online softmax: first units without a valid key, and logits that outgrow the reference again and
 again along the walk."""
 import numpy as np
@@ -33,7 +33,7 @@ def random_lists(wl, g, seed):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H", [1, 3])  # 96 query blocks each: four wavefronts per workgroup, two
+@pytest.mark.parametrize("H", [1, 3])  # 96 query blocks each: four wavefronts (d = 128, 3 heads: two; few tiles: short lists)
 @pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 65])
 def test_walks_of_every_length(K, H, d):
     wl = Workload("fwd_units", 1, H, 7, 22, 30, d, K)
@@ -41,10 +41,29 @@ def test_walks_of_every_length(K, H, d):
     run_and_check(wl, tiled_bits(wl, seed=K + d + H, pad_garbage=True), random_lists(wl, g, K))
 
 
+# d, heads of 96 query blocks, list lengths: the general kernel with two wavefronts per workgroup
+TWO_WAVES = [(128, 3, K) for K in (9, 10, 11, 12, 13, 14, 65)] + [(64, 9, K) for K in (3, 4, 5, 6, 7, 8, 65)]
+
+
+@pytest.mark.parametrize("d,H,K", TWO_WAVES)
+def test_walks_of_two_wavefronts(d, H, K):
+    wl = Workload("fwd_two", 1, H, 7, 22, 30, d, K)
+    g = grid_of(wl)
+    run_and_check(wl, tiled_bits(wl, seed=300 + K + d, pad_garbage=True), random_lists(wl, g, K))
+
+
+@pytest.mark.parametrize("d,K", [(128, 60), (128, 61), (64, 14), (64, 15), (64, 65)])
+def test_both_sides_of_the_short_list_rule(d, K):
+    """576 query blocks: up to 60 tiles (d = 64: 14) the kernel for short lists, then two (four) wavefronts."""
+    wl = Workload("fwd_rule", 1, 6, 7, 22, 30, d, K)
+    g = grid_of(wl)
+    run_and_check(wl, tiled_bits(wl, seed=400 + K + d, pad_garbage=True), random_lists(wl, g, K))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("K", [1, 2, 12, 13])
 def test_short_walks_of_larger_launches(K, d):
-    """576 query blocks: up to 12 tiles the kernel for short lists, then the general one."""
+    """576 query blocks: the kernel for short lists."""
     wl = Workload("fwd_short", 1, 6, 7, 22, 30, d, K)
     g = grid_of(wl)
     run_and_check(wl, tiled_bits(wl, seed=200 + K + d, pad_garbage=True), random_lists(wl, g, K))
@@ -52,10 +71,10 @@ def test_short_walks_of_larger_launches(K, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H", [1, 3])
-def test_walks_that_begin_without_a_valid_key(H, d):
+def test_walks_that_begin_without_a_valid_key(H, d, K=9):
     """6 frames: in the last layer of cubes slots 32..63 are pads, so the wavefronts of the second key half meet only
     pads in lists of that layer (even rows) and a valid key late in the others."""
-    wl = Workload("fwd_dead", 1, H, 6, 22, 30, d, 9)
+    wl = Workload("fwd_dead", 1, H, 6, 22, 30, d, K)
     g = grid_of(wl)
     idx = random_lists(wl, g, 5)
     layer = np.arange(g.Nc // 2, g.Nc)
@@ -67,6 +86,17 @@ def test_walks_that_begin_without_a_valid_key(H, d):
                 pick[-1] = c % (g.Nc // 2)  # (the order of a list is free)
             idx[0, h, c] = pick
     run_and_check(wl, tiled_bits(wl, seed=3, pad_garbage=True), idx)
+
+
+@pytest.mark.parametrize("d,H,K", [(64, 9, 9), (64, 9, 14), (64, 6, 9), (128, 6, 9), (128, 3, 14)])
+def test_walks_of_two_wavefronts_that_begin_without_a_valid_key(d, H, K):
+    """Two wavefronts; (6 heads) the kernel for short lists."""
+    test_walks_that_begin_without_a_valid_key(H, d, K)
+
+
+@pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
+def test_reference_of_two_wavefronts(order):
+    test_reference_follows_the_logits(order, 9, 64)
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -93,11 +123,12 @@ def test_reference_follows_the_logits(order, H, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H", [1, 6])
+@pytest.mark.parametrize("waves", [4, 2])
 @pytest.mark.parametrize("scale", [2.0 ** 60, 2.0 ** 110])
-def test_values_of_any_magnitude(scale, H, d):
+def test_values_of_any_magnitude(scale, waves, d):
     """Rising logits, up to 57 (log2 units) above the first unit's: V of magnitude 2^60 still fits beside them before O is
     normalised, 2^110 does not."""
+    H = 1 if waves == 4 else {64: 9, 128: 3}[d]
     wl = Workload("fwd_big", 1, H, 7, 22, 30, d, 40)
     g = grid_of(wl)
     bits = tiled_bits(wl, seed=d + 1, pad_garbage=True)
@@ -111,10 +142,10 @@ def test_values_of_any_magnitude(scale, H, d):
     run_and_check(wl, bits, random_lists(wl, g, 11))
 
 
-@pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H,K", [(1, 9), (6, 5), (6, 20)])  # four wavefronts, the kernel for short lists, two wavefronts
+@pytest.mark.parametrize("H,K,d", [(1, 9, 64), (1, 9, 128), (6, 5, 64), (6, 5, 128), (9, 20, 64), (3, 20, 128)])
 def test_rows_whose_logits_are_all_minus_infinity(H, K, d):
-    """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys."""
+    """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys.  (Four wavefronts, the
+    kernel for short lists, two wavefronts.)"""
     import torch
     from paper_2505_13389_amd import vsa
     wl = Workload("fwd_minf", 1, H, 7, 22, 30, d, K)

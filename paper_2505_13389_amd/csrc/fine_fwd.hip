@@ -58,11 +58,11 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // is in it for the second one that wants it only if both are at about the same place of their (ascending) lists.
 // They start together, but every workgroup starts when an earlier one ends, and after many generations their places
 // are spread over the whole walk.  So in long launches the workgroups that fill an XCD once form a gang, and those
-// of every `every`-th gang wait until all of it is there.  A wait is bounded (about 25 us: it only costs time if
-// part of the chip is taken by somebody else) and changes no result.  Workgroups are dealt to the 8 XCDs round-robin
+// of every `every`-th gang wait until all of it is there.  A wait is bounded and changes no result.  Where a gang
+// cannot be on the chip all at once -- another stream's kernel holds part of it, or the device is not 8 XCDs of 32 CUs
+// -- every such gang waits out its bound of about 25 us, at most a tenth of the time its 256 tiles take.  Workgroups are dealt to the 8 XCDs round-robin
 // by blockIdx.
-template <int D>
-constexpr unsigned kGang = D == 128 ? 64 : 128;  // 32 CUs x the workgroups of two wavefronts a CU holds
+constexpr unsigned kGang = 64;  // 32 CUs x the workgroups of two wavefronts a CU holds at d = 128
 constexpr int kGangSpins = 40;
 
 __global__ void k_gang_clear(unsigned* __restrict__ arrived, unsigned n) {
@@ -70,13 +70,12 @@ __global__ void k_gang_clear(unsigned* __restrict__ arrived, unsigned n) {
   if (i < n) arrived[i] = 0;
 }
 
-template <unsigned GANG>
 __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
-  const unsigned x = blockIdx.x & 7u, i = blockIdx.x >> 3, gang = i / GANG;
+  const unsigned x = blockIdx.x & 7u, i = blockIdx.x >> 3, gang = i / kGang;
   if (gang % every) return;  // (uniform)
   if (threadIdx.x == 0) {
     unsigned* mine = arrived + gang * 8 + x;
-    const unsigned of_xcd = (gridDim.x + 7 - x) >> 3, size = min(GANG, of_xcd - gang * GANG);
+    const unsigned of_xcd = (gridDim.x + 7 - x) >> 3, size = min(kGang, of_xcd - gang * kGang);
     __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int spin = 0; spin < kGangSpins; ++spin) {
       if (__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= size) break;
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // (plain blockIdx order), which keeps that list's tiles shared chip-wide, and the workgroups that
   // run side by side on an XCD (cubes c, c+8, ...) start their walk a few entries apart and wrap
   // around -- otherwise they ask for the same cache lines in the same cycles.
-  if (NW == 2 && gang_arrived) gang_start<kGang<D>>(gang_arrived, gang_every);
+  if (D == 128 && NW == 2 && gang_arrived) gang_start(gang_arrived, gang_every);
   __shared__ int again;  // O of a valid row overflowed under kMaxSum
   if (threadIdx.x == 0) again = 0;  // (read behind several barriers)
   for (bool tight = false;; tight = true) {
@@ -576,18 +575,20 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   if (fwd_short(d, grid, tiles))
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
                                  out_token_major, m_blocks, key_cubes_16, s);
-  // Gangs where the K and V of a head are many times an L2, the lists differ and there are several generations; one
-  // in about every 256 tiles walked.  16 heads of 1440 blocks (45 MiB), d = 128, i.i.d. lists of 60 / 180 / 480: 4.58 -> 3.97,
-  // 10.0 -> 9.15, 22.9 -> 22.0 ms; 40 heads, 180: 32.9 -> 23.3 ms (L2 hits 0.38 before); 1152 blocks (36 MiB): 5.86 ->
-  // 5.65; 840 blocks (26 MiB), 40: 1.54 -> 1.46; d = 64, 1440 blocks (22.5 MiB): 4.7 to 6.8 -> 4.7.  Below, waiting costs
-  // more than the hits return: 624 blocks (19.5 MiB) 1.23 -> 1.26 ms at one gang in 312 tiles.  Local selections, which hit
-  // anyway: 1440 blocks, lists of 180 / 60: 9.33 -> 8.95, 3.36 -> 3.39 ms.
-  const unsigned gang = d == 128 ? kGang<128> : kGang<64>;
-  const bool gangs = (size_t)Nc * kTile * d * 4 >= ((size_t)22 << 20) && tiles < Nc && grid >= 16 * gang;
+  // Gangs, one in about every 256 tiles walked, at d = 128 where the K and V of a head are many times an L2, the lists differ
+  // and there are 16 generations (heads of 64 MiB: two).  Without / with, lists of N(0,1) inputs, then local ones: 1440
+  // blocks (45 MiB), 40 heads, lists of 96 14.3 / 13.1, 13.4 / 13.0 ms, of 180 32.9 / 23.3 (L2 hits 0.38 without); 16 heads,
+  // 180 9.66 / 9.06, 9.06 / 8.87 ms, 60 3.25 / 3.29, 3.31 / 3.36; 1152 blocks (36 MiB), 12 heads, 32 1.55 / 1.42, 1.10 / 1.13;
+  // 2160 blocks (68 MiB), 2 heads, 180 2.72 / 2.62, 1.60 / 1.59, 4 heads 5.10 / 3.43, 3.17 / 3.20.  Elsewhere the waits
+  // cost more than the hits return: 1440 blocks, 2 heads, 32 228 / 240 us; 624 blocks (19.5 MiB) 1.23 / 1.26 ms; d = 64,
+  // 1440 blocks, 16 heads, 180 4.62 / 4.83, 4.55 / 4.72 ms, 2 heads, 24 105 / 123 us.
+  const size_t head = (size_t)Nc * kTile * d * 4;  // bytes of its K and V
+  const bool gangs = d == 128 && tiles < Nc &&
+                     ((head >= ((size_t)22 << 20) && grid >= 8192) || (head >= ((size_t)64 << 20) && grid >= 1024));
   const unsigned every = gangs ? (unsigned)(255 / tiles + 1) : 1u;
   unsigned* arrived = gangs ? gang_scratch : nullptr;
   if (gangs) {
-    const unsigned n = 8 * ((grid / 8 + gang) / gang + 1);  // (at most BH*Nc/32 + 24 counters)
+    const unsigned n = 8 * ((grid / 8 + kGang) / kGang + 1);  // (at most BH*Nc/32 + 24 counters)
     k_gang_clear<<<(n + 255) / 256, 256, 0, s>>>(arrived, n);
   }
   const long long cpr = d / 8, Np = (long long)Nc * kTile;

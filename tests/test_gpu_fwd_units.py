@@ -179,14 +179,18 @@ def test_rows_whose_logits_are_all_minus_infinity(H, K, d):
     assert np.isfinite(bf16_to_np(buf.dk)).all() and np.isfinite(bf16_to_np(buf.dv)).all()
 
 
-@pytest.mark.parametrize("d,K", [(64, 300), (128, 150), (128, 20)])
-def test_gangs_of_large_heads(d, K):
-    """Heads of 1440 blocks: workgroups start in gangs (every one, every second, only the first; the last gang of an
-    XCD is not a whole one).  Sampled query cubes against the oracle; graph replays, with the counters' memory
-    poisoned in between, bit-identical."""
+LARGE, GANGS = (2, 24, 48, 80), (1, 24, 64, 88)  # heads of 1440 blocks; of 2112 blocks, whose workgroups start in gangs
+
+
+@pytest.mark.parametrize("d,K,shape", [(64, 300, LARGE), (128, 150, LARGE), (128, 20, LARGE), (128, 300, GANGS),
+                                       (128, 150, GANGS), (128, 30, GANGS)])
+def test_gangs_of_large_heads(d, K, shape):
+    """Large heads without gangs, and with (every one, every second, every ninth; the last gang of an XCD is not a whole
+    one).  Sampled query cubes against the oracle; graph replays, with the counters' memory poisoned in between,
+    bit-identical."""
     import torch
     from paper_2505_13389_amd import vsa
-    wl = Workload("fwd_gang", 1, 2, 24, 48, 80, d, K)
+    wl = Workload("fwd_gang", 1, *shape, d, K)
     g = grid_of(wl)
     bits = tiled_bits(wl, seed=K)
     x, dev = widen(bits), to_dev(bits)

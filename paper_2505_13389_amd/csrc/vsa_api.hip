@@ -497,17 +497,22 @@ int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, 
     if (slots_hi > max_slots) max_slots = slots_hi;
     if (nsplit > max_split) max_split = nsplit;
   }
-  {  // every item of every (b, h) belongs to exactly one workgroup of the dK/dV launch
+  {  // every item of every (b, h) belongs to exactly one workgroup of the dK/dV launch; heads are dealt eight at a time
     const int BH = p->B * p->H, per = Nc + cap;
-    std::vector<unsigned char> taken((size_t)BH * per);
-    const unsigned grid = vsa::dkv_grid(BH, per);
-    for (unsigned b = 0; b < grid; ++b) {
-      int bh, item;
-      vsa::dkv_item(b, BH, per, bh, item);
-      if (bh < 0 || bh >= BH || item < 0) ++bad;
-      else if (item < per && taken[(size_t)bh * per + item]++) ++bad;
+    const unsigned grid = vsa::dkv_grid(BH, per), eight = 8u * (unsigned)per;
+    std::vector<unsigned char> taken(eight);
+    for (int first = 0; first < BH; first += 8) {
+      const int heads = BH - first < 8 ? BH - first : 8;
+      const unsigned begin = (unsigned)(first / 8) * eight, end = first + 8 < BH ? begin + eight : grid;
+      std::fill(taken.begin(), taken.end(), 0);
+      for (unsigned b = begin; b < end; ++b) {
+        int bh, item;
+        vsa::dkv_item(b, BH, per, bh, item);
+        if (bh < first || bh >= first + heads || item < 0) ++bad;
+        else if (item < per && taken[(size_t)(bh - first) * per + item]++) ++bad;
+      }
+      for (int i = 0; i < heads * per; ++i) bad += taken[i] != 1;
     }
-    for (unsigned char t : taken) bad += t != 1;
   }
   if (report) {
     report[0] = bad; report[1] = max_deg; report[2] = max_items; report[3] = max_slots;

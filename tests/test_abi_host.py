@@ -3,6 +3,8 @@ and its host-only entry points and argument validation behave as documented."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -180,3 +182,19 @@ def test_dkv_workgroups_cover_every_item_once(lib, BH):
     lists = np.broadcast_to(np.arange(3, dtype=np.int32), (1, BH, Nc, 3))
     rc, rep = vsa.vsa_host_replay_lists(pb, lists)
     assert rc == 0 and rep["violations"] == 0, rep
+
+
+def test_replay_memory_does_not_grow_with_the_number_of_heads(lib):
+    """2^21 heads of one block with 16 MiB to spare: an allocation that fails inside would end the process."""
+    code = """
+import resource, numpy as np
+from paper_2505_13389_amd import vsa
+pb = vsa.Problem(1, 1 << 21, 4, 4, 4, 64, 1)
+lists = np.zeros((1, 1 << 21, 1, 1), np.int32)
+vsa.vsa_host_replay_lists(vsa.Problem(1, 3, 4, 4, 4, 64, 1), lists[:, :3])
+now = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (now + (16 << 20),) * 2)
+rc, rep = vsa.vsa_host_replay_lists(pb, lists)
+assert rc == 0 and rep["violations"] == 0, (rc, rep)
+"""
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0

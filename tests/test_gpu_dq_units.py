@@ -10,8 +10,8 @@ from paper_2505_13389_amd.synth import Workload
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H", [1, 3])  # 96 query blocks each: four wavefronts per workgroup, two
+@pytest.mark.parametrize("H,d", [(1, 64), (3, 64), (1, 128), (3, 128), (6, 64)])  # 96 query blocks a head: four wavefronts
+# per workgroup up to 256 blocks, at d = 64 up to 512, then two
 @pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 65])
 def test_dq_walks_of_every_length(K, H, d):
     import torch

@@ -44,6 +44,10 @@ def random_cases(n, seed=20250515, tag="rnd16"):
 
 
 CASES.update(random_cases(8))
+# Launches of 288 to 864 query blocks, on a clip whose last layer of cubes holds dead key cubes: the kernel for short lists
+# (1 to 18 tiles of four entries, the last one partial or not), two and four wavefronts per workgroup.
+for _d, _H, _ks in ((128, 6, (1, 7, 48, 49, 241)), (128, 3, (33, 49, 70)), (64, 6, (1, 7, 48, 49, 70)), (64, 9, (9, 70))):
+    CASES.update({f"blocks{96 * _H}_d{_d}_k{_k}": Workload(f"blocks{96 * _H}_d{_d}_k{_k}", 1, _H, 6, 22, 30, _d, _k) for _k in _ks})
 
 
 @pytest.fixture(scope="module")

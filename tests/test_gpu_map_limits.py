@@ -1,6 +1,6 @@
 """The transposed block map on both sides of the limit below which it shares the preprocess launch (384 blocks), with
-lists that name a few key blocks very often (split lists) and some never.  These shapes also take the coarse backward
-in one launch, in one chunk of 256 cubes and in two."""
+lists that name a few key blocks very often (split lists) and some never; and the coarse backward by itself, in one
+launch (one chunk of 256 cubes, two and three) and in three."""
 import numpy as np
 import pytest
 
@@ -37,3 +37,32 @@ def test_map_on_both_sides_of_the_limit(grid, blocks, d):
     torch.cuda.synchronize()
     for n in ("dq", "dk", "dv", "dgate_c", "dgate_f"):
         assert_close(bf16_to_np(getattr(buf, n)), ref[n], n)
+
+
+@pytest.mark.parametrize("grid,blocks", [((4, 4, 7), 2), ((20, 12, 68), 255), ((4, 4, 1028), 257), ((23, 32, 30), 384),
+                                         ((20, 27, 44), 385), ((21, 30, 52), 624)])
+@pytest.mark.parametrize("d,H", [(64, 3), (64, 4), (128, 1), (128, 2)])  # 624 blocks: one launch, three, one, three
+@pytest.mark.parametrize("planted", [False, True])
+def test_coarse_gradients_alone(grid, blocks, d, H, planted):
+    """Gate G_f = 0: nothing comes through the fine stage, dq, dk and dv are the pooled coarse gradients.  They are fp32 sums
+    rounded to bf16 once, so off by at most 2^-9 of themselves and what the sums lose (1e-4 of the whole)."""
+    import torch
+    from paper_2505_13389_amd import vsa
+    K = min(5, blocks)
+    wl = Workload("coarse_alone", 1, H, *grid, d, K, planted=planted)
+    g = grid_of(wl)
+    assert g.Nc == blocks
+    bits = tiled_bits(wl, seed=blocks + d, pad_garbage=True)
+    bits["gate_f"][:] = 0
+    x, dev = widen(bits), to_dev(bits)
+    idx = np.tile(np.arange(K, dtype=np.int32), (1, H, g.Nc, 1))
+    ref = orc.backward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], x["dout"], idx, K, real="f64")
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(*a, indices_given=True)
+    buf.backward(*a, dev["dout"])
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv"):
+        assert np.abs(ref[n]).max() > 0
+        assert_close(bf16_to_np(getattr(buf, n)), ref[n], n, rel_l2=2.0 ** -9 + 1e-4)

@@ -47,13 +47,6 @@ constexpr float kMaxSum = 1208925819614629174706176.f;  // 2^80
 constexpr float kTightSum = 256.f;
 constexpr float kNoRef = -1e30f;        // below every reference
 
-// max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
-// round trip through the LDS permute path
-__device__ __forceinline__ float max_across_halves(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // Gangs.  The workgroups that run side by side on an XCD fetch their tiles through one 4 MiB L2, and a tile
 // is in it for the second one that wants it only if both are at about the same place of their (ascending) lists.
 // They start together, but every workgroup starts when an earlier one ends, and after many generations their places

@@ -36,13 +36,6 @@ __device__ __forceinline__ bf16x8 acc_to_operand(const float* p) {
   return __builtin_bit_cast(bf16x8, u);
 }
 
-// max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
-// round trip through the LDS permute path
-__device__ __forceinline__ float max_across_halves(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // The list of key cubes a workgroup streams, with the valid-key mask of one 32-key half of each
 // cube, held in registers 64 entries at a time (lane e holds entry e of the current chunk).  The
 // loops read an entry with v_readlane: no scalar or vector load, and so no wait on one, sits
@@ -84,11 +77,9 @@ struct CubeList {
     cube = __builtin_amdgcn_readlane(idx_v, e & 63);
     km = (uint32_t)__builtin_amdgcn_readlane((int)km_v, e & 63);
   }
-  // The walk in tiles (one tile = one list entry here): number of tiles, whether the list names every
-  // cube, the first source row of this wave's share of tile t (valid after init for the first chunk),
-  // and row + key mask of tile t.
+  // The walk in tiles (one tile = one list entry here): the first source row of this wave's share of tile t
+  // (valid after init for the first chunk), and row + key mask of tile t.
   static constexpr int kEntriesPerTile = 1;
-  __device__ __forceinline__ int tiles() const { return n; }
   __device__ __forceinline__ int first_row(int t) const { return cube(t) * kTile; }
   __device__ __forceinline__ void get_tile(int t, int& row, uint32_t& km) {
     int c;
@@ -128,7 +119,6 @@ struct SubCubeList {
     load_indices(0);
   }
   static constexpr int kEntriesPerTile = 4;
-  __device__ __forceinline__ int tiles() const { return (n + 3) >> 2; }
   __device__ __forceinline__ int row_of_entry(int e) const {  // e in the current chunk
     const int id = __builtin_amdgcn_readlane(idx_v, min(e, n - 1) & 63);
     return (id >> 2) * kTile + subcube_first_slot(id & 3);
@@ -166,14 +156,13 @@ struct TileCopy : Tile<D> {
   // vmcnt in issue order, every wave waits for its own share (s_waitcnt) and a workgroup barrier
   // then makes the whole tile visible.
   static constexpr int IPW = kTile / RPI / 4;    // instructions per wave and tile, 4 waves copying
-  // NW wavefronts share the copy of one tile; `part` in [0, NW) is this wave's share.  The
+  // Four wavefronts share the copy of one tile; `part` is this wave's share.  The
   // offsets come out LESS the instruction offset (i KiB) that copy i of a tile carries: the
   // instruction adds its immediate to both the global and the LDS address, so one M0 value
   // serves all copies of a tile.  (The source row of copy i lies at least i KiB into the tile,
   // so the difference is never negative.)
-  template <int NW = 4>
   __device__ static __forceinline__ void lane_offsets(int part, int lane, unsigned* off) {
-    constexpr int N = kTile / RPI / NW;
+    constexpr int N = IPW;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int r = (part * N + i) * RPI + lane / CPR, pc = lane % CPR;
@@ -184,7 +173,7 @@ struct TileCopy : Tile<D> {
   // copying: the base pointer of wave `part` is the first slot of its key cube, LDS row 16*part + x
   // takes token x of that key cube, and the swizzle follows the LDS row.
   __device__ static __forceinline__ void lane_offsets_sub(int part, int lane, unsigned* off) {
-    constexpr int N = kTile / RPI / 4;
+    constexpr int N = IPW;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int x = i * RPI + lane / CPR, r = part * 16 + x, pc = lane % CPR;
@@ -196,10 +185,9 @@ struct TileCopy : Tile<D> {
   __device__ static __forceinline__ void copy_step(const void* g, const unsigned* off) {
     lds_dma16_at<I * 1024>(g, off[I]);
   }
-  template <int NW = 4>
   __device__ static __forceinline__ void async_load(const uint4* __restrict__ src, long long row0, unsigned char* tile,
                                                     int part, const unsigned* off) {
-    constexpr int N = kTile / RPI / NW;
+    constexpr int N = IPW;
     static_assert(N >= 1 && N <= 4, "copies per wave and tile");
     const void* g = uniform_ptr(src + row0 * CPR);
     set_m0(__builtin_amdgcn_readfirstlane(lds_address(tile) + (unsigned)(part * N) * 1024u));

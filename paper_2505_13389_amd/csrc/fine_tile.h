@@ -118,6 +118,13 @@ __device__ __forceinline__ int merge_offset(int row, int col, int row_stride) {
   return row * row_stride + ((((col >> 2) ^ (row & 15)) << 2));
 }
 
+// max over both lane halves (lanes l and l^32) with one cross-lane VALU instruction instead of a
+// round trip through the LDS permute path
+__device__ __forceinline__ float max_across_halves(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

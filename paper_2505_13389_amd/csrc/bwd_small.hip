@@ -156,7 +156,7 @@ __global__ __launch_bounds__(1024) void k_coarse_bwd_one(int Nc, float scale, co
         const long long qrow = first + (keys ? min(n, Nc - 1) : min(m0 + m, Nc - 1));
         const float a = n < Nc ? fast_exp2((scale * s[i] - lse_c[qrow]) * kLog2e) : 0.f;
         A[m * ROW + wave * 16 + l16] = a;
-        G[m * ROW + wave * 16 + l16] = a * (da[i] - dot[qrow]);
+        G[m * ROW + wave * 16 + l16] = n < Nc ? a * (da[i] - dot[qrow]) : 0.f;  // (chosen, not multiplied: Inf stays where it is)
       }
     }
     __syncthreads();
@@ -166,7 +166,10 @@ __global__ __launch_bounds__(1024) void k_coarse_bwd_one(int Nc, float scale, co
       const int kk = c0 + k0 + 4 * kq;
       float b[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = col[(long long)min(kk + j, Nc - 1) * D];  // (past the end: times zero)
+      for (int j = 0; j < 4; ++j) {
+        const float x = col[(long long)min(kk + j, Nc - 1) * D];
+        b[j] = kk + j < Nc ? x : 0.f;
+      }
       out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[0], out, 0, 0, 0);
       out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[1], out, 0, 0, 0);
       out = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[2], out, 0, 0, 0);

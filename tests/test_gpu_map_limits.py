@@ -66,3 +66,23 @@ def test_coarse_gradients_alone(grid, blocks, d, H, planted):
     for n in ("dq", "dk", "dv"):
         assert np.abs(ref[n]).max() > 0
         assert_close(bf16_to_np(getattr(buf, n)), ref[n], n, rel_l2=2.0 ** -9 + 1e-4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_an_infinite_gradient_of_the_last_cube(d):
+    """175 cubes, not a multiple of 16: an infinite dO in the last one makes that column of dv infinite, not NaN."""
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("coarse_inf", 1, 1, 20, 20, 28, d, 8)
+    g = grid_of(wl)
+    assert g.Nc == 175
+    dev = to_dev(tiled_bits(wl, seed=d))
+    dev["dout"][:, :, 64 * 174, 3] = float("inf")
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"].abs() + 0.1, dev["gate_f"].abs() + 0.1)
+    buf.forward(*a)
+    buf.backward(*a, dev["dout"])
+    torch.cuda.synchronize()
+    dv = bf16_to_np(buf.dv)
+    assert (dv[..., 3] == np.inf).all()
+    assert np.isfinite(np.delete(dv, 3, axis=-1)).all()

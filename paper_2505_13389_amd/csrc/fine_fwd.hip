@@ -366,7 +366,6 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         for (int st = 0; st < 2; ++st) p_items(S, 8 * st + 4 * b, 8 * st + 4 * b + 4, use);
       }
       have = true;
-      asm volatile("s_nop 1");
     }
     lsum[0] += tsum[0];
     lsum[1] += tsum[1];

@@ -26,9 +26,9 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 //   S [32 q x 64 k] = Q K^T,  dP = dO_f V^T,   P = exp2(S'),  dS = P dP',   dV += P^T dO_f,  dK += dS^T Q
 // so every operand it reads from LDS feeds two matrix instructions, and since nobody else reads its
 // rows it copies them into stages of its own: the loop has no barrier, the wavefronts drift freely.
-// dK and dV [64 x d] are 4*d accumulation registers; K stays in registers (2*d/4 of them), V in LDS (one
-// tile for the workgroup), S and dP (64 registers) become P and dS in place.  The four partial results
-// are added once, through LDS, at the end.
+// dK and dV [64 x d] are 2*d accumulation registers; K stays in registers (d/2 of them), and V of the first 32 keys (d/4);
+// V of the other 32 is in LDS, once for the workgroup.  S and dP (64 registers) become P and dS in place.  The NW partial
+// results are added once, through LDS, at the end.
 //
 // The order inside a unit is the dependency order, S | dP | dV | dK: P is formed while dP is multiplied,
 // dS while dV is, so the vector work hides behind matrix work without a second set of registers.  Each

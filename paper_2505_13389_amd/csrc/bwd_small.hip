@@ -580,7 +580,7 @@ __device__ __forceinline__ void map_one(MapOneLds& l, const MapArgs& a, int bh, 
 // 256 blocks, 12 heads 1044 -> 1035, d = 64, 16 heads 795 -> 783; 280 blocks, 5 heads, through the op 562 -> 548.
 // (Workgroups of 256 threads: 57 and, for the last, whose map is then the longer part, 555; of 1024: 57 and 544, but
 // 788 for the one before.)
-template <int D>
+template <int D, bool ONCE>
 __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs map_args, unsigned cubes, int Nc, int m_blocks, const uint64_t* __restrict__ mask, const uint4* __restrict__ dout,
                                                  const uint4* __restrict__ gc, const uint4* __restrict__ gf,
                                                  const uint4* __restrict__ of, const float* __restrict__ oc,
@@ -630,10 +630,10 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
     float dsum = 0.f;
     if (valid) {
       float go[8], gcv[8], gfv[8], ofv[8], t0[8], t1[8], t2[8];
-      unpack8(dout[do0 + r * do_row_stride + ch], go);
-      unpack8(gc[g], gcv);
-      unpack8(of[g], ofv);
-      if (gf) unpack8(gf[g], gfv);
+      unpack8(load16<ONCE>(dout + do0 + r * do_row_stride + ch), go);
+      unpack8(load16<ONCE>(gc + g), gcv);
+      unpack8(load16<ONCE>(of + g), ofv);
+      if (gf) unpack8(load16<ONCE>(gf + g), gfv);
       else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) gfv[e] = 1.f;
@@ -651,8 +651,8 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
 #pragma unroll
       for (int e = 0; e < 8; ++e) dsum = fmaf(t2r[e], ofv[e], dsum);
     }
-    dgc[g] = o_gc;
-    if (dgf) dgf[g] = o_gf;
+    store16<ONCE>(dgc + g, o_gc);
+    if (dgf) store16<ONCE>(dgf + g, o_gf);
     dof[g] = o_dof;
 #pragma unroll
     for (int o = CPR / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
@@ -691,14 +691,19 @@ hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* m
   const float inv_sl2 = 1.0f / (scale * kLog2e);
   const long long cpr = d / 8, Np = (long long)Nc * m_blocks * kTile;
   const long long dhs = dout_token_major ? cpr : Np * cpr, drs = dout_token_major ? H * cpr : cpr;
-  if (d == 128)
-    k_bwd_pre<128><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                        (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                        inv_sl2, doc, dot, lse_f, H, dhs, drs);
-  else
-    k_bwd_pre<64><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, (const uint4*)gate_f,
-                                       (const uint4*)out_fine, oc, (uint4*)dgate_c, (uint4*)dgate_f, (uint4*)dof, rowd,
-                                       inv_sl2, doc, dot, lse_f, H, dhs, drs);
+  const bool stream = (long long)BH * Np * d * 2 >= kStreamBytes;
+#define VSA_PRE(D_, ONCE_)                                                                                              \
+  k_bwd_pre<D_, ONCE_><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, \
+                                                    (const uint4*)gate_f, (const uint4*)out_fine, oc, (uint4*)dgate_c,  \
+                                                    (uint4*)dgate_f, (uint4*)dof, rowd, inv_sl2, doc, dot, lse_f, H, dhs, drs)
+  if (d == 128) {
+    if (stream) VSA_PRE(128, true);
+    else VSA_PRE(128, false);
+  } else {
+    if (stream) VSA_PRE(64, true);
+    else VSA_PRE(64, false);
+  }
+#undef VSA_PRE
   return hipGetLastError();
 }
 

@@ -13,8 +13,8 @@
 
 namespace vsa {
 
-// One workgroup per (b, h, 64-row query block), split into wavefronts that stream units of 32 keys like the forward's
-// (fine_fwd.hip).  A unit is six groups of d/16 matrix instructions, query half by query half:
+// Workgroups of two wavefronts (four in small launches) that stream units of 32 keys like the forward's (fine_fwd.hip),
+// each of a block of its own or sharing one (paired_workgroups).  A unit is six groups of d/16 matrix instructions, query half by query half:
 //   S 0 | S 1 | dP 0 | dP 1 | dQ 0 | dQ 1
 // so that the vector work of one half, P = exp2(S sl2 - lse) and dS = P dP', lies behind the matrix work of the other
 // without a second unit in flight; the LDS operands of a product stay in registers for its second half, so
@@ -27,7 +27,9 @@ namespace vsa {
 //
 // What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 205 others, all issued by one
 // wavefront; at 1.74 GHz the pipe is busy 67 % of the time, an instruction is issued in 57 % of it and 15 % are spent
-// in waits (start-up, merge and stores among them: about 7 us of a workgroup's 95).
+// in waits.  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12
+// heads, d = 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of
+// the time.
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
 // top-78 of 624: 1.61 -> 1.49 ms (1.23 PFLOP/s executed); 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
 // of 256, local lists: 2.83 -> 2.58 ms; d = 64, B = 2, 8 heads, top-32: 220 -> 210 us.
@@ -36,33 +38,41 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
     const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
     const float* __restrict__ rowd, const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
-    uint4* __restrict__ dq, int m_blocks) {
+    uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
-  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
-  constexpr int EPR = NW / 2;           // tiles a round of units takes
+  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32;
   constexpr int HALF = TL::BYTES / 2;   // 32 rows
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int G = KS;                 // matrix instructions of a group
   constexpr int OS = D;
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
+  __shared__ uint32_t masks[NW * 128];
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
   static_assert(G == 2 * DVB && G == NC && G % 4 == 0, "phase interleave: one copy instruction per matrix instruction");
 
-  // (K = Nc: plain blockIdx order and staggered walks, as in the forward kernel)
+  // (as in the forward kernel: the first `pairs` workgroups take two blocks; with K = Nc plain blockIdx order and staggered walks)
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
-  const unsigned wg = same_lists ? blockIdx.x : xcd_chunked_id(blockIdx.x, gridDim.x);
-  const int c = wg % Nc;
-  const long long bh = wg / Nc;
-  const int rot = same_lists ? ((c >> 3) & 15) % tiles : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
-  const int first = wave >> 1, half = wave & 1;  // this wavefront's tiles: first, first + EPR, ...
-  const int nu = tiles > first ? (tiles - first + EPR - 1) / EPR : 0;
-  auto tile_of = [&](int u) { const int t = first + EPR * u + rot; return t >= tiles ? t - tiles : t; };
+  constexpr bool kPairs = NW == 2;
+  const bool paired = kPairs && blockIdx.x < pairs;
+  const unsigned from = paired ? 0u : pairs, those = paired ? pairs : gridDim.x - pairs;
+  const unsigned id = same_lists ? blockIdx.x - from : xcd_chunked_id(blockIdx.x - from, those);
+  const unsigned wg = paired ? 2 * id + wave : 2 * pairs + id;
+  if (paired && wg >= blocks) return;  // (an odd number of blocks)
+  const int c = wg % Nc;
+  const long long bh = wg / Nc;
+  const int rot = same_lists ? ((paired ? c >> 4 : c >> 3) & 15) % tiles : 0;
+  const int nu = paired ? 2 * tiles : tiles > (wave >> 1) ? (tiles - (wave >> 1) + NW / 2 - 1) / (NW / 2) : 0;
+  auto tile_of = [&](int u) {
+    const int t = (paired ? u >> 1 : (wave >> 1) + (NW / 2) * u) + rot;
+    return t >= tiles ? t - tiles : t;
+  };
+  auto half_of = [&](int u) { return (paired ? u : wave) & 1; };
   const long long rows0 = bh * (long long)Nc * kTile;
   const unsigned char* kb = (const unsigned char*)uniform_ptr(k + rows0 * CPR);
   const unsigned char* vb = (const unsigned char*)uniform_ptr(v + rows0 * CPR);
@@ -81,33 +91,47 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     else asm volatile("" : "+v"(op));
   };
 
-  // Start-up: the list first (one round trip), then the copies of the first unit, of Q (which waits in the
-  // second V stages of the first two wavefronts) and of dO_f (in their second K stages), then the row terms and
-  // the key masks, all in flight together.
+  // Start-up: the list, Q, dO_f and the row terms (one round trip), then the key masks and the first two units, of
+  // which the first products need the first alone.  Q and dO_f wait in stages: a wavefront of its own block has all of
+  // them (and the copies of its first unit behind them), where a block is shared the first two wavefronts have one half
+  // each in their second stages.
   UC copy;
   copy.init(lane);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
   UL list;
-  list.init(idx + (bh * Nc + c) * (long long)K, mask, K, half, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  if (!kPairs) list.only = wave & 1;
+  list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
   Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the current unit and the two after it
-  if (nu > 0) {
-    list.rows(tile_of(0), un[0]);
-    copy.all(kb, un[0], lds0);
-  }
   const long long q0 = rows0 + (long long)c * kTile;  // first row of this query block
-  if (NW == 2 || wave < 2) {  // half w of Q and of dO_f by wavefront w
+  {
     UnitCopy<TL, CubeUnits<TL>> cq;
     cq.init(lane);
-    const Unit uq = {(unsigned)half * HALF, (unsigned)half * HALF + HALF / 2, 0};
-    cq.all((const unsigned char*)uniform_ptr(q + q0 * CPR), uq, lds0 + 3 * HALF);
-    cq.all((const unsigned char*)uniform_ptr(dof + q0 * CPR), uq, lds0 + HALF);
+    const unsigned char* qb = (const unsigned char*)uniform_ptr(q + q0 * CPR);
+    const unsigned char* db = (const unsigned char*)uniform_ptr(dof + q0 * CPR);
+    const Unit lo = {0, HALF / 2, 0}, hi = {HALF, HALF + HALF / 2, 0};
+    if (paired) {
+      cq.all(qb, lo, lds0 + 3 * HALF);
+      cq.all(qb, hi, lds0 + 2 * HALF);
+      cq.all(db, lo, lds0 + HALF);
+      cq.all(db, hi, lds0);
+    } else if (NW == 2 || wave < 2) {
+      cq.all(qb, wave & 1 ? hi : lo, lds0 + 3 * HALF);
+      cq.all(db, wave & 1 ? hi : lo, lds0 + HALF);
+    }
   }
-  if (nu > 0) copy.all(vb, un[0], lds0 + 2 * HALF);
-  list.load_masks();
   // row terms of the lane's two query columns: -lse*log2(e)/sl2 (-30000 on pad rows: then P = 0 and the row
   // contributes nothing) and -Delta
   const float* qterm = rowd + 2 * q0 + l32;
   float nlse[2] = {qterm[0], qterm[64]}, ndelta[2] = {qterm[32], qterm[96]};
+  list.arrived();
+  const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(masks)) + (unsigned)wave * 512u;
+  request_masks(list, ml0);
+  auto copy_first = [&]() {
+    list.rows(tile_of(0), half_of(0), un[0]);
+    copy.all(kb, un[0], lds0);
+    copy.all(vb, un[0], lds0 + 2 * HALF);
+  };
+  if (!paired && nu > 0) copy_first();
   f32x16 acc[DVB][2];
 #pragma unroll
   for (int x = 0; x < DVB; ++x)
@@ -119,21 +143,23 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
   for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
     for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
-  asm volatile("" : "+v"(list.km_v), "+v"(nlse[0]), "+v"(nlse[1]), "+v"(ndelta[0]), "+v"(ndelta[1]));
-  if (nu > 0) list.get(tile_of(0), un[0]);
-  if (nu > 1) list.get(tile_of(1), un[1]);
+  asm volatile("" : "+v"(nlse[0]), "+v"(nlse[1]), "+v"(ndelta[0]), "+v"(ndelta[1]));
   wait_vmcnt<0>();
-  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  if (!paired) __syncthreads();
   bf16x8 qreg[2][KS], doreg[2][KS];
   {
+    // halves of a wavefront's own: stages 3 and 2 (Q), 1 and 0 (dO_f); shared: stages 3 and 1 of the first two wavefronts
+    const unsigned char* base = smem + (paired ? wave * (4 * HALF) : 0);
+    const unsigned char* base1 = paired ? base - HALF : base + 4 * HALF;
     const int lane_q = TL::rowmajor_lane(0, lane);
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        qreg[b][s] = TL::rowmajor_at(smem + (4 * b + 3) * HALF, lane_q, s);
-        doreg[b][s] = TL::rowmajor_at(smem + (4 * b + 1) * HALF, lane_q, s);
-      }
+    for (int s = 0; s < KS; ++s) {
+      qreg[0][s] = TL::rowmajor_at(base + 3 * HALF, lane_q, s);
+      qreg[1][s] = TL::rowmajor_at(base1 + 3 * HALF, lane_q, s);
+      doreg[0][s] = TL::rowmajor_at(base + HALF, lane_q, s);
+      doreg[1][s] = TL::rowmajor_at(base1 + HALF, lane_q, s);
+    }
   }
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -142,11 +168,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
       pin_op(qreg[b][s]);
       pin_op(doreg[b][s]);
     }
-  __syncthreads();  // every wavefront has Q and dO_f: the second stages may be filled
+  if (!paired) __syncthreads();  // every wavefront has Q and dO_f: the second stages may be filled
+  take_masks(list, masks + wave * 128);
+  if (paired && nu > 0) copy_first();
+  if (nu > 0) list.get(tile_of(0), half_of(0), un[0]);
   if (nu > 1) {
+    list.get(tile_of(1), half_of(1), un[1]);
     copy.all(kb, un[1], lds0 + HALF);
     copy.all(vb, un[1], lds0 + 3 * HALF);
+    wait_vmcnt<2 * NC>();  // the first unit has landed; newer: the second
+  } else {
+    wait_vmcnt<0>();
   }
+  __builtin_amdgcn_sched_barrier(0);
 
   const int my = wave * (4 * HALF);
   const int lane_a = TL::rowmajor_lane(0, lane) + my;
@@ -303,13 +337,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     const std::integral_constant<int, 0> last;
     int u = 0;
     for (; u + 3 < nu; u += 2) {
-      list.get(tile_of(u + 2), un[2]);
+      list.get(tile_of(u + 2), half_of(u + 2), un[2]);
       body(steady, 0, u);
-      list.get(tile_of(u + 3), un[2]);
+      list.get(tile_of(u + 3), half_of(u + 3), un[2]);
       body(steady, 1, u + 1);
     }
     for (; u + 1 < nu; ++u) {
-      if (u + 2 < nu) list.get(tile_of(u + 2), un[2]);
+      if (u + 2 < nu) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
       body(inner, u & 1, u);
     }
     body(last, u & 1, u);
@@ -321,52 +355,62 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
   __builtin_amdgcn_sched_barrier(0);
 
-  // the pooled-gradient term of this thread's column chunk (the same chunk for all of its items),
-  // requested before the partial results go through LDS
-  static_assert(NT % CPR == 0, "a thread keeps its column chunk");
-  const int ch = tid % CPR;
-  const float* dqcr = dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks
-  const float4 pc0 = *(const float4*)dqcr, pc1 = *(const float4*)(dqcr + 4);
+  // Merge the partial results of the block's wavefronts (P of them), scale, add the pooled-gradient term, store.
   const uint64_t qmask = mask[c];
   const float inv_cnt = 1.0f / (float)cube_count(mask, c, m_blocks);
-  __syncthreads();  // every wavefront is done with its stages
-  {
-    float* Op = (float*)smem + wave * 64 * OS;
+  auto finish = [&](auto parts_tag, auto once_tag) {
+    constexpr bool ONCE = decltype(once_tag)::value;
+    constexpr int P = decltype(parts_tag)::value, NT = 64 * P, LPT = kTile * CPR / NT;
+    static_assert(NT % CPR == 0, "a thread keeps its column chunk");
+    const int t = P == 1 ? lane : tid, ch = t % CPR;
+    float* const bufs = (float*)smem + (P == 1 ? wave * 64 * OS : 0);
+    // the pooled-gradient term of this thread's column chunk, requested before the partial results go through LDS
+    const float* dqcr = dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks
+    const float4 pc0 = *(const float4*)dqcr, pc1 = *(const float4*)(dqcr + 4);
+    if (P > 1) __syncthreads();  // every wavefront is done with its stages
+    {
+      float* Op = bufs + (P == 1 ? 0 : wave) * 64 * OS;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int x = 0; x < DVB; ++x)
+        for (int x = 0; x < DVB; ++x)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-              make_float4(acc[x][b][4 * g4], acc[x][b][4 * g4 + 1], acc[x][b][4 * g4 + 2], acc[x][b][4 * g4 + 3]);
-  }
-  __syncthreads();
+          for (int g4 = 0; g4 < 4; ++g4)
+            *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
+                make_float4(acc[x][b][4 * g4], acc[x][b][4 * g4 + 1], acc[x][b][4 * g4 + 2], acc[x][b][4 * g4 + 3]);
+    }
+    if (P > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses stay in order)
 
-  const float pooled[8] = {pc0.x * inv_cnt, pc0.y * inv_cnt, pc0.z * inv_cnt, pc0.w * inv_cnt,
-                           pc1.x * inv_cnt, pc1.y * inv_cnt, pc1.z * inv_cnt, pc1.w * inv_cnt};
+    const float pooled[8] = {pc0.x * inv_cnt, pc0.y * inv_cnt, pc0.z * inv_cnt, pc0.w * inv_cnt,
+                             pc1.x * inv_cnt, pc1.y * inv_cnt, pc1.z * inv_cnt, pc1.w * inv_cnt};
 #pragma unroll
-  for (int it = 0; it < LPT; ++it) {
-    const int r = (it * NT + tid) / CPR;
-    const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-    float4 a = *(const float4*)((const float*)smem + m0), b = *(const float4*)((const float*)smem + m1);
+    for (int it = 0; it < LPT; ++it) {
+      const int r = (it * NT + t) / CPR;
+      const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
+      float4 a = *(const float4*)(bufs + m0), b = *(const float4*)(bufs + m1);
 #pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      const float4 x = *(const float4*)((const float*)smem + w * 64 * OS + m0);
-      const float4 y = *(const float4*)((const float*)smem + w * 64 * OS + m1);
-      a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
-      b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
+      for (int w = 1; w < P; ++w) {
+        const float4 x = *(const float4*)(bufs + w * 64 * OS + m0);
+        const float4 y = *(const float4*)(bufs + w * 64 * OS + m1);
+        a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
+        b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
+      }
+      const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      uint4 ov = make_uint4(0, 0, 0, 0);
+      if ((qmask >> r) & 1) {
+        float res[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], scale, pooled[e]);
+        ov = pack8(res);
+      }
+      store16<ONCE>(dq + (q0 + r) * CPR + ch, ov);
     }
-    const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint4 ov = make_uint4(0, 0, 0, 0);
-    if ((qmask >> r) & 1) {
-      float res[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], scale, pooled[e]);
-      ov = pack8(res);
-    }
-    dq[(q0 + r) * CPR + ch] = ov;
-  }
+  };
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, NW> all;
+  if (paired) stream ? finish(one, std::true_type{}) : finish(one, std::false_type{});
+  else stream ? finish(all, std::true_type{}) : finish(all, std::false_type{});
 }
 
 // Up to this many query blocks, four wavefronts per workgroup, as in the forward.  (d = 64, top-33: 324 blocks 31.0 against
@@ -380,9 +424,11 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
                               hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
+  const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
+  const unsigned pairs = grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>) ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
 #define VSA_DQ(D_, NW_, LIST_)                                                                                          \
-  k_fine_bwd_dq<D_, NW_, LIST_><<<grid, 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
-                                                (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks)
+  k_fine_bwd_dq<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
+                                                (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks, grid, pairs, stream)
 #define VSA_DQ_NW(D_, LIST_)                        \
   do {                                              \
     if (grid <= kDqFourWaves<D_>) VSA_DQ(D_, 4, LIST_); \

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
                                                          const float* __restrict__ rowd,
                                                          const float* __restrict__ dkc, const float* __restrict__ dvc,
                                                          const uint64_t* __restrict__ mask, uint4* __restrict__ dk,
-                                                         uint4* __restrict__ dv, int m_blocks) {
+                                                         uint4* __restrict__ dv, int m_blocks, int stream) {
   using TL = Tile<D>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
   constexpr int EPR = NW / 2;              // list entries a round of units takes
@@ -459,65 +459,70 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
 
   // Add the partial results in wavefront order through LDS: dK, then dV.
   static_assert(NW * 64 * OS * 4 <= (int)sizeof(smem), "merge buffers must fit");
+  auto finish = [&](auto once_tag) {
+    constexpr bool ONCE = decltype(once_tag)::value;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    __syncthreads();
-    float* bufs = (float*)smem;  // [wavefront][64][OS]
-    {
-      float* Op = bufs + wave * 64 * OS;
+    for (int pass = 0; pass < 2; ++pass) {
+      __syncthreads();
+      float* bufs = (float*)smem;  // [wavefront][64][OS]
+      {
+        float* Op = bufs + wave * 64 * OS;
 #pragma unroll
-      for (int x = 0; x < DVB; ++x)
+        for (int x = 0; x < DVB; ++x)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+          for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x16& a = pass == 0 ? dka[x][b] : dva[x][b];
-            *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-                make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
-          }
-    }
-    __syncthreads();
-    const float4 q0 = pass == 0 ? pk[0] : pv[0], q1 = pass == 0 ? pk[1] : pv[1];
-    const float pooled[8] = {q0.x * inv_cnt, q0.y * inv_cnt, q0.z * inv_cnt, q0.w * inv_cnt,
-                             q1.x * inv_cnt, q1.y * inv_cnt, q1.z * inv_cnt, q1.w * inv_cnt};
-    const float mul = pass == 0 ? scale : 1.0f;
-    uint4* dst = pass == 0 ? dk : dv;
-    float* slot_dst = parts + ((bh * cap + slot) * 2 + pass) * (long long)(64 * D);
-#pragma unroll
-    for (int it = 0; it < LPT; ++it) {
-      const int item = it * NT + tid, r = item / CPR, ch = item % CPR;
-      const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-      float4 a = *(const float4*)(bufs + m0), b = *(const float4*)(bufs + m1);
-#pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        const float4 x = *(const float4*)(bufs + w * 64 * OS + m0), y = *(const float4*)(bufs + w * 64 * OS + m1);
-        a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
-        b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
+            for (int g4 = 0; g4 < 4; ++g4) {
+              const f32x16& a = pass == 0 ? dka[x][b] : dva[x][b];
+              *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
+                  make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
+            }
       }
-      if (slot >= 0) {  // one run of a split list: raw fp32 sums [dK | dV][64][D], finished by k_dkv_reduce
-        float4* o = (float4*)(slot_dst + r * D + ch * 8);
-        o[0] = a;
-        o[1] = b;
-        continue;
-      }
-      const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-      uint4 ov = make_uint4(0, 0, 0, 0);
-      if ((kmask >> r) & 1) {
-        float res[8];
-        if (SUB) {
-          float pl[8];
-          subcube_pooled_term(pass == 0 ? dkc : dvc, (bh * Nc + j) * 4, kmask, r, D, ch, pl);
+      __syncthreads();
+      const float4 q0 = pass == 0 ? pk[0] : pv[0], q1 = pass == 0 ? pk[1] : pv[1];
+      const float pooled[8] = {q0.x * inv_cnt, q0.y * inv_cnt, q0.z * inv_cnt, q0.w * inv_cnt,
+                               q1.x * inv_cnt, q1.y * inv_cnt, q1.z * inv_cnt, q1.w * inv_cnt};
+      const float mul = pass == 0 ? scale : 1.0f;
+      uint4* dst = pass == 0 ? dk : dv;
+      float* slot_dst = parts + ((bh * cap + slot) * 2 + pass) * (long long)(64 * D);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pl[e]);
-        } else {
+      for (int it = 0; it < LPT; ++it) {
+        const int item = it * NT + tid, r = item / CPR, ch = item % CPR;
+        const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
+        float4 a = *(const float4*)(bufs + m0), b = *(const float4*)(bufs + m1);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pooled[e]);
+        for (int w = 1; w < NW; ++w) {
+          const float4 x = *(const float4*)(bufs + w * 64 * OS + m0), y = *(const float4*)(bufs + w * 64 * OS + m1);
+          a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
+          b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
         }
-        ov = pack8(res);
+        if (slot >= 0) {  // one run of a split list: raw fp32 sums [dK | dV][64][D], finished by k_dkv_reduce
+          float4* o = (float4*)(slot_dst + r * D + ch * 8);
+          o[0] = a;
+          o[1] = b;
+          continue;
+        }
+        const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        uint4 ov = make_uint4(0, 0, 0, 0);
+        if ((kmask >> r) & 1) {
+          float res[8];
+          if (SUB) {
+            float pl[8];
+            subcube_pooled_term(pass == 0 ? dkc : dvc, (bh * Nc + j) * 4, kmask, r, D, ch, pl);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pl[e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pooled[e]);
+          }
+          ov = pack8(res);
+        }
+        store16<ONCE>(dst + (rows0 + j * kTile + r) * CPR + ch, ov);
       }
-      dst[(rows0 + j * kTile + r) * CPR + ch] = ov;
     }
-  }
+  };
+  if (stream) finish(std::true_type{});
+  else finish(std::false_type{});
 }
 
 // Sums the fp32 partial results of the split lists in slot order and finishes them like the dK/dV
@@ -585,6 +590,7 @@ hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const 
                                const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const int items = Nc + cap;
+  const int stream = (long long)BH * Nc * kTile * d * 2 >= kStreamBytes;
   const unsigned grid = dkv_grid(BH, items), rgrid = (unsigned)(BH * (cap / 2));
 #define VSA_DKV(D_, SUB_)                                                                                                \
   do {                                                                                                                   \
@@ -595,7 +601,7 @@ hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const 
   do {                                                                                                                   \
     k_fine_bwd_dkv<D_, NW_, SUB_><<<grid, 64 * NW_, 0, s>>>(BH, Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v,    \
                                                   (const uint4*)dof, col, order, items, parts, cap, rowd,                \
-                                                  dkc, dvc, mask, (uint4*)dk, (uint4*)dv, m_blocks);                      \
+                                                  dkc, dvc, mask, (uint4*)dk, (uint4*)dv, m_blocks, stream);              \
     k_dkv_reduce<D_, SUB_><<<rgrid, 256, 0, s>>>(Nc, cap, scale, split, parts, dkc, dvc, mask, (uint4*)dk, (uint4*)dv,    \
                                                  m_blocks);                                                              \
   } while (0)

@@ -1,12 +1,12 @@
 // Fine stage forward (Sec. 2.2 fine stage; Sec. 2.1 attention equation under the block mask)
 // fused with the gated combine O = O_c * G_c + O_f * G_f.
 //
-// One workgroup per (b, h, 64-row query block); "cube" below means such a block (a cube of 64*m tokens is m
-// consecutive blocks, and the lists the kernel gets name blocks).  A workgroup is two wavefronts (four where the
-// launch is too small to fill the chip), each with a list walk, LDS stages and an online softmax of its own:
-// it multiplies UNITS of 32 keys with all 64 query rows (unit_stream.h), so that every operand it reads from
-// LDS feeds two matrix instructions, and since nobody else reads its rows the loop has no barrier.  The partial
-// results are merged once, through LDS, at the end.
+// "Cube" below means a 64-row query block (a cube of 64*m tokens is m consecutive blocks, and the lists the kernel
+// gets name blocks).  A workgroup is two wavefronts (four where the launch is too small to fill the chip), each with a
+// list walk, LDS stages and an online softmax of its own: it multiplies UNITS of 32 keys with all 64 query rows
+// (unit_stream.h), so that every operand it reads from LDS feeds two matrix instructions, and since nobody else reads
+// its rows the loop has no barrier.  A workgroup takes one block, whose units its wavefronts share and whose partial
+// results they merge through LDS, or (d = 128) two blocks, one per wavefront: see paired_workgroups.
 //
 // Everything is computed transposed so that softmax statistics are per-lane scalars:
 //   S^T[key, q]  = K rows (A operand, row-major LDS reads) x Q^T (B operand, registers)
@@ -19,10 +19,14 @@
 // multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
 // one.  d = 64 takes two wavefronts per SIMD.
 //
-// What bounds it: instruction issue.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma, exp2, sum,
-// half a conversion per value; 24 LDS reads, 16 copies): 1650 cycles at 1.77 GHz where the matrix pipe needs 1024;
-// without waiting for any copy it is as fast, and without the copies 6 to 15 % faster.  About 7 us of a workgroup's
-// 80 are start-up, merge and stores, which nothing overlaps on its SIMD.
+// What bounds it: instruction issue and power.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma,
+// exp2, sum, half a conversion per value; 24 LDS reads, 16 copies): 1650 cycles where the matrix pipe needs 1024, at a
+// clock that falls as the chip fills (1.75 GHz; 2.1 while the last workgroups of a launch run).  Around the walk a wavefront
+// spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
+// normalising, gating and storing, which nothing overlaps on its SIMD: halved per block where a wavefront has a block of
+// its own.  That, one factor per lane instead of per row and item on the way out, and a start that waits for K alone:
+// 39936 tokens, 12 heads, d = 128, top-78 of 624 1257 -> 1225 us (i.i.d.); 16384 tokens, top-32 of 256 246 -> 233 us, without
+// a fine gate 288 -> 264 for the whole forward; 9 % to 17 % where lists are shorter (rules below).
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD (every operand fed one
 // matrix instruction; the vector work of one wavefront behind the matrix work of another): 39936 tokens, 12
 // heads, d = 128, top-78 of 624: 1.47 -> 1.28 ms (i.i.d. selections), 1.43 -> 1.22 ms (local ones); 16384 tokens,
@@ -84,12 +88,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
     const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
     uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
-    int m_blocks, unsigned* __restrict__ gang_arrived, unsigned gang_every) {
+    int m_blocks, unsigned blocks, unsigned pairs, int stream, unsigned* __restrict__ gang_arrived, unsigned gang_every) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
-  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
-  constexpr int EPR = NW / 2;           // tiles a round of units takes
+  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32;
   constexpr int HALF = TL::BYTES / 2;   // 32 rows
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int NPV = 2 * DVB;          // steps of the PV phase
@@ -97,6 +100,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   constexpr int kAhead = D == 128 ? 4 : 2;
   constexpr int kEarly = 7;             // of the 16 softmax items of a unit, those behind the PV phase before it
   constexpr int OS = D;
+  constexpr bool kPairs = D == 128 && NW == 2;  // (d = 64: two wavefronts per SIMD hide one another's start-up)
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
   __shared__ float ml[NW * 64 * 2];
@@ -118,21 +122,30 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   asm volatile("" : "+s"(block), "+v"(tid), "+s"(Nc), "+s"(K));
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
-  const unsigned wg = same_lists ? block : xcd_chunked_id(block, gridDim.x);
-  const int c = wg % Nc;
-  const long long bh = wg / Nc;
-  const int rot = same_lists ? ((c >> 3) & 15) % tiles : 0;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
-  const int first = wave >> 1, half = wave & 1;  // this wavefront's tiles: first, first + EPR, ...
-  const int nu = tiles > first ? (tiles - first + EPR - 1) / EPR : 0;
-  auto tile_of = [&](int u) { const int t = first + EPR * u + rot; return t >= tiles ? t - tiles : t; };
+  // the first `pairs` workgroups take two blocks, one per wavefront; the others one, whose units they share
+  const bool paired = kPairs && block < pairs;
+  const unsigned from = paired ? 0u : pairs, those = paired ? pairs : gridDim.x - pairs;
+  const unsigned id = same_lists ? block - from : xcd_chunked_id(block - from, those);
+  const unsigned wg = paired ? 2 * id + wave : 2 * pairs + id;
+  if (paired && wg >= blocks) return;  // (an odd number of blocks)
+  const int c = wg % Nc;
+  const long long bh = wg / Nc;
+  const int rot = same_lists ? ((paired ? c >> 4 : c >> 3) & 15) % tiles : 0;
+  const int nu = paired ? 2 * tiles : tiles > (wave >> 1) ? (tiles - (wave >> 1) + NW / 2 - 1) / (NW / 2) : 0;
+  auto tile_of = [&](int u) {
+    const int t = (paired ? u >> 1 : (wave >> 1) + (NW / 2) * u) + rot;
+    return t >= tiles ? t - tiles : t;
+  };
+  auto half_of = [&](int u) { return (paired ? u : wave) & 1; };
   const long long rows0 = bh * (long long)Nc * kTile;  // first row of this (b,h)
   const unsigned char* kb = (const unsigned char*)uniform_ptr(k + rows0 * CPR);
   const unsigned char* vb = (const unsigned char*)uniform_ptr(v + rows0 * CPR);
 
-  // Start-up: the list first (one round trip), then the copies of the first units and of Q (which waits in
-  // the second V stages of the first two wavefronts), then the key masks, all in flight together.
+  // Start-up: the list and Q (one round trip), then the key masks and the copies of the first units, of which the
+  // first products need K of the first alone.  Q waits in second stages: a wavefront of its own block has both halves
+  // of it, of V and then of K; where a block is shared the first two wavefronts have one each, of V.
   // O: accumulation registers where the kernel has them (one wavefront per SIMD)
   auto mfma_o = [](f32x16& acc, bf16x8 a, bf16x8 b) {
     if (D == 128) mfma_a(acc, a, b);
@@ -147,58 +160,73 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   copy.init(lane);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
   UL list;
-  list.init(idx + (bh * Nc + c) * (long long)K, mask, K, half, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  if (!kPairs) list.only = wave & 1;
   Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the units after the current one
   Unit u0 = {0, 0, 0};
-  bool second = false;  // unit 1 is requested already
-  if (nu > 0) {
-    list.rows(tile_of(0), u0);
-    copy.all(kb, u0, lds0);
-  }
-  if (NW == 2 || wave < 2) {  // half w of Q by wavefront w
+  list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  {
     UnitCopy<TL, CubeUnits<TL>> cq;
     cq.init(lane);
-    const Unit uq = {(unsigned)half * HALF, (unsigned)half * HALF + HALF / 2, 0};
-    cq.all((const unsigned char*)uniform_ptr(q + (rows0 + (long long)c * kTile) * CPR), uq, lds0 + 3 * HALF);
+    const unsigned char* qb = (const unsigned char*)uniform_ptr(q + (rows0 + (long long)c * kTile) * CPR);
+    const Unit q0 = {0, HALF / 2, 0}, q1 = {HALF, HALF + HALF / 2, 0};
+    if (paired) {
+      cq.all(qb, q0, lds0 + 3 * HALF);
+      cq.all(qb, q1, lds0 + HALF);
+    } else if (NW == 2 || wave < 2) {
+      cq.all(qb, wave & 1 ? q1 : q0, lds0 + 3 * HALF);
+    }
+  }
+  list.arrived();  // (and Q with it)
+  const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(ml)) + (unsigned)wave * 512u;
+  request_masks(list, ml0);
+  if (nu > 0) {
+    list.rows(tile_of(0), half_of(0), u0);
+    copy.all(kb, u0, lds0);
+  }
+  const bool second = !paired && nu > 1 && list.loaded(tile_of(1));  // unit 1 is requested already
+  if (second) {
+    list.rows(tile_of(1), half_of(1), un[0]);
+    copy.all(kb, un[0], lds0 + HALF);
   }
   if (nu > 0) copy.all(vb, u0, lds0 + 2 * HALF);
-  if (nu > 1 && list.loaded(tile_of(1))) {
-    list.rows(tile_of(1), un[0]);
-    copy.all(kb, un[0], lds0 + HALF);
-    second = true;
-  }
-  list.load_masks();
-  asm volatile("" : "+v"(list.km_v));
+  float nil = 0.f;
+  asm volatile("" : "+v"(nil));  // (made anew in every round: a vector of zeros kept from the first would be spilled)
 #pragma unroll
   for (int x = 0; x < DVB; ++x)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o[x][b][i] = 0.f;
+      for (int i = 0; i < 16; ++i) o[x][b][i] = nil;
 #pragma unroll
   for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
     for (int b = 0; b < 2; ++b) pin_o(o[x][b]);
-  if (nu > 0) list.get(tile_of(0), u0);
-  if (nu > 1) {
-    list.get(tile_of(1), un[0]);
-    if (!second) copy.all(kb, un[0], lds0 + HALF);
-  }
-  if (nu > 2) list.get(tile_of(2), un[1]);
-  wait_vmcnt<0>();
-  __syncthreads();
+  if (!paired) __syncthreads();
   bf16x8 qreg[2][KS];
   {
-    const int lane_q = TL::rowmajor_lane(0, lane) + 3 * HALF;
+    const unsigned char* first_half = smem + (paired ? wave * (4 * HALF) : 0) + 3 * HALF;
+    const unsigned char* second_half = smem + (paired ? wave * (4 * HALF) + HALF : 7 * HALF);
+    const int lane_q = TL::rowmajor_lane(0, lane);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      qreg[0][s] = TL::rowmajor_at(smem, lane_q, s);
-      qreg[1][s] = TL::rowmajor_at(smem + 4 * HALF, lane_q, s);
+      qreg[0][s] = TL::rowmajor_at(first_half, lane_q, s);
+      qreg[1][s] = TL::rowmajor_at(second_half, lane_q, s);
     }
   }
 #pragma unroll
   for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qreg[0][s]), "+v"(qreg[1][s]));
-  __syncthreads();  // every wavefront has Q: the second V stages may be filled
+  if (!paired) __syncthreads();  // every wavefront has Q: the second V stages may be filled
+  // the masks and K of the first unit have landed; newer: V of the first and, ahead of it, K of the second
+  if (second) wait_vmcnt<2 * NC>();
+  else wait_vmcnt<NC>();
+  __builtin_amdgcn_sched_barrier(0);
+  take_masks(list, ml + wave * 128);
+  if (nu > 0) list.get(tile_of(0), half_of(0), u0);
+  if (nu > 1) {
+    list.get(tile_of(1), half_of(1), un[0]);
+    if (!second) copy.all(kb, un[0], lds0 + HALF);
+  }
+  if (nu > 2) list.get(tile_of(2), half_of(2), un[1]);
 
   const int my = wave * (4 * HALF);
   const int lane_a = TL::rowmajor_lane(0, lane) + my;
@@ -270,6 +298,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (u0.valid != 0xffffffffu) add_bias(s0, u0.valid);
     __builtin_amdgcn_sched_barrier(0);  // (the matrix instructions above have waited for the reads of this stage)
     if (nu > 2) copy.all(kb, un[1], lds0);
+    // K(1) has landed; newer: K(2) and, where K(1) was requested early, V(0)
+    if (second && nu > 2) wait_vmcnt<2 * NC>();
+    else if (nu > 2) wait_vmcnt<NC>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < kAhead; ++s) kcur[s] = TL::rowmajor_at(smem + HALF, lane_a, s);
     valid = u0.valid;
@@ -371,7 +404,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     lsum[1] += tsum[1];
     // ---- PV(u) | the first of P(u+1), the copy of K(u+3), the first K operands of u+2
     const uint4 pc[2][2] = {{pb[0][0], pb[0][1]}, {pb[1][0], pb[1][1]}};
-    if (more3) list.get(tile_of(u + 3), un[2]);
+    if (more3) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 1");  // (two wait states between the moves to pc and the first matrix instruction)
 #pragma unroll
@@ -436,89 +469,132 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // `out` may be head-major [B,H,Np,D] or token-major [B,Np,H,D] (same batch stride): chunk ch of
   // tiled row n of head h of batch b sits at b*H*Np*CPR + h*out_head_stride + n*out_row_stride + ch
   const long long out0 = (bh / H) * ((long long)H * Nc * kTile * CPR) + (bh % H) * out_head_stride;
-  // ---- merge the wavefronts' partial results, normalise, gate, store
-  // The gates and the coarse output of this thread's items are requested first: they arrive while
-  // the partial results go through LDS.  Pad rows are loaded too (they exist in memory) and ignored.
-  static_assert(NT % CPR == 0, "a thread keeps its column chunk");
+  // ---- merge the partial results of the block's wavefronts (P of them), normalise, gate, store
   const uint64_t qmask = mask[c];
-  const int ch = tid % CPR;
-  uint4 gc_raw[LPT], gf_raw[LPT];
-  const float* ocr = oc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // O_c is per cube = m_blocks blocks
-  const float4 c0 = *(const float4*)ocr, c1 = *(const float4*)(ocr + 4);
+  auto finish = [&](auto parts_tag, auto once_tag) {
+    constexpr bool ONCE = decltype(once_tag)::value;
+    constexpr int P = decltype(parts_tag)::value, NT = 64 * P, LPT = kTile * CPR / NT, AT_ONCE = LPT < 8 ? LPT : 8;
+    static_assert(NT % CPR == 0, "a thread keeps its column chunk");
+    const int t = P == 1 ? lane : tid, ch = t % CPR;
+    float* const bufs = (float*)smem + (P == 1 ? wave * 64 * OS : 0);
+    // The gates and the coarse output of this thread's first items are requested first: they arrive while
+    // the partial results go through LDS.  Pad rows are loaded too (they exist in memory) and ignored.
+    const long long g0 = (rows0 + c * kTile + t / CPR) * CPR + ch;
+    uint4 gc_raw[AT_ONCE], gf_raw[AT_ONCE];
+    auto request = [&](int it) {
+      gc_raw[it % AT_ONCE] = load16<ONCE>(gc + g0 + it * NT);
+      gf_raw[it % AT_ONCE] = gf ? load16<ONCE>(gf + g0 + it * NT) : make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);  // bf16 ones
+    };
 #pragma unroll
-  for (int it = 0; it < LPT; ++it) {
-    const long long g = (rows0 + c * kTile + (it * NT + tid) / CPR) * CPR + ch;
-    gc_raw[it] = gc[g];
-    gf_raw[it] = gf ? gf[g] : make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);  // bf16 ones
-  }
-  __syncthreads();  // every wavefront is done with its stages
-  {
-    float* Op = (float*)smem + wave * 64 * OS;
+    for (int it = 0; it < AT_ONCE; ++it) request(it);
+    const float* ocr = oc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // O_c is per cube = m_blocks blocks
+    const float4 c0 = *(const float4*)ocr, c1 = *(const float4*)(ocr + 4);
+
+    // M, L: reference and sum of a column.  (M = -inf: the list named no valid key at all -- only a caller-supplied
+    // list can, e.g. one made of dead key cubes -- or every logit of the column was -inf; the row then gets O_f = 0
+    // and lse = 0 instead of NaN)
+    auto logsum = [&](float M, float L) { return M == -INFINITY ? 0.f : (M + fast_log2(L)) * kLn2; };
+    auto merge = [&](int r, float& M, float& L, float& biggest) {
+      float m[P], l[P];
+#pragma unroll
+      for (int w = 0; w < P; ++w) {
+        m[w] = ml[(w * 64 + r) * 2];
+        l[w] = ml[(w * 64 + r) * 2 + 1];
+        biggest = fmaxf(biggest, l[w]);
+      }
+      M = m[0];
+#pragma unroll
+      for (int w = 1; w < P; ++w) M = fmaxf(M, m[w]);
+      L = 0.f;
+#pragma unroll
+      for (int w = 0; w < P; ++w) L += M == -INFINITY ? 0.f : l[w] * fast_exp2(m[w] - M);
+    };
+    // Up to two wavefronts normalise O on the way to LDS, one factor per lane and query half; four, whose threads have
+    // few rows each, save the barrier before it and weigh the parts row by row.
+    constexpr bool kByRow = P > 2;
+    float M[2], L[2], f[2] = {1.f, 1.f}, most = 0.f;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
+      M[b] = have && ref[b] > kNoRef ? ref[b] : -INFINITY;
+      L[b] = lsum[b] + __shfl_xor(lsum[b], 32);
+      most = fmaxf(most, L[b]);
+      if (P > 1 && h == 0) *(float2*)&ml[(wave * 64 + b * 32 + l32) * 2] = make_float2(M[b], L[b]);
+    }
+    if (P > 1) __syncthreads();  // (every wavefront is done with its stages, too)
+    if (!kByRow) {
 #pragma unroll
-      for (int x = 0; x < DVB; ++x)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-              make_float4(o[x][b][4 * g4], o[x][b][4 * g4 + 1], o[x][b][4 * g4 + 2], o[x][b][4 * g4 + 3]);
-      const float l = lsum[b] + __shfl_xor(lsum[b], 32);
-      if (h == 0) {
-        // (kNoRef: every logit of the column was -inf)
-        ml[(wave * 64 + b * 32 + l32) * 2] = have && ref[b] > kNoRef ? ref[b] : -INFINITY;
-        ml[(wave * 64 + b * 32 + l32) * 2 + 1] = l;
+      for (int b = 0; b < 2; ++b) {
+        const int r = b * 32 + l32;
+        const float mine = M[b];
+        if (P > 1) merge(r, M[b], L[b], most);
+        f[b] = M[b] == -INFINITY ? 0.f : (P > 1 ? fast_exp2(mine - M[b]) : 1.0f) / L[b];
+        if (lse_f && h == 0 && (P == 1 || wave == 0)) lse_f[rows0 + c * kTile + r] = (qmask >> r) & 1 ? logsum(M[b], L[b]) : 0.f;
       }
     }
-  }
-  __syncthreads();
+    {
+      float* Op = bufs + (P == 1 ? 0 : wave) * 64 * OS;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int x = 0; x < DVB; ++x)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4)
+            *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
+                make_float4(o[x][b][4 * g4] * f[b], o[x][b][4 * g4 + 1] * f[b], o[x][b][4 * g4 + 2] * f[b], o[x][b][4 * g4 + 3] * f[b]);
+    }
+    if (P > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses stay in order)
 
-  bool overflow = false;
+    const bool check = kByRow || __any(most > kTightSum);  // (only then can O have overflowed before it was normalised)
+    bool overflow = false;
+    uint4* const orow = out + out0 + (long long)(c * kTile + t / CPR) * out_row_stride + ch;
+    const float ocv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
 #pragma unroll
-  for (int it = 0; it < LPT; ++it) {
-    const int r = (it * NT + tid) / CPR;
-    float M = ml[r * 2], L = 0.f, most = 0.f, f[NW];
+    for (int it = 0; it < LPT; ++it) {
+      const int r = (it * NT + t) / CPR;
+      const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
+      float of[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, Mr = 0.f, Lr = 1.f, seen = 0.f;
+      if (kByRow) merge(r, Mr, Lr, seen);
+      const float inv = Mr == -INFINITY ? 0.f : 1.0f / Lr;
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[(w * 64 + r) * 2]);
-    // (M = -inf: the list named no valid key at all -- only a caller-supplied list can, e.g. one made of
-    // dead key cubes; the row then gets O_f = 0 and lse = 0 instead of NaN)
-    const bool none = M == -INFINITY;
+      for (int w = 0; w < P; ++w) {
+        const float4 x = *(const float4*)(bufs + w * 64 * OS + m0), y = *(const float4*)(bufs + w * 64 * OS + m1);
+        const float part_of[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        const float fw = !kByRow ? 1.f : (Mr == -INFINITY ? 0.f : fast_exp2(ml[(w * 64 + r) * 2] - Mr) * inv);
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      f[w] = none ? 0.f : fast_exp2(ml[(w * 64 + r) * 2] - M);
-      L += ml[(w * 64 + r) * 2 + 1] * f[w];
-      most = fmaxf(most, ml[(w * 64 + r) * 2 + 1]);
-    }
-    const float inv = none ? 0.f : 1.0f / L;
-    const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-    float of[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, res[8];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float* Op = (const float*)smem + w * 64 * OS;
-      const float4 a0 = *(const float4*)(Op + m0), a1 = *(const float4*)(Op + m1);
-      const float fw = f[w] * inv;
-      of[0] = fmaf(a0.x, fw, of[0]); of[1] = fmaf(a0.y, fw, of[1]); of[2] = fmaf(a0.z, fw, of[2]); of[3] = fmaf(a0.w, fw, of[3]);
-      of[4] = fmaf(a1.x, fw, of[4]); of[5] = fmaf(a1.y, fw, of[5]); of[6] = fmaf(a1.z, fw, of[6]); of[7] = fmaf(a1.w, fw, of[7]);
-    }
-    const long long g = (rows0 + c * kTile + r) * CPR + ch;
-    uint4 ov = make_uint4(0, 0, 0, 0), fv = make_uint4(0, 0, 0, 0);
-    if ((qmask >> r) & 1) {
-      float gcv[8], gfv[8];
-      unpack8(gc_raw[it], gcv);
-      unpack8(gf_raw[it], gfv);
-      const float ocv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+        for (int e = 0; e < 8; ++e) of[e] = kByRow ? fmaf(part_of[e], fw, of[e]) : w == 0 ? part_of[e] : of[e] + part_of[e];
+      }
+      float gcv[8], gfv[8], res[8];
+      unpack8(gc_raw[it % AT_ONCE], gcv);
+      unpack8(gf_raw[it % AT_ONCE], gfv);
+      if (it + AT_ONCE < LPT) request(it + AT_ONCE);
 #pragma unroll
       for (int e = 0; e < 8; ++e) res[e] = fmaf(ocv[e], gcv[e], of[e] * gfv[e]);
-      ov = pack8(res);
-      fv = pack8(of);
-      float nought = 0.f;
+      const bool live = (qmask >> r) & 1;
+      uint4 ov = pack8(res), fv = pack8(of);
+      if (!live) ov = fv = make_uint4(0, 0, 0, 0);
+      if (check) {
+        float nought = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) nought = fmaf(of[e], 0.f, nought);  // NaN unless all of them are finite
-      overflow |= most > kTightSum && nought != 0.f;
+        for (int e = 0; e < 8; ++e) nought = fmaf(of[e], 0.f, nought);  // NaN unless all of them are finite
+        overflow |= live && nought != 0.f && (!kByRow || seen > kTightSum);
+      }
+      store16<ONCE>(orow + (long long)(it * (NT / CPR)) * out_row_stride, ov);
+      if (out_fine) out_fine[g0 + it * NT] = fv;
+      if (kByRow && lse_f && ch == 0) lse_f[rows0 + c * kTile + r] = live ? logsum(Mr, Lr) : 0.f;
+      if (LPT > AT_ONCE) __builtin_amdgcn_sched_barrier(0);  // (item by item: the loads of later ones stay ahead of the stores)
     }
-    out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
-    if (out_fine) out_fine[g] = fv;
-    if (lse_f && ch == 0) lse_f[rows0 + c * kTile + r] = (((qmask >> r) & 1) && !none) ? (M + fast_log2(L)) * kLn2 : 0.f;
+    return overflow;
+  };
+  if constexpr (kPairs) {
+    if (paired) {
+      const bool overflow = stream ? finish(std::integral_constant<int, 1>{}, std::true_type{}) : finish(std::integral_constant<int, 1>{}, std::false_type{});
+      if (tight || !__any(overflow)) return;
+      continue;
+    }
   }
+  const std::integral_constant<int, NW> all;
+  const bool overflow = stream ? finish(all, std::true_type{}) : finish(all, std::false_type{});
   if (tight) return;
   if (overflow) again = 1;
   __syncthreads();
@@ -526,28 +602,31 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Which kernel, by the number of query blocks and of 64-key tiles in a list (times in us: one head size, lists of N(0,1)
-// inputs, B*H*Nb from 64 to 7488).  512 workgroups of the d = 128 kernels are on the chip at a time, 1024 of the d = 64
-// kernel with two wavefronts, 512 of the one with four.
+// Which kernel, by the number of query blocks and of 64-key tiles in a list (lists of N(0,1) inputs, one head size, 288 to
+// 8192 blocks, 1 to 56 tiles; figures: time of the general kernel over that of the other).
 //
 // The kernel for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile:
-//   d = 128  full generations: 384 blocks, 6 tiles 17.7 against 17.4; 512, 8 tiles 21.0 / 22.4, 12 tiles 25.0 / 24.4; 1024, 20 tiles 59.5 / 60.1, 24
-//            tiles 69.5 / 67.2; 3072, 20 tiles 165 / 166, 33 tiles 246 / 237.  A last generation that is at most half
-//            full costs the general kernel more, the less the more generations there are: 576 blocks, 16 tiles 40.3 / 43.9,
-//            56 tiles 104 / 108; 1152, 16 tiles 62.2 / 69.5, 48 tiles 145 / 149; 1600, 28 tiles 127 / 134; 4160, 24 tiles 1.02.
-//   d = 64   up to 14 tiles, unless the blocks just fill the chip with two-wavefront workgroups (1024 blocks, 12 tiles 27.4 /
-//            23.8) or there are generations enough (4160, 12 tiles 0.95).
-//   one or two tiles: 256 blocks 7.3 / 7.8, 9.2 / 9.6.
+//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup).  Where the last one is nearly empty, it
+//            loses: 576 blocks, 3 tiles 1.05, 14 1.03, 20 0.99, 56 0.93; 768, 14 1.04, 20 1.03; 1152, 20 1.06, 34 1.05, 44 0.99;
+//            2304, 20 1.03, 28 0.99; 1536, 6 1.06, 20 0.99; 1728, 20 1.02, 24 1.00; 2688, 8 1.02, 20 0.98; 1920, 6 1.03, 12 1.00.
+//            Elsewhere it wins: 480, 4 0.98, 12 0.94; 960, 8 0.93; 2048, 8 0.95, 20 0.92; 3072 and more from 0.99 at 3 tiles
+//            to 0.91 at 12; 8192, 12 0.85.
+//   d = 64   768 blocks, 4 tiles 0.97; 1152, 4 1.07, 14 1.02; 1536, 8 1.09; 2016, 4 1.00, 12 0.93; 2048, 8 1.02; 3456, 3 1.08,
+//            8 0.98; 7488, 2 0.88.
+//   256 blocks, one or two tiles: 1.07, 1.04.
 inline bool fwd_short(int d, unsigned grid, int tiles) {
-  if (tiles <= 2) return true;
-  if (d == 128) {
-    const unsigned full = grid / 512, last = grid % 512;
-    if (grid <= 256) return false;
-    if (grid <= 512) return tiles <= (grid > 448 ? 12 : 8);
-    return tiles <= (last > 0 && last <= 256 ? 20 + 40 / (int)full : 20);
+  if (grid <= 256) return tiles <= 2;
+  if (d == 64) {
+    if (grid <= 1024 || grid > 5000) return false;
+    return tiles <= (grid < 1664 ? 14 : grid < 2048 ? 4 : grid < 3072 ? 10 : 3);
   }
-  if (grid <= 512 || (grid > 768 && grid <= 1024) || grid > 4096) return false;
-  return tiles <= (grid <= 2560 ? 14 : 8);
+  if (grid <= 512 || grid >= 3072) return false;
+  const int full = (int)(grid / 1024), rest = (int)(grid % 1024);
+  if (full == 0) return grid <= 768 && tiles <= 16;
+  if (rest == 0) return tiles <= 3;
+  if (rest <= 256) return tiles <= 8 + 32 / full;
+  if (rest <= 512) return tiles <= 10;
+  return tiles <= (rest <= 768 ? 20 : 8) / full;
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
 // with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks
@@ -557,6 +636,7 @@ inline bool fwd_four_waves(int d, unsigned grid, int tiles) {
   return grid <= 512 || (tiles > 14 && grid <= 2560 && !(grid > 768 && grid <= 1024));
 }
 
+
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
@@ -564,6 +644,8 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
+  const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
+  const unsigned pairs = d == 64 || fwd_four_waves(d, grid, tiles) ? 0 : paired_workgroups(grid, 512);
   if (fwd_short(d, grid, tiles))
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
                                  out_token_major, m_blocks, key_cubes_16, s);
@@ -577,7 +659,7 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const size_t head = (size_t)Nc * kTile * d * 4;  // bytes of its K and V
   const bool gangs = d == 128 && tiles < Nc &&
                      ((head >= ((size_t)22 << 20) && grid >= 8192) || (head >= ((size_t)64 << 20) && grid >= 1024));
-  const unsigned every = gangs ? (unsigned)(255 / tiles + 1) : 1u;
+  const unsigned every = gangs ? (unsigned)(127 / tiles + 1) : 1u;
   unsigned* arrived = gangs ? gang_scratch : nullptr;
   if (gangs) {
     const unsigned n = 8 * ((grid / 8 + kGang) / kGang + 1);  // (at most BH*Nc/32 + 24 counters)
@@ -586,9 +668,9 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
 #define VSA_FWD(D_, NW_, LIST_)                                                                                      \
-  k_fine_fwd<D_, NW_, LIST_><<<grid, 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
+  k_fine_fwd<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, arrived, every)
+                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every)
 #define VSA_FWD_NW(D_, LIST_)                     \
   do {                                            \
     if (fwd_four_waves(D_, grid, tiles)) VSA_FWD(D_, 4, LIST_); \

@@ -41,10 +41,12 @@ __device__ __forceinline__ void lds_dma16_at(const void* base, unsigned voff) {
 __device__ __forceinline__ void set_m0(unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "m0", "memory");
 }
+// (NOPS 4: for a base that the compiler may fetch from a vector register right before, which takes 5 wait states)
+template <int NOPS = 0>
 __device__ __forceinline__ void lds_dma4(const void* base, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop %3\n\tglobal_load_lds_dword %0, %1"
                :
-               : "v"(voff), "s"(base), "s"(lds_addr)
+               : "v"(voff), "s"(base), "s"(lds_addr), "n"(NOPS)
                : "memory", "m0");
 }
 #pragma clang diagnostic pop

@@ -1,6 +1,6 @@
 // The stream of the forward and the dQ kernel: UNITS of 32 key rows, each copied by the one wavefront that
-// multiplies it, global -> LDS, into stages of that wavefront's own.  A workgroup's list is walked in
-// tiles of 64 keys; wavefront w takes half w & 1 of the tiles w >> 1, (w >> 1) + NW/2, ...
+// multiplies it, global -> LDS, into stages of that wavefront's own.  A list is walked in tiles of 64 keys = two
+// units each; of P wavefronts that share a list wavefront w takes the units w, w + P, ...
 //
 // A unit is two groups of 16 consecutive LDS rows whose sources may lie apart (lists that name key cubes of
 // 16 tokens gather a tile from four entries).  The list sits in a register, 64 entries at a time (lane e
@@ -24,39 +24,49 @@ template <class TL>
 struct CubeUnits {
   const int32_t* list;
   const uint64_t* mask;
-  int n, half, lane, chunk, idx_v, ncubes;
-  uint32_t km_v;
+  int n, lane, chunk, idx_v, ncubes;
+  int only = -1;     // the half that all units of this wavefront are (-1: both)
+  uint32_t km_v[2];  // valid-key bits of the two halves of the lane's entry
   static constexpr int kEntriesPerTile = 1, kTilesPerChunk = 64;
   static constexpr bool kContiguous = true;  // a unit's 32 rows lie one behind the other
+  __device__ __forceinline__ void arrived() {
+    asm volatile("" : "+v"(idx_v));  // consumed here: the compiler's wait for the load is placed right here
+    idx_v = clamp_cube(idx_v, ncubes);  // (a caller-supplied list is not trusted)
+  }
   __device__ __forceinline__ void load_indices(int c) {
     chunk = c;
     idx_v = list[list_slot(c, lane, n)];
-    asm volatile("" : "+v"(idx_v));  // consumed at once: the compiler's wait for the load is placed right here
-    idx_v = clamp_cube(idx_v, ncubes);  // (a caller-supplied list is not trusted)
+    arrived();
   }
-  __device__ __forceinline__ void load_masks() {
-    const uint64_t m = mask[idx_v];
-    km_v = half ? (uint32_t)(m >> 32) : (uint32_t)m;
+  __device__ __forceinline__ int mask_block() const { return idx_v; }
+  __device__ __forceinline__ void set_masks(uint64_t m) {
+    km_v[0] = (uint32_t)m;
+    km_v[1] = (uint32_t)(m >> 32);
+    if (only >= 0) km_v[0] = km_v[only ? 1 : 0];
   }
-  // (after init the offsets of the units of tile t's chunk are there; the valid-key bits come with load_masks)
-  __device__ __forceinline__ void init(const int32_t* list_, const uint64_t* mask_, int n_, int half_, int lane_,
-                                       int ncubes_, int t) {
-    list = list_, mask = mask_, n = n_, half = half_, lane = lane_, ncubes = ncubes_;
-    load_indices(t / kTilesPerChunk);
+  // (after arrived() the offsets of the units of tile t's chunk are there; the valid-key bits come with set_masks)
+  __device__ __forceinline__ void request(const int32_t* list_, const uint64_t* mask_, int n_, int lane_, int ncubes_, int t) {
+    list = list_, mask = mask_, n = n_, lane = lane_, ncubes = ncubes_;
+    chunk = t / kTilesPerChunk;
+    idx_v = list[list_slot(chunk, lane, n)];
   }
   __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
-  __device__ __forceinline__ void rows(int t, Unit& u) const {
+  __device__ __forceinline__ void rows(int t, int half, Unit& u) const {
     u.a = (unsigned)__builtin_amdgcn_readlane(idx_v, t & 63) * (unsigned)TL::BYTES + (unsigned)half * (TL::BYTES / 2);
     u.b = u.a + TL::BYTES / 4;
   }
-  __device__ __forceinline__ void get(int t, Unit& u) {
+  __device__ __forceinline__ void get(int t, int half, Unit& u) {
     if (!loaded(t)) {
       load_indices(t / kTilesPerChunk);
-      load_masks();
-      asm volatile("" : "+v"(km_v));
+      set_masks(mask[mask_block()]);
+      asm volatile("" : "+v"(km_v[0]), "+v"(km_v[1]));
     }
-    rows(t, u);
-    u.valid = (uint32_t)__builtin_amdgcn_readlane((int)km_v, t & 63);
+    rows(t, half, u);
+    u.valid = (uint32_t)__builtin_amdgcn_readlane((int)km_v[0], t & 63);
+    if (only < 0) {
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)km_v[1], t & 63);
+      u.valid = half ? hi : u.valid;
+    }
   }
   __device__ static __forceinline__ int source_row(int x) { return x; }
 };
@@ -67,38 +77,43 @@ template <class TL>
 struct SubCubeUnits {
   const int32_t* list;
   const uint64_t* mask;
-  int n, half, lane, chunk, idx_v, ncubes;
+  int n, lane, chunk, idx_v, ncubes;
+  int only = -1;  // (as in CubeUnits; of no use here)
   uint32_t km_v;  // 16 valid-key bits of the lane's entry
   static constexpr int kEntriesPerTile = 4, kTilesPerChunk = 16;
   static constexpr bool kContiguous = false;
-  __device__ __forceinline__ void load_indices(int c) {
-    chunk = c;
-    idx_v = list[list_slot(c, lane, n)];
+  __device__ __forceinline__ void arrived() {
     asm volatile("" : "+v"(idx_v));
     idx_v = clamp_cube(idx_v, 4 * ncubes);
   }
-  __device__ __forceinline__ void load_masks() { km_v = subcube_mask16(mask[idx_v >> 2], idx_v & 3); }
-  __device__ __forceinline__ void init(const int32_t* list_, const uint64_t* mask_, int n_, int half_, int lane_,
-                                       int ncubes_, int t) {
-    list = list_, mask = mask_, n = n_, half = half_, lane = lane_, ncubes = ncubes_;
-    load_indices(t / kTilesPerChunk);
+  __device__ __forceinline__ void load_indices(int c) {
+    chunk = c;
+    idx_v = list[list_slot(c, lane, n)];
+    arrived();
+  }
+  __device__ __forceinline__ int mask_block() const { return idx_v >> 2; }
+  __device__ __forceinline__ void set_masks(uint64_t m) { km_v = subcube_mask16(m, idx_v & 3); }
+  __device__ __forceinline__ void request(const int32_t* list_, const uint64_t* mask_, int n_, int lane_, int ncubes_, int t) {
+    list = list_, mask = mask_, n = n_, lane = lane_, ncubes = ncubes_;
+    chunk = t / kTilesPerChunk;
+    idx_v = list[list_slot(chunk, lane, n)];
   }
   __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
   __device__ __forceinline__ unsigned entry_offset(int e) const {  // e in the current chunk
     const int id = __builtin_amdgcn_readlane(idx_v, min(e, n - 1) & 63);
     return (unsigned)(id >> 2) * (unsigned)TL::BYTES + (unsigned)subcube_first_slot(id & 3) * (unsigned)TL::ROW_BYTES;
   }
-  __device__ __forceinline__ void rows(int t, Unit& u) const {
+  __device__ __forceinline__ void rows(int t, int half, Unit& u) const {
     u.a = entry_offset(4 * t + 2 * half);
     u.b = entry_offset(4 * t + 2 * half + 1);
   }
-  __device__ __forceinline__ void get(int t, Unit& u) {
+  __device__ __forceinline__ void get(int t, int half, Unit& u) {
     if (!loaded(t)) {
       load_indices(t / kTilesPerChunk);
-      load_masks();
+      set_masks(mask[mask_block()]);
       asm volatile("" : "+v"(km_v));
     }
-    rows(t, u);
+    rows(t, half, u);
     const int ea = 4 * t + 2 * half, eb = ea + 1;
     const uint32_t ma = (uint32_t)__builtin_amdgcn_readlane((int)km_v, ea & 63);
     const uint32_t mb = (uint32_t)__builtin_amdgcn_readlane((int)km_v, eb & 63);
@@ -106,6 +121,32 @@ struct SubCubeUnits {
   }
   __device__ static __forceinline__ int source_row(int x) { return subcube_slot(x); }
 };
+
+// Forward and dQ: a workgroup of two wavefronts takes one block, whose units they share, or two blocks, one each.  The
+// second form has half as many starts and nothing to merge, but its workgroups run twice as long; so all blocks are
+// paired where that takes no more generations of `places` workgroups -- with two workgroups' wavefronts on a SIMD, whose
+// speed depends on the other, where the last one is three quarters full -- else those of the generations that are full.
+// (dQ, d = 64: 1152 blocks all paired 1.10 times as long as none, 3456 1.05, 1536 0.95.)
+inline unsigned paired_workgroups(unsigned blocks, unsigned places) {
+  const unsigned rest = blocks % (2 * places), enough = places > 512 ? places + places / 2 - 1 : places;
+  return rest == 0 || rest > enough ? (blocks + 1) / 2 : blocks / (2 * places) * places;
+}
+inline unsigned workgroups(unsigned blocks, unsigned pairs) { return 2 * pairs >= blocks ? pairs : blocks - pairs; }
+
+// The masks of the first chunk's entries by way of LDS (512 bytes at `lds`), like the copies they precede: a load to
+// registers among the copies would make the compiler wait for all of them.
+template <class UNITS>
+__device__ __forceinline__ void request_masks(const UNITS& list, unsigned lds) {
+  const unsigned char* base = (const unsigned char*)list.mask;  // (a kernel argument)
+  const unsigned off = (unsigned)list.mask_block() * 8u;
+  lds_dma4<4>(base, off, lds);
+  lds_dma4<4>(base + 4, off, lds + 256);
+}
+template <class UNITS>
+__device__ __forceinline__ void take_masks(UNITS& list, const void* lds) {
+  const uint32_t* m = (const uint32_t*)lds + list.lane;
+  list.set_masks(m[0] | ((uint64_t)m[64] << 32));
+}
 
 // Copies of 32 rows by one wavefront (global_load_lds_dwordx4, see lds_dma16_at): instruction c fills rows c*RPI ..,
 // the swizzle is applied on the SOURCE side (the lane that writes physical chunk pc of row r fetches logical chunk

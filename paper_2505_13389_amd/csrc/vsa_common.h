@@ -46,6 +46,28 @@ __device__ __forceinline__ uint4 pack8(const float* f) {
   return u;
 }
 
+// Accesses to what a launch touches once, non-temporal if ONCE: then it does not push the tiles that other workgroups are
+// about to gather out of the L2, nor what the next kernels read out of the 256 MiB behind it.  Only for tensors too large
+// to be found there by those who read them next: forward+backward at 50 MiB a tensor 1036 -> 1000 us (top-8: 529 -> 477), at
+// 100 MiB 1.5 %; at 23 MiB the kernels that read a result in turn lose what its writer gains.
+constexpr long long kStreamBytes = 40ll << 20;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <bool ONCE>
+__device__ __forceinline__ uint4 load16(const uint4* p) {
+  if (!ONCE) return *p;
+  const u32x4 x = __builtin_nontemporal_load((const u32x4*)p);
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
+template <bool ONCE>
+__device__ __forceinline__ void store16(uint4* p, const uint4& v) {
+  if (!ONCE) {
+    *p = v;
+    return;
+  }
+  const u32x4 x = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(x, (u32x4*)p);
+}
+
 // Workgroups are dealt to the 8 XCDs (each with its own L2) round-robin by blockIdx.  This maps
 // blockIdx to a logical id such that every XCD works through one contiguous run of logical ids
 // (a bijection on [0, total) for any total): neighbouring query cubes, whose selected key cubes

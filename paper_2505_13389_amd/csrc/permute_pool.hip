@@ -7,14 +7,18 @@ namespace vsa {
 
 // One workgroup per 64 destination rows of one (b, h).  The first wavefront works out, one row per
 // lane, where each destination row comes from (the index arithmetic of the Sec. 2.2 equation, with
-// its integer divisions, once per row instead of once per 16-byte chunk); then all 256 threads copy,
-// several 16-byte chunks in flight per thread.
+// its integer divisions, once per row instead of once per 16-byte chunk); then all threads copy, several
+// 16-byte chunks in flight per thread: four with 256 threads, or, for tensors that no cache holds, two with 512 and
+// past the caches (39936 tokens, 12 heads, d = 128: token-major in 47.9 -> 40.7 us, out 42.4 -> 38.7; 92160 tokens, 40 heads
+// 326 -> 286, 289 -> 273.  At 17 MiB a tensor four with 256 are faster, 8.8 against 10.2 us).  Workgroups of the heads of
+// the same rows next to each other: slower, whole launch or XCD by XCD (46.5, 51.5 us).
 // Forward: destination = tiled row; its source is the raster row of the same (t,h,w), or zeros for
 // a pad slot.  Inverse: destination = raster row.  H > 0: the raster tensor is [B, L, H, d]
 // (token-major); H == 0: [B, H, L, d].
-template <bool kInverse>
-__global__ __launch_bounds__(256) void k_tile_permute(Geo g, int H, int chunks_per_row,
+template <bool kInverse, bool ONCE>
+__global__ __launch_bounds__(ONCE ? 512 : 256) void k_tile_permute(Geo g, int H, int chunks_per_row,
                                                       const uint4* __restrict__ src, uint4* __restrict__ dst) {
+  constexpr int NT = ONCE ? 512 : 256, U = 1024 / NT;
   __shared__ long long from[kTile], to[kTile];  // row numbers in units of rows; from < 0: a pad slot (zeros)
   const long long rows_dst = kInverse ? (long long)g.L : g.Np;
   const long long bh = blockIdx.y;
@@ -47,22 +51,22 @@ __global__ __launch_bounds__(256) void k_tile_permute(Geo g, int H, int chunks_p
   }
   __syncthreads();
   const int items = kTile * chunks_per_row;
-  for (int i0 = 0; i0 < items; i0 += 4 * 256) {
-    uint4 val[4];
-    long long dsta[4];
+  for (int i0 = 0; i0 < items; i0 += U * NT) {
+    uint4 val[U];
+    long long dsta[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int item = i0 + u * 256 + threadIdx.x, r = item / chunks_per_row, ch = item % chunks_per_row;
+    for (int u = 0; u < U; ++u) {
+      const int item = i0 + u * NT + threadIdx.x, r = item / chunks_per_row, ch = item % chunks_per_row;
       dsta[u] = -1;
       val[u] = make_uint4(0, 0, 0, 0);
       if (item < items && to[r] >= 0) {
         dsta[u] = to[r] * chunks_per_row + ch;
-        if (from[r] >= 0) val[u] = src[from[r] * chunks_per_row + ch];
+        if (from[r] >= 0) val[u] = load16<ONCE>(src + from[r] * chunks_per_row + ch);
       }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (dsta[u] >= 0) dst[dsta[u]] = val[u];
+    for (int u = 0; u < U; ++u)
+      if (dsta[u] >= 0) store16<ONCE>(dst + dsta[u], val[u]);
   }
 }
 
@@ -71,10 +75,17 @@ hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, const vo
   const int cpr = d / 8;
   const long long rows_dst = inverse ? (long long)g.L : g.Np;
   dim3 grid((unsigned)((rows_dst + kTile - 1) / kTile), (unsigned)BH);
-  if (inverse)
-    k_tile_permute<true><<<grid, 256, 0, s>>>(g, H_blhd, cpr, (const uint4*)src, (uint4*)dst);
-  else
-    k_tile_permute<false><<<grid, 256, 0, s>>>(g, H_blhd, cpr, (const uint4*)src, (uint4*)dst);
+  const bool stream = (long long)BH * g.Np * d * 2 >= kStreamBytes;
+#define VSA_PERMUTE(INV_, ONCE_) \
+  k_tile_permute<INV_, ONCE_><<<grid, ONCE_ ? 512 : 256, 0, s>>>(g, H_blhd, cpr, (const uint4*)src, (uint4*)dst)
+  if (inverse) {
+    if (stream) VSA_PERMUTE(true, true);
+    else VSA_PERMUTE(true, false);
+  } else {
+    if (stream) VSA_PERMUTE(false, true);
+    else VSA_PERMUTE(false, false);
+  }
+#undef VSA_PERMUTE
   return hipGetLastError();
 }
 

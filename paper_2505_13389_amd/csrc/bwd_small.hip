@@ -325,17 +325,17 @@ __device__ __forceinline__ int block_sum(int x, int* wsum, int tid) {
 // order among equal lengths is whatever the LDS atomics give, it only decides which workgroup
 // starts when).  An item is a key cube's whole list, or -- for a list longer than the split length
 // -- one of ceil(deg / length) nearly equal runs of it; each run of such a SPLIT list accumulates
-// fp32 partial dK, dV into a numbered slot, summed afterwards in slot order by k_dkv_reduce, so the
+// fp32 partial dK, dV into a numbered slot, summed in slot order by the last run to arrive, so the
 // result does not depend on which workgroup ran when.  The split length of a (b, h) is the smallest
 // one, not below `seg_min`, at which the runs of all its long lists fit into the `cap` slots the
 // slot buffer holds per (b, h): it depends on the in-degrees alone.
-//   order: one 16-byte descriptor (key cube, begin, end of the run in col, slot or -1) per dK/dV
-//          workgroup, Nc + cap of them per (b, h); unused ones carry key cube -1
+//   order: one 16-byte descriptor (key cube, begin, end of the run in col, slot + 65536 * number of the split list or -1)
+//          per dK/dV workgroup, Nc + cap of them per (b, h); unused ones carry key cube -1
 //   split: per (b, h) cap/2 + 1 descriptors: [0] = (number of split lists, 0, 0, 0), then
-//          (key cube, first slot, number of slots, 0) per split list, in cube order
+//          (key cube, first slot, number of slots, runs arrived: 0) per split list, in cube order
 // (the body, for the NT threads of one workgroup: thread `tid` owns cubes PT*tid .. PT*tid+PT-1, Nc <= PT*NT, whose
 // in-degrees it passes in `deg`; `v` returns where their lists begin.  wsum[NT/64] and hist[PT*NT] are
-// LDS scratch: bucket x of hist counts the items of length Nc - x (the last bucket also takes what
+// LDS scratch: bucket x of hist counts the items that go by the length Nc - x (the last bucket also takes what
 // lies beyond it), then holds the next free slot of the bucket)
 template <int PT, int NT>
 __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int bh, int tid, const int (&deg)[PT], int (&v)[PT],
@@ -394,13 +394,17 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
   }
   const int items = Nc + block_scan<PT, NT>(extra, wsum, tid);
 
-  // counting sort of the items by length, descending
+  // counting sort of the items by length, descending; the runs of a split list as if they were kRunExtra entries longer,
+  // which is about what leaving and adding up the partial results takes (as whole lists of their length they would
+  // come last and end after everything else)
+  constexpr int kRunExtra = 10;
+  auto bucket = [&](int len, int runs) { return min(Nc - min(Nc, runs > 1 ? len + kRunExtra : len), PT * NT - 1); };
 #pragma unroll
   for (int i = 0; i < PT; ++i)
     if (j0 + i < Nc)
       for (int r = 0; r < nseg[i]; ++r) {
         const int len = run_bound(deg[i], nseg[i], r + 1) - run_bound(deg[i], nseg[i], r);
-        atomicAdd(&hist[min(Nc - len, PT * NT - 1)], 1);
+        atomicAdd(&hist[bucket(len, nseg[i])], 1);
       }
   __syncthreads();
   int first[PT];
@@ -416,8 +420,8 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
     if (j0 + i < Nc)
       for (int r = 0; r < nseg[i]; ++r) {
         const int lo = run_bound(deg[i], nseg[i], r), hi = run_bound(deg[i], nseg[i], r + 1);
-        ord[atomicAdd(&hist[min(Nc - (hi - lo), PT * NT - 1)], 1)] =
-            make_int4(j0 + i, v[i] + lo, v[i] + hi, nseg[i] > 1 ? slot[i] + r : -1);
+        ord[atomicAdd(&hist[bucket(hi - lo, nseg[i])], 1)] =
+            make_int4(j0 + i, v[i] + lo, v[i] + hi, nseg[i] > 1 ? (rank[i] << 16) | (slot[i] + r) : -1);
       }
   for (int e = items + tid; e < Nc + cap; e += NT) ord[e] = make_int4(-1, 0, 0, -1);
 }

@@ -3,13 +3,12 @@
 //   P_ij = exp(S_ij - lse_i),  dP_ij = dOf_i . v_j,  dS_ij = P_ij (dP_ij - Delta_i)
 //   dQ_i = scale sum_j dS_ij k_j      (query-block-major pass over the index list: this file)
 //   dK_j = scale sum_i dS_ij q_i,  dV_j = sum_i P_ij dOf_i   (key-block-major pass over the transposed
-//                                                             block map: fine_bwd_dkv.hip)
+//                                                             block map: fine_bwd_dkv.h)
 // Both passes add the pooled-path gradient dXc[cube]/cnt to every valid row in their epilogue
 // and write zeros to pad rows.
 #include <type_traits>
 
-#include "unit_stream.h"
-#include "vsa_kernels.h"
+#include "fine_bwd_dkv.h"
 
 namespace vsa {
 
@@ -33,25 +32,32 @@ namespace vsa {
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
 // top-78 of 624: 1.61 -> 1.49 ms (1.23 PFLOP/s executed); 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
 // of 256, local lists: 2.83 -> 2.58 ms; d = 64, B = 2, 8 heads, top-32: 220 -> 210 us.
-template <int D, int NW, template <class> class UNITS>
-__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
-    int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
-    const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
-    const float* __restrict__ rowd, const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
-    uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream) {
+template <int D, int NW>
+struct DqShape {
+  static constexpr int HALF = Tile<D>::BYTES / 2;  // 32 rows
+  static constexpr int LDS = NW * 4 * HALF;        // per wavefront: K of two units, V of two units
+};
+
+// `smem`: DqShape::LDS bytes, aligned to 1024; `masks`: 128 words per wavefront.  `block` of `grid` workgroups.  COARSE: the
+// pooled-gradient term is formed here (NW = 4, cubes of one block), in `lc`, and dqc is not read.
+template <int D, int NW, template <class> class UNITS, bool COARSE>
+__device__ __forceinline__ void dq_block(
+    unsigned char* smem, uint32_t* masks, unsigned block, unsigned grid, int Nc, int K, float sl2, float scale,
+    const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v, const uint4* __restrict__ dof,
+    const int32_t* __restrict__ idx, const float* __restrict__ rowd, const float* __restrict__ dqc,
+    const uint64_t* __restrict__ mask, uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream,
+    const SmallCoarseArgs& sc, SmallCoarse<D>* lc) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32;
-  constexpr int HALF = TL::BYTES / 2;   // 32 rows
+  constexpr int HALF = DqShape<D, NW>::HALF;
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int G = KS;                 // matrix instructions of a group
   constexpr int OS = D;
-  // per wavefront: K of two units, V of two units
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
-  __shared__ uint32_t masks[NW * 128];
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
   static_assert(G == 2 * DVB && G == NC && G % 4 == 0, "phase interleave: one copy instruction per matrix instruction");
+  static_assert(!COARSE || 64 * NW == kSmallThreads, "the coarse backward takes 256 threads");
 
   // (as in the forward kernel: the first `pairs` workgroups take two blocks; with K = Nc plain blockIdx order and staggered walks)
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
@@ -59,9 +65,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   constexpr bool kPairs = NW == 2;
-  const bool paired = kPairs && blockIdx.x < pairs;
-  const unsigned from = paired ? 0u : pairs, those = paired ? pairs : gridDim.x - pairs;
-  const unsigned id = same_lists ? blockIdx.x - from : xcd_chunked_id(blockIdx.x - from, those);
+  const bool paired = kPairs && block < pairs;
+  const unsigned from = paired ? 0u : pairs, those = paired ? pairs : grid - pairs;
+  const unsigned id = same_lists ? block - from : xcd_chunked_id(block - from, those);
   const unsigned wg = paired ? 2 * id + wave : 2 * pairs + id;
   if (paired && wg >= blocks) return;  // (an odd number of blocks)
   const int c = wg % Nc;
@@ -144,6 +150,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
 #pragma unroll
     for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
   asm volatile("" : "+v"(nlse[0]), "+v"(nlse[1]), "+v"(ndelta[0]), "+v"(ndelta[1]));
+  if (COARSE) small_coarse_bwd<D, false>(*lc, Nc, c, bh * Nc, scale, sc.qc, sc.kc, sc.vc, sc.doc, sc.lse_c, sc.dot, tid);
   wait_vmcnt<0>();
   __builtin_amdgcn_sched_barrier(0);
   if (!paired) __syncthreads();
@@ -365,7 +372,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     const int t = P == 1 ? lane : tid, ch = t % CPR;
     float* const bufs = (float*)smem + (P == 1 ? wave * 64 * OS : 0);
     // the pooled-gradient term of this thread's column chunk, requested before the partial results go through LDS
-    const float* dqcr = dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks
+    const float* dqcr = COARSE ? lc->sum[0] + ch * 8 : dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks
     const float4 pc0 = *(const float4*)dqcr, pc1 = *(const float4*)(dqcr + 4);
     if (P > 1) __syncthreads();  // every wavefront is done with its stages
     {
@@ -413,6 +420,71 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
   else stream ? finish(all, std::true_type{}) : finish(all, std::false_type{});
 }
 
+template <int D, int NW, template <class> class UNITS>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
+    int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
+    const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
+    const float* __restrict__ rowd, const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
+    uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<D, NW>::LDS];
+  __shared__ uint32_t masks[NW * 128];
+  dq_block<D, NW, UNITS, false>(smem, masks, blockIdx.x, gridDim.x, Nc, K, sl2, scale, q, k, v, dof, idx, rowd, dqc, mask, dq,
+                                m_blocks, blocks, pairs, stream, SmallCoarseArgs{}, nullptr);
+}
+
+// Both passes of a small problem in one launch, four wavefronts per workgroup: neither fills the chip, so they run side by
+// side, dK/dV, whose walks are the longer ones, first.  COARSE: with the coarse backward (see coarse_small.h).
+// Bound by latency.  32 cubes, 2 heads, d = 64, top-8: dQ 9.3, dK/dV with its reduction 14.1 and the coarse backward 7.2 us
+// between events became 15.0 of one launch; the whole backward 31 -> 19 us, 64 cubes, 4 heads 0.77 to 0.94 of the time.  Not for
+// larger launches: at 256 blocks each pass fills the chip by itself.
+template <int D, bool COARSE>
+__global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
+    unsigned dkv_blocks, int BH, int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
+    const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx, const int32_t* __restrict__ col,
+    const int32_t* __restrict__ order, int items, int32_t* __restrict__ split, float* parts, int cap,
+    const float* __restrict__ rowd, const float* __restrict__ dqc, const float* __restrict__ dkc, const float* __restrict__ dvc,
+    const uint64_t* __restrict__ mask, uint4* __restrict__ dq, uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks,
+    SmallCoarseArgs sc) {
+  constexpr int LDS = DkvShape<D, 4>::LDS > DqShape<D, 4>::LDS ? DkvShape<D, 4>::LDS : DqShape<D, 4>::LDS;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
+  __shared__ uint32_t masks[4 * 128];
+  __shared__ int last_run;
+  __shared__ SmallCoarse<D> lc;
+  if (blockIdx.x < dkv_blocks)
+    dkv_block<D, 4, false, COARSE>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items, split, parts,
+                                   cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, 0, sc, &lc);
+  else
+    dq_block<D, 4, CubeUnits, COARSE>(smem, masks, blockIdx.x - dkv_blocks, gridDim.x - dkv_blocks, Nc, K, sl2, scale, q, k, v, dof,
+                                      idx, rowd, dqc, mask, dq, m_blocks, (unsigned)(BH * Nc), 0, 0, sc, &lc);
+}
+
+bool fine_bwd_in_one(int BH, int Nc, int key_cubes_16) { return !key_cubes_16 && BH * Nc <= kDkvFourWaves; }
+bool fine_bwd_with_coarse(int Nc, int m_blocks) { return m_blocks == 1 && Nc <= kSmallCubes; }
+
+hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
+                               const void* dof, const int32_t* idx, const int32_t* col, const int32_t* order, int32_t* split,
+                               float* parts, int cap, const float* rowd, const float* dqc, const float* dkc, const float* dvc,
+                               const uint64_t* mask, void* dq, void* dk, void* dv, int m_blocks, const float* qc, const float* kc,
+                               const float* vc, const float* doc, const float* lse_c, const float* dot, hipStream_t s) {
+  const int items = Nc + cap;
+  const unsigned dkv_blocks = dkv_grid(BH, items), grid = dkv_blocks + (unsigned)(BH * Nc);  // (dkv_grid is a multiple of 8: the XCDs stay)
+  const SmallCoarseArgs sc = {qc, kc, vc, doc, lse_c, dot};
+#define VSA_ONE(D_, COARSE_)                                                                                             \
+  k_fine_bwd_one<D_, COARSE_><<<grid, 256, 0, s>>>(dkv_blocks, BH, Nc, K, scale * kLog2e, scale, (const uint4*)q, (const uint4*)k, \
+                                                   (const uint4*)v, (const uint4*)dof, idx, col, order, items, split, parts, cap, \
+                                                   rowd, dqc, dkc, dvc, mask, (uint4*)dq, (uint4*)dk, (uint4*)dv, m_blocks, sc)
+  const bool coarse = fine_bwd_with_coarse(Nc, m_blocks);
+  if (d == 128) {
+    if (coarse) VSA_ONE(128, true);
+    else VSA_ONE(128, false);
+  } else {
+    if (coarse) VSA_ONE(64, true);
+    else VSA_ONE(64, false);
+  }
+#undef VSA_ONE
+  return hipGetLastError();
+}
+
 // Up to this many query blocks, four wavefronts per workgroup, as in the forward.  (d = 64, top-33: 324 blocks 31.0 against
 // 46.3 us, 432 blocks 31.9 against 46.9; d = 128, 324 blocks 48.6 against 45.0.)
 template <int D>
@@ -425,23 +497,21 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
-  const unsigned pairs = grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>) ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
+  const bool four = grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>);
+  const unsigned pairs = four ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
 #define VSA_DQ(D_, NW_, LIST_)                                                                                          \
   k_fine_bwd_dq<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
                                                 (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks, grid, pairs, stream)
-#define VSA_DQ_NW(D_, LIST_)                        \
-  do {                                              \
-    if (grid <= kDqFourWaves<D_>) VSA_DQ(D_, 4, LIST_); \
-    else VSA_DQ(D_, 2, LIST_);                      \
-  } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
-    if (d == 128) VSA_DQ_NW(128, SubCubeUnits);
-    else VSA_DQ_NW(64, SubCubeUnits);
-  } else {
-    if (d == 128) VSA_DQ_NW(128, CubeUnits);
-    else VSA_DQ_NW(64, CubeUnits);
+    if (d == 128 && four) VSA_DQ(128, 4, SubCubeUnits);
+    else if (d == 128) VSA_DQ(128, 2, SubCubeUnits);
+    else if (four) VSA_DQ(64, 4, SubCubeUnits);
+    else VSA_DQ(64, 2, SubCubeUnits);
+  } else {  // (with 256 blocks and fewer: launch_fine_bwd_one)
+    if (d == 128) VSA_DQ(128, 2, CubeUnits);
+    else if (four) VSA_DQ(64, 4, CubeUnits);
+    else VSA_DQ(64, 2, CubeUnits);
   }
-#undef VSA_DQ_NW
 #undef VSA_DQ
   return hipGetLastError();
 }

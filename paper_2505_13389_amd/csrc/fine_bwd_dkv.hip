@@ -1,619 +1,46 @@
-// Fine stage backward, dK/dV pass (the formulas are in fine_bwd.hip): key-block-major over the transposed
-// block map.
-#include <type_traits>
-
-#include "unit_stream.h"
-#include "vsa_kernels.h"
+// The dK/dV kernels of larger launches (the body of a workgroup is in fine_bwd_dkv.h).
+#include "fine_bwd_dkv.h"
 
 namespace vsa {
 
-// Key cubes of 16 tokens: the pooled-gradient term of row r of a key block, chunk ch -- the pooled
-// gradient of the row's key cube (rows 4*block .. 4*block+3 of `pooled`) over the cube's valid tokens.
-__device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ pooled, long long first_row, uint64_t kmask,
-                                                    int r, int D, int ch, float* out) {
-  const int sc = 2 * (r >> 5) + ((r >> 1) & 1);
-  const float inv = 1.0f / (float)__popcll(kmask & subcube_pattern(sc));  // (row r is valid: at least 1)
-  const float* p = pooled + (first_row + sc) * D + ch * 8;
-  const float4 p0 = *(const float4*)p, p1 = *(const float4*)(p + 4);
-  out[0] = p0.x * inv; out[1] = p0.y * inv; out[2] = p0.z * inv; out[3] = p0.w * inv;
-  out[4] = p1.x * inv; out[5] = p1.y * inv; out[6] = p1.z * inv; out[7] = p1.w * inv;
-}
-
-// One workgroup of NW = 2 wavefronts per (b, h, key block), two per CU (512 registers per wavefront: one
-// wavefront per SIMD); NW = 4 for launches too small to fill the chip that way.  The streamed work is cut
-// into UNITS of 32 query rows: wavefront w takes half w & 1 of the list entries w >> 1, (w >> 1) + NW/2, ...
-// and multiplies its units with ALL 64 keys:
-//   S [32 q x 64 k] = Q K^T,  dP = dO_f V^T,   P = exp2(S'),  dS = P dP',   dV += P^T dO_f,  dK += dS^T Q
-// so every operand it reads from LDS feeds two matrix instructions, and since nobody else reads its
-// rows it copies them into stages of its own: the loop has no barrier, the wavefronts drift freely.
-// dK and dV [64 x d] are 2*d accumulation registers; K stays in registers (d/2 of them), and V of the first 32 keys (d/4);
-// V of the other 32 is in LDS, once for the workgroup.  S and dP (64 registers) become P and dS in place.  The NW partial
-// results are added once, through LDS, at the end.
-//
-// The order inside a unit is the dependency order, S | dP | dV | dK: P is formed while dP is multiplied,
-// dS while dV is, so the vector work hides behind matrix work without a second set of registers.  Each
-// phase is a run of STEPS, pinned by scheduling barriers: one step = one LDS operand multiplied with both
-// key halves (two matrix instructions, 64 cycles), the operand reads of the step kAhead later, and a
-// share of the copies and of the vector work.
-// The row terms enter through the accumulators' initial value: the preprocess kernel stores -lse*log2e/sl2
-// (then P = exp2(S' * sl2); -30000 on pad rows, whose P underflows to 0) and -Delta per row, and a lane
-// reads those of its 16 rows straight into the first matrix instruction's C operand.  Pad KEY rows need
-// no bias: a key's products only ever meet its own rows of dK and dV, which are stored as zeros.
-//
-// SUB: the lists name key cubes of 16 tokens (Sec. 3.2, the 64 x 16 row of the tile-size tables).  The
-// workgroup still owns a 64-row key block; its list is the union of the lists of the block's four key
-// cubes, and every entry says (bits 16..19) which of them the query block selected: one more matrix
-// instruction per key half subtracts a large number from S of the other keys.  The pooled-gradient terms
-// are per key cube.
-//
-// What bounds it: the matrix pipe is busy 69 % of the time at 1.6 GHz (power: the clock falls as the pipe
-// fills: 12 % fewer instructions, by addresses held in registers and one wait per two steps, 391 -> 346 per 64 matrix
-// instructions, gave 2 %); 3 us of start-up and 5 us of merge and stores per
-// workgroup, which the other workgroup of the CU overlaps.  Before (32 keys x 32 queries per wavefront, 4
-// wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
-// 12 heads, d = 128, top-78 of 624: 2.68 -> 1.97 ms (1.22 PFLOP/s executed); 16384 tokens, top-32: 529 -> 370
-// us; d = 64, B = 2, 8 heads, top-32: 485 -> 288 us.  Four wavefronts (one workgroup
-// per CU, merging four partial results) instead of two: 2.20 ms, 426 us, 216 us, 349 us.
 template <int D, int NW, bool SUB>
 __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int K, float sl2, float scale, const uint4* __restrict__ q,
-                                                         const uint4* __restrict__ k, const uint4* __restrict__ v,
-                                                         const uint4* __restrict__ dof,
-                                                         const int32_t* __restrict__ col,
-                                                         const int32_t* __restrict__ order, int items_per_bh,
-                                                         float* __restrict__ parts, int cap,
-                                                         const float* __restrict__ rowd,
-                                                         const float* __restrict__ dkc, const float* __restrict__ dvc,
-                                                         const uint64_t* __restrict__ mask, uint4* __restrict__ dk,
-                                                         uint4* __restrict__ dv, int m_blocks, int stream) {
-  using TL = Tile<D>;
-  constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
-  constexpr int EPR = NW / 2;              // list entries a round of units takes
-  constexpr int HALF = TL::BYTES / 2;      // 32 rows
-  constexpr int STAGE = 2 * HALF + 256;    // Q rows, dO_f rows, row terms of one unit
-  constexpr int NST = D == 128 ? 2 : 4;    // stages per wavefront
-  constexpr int NC = HALF / 1024;          // copy instructions per 32 rows
-  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use: a pair of steps reads for the next pair
-  constexpr int NCD = 2 * DVB;             // steps of the dV and of the dK phase
-  constexpr int OS = D;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[HALF + NW * NST * STAGE];
-  static_assert(HALF % 256 == 0 && STAGE % 256 == 0, "the operand addresses XOR the bits below 256");
-  static_assert(KS == NCD && NC <= 2 * DVB && 8 % NC == 0, "phase interleave");
-
-  // Start-up: one descriptor load (key block, begin and end of its run of the block's list, slot; the
-  // items of a (b, h) come longest first), then the list chunk, then the first copies, then the resident
-  // K rows.  A list longer than the split length is shared by several workgroups, each of which leaves
-  // its fp32 partial sums in its slot (desc.w >= 0) for k_dkv_reduce; unused descriptors carry block -1.
-  int bh_, item;
-  dkv_item(blockIdx.x, BH, items_per_bh, bh_, item);
-  if (item >= items_per_bh) return;
-  const long long bh = bh_;
-  const int4 desc = ((const int4*)order)[bh * items_per_bh + item];
-  if (desc.x < 0) return;
-  const int j = desc.x, beg = desc.y, n = desc.z - desc.y, slot = desc.w;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, h = lane >> 5;
-  const long long rows0 = bh * (long long)Nc * kTile;
-  const int32_t* my_col = col + bh * (long long)Nc * K + beg;
-  const uint64_t kmask = mask[j];
-
-  // The list sits in a register, 64 entries at a time (lane e holds entry e of the current chunk).
-  int chunk = 0;
-  int col_v = n > 0 ? my_col[list_slot(0, lane, n)] : 0;
-  asm volatile("" : "+v"(col_v));
-  const int first = wave >> 1, half = wave & 1;  // this wavefront's entries: first, first + EPR, ...
-  const int nu = n > first ? (n - first + EPR - 1) / EPR : 0;
-  auto entry = [&](int u) {  // list entry of unit u (ascending u)
-    const int e = first + EPR * u;
-    if ((e >> 6) != chunk) {
-      chunk = e >> 6;
-      col_v = my_col[list_slot(chunk, lane, n)];
-      asm volatile("" : "+v"(col_v));  // its wait stays inside this branch
-    }
-    return __builtin_amdgcn_readlane(col_v, e & 63);
-  };
-  // a unit's bytes: its block's offset from this wavefront's first rows of the (b, h) (at most 4096 blocks of 16 KiB)
-  auto unit_off = [&](int raw) { return (unsigned)(SUB ? raw & 0xffff : raw) * (unsigned)TL::BYTES; };
-  const unsigned char* qw = (const unsigned char*)uniform_ptr(q + (rows0 + half * 32) * CPR);
-  const unsigned char* dw = (const unsigned char*)uniform_ptr(dof + (rows0 + half * 32) * CPR);
-  const unsigned char* rw = (const unsigned char*)uniform_ptr(rowd + 2 * (rows0 + half * 32));  // 32 + 32 floats per 32 rows
-  constexpr int ROWD_SHIFT = D == 128 ? 5 : 4;  // bytes of a block's Q rows / bytes of its row terms
-
-  // Copies (see UnitCopy): instruction c of 32 rows fills rows c*RPI ..; the swizzle repeats after
-  // 16 rows = 4 KiB (d = 128), so four lane offsets serve and the second group moves both bases by 4 KiB.
-  constexpr int NOFF = NC < 4 ? NC : 4;
-  unsigned goff[NOFF];
-#pragma unroll
-  for (int i = 0; i < NOFF; ++i) {
-    const int r = i * TL::RPI + lane / CPR, pc = lane % CPR;
-    goff[i] = (unsigned)((r * CPR + (pc ^ TL::swz(r))) * 16) - (unsigned)i * 1024u;
-  }
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-  const unsigned wbase = lds0 + HALF + (unsigned)wave * (NST * STAGE);
-  auto copy_piece = [&](const void* g, unsigned lds, int c) {  // copy c of 32 rows; `g`, `lds` uniform
-    const void* gb = (const unsigned char*)g + (c >> 2) * 4096;
-    if ((c & 3) == 0) set_m0(lds + (c >> 2) * 4096);
-    const int r = c & 3;
-    if (r == 0) lds_dma16_at<0>(gb, goff[0]);
-    if (r == 1) lds_dma16_at<1024>(gb, goff[1 % NOFF]);
-    if (r == 2) lds_dma16_at<2048>(gb, goff[2 % NOFF]);
-    if (r == 3) lds_dma16_at<3072>(gb, goff[3 % NOFF]);
-  };
-  auto copy_rows = [&](unsigned off, unsigned lds) { lds_dma4(rw + (off >> ROWD_SHIFT), (unsigned)lane * 4u, lds); };
-
-  // K and V reach the registers through LDS as well (coalesced copies, one per workgroup): K waits in the Q
-  // slots of the first two wavefronts' last stages, V of the first 32 keys in the dO_f slot of the first
-  // one's, V of the last 32 keys stays where the dP products read it.
-  constexpr int LAST = HALF + (NST - 1) * STAGE;  // the first wavefront's last stage
-  auto copy_half = [&](const uint4* src, unsigned lds) {
-    const unsigned char* g = (const unsigned char*)uniform_ptr(src);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) copy_piece(g, lds, c);
-  };
-  {
-    const long long kv0 = (rows0 + (long long)j * kTile) * CPR;
-    if (NW == 2 || wave < 2) copy_half(k + kv0 + half * 32 * CPR, lds0 + LAST + half * (NST * STAGE));
-    if (NW == 2 || wave >= 2) copy_half(v + kv0 + half * 32 * CPR, lds0 + (half ? 0 : LAST + HALF));
-  }
-  // the first units; the dO_f rows of the last stage follow once K and V have left it, its Q rows in the
-  // first S phase, as in the loop
-  int raws[NST];  // SUB: the entries of units u .. u + NST-1
-  unsigned next_off = 0;  // offset of the unit whose Q rows are copied next
-#pragma unroll
-  for (int s = 0; s < NST; ++s) {
-    raws[s] = 0;
-    if (s < nu) {
-      raws[s] = entry(s);
-      next_off = unit_off(raws[s]);
-      if (s < NST - 1) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) copy_piece(dw + next_off, wbase + s * STAGE + HALF, c);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) copy_piece(qw + next_off, wbase + s * STAGE, c);
-        copy_rows(next_off, wbase + s * STAGE + 2 * HALF);
-      }
-    }
-  }
-  f32x16 dka[DVB][2], dva[DVB][2];
-#pragma unroll
-  for (int x = 0; x < DVB; ++x)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) { dka[x][b][i] = 0.f; dva[x][b][i] = 0.f; }
-#pragma unroll
-  for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) asm volatile("" : "+a"(dka[x][b]), "+a"(dva[x][b]));
-  constexpr int G = 2 * NC + 1;  // copies of one unit
-  if (nu >= NST - 1) wait_vmcnt<(NST - 1) * G>();
-  else wait_vmcnt<0>();
-  __syncthreads();
-  bf16x8 kreg[2][KS], vreg[KS];  // K, and V of the first 32 keys
-  {
-    const int lane_k = TL::rowmajor_lane(0, lane) + LAST;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      kreg[0][s] = TL::rowmajor_at(smem, lane_k, s);
-      kreg[1][s] = TL::rowmajor_at(smem + NST * STAGE, lane_k, s);
-      vreg[s] = TL::rowmajor_at(smem + HALF, lane_k, s);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(kreg[0][s]), "+v"(kreg[1][s]), "+v"(vreg[s]));
-  __syncthreads();  // every wavefront has K and V: the last stages may be filled
-  if (nu >= NST) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) copy_piece(dw + next_off, wbase + (NST - 1) * STAGE + HALF, c);
-    wait_vmcnt<(NST - 2) * G + NC>();
-  } else {
-    wait_vmcnt<0>();
-  }
-
-  // SUB: A operand (1 in contraction slot 0) and the bit of the entry that selects this lane's key cube
-  bf16x8 ones_a = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (SUB && h == 0) ones_a[0] = (__bf16)1.f;
-
-  const int lane_q = TL::rowmajor_lane(0, lane) + (int)(HALF + wave * (NST * STAGE));
-  const int lane_v = TL::rowmajor_lane(0, lane);
-  int lane_b0, lane_b1;
-  TL::transposed_lane(0, lane, lane_b0, lane_b1);
-  lane_b0 += (int)(HALF + wave * (NST * STAGE));
-  lane_b1 += (int)(HALF + wave * (NST * STAGE));
-  const int lane_r = (int)(HALF + wave * (NST * STAGE)) + 2 * HALF + 16 * h;
-
-  // initial value of an accumulator: the row term of rows 8*(i/4) + 4*h + i%4
-  auto row_init = [&](int off, int which) {
-    f32x16 r;
-    const unsigned char* p = smem + (lane_r + off) + which * 128;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 x = *(const f32x4*)(p + 32 * g);
-      r[4 * g] = x[0]; r[4 * g + 1] = x[1]; r[4 * g + 2] = x[2]; r[4 * g + 3] = x[3];
-    }
-    return r;
-  };
-
-  bf16x8 qcur[kAhead];  // Q operands of a unit's first steps, read during the unit before
-  f32x16 sinit;
-  if (nu > 0) {
-#pragma unroll
-    for (int s = 0; s < kAhead; ++s) qcur[s] = TL::rowmajor_at(smem, lane_q, s);
-    sinit = row_init(0, 0);
-  }
-
-  // One unit, whose rows lie in the wavefront's stage `st` (a constant in the unrolled loop).
-  auto body = [&](auto steady_tag, int u, int st) {
-    constexpr bool STEADY = decltype(steady_tag)::value;  // the units up to u + NST exist
-    const bool more_q = STEADY || u + NST - 1 < nu;
-    const int st_off = st * STAGE, next_st = st == NST - 1 ? 0 : st_off + STAGE;
-    const int prev_st = st == 0 ? (NST - 1) * STAGE : st_off - STAGE;
-    // (the addresses of V, and with key cubes of 16 all of them, are rebuilt per unit: registers are short)
-    int lv = lane_v, lq = lane_q, lb0 = lane_b0, lb1 = lane_b1;
-    asm volatile("" : "+v"(lv));
-    if (SUB) asm volatile("" : "+v"(lq), "+v"(lb0), "+v"(lb1));
-    const unsigned char* Qs = smem + st_off;
-    const unsigned char* Ds = smem + st_off + HALF;
-    const unsigned char* Qn = smem + next_st;
-    bf16x8 qa[KS], da[KS], va[KS], dt[NCD], qt[NCD];
-    f32x16 dpinit;
-#pragma unroll
-    for (int s = 0; s < kAhead; ++s) qa[s] = qcur[s];
-    // operand reads of step m: S steps, dP steps, dV steps, dK steps, then the S steps of the next unit
-    auto read_step = [&](int m) {
-      if (m < KS) {
-        qa[m] = TL::rowmajor_at(Qs, lq, m);
-      } else if (m < 2 * KS) {
-        const int s = m - KS;
-        if (s == 0) dpinit = row_init(st_off, 1);
-        da[s] = TL::rowmajor_at(Ds, lq, s);
-        va[s] = TL::rowmajor_at(smem, lv, s);
-      } else if (m < 2 * KS + NCD) {
-        const int c = m - 2 * KS;
-        dt[c] = TL::transposed_at(Ds, lb0, lb1, c / DVB, c % DVB);
-      } else if (m < 2 * KS + 2 * NCD) {
-        const int c = m - 2 * KS - NCD;
-        qt[c] = TL::transposed_at(Qs, lb0, lb1, c / DVB, c % DVB);
-      } else {
-        const int s = m - 2 * KS - 2 * NCD;
-        if (s == 0) sinit = row_init(next_st, 0);
-        qcur[s] = TL::rowmajor_at(Qn, lq, s);
-      }
-    };
-    // at the first step of a pair: its operands are there; those of the next pair are requested
-    auto pair_begins = [&](int m) {
-      if (m % 2 == 0) {
-        wait_lgkmcnt<0>();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    auto pair_reads = [&](int m) {
-      if (m % 2 == 0) {
-        read_step(m + kAhead);
-        read_step(m + kAhead + 1);
-      }
-    };
-    // ---- S
-    f32x16 s0, s1, p0, p1;
-    bf16x8 bias0 = {0, 0, 0, 0, 0, 0, 0, 0}, bias1 = bias0;
-    if (SUB) {
-      // key row l32 of key half b belongs to key cube 2b + (row/2)%2 of the block's four
-      const unsigned sel = (unsigned)(raws[0] >> 16) >> ((l32 >> 1) & 1);
-      bias0[0] = (h == 0 && !(sel & 1u)) ? (__bf16)-30000.f : (__bf16)0.f;
-      bias1[0] = (h == 0 && !(sel & 4u)) ? (__bf16)-30000.f : (__bf16)0.f;
-    }
-    const unsigned char* gq = qw + next_off;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      pair_begins(s);
-      if (s == 0) mfma_v_from(s0, qa[0], kreg[0][0], sinit);
-      else mfma_v(s0, qa[s], kreg[0][s]);
-      if (more_q) {
-#pragma unroll
-        for (int c = s * NC / KS; c < (s + 1) * NC / KS; ++c) copy_piece(gq, wbase + prev_st, c);
-        if (s == KS - 1) copy_rows(next_off, wbase + prev_st + 2 * HALF);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (s == 0) s1 = sinit;
-      mfma_v(s1, qa[s], kreg[1][s]);
-      pair_reads(s);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (SUB) {
-      asm volatile("s_nop 1");  // (two wait states between the moves to the bias operands and the matrix instruction)
-      mfma_v(s0, ones_a, bias0);
-      mfma_v(s1, ones_a, bias1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- dP, with P = exp2(S' sl2) of both key halves behind it.  Item k of 16: one pair of values, first
-    // those of contraction step 0 of the dV products (accumulator values 0..7), then those of step 1.
-    uint4 pb[2][2], sb[2][2];
-    auto put = [](uint4& u4, int w, uint32_t x) {
-      if (w == 0) u4.x = x;
-      if (w == 1) u4.y = x;
-      if (w == 2) u4.z = x;
-      if (w == 3) u4.w = x;
-    };
-    auto p_item = [&](int it) {
-      const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
-      f32x16& S = b ? s1 : s0;
-      S[e] = fast_exp2(S[e] * sl2);
-      S[e + 1] = fast_exp2(S[e + 1] * sl2);
-      const uint32_t pp = pack_bf16(S[e], S[e + 1]);
-      put(pb[b][st], w, pp);
-      asm volatile("" : : "v"(pp));  // (pure arithmetic has no place of its own in the order: tie it to this step)
-    };
-    auto s_item = [&](int it) {
-      const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
-      const f32x16& S = b ? s1 : s0;
-      const f32x16& P = b ? p1 : p0;
-      const uint32_t ss = pack_bf16(S[e] * P[e], S[e + 1] * P[e + 1]);
-      put(sb[b][st], w, ss);
-      asm volatile("" : : "v"(ss));
-    };
-    constexpr int P_DP = 10;  // P items behind the dP steps 1 .. KS-2, the rest behind the first dV steps
-    auto p_items = [&](int from, int to) {
-#pragma unroll
-      for (int it = from; it < to; ++it) p_item(it);
-    };
-    auto s_items = [&](int from, int to) {
-#pragma unroll
-      for (int it = from; it < to; ++it) s_item(it);
-    };
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const bool on = s >= 1 && s <= KS - 2;
-      const int i0 = (s - 1) * P_DP / (KS - 2), i2 = s * P_DP / (KS - 2), i1 = (i0 + i2) / 2;
-      pair_begins(KS + s);
-      if (s == 0) mfma_v_from(p0, da[0], vreg[0], dpinit);
-      else mfma_v(p0, da[s], vreg[s]);
-      pair_reads(KS + s);
-      if (on) p_items(i0, i1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s == 0) p1 = dpinit;
-      mfma_v(p1, da[s], va[s]);
-      if (on) p_items(i1, i2);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- dV, contraction step 0 first; the remaining P items have to be done one step before step 1 begins,
-    // the dS items of step 0 one step before the dK phase begins
-    auto opnd = [](const uint4& x) { return __builtin_bit_cast(bf16x8, x); };
-    constexpr int S_DV = DVB == 4 ? 10 : 8;  // dS items behind the dV steps DVB-1 .. NCD-1, the rest behind the first dK steps
-#pragma unroll
-    for (int c = 0; c < NCD; ++c) {
-      const bool pv_on = c < DVB - 1, ds_on = c >= DVB - 1;
-      const int i0 = P_DP + c * (16 - P_DP) / (DVB - 1), i2 = P_DP + (c + 1) * (16 - P_DP) / (DVB - 1), i1 = (i0 + i2) / 2;
-      // (those of step 0 are the first eight: done one step before the end)
-      const int e0 = (c - DVB + 1) * 8 / DVB, e2 = c == NCD - 1 ? S_DV : (c - DVB + 2) * 8 / DVB, e1 = (e0 + e2) / 2;
-      pair_begins(2 * KS + c);
-      mfma_a(dva[c % DVB][0], dt[c], opnd(pb[0][c / DVB]));
-      if (pv_on) p_items(i0, i1);
-      if (ds_on) s_items(e0, e1);
-      pair_reads(2 * KS + c);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_a(dva[c % DVB][1], dt[c], opnd(pb[1][c / DVB]));
-      if (pv_on) p_items(i1, i2);
-      if (ds_on) s_items(e1, e2);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- dK; the dO_f rows of this stage are done with: refill them (unit u + NST), then wait for the Q
-    // rows of the next unit -- everything issued before this phase's copies but the dO_f, Q groups after them
-#pragma unroll
-    for (int s = 0; s + 1 < NST; ++s) raws[s] = raws[s + 1];
-    if (STEADY) {
-      raws[NST - 1] = entry(u + NST);
-      next_off = unit_off(raws[NST - 1]);
-    }
-    const unsigned char* gd = dw + next_off;
-#pragma unroll
-    for (int c = 0; c < NCD; ++c) {
-      const bool ds_on = c < DVB - 1;
-      const int i0 = S_DV + c * (16 - S_DV) / (DVB - 1), i2 = S_DV + (c + 1) * (16 - S_DV) / (DVB - 1), i1 = (i0 + i2) / 2;
-      // copies of this step (they end DVB steps before the phase does)
-      const int g0 = c * NC / DVB, g2 = (c + 1) * NC / DVB, g1 = (g0 + g2) / 2;
-      auto copies = [&](int from, int to) {
-        if (STEADY && c < DVB)
-#pragma unroll
-          for (int e = from; e < to; ++e) copy_piece(gd, wbase + st_off + HALF, e);
-      };
-      pair_begins(2 * KS + NCD + c);
-      mfma_a(dka[c % DVB][0], qt[c], opnd(sb[0][c / DVB]));
-      if (ds_on) s_items(i0, i1);
-      copies(g0, g1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_a(dka[c % DVB][1], qt[c], opnd(sb[1][c / DVB]));
-      if (ds_on) s_items(i1, i2);
-      copies(g1, g2);
-      if (c == NCD - kAhead) {
-        // newer than the next unit's Q group: the dO_f and Q groups of the units after it requested so far
-        const int left = nu - 1 - (u + 1);  // units after the next one
-        if (STEADY) wait_vmcnt<(NST - 2) * G + NC>();
-        else if (NST > 2 && left == 2) wait_vmcnt<2 * G>();
-        else if (NST > 2 && left == 1) wait_vmcnt<G>();
-        else wait_vmcnt<0>();
-      }
-      pair_reads(2 * KS + NCD + c);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  int u = 0;
-  for (; u + 2 * NST - 1 < nu; u += NST) {
-#pragma unroll
-    for (int st = 0; st < NST; ++st) body(std::true_type{}, u + st, st);
-  }
-  for (; u + NST < nu; ++u) body(std::true_type{}, u, u % NST);
-  for (; u < nu; ++u) body(std::false_type{}, u, u % NST);
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix results land before they are read
-  __builtin_amdgcn_sched_barrier(0);
-
-  // the pooled-gradient terms of this thread's column chunk (the same chunk for all of its items),
-  // requested before the partial results go through LDS
-  static_assert(NT % CPR == 0, "a thread keeps its column chunk");
-  float4 pk[2] = {}, pv[2] = {};
-  if (!SUB) {
-    const float* a = dkc + ((bh * Nc + j) / m_blocks) * D + (tid % CPR) * 8;  // per cube = m_blocks blocks
-    const float* b = dvc + ((bh * Nc + j) / m_blocks) * D + (tid % CPR) * 8;
-    pk[0] = *(const float4*)a, pk[1] = *(const float4*)(a + 4);
-    pv[0] = *(const float4*)b, pv[1] = *(const float4*)(b + 4);
-  }
-  const float inv_cnt = 1.0f / (float)cube_count(mask, j, m_blocks);
-
-  // Add the partial results in wavefront order through LDS: dK, then dV.
-  static_assert(NW * 64 * OS * 4 <= (int)sizeof(smem), "merge buffers must fit");
-  auto finish = [&](auto once_tag) {
-    constexpr bool ONCE = decltype(once_tag)::value;
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      __syncthreads();
-      float* bufs = (float*)smem;  // [wavefront][64][OS]
-      {
-        float* Op = bufs + wave * 64 * OS;
-#pragma unroll
-        for (int x = 0; x < DVB; ++x)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const f32x16& a = pass == 0 ? dka[x][b] : dva[x][b];
-              *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-                  make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
-            }
-      }
-      __syncthreads();
-      const float4 q0 = pass == 0 ? pk[0] : pv[0], q1 = pass == 0 ? pk[1] : pv[1];
-      const float pooled[8] = {q0.x * inv_cnt, q0.y * inv_cnt, q0.z * inv_cnt, q0.w * inv_cnt,
-                               q1.x * inv_cnt, q1.y * inv_cnt, q1.z * inv_cnt, q1.w * inv_cnt};
-      const float mul = pass == 0 ? scale : 1.0f;
-      uint4* dst = pass == 0 ? dk : dv;
-      float* slot_dst = parts + ((bh * cap + slot) * 2 + pass) * (long long)(64 * D);
-#pragma unroll
-      for (int it = 0; it < LPT; ++it) {
-        const int item = it * NT + tid, r = item / CPR, ch = item % CPR;
-        const int m0 = merge_offset(r, ch * 8, OS), m1 = merge_offset(r, ch * 8 + 4, OS);
-        float4 a = *(const float4*)(bufs + m0), b = *(const float4*)(bufs + m1);
-#pragma unroll
-        for (int w = 1; w < NW; ++w) {
-          const float4 x = *(const float4*)(bufs + w * 64 * OS + m0), y = *(const float4*)(bufs + w * 64 * OS + m1);
-          a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
-          b.x += y.x; b.y += y.y; b.z += y.z; b.w += y.w;
-        }
-        if (slot >= 0) {  // one run of a split list: raw fp32 sums [dK | dV][64][D], finished by k_dkv_reduce
-          float4* o = (float4*)(slot_dst + r * D + ch * 8);
-          o[0] = a;
-          o[1] = b;
-          continue;
-        }
-        const float sum[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        uint4 ov = make_uint4(0, 0, 0, 0);
-        if ((kmask >> r) & 1) {
-          float res[8];
-          if (SUB) {
-            float pl[8];
-            subcube_pooled_term(pass == 0 ? dkc : dvc, (bh * Nc + j) * 4, kmask, r, D, ch, pl);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pl[e]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pooled[e]);
-          }
-          ov = pack8(res);
-        }
-        store16<ONCE>(dst + (rows0 + j * kTile + r) * CPR + ch, ov);
-      }
-    }
-  };
-  if (stream) finish(std::true_type{});
-  else finish(std::false_type{});
+                                                             const uint4* __restrict__ k, const uint4* __restrict__ v,
+                                                             const uint4* __restrict__ dof, const int32_t* __restrict__ col,
+                                                             const int32_t* __restrict__ order, int items_per_bh,
+                                                             int32_t* __restrict__ split, float* parts, int cap,
+                                                             const float* __restrict__ rowd, const float* __restrict__ dkc,
+                                                             const float* __restrict__ dvc, const uint64_t* __restrict__ mask,
+                                                             uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks, int stream) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D, NW>::LDS];
+  __shared__ int last_run;
+  dkv_block<D, NW, SUB, false>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items_per_bh, split,
+                               parts, cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, stream, SmallCoarseArgs{}, nullptr);
 }
-
-// Sums the fp32 partial results of the split lists in slot order and finishes them like the dK/dV
-// epilogue does (scale, pooled-gradient term, zero pad rows, one rounding to bf16).  One workgroup
-// per possible split list of a (b, h); those beyond the actual number exit at once.
-template <int D, bool SUB>
-__global__ __launch_bounds__(256) void k_dkv_reduce(int Nc, int cap, float scale, const int32_t* __restrict__ split,
-                                                    const float* __restrict__ parts, const float* __restrict__ dkc,
-                                                    const float* __restrict__ dvc, const uint64_t* __restrict__ mask,
-                                                    uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks) {
-  constexpr int CPR = D / 8, LPT = kTile * CPR / 256;
-  const int per = cap / 2, r_ = blockIdx.x % per, tid = threadIdx.x;
-  const long long bh = blockIdx.x / per;
-  const int4* sp = (const int4*)split + bh * (per + 1);
-  if (r_ >= sp[0].x) return;
-  const int4 desc = sp[1 + r_];
-  const int j = desc.x, slot0 = desc.y, runs = desc.z;
-  const uint64_t kmask = mask[j];
-  const float inv_cnt = 1.0f / (float)cube_count(mask, j, m_blocks);
-  const long long rows0 = bh * (long long)Nc * kTile;
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const float* pooled_row = (pass == 0 ? dkc : dvc) + ((bh * Nc + j) / m_blocks) * D + (tid % CPR) * 8;
-    const float4 p0 = *(const float4*)pooled_row, p1 = *(const float4*)(pooled_row + 4);
-    const float pooled[8] = {p0.x * inv_cnt, p0.y * inv_cnt, p0.z * inv_cnt, p0.w * inv_cnt,
-                             p1.x * inv_cnt, p1.y * inv_cnt, p1.z * inv_cnt, p1.w * inv_cnt};
-    const float mul = pass == 0 ? scale : 1.0f;
-    uint4* dst = pass == 0 ? dk : dv;
-#pragma unroll
-    for (int it = 0; it < LPT; ++it) {
-      const int item = it * 256 + tid, r = item / CPR, ch = item % CPR;
-      float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < runs; ++s) {
-        const float4* src = (const float4*)(parts + (((bh * cap + slot0 + s) * 2 + pass) * 64 + r) * (long long)D + ch * 8);
-        const float4 a = src[0], b = src[1];
-        sum[0] += a.x; sum[1] += a.y; sum[2] += a.z; sum[3] += a.w;
-        sum[4] += b.x; sum[5] += b.y; sum[6] += b.z; sum[7] += b.w;
-      }
-      uint4 ov = make_uint4(0, 0, 0, 0);
-      if ((kmask >> r) & 1) {
-        float res[8];
-        if (SUB) {
-          float pl[8];
-          subcube_pooled_term(pass == 0 ? dkc : dvc, (bh * Nc + j) * 4, kmask, r, D, ch, pl);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pl[e]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], mul, pooled[e]);
-        }
-        ov = pack8(res);
-      }
-      dst[(rows0 + j * kTile + r) * CPR + ch] = ov;
-    }
-  }
-}
-
-// Up to this many key blocks, four wavefronts per workgroup: the launch does not fill the 512 places of
-// two-wavefront workgroups, and half as long a list walk counts (64 blocks, d = 64, top-8: 10.7 against 13.7 us).
-constexpr int kDkvFourWaves = 256;
 
 hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
-                               const void* dof, const int32_t* col, const int32_t* order, const int32_t* split,
+                               const void* dof, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dkc, const float* dvc,
                                const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const int items = Nc + cap;
   const int stream = (long long)BH * Nc * kTile * d * 2 >= kStreamBytes;
-  const unsigned grid = dkv_grid(BH, items), rgrid = (unsigned)(BH * (cap / 2));
-#define VSA_DKV(D_, SUB_)                                                                                                \
-  do {                                                                                                                   \
-    if (BH * Nc <= kDkvFourWaves) VSA_DKV_NW(D_, 4, SUB_);                                                               \
-    else VSA_DKV_NW(D_, 2, SUB_);                                                                                        \
-  } while (0)
-#define VSA_DKV_NW(D_, NW_, SUB_)                                                                                                \
-  do {                                                                                                                   \
-    k_fine_bwd_dkv<D_, NW_, SUB_><<<grid, 64 * NW_, 0, s>>>(BH, Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v,    \
-                                                  (const uint4*)dof, col, order, items, parts, cap, rowd,                \
-                                                  dkc, dvc, mask, (uint4*)dk, (uint4*)dv, m_blocks, stream);              \
-    k_dkv_reduce<D_, SUB_><<<rgrid, 256, 0, s>>>(Nc, cap, scale, split, parts, dkc, dvc, mask, (uint4*)dk, (uint4*)dv,    \
-                                                 m_blocks);                                                              \
-  } while (0)
+  const unsigned grid = dkv_grid(BH, items);
+#define VSA_DKV(D_, NW_, SUB_)                                                                                                \
+  k_fine_bwd_dkv<D_, NW_, SUB_><<<grid, 64 * NW_, 0, s>>>(BH, Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
+                                                          (const uint4*)dof, col, order, items, split, parts, cap, rowd, dkc, dvc, \
+                                                          mask, (uint4*)dk, (uint4*)dv, m_blocks, stream)
   if (key_cubes_16) {  // lists of key cubes of 16 tokens: the pooled terms dkc, dvc are [BH, 4 Nc, d]
-    if (d == 128) VSA_DKV(128, true);
-    else VSA_DKV(64, true);
+    const bool four = BH * Nc <= kDkvFourWaves;  // (lists of blocks: launch_fine_bwd_one)
+    if (d == 128 && four) VSA_DKV(128, 4, true);
+    else if (d == 128) VSA_DKV(128, 2, true);
+    else if (four) VSA_DKV(64, 4, true);
+    else VSA_DKV(64, 2, true);
   } else {
-    if (d == 128) VSA_DKV(128, false);
-    else VSA_DKV(64, false);
+    if (d == 128) VSA_DKV(128, 2, false);
+    else VSA_DKV(64, 2, false);
   }
 #undef VSA_DKV
-#undef VSA_DKV_NW
   return hipGetLastError();
 }
 

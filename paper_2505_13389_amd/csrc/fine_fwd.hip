@@ -602,31 +602,26 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Which kernel, by the number of query blocks and of 64-key tiles in a list (lists of N(0,1) inputs, one head size, 288 to
-// 8192 blocks, 1 to 56 tiles; figures: time of the general kernel over that of the other).
+// Which kernel, by the number of query blocks and of 64-key tiles in a list (whole forwards back to back, lists of N(0,1)
+// inputs, heads of 96 and 256 blocks; figures: time with the general kernel over that with the other).
 //
 // The kernel for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile:
-//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup).  Where the last one is nearly empty, it
-//            loses: 576 blocks, 3 tiles 1.05, 14 1.03, 20 0.99, 56 0.93; 768, 14 1.04, 20 1.03; 1152, 20 1.06, 34 1.05, 44 0.99;
-//            2304, 20 1.03, 28 0.99; 1536, 6 1.06, 20 0.99; 1728, 20 1.02, 24 1.00; 2688, 8 1.02, 20 0.98; 1920, 6 1.03, 12 1.00.
-//            Elsewhere it wins: 480, 4 0.98, 12 0.94; 960, 8 0.93; 2048, 8 0.95, 20 0.92; 3072 and more from 0.99 at 3 tiles
-//            to 0.91 at 12; 8192, 12 0.85.
-//   d = 64   768 blocks, 4 tiles 0.97; 1152, 4 1.07, 14 1.02; 1536, 8 1.09; 2016, 4 1.00, 12 0.93; 2048, 8 1.02; 3456, 3 1.08,
-//            8 0.98; 7488, 2 0.88.
-//   256 blocks, one or two tiles: 1.07, 1.04.
+//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup).  It loses where the last one is nearly
+//            empty: 1056 blocks, 12 tiles 1.01, 28 1.02, 40 1.01; 1248, 12 1.02, 40 0.99; 2304, 4 1.04, 12 1.02, 20 0.99; 2688, 8
+//            1.02, 16 0.99; and in the smallest launches: 96, 4 1.01, 8 0.96; 480, 4 1.03, 12 1.00 (512, 12 1.02).  Elsewhere it wins: 576, 8
+//            0.99; 960, 8 0.90; 1344, 8 0.97; 1920, 8 0.93; 2048, 8 0.91; 3072, 8 0.96; 8192, 12 0.88.
+//   d = 64   480 blocks, 2 tiles 1.01, 8 0.99; 768, 8 1.03, 16 1.01, 20 0.98; 960, 4 0.96; 1152, 8 1.03, 20 0.97; 1536, 8 1.07;
+//            1920, 4 1.00, 8 0.97; 2048, 12 1.02; 2688, 12 1.02; 3072, 2 1.02, 4 0.98; 8192, 2 0.90.
 inline bool fwd_short(int d, unsigned grid, int tiles) {
-  if (grid <= 256) return tiles <= 2;
   if (d == 64) {
-    if (grid <= 1024 || grid > 5000) return false;
-    return tiles <= (grid < 1664 ? 14 : grid < 2048 ? 4 : grid < 3072 ? 10 : 3);
+    if (grid <= 512) return tiles <= 2;
+    if (grid <= 768) return tiles <= 14;
+    if (grid <= 1024 || grid > 4096) return false;
+    return tiles <= (grid < 1792 ? 14 : grid < 2048 ? 4 : grid < 2816 ? 14 : 3);
   }
-  if (grid <= 512 || grid >= 3072) return false;
-  const int full = (int)(grid / 1024), rest = (int)(grid % 1024);
-  if (full == 0) return grid <= 768 && tiles <= 16;
-  if (rest == 0) return tiles <= 3;
-  if (rest <= 256) return tiles <= 8 + 32 / full;
-  if (rest <= 512) return tiles <= 10;
-  return tiles <= (rest <= 768 ? 20 : 8) / full;
+  if (grid <= 512) return tiles <= (grid > 448 ? 12 : 4);
+  if (grid > 1024 && grid <= 1280) return tiles <= 32;
+  return grid > 2112 && grid < 2816 && tiles <= 12;
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
 // with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks

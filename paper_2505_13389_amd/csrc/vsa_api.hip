@@ -382,9 +382,16 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
   const bool map_aside = vsa::map_with_bwd_pre(g.Nb, sub ? 1 : 0);
   VSA_TRY("bwd_pre", vsa::launch_bwd_pre(BH, g.Nc, g.m, p->d, w.mask, dout, gate_c, gate_f, out_fine, out_coarse, dgate_c, dgate_f,
                               w.dof, w.rowd, scale, w.doc, dot, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, map_aside ? &map : nullptr, s));
-  VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, dot, w.ac, w.dsc,
+  const bool one = vsa::fine_bwd_in_one(BH, g.Nb, sub ? 1 : 0);
+  if (!one || !vsa::fine_bwd_with_coarse(g.Nc, g.m))
+    VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, dot, w.ac, w.dsc,
                                  w.dqc, w.dkc, w.dvc, w.kcnt, s));
   if (!map_aside) VSA_TRY("transpose_map", vsa::launch_transpose_map(BH, map, w.bits, sub ? 1 : 0, s));
+  if (one) {
+    VSA_TRY("fine_bwd", vsa::launch_fine_bwd_one(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.col, w.order, w.split, w.parts, w.cap,
+                                 w.rowd, w.dqc, w.dkc, w.dvc, w.mask, dq, dk, dv, g.m, w.qc, w.kc, w.vc, w.doc, lse_coarse, dot, s));
+    return VSA_OK;
+  }
   VSA_TRY("fine_bwd_dq", vsa::launch_fine_bwd_dq(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.rowd,
                                   w.dqc, w.mask, dq, g.m, sub ? 1 : 0, s));
   VSA_TRY("fine_bwd_dkv", vsa::launch_fine_bwd_dkv(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, w.col, w.order, w.split, w.parts,

@@ -60,8 +60,20 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,
                               hipStream_t s);
 hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
-                               const void* dof, const int32_t* col, const int32_t* order, const int32_t* split,
+                               const void* dof, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dkc, const float* dvc,
                                const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s);
+// Up to this many blocks dK/dV and, at d = 128, dQ take four wavefronts per workgroup: the launch does not fill the 512
+// places of two-wavefront workgroups, and half as long a list walk counts (64 blocks, d = 64, top-8: 10.7 against 13.7 us).
+constexpr int kDkvFourWaves = 256;
+// Both passes of a small problem in one launch (BH*Nc up to kDkvFourWaves blocks, lists of blocks).  `coarse` (cubes of one block,
+// Nc up to kSmallCubes): the coarse backward too; qc .. dot are read then, dqc, dkc, dvc are not.
+bool fine_bwd_in_one(int BH, int Nc, int key_cubes_16);
+bool fine_bwd_with_coarse(int Nc, int m_blocks);
+hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
+                               const void* dof, const int32_t* idx, const int32_t* col, const int32_t* order, int32_t* split,
+                               float* parts, int cap, const float* rowd, const float* dqc, const float* dkc, const float* dvc,
+                               const uint64_t* mask, void* dq, void* dk, void* dv, int m_blocks, const float* qc, const float* kc,
+                               const float* vc, const float* doc, const float* lse_c, const float* dot, hipStream_t s);
 
 }  // namespace vsa

@@ -1,9 +1,13 @@
 // The coarse stage of short sequences inside the fine kernels: with up to 64 cubes a (b, h) a workgroup of 256 threads forms
 // the one row (or column) of the coarse matrices that belongs to its block by itself -- 64 x d multiply-adds a
 // product -- while its list and its first tiles are on their way, instead of waiting for a launch of its own that
-// hardly fills a compute unit.  fp32 products and sums, in a fixed order.
+// hardly fills a compute unit.  fp32 products and sums, in a fixed order.  Bound by latency: rows are requested before
+// their weights are formed (64 cubes, d = 128, top-1: forward 21.5 -> 15.7 us; 18.7 with a launch for the coarse stage).
+// Forwards of 12 to 64 cubes, up to 256 blocks (d = 64: 512), 0.73 to 0.93 of the time; 32 cubes, 2 heads, d = 64, top-8 17.0 ->
+// 13.4 us.  In launches of several generations every one of them would pay what one launch costs.
 #pragma once
-#include "vsa_common.h"
+#include "coarse_row.h"
+#include "vsa_kernels.h"
 
 namespace vsa {
 
@@ -12,9 +16,10 @@ constexpr int kSmallThreads = 256;
 
 template <int D>
 struct SmallCoarse {
-  float w[2][kSmallCubes];             // weights of the sums below
+  static constexpr int PER_ROW = D / 4, PARTS = kSmallThreads / PER_ROW;  // threads a row of the sums, partial sums
+  float w[2][kSmallCubes];  // weights of the sums below
   float sum[2][D];
-  float part[2][kSmallThreads];
+  float part[2][PARTS][D];
 };
 
 __device__ __forceinline__ float dot4(const float4& a, const float4& b, float s) {
@@ -34,21 +39,66 @@ __device__ __forceinline__ float small_dot(const float* __restrict__ x, const fl
   return s;
 }
 
-// sum over n < Nc of w[n] rows[n][e], e = tid % D, the partial sum of n = tid / D, tid / D + 256 / D, ...
+// Sums over n < Nc of w[n] rows[n][e]: a thread takes four columns of every PARTS-th row, which it requests well before the
+// weights are known (nothing in these kernels hides the trip but that).
 template <int D>
-__device__ __forceinline__ float small_part(const float* w, const float* __restrict__ rows, int Nc, int tid) {
-  const int e = tid % D;
-  float s = 0.f;
-#pragma unroll 8
-  for (int n = tid / D; n < Nc; n += kSmallThreads / D) s = fmaf(w[n], rows[n * D + e], s);
+struct SmallRows {
+  using L = SmallCoarse<D>;
+  static constexpr int ROWS = kSmallCubes / L::PARTS;
+  float4 x[ROWS];
+  __device__ __forceinline__ void request(const float* __restrict__ rows, int Nc, int tid) {
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) x[i] = *(const float4*)(rows + min(tid / L::PER_ROW + i * L::PARTS, Nc - 1) * D + tid % L::PER_ROW * 4);
+  }
+  __device__ __forceinline__ void weigh(const float* w, float (*part)[D], int Nc, int tid) const {
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int n = tid / L::PER_ROW + i * L::PARTS;
+      if (n < Nc) {
+        const float a = w[n];
+        s.x = fmaf(a, x[i].x, s.x); s.y = fmaf(a, x[i].y, s.y); s.z = fmaf(a, x[i].z, s.z); s.w = fmaf(a, x[i].w, s.w);
+      }
+    }
+    *(float4*)&part[tid / L::PER_ROW][tid % L::PER_ROW * 4] = s;
+  }
+};
+template <int D>
+__device__ __forceinline__ float small_sum(const float (*part)[D], int e) {
+  float s = part[0][e];
+#pragma unroll
+  for (int i = 1; i < SmallCoarse<D>::PARTS; ++i) s += part[i][e];
   return s;
 }
+
+// The coarse stage of query cube `own`: l.sum[0] = O_c, `list` the K cubes it selects; both, and its log-sum-exp, go to memory
+// too.  In two steps of all 256 threads, each ending with a barrier: the copies that the list names are issued in between.
 template <int D>
-__device__ __forceinline__ float small_sum(const float* part, int e) {
-  float s = part[e];
-#pragma unroll
-  for (int i = 1; i < kSmallThreads / D; ++i) s += part[i * D + e];
-  return s;
+__device__ __forceinline__ void small_select(SmallCoarse<D>& l, int32_t* list, int Nc, int K, int own, long long first,
+                                             const SmallForwardArgs& a, SmallRows<D>& v, int tid) {
+  v.request(a.vc + first * D, Nc, tid);
+  const float s = small_dot<D>(a.qc + (first + own) * D, a.kc + first * D, Nc, tid);
+  if ((tid & 3) == 0) l.w[0][tid >> 2] = a.scale * s;
+  if (tid < kSmallCubes) list[tid] = 0;  // (logits that are not numbers may select fewer)
+  __syncthreads();
+  if (tid < 64) {
+    coarse_row<1>(l.w[0], Nc, K, a.lse_c ? a.lse_c + first + own : nullptr, list, 1, tid);
+    __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses stay in order)
+    if (tid < K) a.idx[(first + own) * K + tid] = list[tid];
+  }
+  __syncthreads();
+}
+template <int D>
+__device__ __forceinline__ void small_output(SmallCoarse<D>& l, int Nc, int own, long long first, const SmallForwardArgs& a,
+                                             const SmallRows<D>& v, int tid) {
+  v.weigh(l.w[0], l.part[0], Nc, tid);
+  __syncthreads();
+  if (tid < D) {
+    const float o = small_sum<D>(l.part[0], tid);
+    l.sum[0][tid] = o;
+    a.oc[(first + own) * D + tid] = o;
+  }
+  __syncthreads();
 }
 
 // The coarse backward of one query cube (KEYS false: sum[0] = dQc of the cube) or key cube (KEYS true: sum[0] = dKc, sum[1] =
@@ -64,6 +114,9 @@ __device__ __forceinline__ void small_coarse_bwd(SmallCoarse<D>& l, int Nc, int 
   const int n = tid >> 2;
   const long long row = first + (KEYS ? min(n, Nc - 1) : own);  // the query cube the row terms belong to
   const float lse = lse_c[row], dt = dot[row];
+  SmallRows<D> rp, rr;
+  rp.request(p, Nc, tid);
+  if (KEYS) rr.request(r, Nc, tid);
   const float s = small_dot<D>(x, p, Nc, tid), da = small_dot<D>(y, r, Nc, tid);
   if ((tid & 3) == 0) {
     const float a = fast_exp2((scale * s - lse) * kLog2e);
@@ -71,8 +124,8 @@ __device__ __forceinline__ void small_coarse_bwd(SmallCoarse<D>& l, int Nc, int 
     l.w[1][n] = a;
   }
   __syncthreads();
-  l.part[0][tid] = small_part<D>(l.w[0], p, Nc, tid);
-  if (KEYS) l.part[1][tid] = small_part<D>(l.w[1], r, Nc, tid);
+  rp.weigh(l.w[0], l.part[0], Nc, tid);
+  if (KEYS) rr.weigh(l.w[1], l.part[1], Nc, tid);
   __syncthreads();
   if (tid < D) {
     l.sum[0][tid] = scale * small_sum<D>(l.part[0], tid);

@@ -34,6 +34,7 @@
 // 193 -> 172 us.
 #include <type_traits>
 
+#include "coarse_small.h"
 #include "unit_stream.h"
 #include "vsa_kernels.h"
 
@@ -82,13 +83,14 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
   __syncthreads();
 }
 
-template <int D, int NW, template <class> class UNITS>
+// COARSE: short sequences, whose coarse stage a workgroup does for its block on the way (NW = 4, see coarse_small.h).
+template <int D, int NW, template <class> class UNITS, bool COARSE>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     int Nc_, int K_, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
     const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
     uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
-    int m_blocks, unsigned blocks, unsigned pairs, int stream, unsigned* __restrict__ gang_arrived, unsigned gang_every) {
+    int m_blocks, unsigned blocks, unsigned pairs, int stream, unsigned* __restrict__ gang_arrived, unsigned gang_every, SmallForwardArgs small) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
@@ -104,6 +106,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
   __shared__ float ml[NW * 64 * 2];
+  __shared__ SmallCoarse<COARSE ? D : 4> lc;
+  __shared__ int32_t lc_list[COARSE ? kSmallCubes : 1];
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
   static_assert(KS == NPV && KS > kAhead, "phase interleave");
 
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   if (!kPairs) list.only = wave & 1;
   Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the units after the current one
   Unit u0 = {0, 0, 0};
-  list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
+  if constexpr (!COARSE) list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
   {
     UnitCopy<TL, CubeUnits<TL>> cq;
     cq.init(lane);
@@ -175,6 +179,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     } else if (NW == 2 || wave < 2) {
       cq.all(qb, wave & 1 ? q1 : q0, lds0 + 3 * HALF);
     }
+  }
+  SmallRows<COARSE ? D : 4> vrows;
+  if constexpr (COARSE) {
+    if (!tight) small_select<D>(lc, lc_list, Nc, K, c, bh * Nc, small, vrows, tid);
+    list.take(lc_list, mask, K, lane, Nc);
   }
   list.arrived();  // (and Q with it)
   const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(ml)) + (unsigned)wave * 512u;
@@ -201,7 +210,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
     for (int b = 0; b < 2; ++b) pin_o(o[x][b]);
-  if (!paired) __syncthreads();
+  if constexpr (COARSE) {
+    wait_vmcnt<0>();  // Q has landed (and with it the copies, which the loads of the next step would wait for anyway)
+    if (!tight) small_output<D>(lc, Nc, c, bh * Nc, small, vrows, tid);
+    else __syncthreads();
+  } else if (!paired) {
+    __syncthreads();
+  }
   bf16x8 qreg[2][KS];
   {
     const unsigned char* first_half = smem + (paired ? wave * (4 * HALF) : 0) + 3 * HALF;
@@ -488,6 +503,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 #pragma unroll
     for (int it = 0; it < AT_ONCE; ++it) request(it);
     const float* ocr = oc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // O_c is per cube = m_blocks blocks
+    if constexpr (COARSE) ocr = lc.sum[0] + ch * 8;
     const float4 c0 = *(const float4*)ocr, c1 = *(const float4*)(ocr + 4);
 
     // M, L: reference and sum of a column.  (M = -inf: the list named no valid key at all -- only a caller-supplied
@@ -632,18 +648,22 @@ inline bool fwd_four_waves(int d, unsigned grid, int tiles) {
 }
 
 
+bool fine_fwd_with_coarse(int BH, int Nc, int d, int m_blocks) {
+  return m_blocks == 1 && Nc <= kSmallCubes && BH * Nc <= (d == 128 ? 256 : 512);
+}
+
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, hipStream_t s) {
+                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
-  const unsigned pairs = d == 64 || fwd_four_waves(d, grid, tiles) ? 0 : paired_workgroups(grid, 512);
-  if (fwd_short(d, grid, tiles))
+  if (!coarse && fwd_short(d, grid, tiles))
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
                                  out_token_major, m_blocks, key_cubes_16, s);
+  const unsigned pairs = d == 64 || fwd_four_waves(d, grid, tiles) ? 0 : paired_workgroups(grid, 512);
   // Gangs, one in about every 256 tiles walked, at d = 128 where the K and V of a head are many times an L2, the lists differ
   // and there are 16 generations (heads of 64 MiB: two).  Without / with, lists of N(0,1) inputs, then local ones: 1440
   // blocks (45 MiB), 40 heads, lists of 96 14.3 / 13.1, 13.4 / 13.0 ms, of 180 32.9 / 23.3 (L2 hits 0.38 without); 16 heads,
@@ -662,15 +682,21 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   }
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
-#define VSA_FWD(D_, NW_, LIST_)                                                                                      \
-  k_fine_fwd<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
+  const SmallForwardArgs small = coarse ? *coarse : SmallForwardArgs{};
+#define VSA_FWD(D_, NW_, LIST_, COARSE_)                                                                             \
+  k_fine_fwd<D_, NW_, LIST_, COARSE_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every)
+                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every, small)
 #define VSA_FWD_NW(D_, LIST_)                     \
   do {                                            \
-    if (fwd_four_waves(D_, grid, tiles)) VSA_FWD(D_, 4, LIST_); \
-    else VSA_FWD(D_, 2, LIST_);                   \
+    if (fwd_four_waves(D_, grid, tiles)) VSA_FWD(D_, 4, LIST_, false); \
+    else VSA_FWD(D_, 2, LIST_, false);            \
   } while (0)
+  if (coarse) {
+    if (d == 128) VSA_FWD(128, 4, CubeUnits, true);
+    else VSA_FWD(64, 4, CubeUnits, true);
+    return hipGetLastError();
+  }
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
     if (d == 128) VSA_FWD_NW(128, SubCubeUnits);
     else VSA_FWD_NW(64, SubCubeUnits);

@@ -50,6 +50,11 @@ struct CubeUnits {
     chunk = t / kTilesPerChunk;
     idx_v = list[list_slot(chunk, lane, n)];
   }
+  // a list of up to 64 entries, in LDS
+  __device__ __forceinline__ void take(const int32_t* lds_list, const uint64_t* mask_, int n_, int lane_, int ncubes_) {
+    list = nullptr, mask = mask_, n = n_, lane = lane_, ncubes = ncubes_, chunk = 0;
+    idx_v = lds_list[list_slot(0, lane, n)];
+  }
   __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
   __device__ __forceinline__ void rows(int t, int half, Unit& u) const {
     u.a = (unsigned)__builtin_amdgcn_readlane(idx_v, t & 63) * (unsigned)TL::BYTES + (unsigned)half * (TL::BYTES / 2);

@@ -242,7 +242,10 @@ int enqueue_forward(const vsa_params_t* p, const Geo& g, const void* q, const vo
   VSA_TRY("pool", vsa::launch_pool(g, BH, p->d, w.mask, q, k, v, w.qc, w.kc, w.vc, sub ? 1 : 3, s));
   if (sub) VSA_TRY("pool", vsa::launch_pool_keys16(BH, g.Nc, p->d, w.mask, w.kcnt, k, v, w.kc, w.vc, s));
   const bool pooled = pooled_select(p);
-  VSA_TRY("coarse", vsa::launch_coarse(BH, g.Nc, key_rows(p, g), p->d, p->topk, scale, w.qc, w.kc, w.vc, w.sc, oc, lse_c, idx,
+  const bool small = !given && !pooled && !sub && !(p->flags & (VSA_FLAG_COARSE_FUSED | VSA_FLAG_COARSE_UNFUSED)) &&
+                     vsa::fine_fwd_with_coarse(BH, g.Nc, p->d, g.m);
+  if (!small)
+    VSA_TRY("coarse", vsa::launch_coarse(BH, g.Nc, key_rows(p, g), p->d, p->topk, scale, w.qc, w.kc, w.vc, w.sc, oc, lse_c, idx,
                             (given || pooled) ? 0 : 1, (pooled || sub) ? 0 : coarse_form(p, g), w.kcnt, s));
   // the fine stage works on 64-row blocks: a cube of m blocks contributes m list entries, a tile of
   // (1,2,2) cubes its four cubes
@@ -255,9 +258,10 @@ int enqueue_forward(const vsa_params_t* p, const Geo& g, const void* q, const vo
     VSA_TRY("expand_lists", vsa::launch_expand_lists(BH, g.Nc, p->topk, g.m, idx, w.idx_blocks, s));
     lists = w.idx_blocks;
   }
+  const vsa::SmallForwardArgs coarse_args = {w.qc, w.kc, w.vc, oc, lse_c, idx, scale};
   // (the coarse scores have been read by now: [BH, Nc, key rows] floats, more than the counters need by far)
   VSA_TRY("fine_fwd", vsa::launch_fine_fwd(BH, g.Nb, p->d, p->topk * blocks_per_entry(p, g), scale, q, k, v, gate_c, gate_f, lists, oc, w.mask, out,
-                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, (unsigned*)w.sc, s));
+                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, (unsigned*)w.sc, small ? &coarse_args : nullptr, s));
   return VSA_OK;
 }
 

@@ -22,11 +22,20 @@ hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, cons
                                  const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                                  const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
                                  int m_blocks, int key_cubes_16, hipStream_t s);
-// gang_scratch: BH*Nc/32 + 24 counters' worth of memory that nothing else uses during the launch
+// What the forward of a short sequence forms its coarse stage from, row by row in the fine kernel, and where it leaves it.
+struct SmallForwardArgs {
+  const float *qc, *kc, *vc;
+  float *oc, *lse_c;
+  int32_t* idx;
+  float scale;
+};
+bool fine_fwd_with_coarse(int BH, int Nc, int d, int m_blocks);
+// gang_scratch: BH*Nc/32 + 24 counters' worth of memory that nothing else uses during the launch.  `coarse` (or NULL): the coarse
+// stage is done on the way, idx and oc are its results.
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, hipStream_t s);
+                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, hipStream_t s);
 // lists of cubes -> lists of 64-row blocks, for cubes of m blocks: every block of query cube c gets
 // the m blocks of each of the cube's K key cubes, ascending ([BH,Nc,K] -> [BH,Nc*m,K*m])
 // mismatched granularity: top-K on the coarse map pooled over (1,2,2) cubes, and its lists of tiles

@@ -92,6 +92,12 @@ typedef enum {
                                      not together with VSA_FLAG_SELECT_POOLED_2X2; the coarse stage runs
                                      as three launches.  Pass the flag to vsa_forward, vsa_backward and
                                      vsa_workspace_bytes alike. */
+#define VSA_FLAG_RASTER_IO 256u /* the tensors that a caller with raster activations exchanges with the attention are
+                                  raster token-major, bf16 [B, T*Hh*W, H, d], and need no permutation pass:
+                                  vsa_forward writes `out`, vsa_backward reads `dout` and writes dq, dk, dv,
+                                  dgate_c and dgate_f that way (valid tokens only; a raster tensor has no pad
+                                  rows).  q, k, v, the gates and out_fine stay tiled.  Overrides
+                                  VSA_FLAG_OUT_TOKEN_MAJOR. */
 #define VSA_MIN_SOFTMAX_SCALE (1.0f / 64.0f) /* smallest explicit softmax_scale accepted (the pad-key bias of
                                                -30000 must still underflow the exponential once scaled) */
 #define VSA_MAX_CUBES 4096        /* largest supported Np / 64 (= Nc for 64-token cubes)  */

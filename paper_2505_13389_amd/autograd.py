@@ -23,43 +23,44 @@ class _VideoSparseAttention(torch.autograd.Function):
         T, Hh, W = grid
         assert L == T * Hh * W, "q is [B, T*Hh*W, H, d]"
         pb = vsa.Problem(B, H, T, Hh, W, d, topk, tuple(cube), float(softmax_scale or 0.0), int(flags))
-        buf = vsa.Buffers(pb, device=q.device, backward=False)
-        shape = (B, H, buf.Np, d)
+        Np, Nc = vsa.vsa_padded_tokens(pb)
+        shape = (B, H, Np, d)
+        bf = dict(dtype=torch.bfloat16, device=q.device)
+        f32 = dict(dtype=torch.float32, device=q.device)
 
         def tiled(x):
-            y = torch.empty(shape, dtype=torch.bfloat16, device=q.device)
+            y = torch.empty(shape, **bf)
             vsa.vsa_tile_permute(pb, x.contiguous(), y, inverse=False, blhd=True)
             return y
 
         tq, tk, tv, tgc = tiled(q), tiled(k), tiled(v), tiled(gate_c)
         tgf = None if gate_f is None else tiled(gate_f)
-        buf.forward(tq, tk, tv, tgc, tgf)
-        out = torch.empty_like(q)
-        vsa.vsa_tile_permute(pb, buf.out, out, inverse=True, blhd=True)
-        ctx.pb, ctx.buf = pb, buf
+        # the attention writes raster tokens and, in the backward, reads and writes them: no permutation on that side
+        pb = vsa.Problem(B, H, T, Hh, W, d, topk, tuple(cube), float(softmax_scale or 0.0),
+                         int(flags) | vsa.VSA_FLAG_RASTER_IO)
+        out = torch.empty_like(q, memory_format=torch.contiguous_format)
+        rows = Nc // 4 if pb.flags & vsa.VSA_FLAG_SELECT_POOLED_2X2 else Nc
+        idx = torch.empty((B, H, rows, pb.topk), dtype=torch.int32, device=q.device)
+        out_fine, lse_fine = torch.empty(shape, **bf), torch.empty((B, H, Np), **f32)
+        out_coarse, lse_coarse = torch.empty((B, H, Nc, d), **f32), torch.empty((B, H, Nc), **f32)
+        workspace = torch.empty(vsa.vsa_workspace_bytes(pb, False), dtype=torch.uint8, device=q.device)
+        vsa.vsa_forward(pb, tq, tk, tv, tgc, tgf, out, idx, out_fine, lse_fine, out_coarse, lse_coarse, workspace)
+        ctx.pb, ctx.kept = pb, (idx, out_fine, lse_fine, out_coarse, lse_coarse)
         ctx.save_for_backward(tq, tk, tv, tgc, tgf)
         return out
 
     @staticmethod
     def backward(ctx, dout):
-        pb, fw = ctx.pb, ctx.buf
+        pb = ctx.pb
         tq, tk, tv, tgc, tgf = ctx.saved_tensors
-        shape = tq.shape
-        tdo = torch.empty(shape, dtype=torch.bfloat16, device=tq.device)
-        vsa.vsa_tile_permute(pb, dout.contiguous(), tdo, inverse=False, blhd=True)
-        bw = vsa.Buffers(pb, device=tq.device, backward=True, with_gate_f=tgf is not None)
-        vsa.vsa_backward(pb, tq, tk, tv, tgc, tgf, tdo, fw.block_idx, fw.out_fine, fw.lse_fine, fw.out_coarse,
-                         fw.lse_coarse, bw.dq, bw.dk, bw.dv, bw.dgate_c, bw.dgate_f, bw.workspace)
-
-        def raster(x):
-            if x is None:
-                return None
-            y = torch.empty((pb.B, pb.T * pb.Hh * pb.W, pb.H, pb.d), dtype=torch.bfloat16, device=x.device)
-            vsa.vsa_tile_permute(pb, x, y, inverse=True, blhd=True)
-            return y
-
-        return (raster(bw.dq), raster(bw.dk), raster(bw.dv), raster(bw.dgate_c), raster(bw.dgate_f),
-                None, None, None, None, None)
+        idx, out_fine, lse_fine, out_coarse, lse_coarse = ctx.kept
+        dout = dout.contiguous()
+        dq, dk, dv, dgc = (torch.empty_like(dout) for _ in range(4))
+        dgf = None if tgf is None else torch.empty_like(dout)
+        workspace = torch.empty(vsa.vsa_workspace_bytes(pb, True), dtype=torch.uint8, device=dout.device)
+        vsa.vsa_backward(pb, tq, tk, tv, tgc, tgf, dout, idx, out_fine, lse_fine, out_coarse, lse_coarse, dq, dk, dv, dgc,
+                         dgf, workspace)
+        return dq, dk, dv, dgc, dgf, None, None, None, None, None
 
 
 def video_sparse_attention(q, k, v, gate_c, gate_f=None, *, grid, topk, cube=(4, 4, 4), softmax_scale=None, flags=0):

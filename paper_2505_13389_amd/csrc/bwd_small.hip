@@ -584,7 +584,8 @@ __device__ __forceinline__ void map_one(MapOneLds& l, const MapArgs& a, int bh, 
 // 256 blocks, 12 heads 1044 -> 1035, d = 64, 16 heads 795 -> 783; 280 blocks, 5 heads, through the op 562 -> 548.
 // (Workgroups of 256 threads: 57 and, for the last, whose map is then the longer part, 555; of 1024: 57 and 544, but
 // 788 for the one before.)
-template <int D, bool ONCE>
+// KIND 0, 1: dout and the gates' gradients tiled, 1 past the caches; 2: raster.
+template <int D, int KIND>
 __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs map_args, unsigned cubes, int Nc, int m_blocks, const uint64_t* __restrict__ mask, const uint4* __restrict__ dout,
                                                  const uint4* __restrict__ gc, const uint4* __restrict__ gf,
                                                  const uint4* __restrict__ of, const float* __restrict__ oc,
@@ -592,7 +593,8 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
                                                  uint4* __restrict__ dof, float* __restrict__ rowd, float inv_sl2,
                                                  float* __restrict__ doc, float* __restrict__ dot,
                                                  const float* __restrict__ lse_f, int H, long long do_head_stride,
-                                                 long long do_row_stride) {
+                                                 long long do_row_stride, RasterMap raster) {
+  constexpr bool ONCE = KIND == 1;
   constexpr int CPR = D / 8, RG = 256 / CPR, RPT = kTile / RG;
   __shared__ union {
     float part[kPreThreads / 256][RG][D + 4];
@@ -621,6 +623,7 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
   const long long blk = (bh * Nc + c) * m_blocks + sb;  // block index over all (b, h)
   const uint64_t m = mask[c * m_blocks + sb];
   const long long row0 = blk * (long long)kTile;
+  const RasterRows rows_r(raster, bh, c * m_blocks + sb, CPR);
   // dout may be head-major [B,H,Np,D] or token-major [B,Np,H,D] (see the forward's `out`)
   const long long Npad = (long long)Nc * m_blocks * kTile;
   const long long do0 = (bh / H) * ((long long)H * Npad * CPR) + (bh % H) * do_head_stride +
@@ -634,7 +637,7 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
     float dsum = 0.f;
     if (valid) {
       float go[8], gcv[8], gfv[8], ofv[8], t0[8], t1[8], t2[8];
-      unpack8(load16<ONCE>(dout + do0 + r * do_row_stride + ch), go);
+      unpack8(load16<ONCE>(dout + (KIND == 2 ? rows_r.at(r) : do0 + r * do_row_stride) + ch), go);
       unpack8(load16<ONCE>(gc + g), gcv);
       unpack8(load16<ONCE>(of + g), ofv);
       if (gf) unpack8(load16<ONCE>(gf + g), gfv);
@@ -655,8 +658,11 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
 #pragma unroll
       for (int e = 0; e < 8; ++e) dsum = fmaf(t2r[e], ofv[e], dsum);
     }
-    store16<ONCE>(dgc + g, o_gc);
-    if (dgf) store16<ONCE>(dgf + g, o_gf);
+    if (KIND < 2 || valid) {
+      const long long to = KIND == 2 ? rows_r.at(r) + ch : g;
+      store16<ONCE>(dgc + to, o_gc);
+      if (dgf) store16<ONCE>(dgf + to, o_gf);
+    }
     dof[g] = o_dof;
 #pragma unroll
     for (int o = CPR / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
@@ -688,7 +694,7 @@ __global__ __launch_bounds__(kPreThreads) void k_bwd_pre(int map_blocks, MapArgs
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
                           void* dof, float* rowd, float scale, float* doc, float* dot, const float* lse_f, int H,
-                          int dout_token_major, const MapArgs* map, hipStream_t s) {
+                          int dout_token_major, const MapArgs* map, const RasterMap& raster, hipStream_t s) {
   const MapArgs m = map ? *map : MapArgs{};
   const int mb = map ? BH : 0;  // workgroups that transpose the map, ahead of the others
   const unsigned cubes = (unsigned)(BH * Nc), per = kPreThreads / 256, grid = (cubes + per - 1) / per + (unsigned)mb;
@@ -696,16 +702,18 @@ hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* m
   const long long cpr = d / 8, Np = (long long)Nc * m_blocks * kTile;
   const long long dhs = dout_token_major ? cpr : Np * cpr, drs = dout_token_major ? H * cpr : cpr;
   const bool stream = (long long)BH * Np * d * 2 >= kStreamBytes;
-#define VSA_PRE(D_, ONCE_)                                                                                              \
-  k_bwd_pre<D_, ONCE_><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, \
+#define VSA_PRE(D_, KIND_)                                                                                              \
+  k_bwd_pre<D_, KIND_><<<grid, kPreThreads, 0, s>>>(mb, m, cubes, Nc, m_blocks, mask, (const uint4*)dout, (const uint4*)gate_c, \
                                                     (const uint4*)gate_f, (const uint4*)out_fine, oc, (uint4*)dgate_c,  \
-                                                    (uint4*)dgate_f, (uint4*)dof, rowd, inv_sl2, doc, dot, lse_f, H, dhs, drs)
+                                                    (uint4*)dgate_f, (uint4*)dof, rowd, inv_sl2, doc, dot, lse_f, H, dhs, drs, raster)
   if (d == 128) {
-    if (stream) VSA_PRE(128, true);
-    else VSA_PRE(128, false);
+    if (raster.on) VSA_PRE(128, 2);
+    else if (stream) VSA_PRE(128, 1);
+    else VSA_PRE(128, 0);
   } else {
-    if (stream) VSA_PRE(64, true);
-    else VSA_PRE(64, false);
+    if (raster.on) VSA_PRE(64, 2);
+    else if (stream) VSA_PRE(64, 1);
+    else VSA_PRE(64, 0);
   }
 #undef VSA_PRE
   return hipGetLastError();

@@ -46,7 +46,7 @@ __device__ __forceinline__ void dq_block(
     const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v, const uint4* __restrict__ dof,
     const int32_t* __restrict__ idx, const float* __restrict__ rowd, const float* __restrict__ dqc,
     const uint64_t* __restrict__ mask, uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream,
-    const SmallCoarseArgs& sc, SmallCoarse<D>* lc) {
+    const RasterMap& raster, const SmallCoarseArgs& sc, SmallCoarse<D>* lc) {
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
@@ -365,8 +365,11 @@ __device__ __forceinline__ void dq_block(
   // Merge the partial results of the block's wavefronts (P of them), scale, add the pooled-gradient term, store.
   const uint64_t qmask = mask[c];
   const float inv_cnt = 1.0f / (float)cube_count(mask, c, m_blocks);
-  auto finish = [&](auto parts_tag, auto once_tag) {
-    constexpr bool ONCE = decltype(once_tag)::value;
+  // KIND 0, 1: dQ tiled, 1 past the caches; 2: raster
+  auto finish = [&](auto parts_tag, auto kind_tag) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool ONCE = KIND == 1;
+    const RasterRows rows_r(raster, bh, c, CPR);
     constexpr int P = decltype(parts_tag)::value, NT = 64 * P, LPT = kTile * CPR / NT;
     static_assert(NT % CPR == 0, "a thread keeps its column chunk");
     const int t = P == 1 ? lane : tid, ch = t % CPR;
@@ -411,13 +414,16 @@ __device__ __forceinline__ void dq_block(
         for (int e = 0; e < 8; ++e) res[e] = fmaf(sum[e], scale, pooled[e]);
         ov = pack8(res);
       }
-      store16<ONCE>(dq + (q0 + r) * CPR + ch, ov);
+      if (KIND < 2) store16<ONCE>(dq + (q0 + r) * CPR + ch, ov);
+      else if ((qmask >> r) & 1) dq[rows_r.at(r) + ch] = ov;
     }
   };
   const std::integral_constant<int, 1> one;
   const std::integral_constant<int, NW> all;
-  if (paired) stream ? finish(one, std::true_type{}) : finish(one, std::false_type{});
-  else stream ? finish(all, std::true_type{}) : finish(all, std::false_type{});
+  const std::integral_constant<int, 0> plain;
+  const std::integral_constant<int, 2> out_of_order;
+  if (paired) raster.on ? finish(one, out_of_order) : stream ? finish(one, one) : finish(one, plain);
+  else raster.on ? finish(all, out_of_order) : stream ? finish(all, one) : finish(all, plain);
 }
 
 template <int D, int NW, template <class> class UNITS>
@@ -425,11 +431,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
     const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
     const float* __restrict__ rowd, const float* __restrict__ dqc, const uint64_t* __restrict__ mask,
-    uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream) {
+    uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream, RasterMap raster) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<D, NW>::LDS];
   __shared__ uint32_t masks[NW * 128];
   dq_block<D, NW, UNITS, false>(smem, masks, blockIdx.x, gridDim.x, Nc, K, sl2, scale, q, k, v, dof, idx, rowd, dqc, mask, dq,
-                                m_blocks, blocks, pairs, stream, SmallCoarseArgs{}, nullptr);
+                                m_blocks, blocks, pairs, stream, raster, SmallCoarseArgs{}, nullptr);
 }
 
 // Both passes of a small problem in one launch, four wavefronts per workgroup: neither fills the chip, so they run side by
@@ -444,7 +450,7 @@ __global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
     const int32_t* __restrict__ order, int items, int32_t* __restrict__ split, float* parts, int cap,
     const float* __restrict__ rowd, const float* __restrict__ dqc, const float* __restrict__ dkc, const float* __restrict__ dvc,
     const uint64_t* __restrict__ mask, uint4* __restrict__ dq, uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks,
-    SmallCoarseArgs sc) {
+    RasterMap raster, SmallCoarseArgs sc) {
   constexpr int LDS = DkvShape<D, 4>::LDS > DqShape<D, 4>::LDS ? DkvShape<D, 4>::LDS : DqShape<D, 4>::LDS;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
   __shared__ uint32_t masks[4 * 128];
@@ -452,10 +458,10 @@ __global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
   __shared__ SmallCoarse<D> lc;
   if (blockIdx.x < dkv_blocks)
     dkv_block<D, 4, false, COARSE>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items, split, parts,
-                                   cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, 0, sc, &lc);
+                                   cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, 0, raster, sc, &lc);
   else
     dq_block<D, 4, CubeUnits, COARSE>(smem, masks, blockIdx.x - dkv_blocks, gridDim.x - dkv_blocks, Nc, K, sl2, scale, q, k, v, dof,
-                                      idx, rowd, dqc, mask, dq, m_blocks, (unsigned)(BH * Nc), 0, 0, sc, &lc);
+                                      idx, rowd, dqc, mask, dq, m_blocks, (unsigned)(BH * Nc), 0, 0, raster, sc, &lc);
 }
 
 bool fine_bwd_in_one(int BH, int Nc, int key_cubes_16) { return !key_cubes_16 && BH * Nc <= kDkvFourWaves; }
@@ -465,14 +471,14 @@ hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const 
                                const void* dof, const int32_t* idx, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dqc, const float* dkc, const float* dvc,
                                const uint64_t* mask, void* dq, void* dk, void* dv, int m_blocks, const float* qc, const float* kc,
-                               const float* vc, const float* doc, const float* lse_c, const float* dot, hipStream_t s) {
+                               const float* vc, const float* doc, const float* lse_c, const float* dot, const RasterMap& raster, hipStream_t s) {
   const int items = Nc + cap;
   const unsigned dkv_blocks = dkv_grid(BH, items), grid = dkv_blocks + (unsigned)(BH * Nc);  // (dkv_grid is a multiple of 8: the XCDs stay)
   const SmallCoarseArgs sc = {qc, kc, vc, doc, lse_c, dot};
 #define VSA_ONE(D_, COARSE_)                                                                                             \
   k_fine_bwd_one<D_, COARSE_><<<grid, 256, 0, s>>>(dkv_blocks, BH, Nc, K, scale * kLog2e, scale, (const uint4*)q, (const uint4*)k, \
                                                    (const uint4*)v, (const uint4*)dof, idx, col, order, items, split, parts, cap, \
-                                                   rowd, dqc, dkc, dvc, mask, (uint4*)dq, (uint4*)dk, (uint4*)dv, m_blocks, sc)
+                                                   rowd, dqc, dkc, dvc, mask, (uint4*)dq, (uint4*)dk, (uint4*)dv, m_blocks, raster, sc)
   const bool coarse = fine_bwd_with_coarse(Nc, m_blocks);
   if (d == 128) {
     if (coarse) VSA_ONE(128, true);
@@ -493,7 +499,7 @@ constexpr unsigned kDqFourWaves = D == 128 ? 256 : 512;
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,
-                              hipStream_t s) {
+                              const RasterMap& raster, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
@@ -501,7 +507,7 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
   const unsigned pairs = four ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
 #define VSA_DQ(D_, NW_, LIST_)                                                                                          \
   k_fine_bwd_dq<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
-                                                (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks, grid, pairs, stream)
+                                                (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks, grid, pairs, stream, raster)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
     if (d == 128 && four) VSA_DQ(128, 4, SubCubeUnits);
     else if (d == 128) VSA_DQ(128, 2, SubCubeUnits);

@@ -88,7 +88,8 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
                                           float* parts, int cap, const float* __restrict__ rowd,
                                           const float* __restrict__ dkc, const float* __restrict__ dvc,
                                           const uint64_t* __restrict__ mask, uint4* __restrict__ dk, uint4* __restrict__ dv,
-                                          int m_blocks, int stream, const SmallCoarseArgs& sc, SmallCoarse<D>* lc) {
+                                          int m_blocks, int stream, const RasterMap& raster, const SmallCoarseArgs& sc,
+                                          SmallCoarse<D>* lc) {
   using TL = Tile<D>;
   using SH = DkvShape<D, NW>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
@@ -488,8 +489,11 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
 
   // Add the partial results in wavefront order through LDS: dK, then dV.
   static_assert(NW * 64 * OS * 4 <= SH::LDS, "merge buffers must fit");
-  auto finish = [&](auto once_tag) {
-    constexpr bool ONCE = decltype(once_tag)::value;
+  // KIND 0, 1: dK and dV tiled, 1 past the caches; 2: raster
+  auto finish = [&](auto kind_tag) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool ONCE = KIND == 1;
+    const RasterRows rows_r(raster, bh, j, CPR);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       __syncthreads();
@@ -548,12 +552,14 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
           }
           ov = pack8(res);
         }
-        store16<ONCE>(dst + (rows0 + j * kTile + r) * CPR + ch, ov);
+        if (KIND < 2) store16<ONCE>(dst + (rows0 + j * kTile + r) * CPR + ch, ov);
+        else if ((kmask >> r) & 1) dst[rows_r.at(r) + ch] = ov;
       }
     }
   };
-  if (stream) finish(std::true_type{});
-  else finish(std::false_type{});
+  if (raster.on) finish(std::integral_constant<int, 2>{});
+  else if (stream) finish(std::integral_constant<int, 1>{});
+  else finish(std::integral_constant<int, 0>{});
   if (slot < 0) return;
 
   // A run of a split list.  The last of them to arrive (the count starts at zero, written with the list's descriptor: cube,
@@ -619,7 +625,8 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
         }
         ov = pack8(res);
       }
-      dst[(rows0 + j * kTile + r) * CPR + ch] = ov;
+      if (!raster.on) dst[(rows0 + j * kTile + r) * CPR + ch] = ov;
+      else if ((kmask >> r) & 1) dst[RasterRows(raster, bh, j, CPR).at(r) + ch] = ov;
     }
   }
 }

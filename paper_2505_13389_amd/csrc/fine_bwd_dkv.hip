@@ -11,17 +11,19 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fine_bwd_dkv(int BH, int Nc, int
                                                              int32_t* __restrict__ split, float* parts, int cap,
                                                              const float* __restrict__ rowd, const float* __restrict__ dkc,
                                                              const float* __restrict__ dvc, const uint64_t* __restrict__ mask,
-                                                             uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks, int stream) {
+                                                             uint4* __restrict__ dk, uint4* __restrict__ dv, int m_blocks, int stream,
+                                                             RasterMap raster) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D, NW>::LDS];
   __shared__ int last_run;
   dkv_block<D, NW, SUB, false>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items_per_bh, split,
-                               parts, cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, stream, SmallCoarseArgs{}, nullptr);
+                               parts, cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, stream, raster, SmallCoarseArgs{}, nullptr);
 }
 
 hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                                const void* dof, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dkc, const float* dvc,
-                               const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s) {
+                               const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, const RasterMap& raster,
+                               hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const int items = Nc + cap;
   const int stream = (long long)BH * Nc * kTile * d * 2 >= kStreamBytes;
@@ -29,7 +31,7 @@ hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const 
 #define VSA_DKV(D_, NW_, SUB_)                                                                                                \
   k_fine_bwd_dkv<D_, NW_, SUB_><<<grid, 64 * NW_, 0, s>>>(BH, Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
                                                           (const uint4*)dof, col, order, items, split, parts, cap, rowd, dkc, dvc, \
-                                                          mask, (uint4*)dk, (uint4*)dv, m_blocks, stream)
+                                                          mask, (uint4*)dk, (uint4*)dv, m_blocks, stream, raster)
   if (key_cubes_16) {  // lists of key cubes of 16 tokens: the pooled terms dkc, dvc are [BH, 4 Nc, d]
     const bool four = BH * Nc <= kDkvFourWaves;  // (lists of blocks: launch_fine_bwd_one)
     if (d == 128 && four) VSA_DKV(128, 4, true);

@@ -84,13 +84,15 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
 }
 
 // COARSE: short sequences, whose coarse stage a workgroup does for its block on the way (NW = 4, see coarse_small.h).
-template <int D, int NW, template <class> class UNITS, bool COARSE>
+// RASTER: RasterMap or NoRaster (as a runtime choice it cost the smallest launches 0.8 us of 13).
+template <int D, int NW, template <class> class UNITS, bool COARSE, class RASTER>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     int Nc_, int K_, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
     const float* __restrict__ oc, const uint64_t* __restrict__ mask, uint4* __restrict__ out,
     uint4* __restrict__ out_fine, float* __restrict__ lse_f, int H, long long out_head_stride, long long out_row_stride,
-    int m_blocks, unsigned blocks, unsigned pairs, int stream, unsigned* __restrict__ gang_arrived, unsigned gang_every, SmallForwardArgs small) {
+    int m_blocks, unsigned blocks, unsigned pairs, int stream, unsigned* __restrict__ gang_arrived, unsigned gang_every, SmallForwardArgs small, RASTER raster) {
+  constexpr bool kRaster = std::is_same_v<RASTER, RasterMap>;
   using TL = Tile<D>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
@@ -486,8 +488,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   const long long out0 = (bh / H) * ((long long)H * Nc * kTile * CPR) + (bh % H) * out_head_stride;
   // ---- merge the partial results of the block's wavefronts (P of them), normalise, gate, store
   const uint64_t qmask = mask[c];
-  auto finish = [&](auto parts_tag, auto once_tag) {
-    constexpr bool ONCE = decltype(once_tag)::value;
+  // KIND 0, 1: `out` tiled, 1 past the caches; 2: raster
+  auto finish = [&](auto parts_tag, auto kind_tag) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool ONCE = KIND == 1;
     constexpr int P = decltype(parts_tag)::value, NT = 64 * P, LPT = kTile * CPR / NT, AT_ONCE = LPT < 8 ? LPT : 8;
     static_assert(NT % CPR == 0, "a thread keeps its column chunk");
     const int t = P == 1 ? lane : tid, ch = t % CPR;
@@ -564,6 +568,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     const bool check = kByRow || __any(most > kTightSum);  // (only then can O have overflowed before it was normalised)
     bool overflow = false;
     uint4* const orow = out + out0 + (long long)(c * kTile + t / CPR) * out_row_stride + ch;
+    auto raster_row = [&](int r) {
+      if constexpr (kRaster) return RasterRows(raster, bh, c, CPR).at(r);
+      else return 0ll;
+    };
     const float ocv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
 #pragma unroll
     for (int it = 0; it < LPT; ++it) {
@@ -595,7 +603,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         for (int e = 0; e < 8; ++e) nought = fmaf(of[e], 0.f, nought);  // NaN unless all of them are finite
         overflow |= live && nought != 0.f && (!kByRow || seen > kTightSum);
       }
-      store16<ONCE>(orow + (long long)(it * (NT / CPR)) * out_row_stride, ov);
+      if (KIND < 2) store16<ONCE>(orow + (long long)(it * (NT / CPR)) * out_row_stride, ov);
+      else if (live) out[raster_row(r) + ch] = ov;
       if (out_fine) out_fine[g0 + it * NT] = fv;
       if (kByRow && lse_f && ch == 0) lse_f[rows0 + c * kTile + r] = live ? logsum(Mr, Lr) : 0.f;
       if (LPT > AT_ONCE) __builtin_amdgcn_sched_barrier(0);  // (item by item: the loads of later ones stay ahead of the stores)
@@ -604,13 +613,18 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   };
   if constexpr (kPairs) {
     if (paired) {
-      const bool overflow = stream ? finish(std::integral_constant<int, 1>{}, std::true_type{}) : finish(std::integral_constant<int, 1>{}, std::false_type{});
+      const std::integral_constant<int, 1> one;
+      bool overflow;
+      if constexpr (kRaster) overflow = finish(one, std::integral_constant<int, 2>{});
+      else overflow = stream ? finish(one, one) : finish(one, std::integral_constant<int, 0>{});
       if (tight || !__any(overflow)) return;
       continue;
     }
   }
   const std::integral_constant<int, NW> all;
-  const bool overflow = stream ? finish(all, std::true_type{}) : finish(all, std::false_type{});
+  bool overflow;
+  if constexpr (kRaster) overflow = finish(all, std::integral_constant<int, 2>{});
+  else overflow = stream ? finish(all, std::integral_constant<int, 1>{}) : finish(all, std::integral_constant<int, 0>{});
   if (tight) return;
   if (overflow) again = 1;
   __syncthreads();
@@ -655,14 +669,14 @@ bool fine_fwd_with_coarse(int BH, int Nc, int d, int m_blocks) {
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, hipStream_t s) {
+                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, const RasterMap& raster, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
   if (!coarse && fwd_short(d, grid, tiles))
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
-                                 out_token_major, m_blocks, key_cubes_16, s);
+                                 out_token_major, m_blocks, key_cubes_16, raster, s);
   const unsigned pairs = d == 64 || fwd_four_waves(d, grid, tiles) ? 0 : paired_workgroups(grid, 512);
   // Gangs, one in about every 256 tiles walked, at d = 128 where the K and V of a head are many times an L2, the lists differ
   // and there are 16 generations (heads of 64 MiB: two).  Without / with, lists of N(0,1) inputs, then local ones: 1440
@@ -683,29 +697,32 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
   const SmallForwardArgs small = coarse ? *coarse : SmallForwardArgs{};
-#define VSA_FWD(D_, NW_, LIST_, COARSE_)                                                                             \
-  k_fine_fwd<D_, NW_, LIST_, COARSE_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,  \
-                                             (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every, small)
-#define VSA_FWD_NW(D_, LIST_)                     \
-  do {                                            \
-    if (fwd_four_waves(D_, grid, tiles)) VSA_FWD(D_, 4, LIST_, false); \
-    else VSA_FWD(D_, 2, LIST_, false);            \
+#define VSA_FWD_AS(D_, NW_, LIST_, COARSE_, RASTER_, MAP_)                                                            \
+  k_fine_fwd<D_, NW_, LIST_, COARSE_, RASTER_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(                           \
+      Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v, (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, \
+      (uint4*)out, (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every, small, MAP_)
+#define VSA_FWD(D_, NW_, LIST_, COARSE_)                                         \
+  do {                                                                           \
+    if (raster.on) VSA_FWD_AS(D_, NW_, LIST_, COARSE_, RasterMap, raster);       \
+    else VSA_FWD_AS(D_, NW_, LIST_, COARSE_, NoRaster, NoRaster{});              \
   } while (0)
+  const bool four = fwd_four_waves(d, grid, tiles);
   if (coarse) {
     if (d == 128) VSA_FWD(128, 4, CubeUnits, true);
     else VSA_FWD(64, 4, CubeUnits, true);
-    return hipGetLastError();
-  }
-  if (key_cubes_16) {  // K counts key cubes of 16 tokens
-    if (d == 128) VSA_FWD_NW(128, SubCubeUnits);
-    else VSA_FWD_NW(64, SubCubeUnits);
+  } else if (key_cubes_16) {  // K counts key cubes of 16 tokens
+    if (d == 128 && four) VSA_FWD(128, 4, SubCubeUnits, false);
+    else if (d == 128) VSA_FWD(128, 2, SubCubeUnits, false);
+    else if (four) VSA_FWD(64, 4, SubCubeUnits, false);
+    else VSA_FWD(64, 2, SubCubeUnits, false);
   } else {
-    if (d == 128) VSA_FWD_NW(128, CubeUnits);
-    else VSA_FWD_NW(64, CubeUnits);
+    if (d == 128 && four) VSA_FWD(128, 4, CubeUnits, false);
+    else if (d == 128) VSA_FWD(128, 2, CubeUnits, false);
+    else if (four) VSA_FWD(64, 4, CubeUnits, false);
+    else VSA_FWD(64, 2, CubeUnits, false);
   }
-#undef VSA_FWD_NW
 #undef VSA_FWD
+#undef VSA_FWD_AS
   return hipGetLastError();
 }
 

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float 
                                                      const uint64_t* __restrict__ mask, uint4* __restrict__ out,
                                                      uint4* __restrict__ out_fine, float* __restrict__ lse_f,
                                                      int H, long long out_head_stride, long long out_row_stride,
-                                                     int m_blocks) {
+                                                     int m_blocks, RasterMap raster) {
   using TL = TileCopy<D>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, LPT = TL::LPT;
   constexpr int OS = D;  // fp32 row stride of the merge buffer
@@ -481,7 +481,8 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float 
       ov = pack8(res);
       fv = pack8(of);
     }
-    out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
+    if (!raster.on) out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
+    else if (valid) out[RasterRows(raster, bh, c, CPR).at(r) + ch] = ov;
     if (out_fine) out_fine[g] = fv;
   }
   if (lse_f && tid < kTile) {
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float 
 hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, hipStream_t s) {
+                           int m_blocks, int key_cubes_16, const RasterMap& raster, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
@@ -505,7 +506,7 @@ hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, cons
 #define VSA_FWD_SHORT(D_, LIST_)                                                                                           \
   k_fine_fwd_short<D_, LIST_><<<grid, 256, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,           \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks)
+                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, raster)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
     if (d == 128) VSA_FWD_SHORT(128, SubCubeList);
     else VSA_FWD_SHORT(64, SubCubeList);

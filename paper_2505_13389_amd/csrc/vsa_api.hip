@@ -80,6 +80,10 @@ int check_topk(const vsa_params_t* p, const Geo& g) {
 
 bool misaligned(const void* ptr) { return ptr && ((uintptr_t)ptr & 15u); }
 
+vsa::RasterMap raster_of(const vsa_params_t* p, const Geo& g) {
+  return (p->flags & VSA_FLAG_RASTER_IO) ? vsa::raster_map(g, p->H) : vsa::tiled_map();
+}
+
 float scale_of(const vsa_params_t* p) { return p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d); }
 
 // Bump allocator over the caller's workspace.
@@ -261,7 +265,7 @@ int enqueue_forward(const vsa_params_t* p, const Geo& g, const void* q, const vo
   const vsa::SmallForwardArgs coarse_args = {w.qc, w.kc, w.vc, oc, lse_c, idx, scale};
   // (the coarse scores have been read by now: [BH, Nc, key rows] floats, more than the counters need by far)
   VSA_TRY("fine_fwd", vsa::launch_fine_fwd(BH, g.Nb, p->d, p->topk * blocks_per_entry(p, g), scale, q, k, v, gate_c, gate_f, lists, oc, w.mask, out,
-                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, (unsigned*)w.sc, small ? &coarse_args : nullptr, s));
+                               out_fine, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, g.m, sub ? 1 : 0, (unsigned*)w.sc, small ? &coarse_args : nullptr, raster_of(p, g), s));
   return VSA_OK;
 }
 
@@ -383,9 +387,10 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
   }
   const vsa::MapArgs map = {g.Nb, kb, w.seg, w.cap, lists, w.row_ptr, w.col, w.order, w.split};
   float* dot = w.dsc;  // [BH, Nc], read by the one-launch coarse backward; the other form overwrites it with its scratch
+  const vsa::RasterMap raster = raster_of(p, g);
   const bool map_aside = vsa::map_with_bwd_pre(g.Nb, sub ? 1 : 0);
   VSA_TRY("bwd_pre", vsa::launch_bwd_pre(BH, g.Nc, g.m, p->d, w.mask, dout, gate_c, gate_f, out_fine, out_coarse, dgate_c, dgate_f,
-                              w.dof, w.rowd, scale, w.doc, dot, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, map_aside ? &map : nullptr, s));
+                              w.dof, w.rowd, scale, w.doc, dot, lse_fine, p->H, (p->flags & VSA_FLAG_OUT_TOKEN_MAJOR) ? 1 : 0, map_aside ? &map : nullptr, raster, s));
   const bool one = vsa::fine_bwd_in_one(BH, g.Nb, sub ? 1 : 0);
   if (!one || !vsa::fine_bwd_with_coarse(g.Nc, g.m))
     VSA_TRY("coarse_bwd", vsa::launch_coarse_bwd(BH, g.Nc, key_rows(p, g), p->d, scale, w.qc, w.kc, w.vc, lse_coarse, w.doc, dot, w.ac, w.dsc,
@@ -393,13 +398,13 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
   if (!map_aside) VSA_TRY("transpose_map", vsa::launch_transpose_map(BH, map, w.bits, sub ? 1 : 0, s));
   if (one) {
     VSA_TRY("fine_bwd", vsa::launch_fine_bwd_one(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.col, w.order, w.split, w.parts, w.cap,
-                                 w.rowd, w.dqc, w.dkc, w.dvc, w.mask, dq, dk, dv, g.m, w.qc, w.kc, w.vc, w.doc, lse_coarse, dot, s));
+                                 w.rowd, w.dqc, w.dkc, w.dvc, w.mask, dq, dk, dv, g.m, w.qc, w.kc, w.vc, w.doc, lse_coarse, dot, raster, s));
     return VSA_OK;
   }
   VSA_TRY("fine_bwd_dq", vsa::launch_fine_bwd_dq(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, lists, w.rowd,
-                                  w.dqc, w.mask, dq, g.m, sub ? 1 : 0, s));
+                                  w.dqc, w.mask, dq, g.m, sub ? 1 : 0, raster, s));
   VSA_TRY("fine_bwd_dkv", vsa::launch_fine_bwd_dkv(BH, g.Nb, p->d, kb, scale, q, k, v, w.dof, w.col, w.order, w.split, w.parts,
-                                   w.cap, w.rowd, w.dkc, w.dvc, w.mask, dk, dv, g.m, sub ? 1 : 0, s));
+                                   w.cap, w.rowd, w.dkc, w.dvc, w.mask, dk, dv, g.m, sub ? 1 : 0, raster, s));
   return VSA_OK;
 }
 

@@ -27,6 +27,35 @@ struct Geo {
   long long Np;     // padded tokens = V * Nc
 };
 
+// Where the rows of a block lie in a raster token-major tensor [B,L,H,d] (VSA_FLAG_RASTER_IO), by value.  Cubes have
+// 64, 128 or 256 tokens, so their edges are powers of two.
+struct RasterMap {
+  int on, H, T, Hh, W, Nh, Nw, lct, lch, lcw, m;  // lct, lch, lcw: logarithms of the cube's edges; m: blocks per cube
+};
+inline RasterMap raster_map(const Geo& g, int H) {
+  auto lg = [](int x) { int l = 0; while ((1 << l) < x) ++l; return l; };
+  return {1, H, g.T, g.Hh, g.W, g.Nh, g.Nw, lg(g.Ct), lg(g.Ch), lg(g.Cw), g.m};
+}
+struct NoRaster {  // in kernel instances that write tiled tensors only
+  int on = 0;
+};
+inline RasterMap tiled_map() { return {0, 1, 1, 1, 1, 1, 1, 0, 0, 0, 1}; }
+struct RasterRows {  // of block c of (b, h) number bh: offsets in 16-byte chunks
+  long long first;
+  int slot0, Hh, W, lch, lcw, pitch;
+  __device__ __forceinline__ RasterRows(const RasterMap& r, long long bh, int c, int cpr) {
+    const int cube = c / r.m, cw = cube % r.Nw, chh = (cube / r.Nw) % r.Nh, ct = cube / (r.Nw * r.Nh);
+    slot0 = (c % r.m) * kTile;
+    Hh = r.Hh, W = r.W, lch = r.lch, lcw = r.lcw, pitch = r.H * cpr;
+    const long long L = (long long)r.T * r.Hh * r.W, n = ((long long)(ct << r.lct) * Hh + (chh << lch)) * W + (cw << lcw);
+    first = ((bh / r.H) * L + n) * pitch + (bh % r.H) * cpr;
+  }
+  __device__ __forceinline__ long long at(int row) const {  // (of a valid row)
+    const int s = slot0 + row, pw = s & ((1 << lcw) - 1), ph = (s >> lcw) & ((1 << lch) - 1), pt = s >> (lcw + lch);
+    return first + (long long)((pt * Hh + ph) * W + pw) * pitch;
+  }
+};
+
 // bf16 bits <-> fp32.  Widening is exact; narrowing rounds to nearest even in hardware.
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }

@@ -5,6 +5,7 @@
 
 namespace vsa {
 
+// `raster` (raster_map or tiled_map): where `out`, `dout` and the gradients lie
 hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, const void* src, void* dst, bool inverse,
                                hipStream_t s);
 hipError_t launch_mfma_rate(const void* operands, float* sink, int workgroups, int iters, hipStream_t s);
@@ -21,7 +22,7 @@ hipError_t launch_coarse(int BH, int Nq, int Nk, int d, int K, float scale, cons
 hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                                  const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                                  const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                                 int m_blocks, int key_cubes_16, hipStream_t s);
+                                 int m_blocks, int key_cubes_16, const RasterMap& raster, hipStream_t s);
 // What the forward of a short sequence forms its coarse stage from, row by row in the fine kernel, and where it leaves it.
 struct SmallForwardArgs {
   const float *qc, *kc, *vc;
@@ -35,7 +36,7 @@ bool fine_fwd_with_coarse(int BH, int Nc, int d, int m_blocks);
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
-                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, hipStream_t s);
+                           int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, const RasterMap& raster, hipStream_t s);
 // lists of cubes -> lists of 64-row blocks, for cubes of m blocks: every block of query cube c gets
 // the m blocks of each of the cube's K key cubes, ascending ([BH,Nc,K] -> [BH,Nc*m,K*m])
 // mismatched granularity: top-K on the coarse map pooled over (1,2,2) cubes, and its lists of tiles
@@ -59,7 +60,7 @@ bool map_with_bwd_pre(int Nc, int key_cubes_16);
 hipError_t launch_bwd_pre(int BH, int Nc, int m_blocks, int d, const uint64_t* mask, const void* dout, const void* gate_c,
                           const void* gate_f, const void* out_fine, const float* oc, void* dgate_c, void* dgate_f,
                           void* dof, float* rowd, float scale, float* doc, float* dot, const float* lse_f, int H,
-                          int dout_token_major, const MapArgs* map, hipStream_t s);
+                          int dout_token_major, const MapArgs* map, const RasterMap& raster, hipStream_t s);
 hipError_t launch_coarse_bwd(int BH, int Nq, int Nk, int d, float scale, const float* qc, const float* kc,
                              const float* vc, const float* lse_c, const float* doc, const float* dot, float* ac,
                              float* dsc, float* dqc, float* dkc, float* dvc, const int32_t* kcnt, hipStream_t s);
@@ -67,11 +68,12 @@ hipError_t launch_transpose_map(int BH, const MapArgs& a, uint32_t* bits, int ke
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,
-                              hipStream_t s);
+                              const RasterMap& raster, hipStream_t s);
 hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                                const void* dof, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dkc, const float* dvc,
-                               const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, hipStream_t s);
+                               const uint64_t* mask, void* dk, void* dv, int m_blocks, int key_cubes_16, const RasterMap& raster,
+                               hipStream_t s);
 // Up to this many blocks dK/dV and, at d = 128, dQ take four wavefronts per workgroup: the launch does not fill the 512
 // places of two-wavefront workgroups, and half as long a list walk counts (64 blocks, d = 64, top-8: 10.7 against 13.7 us).
 constexpr int kDkvFourWaves = 256;
@@ -83,6 +85,6 @@ hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const 
                                const void* dof, const int32_t* idx, const int32_t* col, const int32_t* order, int32_t* split,
                                float* parts, int cap, const float* rowd, const float* dqc, const float* dkc, const float* dvc,
                                const uint64_t* mask, void* dq, void* dk, void* dv, int m_blocks, const float* qc, const float* kc,
-                               const float* vc, const float* doc, const float* lse_c, const float* dot, hipStream_t s);
+                               const float* vc, const float* doc, const float* lse_c, const float* dot, const RasterMap& raster, hipStream_t s);
 
 }  // namespace vsa

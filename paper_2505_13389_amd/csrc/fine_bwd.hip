@@ -473,7 +473,7 @@ hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const 
                                const uint64_t* mask, void* dq, void* dk, void* dv, int m_blocks, const float* qc, const float* kc,
                                const float* vc, const float* doc, const float* lse_c, const float* dot, const RasterMap& raster, hipStream_t s) {
   const int items = Nc + cap;
-  const unsigned dkv_blocks = dkv_grid(BH, items), grid = dkv_blocks + (unsigned)(BH * Nc);  // (dkv_grid is a multiple of 8: the XCDs stay)
+  const unsigned dkv_blocks = dkv_grid(BH, items, dkv_heads_at_once(Nc, d)), grid = dkv_blocks + (unsigned)(BH * Nc);  // (dkv_grid is a multiple of 8: the XCDs stay)
   const SmallCoarseArgs sc = {qc, kc, vc, doc, lse_c, dot};
 #define VSA_ONE(D_, COARSE_)                                                                                             \
   k_fine_bwd_one<D_, COARSE_><<<grid, 256, 0, s>>>(dkv_blocks, BH, Nc, K, scale * kLog2e, scale, (const uint4*)q, (const uint4*)k, \

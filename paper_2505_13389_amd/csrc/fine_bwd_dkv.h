@@ -109,7 +109,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   // its fp32 partial sums in its slot (the low 16 bits of desc.w) and the last of which to arrive adds all of them, in slot
   // order; unused descriptors carry block -1.
   int bh_, item;
-  dkv_item(block, BH, items_per_bh, bh_, item);
+  dkv_item(block, BH, items_per_bh, dkv_heads_at_once(Nc, D), bh_, item);
   if (item >= items_per_bh) return;
   const long long bh = bh_;
   const int4 desc = ((const int4*)order)[bh * items_per_bh + item];

@@ -27,7 +27,7 @@ hipError_t launch_fine_bwd_dkv(int BH, int Nc, int d, int K, float scale, const 
   const float sl2 = scale * kLog2e;
   const int items = Nc + cap;
   const int stream = (long long)BH * Nc * kTile * d * 2 >= kStreamBytes;
-  const unsigned grid = dkv_grid(BH, items);
+  const unsigned grid = dkv_grid(BH, items, dkv_heads_at_once(Nc, d));
 #define VSA_DKV(D_, NW_, SUB_)                                                                                                \
   k_fine_bwd_dkv<D_, NW_, SUB_><<<grid, 64 * NW_, 0, s>>>(BH, Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
                                                           (const uint4*)dof, col, order, items, split, parts, cap, rowd, dkc, dvc, \

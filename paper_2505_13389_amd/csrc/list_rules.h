@@ -84,34 +84,43 @@ VSA_RULE bool split_granted(int runs, int wanted_before, int cap) { return runs 
 // heads and an eighth, always dealing a head's items in turn so that the XCDs carry the same load.
 // Against all XCDs on one head after the other (B*H = 16 .. 32): 3 to 14 % (d = 64, 256 blocks, top-32,
 // local lists: 343 -> 295 us).
+//
+// `at_once`: heads worked on at a time, 8, 4 or 2 (dkv_heads_at_once).
 VSA_RULE int dkv_share(int heads, int items) { return (heads * items + 7) / 8; }  // per XCD
-VSA_RULE void dkv_item(unsigned b, int BH, int items, int& bh, int& item) {
-  const unsigned x = b & 7u;
+VSA_RULE void dkv_item(unsigned b, int BH, int items, int at_once, int& bh, int& item) {
+  const unsigned x = b & 7u, each = (unsigned)dkv_share(at_once, items), whole = (unsigned)(BH / at_once) * each;
   unsigned i = b >> 3;
-  const unsigned whole = (unsigned)(BH >> 3) * items;
+  int base, g = at_once;
   if (i < whole) {
-    bh = (int)(x + 8u * (i / items));
-    item = (int)(i % items);
-    return;
-  }
-  i -= whole;
-  int base = BH & ~7, g = 4;  // groups of 4, 2 and 1 heads, in this order
-  while (!(BH & g) || i >= (unsigned)dkv_share(g, items)) {
-    if (BH & g) {
-      i -= dkv_share(g, items);
-      base += g;
+    base = at_once * (int)(i / each);
+    i %= each;
+  } else {
+    i -= whole;
+    base = BH / at_once * at_once;
+    g >>= 1;  // groups of half as many heads, and so on
+    while (!(BH & g) || i >= (unsigned)dkv_share(g, items)) {
+      if (BH & g) {
+        i -= dkv_share(g, items);
+        base += g;
+      }
+      g >>= 1;
     }
-    g >>= 1;
   }
   const unsigned n = x + 8u * i;
   bh = base + (int)(n & (g - 1));
   item = (int)(n / g);
 }
-VSA_RULE unsigned dkv_grid(int BH, int items) {
-  int per = (BH >> 3) * items;
-  for (int g = 4; g; g >>= 1)
+VSA_RULE unsigned dkv_grid(int BH, int items, int at_once) {
+  int per = BH / at_once * dkv_share(at_once, items);
+  for (int g = at_once >> 1; g; g >>= 1)
     if (BH & g) per += dkv_share(g, items);
   return 8u * (unsigned)per;
 }
+// Eight heads in flight, one per XCD, unless their Q and dO_f together outgrow the 256 MiB cache behind the L2s: with four, two
+// XCDs to a head, more of what misses an L2 is found there.  Eight / four heads, ms: 1440 blocks, d = 128 (45 MiB a head),
+// 40 heads, top-180 37.7 / 36.4, local lists of 60 13.7 / 13.1, 16 heads 15.1 / 14.4; 1152 (36 MiB) 3.38 / 3.23; 2160, d = 64
+// (34 MiB) 3.63 / 3.49; 840 (26 MiB) 3.01 / 3.03; 1440, d = 64 (23 MiB) 11.48 / 11.48; 624 (20 MiB) 1.937 / 1.956.  Two heads:
+// as four or slower.
+VSA_RULE int dkv_heads_at_once(int Nc, int d) { return (long long)Nc * 64 * d * 4 >= (30ll << 20) ? 4 : 8; }
 
 }  // namespace vsa

@@ -513,17 +513,18 @@ int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, 
     if (slots_hi > max_slots) max_slots = slots_hi;
     if (nsplit > max_split) max_split = nsplit;
   }
-  {  // every item of every (b, h) belongs to exactly one workgroup of the dK/dV launch; heads are dealt eight at a time
+  {  // every item of every (b, h) belongs to exactly one workgroup of the dK/dV launch; heads are dealt in groups
     const int BH = p->B * p->H, per = Nc + cap;
-    const unsigned grid = vsa::dkv_grid(BH, per), eight = 8u * (unsigned)per;
-    std::vector<unsigned char> taken(eight);
-    for (int first = 0; first < BH; first += 8) {
-      const int heads = BH - first < 8 ? BH - first : 8;
-      const unsigned begin = (unsigned)(first / 8) * eight, end = first + 8 < BH ? begin + eight : grid;
+    const int at_once = vsa::dkv_heads_at_once(Nc, p->d);
+    const unsigned grid = vsa::dkv_grid(BH, per, at_once), group = 8u * (unsigned)vsa::dkv_share(at_once, per);
+    std::vector<unsigned char> taken((size_t)at_once * per);
+    for (int first = 0; first < BH; first += at_once) {
+      const int heads = BH - first < at_once ? BH - first : at_once;
+      const unsigned begin = (unsigned)(first / at_once) * group, end = first + at_once < BH ? begin + group : grid;
       std::fill(taken.begin(), taken.end(), 0);
       for (unsigned b = begin; b < end; ++b) {
         int bh, item;
-        vsa::dkv_item(b, BH, per, bh, item);
+        vsa::dkv_item(b, BH, per, at_once, bh, item);
         if (bh < first || bh >= first + heads || item < 0) ++bad;
         else if (item < per && taken[(size_t)(bh - first) * per + item]++) ++bad;
       }

@@ -198,7 +198,7 @@ struct TileCopy : Tile<D> {
   }
 };
 
-template <int D, class LIST>
+template <int D, class LIST, class RASTER>  // (RasterMap or NoRaster)
 __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float sl2, const uint4* __restrict__ q,
                                                      const uint4* __restrict__ k, const uint4* __restrict__ v,
                                                      const uint4* __restrict__ gc, const uint4* __restrict__ gf,
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float 
                                                      const uint64_t* __restrict__ mask, uint4* __restrict__ out,
                                                      uint4* __restrict__ out_fine, float* __restrict__ lse_f,
                                                      int H, long long out_head_stride, long long out_row_stride,
-                                                     int m_blocks, RasterMap raster) {
+                                                     int m_blocks, RASTER raster) {
   using TL = TileCopy<D>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, LPT = TL::LPT;
   constexpr int OS = D;  // fp32 row stride of the merge buffer
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void k_fine_fwd_short(int Nc, int K, float 
       ov = pack8(res);
       fv = pack8(of);
     }
-    if (!raster.on) out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
+    if constexpr (std::is_same_v<RASTER, NoRaster>) out[out0 + (long long)(c * kTile + r) * out_row_stride + ch] = ov;
     else if (valid) out[RasterRows(raster, bh, c, CPR).at(r) + ch] = ov;
     if (out_fine) out_fine[g] = fv;
   }
@@ -503,10 +503,15 @@ hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, cons
   const unsigned grid = (unsigned)(BH * Nc);
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
-#define VSA_FWD_SHORT(D_, LIST_)                                                                                           \
-  k_fine_fwd_short<D_, LIST_><<<grid, 256, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,           \
+#define VSA_FWD_SHORT_AS(D_, LIST_, RASTER_, MAP_)                                                                          \
+  k_fine_fwd_short<D_, LIST_, RASTER_><<<grid, 256, 0, s>>>(Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v,   \
                                              (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, (uint4*)out, \
-                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, raster)
+                                             (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, MAP_)
+#define VSA_FWD_SHORT(D_, LIST_)                                     \
+  do {                                                               \
+    if (raster.on) VSA_FWD_SHORT_AS(D_, LIST_, RasterMap, raster);   \
+    else VSA_FWD_SHORT_AS(D_, LIST_, NoRaster, NoRaster{});          \
+  } while (0)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
     if (d == 128) VSA_FWD_SHORT(128, SubCubeList);
     else VSA_FWD_SHORT(64, SubCubeList);
@@ -515,6 +520,7 @@ hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, cons
     else VSA_FWD_SHORT(64, CubeList);
   }
 #undef VSA_FWD_SHORT
+#undef VSA_FWD_SHORT_AS
   return hipGetLastError();
 }
 

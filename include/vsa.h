@@ -100,6 +100,7 @@ typedef enum {
                                   VSA_FLAG_OUT_TOKEN_MAJOR. */
 #define VSA_MIN_SOFTMAX_SCALE (1.0f / 64.0f) /* smallest explicit softmax_scale accepted (the pad-key bias of
                                                -30000 must still underflow the exponential once scaled) */
+#define VSA_MAX_PERMUTE_TENSORS 8 /* tensors of one vsa_tile_permute_many call             */
 #define VSA_MAX_CUBES 4096        /* largest supported Np / 64 (= Nc for 64-token cubes)  */
 #define VSA_STATIC_SCRATCH_MIB 40 /* size of the scratch buffer behind vsa_forward_static, MiB */
 
@@ -131,6 +132,12 @@ size_t vsa_workspace_bytes(const vsa_params_t* p, int backward);
  * rides on the permutation instead of costing a pass of its own.  The tiled side is unchanged.
  * src and dst must not overlap. */
 int vsa_tile_permute(const vsa_params_t* p, const void* src, void* dst, int inverse, void* hip_stream);
+
+/* vsa_tile_permute of `count` tensors (1..VSA_MAX_PERMUTE_TENSORS) of the same shape and direction in one launch:
+ * src[i] -> dst[i].  The arrays are host memory, read before the call returns; no dst may overlap any src or
+ * another dst. */
+int vsa_tile_permute_many(const vsa_params_t* p, int count, const void* const* src, void* const* dst, int inverse,
+                          void* hip_stream);
 
 /* Forward (Sec. 2.2; App. B): pooling -> coarse attention -> per-row top-K -> fine
  * block-sparse attention -> gated sum.

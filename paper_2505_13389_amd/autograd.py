@@ -28,13 +28,10 @@ class _VideoSparseAttention(torch.autograd.Function):
         bf = dict(dtype=torch.bfloat16, device=q.device)
         f32 = dict(dtype=torch.float32, device=q.device)
 
-        def tiled(x):
-            y = torch.empty(shape, **bf)
-            vsa.vsa_tile_permute(pb, x.contiguous(), y, inverse=False, blhd=True)
-            return y
-
-        tq, tk, tv, tgc = tiled(q), tiled(k), tiled(v), tiled(gate_c)
-        tgf = None if gate_f is None else tiled(gate_f)
+        raster = [x.contiguous() for x in (q, k, v, gate_c, gate_f) if x is not None]
+        tiled = [torch.empty(shape, **bf) for _ in raster]
+        vsa.vsa_tile_permute_many(pb, raster, tiled, inverse=False, blhd=True)
+        tq, tk, tv, tgc, tgf = tiled if gate_f is not None else tiled + [None]
         # the attention writes raster tokens and, in the backward, reads and writes them: no permutation on that side
         pb = vsa.Problem(B, H, T, Hh, W, d, topk, tuple(cube), float(softmax_scale or 0.0),
                          int(flags) | vsa.VSA_FLAG_RASTER_IO)

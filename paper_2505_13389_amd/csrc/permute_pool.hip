@@ -5,7 +5,7 @@
 
 namespace vsa {
 
-// One workgroup per 64 destination rows of one (b, h).  The first wavefront works out, one row per
+// One workgroup per 64 destination rows of one (b, h) of one of the launch's tensors.  The first wavefront works out, one row per
 // lane, where each destination row comes from (the index arithmetic of the Sec. 2.2 equation, with
 // its integer divisions, once per row instead of once per 16-byte chunk); then all threads copy, several
 // 16-byte chunks in flight per thread: four with 256 threads, or, for tensors that no cache holds, two with 512 and
@@ -15,9 +15,13 @@ namespace vsa {
 // Forward: destination = tiled row; its source is the raster row of the same (t,h,w), or zeros for
 // a pad slot.  Inverse: destination = raster row.  H > 0: the raster tensor is [B, L, H, d]
 // (token-major); H == 0: [B, H, L, d].
+// Several tensors of one call share a launch (blockIdx.z), whose start and last workgroups are then paid for once: token-major
+// in, one launch each / one for all, us: 5 of 0.5 MiB 19.9 / 14.1, of 11 MiB 31.0 / 21.3, 4 of 22 MiB 36.7 / 28.8, 5 of 52 MiB
+// 98 / 84, of 117 MiB 227 / 208, of 900 MiB 1582 / 1594.
 template <bool kInverse, bool ONCE>
-__global__ __launch_bounds__(ONCE ? 512 : 256) void k_tile_permute(Geo g, int H, int chunks_per_row,
-                                                      const uint4* __restrict__ src, uint4* __restrict__ dst) {
+__global__ __launch_bounds__(ONCE ? 512 : 256) void k_tile_permute(Geo g, int H, int chunks_per_row, PermuteTensors tensors) {
+  const uint4* __restrict__ const src = (const uint4*)tensors.src[blockIdx.z];
+  uint4* __restrict__ const dst = (uint4*)tensors.dst[blockIdx.z];
   constexpr int NT = ONCE ? 512 : 256, U = 1024 / NT;
   __shared__ long long from[kTile], to[kTile];  // row numbers in units of rows; from < 0: a pad slot (zeros)
   const long long rows_dst = kInverse ? (long long)g.L : g.Np;
@@ -70,14 +74,14 @@ __global__ __launch_bounds__(ONCE ? 512 : 256) void k_tile_permute(Geo g, int H,
   }
 }
 
-hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, const void* src, void* dst, bool inverse,
+hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, int count, const PermuteTensors& tensors, bool inverse,
                                hipStream_t s) {
   const int cpr = d / 8;
   const long long rows_dst = inverse ? (long long)g.L : g.Np;
-  dim3 grid((unsigned)((rows_dst + kTile - 1) / kTile), (unsigned)BH);
+  dim3 grid((unsigned)((rows_dst + kTile - 1) / kTile), (unsigned)BH, (unsigned)count);
   const bool stream = (long long)BH * g.Np * d * 2 >= kStreamBytes;
 #define VSA_PERMUTE(INV_, ONCE_) \
-  k_tile_permute<INV_, ONCE_><<<grid, ONCE_ ? 512 : 256, 0, s>>>(g, H_blhd, cpr, (const uint4*)src, (uint4*)dst)
+  k_tile_permute<INV_, ONCE_><<<grid, ONCE_ ? 512 : 256, 0, s>>>(g, H_blhd, cpr, tensors)
   if (inverse) {
     if (stream) VSA_PERMUTE(true, true);
     else VSA_PERMUTE(true, false);

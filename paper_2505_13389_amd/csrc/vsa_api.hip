@@ -308,13 +308,27 @@ size_t vsa_workspace_bytes(const vsa_params_t* p, int backward) {
 }
 
 int vsa_tile_permute(const vsa_params_t* p, const void* src, void* dst, int inverse, void* hip_stream) {
+  return vsa_tile_permute_many(p, 1, &src, &dst, inverse, hip_stream);
+}
+
+int vsa_tile_permute_many(const vsa_params_t* p, int count, const void* const* src, void* const* dst, int inverse,
+                          void* hip_stream) {
   Geo g;
   int rc = check_params(p, &g);
   if (rc != VSA_OK) return rc;
   if (!src || !dst) return VSA_ERR_NULL;
-  if (misaligned(src) || misaligned(dst)) return VSA_ERR_ALIGN;
+  if (count < 1 || count > VSA_MAX_PERMUTE_TENSORS) return VSA_ERR_BAD_ARG;
+  static_assert(VSA_MAX_PERMUTE_TENSORS == vsa::kPermuteTensors, "by value in the kernel's arguments");
+  vsa::PermuteTensors tensors = {};
+  for (int i = 0; i < count; ++i) {
+    if (!src[i] || !dst[i]) return VSA_ERR_NULL;
+    tensors.src[i] = src[i];
+    tensors.dst[i] = dst[i];
+  }
+  for (int i = 0; i < count; ++i)
+    if (misaligned(src[i]) || misaligned(dst[i])) return VSA_ERR_ALIGN;
   hipStream_t s = (hipStream_t)hip_stream;
-  VSA_TRY("tile_permute", vsa::launch_tile_permute(g, p->B * p->H, (p->flags & VSA_FLAG_RASTER_BLHD) ? p->H : 0, p->d, src, dst, inverse != 0, s));
+  VSA_TRY("tile_permute", vsa::launch_tile_permute(g, p->B * p->H, (p->flags & VSA_FLAG_RASTER_BLHD) ? p->H : 0, p->d, count, tensors, inverse != 0, s));
   return VSA_OK;
 }
 

@@ -6,7 +6,12 @@
 namespace vsa {
 
 // `raster` (raster_map or tiled_map): where `out`, `dout` and the gradients lie
-hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, const void* src, void* dst, bool inverse,
+constexpr int kPermuteTensors = 8;  // of one launch, by value
+struct PermuteTensors {
+  const void* src[kPermuteTensors];
+  void* dst[kPermuteTensors];
+};
+hipError_t launch_tile_permute(const Geo& g, int BH, int H_blhd, int d, int count, const PermuteTensors& tensors, bool inverse,
                                hipStream_t s);
 hipError_t launch_mfma_rate(const void* operands, float* sink, int workgroups, int iters, hipStream_t s);
 // tensors = 3: Q, K, V pooled per cube; 1: Q only (with launch_pool_keys16 for K and V)

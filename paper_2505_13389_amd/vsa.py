@@ -24,7 +24,7 @@ VSA_FLAG_KEY_CUBES_16 = 128
 VSA_FLAG_RASTER_IO = 256
 STATUS = {0: "VSA_OK", -1: "VSA_ERR_NULL", -2: "VSA_ERR_BAD_ARG", -3: "VSA_ERR_UNSUPPORTED", -4: "VSA_ERR_ALIGN",
           -5: "VSA_ERR_WORKSPACE", -6: "VSA_ERR_HIP", -7: "VSA_ERR_SCRATCH_LIMIT"}
-EXPORTS = ["vsa_padded_tokens", "vsa_workspace_bytes", "vsa_tile_permute", "vsa_forward", "vsa_backward",
+EXPORTS = ["vsa_padded_tokens", "vsa_workspace_bytes", "vsa_tile_permute", "vsa_tile_permute_many", "vsa_forward", "vsa_backward",
            "vsa_status_string", "vsa_profile_begin", "vsa_profile_count", "vsa_profile_name", "vsa_profile_ms",
            "vsa_profile_end", "vsa_bench_mfma_rate", "vsa_forward_static", "vsa_static_scratch_bytes", "vsa_host_replay_lists"]
 
@@ -59,6 +59,8 @@ def lib():
         L.vsa_workspace_bytes.restype = C.c_size_t
         L.vsa_tile_permute.argtypes = [C.POINTER(VsaParams), vp, vp, C.c_int, vp]
         L.vsa_tile_permute.restype = C.c_int
+        L.vsa_tile_permute_many.argtypes = [C.POINTER(VsaParams), C.c_int, C.POINTER(vp), C.POINTER(vp), C.c_int, vp]
+        L.vsa_tile_permute_many.restype = C.c_int
         L.vsa_forward.argtypes = [C.POINTER(VsaParams)] + [vp] * 12 + [C.c_size_t, vp]
         L.vsa_forward.restype = C.c_int
         L.vsa_forward_static.argtypes = [C.POINTER(VsaParams)] + [vp] * 12
@@ -130,6 +132,17 @@ def vsa_tile_permute(pb: Problem, src: torch.Tensor, dst: torch.Tensor, inverse:
     rc = lib().vsa_tile_permute(C.byref(pb.params(flags)), _p(src), _p(dst), int(inverse), _stream())
     if rc:
         raise VsaError("vsa_tile_permute", rc)
+
+
+def vsa_tile_permute_many(pb: Problem, srcs, dsts, inverse: bool = False, blhd: bool = False):
+    """vsa_tile_permute of several tensors of one shape in one launch."""
+    assert len(srcs) == len(dsts)
+    flags = pb.flags | (VSA_FLAG_RASTER_BLHD if blhd else 0)
+    n = len(srcs)
+    rc = lib().vsa_tile_permute_many(C.byref(pb.params(flags)), n, (C.c_void_p * n)(*map(_p, srcs)),
+                                     (C.c_void_p * n)(*map(_p, dsts)), int(inverse), _stream())
+    if rc:
+        raise VsaError("vsa_tile_permute_many", rc)
 
 
 def vsa_forward(pb: Problem, q, k, v, gate_c, gate_f, out, block_idx, out_fine, lse_fine, out_coarse, lse_coarse,

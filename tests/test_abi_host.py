@@ -198,3 +198,14 @@ rc, rep = vsa.vsa_host_replay_lists(pb, lists)
 assert rc == 0 and rep["violations"] == 0, (rc, rep)
 """
     assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
+
+
+def test_permute_many_refuses_bad_counts_and_pointers(lib):
+    pb = vsa.Problem(1, 1, 4, 4, 4, 64, 1)
+    p = C.byref(pb.params())
+    ptr = lambda *x: (C.c_void_p * len(x))(*x)
+    assert lib.vsa_tile_permute_many(p, 1, None, None, 0, None) == -1
+    for n in (0, -1, 9):
+        assert lib.vsa_tile_permute_many(p, n, ptr(*[4096] * 9), ptr(*[8192] * 9), 0, None) == -2
+    assert lib.vsa_tile_permute_many(p, 2, ptr(4096, None), ptr(8192, 16384), 0, None) == -1
+    assert lib.vsa_tile_permute_many(p, 2, ptr(4096, 4096), ptr(8192, 16392), 0, None) == -4

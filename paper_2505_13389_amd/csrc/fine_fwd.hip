@@ -189,17 +189,17 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
   list.arrived();  // (and Q with it)
   const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(ml)) + (unsigned)wave * 512u;
-  request_masks(list, ml0);
-  if (nu > 0) {
+  const bool second = !paired && nu > 1 && list.loaded(tile_of(1));  // unit 1 is requested already
+  if (nu > 0) {  // (a wavefront without units has nothing in flight behind this: `ml` is written again, without a wait)
+    request_masks(list, ml0);
     list.rows(tile_of(0), half_of(0), u0);
     copy.all(kb, u0, lds0);
+    if (second) {
+      list.rows(tile_of(1), half_of(1), un[0]);
+      copy.all(kb, un[0], lds0 + HALF);
+    }
+    copy.all(vb, u0, lds0 + 2 * HALF);
   }
-  const bool second = !paired && nu > 1 && list.loaded(tile_of(1));  // unit 1 is requested already
-  if (second) {
-    list.rows(tile_of(1), half_of(1), un[0]);
-    copy.all(kb, un[0], lds0 + HALF);
-  }
-  if (nu > 0) copy.all(vb, u0, lds0 + 2 * HALF);
   float nil = 0.f;
   asm volatile("" : "+v"(nil));  // (made anew in every round: a vector of zeros kept from the first would be spilled)
 #pragma unroll
@@ -234,8 +234,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qreg[0][s]), "+v"(qreg[1][s]));
   if (!paired) __syncthreads();  // every wavefront has Q: the second V stages may be filled
   // the masks and K of the first unit have landed; newer: V of the first and, ahead of it, K of the second
-  if (second) wait_vmcnt<2 * NC>();
-  else wait_vmcnt<NC>();
+  wait_vmcnt<2 * NC>();
+  if (!second) wait_vmcnt<NC>();
   __builtin_amdgcn_sched_barrier(0);
   take_masks(list, ml + wave * 128);
   if (nu > 0) list.get(tile_of(0), half_of(0), u0);

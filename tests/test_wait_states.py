@@ -1,5 +1,6 @@
 """Wait states around the instructions that the fine kernels write as inline assembly: the compiler inserts none for
-them, so the emitted code of every kernel instance is checked, over all paths.
+them, so the emitted code of every kernel instance is checked, over all paths; and, in the forward, that copies to LDS have
+landed before their place is used for anything else.
 
   M0 written by a scalar instruction, then read by a copy to LDS            1 wait state
   scalar register written by a vector instruction, then a copy's address    5
@@ -121,6 +122,31 @@ def faults(code):
     return found
 
 
+def before_it_lands(code, start, hit):
+    """Instructions that `hit` accepts and that some path reaches from the copy `start` before it has waited for the copy:
+    vector memory accesses count down in issue order, so the wait is for no more of them than were issued behind it."""
+    found, best, todo = [], {}, [(n, 0) for n in code[start].next]
+    while todo:
+        n, behind = todo.pop()
+        if best.get(n, behind + 1) <= behind:
+            continue
+        best[n] = behind
+        i = code[n]
+        wait = re.search(r"vmcnt\((\d+)\)", i.text) if i.op == "s_waitcnt" else None
+        if wait and int(wait[1]) <= behind:
+            continue
+        if hit(i):
+            found.append(i)
+            continue
+        behind += i.op.startswith(("global_", "buffer_", "flat_", "scratch_"))
+        todo += [(m, behind) for m in i.next]
+    return found
+
+
+def mask_copies(code):
+    return [n for n, i in enumerate(code) if i.op == "global_load_lds_dword"]
+
+
 def kernels(path):
     name, lines = None, []
     for line in open(path):
@@ -135,18 +161,54 @@ def kernels(path):
             lines.append(line)
 
 
-@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no compiler")
+@pytest.fixture(scope="module")
+def emitted(tmp_path_factory):
+    """source -> path of the code the compiler emits for it."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("no compiler")
+    done = {}
+
+    def of(source):
+        if source not in done:
+            done[source] = str(tmp_path_factory.mktemp("emitted") / "kernels.s")
+            subprocess.run(["hipcc", *build.FLAGS, *build.FILE_FLAGS.get(source, []), "-S", "--offload-device-only",
+                            os.path.join(build.CSRC, source), "-o", done[source]], check=True, capture_output=True)
+        return done[source]
+    return of
+
+
 @pytest.mark.parametrize("source", FILES)
-def test_wait_states_of_the_emitted_code(source, tmp_path):
-    out = str(tmp_path / "kernels.s")
-    subprocess.run(["hipcc", *build.FLAGS, *build.FILE_FLAGS.get(source, []), "-S", "--offload-device-only",
-                    os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
+def test_wait_states_of_the_emitted_code(source, emitted):
     seen = 0
-    for name, code in kernels(out):
+    for name, code in kernels(emitted(source)):
         seen += sum(i.copy for i in code)
         found = faults(code)
         assert not found, f"{name}: {len(found)}, the first: {found[0]}"
     assert seen  # (the copies are where the test looks for them)
+
+
+def test_key_masks_land_before_their_place_is_used_again(emitted):
+    """Forward: the key masks reach registers by way of the memory that holds the softmax statistics at the end, also in a
+    wavefront that has no unit to multiply."""
+    seen = 0
+    for name, code in kernels(emitted("fine_fwd.hip")):
+        for n in mask_copies(code):
+            seen += 1
+            early = before_it_lands(code, n, lambda i: i.op.startswith("ds_write"))
+            assert not early, f"{name}: '{early[0].text}' while '{code[n].text}' may be in flight"
+    assert seen
+
+
+def test_the_check_sees_a_copy_in_flight():
+    def of(*text):
+        code = parse(text + ("ds_write_b64 v9, v[2:3]", "s_endpgm"))
+        return [before_it_lands(code, n, lambda i: i.op.startswith("ds_write")) for n in mask_copies(code)]
+    copy, load = "global_load_lds_dword v1, s[4:5]", "global_load_dwordx4 v[4:7], v8, s[6:7]"
+    assert of(copy)[0] and of(copy, load, load, "s_waitcnt vmcnt(3)")[0] and of(copy, "s_waitcnt lgkmcnt(0)")[0]
+    assert not of(copy, "s_waitcnt vmcnt(0)")[0] and not of(copy, load, load, "s_waitcnt vmcnt(2) lgkmcnt(0)")[0]
+    # on one path of two
+    assert of(copy, "s_cbranch_scc1 .LBB0_1", load, "s_waitcnt vmcnt(1)", ".LBB0_1:")[0]
+    assert of(copy, "s_cbranch_scc1 .LBB0_1", load, ".LBB0_1:", "s_waitcnt vmcnt(1)")[0]
 
 
 def test_the_check_sees_a_missing_wait():

@@ -186,8 +186,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   if constexpr (COARSE) {
     if (!tight) small_select<D>(lc, lc_list, Nc, K, c, bh * Nc, small, vrows, tid);
     list.take(lc_list, mask, K, lane, Nc);
+  } else {
+    wait_vmcnt<0>();  // the list and Q have landed (COARSE: Q is waited for below)
   }
-  list.arrived();  // (and Q with it)
+  list.arrived();
   const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(ml)) + (unsigned)wave * 512u;
   const bool second = !paired && nu > 1 && list.loaded(tile_of(1));  // unit 1 is requested already
   if (nu > 0) {  // (a wavefront without units has nothing in flight behind this: `ml` is written again, without a wait)

@@ -199,6 +199,25 @@ def test_key_masks_land_before_their_place_is_used_again(emitted):
     assert seen
 
 
+def test_q_lands_before_it_is_read(emitted):
+    """Forward: the copies of Q, those ahead of the first key masks, have landed in every wavefront before the barrier
+    behind which all of them read Q (the coarse stage inside the kernel has barriers of its own before that) and before
+    the first operand is read."""
+    seen = 0
+    for name, code in kernels(emitted("fine_fwd.hip")):
+        masks = mask_copies(code)
+        if not masks:
+            continue
+        coarse = "ELb1E" in name
+        for n in range(masks[0]):
+            if code[n].op == "global_load_lds_dwordx4":
+                seen += 1
+                early = before_it_lands(code, n, lambda i: i.op in ("ds_read_b128", "ds_read_b64_tr_b16") or
+                                        not coarse and i.op == "s_barrier")
+                assert not early, f"{name}: '{early[0].text}' while '{code[n].text}' may be in flight"
+    assert seen
+
+
 def test_the_check_sees_a_copy_in_flight():
     def of(*text):
         code = parse(text + ("ds_write_b64 v9, v[2:3]", "s_endpgm"))

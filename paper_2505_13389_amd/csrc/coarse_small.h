@@ -6,6 +6,8 @@
 // Forwards of 12 to 64 cubes, up to 256 blocks (d = 64: 512), 0.73 to 0.93 of the time; 32 cubes, 2 heads, d = 64, top-8 17.0 ->
 // 13.4 us.  In launches of several generations every one of them would pay what one launch costs.
 #pragma once
+#include <cstddef>
+
 #include "coarse_row.h"
 #include "vsa_kernels.h"
 
@@ -15,12 +17,17 @@ constexpr int kSmallCubes = 64;
 constexpr int kSmallThreads = 256;
 
 template <int D>
-struct SmallCoarse {
+struct alignas(16) SmallCoarse {
   static constexpr int PER_ROW = D / 4, PARTS = kSmallThreads / PER_ROW;  // threads a row of the sums, partial sums
   float w[2][kSmallCubes];  // weights of the sums below
   float sum[2][D];
   float part[2][PARTS][D];
 };
+// (rows of `sum` and `part` are read and written 16 bytes at a time)
+template <int D>
+constexpr bool kSmallRowsAligned = alignof(SmallCoarse<D>) % 16 == 0 && offsetof(SmallCoarse<D>, sum) % 16 == 0 &&
+                                   offsetof(SmallCoarse<D>, part) % 16 == 0;
+static_assert(kSmallRowsAligned<64> && kSmallRowsAligned<128>, "16-byte accesses");
 
 __device__ __forceinline__ float dot4(const float4& a, const float4& b, float s) {
   return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, fmaf(a.x, b.x, s))));

@@ -372,7 +372,9 @@ __device__ __forceinline__ void dq_block(
     const RasterRows rows_r(raster, bh, c, CPR);
     constexpr int P = decltype(parts_tag)::value, NT = 64 * P, LPT = kTile * CPR / NT;
     static_assert(NT % CPR == 0, "a thread keeps its column chunk");
-    const int t = P == 1 ? lane : tid, ch = t % CPR;
+    int t = P == 1 ? lane : tid;
+    asm volatile("" : "+v"(t));  // (rows worked out anew: the copies' own, kept through the walk, took private memory at d = 64)
+    const int ch = t % CPR;
     float* const bufs = (float*)smem + (P == 1 ? wave * 64 * OS : 0);
     // the pooled-gradient term of this thread's column chunk, requested before the partial results go through LDS
     const float* dqcr = COARSE ? lc->sum[0] + ch * 8 : dqc + ((bh * Nc + c) / m_blocks) * D + ch * 8;  // per cube = m_blocks blocks

@@ -15,6 +15,7 @@ import os
 import re
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -163,24 +164,24 @@ def kernels(path):
 
 @pytest.fixture(scope="module")
 def emitted(tmp_path_factory):
-    """source -> path of the code the compiler emits for it."""
+    """Source -> path of the code the compiler emits for it."""
     if shutil.which("hipcc") is None:
         pytest.skip("no compiler")
-    done = {}
+    place = tmp_path_factory.mktemp("emitted")
 
-    def of(source):
-        if source not in done:
-            done[source] = str(tmp_path_factory.mktemp("emitted") / "kernels.s")
-            subprocess.run(["hipcc", *build.FLAGS, *build.FILE_FLAGS.get(source, []), "-S", "--offload-device-only",
-                            os.path.join(build.CSRC, source), "-o", done[source]], check=True, capture_output=True)
-        return done[source]
-    return of
+    def compile_one(source):
+        out = str(place / source.replace(".hip", ".s"))
+        subprocess.run(["hipcc", *build.FLAGS, *build.FILE_FLAGS.get(source, []), "-S", "--offload-device-only",
+                        os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
+        return out
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        return dict(zip(build.SOURCES, ex.map(compile_one, build.SOURCES)))
 
 
 @pytest.mark.parametrize("source", FILES)
 def test_wait_states_of_the_emitted_code(source, emitted):
     seen = 0
-    for name, code in kernels(emitted(source)):
+    for name, code in kernels(emitted[source]):
         seen += sum(i.copy for i in code)
         found = faults(code)
         assert not found, f"{name}: {len(found)}, the first: {found[0]}"
@@ -191,7 +192,7 @@ def test_key_masks_land_before_their_place_is_used_again(emitted):
     """Forward: the key masks reach registers by way of the memory that holds the softmax statistics at the end, also in a
     wavefront that has no unit to multiply."""
     seen = 0
-    for name, code in kernels(emitted("fine_fwd.hip")):
+    for name, code in kernels(emitted["fine_fwd.hip"]):
         for n in mask_copies(code):
             seen += 1
             early = before_it_lands(code, n, lambda i: i.op.startswith("ds_write"))
@@ -204,7 +205,7 @@ def test_q_lands_before_it_is_read(emitted):
     behind which all of them read Q (the coarse stage inside the kernel has barriers of its own before that) and before
     the first operand is read."""
     seen = 0
-    for name, code in kernels(emitted("fine_fwd.hip")):
+    for name, code in kernels(emitted["fine_fwd.hip"]):
         masks = mask_copies(code)
         if not masks:
             continue
@@ -216,6 +217,14 @@ def test_q_lands_before_it_is_read(emitted):
                                         not coarse and i.op == "s_barrier")
                 assert not early, f"{name}: '{early[0].text}' while '{code[n].text}' may be in flight"
     assert seen
+
+
+@pytest.mark.parametrize("source", build.SOURCES)
+def test_no_kernel_needs_private_memory(source, emitted):
+    """The runtime provides private memory when a kernel that needs it is launched, and the library never allocates."""
+    text = open(emitted[source]).read()
+    sizes = re.findall(r"\.private_segment_fixed_size: +(\d+)", text)
+    assert len(sizes) == len(re.findall(r"^\s*\.amdhsa_kernel ", text, re.M)) and not any(map(int, sizes)), sizes
 
 
 def test_the_check_sees_a_copy_in_flight():

@@ -38,9 +38,10 @@ struct DqShape {
   static constexpr int LDS = NW * 4 * HALF;        // per wavefront: K of two units, V of two units
 };
 
-// `smem`: DqShape::LDS bytes, aligned to 1024; `masks`: 128 words per wavefront.  `block` of `grid` workgroups.  COARSE: the
+// `smem`: DqShape::LDS bytes, aligned to 1024; `masks`: 128 words per wavefront.  `block` of `grid` workgroups.  PAIRS: the
+// first `pairs` of them take two blocks (NW = 2; launches without pairs have instances of their own, as in the forward).  COARSE: the
 // pooled-gradient term is formed here (NW = 4, cubes of one block), in `lc`, and dqc is not read.
-template <int D, int NW, template <class> class UNITS, bool COARSE>
+template <int D, int NW, template <class> class UNITS, bool PAIRS, bool COARSE>
 __device__ __forceinline__ void dq_block(
     unsigned char* smem, uint32_t* masks, unsigned block, unsigned grid, int Nc, int K, float sl2, float scale,
     const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v, const uint4* __restrict__ dof,
@@ -64,8 +65,7 @@ __device__ __forceinline__ void dq_block(
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
-  constexpr bool kPairs = NW == 2;
-  const bool paired = kPairs && block < pairs;
+  const bool paired = PAIRS && block < pairs;
   const unsigned from = paired ? 0u : pairs, those = paired ? pairs : grid - pairs;
   const unsigned id = same_lists ? block - from : xcd_chunked_id(block - from, those);
   const unsigned wg = paired ? 2 * id + wave : 2 * pairs + id;
@@ -105,7 +105,7 @@ __device__ __forceinline__ void dq_block(
   copy.init(lane);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
   UL list;
-  if (!kPairs) list.only = wave & 1;
+  if (!PAIRS) list.only = wave & 1;
   list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
   Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the current unit and the two after it
   const long long q0 = rows0 + (long long)c * kTile;  // first row of this query block
@@ -424,11 +424,11 @@ __device__ __forceinline__ void dq_block(
   const std::integral_constant<int, NW> all;
   const std::integral_constant<int, 0> plain;
   const std::integral_constant<int, 2> out_of_order;
-  if (paired) raster.on ? finish(one, out_of_order) : stream ? finish(one, one) : finish(one, plain);
+  if (PAIRS && paired) raster.on ? finish(one, out_of_order) : stream ? finish(one, one) : finish(one, plain);
   else raster.on ? finish(all, out_of_order) : stream ? finish(all, one) : finish(all, plain);
 }
 
-template <int D, int NW, template <class> class UNITS>
+template <int D, int NW, template <class> class UNITS, bool PAIRS>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
     const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx,
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
     uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream, RasterMap raster) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShape<D, NW>::LDS];
   __shared__ uint32_t masks[NW * 128];
-  dq_block<D, NW, UNITS, false>(smem, masks, blockIdx.x, gridDim.x, Nc, K, sl2, scale, q, k, v, dof, idx, rowd, dqc, mask, dq,
+  dq_block<D, NW, UNITS, PAIRS, false>(smem, masks, blockIdx.x, gridDim.x, Nc, K, sl2, scale, q, k, v, dof, idx, rowd, dqc, mask, dq,
                                 m_blocks, blocks, pairs, stream, raster, SmallCoarseArgs{}, nullptr);
 }
 
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
     dkv_block<D, 4, false, COARSE>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items, split, parts,
                                    cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, 0, raster, sc, &lc);
   else
-    dq_block<D, 4, CubeUnits, COARSE>(smem, masks, blockIdx.x - dkv_blocks, gridDim.x - dkv_blocks, Nc, K, sl2, scale, q, k, v, dof,
+    dq_block<D, 4, CubeUnits, false, COARSE>(smem, masks, blockIdx.x - dkv_blocks, gridDim.x - dkv_blocks, Nc, K, sl2, scale, q, k, v, dof,
                                       idx, rowd, dqc, mask, dq, m_blocks, (unsigned)(BH * Nc), 0, 0, raster, sc, &lc);
 }
 
@@ -507,8 +507,13 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
   const bool four = grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>);
   const unsigned pairs = four ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
-#define VSA_DQ(D_, NW_, LIST_)                                                                                          \
-  k_fine_bwd_dq<D_, NW_, LIST_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
+#define VSA_DQ(D_, NW_, LIST_)             \
+  do {                                     \
+    if (NW_ == 2 && pairs) VSA_DQ_AS(D_, NW_, LIST_, (NW_ == 2)); \
+    else VSA_DQ_AS(D_, NW_, LIST_, false); \
+  } while (0)
+#define VSA_DQ_AS(D_, NW_, LIST_, PAIRS_)                                                                               \
+  k_fine_bwd_dq<D_, NW_, LIST_, PAIRS_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(Nc, K, sl2, scale, (const uint4*)q, (const uint4*)k, (const uint4*)v, \
                                                 (const uint4*)dof, idx, rowd, dqc, mask, (uint4*)dq, m_blocks, grid, pairs, stream, raster)
   if (key_cubes_16) {  // K counts key cubes of 16 tokens
     if (d == 128 && four) VSA_DQ(128, 4, SubCubeUnits);
@@ -521,6 +526,7 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
     else VSA_DQ(64, 2, CubeUnits);
   }
 #undef VSA_DQ
+#undef VSA_DQ_AS
   return hipGetLastError();
 }
 

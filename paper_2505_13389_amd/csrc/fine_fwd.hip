@@ -83,9 +83,12 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
   __syncthreads();
 }
 
+// PAIRS: the first `pairs` workgroups take two blocks, one per wavefront (d = 128, NW = 2; at d = 64 two wavefronts per SIMD hide one
+// another's start-up).  Launches without pairs have instances of their own, which know each wavefront's key half: 288 blocks,
+// top-26 32.7 -> 32.1 us, top-50 49.2 -> 48.1.
 // COARSE: short sequences, whose coarse stage a workgroup does for its block on the way (NW = 4, see coarse_small.h).
 // RASTER: RasterMap or NoRaster (as a runtime choice it cost the smallest launches 0.8 us of 13).
-template <int D, int NW, template <class> class UNITS, bool COARSE, class RASTER>
+template <int D, int NW, template <class> class UNITS, bool PAIRS, bool COARSE, class RASTER>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     int Nc_, int K_, float sl2, const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
     const uint4* __restrict__ gc, const uint4* __restrict__ gf, const int32_t* __restrict__ idx,
@@ -104,7 +107,6 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   constexpr int kAhead = D == 128 ? 4 : 2;
   constexpr int kEarly = 7;             // of the 16 softmax items of a unit, those behind the PV phase before it
   constexpr int OS = D;
-  constexpr bool kPairs = D == 128 && NW == 2;  // (d = 64: two wavefronts per SIMD hide one another's start-up)
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
   __shared__ float ml[NW * 64 * 2];
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   // the first `pairs` workgroups take two blocks, one per wavefront; the others one, whose units they share
-  const bool paired = kPairs && block < pairs;
+  const bool paired = PAIRS && block < pairs;
   const unsigned from = paired ? 0u : pairs, those = paired ? pairs : gridDim.x - pairs;
   const unsigned id = same_lists ? block - from : xcd_chunked_id(block - from, those);
   const unsigned wg = paired ? 2 * id + wave : 2 * pairs + id;
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   copy.init(lane);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + (unsigned)wave * (4 * HALF);
   UL list;
-  if (!kPairs) list.only = wave & 1;
+  if (!PAIRS) list.only = wave & 1;
   Unit un[3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // the units after the current one
   Unit u0 = {0, 0, 0};
   if constexpr (!COARSE) list.request(idx + (bh * Nc + c) * (long long)K, mask, K, lane, Nc, nu > 0 ? tile_of(0) : 0);
@@ -613,7 +615,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     }
     return overflow;
   };
-  if constexpr (kPairs) {
+  if constexpr (PAIRS) {
     if (paired) {
       const std::integral_constant<int, 1> one;
       bool overflow;
@@ -699,14 +701,19 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   const long long cpr = d / 8, Np = (long long)Nc * kTile;
   const long long ohs = out_token_major ? cpr : Np * cpr, ors = out_token_major ? H * cpr : cpr;
   const SmallForwardArgs small = coarse ? *coarse : SmallForwardArgs{};
-#define VSA_FWD_AS(D_, NW_, LIST_, COARSE_, RASTER_, MAP_)                                                            \
-  k_fine_fwd<D_, NW_, LIST_, COARSE_, RASTER_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(                           \
+#define VSA_FWD_AS(D_, NW_, LIST_, PAIRS_, COARSE_, RASTER_, MAP_)                                                    \
+  k_fine_fwd<D_, NW_, LIST_, PAIRS_, COARSE_, RASTER_><<<workgroups(grid, pairs), 64 * NW_, 0, s>>>(                   \
       Nc, K, sl2, (const uint4*)q, (const uint4*)k, (const uint4*)v, (const uint4*)gate_c, (const uint4*)gate_f, idx, oc, mask, \
       (uint4*)out, (uint4*)out_fine, lse_f, H, ohs, ors, m_blocks, grid, pairs, stream, arrived, every, small, MAP_)
-#define VSA_FWD(D_, NW_, LIST_, COARSE_)                                         \
-  do {                                                                           \
-    if (raster.on) VSA_FWD_AS(D_, NW_, LIST_, COARSE_, RasterMap, raster);       \
-    else VSA_FWD_AS(D_, NW_, LIST_, COARSE_, NoRaster, NoRaster{});              \
+#define VSA_FWD_IO(D_, NW_, LIST_, PAIRS_, COARSE_)                                    \
+  do {                                                                                 \
+    if (raster.on) VSA_FWD_AS(D_, NW_, LIST_, PAIRS_, COARSE_, RasterMap, raster);     \
+    else VSA_FWD_AS(D_, NW_, LIST_, PAIRS_, COARSE_, NoRaster, NoRaster{});            \
+  } while (0)
+#define VSA_FWD(D_, NW_, LIST_, COARSE_)                                               \
+  do {                                                                                 \
+    if (pairs) VSA_FWD_IO(D_, NW_, LIST_, (D_ == 128 && NW_ == 2), COARSE_);           \
+    else VSA_FWD_IO(D_, NW_, LIST_, false, COARSE_);                                   \
   } while (0)
   const bool four = fwd_four_waves(d, grid, tiles);
   if (coarse) {
@@ -725,6 +732,7 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   }
 #undef VSA_FWD
 #undef VSA_FWD_AS
+#undef VSA_FWD_IO
   return hipGetLastError();
 }
 

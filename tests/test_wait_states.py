@@ -209,7 +209,7 @@ def test_q_lands_before_it_is_read(emitted):
         masks = mask_copies(code)
         if not masks:
             continue
-        coarse = "ELb1E" in name
+        coarse = re.search(r"ELb[01]ELb1E", name)  # (template arguments ..., PAIRS, COARSE, ...)
         for n in range(masks[0]):
             if code[n].op == "global_load_lds_dwordx4":
                 seen += 1

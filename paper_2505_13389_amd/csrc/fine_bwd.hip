@@ -425,7 +425,7 @@ __device__ __forceinline__ void dq_block(
   const std::integral_constant<int, 0> plain;
   const std::integral_constant<int, 2> out_of_order;
   if (PAIRS && paired) raster.on ? finish(one, out_of_order) : stream ? finish(one, one) : finish(one, plain);
-  else raster.on ? finish(all, out_of_order) : stream ? finish(all, one) : finish(all, plain);
+  else raster.on ? finish(all, out_of_order) : NW == 2 && stream ? finish(all, one) : finish(all, plain);  // (four: small launches)
 }
 
 template <int D, int NW, template <class> class UNITS, bool PAIRS>

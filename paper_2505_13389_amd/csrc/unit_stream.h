@@ -129,12 +129,16 @@ struct SubCubeUnits {
 
 // Forward and dQ: a workgroup of two wavefronts takes one block, whose units they share, or two blocks, one each.  The
 // second form has half as many starts and nothing to merge, but its workgroups run twice as long; so all blocks are
-// paired where that takes no more generations of `places` workgroups -- with two workgroups' wavefronts on a SIMD, whose
-// speed depends on the other, where the last one is three quarters full -- else those of the generations that are full.
-// (dQ, d = 64: 1152 blocks all paired 1.10 times as long as none, 3456 1.05, 1536 0.95.)
+// paired where that takes no more generations of `places` workgroups, else those of the generations that are full.
+// With two workgroups' wavefronts on a SIMD, whose speed depends on the other (dQ, d = 64: 1024 places), all are paired where the last
+// generation is three quarters full, and none where it is between an eighth and that.  None / those of full generations, us, top-9
+// and top-32: 2304 blocks 48.6 / 46.3, 124.8 / 124.0; 2400 51.8 / 53.5, 130 / 137; 2520, top-8 and 30 44.9 / 47.5, 122 / 136; 3360 56.0 /
+// 58.4, 163 / 167.  None / all: 1536 37.6 / 35.3, 97.2 / 93.9; 2048 46.7 / 40.5, 108.9 / 107.7; 8192 142.7 / 141.8, 407 / 401.
 inline unsigned paired_workgroups(unsigned blocks, unsigned places) {
-  const unsigned rest = blocks % (2 * places), enough = places > 512 ? places + places / 2 - 1 : places;
-  return rest == 0 || rest > enough ? (blocks + 1) / 2 : blocks / (2 * places) * places;
+  const bool two = places > 512;
+  const unsigned rest = blocks % (2 * places), enough = two ? places + places / 2 - 1 : places;
+  if (rest == 0 || rest > enough) return (blocks + 1) / 2;
+  return two && rest > places / 4 ? 0 : blocks / (2 * places) * places;
 }
 inline unsigned workgroups(unsigned blocks, unsigned pairs) { return 2 * pairs >= blocks ? pairs : blocks - pairs; }
 

@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 # d, heads of 95 query blocks, list length
 #   128, 7: all paired, the last workgroup has one block (forward: from 17 tiles on); 128, 11: 512 pairs, 21 blocks shared
-#   64, 17 and 22 (dQ alone): all paired, 1024 pairs and 42 blocks shared
+#   64, 17, 22 and 25 (dQ alone): all paired; 1024 pairs, 42 blocks shared; 2375 blocks, none paired
 CASES = ([(128, 7, K) for K in (1, 2, 3, 17, 18, 65, 95)] + [(128, 11, K) for K in (1, 41)] +
-         [(64, 17, K) for K in (1, 2, 9)] + [(64, 22, 3)])
+         [(64, 17, K) for K in (1, 2, 9)] + [(64, 22, 3), (64, 25, 3)])
 
 
 def check_heads(wl, bits, idx, heads):

@@ -637,26 +637,33 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Which kernel, by the number of query blocks and of 64-key tiles in a list (whole forwards back to back, lists of N(0,1)
-// inputs, heads of 96 and 256 blocks; figures: time with the general kernel over that with the other).
-//
-// The kernel for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile:
-//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup).  It loses where the last one is nearly
-//            empty: 1056 blocks, 12 tiles 1.01, 28 1.02, 40 1.01; 1248, 12 1.02, 40 0.99; 2304, 4 1.04, 12 1.02, 20 0.99; 2688, 8
-//            1.02, 16 0.99; and in the smallest launches: 96, 4 1.01, 8 0.96; 480, 4 1.03, 12 1.00 (512, 12 1.02).  Elsewhere it wins: 576, 8
-//            0.99; 960, 8 0.90; 1344, 8 0.97; 1920, 8 0.93; 2048, 8 0.91; 3072, 8 0.96; 8192, 12 0.88.
-//   d = 64   480 blocks, 2 tiles 1.01, 8 0.99; 768, 8 1.03, 16 1.01, 20 0.98; 960, 4 0.96; 1152, 8 1.03, 20 0.97; 1536, 8 1.07;
-//            1920, 4 1.00, 8 0.97; 2048, 12 1.02; 2688, 12 1.02; 3072, 2 1.02, 4 0.98; 8192, 2 0.90.
+// Which kernel, by the number of query blocks and of 64-key tiles in a list.  From whole forwards back to back, N(0,1) inputs, 79
+// launches of 288 to 8192 blocks in heads of 72 to 500, lists of 2 to 44 tiles; figures: time with the general kernel over that with
+// the one for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile.
+//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  The general one loses where its
+//            last generation is nearly empty -- 1056 blocks, 10 tiles 1.03, 26 1.04, 44 1.01; 1280, 26 1.01, 44 0.99; 2304, 12 1.05, 26
+//            1.01, 34 0.99; 2500, 8 1.00, 12 0.97; 2736, 16 1.02, 26 0.98; 2940, 4 1.01, 6 0.99; 3096, 12 1.03, 26 0.99; 4500, 4 1.03, 8 0.97 --
+//            and where the blocks are shared and nearly fill a generation of the other: 360, 4 1.00, 8 0.99; 384, 8 1.00, 16 0.98; 448, 12
+//            1.01, 20 0.98; 512, 16 1.00, 20 0.99.  Elsewhere it wins: 576, 4 0.98, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 4096, 12 0.91; 8192, 12 0.90.
+//   d = 64   a generation of the general kernel is 1024 blocks: 384, 2 0.98; 560, 8 1.01, 16 1.01, 20 0.98; 1000, 4 0.96; 1056, 8 1.06, 20
+//            0.97; 1536, 12 1.08, 20 0.98; 2000, 4 0.99, 10 0.99; 2240, 8 1.04, 16 1.00; 2660, 8 1.02, 12 0.99; 3500, 6 1.00, 12 0.98; 4500, 2
+//            1.03, 6 1.00; 6144, 4 0.90.
 inline bool fwd_short(int d, unsigned grid, int tiles) {
   if (d == 64) {
     if (grid <= 512) return tiles <= 2;
-    if (grid <= 768) return tiles <= 14;
-    if (grid <= 1024 || grid > 4096) return false;
-    return tiles <= (grid < 1792 ? 14 : grid < 2048 ? 4 : grid < 2816 ? 14 : 3);
+    if (grid <= 768) return tiles <= 16;
+    if (grid <= 1024) return false;
+    if (grid <= 1792) return tiles <= 14;
+    if (grid < 2048) return tiles <= 4;
+    if (grid <= 2560) return tiles <= 12;
+    return tiles <= (grid < 2816 ? 9 : grid <= 4096 ? 6 : grid <= 5120 ? 2 : 0);
   }
-  if (grid <= 512) return tiles <= (grid > 448 ? 12 : 4);
-  if (grid > 1024 && grid <= 1280) return tiles <= 32;
-  return grid > 2112 && grid < 2816 && tiles <= 12;
+  if (grid <= 512) return tiles <= (grid > 448 ? 16 : grid > 368 ? 12 : 4);
+  if (grid <= 1024) return false;
+  if (grid <= 1280) return tiles <= 44;
+  if (grid <= 2048) return false;
+  if (grid <= 3072) return tiles <= (grid <= 2304 ? 26 : grid <= 2560 ? 8 : grid < 2816 ? 18 : grid < 3072 ? 4 : 0);
+  return tiles <= (grid <= 3264 ? 20 : grid > 4096 && grid <= 4608 ? 4 : 0);
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
 // with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks

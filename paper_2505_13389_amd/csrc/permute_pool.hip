@@ -9,8 +9,9 @@ namespace vsa {
 // lane, where each destination row comes from (the index arithmetic of the Sec. 2.2 equation, with
 // its integer divisions, once per row instead of once per 16-byte chunk); then all threads copy, several
 // 16-byte chunks in flight per thread: four with 256 threads, or, for tensors that no cache holds, two with 512 and
-// past the caches (39936 tokens, 12 heads, d = 128: token-major in 47.9 -> 40.7 us, out 42.4 -> 38.7; 92160 tokens, 40 heads
-// 326 -> 286, 289 -> 273.  At 17 MiB a tensor four with 256 are faster, 8.8 against 10.2 us).  Workgroups of the heads of
+// past the caches (39936 tokens, 12 heads, d = 128: token-major in 47.8 -> 40.3 us, out 42.2 -> 38.3; 92160 tokens, 40 heads
+// 326 -> 286, 289 -> 273; at d = 64, where a row is 8 chunks and 512 threads have one each, 92160 tokens, 40 heads 168 -> 154, 151 -> 143,
+// head-major 150 -> 150, 141 -> 139.  At 17 MiB a tensor four with 256 are faster, 8.8 against 10.2 us).  Workgroups of the heads of
 // the same rows next to each other: slower, whole launch or XCD by XCD (46.5, 51.5 us).
 // Forward: destination = tiled row; its source is the raster row of the same (t,h,w), or zeros for
 // a pad slot.  Inverse: destination = raster row.  H > 0: the raster tensor is [B, L, H, d]

@@ -329,10 +329,10 @@ __device__ __forceinline__ int block_sum(int x, int* wsum, int tid) {
 // result does not depend on which workgroup ran when.  The split length of a (b, h) is the smallest
 // one, not below `seg_min`, at which the runs of all its long lists fit into the `cap` slots the
 // slot buffer holds per (b, h): it depends on the in-degrees alone.
-//   order: one 16-byte descriptor (key cube, begin, end of the run in col, slot + 65536 * number of the split list or -1)
-//          per dK/dV workgroup, Nc + cap of them per (b, h); unused ones carry key cube -1
-//   split: per (b, h) cap/2 + 1 descriptors: [0] = (number of split lists, 0, 0, 0), then
-//          (key cube, first slot, number of slots, runs arrived: 0) per split list, in cube order
+//   order: one 16-byte descriptor (key cube, begin, end of the run in col, run_word or -1) per dK/dV workgroup, Nc + cap of them
+//          per (b, h); unused ones carry key cube -1
+//   split: per (b, h) cap/2 + 1 descriptors: [0] is not used, then (key cube, first slot, number of slots, runs arrived: 0) per
+//          split list, in cube order
 // (the body, for the NT threads of one workgroup: thread `tid` owns cubes PT*tid .. PT*tid+PT-1, Nc <= PT*NT, whose
 // in-degrees it passes in `deg`; `v` returns where their lists begin.  wsum[NT/64] and hist[PT*NT] are
 // LDS scratch: bucket x of hist counts the items that go by the length Nc - x (the last bucket also takes what
@@ -383,9 +383,8 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
     if (nseg[i] > 1 && !split_granted(nseg[i], slot[i], cap)) nseg[i] = 1;
     rank[i] = nseg[i] > 1 ? 1 : 0;
   }
-  const int nsplit = block_scan<PT, NT>(rank, wsum, tid);
+  block_scan<PT, NT>(rank, wsum, tid);
   int4* sp = (int4*)split + (long long)bh * (cap / 2 + 1);
-  if (tid == 0) sp[0] = make_int4(nsplit, 0, 0, 0);
   int extra[PT];
 #pragma unroll
   for (int i = 0; i < PT; ++i) {
@@ -421,7 +420,7 @@ __device__ __forceinline__ void map_scan_body(int Nc, int seg_min, int cap, int 
       for (int r = 0; r < nseg[i]; ++r) {
         const int lo = run_bound(deg[i], nseg[i], r), hi = run_bound(deg[i], nseg[i], r + 1);
         ord[atomicAdd(&hist[bucket(hi - lo, nseg[i])], 1)] =
-            make_int4(j0 + i, v[i] + lo, v[i] + hi, nseg[i] > 1 ? (rank[i] << 16) | (slot[i] + r) : -1);
+            make_int4(j0 + i, v[i] + lo, v[i] + hi, nseg[i] > 1 ? run_word(rank[i], slot[i] + r) : -1);
       }
   for (int e = items + tid; e < Nc + cap; e += NT) ord[e] = make_int4(-1, 0, 0, -1);
 }

@@ -106,7 +106,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   // Start-up: one descriptor load (key block, begin and end of its run of the block's list, slot; the
   // items of a (b, h) come longest first), then the list chunk, then the first copies, then the resident
   // K rows.  A list longer than the split length is shared by several workgroups, each of which leaves
-  // its fp32 partial sums in its slot (the low 16 bits of desc.w) and the last of which to arrive adds all of them, in slot
+  // its fp32 partial sums in its slot (run_word in desc.w) and the last of which to arrive adds all of them, in slot
   // order; unused descriptors carry block -1.
   int bh_, item;
   dkv_item(block, BH, items_per_bh, dkv_heads_at_once(Nc, D), bh_, item);
@@ -114,7 +114,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   const long long bh = bh_;
   const int4 desc = ((const int4*)order)[bh * items_per_bh + item];
   if (desc.x < 0) return;
-  const int j = desc.x, beg = desc.y, n = desc.z - desc.y, slot = desc.w < 0 ? -1 : desc.w & 0xffff;
+  const int j = desc.x, beg = desc.y, n = desc.z - desc.y, slot = run_slot(desc.w);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   const long long rows0 = bh * (long long)Nc * kTile;
@@ -569,7 +569,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   // invalidated: a part is there for the others once its stores are done.
   wait_vmcnt<0>();
   __syncthreads();
-  int4* const sp = (int4*)split + bh * (cap / 2 + 1) + 1 + (desc.w >> 16);
+  int4* const sp = (int4*)split + bh * (cap / 2 + 1) + 1 + run_list(desc.w);
   if (tid == 0) *last_run = atomicAdd(&sp->w, 1) == sp->z - 1;
   __syncthreads();
   if (!*last_run) return;

@@ -78,6 +78,12 @@ VSA_RULE int slots_wanted(int deg, int seg) { const int r = split_runs(deg, seg)
 // stay within `cap`.
 VSA_RULE bool split_granted(int runs, int wanted_before, int cap) { return runs > 1 && wanted_before + runs <= cap; }
 
+// What a run's descriptor carries of its split list: the number of the list among those of the (b, h), by which the runs that have
+// arrived are counted, and the run's slot.  A whole list's descriptor carries -1.
+VSA_RULE int run_word(int list, int slot) { return (list << 16) | slot; }
+VSA_RULE int run_slot(int word) { return word < 0 ? -1 : word & 0xffff; }
+VSA_RULE int run_list(int word) { return word >> 16; }
+
 // dK/dV pass: workgroup -> (b, h) and item of its longest-first order.  Workgroups are dealt to the 8 XCDs round-robin
 // by blockIdx and every XCD has an L2 of its own, so an XCD takes whole heads as long as there are 8 of
 // them left (two heads' tiles in an L2 instead of parts of all the heads in flight), then half heads, quarter
@@ -85,7 +91,7 @@ VSA_RULE bool split_granted(int runs, int wanted_before, int cap) { return runs 
 // Against all XCDs on one head after the other (B*H = 16 .. 32): 3 to 14 % (d = 64, 256 blocks, top-32,
 // local lists: 343 -> 295 us).
 //
-// `at_once`: heads worked on at a time, 8, 4 or 2 (dkv_heads_at_once).
+// `at_once`: heads worked on at a time, 8 or 4 (dkv_heads_at_once).
 VSA_RULE int dkv_share(int heads, int items) { return (heads * items + 7) / 8; }  // per XCD
 VSA_RULE void dkv_item(unsigned b, int BH, int items, int at_once, int& bh, int& item) {
   const unsigned x = b & 7u, each = (unsigned)dkv_share(at_once, items), whole = (unsigned)(BH / at_once) * each;

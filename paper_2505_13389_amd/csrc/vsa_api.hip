@@ -510,6 +510,10 @@ int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, 
         const int lo = vsa::run_bound(deg[j], runs, r), hi = vsa::run_bound(deg[j], runs, r + 1);
         if (lo != covered || hi < lo || hi > deg[j]) ++bad;
         covered = hi;
+        if (runs > 1) {  // the slot it leaves its part in, and the entry of the split-list table it is counted in
+          const int word = vsa::run_word(nsplit - 1, slot0 + r);
+          if (word < 0 || vsa::run_slot(word) != slot0 + r || vsa::run_list(word) != nsplit - 1 || vsa::run_list(word) >= cap / 2) ++bad;
+        }
         // the dK/dV workgroup of this run reads col[beg + lo + list_slot(chunk, lane, hi - lo)]
         const int n = hi - lo;
         for (int chunk = 0; chunk * 64 < n; ++chunk)

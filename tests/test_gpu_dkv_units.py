@@ -46,3 +46,30 @@ def test_dkv_lists_of_every_length(d, H):
     assert_close(bf16_to_np(buf.out), fwd["out"], "out")
     for n in ("dq", "dk", "dv"):
         assert_close(bf16_to_np(getattr(buf, n)), ref[n], n)
+
+
+def test_four_heads_at_a_time(d=128, H=5, K=3):
+    """960 blocks, d = 128: from this head size on four heads are in flight, not eight.  Two heads of the group of four and the one
+    left over; lists of three, whose transposed lists are short and sometimes empty, and in the last head three sinks, split
+    among workgroups."""
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("dkv_four", 1, H, 20, 48, 64, d, K)
+    bits = tiled_bits(wl, seed=77)
+    x, dev, g = widen(bits), to_dev(bits), grid_of(wl)
+    assert g.Nc * 64 * d * 4 == 30 << 20
+    rng = np.random.default_rng(4)
+    idx = np.sort(np.stack([rng.permutation(g.Nc)[:K] for _ in range(H * g.Nc)]).reshape(1, H, g.Nc, K).astype(np.int32), axis=-1)
+    idx[0, H - 1] = np.sort(rng.permutation(g.Nc)[:K])
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(*a, indices_given=True)
+    buf.backward(*a, dev["dout"], workspace_kept=True)
+    torch.cuda.synchronize()
+    heads = [0, 3, H - 1]
+    x = {n: np.ascontiguousarray(v[:, heads]) for n, v in x.items()}
+    ref = orc.backward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], x["dout"], np.ascontiguousarray(idx[:, heads]), K, real="f32")
+    for n in ("dq", "dk", "dv"):
+        for i, h in enumerate(heads):
+            assert_close(bf16_to_np(getattr(buf, n)[:, h]), ref[n][:, i], f"{n} of head {h}")

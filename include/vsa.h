@@ -213,6 +213,13 @@ int vsa_backward(const vsa_params_t* p, const void* q, const void* k, const void
  * Returns VSA_OK when no access leaves its buffer, VSA_ERR_BAD_ARG otherwise (or for bad params). */
 int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, int64_t* report);
 
+/* Host-only diagnostic (no GPU, nothing enqueued): which instances of the fine kernels calls with these parameters take.
+ *   report   HOST int32[6]: wavefronts per workgroup of the forward (0: the kernel for short lists), its
+ *            workgroups that take two query blocks, whether it does the coarse stage on the way; whether
+ *            dQ, dK and dV come from one launch, wavefronts per workgroup of dQ, its workgroups that take two
+ *            query blocks */
+int vsa_host_routes(const vsa_params_t* p, int32_t* report);
+
 /* Per-kernel timing for benchmarks (not part of the paper's method).  Between
  * vsa_profile_begin and vsa_profile_end every kernel the other entry points enqueue is
  * bracketed by a pair of HIP events on the caller's stream, up to max_records kernels

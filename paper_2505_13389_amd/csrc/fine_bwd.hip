@@ -498,6 +498,12 @@ hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const 
 template <int D>
 constexpr unsigned kDqFourWaves = D == 128 ? 256 : 512;
 
+FineRoute fine_bwd_dq_route(int BH, int Nc, int d) {
+  const unsigned grid = (unsigned)(BH * Nc);
+  if (grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>)) return {4, 0};
+  return {2, paired_workgroups(grid, d == 128 ? 512 : 1024)};
+}
+
 hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                               const void* dof, const int32_t* idx, const float* rowd,
                               const float* dqc, const uint64_t* mask, void* dq, int m_blocks, int key_cubes_16,
@@ -505,8 +511,9 @@ hipError_t launch_fine_bwd_dq(int BH, int Nc, int d, int K, float scale, const v
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
-  const bool four = grid <= (d == 128 ? kDqFourWaves<128> : kDqFourWaves<64>);
-  const unsigned pairs = four ? 0 : paired_workgroups(grid, d == 128 ? 512 : 1024);
+  const FineRoute route = fine_bwd_dq_route(BH, Nc, d);
+  const bool four = route.waves == 4;
+  const unsigned pairs = route.pairs;
 #define VSA_DQ(D_, NW_, LIST_)             \
   do {                                     \
     if (NW_ == 2 && pairs) VSA_DQ_AS(D_, NW_, LIST_, (NW_ == 2)); \

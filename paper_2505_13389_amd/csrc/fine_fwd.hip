@@ -680,18 +680,29 @@ bool fine_fwd_with_coarse(int BH, int Nc, int d, int m_blocks) {
   return m_blocks == 1 && Nc <= kSmallCubes && BH * Nc <= (d == 128 ? 256 : 512);
 }
 
+static int fwd_tiles(int K, int key_cubes_16) { return key_cubes_16 ? (K + 3) / 4 : K; }
+FineRoute fine_fwd_route(int BH, int Nc, int d, int K, int key_cubes_16, bool coarse) {
+  const unsigned grid = (unsigned)(BH * Nc);
+  const int tiles = fwd_tiles(K, key_cubes_16);
+  if (coarse) return {4, 0};
+  if (fwd_short(d, grid, tiles)) return {0, 0};
+  if (fwd_four_waves(d, grid, tiles)) return {4, 0};
+  return {2, d == 128 ? paired_workgroups(grid, 512) : 0};
+}
+
 hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void* q, const void* k, const void* v,
                            const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                            const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
                            int m_blocks, int key_cubes_16, unsigned* gang_scratch, const SmallForwardArgs* coarse, const RasterMap& raster, hipStream_t s) {
   const float sl2 = scale * kLog2e;
   const unsigned grid = (unsigned)(BH * Nc);
-  const int tiles = key_cubes_16 ? (K + 3) / 4 : K;
+  const int tiles = fwd_tiles(K, key_cubes_16);
   const int stream = (long long)grid * kTile * d * 2 >= kStreamBytes;
-  if (!coarse && fwd_short(d, grid, tiles))
+  const FineRoute route = fine_fwd_route(BH, Nc, d, K, key_cubes_16, coarse != nullptr);
+  if (route.waves == 0)
     return launch_fine_fwd_short(BH, Nc, d, K, scale, q, k, v, gate_c, gate_f, idx, oc, mask, out, out_fine, lse_f, H,
                                  out_token_major, m_blocks, key_cubes_16, raster, s);
-  const unsigned pairs = d == 64 || fwd_four_waves(d, grid, tiles) ? 0 : paired_workgroups(grid, 512);
+  const unsigned pairs = route.pairs;
   // Gangs, one in about every 256 tiles walked, at d = 128 where the K and V of a head are many times an L2, the lists differ
   // and there are 16 generations (heads of 64 MiB: two).  Without / with, lists of N(0,1) inputs, then local ones: 1440
   // blocks (45 MiB), 40 heads, lists of 96 14.3 / 13.1, 13.4 / 13.0 ms, of 180 32.9 / 23.3 (L2 hits 0.38 without); 16 heads,
@@ -725,7 +736,7 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
     if (pairs) VSA_FWD_IO(D_, NW_, LIST_, (D_ == 128 && NW_ == 2), COARSE_);           \
     else VSA_FWD_IO(D_, NW_, LIST_, false, COARSE_);                                   \
   } while (0)
-  const bool four = fwd_four_waves(d, grid, tiles);
+  const bool four = route.waves == 4;
   if (coarse) {
     if (d == 128) VSA_FWD(128, 4, CubeUnits, true);
     else VSA_FWD(64, 4, CubeUnits, true);

@@ -84,6 +84,12 @@ vsa::RasterMap raster_of(const vsa_params_t* p, const Geo& g) {
   return (p->flags & VSA_FLAG_RASTER_IO) ? vsa::raster_map(g, p->H) : vsa::tiled_map();
 }
 
+// The coarse stage inside the forward's fine kernel (short sequences that make their own selection).
+bool coarse_inside(const vsa_params_t* p, const Geo& g) {
+  return !(p->flags & (VSA_FLAG_INDICES_GIVEN | VSA_FLAG_COARSE_FUSED | VSA_FLAG_COARSE_UNFUSED)) && !pooled_select(p) && !key16(p) &&
+         vsa::fine_fwd_with_coarse(p->B * p->H, g.Nc, p->d, g.m);
+}
+
 float scale_of(const vsa_params_t* p) { return p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d); }
 
 // Bump allocator over the caller's workspace.
@@ -246,8 +252,7 @@ int enqueue_forward(const vsa_params_t* p, const Geo& g, const void* q, const vo
   VSA_TRY("pool", vsa::launch_pool(g, BH, p->d, w.mask, q, k, v, w.qc, w.kc, w.vc, sub ? 1 : 3, s));
   if (sub) VSA_TRY("pool", vsa::launch_pool_keys16(BH, g.Nc, p->d, w.mask, w.kcnt, k, v, w.kc, w.vc, s));
   const bool pooled = pooled_select(p);
-  const bool small = !given && !pooled && !sub && !(p->flags & (VSA_FLAG_COARSE_FUSED | VSA_FLAG_COARSE_UNFUSED)) &&
-                     vsa::fine_fwd_with_coarse(BH, g.Nc, p->d, g.m);
+  const bool small = coarse_inside(p, g);
   if (!small)
     VSA_TRY("coarse", vsa::launch_coarse(BH, g.Nc, key_rows(p, g), p->d, p->topk, scale, w.qc, w.kc, w.vc, w.sc, oc, lse_c, idx,
                             (given || pooled) ? 0 : 1, (pooled || sub) ? 0 : coarse_form(p, g), w.kcnt, s));
@@ -554,6 +559,22 @@ int vsa_host_replay_lists(const vsa_params_t* p, const int32_t* host_block_idx, 
     report[4] = max_split; report[5] = max_col; report[6] = seg_min; report[7] = cap;
   }
   return bad ? VSA_ERR_BAD_ARG : VSA_OK;
+}
+
+int vsa_host_routes(const vsa_params_t* p, int32_t* report) {
+  Geo g;
+  int rc = check_params(p, &g);
+  if (rc != VSA_OK) return rc;
+  if ((rc = check_topk(p, g)) != VSA_OK) return rc;
+  if (!report) return VSA_ERR_NULL;
+  const int BH = p->B * p->H;
+  const bool inside = coarse_inside(p, g);
+  const vsa::FineRoute fwd = vsa::fine_fwd_route(BH, g.Nb, p->d, p->topk * blocks_per_entry(p, g), key16(p) ? 1 : 0, inside);
+  const bool one = vsa::fine_bwd_in_one(BH, g.Nb, key16(p) ? 1 : 0);
+  const vsa::FineRoute dq = one ? vsa::FineRoute{4, 0} : vsa::fine_bwd_dq_route(BH, g.Nb, p->d);
+  report[0] = fwd.waves; report[1] = (int32_t)fwd.pairs; report[2] = inside;
+  report[3] = one; report[4] = dq.waves; report[5] = (int32_t)dq.pairs;
+  return VSA_OK;
 }
 
 int vsa_profile_begin(int max_records) {

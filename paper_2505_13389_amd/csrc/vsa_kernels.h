@@ -28,6 +28,14 @@ hipError_t launch_fine_fwd_short(int BH, int Nc, int d, int K, float scale, cons
                                  const void* gate_c, const void* gate_f, const int32_t* idx, const float* oc,
                                  const uint64_t* mask, void* out, void* out_fine, float* lse_f, int H, int out_token_major,
                                  int m_blocks, int key_cubes_16, const RasterMap& raster, hipStream_t s);
+// Which instance of a fine kernel a launch takes: wavefronts per workgroup (0: the forward's kernel for short lists) and how many
+// workgroups take two blocks.  `Nc`: blocks; `coarse`: the coarse stage is done on the way.
+struct FineRoute {
+  int waves;
+  unsigned pairs;
+};
+FineRoute fine_fwd_route(int BH, int Nc, int d, int K, int key_cubes_16, bool coarse);
+FineRoute fine_bwd_dq_route(int BH, int Nc, int d);
 // What the forward of a short sequence forms its coarse stage from, row by row in the fine kernel, and where it leaves it.
 struct SmallForwardArgs {
   const float *qc, *kc, *vc;

@@ -26,7 +26,8 @@ STATUS = {0: "VSA_OK", -1: "VSA_ERR_NULL", -2: "VSA_ERR_BAD_ARG", -3: "VSA_ERR_U
           -5: "VSA_ERR_WORKSPACE", -6: "VSA_ERR_HIP", -7: "VSA_ERR_SCRATCH_LIMIT"}
 EXPORTS = ["vsa_padded_tokens", "vsa_workspace_bytes", "vsa_tile_permute", "vsa_tile_permute_many", "vsa_forward", "vsa_backward",
            "vsa_status_string", "vsa_profile_begin", "vsa_profile_count", "vsa_profile_name", "vsa_profile_ms",
-           "vsa_profile_end", "vsa_bench_mfma_rate", "vsa_forward_static", "vsa_static_scratch_bytes", "vsa_host_replay_lists"]
+           "vsa_profile_end", "vsa_bench_mfma_rate", "vsa_forward_static", "vsa_static_scratch_bytes", "vsa_host_replay_lists",
+           "vsa_host_routes"]
 
 
 class VsaParams(C.Structure):
@@ -69,6 +70,8 @@ def lib():
         L.vsa_static_scratch_bytes.restype = C.c_size_t
         L.vsa_host_replay_lists.argtypes = [C.POINTER(VsaParams), vp, vp]
         L.vsa_host_replay_lists.restype = C.c_int
+        L.vsa_host_routes.argtypes = [C.POINTER(VsaParams), C.POINTER(C.c_int32)]
+        L.vsa_host_routes.restype = C.c_int
         L.vsa_backward.argtypes = [C.POINTER(VsaParams)] + [vp] * 17 + [C.c_size_t, vp]
         L.vsa_backward.restype = C.c_int
         L.vsa_bench_mfma_rate.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.POINTER(C.c_double), C.c_void_p]
@@ -221,6 +224,16 @@ def vsa_host_replay_lists(pb: Problem, block_idx):
     rc = lib().vsa_host_replay_lists(C.byref(pb.params()), idx.ctypes.data_as(C.c_void_p), rep)
     names = ("violations", "longest_list", "items", "slots", "split_lists", "col_entries", "seg", "cap")
     return rc, dict(zip(names, (int(v) for v in rep)))
+
+
+def vsa_host_routes(pb: Problem, indices_given: bool = False):
+    """Host-only: which instances of the fine kernels calls of this shape take."""
+    rep = (C.c_int32 * 6)()
+    flags = pb.flags | (VSA_FLAG_INDICES_GIVEN if indices_given else 0)
+    rc = lib().vsa_host_routes(C.byref(pb.params(flags)), rep)
+    if rc:
+        raise VsaError("vsa_host_routes", rc)
+    return dict(zip(("fwd_waves", "fwd_pairs", "coarse_inside", "bwd_in_one", "dq_waves", "dq_pairs"), map(int, rep)))
 
 
 def vsa_bench_mfma_rate(operands: torch.Tensor, sink: torch.Tensor, workgroups: int, iters: int) -> float:

@@ -120,6 +120,28 @@ def test_list_index_rules_with_key_cube_lists(lib):
         assert rep["longest_list"] <= Nc and rep["col_entries"] <= Nc * 21
 
 
+def test_routes(lib):
+    """The instances of the fine kernels by size: one launch does everything, four wavefronts, two sharing a block, two blocks
+    each, the forward's kernel for short lists; what it is at given lists and what it refuses."""
+    import ctypes
+    import dataclasses
+
+    def of(*a, given=False, flags=0):
+        r = vsa.vsa_host_routes(dataclasses.replace(vsa.Problem(*a), flags=flags), indices_given=given)
+        return tuple(r.values())
+    tiny, ragged = (1, 2, 8, 16, 16, 64, 8), (1, 3, 7, 22, 30, 128, 9)  # 64 and 288 blocks
+    assert of(*tiny) == (4, 0, 1, 1, 4, 0)
+    assert of(*tiny, flags=vsa.VSA_FLAG_COARSE_UNFUSED)[:3] == (4, 0, 0) and of(*tiny, given=True)[2] == 0
+    assert of(*ragged) == (2, 0, 0, 0, 2, 0)
+    assert of(1, 12, 16, 32, 32, 128, 32) == (2, 1536, 0, 0, 2, 1536)
+    assert of(1, 12, 7, 22, 30, 128, 9)[:2] == (0, 0)
+    assert vsa.vsa_host_routes(dataclasses.replace(vsa.Problem(*ragged[:-1], 36), flags=vsa.VSA_FLAG_KEY_CUBES_16))["fwd_waves"] == 2
+    for pb in (vsa.Problem(*tiny[:-1], 33), vsa.Problem(*tiny[:-1], 0), vsa.Problem(1, 2, 8, 16, 16, 96, 8)):
+        with pytest.raises(vsa.VsaError):
+            vsa.vsa_host_routes(pb)
+    assert lib.vsa_host_routes(ctypes.byref(vsa.Problem(*tiny).params()), None) == -1
+
+
 def test_status_strings(lib):
     seen = set()
     for s in range(0, -8, -1):

@@ -12,19 +12,31 @@ from paper_2505_13389_amd.synth import Workload
 pytestmark = pytest.mark.gpu
 
 
-def run_and_check(wl, bits, idx):
+SHORT, TWO, FOUR = 0, 2, 4  # the kernel for short lists; the general one, by wavefronts per workgroup
+
+
+def assert_kernel(wl, waves, paired=False):
+    from paper_2505_13389_amd import vsa
+    route = vsa.vsa_host_routes(problem_of(wl), indices_given=True)
+    assert (route["fwd_waves"], route["fwd_pairs"] > 0) == (waves, paired), route
+
+
+def run_and_check(wl, bits, idx, heads=None):
+    """`heads`: those compared with the oracle (all)."""
     import torch
     from paper_2505_13389_amd import vsa
-    x, dev, g = widen(bits), to_dev(bits), grid_of(wl)
-    ref = orc.forward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], wl.topk, real="f32", block_idx=idx)
+    dev, g, heads = to_dev(bits), grid_of(wl), list(range(wl.H)) if heads is None else heads
+    x = {n: np.ascontiguousarray(v[:, heads]) for n, v in widen(bits).items()}
+    ref = orc.forward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], wl.topk, real="f32",
+                      block_idx=np.ascontiguousarray(idx[:, heads]))
     buf = vsa.Buffers(problem_of(wl))
     buf.block_idx.copy_(torch.from_numpy(idx))
     buf.forward(dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"], indices_given=True)
     torch.cuda.synchronize()
-    assert_close(bf16_to_np(buf.out), ref["out"], "out")
-    assert_close(bf16_to_np(buf.out_fine), ref["out_fine"], "out_fine")
+    assert_close(bf16_to_np(buf.out)[:, heads], ref["out"], "out")
+    assert_close(bf16_to_np(buf.out_fine)[:, heads], ref["out_fine"], "out_fine")
     # fp32 sums of up to a few thousand terms, logits of magnitude up to 500 (log2 units): 1e-3 is 8 spacings there
-    assert np.abs(buf.lse_fine.cpu().numpy() - ref["lse_fine"]).max() < 1e-3
+    assert np.abs(buf.lse_fine.cpu().numpy()[:, heads] - ref["lse_fine"]).max() < 1e-3
 
 
 def random_lists(wl, g, seed):
@@ -49,23 +61,32 @@ TWO_WAVES = [(128, 3, K) for K in (9, 10, 11, 12, 13, 14, 65)] + [(64, 9, K) for
 def test_walks_of_two_wavefronts(d, H, K):
     wl = Workload("fwd_two", 1, H, 7, 22, 30, d, K)
     g = grid_of(wl)
+    assert_kernel(wl, TWO)
     run_and_check(wl, tiled_bits(wl, seed=300 + K + d, pad_garbage=True), random_lists(wl, g, K))
 
 
-@pytest.mark.parametrize("d,K", [(128, 60), (128, 61), (64, 14), (64, 15), (64, 65)])
-def test_both_sides_of_the_short_list_rule(d, K):
-    """576 query blocks: up to 60 tiles (d = 64: 14) the kernel for short lists, then two (four) wavefronts."""
-    wl = Workload("fwd_rule", 1, 6, 7, 22, 30, d, K)
+# d, heads of 96 query blocks, list length, kernel, whether workgroups take two blocks
+RULE = [(128, 5, 16, SHORT, False), (128, 5, 17, TWO, False), (128, 12, 44, SHORT, False), (128, 12, 45, TWO, True),
+        (128, 24, 26, SHORT, False), (128, 24, 27, TWO, True), (128, 28, 18, SHORT, False), (128, 28, 19, TWO, True),
+        (64, 6, 16, SHORT, False), (64, 6, 17, FOUR, False), (64, 12, 14, SHORT, False), (64, 12, 15, FOUR, False),
+        (64, 28, 9, SHORT, False), (64, 28, 10, TWO, False)]
+
+
+@pytest.mark.parametrize("d,H,K,waves,paired", RULE)
+def test_both_sides_of_the_short_list_rule(d, H, K, waves, paired):
+    wl = Workload("fwd_rule", 1, H, 7, 22, 30, d, K)
     g = grid_of(wl)
-    run_and_check(wl, tiled_bits(wl, seed=400 + K + d, pad_garbage=True), random_lists(wl, g, K))
+    assert_kernel(wl, waves, paired)
+    run_and_check(wl, tiled_bits(wl, seed=400 + K + d, pad_garbage=True), random_lists(wl, g, K), heads=[0, H // 2, H - 1])
 
 
-@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("d,H", [(64, 6), (128, 12), (128, 5)])  # 576, 1152 and 480 query blocks
 @pytest.mark.parametrize("K", [1, 2, 12, 13])
-def test_short_walks_of_larger_launches(K, d):
-    """576 query blocks: the kernel for short lists."""
-    wl = Workload("fwd_short", 1, 6, 7, 22, 30, d, K)
+def test_short_walks_of_larger_launches(K, d, H):
+    """The kernel for short lists."""
+    wl = Workload("fwd_short", 1, H, 7, 22, 30, d, K)
     g = grid_of(wl)
+    assert_kernel(wl, SHORT)
     run_and_check(wl, tiled_bits(wl, seed=200 + K + d, pad_garbage=True), random_lists(wl, g, K))
 
 
@@ -88,9 +109,11 @@ def test_walks_that_begin_without_a_valid_key(H, d, K=9):
     run_and_check(wl, tiled_bits(wl, seed=3, pad_garbage=True), idx)
 
 
-@pytest.mark.parametrize("d,H,K", [(64, 9, 9), (64, 9, 14), (64, 6, 9), (128, 6, 9), (128, 3, 14)])
-def test_walks_of_two_wavefronts_that_begin_without_a_valid_key(d, H, K):
-    """Two wavefronts; (6 heads) the kernel for short lists."""
+@pytest.mark.parametrize("d,H,K,waves", [(64, 9, 9, TWO), (64, 9, 14, TWO), (64, 6, 9, SHORT), (128, 5, 9, SHORT), (128, 12, 9, SHORT),
+                                         (128, 3, 14, TWO)])
+def test_walks_of_two_wavefronts_that_begin_without_a_valid_key(d, H, K, waves):
+    """Two wavefronts, and the kernel for short lists."""
+    assert_kernel(Workload("fwd_dead", 1, H, 6, 22, 30, d, K), waves)
     test_walks_that_begin_without_a_valid_key(H, d, K)
 
 
@@ -131,6 +154,7 @@ def test_values_of_any_magnitude(scale, waves, d):
     H = 1 if waves == 4 else {64: 9, 128: 3}[d]
     wl = Workload("fwd_big", 1, H, 7, 22, 30, d, 40)
     g = grid_of(wl)
+    assert_kernel(wl, waves)
     bits = tiled_bits(wl, seed=d + 1, pad_garbage=True)
     rng = np.random.default_rng(d + H)
     ramp = np.linspace(-20.0, 20.0, g.Nc)
@@ -142,14 +166,15 @@ def test_values_of_any_magnitude(scale, waves, d):
     run_and_check(wl, bits, random_lists(wl, g, 11))
 
 
-@pytest.mark.parametrize("H,K,d", [(1, 9, 64), (1, 9, 128), (6, 5, 64), (6, 5, 128), (9, 20, 64), (3, 20, 128)])
-def test_rows_whose_logits_are_all_minus_infinity(H, K, d):
-    """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys.  (Four wavefronts, the
-    kernel for short lists, two wavefronts.)"""
+@pytest.mark.parametrize("H,K,d,waves", [(1, 9, 64, FOUR), (1, 9, 128, FOUR), (6, 5, 64, SHORT), (5, 5, 128, SHORT), (9, 20, 64, TWO),
+                                         (3, 20, 128, TWO)])
+def test_rows_whose_logits_are_all_minus_infinity(H, K, d, waves):
+    """As a row without a valid key: O_f = 0, lse = 0, and no NaN in the gradients of the keys."""
     import torch
     from paper_2505_13389_amd import vsa
     wl = Workload("fwd_minf", 1, H, 7, 22, 30, d, K)
     g = grid_of(wl)
+    assert_kernel(wl, waves)
     bits = tiled_bits(wl, seed=K + d)
     valid, _ = orc.valid_mask(g)
     V = g.Np // g.Nc

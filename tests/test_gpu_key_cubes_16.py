@@ -44,10 +44,11 @@ def random_cases(n, seed=20250515, tag="rnd16"):
 
 
 CASES.update(random_cases(8))
-# Launches of 288 to 864 query blocks, on a clip whose last layer of cubes holds dead key cubes: the kernel for short lists
-# (1 to 18 tiles of four entries, the last one partial or not), two and four wavefronts per workgroup.
-for _d, _H, _ks in ((128, 6, (1, 7, 48, 49, 241)), (128, 3, (33, 49, 70)), (64, 6, (1, 7, 48, 49, 70)), (64, 9, (9, 70))):
-    CASES.update({f"blocks{96 * _H}_d{_d}_k{_k}": Workload(f"blocks{96 * _H}_d{_d}_k{_k}", 1, _H, 6, 22, 30, _d, _k) for _k in _ks})
+# Launches of 288 to 1152 query blocks, on a clip whose last layer of cubes holds dead key cubes (tiles of four entries, the last one
+# partial or not): the kernel for short lists (0), two and four wavefronts per workgroup.  d, heads, list length -> kernel
+KERNEL = {(128, 5, 1): 0, (128, 5, 7): 0, (128, 12, 48): 0, (128, 5, 49): 0, (128, 5, 70): 2, (128, 3, 33): 2, (128, 3, 49): 2,
+          (128, 6, 7): 2, (128, 6, 241): 2, (64, 6, 1): 0, (64, 6, 7): 0, (64, 6, 48): 0, (64, 6, 49): 0, (64, 6, 70): 4, (64, 9, 9): 2, (64, 9, 70): 2}
+CASES.update({f"blocks{96 * _H}_d{_d}_k{_k}": Workload(f"blocks{96 * _H}_d{_d}_k{_k}", 1, _H, 6, 22, 30, _d, _k) for _d, _H, _k in KERNEL})
 
 
 @pytest.fixture(scope="module")
@@ -73,6 +74,8 @@ def test_key_cubes_16_forward_backward(vsa, name):
 
     dev = to_dev(bits)
     pb = dataclasses.replace(problem_of(wl), flags=vsa.VSA_FLAG_KEY_CUBES_16)
+    if name.startswith("blocks"):
+        assert vsa.vsa_host_routes(pb)["fwd_waves"] == KERNEL[wl.d, wl.H, wl.topk]
     buf = vsa.Buffers(pb, backward=True, with_gate_f=with_gate_f)
     a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
     buf.forward(*a)

@@ -10,11 +10,20 @@ from paper_2505_13389_amd.synth import Workload
 
 pytestmark = pytest.mark.gpu
 
-# d, heads of 95 query blocks, list length
-#   128, 7: all paired, the last workgroup has one block (forward: from 17 tiles on); 128, 11: 512 pairs, 21 blocks shared
-#   64, 17, 22 and 25 (dQ alone): all paired; 1024 pairs, 42 blocks shared; 2375 blocks, none paired
-CASES = ([(128, 7, K) for K in (1, 2, 3, 17, 18, 65, 95)] + [(128, 11, K) for K in (1, 41)] +
-         [(64, 17, K) for K in (1, 2, 9)] + [(64, 22, 3), (64, 25, 3)])
+# d, heads of 95 query blocks, list length, what the forward (None: not a matter of pairs) and dQ do with the blocks
+ALL, SOME, NONE = "all paired", "full generations paired, the rest shared", "all shared"
+CASES = ([(128, 7, K, ALL, ALL) for K in (1, 2, 3, 17, 18, 65, 95)] +  # (the last workgroup has one block)
+         [(128, 11, 1, None, SOME), (128, 11, 50, SOME, SOME)] + [(128, 15, K, SOME, SOME) for K in (1, 2, 5)] +
+         [(64, 17, K, None, ALL) for K in (1, 2, 9)] + [(64, 22, 3, None, SOME), (64, 25, 3, None, NONE)])
+
+
+def assert_pairs(wl, forward, dq):
+    from paper_2505_13389_amd import vsa
+    blocks = wl.H * grid_of(wl).Nc
+    route = vsa.vsa_host_routes(problem_of(wl), indices_given=True)
+    of = lambda pairs: ALL if 2 * pairs >= blocks else SOME if pairs else NONE
+    assert route["dq_waves"] == 2 and of(route["dq_pairs"]) == dq, route
+    assert forward is None or (route["fwd_waves"] == 2 and of(route["fwd_pairs"]) == forward), route
 
 
 def check_heads(wl, bits, idx, heads):
@@ -38,10 +47,11 @@ def check_heads(wl, bits, idx, heads):
         assert_close(bf16_to_np(getattr(buf, n))[:, heads], grad[n], n)
 
 
-@pytest.mark.parametrize("d,H,K", CASES)
-def test_blocks_of_their_own(d, H, K):
+@pytest.mark.parametrize("d,H,K,forward,dq", CASES)
+def test_blocks_of_their_own(d, H, K, forward, dq):
     wl = Workload("paired", 1, H, 18, 74, 4, d, K)
     g = grid_of(wl)
+    assert_pairs(wl, forward, dq)
     rng = np.random.default_rng(K)
     idx = np.sort(rng.permuted(np.tile(np.arange(g.Nc, dtype=np.int32), (1, H, g.Nc, 1)), axis=-1)[..., :K])
     check_heads(wl, tiled_bits(wl, seed=500 + K + H, pad_garbage=True), idx, [0, H // 2, H - 2, H - 1])
@@ -55,6 +65,7 @@ def test_values_of_any_magnitude_per_wavefront(scale, d=128, H=7, K=40):
     from paper_2505_13389_amd import vsa
     wl = Workload("paired_big", 1, H, 18, 74, 4, d, K)
     g = grid_of(wl)
+    assert_pairs(wl, ALL, ALL)
     bits = tiled_bits(wl, seed=9, pad_garbage=True)
     rng = np.random.default_rng(4)
     ramp = np.linspace(-20.0, 20.0, g.Nc)

@@ -25,7 +25,9 @@
  *     input are ignored (NaN or Inf there is not allowed).
  *   - Value range: raw dot products |q . k| of token pairs must stay below 15000 (the pad
  *     keys of a partially filled cube are removed by adding -30000 to their raw logits).
- *   - Results are deterministic (bit-identical across calls on the same inputs).
+ *   - Results are deterministic (bit-identical across calls on the same inputs).  Two heads of one call
+ *     that hold equal values need not get equal bits: some blocks of a launch are worked on by one
+ *     wavefront and some shared by two, which rounds the weights differently.
  *   - Return value: VSA_OK (0) or a negative vsa_status.  Validation errors are detected
  *     before anything is enqueued; VSA_ERR_HIP (a launch rejected by the runtime) can leave
  *     the earlier kernels of that call enqueued.
@@ -60,9 +62,11 @@ typedef enum {
 #define VSA_FLAG_COARSE_FUSED 8u    /* vsa_forward: run the coarse stage as ONE launch that keeps the score block
                                       in LDS (Sec. 2.4, App. D; up to 1536 cubes, ignored above) ...          */
 #define VSA_FLAG_COARSE_UNFUSED 64u /* ... or as three launches with the score matrix in the workspace.  With
-                                      neither flag the library picks the faster form for the shape.  The two
-                                      forms use different matrix instructions: their logits agree to the last
-                                      few bits, so their selections can differ on near ties only.            */
+                                      neither flag the library picks the fastest form for the shape, for short
+                                      sequences (up to 64 cubes, small launches) a third one that has no launch
+                                      of its own: the fine kernel forms each block's row on the way.  The
+                                      forms sum in different orders: their logits agree to the last few bits,
+                                      so their selections can differ on near ties only.                      */
 #define VSA_FLAG_OUT_TOKEN_MAJOR 16u /* vsa_forward: `out` is written token-major, bf16 [B,Np,H,d] = [B,Np,H*d]
                                        in tiled token order: the layout the output projection consumes
                                        ("b h l d -> b l (h d)", last line of the App. B listing) when

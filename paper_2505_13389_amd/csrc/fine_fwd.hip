@@ -22,7 +22,7 @@
 // multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
 // one.  d = 64 takes two wavefronts per SIMD.
 //
-// What bounds it: instruction issue and power.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma,
+// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma,
 // exp2, sum, half a conversion per value; 24 LDS reads, 16 copies): 1650 cycles where the matrix pipe needs 1024, at a
 // clock that falls as the chip fills (1.75 GHz; 2.1 while the last workgroups of a launch run).  Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on

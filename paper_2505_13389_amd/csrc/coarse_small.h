@@ -1,8 +1,9 @@
 // The coarse stage of short sequences inside the fine kernels: with up to 64 cubes a (b, h) a workgroup of 256 threads forms
 // the one row (or column) of the coarse matrices that belongs to its block by itself -- 64 x d multiply-adds a
 // product -- while its list and its first tiles are on their way, instead of waiting for a launch of its own that
-// hardly fills a compute unit.  fp32 products and sums, in a fixed order.  Bound by latency: rows are requested before
-// their weights are formed (64 cubes, d = 128, top-1: forward 21.5 -> 15.7 us; 18.7 with a launch for the coarse stage).
+// hardly fills a compute unit.  fp32 products and sums, in a fixed order.  Bound by latency: the rows that are
+// summed are requested before their weights are formed (64 cubes, d = 128, top-1: forward 21.5 -> 15.7 us; 18.7 with a launch for the
+// coarse stage).  The chunks of the logits' products are not: at d = 128 those rows leave no registers and they come in eight trips.
 // Forwards of 12 to 64 cubes, up to 256 blocks (d = 64: 512), 0.73 to 0.93 of the time; 32 cubes, 2 heads, d = 64, top-8 17.0 ->
 // 13.4 us.  In launches of several generations every one of them would pay what one launch costs.
 #pragma once

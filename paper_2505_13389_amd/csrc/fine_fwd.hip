@@ -22,9 +22,16 @@
 // multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
 // one.  d = 64 takes two wavefronts per SIMD.
 //
-// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 190 others (112 of softmax: fma,
-// exp2, sum, half a conversion per value; 24 LDS reads, 16 copies): 1650 cycles where the matrix pipe needs 1024, at a
-// clock that falls as the chip fills (1.75 GHz; 2.1 while the last workgroups of a launch run).  Around the walk a wavefront
+// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 190 others (110 of softmax: fma,
+// exp2, sum, half a conversion per value; 24 LDS reads, 16 copies): 1490 cycles where the matrix pipe needs 1024, at a
+// clock that falls as the chip fills (1.6 to 1.75 GHz; 2.1 while the last workgroups of a launch run).  What an instruction costs a
+// wavefront that is alone on its SIMD, measured behind matrix instructions: 5 cycles in vector arithmetic, 8 if the next one
+// needs its result, exp2 9, an LDS read 8, scalar ones and waits 4; five or six plain ones fit behind a matrix instruction,
+// and none is made up for by fewer behind the next.  So the softmax is a pipeline of stages without neighbours that depend on one another,
+// the stages, operand reads and copies are dealt to the 32 matrix instructions one by one, and what is rare (a moved
+// reference, pad keys, a new chunk of the list) lies out of the loop's line: 1730 -> 1490 cycles a unit (768 blocks, top-64
+// to 192), whole launches 8.5 % fewer at 39936 tokens, top-78, of which the clock leaves 3.8 % of the time: 1306 -> 1258 us for the
+// forward, 264 -> 259 at 16384 tokens, top-32 (two generations' start-up and end in it).  Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
 // normalising, gating and storing, which nothing overlaps on its SIMD: halved per block where a wavefront has a block of
 // its own.  That, one factor per lane instead of per row and item on the way out, and a start that waits for K alone:
@@ -86,6 +93,23 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
   __syncthreads();
 }
 
+// The softmax stages of a unit (p_stages) that precede matrix instruction j + 1 of the PV phase before it, and matrix instruction
+// j + 1 of the S phase of the unit after it: few where copies and transposing reads are many.
+template <int D>
+struct FwdStages {
+  static constexpr int pv(int j) {
+    constexpr int wide[16] = {0, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1, 2, 1, 1, 1, 2}, narrow[16] = {0, 1, 2, 2, 2, 2, 3, 3};
+    return D == 128 ? wide[j] : narrow[j];
+  }
+  static constexpr int s(int j) {
+    constexpr int wide[16] = {1, 2, 1, 2, 1, 2, 1, 2, 1, 1, 1, 1, 1, 1, 1, 0}, narrow[16] = {3, 3, 3, 3, 3, 2, 2, 0};
+    return D == 128 ? wide[j] : narrow[j];
+  }
+  static constexpr int before_pv(int j) { return j == 0 ? 0 : before_pv(j - 1) + pv(j - 1); }
+  static constexpr int before_s(int j) { return j == 0 ? before_pv(16) : before_s(j - 1) + s(j - 1); }
+};
+static_assert(FwdStages<128>::before_s(15) == 34 && FwdStages<64>::before_s(7) == 34, "all of them ahead of the check");
+
 // PAIRS: the first `pairs` workgroups take two blocks, one per wavefront (d = 128, NW = 2; at d = 64 two wavefronts per SIMD hide one
 // another's start-up).  Launches without pairs have instances of their own, which know each wavefront's key half: 288 blocks,
 // top-26 32.7 -> 32.1 us, top-50 49.2 -> 48.1.
@@ -106,9 +130,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   constexpr int HALF = TL::BYTES / 2;   // 32 rows
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int NPV = 2 * DVB;          // steps of the PV phase
-  // LDS operands are read in pairs (one wait for both), kAhead steps before the first of them is used
-  constexpr int kAhead = D == 128 ? 4 : 2;
-  constexpr int kEarly = 7;             // of the 16 softmax items of a unit, those behind the PV phase before it
+  // LDS operands are waited for in pairs of steps, and read kAhead steps before the first of them is used
+  constexpr int kAhead = D == 128 ? 6 : 2;
+  constexpr int kEarly = FwdStages<D>::before_pv(16);  // of the 34 softmax stages of a unit, those behind the PV phase before it
   constexpr int OS = D;
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
@@ -116,7 +140,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   __shared__ SmallCoarse<COARSE ? D : 4> lc;
   __shared__ int32_t lc_list[COARSE ? kSmallCubes : 1];
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
-  static_assert(KS == NPV && KS > kAhead, "phase interleave");
+  constexpr int kEvery = D == 128 ? 2 : 1;  // a copy behind every other, or every, matrix instruction of a phase until all are requested
+  // copies of a phase that precede its wait for earlier ones
+  constexpr int kPart = 2 * (KS - kAhead) / kEvery < NC ? 2 * (KS - kAhead) / kEvery : NC;
+  static_assert(KS == NPV && KS == NC && KS > kAhead, "phase interleave");
 
   // With K = Nc every workgroup of a head walks the same list: then all XCDs work on the same head
   // (plain blockIdx order), which keeps that list's tiles shared chip-wide, and the workgroups that
@@ -274,7 +301,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // references of the lane's two query columns; zero, and `have` false, until the first unit with a valid key
   float ref[2] = {0.f, 0.f};
   bool have = false;
-  float lsum[2] = {0.f, 0.f}, tsum[2] = {0.f, 0.f};
+  float lsum[2] = {0.f, 0.f};
+  float ta[2] = {0.f, 0.f}, tb[2] = {0.f, 0.f};  // the unit's sums of a column, even and odd values
   uint4 pb[2][2];  // P^T of the current unit as operands: [query half][contraction step]
   auto put = [](uint4& u4, int w, uint32_t x) {
     if (w == 0) u4.x = x;
@@ -282,18 +310,47 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (w == 2) u4.z = x;
     if (w == 3) u4.w = x;
   };
-  // softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0
-  auto p_item = [&](const f32x16 (&S)[2], int it, const float* rf) {
-    const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
-    const float x0 = fast_exp2(fmaf(S[b][e], sl2, -rf[b])), x1 = fast_exp2(fmaf(S[b][e + 1], sl2, -rf[b]));
-    tsum[b] = (it & 11) == 0 ? x0 + x1 : tsum[b] + x0 + x1;
-    const uint32_t pp = pack_bf16(x0, x1);
-    put(pb[b][st], w, pp);
-    asm volatile("" : "+v"(tsum[b]) : "v"(pp));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+  // Softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0.  Its arithmetic goes
+  // through a pipeline of STAGES, one or two of them behind a matrix instruction, in which no result is used by the next
+  // instruction (that costs 8 cycles instead of 5) and exponentials (9) are apart: stage 0 the fma's of item 0; stage 2g + 1 the first
+  // exponential of item g and the fma's of the next; stage 2g + 2 its second exponential, and the sums and the conversion of
+  // the item before; stage 33 those of the last item.
+  float xf[2][2] = {}, xe[2][2] = {};  // arguments and exponentials of an item, by its parity
+  auto p_fma = [&](const f32x16 (&S)[2], int it, const float* rf) {
+    const int b = (it >> 2) & 1, e = 8 * (it >> 3) + 2 * (it & 3);
+    float (&f)[2] = xf[it & 1];
+    f[0] = fmaf(S[b][e], sl2, -rf[b]);
+    f[1] = fmaf(S[b][e + 1], sl2, -rf[b]);
+    asm volatile("" : "+v"(f[0]), "+v"(f[1]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
   };
-  auto p_items = [&](const f32x16 (&S)[2], int from, int to, const float* rf) {
+  auto p_exp = [&](int it, int i) {
+    xe[it & 1][i] = fast_exp2(xf[it & 1][i]);
+    asm volatile("" : "+v"(xe[it & 1][i]));
+  };
+  auto p_sum = [&](int it) {
+    const int b = (it >> 2) & 1;
+    const float x0 = xe[it & 1][0], x1 = xe[it & 1][1];
+    const uint32_t pp = pack_bf16(x0, x1);
+    ta[b] = (it & 11) == 0 ? x0 : ta[b] + x0;
+    tb[b] = (it & 11) == 0 ? x1 : tb[b] + x1;
+    put(pb[b][it >> 3], it & 3, pp);
+    asm volatile("" : "+v"(ta[b]), "+v"(tb[b]) : "v"(pp));
+  };
+  auto p_stages = [&](const f32x16 (&S)[2], int from, int to, const float* rf) {
 #pragma unroll
-    for (int it = from; it < to; ++it) p_item(S, it, rf);
+    for (int n = from; n < to; ++n) {
+      const int g = (n - 1) >> 1;
+      if (n == 0) p_fma(S, 0, rf);
+      else if (n == 33) p_sum(15);
+      else p_exp(g, (n - 1) & 1);
+      if (n > 0 && n < 33) {
+        if (n & 1) {
+          if (g < 15) p_fma(S, g + 1, rf);
+        } else if (g > 0) {
+          p_sum(g - 1);
+        }
+      }
+    }
   };
   // the larger of `old` and the largest (scaled) logit of the unit in the lane's query column
   // (pad keys do not count: a column all of whose logits are -inf keeps kNoRef and ends as one without a valid key)
@@ -335,7 +392,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       ref[1] = unit_max(s0[1], valid, kNoRef);
       have = true;
     }
-    p_items(s0, 0, kEarly, ref);
+    p_stages(s0, 0, kEarly, ref);
   }
 
   // One unit u (its S is there, in S): P(u) while S(u+1) is multiplied into T, then PV(u) while P(u+1) begins.
@@ -346,123 +403,133 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu), more3 = KIND == 2 || (KIND == 1 && u + 3 < nu);
     const unsigned char* kn = smem + (1 - par) * HALF;  // K(u+1)
     const unsigned char* vc = smem + (2 + par) * HALF;  // V(u)
-    bf16x8 ka[KS + kAhead], va[NPV + kAhead];
-    auto v_op = [&](int i) { return TL::transposed_at(vc, lane_b0, lane_b1, i / DVB, i % DVB); };
+    bf16x8 ka[KS + kAhead];
+    bf16x4 va[NPV + kAhead][2];
+    auto v_half = [&](int i, int part) { return TL::transposed_half(vc, part ? lane_b1 : lane_b0, i / DVB, i % DVB); };
+    // The operand reads for the two steps kAhead further on, spread over the four matrix instructions of two steps (d = 64: over the
+    // first two): `k` reads a step's row-major operand, V operands are two reads.  q = 0 .. 3; `pv`: step of the PV phase.
+    constexpr int kSpread = D == 128 ? 4 : 2;
+    auto read_v = [&](int i, int q) {  // of steps i and i + 1
+#pragma unroll
+      for (int r = q * 4 / kSpread; r < (q + 1) * 4 / kSpread; ++r)
+        if (q < kSpread) va[i + (r >> 1)][r & 1] = v_half(i + (r >> 1), r & 1);
+    };
+    // reads requested behind those of the pair of steps (s, s + 1), of a phase of n steps: `now` for a pair of this phase, `next` of the next
+    constexpr auto reads_between = [](int s, int n, int now, int next) {
+      int r = 0;
+      for (int t = s + 2; t < s + kAhead; t += 2) r += t < n ? now : next;
+      return r;
+    };
+    auto reads_row = [&](int q, int w) { return q == 2 * w * kSpread / 4; };  // the w-th of two row-major operands is read now
+    auto v_op = [&](int i) { return __builtin_shufflevector(va[i][0], va[i][1], 0, 1, 2, 3, 4, 5, 6, 7); };
     if (more1) {
 #pragma unroll
       for (int s = 0; s < kAhead; ++s) ka[s] = kcur[s];
     }
     __builtin_amdgcn_sched_barrier(0);
     // ---- S(u+1) | the rest of P(u), the copy of V(u+1), the first V operands
-    constexpr int LATE = 16 - kEarly;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const int i0 = kEarly + s * LATE / KS, i2 = kEarly + (s + 1) * LATE / KS, i1 = (i0 + i2) / 2;
-      if (more1 && s % 2 == 0) {  // this pair is there; newer: the next one
-        if (kAhead == 2) wait_lgkmcnt<0>();
-        else if (s + 2 < KS) wait_lgkmcnt<2>();
-        else wait_lgkmcnt<4>();
+    in_steps<2 * KS>([&](auto number) {
+      constexpr int j = decltype(number)::value, s = j >> 1, q = j & 3;
+      if (more1 && q == 0 && j < kEvery * NC) copy.aim(lds0 + (3 - par) * HALF, j / kEvery);
+      if (more1 && q == 0) {  // this pair of steps is there; newer: the next one
+        wait_lgkmcnt<reads_between(s, KS, 2, 4)>();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (more1) {
-        T[0] = mfma32(ka[s], qreg[0][s], s == 0 ? zero16 : T[0]);
-        if (s < KS - kAhead) {
-#pragma unroll
-          for (int e = s * NC / (KS - kAhead); e < (s + 1) * NC / (KS - kAhead); ++e)
-            copy.piece(vb, un[0], lds0 + (3 - par) * HALF, e);
-        }
-      }
-      p_items(S, i0, i1, ref);
-      if (s == KS - kAhead) {  // V(u) has landed; newer: K(u+2) and V(u+1)
-        if (more2) wait_vmcnt<2 * NC>();
-        else if (more1) wait_vmcnt<NC>();
+      if (more1) T[j & 1] = mfma32(ka[s], qreg[j & 1][s], s == 0 ? zero16 : T[j & 1]);
+      if (j == 2 * (KS - kAhead)) {  // V(u) has landed; newer: K(u+2) and a part of V(u+1)
+        if (more2) wait_vmcnt<NC + kPart>();
+        else if (more1) wait_vmcnt<kPart>();
         else wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
       }
+      if (more1 && j % kEvery == 0 && j < kEvery * NC) copy.piece(vb, un[0], lds0 + (3 - par) * HALF, j / kEvery, q == 0);
+      constexpr int to = s - s % 2 + kAhead;  // the two steps whose operands are requested now
+      if constexpr (to >= KS) {
+        read_v(to - KS, q);
+      } else if (more1) {
+        if (reads_row(q, 0)) ka[to] = TL::rowmajor_at(kn, lane_a, to);
+        if (reads_row(q, 1)) ka[to + 1] = TL::rowmajor_at(kn, lane_a, to + 1);
+      }
+      if (j == 3 && more3) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
+      p_stages(S, FwdStages<D>::before_s(j), FwdStages<D>::before_s(j + 1), ref);
       __builtin_amdgcn_sched_barrier(0);
-      if (more1) {
-        T[1] = mfma32(ka[s], qreg[1][s], s == 0 ? zero16 : T[1]);
-      }
-      if (s % 2 == 0) {
+      if (j == 2 * KS - 2) {
+        // The reference of a column stays as long as neither lane's sum of 16 values exceeds `limit`: then no value does, and
+        // the rescaling of O is skipped for almost every unit.  The result is exact either way, and a lane's arithmetic
+        // never depends on what other query columns (pad rows included) hold.
+        // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
+        float tsum[2] = {ta[0] + tb[0], ta[1] + tb[1]};
+        const bool rare = (!have & (valid != 0)) | (__any(fmaxf(tsum[0], tsum[1]) > limit) != 0);
+        if (__builtin_expect(rare, 0)) {
+          // (the last products that wrote O lie almost a whole S phase back, so it can be read at once)
 #pragma unroll
-        for (int j = s + kAhead; j < s + kAhead + 2; ++j) {
-          if (j >= KS) va[j - KS] = v_op(j - KS);
-          else if (more1) ka[j] = TL::rowmajor_at(kn, lane_a, j);
+          for (int b = 0; b < 2; ++b) {
+            const bool moves = !have || max_across_halves(tsum[b]) > limit;
+            if (!__any(moves)) continue;
+            const float old = have ? ref[b] : kNoRef, mnew = moves ? unit_max(S[b], valid, old) : old;
+            const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
+            lsum[b] *= alpha;
+#pragma unroll
+            for (int x = 0; x < DVB; ++x) {
+              pin_o(o[x][b]);  // (moved to ordinary registers from here on and not before the branch)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) o[x][b][i] *= alpha;
+              pin_o(o[x][b]);
+              __builtin_amdgcn_sched_barrier(0);  // (one block of O in ordinary registers at a time)
+            }
+            ref[b] = mnew;
+            // (no reference yet: -inf in every key, and nothing of the pad keys either)
+            const float use[2] = {ref[0] > kNoRef ? ref[0] : -kNoRef, ref[1] > kNoRef ? ref[1] : -kNoRef};
+#pragma unroll
+            for (int st = 0; st < 2; ++st)
+#pragma unroll
+              for (int w = 0; w < 4; ++w) {
+                const int it = 8 * st + 4 * b + w;
+                p_fma(S, it, use);
+                p_exp(it, 0);
+                p_exp(it, 1);
+                p_sum(it);
+              }
+            tsum[b] = ta[b] + tb[b];
+          }
+          have = true;
         }
+        lsum[0] += tsum[0];
+        lsum[1] += tsum[1];
+        __builtin_amdgcn_sched_barrier(0);
       }
-      p_items(S, i1, i2, ref);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     if (more1) {
-      if (un[0].valid != 0xffffffffu) add_bias(T, un[0].valid);
+      if (__builtin_expect(un[0].valid != 0xffffffffu, 0)) add_bias(T, un[0].valid);
     }
-    // The reference of a column stays as long as neither lane's sum of 16 values exceeds `limit`: then no value does, and
-    // the rescaling of O is skipped for almost every unit.  The result is exact either way, and a lane's arithmetic
-    // never depends on what other query columns (pad rows included) hold.
-    // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
-    if (__builtin_expect((!have && valid) || __any(fmaxf(tsum[0], tsum[1]) > limit), 0)) {
-      // (the last products that wrote O lie a whole S phase back, so it can be read at once)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const bool moves = !have || max_across_halves(tsum[b]) > limit;
-        if (!__any(moves)) continue;
-        const float old = have ? ref[b] : kNoRef, mnew = moves ? unit_max(S[b], valid, old) : old;
-        const float alpha = fast_exp2(old - mnew);  // (nothing accumulated yet: 0 times 0; unchanged: 1)
-        lsum[b] *= alpha;
-#pragma unroll
-        for (int x = 0; x < DVB; ++x) {
-          pin_o(o[x][b]);  // (moved to ordinary registers from here on and not before the branch)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) o[x][b][i] *= alpha;
-          pin_o(o[x][b]);
-          __builtin_amdgcn_sched_barrier(0);  // (one block of O in ordinary registers at a time)
-        }
-        ref[b] = mnew;
-        // (no reference yet: -inf in every key, and nothing of the pad keys either)
-        const float use[2] = {ref[0] > kNoRef ? ref[0] : -kNoRef, ref[1] > kNoRef ? ref[1] : -kNoRef};
-#pragma unroll
-        for (int st = 0; st < 2; ++st) p_items(S, 8 * st + 4 * b, 8 * st + 4 * b + 4, use);
-      }
-      have = true;
-    }
-    lsum[0] += tsum[0];
-    lsum[1] += tsum[1];
     // ---- PV(u) | the first of P(u+1), the copy of K(u+3), the first K operands of u+2
     const uint4 pc[2][2] = {{pb[0][0], pb[0][1]}, {pb[1][0], pb[1][1]}};
-    if (more3) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 1");  // (two wait states between the moves to pc and the first matrix instruction)
-#pragma unroll
-    for (int i = 0; i < NPV; ++i) {
-      const int i0 = i == 0 ? 0 : (i - 1) * kEarly / (NPV - 1), i2 = i * kEarly / (NPV - 1), i1 = (i0 + i2) / 2;
-      if (i % 2 == 0) {
-        if (kAhead == 2) wait_lgkmcnt<0>();
-        else if (i + 2 < NPV) wait_lgkmcnt<4>();
-        else wait_lgkmcnt<2>();
+    in_steps<2 * NPV>([&](auto number) {
+      constexpr int j = decltype(number)::value, i = j >> 1, q = j & 3;
+      if (more3 && q == 0 && j < kEvery * NC) copy.aim(lds0 + (1 - par) * HALF, j / kEvery);
+      if (q == 0) {
+        wait_lgkmcnt<reads_between(i, NPV, 4, 2)>();
         __builtin_amdgcn_sched_barrier(0);
       }
-      mfma_o(o[i % DVB][0], va[i], __builtin_bit_cast(bf16x8, pc[0][i / DVB]));
-      if (more3 && i < NPV - kAhead) {
-#pragma unroll
-        for (int e = i * NC / (NPV - kAhead); e < (i + 1) * NC / (NPV - kAhead); ++e)
-          copy.piece(kb, un[2], lds0 + (1 - par) * HALF, e);
-      }
-      if (more1) p_items(T, i0, i1, ref);
-      if (more1 && i == NPV - kAhead) {  // K(u+2) has landed; newer: V(u+1) and K(u+3)
-        if (more3) wait_vmcnt<2 * NC>();
+      mfma_o(o[i % DVB][j & 1], v_op(i), __builtin_bit_cast(bf16x8, pc[j & 1][i / DVB]));
+      if (more1 && j == 2 * (NPV - kAhead)) {  // K(u+2) has landed; newer: V(u+1) and a part of K(u+3)
+        if (more3) wait_vmcnt<NC + kPart>();
         else if (more2) wait_vmcnt<NC>();
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_o(o[i % DVB][1], va[i], __builtin_bit_cast(bf16x8, pc[1][i / DVB]));
-      if (i % 2 == 0) {
-#pragma unroll
-        for (int j = i + kAhead; j < i + kAhead + 2; ++j) {
-          if (j < NPV) va[j] = v_op(j);
-          else if (more1) kcur[j - NPV] = TL::rowmajor_at(smem + par * HALF, lane_a, j - NPV);  // (unused if u + 2 does not exist)
-        }
+      if (more3 && j % kEvery == 0 && j < kEvery * NC) copy.piece(kb, un[2], lds0 + (1 - par) * HALF, j / kEvery, q == 0);
+      constexpr int to = i - i % 2 + kAhead;
+      if constexpr (to < NPV) {
+        read_v(to, q);
+      } else if (more1) {  // (unused if u + 2 does not exist)
+        if (reads_row(q, 0)) kcur[to - NPV] = TL::rowmajor_at(smem + par * HALF, lane_a, to - NPV);
+        if (reads_row(q, 1)) kcur[to - NPV + 1] = TL::rowmajor_at(smem + par * HALF, lane_a, to - NPV + 1);
       }
-      if (more1) p_items(T, i1, i2, ref);
+      if (more1) p_stages(T, FwdStages<D>::before_pv(j), FwdStages<D>::before_pv(j + 1), ref);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     valid = un[0].valid;
     un[0] = un[1];
     un[1] = un[2];

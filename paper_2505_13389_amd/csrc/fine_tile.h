@@ -7,6 +7,9 @@
 //   - transposed reads (ds_read_b64_tr_b16: 4 consecutive rows x 64 contiguous bytes): the
 //     4 rows land in 4 different 64-byte groups of the 256-byte bank line.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "list_rules.h"
 #include "vsa_common.h"
 
@@ -41,6 +44,8 @@ __device__ __forceinline__ void lds_dma16_at(const void* base, unsigned voff) {
 __device__ __forceinline__ void set_m0(unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "m0", "memory");
 }
+// (with another instruction between it and the copies)
+__device__ __forceinline__ void set_m0_ahead(unsigned lds_addr) { asm volatile("s_mov_b32 m0, %0" : : "s"(lds_addr) : "m0", "memory"); }
 // (NOPS 4: for a base that the compiler may fetch from a vector register right before, which takes 5 wait states)
 template <int NOPS = 0>
 __device__ __forceinline__ void lds_dma4(const void* base, unsigned voff, unsigned lds_addr) {
@@ -67,6 +72,14 @@ template <int N>
 __device__ __forceinline__ void wait_lgkmcnt() {
   __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
 }
+
+// f(0), f(1), ..., f(N - 1), each with its number as a constant
+template <class F, int... M>
+__device__ __forceinline__ void in_steps_of(const F& f, std::integer_sequence<int, M...>) {
+  (f(std::integral_constant<int, M>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void in_steps(const F& f) { in_steps_of(f, std::make_integer_sequence<int, N>{}); }
 
 template <int D>
 struct Tile {
@@ -104,10 +117,12 @@ struct Tile {
     b0 = off(r1, col >> 3) + (col & 7) * 2;
     b1 = off(r1 + 8, col >> 3) + (col & 7) * 2;
   }
-  __device__ static __forceinline__ bf16x8 transposed_at(const unsigned char* tile, int b0, int b1, int s, int x) {
+  __device__ static __forceinline__ bf16x4 transposed_half(const unsigned char* tile, int b, int s, int x) {  // b: b0 or b1
     const unsigned char* p = tile + s * 16 * ROW_BYTES;
-    bf16x4 a0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + (b0 ^ (x << 6))));
-    bf16x4 a1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + (b1 ^ (x << 6))));
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + (b ^ (x << 6))));
+  }
+  __device__ static __forceinline__ bf16x8 transposed_at(const unsigned char* tile, int b0, int b1, int s, int x) {
+    const bf16x4 a0 = transposed_half(tile, b0, s, x), a1 = transposed_half(tile, b1, s, x);
     return __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
   }
 };

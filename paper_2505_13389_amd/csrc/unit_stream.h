@@ -61,7 +61,7 @@ struct CubeUnits {
     u.b = u.a + TL::BYTES / 4;
   }
   __device__ __forceinline__ void get(int t, int half, Unit& u) {
-    if (!loaded(t)) {
+    if (__builtin_expect(!loaded(t), 0)) {
       load_indices(t / kTilesPerChunk);
       set_masks(mask[mask_block()]);
       asm volatile("" : "+v"(km_v[0]), "+v"(km_v[1]));
@@ -113,7 +113,7 @@ struct SubCubeUnits {
     u.b = entry_offset(4 * t + 2 * half + 1);
   }
   __device__ __forceinline__ void get(int t, int half, Unit& u) {
-    if (!loaded(t)) {
+    if (__builtin_expect(!loaded(t), 0)) {
       load_indices(t / kTilesPerChunk);
       set_masks(mask[mask_block()]);
       asm volatile("" : "+v"(km_v));
@@ -174,10 +174,14 @@ struct UnitCopy {
     }
   }
   // instruction c (a constant after unrolling); `base` = first row of the (b, h), `lds` = the stage's address
-  __device__ __forceinline__ void piece(const unsigned char* base, const Unit& u, unsigned lds, int c) const {
+  // (`aimed`: aim(lds, c) and another instruction came before it)
+  __device__ __forceinline__ void aim(unsigned lds, int c) const {
+    if (c % GROUP == 0) set_m0_ahead(lds + (unsigned)(c / GROUP) * (16u * TL::ROW_BYTES));
+  }
+  __device__ __forceinline__ void piece(const unsigned char* base, const Unit& u, unsigned lds, int c, bool aimed = false) const {
     const void* g = base + (UNITS::kContiguous || c < GROUP ? u.a : u.b);
     const int r = c % GROUP, o = UNITS::kContiguous ? c : r;
-    if (r == 0) set_m0(lds + (unsigned)(c / GROUP) * (16u * TL::ROW_BYTES));
+    if (r == 0 && !aimed) set_m0(lds + (unsigned)(c / GROUP) * (16u * TL::ROW_BYTES));
     if (r == 0) lds_dma16_at<0>(g, off[o]);
     if (r == 1) lds_dma16_at<1024>(g, off[o]);
     if (r == 2) lds_dma16_at<2048>(g, off[o]);

@@ -24,9 +24,10 @@ namespace vsa {
 // matrix instruction reads an operand from either file).  d = 64: two wavefronts per SIMD, whose 256 registers do not
 // hold both halves' S and dP: there S 1 follows dP 0, and -Delta is added in vector arithmetic.
 //
-// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 205 others, all issued by one
-// wavefront; at 1.74 GHz the pipe is busy 67 % of the time, an instruction is issued in 57 % of it and 15 % are spent
-// in waits.  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12
+// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 200 others, all issued by one
+// wavefront, in 1930 cycles (d = 128; 2160 with the copies in two runs, one behind every matrix instruction of dP 1 and dQ 0, two
+// transposing reads behind one and items of P whose instructions waited for one another: costs of instructions in fine_fwd.hip),
+// at a clock that falls as the pipe fills (1.6 to 1.75 GHz at 39936 tokens).  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12
 // heads, d = 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of
 // the time.
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
@@ -56,6 +57,7 @@ __device__ __forceinline__ void dq_block(
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int G = KS;                 // matrix instructions of a group
   constexpr int OS = D;
+  constexpr int kEvery = D == 128 ? 2 : 1;  // a copy of K behind every other, or every, matrix instruction of the dQ groups
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
   static_assert(G == 2 * DVB && G == NC && G % 4 == 0, "phase interleave: one copy instruction per matrix instruction");
   static_assert(!COARSE || 64 * NW == kSmallThreads, "the coarse backward takes 256 threads");
@@ -225,6 +227,7 @@ __device__ __forceinline__ void dq_block(
     bf16x8 va[KS], kt[2 * DVB];
     f32x16 S[2], P[2];  // S^T and then P^T; dP^T
     uint4 ds[2][2];     // dS^T as operands: [query half][contraction step]
+    float xf[2][2], xd[2][2];
     auto put = [](uint4& u4, int w, uint32_t x) {
       if (w == 0) u4.x = x;
       if (w == 1) u4.y = x;
@@ -251,9 +254,46 @@ __device__ __forceinline__ void dq_block(
         asm volatile("" : : "v"(x));
       }
     };
+    // d = 128: the same in stages, dealt to the matrix instructions so that no result is used by the next instruction (see p_stages in
+    // fine_fwd.hip).  P: stage 0 the fma's of item 0 of 16, both halves'; 2g + 1 the first exponential of item g and the fma's of the
+    // next; 2g + 2 its second.  dS of half b: stage k the products of item k and the conversion of the item before.
+    auto p_stages = [&](int from, int to) {
+#pragma unroll
+      for (int n = from; n < to; ++n) {
+        const int g = (n - 1) >> 1, next = n == 0 ? 0 : g + 1;
+        if (n > 0) {
+          float x = fast_exp2(xf[g & 1][(n - 1) & 1]);
+          asm volatile("" : : "v"(x));
+          S[g >> 3][2 * (g & 7) + ((n - 1) & 1)] = x;
+        }
+        if ((n == 0 || n % 2 == 1) && next < 16) {
+          const int b = next >> 3, i = 2 * (next & 7);
+          float (&f)[2] = xf[next & 1];
+          f[0] = fmaf(S[b][i], sl2, crow[b]);
+          f[1] = fmaf(S[b][i + 1], sl2, crow[b]);
+          asm volatile("" : : "v"(f[0]), "v"(f[1]));
+        }
+      }
+    };
+    auto d_stages = [&](int b, int from, int to) {
+#pragma unroll
+      for (int k = from; k < to; ++k) {
+        if (k > 0) {
+          const uint32_t x = pack_bf16(xd[(k - 1) & 1][0], xd[(k - 1) & 1][1]);
+          put(ds[b][(k - 1) >> 2], (k - 1) & 3, x);
+          asm volatile("" : : "v"(x));
+        }
+        if (k < 8) {
+          float (&f)[2] = xd[k & 1];
+          f[0] = S[b][2 * k] * P[b][2 * k];
+          f[1] = S[b][2 * k + 1] * P[b][2 * k + 1];
+          asm volatile("" : : "v"(f[0]), "v"(f[1]));
+        }
+      }
+    };
     // pad keys never take part: one extra matrix step adds a large negative bias to their rows of S^T
     auto bias = [&](int b) {
-      if (un[0].valid != 0xffffffffu) {
+      if (__builtin_expect(un[0].valid != 0xffffffffu, 0)) {
         int ln = threadIdx.x & 63;
         asm volatile("" : "+v"(ln));  // (built here, not held in registers across the loop)
         const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -271,9 +311,10 @@ __device__ __forceinline__ void dq_block(
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         if (b == 0 && m == 0) wait_lgkmcnt<G / 2>();      // the first half of the K operands; newer: the second
-        if (b == 0 && m == G / 2) wait_lgkmcnt<G / 2>();  // the second half; newer: the V operands read so far
+        if (b == 0 && m == G / 2) wait_lgkmcnt<D == 128 ? G / 2 + G / 4 : G / 2>();  // the second half; newer: the V, and K^T, operands read so far
         S[b] = mfma32(ka[m], qreg[b][m], m == 0 ? zero16 : S[b]);
         if (b == 0) va[m] = TL::rowmajor_at(vc, lane_a, m);
+        if (b == 0 && D == 128 && m % 2 == 1) kt[m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, m / 2 / DVB, m / 2 % DVB);
         with(m);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -284,22 +325,27 @@ __device__ __forceinline__ void dq_block(
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         P[b] = mfma32(va[m], doreg[b][m], m == 0 ? dinit[b] : P[b]);
-        if (b == 0) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
-        if (b == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);  // (V(u) is in registers)
+        if (b == 0 && D == 64) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
+        if (b == 0 && D == 128 && m % 2 == 0) kt[G / 2 + m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, 1, m / 2);
+        // the copy of V(u+2) (V(u) is in registers): d = 128 behind every other matrix instruction of both halves
+        if (D == 128 && m % 2 == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, b * (G / 2) + m / 2);
+        if (D == 64 && b == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);
         with(m);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     if constexpr (D == 128) {
       s_group(0, [&](int) {});
-      s_group(1, [&](int m) { p_items(0, share(6, m, 1, G), share(6, m + 1, 1, G)); });
-      d_group(0, [&](int m) {
-        p_items(0, 6 + share(2, m, 0, G / 4), 6 + share(2, m + 1, 0, G / 4));
-        p_items(1, share(4, m, G / 4, G), share(4, m + 1, G / 4, G));
-      });
+      // stages of P that precede step m of S 1, dP 0, dP 1 (S 0 can be read two steps into S 1, S 1 two steps into dP 0)
+      auto upto = [](int group, int m) {
+        constexpr int n[3][9] = {{0, 0, 1, 3, 5, 7, 9, 11, 13}, {13, 14, 16, 17, 19, 20, 22, 23, 25}, {25, 27, 29, 31, 33, 33, 33, 33, 33}};
+        return n[group][m];
+      };
+      s_group(1, [&](int m) { p_stages(upto(0, m), upto(0, m + 1)); });
+      d_group(0, [&](int m) { p_stages(upto(1, m), upto(1, m + 1)); });
       d_group(1, [&](int m) {
-        p_items(1, 4 + share(4, m, 0, G / 2), 4 + share(4, m + 1, 0, G / 2));
-        d_items(0, share(4, m, G / 2, G), share(4, m + 1, G / 2, G));
+        p_stages(upto(2, m), upto(2, m + 1));
+        d_stages(0, m < 4 ? 0 : m - 4, m < 4 ? 0 : m == 7 ? 5 : m - 3);
       });
     } else {  // one half after the other: fewer registers, and another wavefront fills the gaps
       s_group(0, [&](int) {});
@@ -313,15 +359,21 @@ __device__ __forceinline__ void dq_block(
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < G; ++m) {
+      if (more2 && m % kEvery == 0) copy.aim(lds0 + par * HALF, m / kEvery);
       mfma_acc(acc[m % DVB][0], kt[m], __builtin_bit_cast(bf16x8, ds[0][m / DVB]));
-      if (more2) copy.piece(kb, un[2], lds0 + par * HALF, m);
-      d_items(0, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
-      d_items(1, share(4, m, DVB - 1, G), share(4, m + 1, DVB - 1, G));
+      if (more2 && m % kEvery == 0) copy.piece(kb, un[2], lds0 + par * HALF, m / kEvery, true);
+      if constexpr (D == 128) {
+        if (m < 3) d_stages(0, 5 + m, m == 2 ? 9 : 6 + m);
+        if (m >= 3) d_stages(1, m - 3, m - 2);
+      } else {
+        d_items(0, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+        d_items(1, share(4, m, DVB - 1, G), share(4, m + 1, DVB - 1, G));
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     // ---- dQ of half 1 | the rest of its dS, the K operands of the next unit
     if (more1) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2)
-      if (more2) wait_vmcnt<2 * NC>();
+      if (more2) wait_vmcnt<NC + NC / kEvery>();
       else wait_vmcnt<0>();
     }
     asm volatile("s_nop 1");
@@ -330,8 +382,14 @@ __device__ __forceinline__ void dq_block(
     for (int m = 0; m < G; ++m) {
       // (behind the last unit no operand reads lie between the last item of step 1 and the matrix instruction that reads it)
       if (!more1 && m == DVB) asm volatile("s_nop 1");
+      if (more2 && kEvery == 2 && m % 2 == 0) copy.aim(lds0 + par * HALF, (G + m) / 2);
       mfma_acc(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
-      d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+      if (more2 && kEvery == 2 && m % 2 == 0) copy.piece(kb, un[2], lds0 + par * HALF, (G + m) / 2, true);
+      if constexpr (D == 128) {
+        if (m < 3) d_stages(1, 5 + m, m == 2 ? 9 : 6 + m);
+      } else {
+        d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+      }
       if (more1) ka[m] = TL::rowmajor_at(smem + (1 - par) * HALF, lane_a, m);
       __builtin_amdgcn_sched_barrier(0);
     }

@@ -129,7 +129,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   const int nu = n > first ? (n - first + EPR - 1) / EPR : 0;
   auto entry = [&](int u) {  // list entry of unit u (ascending u)
     const int e = first + EPR * u;
-    if ((e >> 6) != chunk) {
+    if (__builtin_expect((e >> 6) != chunk, 0)) {
       chunk = e >> 6;
       col_v = my_col[list_slot(chunk, lane, n)];
       asm volatile("" : "+v"(col_v));  // its wait stays inside this branch

@@ -321,11 +321,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     float (&f)[2] = xf[it & 1];
     f[0] = fmaf(S[b][e], sl2, -rf[b]);
     f[1] = fmaf(S[b][e + 1], sl2, -rf[b]);
-    asm volatile("" : "+v"(f[0]), "+v"(f[1]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+    asm volatile("" : : "v"(f[0]), "v"(f[1]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
   };
   auto p_exp = [&](int it, int i) {
     xe[it & 1][i] = fast_exp2(xf[it & 1][i]);
-    asm volatile("" : "+v"(xe[it & 1][i]));
+    asm volatile("" : : "v"(xe[it & 1][i]));
   };
   auto p_sum = [&](int it) {
     const int b = (it >> 2) & 1;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     ta[b] = (it & 11) == 0 ? x0 : ta[b] + x0;
     tb[b] = (it & 11) == 0 ? x1 : tb[b] + x1;
     put(pb[b][it >> 3], it & 3, pp);
-    asm volatile("" : "+v"(ta[b]), "+v"(tb[b]) : "v"(pp));
+    asm volatile("" : : "v"(ta[b]), "v"(tb[b]), "v"(pp));
   };
   auto p_stages = [&](const f32x16 (&S)[2], int from, int to, const float* rf) {
 #pragma unroll

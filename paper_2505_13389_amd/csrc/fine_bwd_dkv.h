@@ -35,8 +35,8 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // The order inside a unit is the dependency order, S | dP | dV | dK: P is formed while dP is multiplied,
 // dS while dV is, so the vector work hides behind matrix work without a second set of registers.  Each
 // phase is a run of STEPS, pinned by scheduling barriers: one step = one LDS operand multiplied with both
-// key halves (two matrix instructions, 64 cycles), the operand reads of the step kAhead later, and a
-// share of the copies and of the vector work.
+// key halves (two matrix instructions, 64 cycles), the operand reads of the step kAhead later, and behind either
+// instruction a share of the copies and of the vector work (DkvStages).
 // The row terms enter through the accumulators' initial value: the preprocess kernel stores -lse*log2e/sl2
 // (then P = exp2(S' * sl2); -30000 on pad rows, whose P underflows to 0) and -Delta per row, and a lane
 // reads those of its 16 rows straight into the first matrix instruction's C operand.  Pad KEY rows need
@@ -48,10 +48,12 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // instruction per key half subtracts a large number from S of the other keys.  The pooled-gradient terms
 // are per key cube.
 //
-// What bounds it: the matrix pipe is busy 69 % of the time at 1.6 GHz (power: the clock falls as the pipe
-// fills: 12 % fewer instructions, by addresses held in registers and one wait per two steps, 391 -> 346 per 64 matrix
-// instructions, gave 2 %); 3 us of start-up and 5 us of merge and stores per
-// workgroup, which the other workgroup of the CU overlaps.  Before (32 keys x 32 queries per wavefront, 4
+// What bounds it: the clock, which falls as the matrix pipe fills (1.6 to 1.75 GHz at 39936 tokens), and the instructions of one
+// wavefront: a unit is 64 matrix instructions (2048 cycles of the pipe) and 280 others, in 2400 cycles at d = 128 (2590 with the
+// operand reads of two steps behind one matrix instruction, a wait for all of them two steps later and items whose instructions
+// waited for one another; costs of instructions in fine_fwd.hip), 32 and 240 in 1480 at d = 64 (1640 so); 3 us of start-up and 5 us of
+// merge and stores per workgroup, which the other workgroup of the CU overlaps.  d = 64 with two wavefronts per SIMD (256 registers
+// each, four to a workgroup; K and V in LDS) took 1700.  Before (32 keys x 32 queries per wavefront, 4
 // wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
 // 12 heads, d = 128, top-78 of 624: 2.68 -> 1.97 ms (1.22 PFLOP/s executed); 16384 tokens, top-32: 529 -> 370
 // us; d = 64, B = 2, 8 heads, top-32: 485 -> 288 us.  Four wavefronts (one workgroup
@@ -63,6 +65,28 @@ struct DkvShape {
   static constexpr int NST = D == 128 ? 2 : 4;       // stages per wavefront
   static constexpr int LDS = HALF + NW * NST * STAGE;
 };
+// What lies behind which matrix instruction of a unit: the P stages ahead of instruction j of the dP phase and, behind those, of the dV
+// phase; the dS stages ahead of instruction j of the dV and dK phases; the copy of dO_f rows behind instruction j of the dK phase (-1: none).
+template <int D>
+struct DkvStages {
+  static constexpr int p_at(int j) {
+    constexpr int wide[32] = {1, 1, 2, 1, 2, 2, 1, 2, 1, 2, 1, 2, 1, 2, 1, 2, 2, 2, 2, 2, 1, 1}, narrow[16] = {3, 3, 3, 3, 3, 3, 3, 3, 4, 3, 3};
+    return D == 128 ? wide[j] : narrow[j];
+  }
+  static constexpr int s_at(int j) {
+    constexpr int wide[32] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, narrow[16] = {0, 0, 0, 2, 2, 2, 2, 2, 3, 2, 2};
+    return D == 128 ? wide[j] : narrow[j];
+  }
+  static constexpr int p(int j) { return j == 0 ? 0 : p(j - 1) + p_at(j - 1); }
+  static constexpr int s(int j) { return j == 0 ? 0 : s(j - 1) + s_at(j - 1); }
+  static constexpr int copy(int j) {
+    constexpr int wide[16] = {-1, 0, -1, 1, -1, 2, -1, 3, 4, 5, 6, 7, -1, -1, -1, -1}, narrow[8] = {0, 1, 2, 3, -1, -1, -1, -1};
+    return D == 128 ? wide[j] : narrow[j];
+  }
+};
+// P of contraction step 0 (18 stages and its last conversion) ahead of dV, all of it ahead of step 1; dS likewise in dK
+static_assert(DkvStages<128>::p(16) > 18 && DkvStages<128>::p(23) == 34 && DkvStages<128>::s(16) > 8 && DkvStages<128>::s(23) == 17, "d = 128");
+static_assert(DkvStages<64>::p(8) > 18 && DkvStages<64>::p(11) == 34 && DkvStages<64>::s(8) > 8 && DkvStages<64>::s(11) == 17, "d = 64");
 // What the coarse backward of a short sequence is formed from (see coarse_small.h).
 struct SmallCoarseArgs {
   const float *qc, *kc, *vc, *doc, *lse_c, *dot;
@@ -96,11 +120,11 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   constexpr int EPR = NW / 2;              // list entries a round of units takes
   constexpr int HALF = SH::HALF, STAGE = SH::STAGE, NST = SH::NST;
   constexpr int NC = HALF / 1024;          // copy instructions per 32 rows
-  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use: a pair of steps reads for the next pair
+  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use
   constexpr int NCD = 2 * DVB;             // steps of the dV and of the dK phase
   constexpr int OS = D;
   static_assert(HALF % 256 == 0 && STAGE % 256 == 0, "the operand addresses XOR the bits below 256");
-  static_assert(KS == NCD && NC <= 2 * DVB && 8 % NC == 0, "phase interleave");
+  static_assert(KS == NCD && NC == KS && kAhead == 2, "phase interleave");
   static_assert(!COARSE || (NT == kSmallThreads && !SUB), "the coarse backward takes 256 threads");
 
   // Start-up: one descriptor load (key block, begin and end of its run of the block's list, slot; the
@@ -154,9 +178,12 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
   const unsigned wbase = lds0 + HALF + (unsigned)wave * (NST * STAGE);
-  auto copy_piece = [&](const void* g, unsigned lds, int c) {  // copy c of 32 rows; `g`, `lds` uniform
+  auto copy_aim = [&](unsigned lds, int c) {  // (another instruction between it and copy_piece)
+    if ((c & 3) == 0) set_m0_ahead(lds + (c >> 2) * 4096);
+  };
+  auto copy_piece = [&](const void* g, unsigned lds, int c, bool aimed = false) {  // copy c of 32 rows; `g`, `lds` uniform
     const void* gb = (const unsigned char*)g + (c >> 2) * 4096;
-    if ((c & 3) == 0) set_m0(lds + (c >> 2) * 4096);
+    if ((c & 3) == 0 && !aimed) set_m0(lds + (c >> 2) * 4096);
     const int r = c & 3;
     if (r == 0) lds_dma16_at<0>(gb, goff[0]);
     if (r == 1) lds_dma16_at<1024>(gb, goff[1 % NOFF]);
@@ -262,9 +289,9 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   bf16x8 qcur[kAhead];  // Q operands of a unit's first steps, read during the unit before
   f32x16 sinit;
   if (nu > 0) {
+    sinit = row_init(0, 0);
 #pragma unroll
     for (int s = 0; s < kAhead; ++s) qcur[s] = TL::rowmajor_at(smem, lane_q, s);
-    sinit = row_init(0, 0);
   }
 
   // One unit, whose rows lie in the wavefront's stage `st` (a constant in the unrolled loop).
@@ -280,43 +307,36 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     const unsigned char* Qs = smem + st_off;
     const unsigned char* Ds = smem + st_off + HALF;
     const unsigned char* Qn = smem + next_st;
-    bf16x8 qa[KS], da[KS], va[KS], dt[NCD], qt[NCD];
+    bf16x8 qa[KS], da[KS], va[KS];
+    bf16x4 dt[NCD][2], qt[NCD][2];
     f32x16 dpinit;
 #pragma unroll
     for (int s = 0; s < kAhead; ++s) qa[s] = qcur[s];
-    // operand reads of step m: S steps, dP steps, dV steps, dK steps, then the S steps of the next unit
-    auto read_step = [&](int m) {
+    // operand reads of step m: S steps, dP steps, dV steps, dK steps, then the S steps of the next unit; `part` 0, 1: behind the
+    // first or the second matrix instruction of a step.  Row terms come with the first operands of their phase.
+    auto read_part = [&](int m, int part) {
       if (m < KS) {
-        qa[m] = TL::rowmajor_at(Qs, lq, m);
+        if (part == 0) qa[m] = TL::rowmajor_at(Qs, lq, m);
       } else if (m < 2 * KS) {
         const int s = m - KS;
-        if (s == 0) dpinit = row_init(st_off, 1);
-        da[s] = TL::rowmajor_at(Ds, lq, s);
-        va[s] = TL::rowmajor_at(smem, lv, s);
-      } else if (m < 2 * KS + NCD) {
-        const int c = m - 2 * KS;
-        dt[c] = TL::transposed_at(Ds, lb0, lb1, c / DVB, c % DVB);
+        if (s == 0 && part == 0) dpinit = row_init(st_off, 1);
+        if (part == 0) da[s] = TL::rowmajor_at(Ds, lq, s);
+        if (part == 1) va[s] = TL::rowmajor_at(smem, lv, s);
       } else if (m < 2 * KS + 2 * NCD) {
-        const int c = m - 2 * KS - NCD;
-        qt[c] = TL::transposed_at(Qs, lb0, lb1, c / DVB, c % DVB);
-      } else {
+        const bool of_dv = m < 2 * KS + NCD;
+        const int c = m - 2 * KS - (of_dv ? 0 : NCD);
+        (of_dv ? dt : qt)[c][part] = TL::transposed_half(of_dv ? Ds : Qs, part ? lb1 : lb0, c / DVB, c % DVB);
+      } else if (part == 0) {
         const int s = m - 2 * KS - 2 * NCD;
         if (s == 0) sinit = row_init(next_st, 0);
         qcur[s] = TL::rowmajor_at(Qn, lq, s);
       }
     };
-    // at the first step of a pair: its operands are there; those of the next pair are requested
-    auto pair_begins = [&](int m) {
-      if (m % 2 == 0) {
-        wait_lgkmcnt<0>();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    auto pair_reads = [&](int m) {
-      if (m % 2 == 0) {
-        read_step(m + kAhead);
-        read_step(m + kAhead + 1);
-      }
+    auto both = [](const bf16x4 (&x)[2]) { return __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7); };
+    // at the first matrix instruction of step m: its operands, requested two steps before, are there; newer: those of the next
+    constexpr auto reads_in = [](int m) {  // reads requested in step m
+      const int steps = 2 * KS + 2 * NCD, to = (m + 2 + steps) % steps;
+      return (to < KS ? 1 : 2) + (to == 0 || to == KS ? 4 : 0);
     };
     // ---- S
     f32x16 s0, s1, p0, p1;
@@ -328,22 +348,22 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       bias1[0] = (h == 0 && !(sel & 4u)) ? (__bf16)-30000.f : (__bf16)0.f;
     }
     const unsigned char* gq = qw + next_off;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      pair_begins(s);
+    in_steps<KS>([&](auto number) {
+      constexpr int s = decltype(number)::value;
+      wait_lgkmcnt<reads_in(s - 1)>();
+      __builtin_amdgcn_sched_barrier(0);
+      if (more_q) copy_aim(wbase + prev_st, s);
       if (s == 0) mfma_v_from(s0, qa[0], kreg[0][0], sinit);
       else mfma_v(s0, qa[s], kreg[0][s]);
-      if (more_q) {
-#pragma unroll
-        for (int c = s * NC / KS; c < (s + 1) * NC / KS; ++c) copy_piece(gq, wbase + prev_st, c);
-        if (s == KS - 1) copy_rows(next_off, wbase + prev_st + 2 * HALF);
-      }
+      if (more_q) copy_piece(gq, wbase + prev_st, s, true);
+      read_part(s + 2, 0);
       __builtin_amdgcn_sched_barrier(0);
       if (s == 0) s1 = sinit;
       mfma_v(s1, qa[s], kreg[1][s]);
-      pair_reads(s);
+      if (s == KS - 1 && more_q) copy_rows(next_off, wbase + prev_st + 2 * HALF);
+      read_part(s + 2, 1);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     if (SUB) {
       asm volatile("s_nop 1");  // (two wait states between the moves to the bias operands and the matrix instruction)
       mfma_v(s0, ones_a, bias0);
@@ -351,7 +371,10 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       __builtin_amdgcn_sched_barrier(0);
     }
     // ---- dP, with P = exp2(S' sl2) of both key halves behind it.  Item k of 16: one pair of values, first
-    // those of contraction step 0 of the dV products (accumulator values 0..7), then those of step 1.
+    // those of contraction step 0 of the dV products (accumulator values 0..7), then those of step 1.  The items go through
+    // stages whose neighbours do not depend on one another (see fine_fwd.hip), dealt to the matrix instructions.  P: stage 0 the products of
+    // item 0; 2g + 1 the first exponential of item g and the products of the next; 2g + 2 its second, and the conversion of the
+    // item before; 33 that of the last.  dS: stage k the products of item k and the conversion of the item before.
     uint4 pb[2][2], sb[2][2];
     auto put = [](uint4& u4, int w, uint32_t x) {
       if (w == 0) u4.x = x;
@@ -359,68 +382,97 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       if (w == 2) u4.z = x;
       if (w == 3) u4.w = x;
     };
-    auto p_item = [&](int it) {
-      const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
-      f32x16& S = b ? s1 : s0;
-      S[e] = fast_exp2(S[e] * sl2);
-      S[e + 1] = fast_exp2(S[e + 1] * sl2);
-      const uint32_t pp = pack_bf16(S[e], S[e + 1]);
-      put(pb[b][st], w, pp);
-      asm volatile("" : : "v"(pp));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+    float xp[2][2], xd[2][2];  // products of an item, by its parity
+    auto first_of = [](int it) { return 8 * (it >> 3) + 2 * (it & 3); };
+    auto p_multiply = [&](int it) {
+      const f32x16& S = (it >> 2) & 1 ? s1 : s0;
+      const int e = first_of(it);
+      xp[it & 1][0] = S[e] * sl2;
+      xp[it & 1][1] = S[e + 1] * sl2;
+      asm volatile("" : : "v"(xp[it & 1][0]), "v"(xp[it & 1][1]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
     };
-    auto s_item = [&](int it) {
-      const int st = it >> 3, b = (it >> 2) & 1, w = it & 3, e = 8 * st + 2 * w;
-      const f32x16& S = b ? s1 : s0;
-      const f32x16& P = b ? p1 : p0;
-      const uint32_t ss = pack_bf16(S[e] * P[e], S[e + 1] * P[e + 1]);
-      put(sb[b][st], w, ss);
-      asm volatile("" : : "v"(ss));
+    auto p_exp = [&](int it, int i) {
+      f32x16& S = (it >> 2) & 1 ? s1 : s0;
+      const float x = fast_exp2(xp[it & 1][i]);
+      asm volatile("" : : "v"(x));
+      S[first_of(it) + i] = x;
     };
-    constexpr int P_DP = 10;  // P items behind the dP steps 1 .. KS-2, the rest behind the first dV steps
-    auto p_items = [&](int from, int to) {
+    auto p_convert = [&](int it) {
+      const f32x16& S = (it >> 2) & 1 ? s1 : s0;
+      const uint32_t pp = pack_bf16(S[first_of(it)], S[first_of(it) + 1]);
+      put(pb[(it >> 2) & 1][it >> 3], it & 3, pp);
+      asm volatile("" : : "v"(pp));
+    };
+    auto p_stages = [&](int from, int to) {
 #pragma unroll
-      for (int it = from; it < to; ++it) p_item(it);
+      for (int n = from; n < to; ++n) {
+        const int g = (n - 1) >> 1;
+        if (n == 0) p_multiply(0);
+        else if (n == 33) p_convert(15);
+        else p_exp(g, (n - 1) & 1);
+        if (n > 0 && n < 33) {
+          if (n & 1) {
+            if (g < 15) p_multiply(g + 1);
+          } else if (g > 0) {
+            p_convert(g - 1);
+          }
+        }
+      }
     };
-    auto s_items = [&](int from, int to) {
+    auto s_stages = [&](int from, int to) {
 #pragma unroll
-      for (int it = from; it < to; ++it) s_item(it);
+      for (int k = from; k < to; ++k) {
+        if (k > 0) {
+          const int it = k - 1;
+          const uint32_t ss = pack_bf16(xd[it & 1][0], xd[it & 1][1]);
+          put(sb[(it >> 2) & 1][it >> 3], it & 3, ss);
+          asm volatile("" : : "v"(ss));
+        }
+        if (k < 16) {
+          const f32x16& S = (k >> 2) & 1 ? s1 : s0;
+          const f32x16& P = (k >> 2) & 1 ? p1 : p0;
+          const int e = first_of(k);
+          xd[k & 1][0] = S[e] * P[e];
+          xd[k & 1][1] = S[e + 1] * P[e + 1];
+          asm volatile("" : : "v"(xd[k & 1][0]), "v"(xd[k & 1][1]));
+        }
+      }
     };
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const bool on = s >= 1 && s <= KS - 2;
-      const int i0 = (s - 1) * P_DP / (KS - 2), i2 = s * P_DP / (KS - 2), i1 = (i0 + i2) / 2;
-      pair_begins(KS + s);
+    using DS = DkvStages<D>;
+    in_steps<KS>([&](auto number) {
+      constexpr int s = decltype(number)::value, m = KS + s;
+      wait_lgkmcnt<reads_in(m - 1)>();
+      __builtin_amdgcn_sched_barrier(0);
       if (s == 0) mfma_v_from(p0, da[0], vreg[0], dpinit);
       else mfma_v(p0, da[s], vreg[s]);
-      pair_reads(KS + s);
-      if (on) p_items(i0, i1);
+      read_part(m + 2, 0);
+      p_stages(DS::p(2 * s), DS::p(2 * s + 1));
       __builtin_amdgcn_sched_barrier(0);
       if (s == 0) p1 = dpinit;
       mfma_v(p1, da[s], va[s]);
-      if (on) p_items(i1, i2);
+      read_part(m + 2, 1);
+      p_stages(DS::p(2 * s + 1), DS::p(2 * s + 2));
       __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- dV, contraction step 0 first; the remaining P items have to be done one step before step 1 begins,
-    // the dS items of step 0 one step before the dK phase begins
+    });
+    // ---- dV, contraction step 0 first; the remaining P items have to be done before step 1 begins, the dS items of
+    // step 0 before the dK phase begins
     auto opnd = [](const uint4& x) { return __builtin_bit_cast(bf16x8, x); };
-    constexpr int S_DV = DVB == 4 ? 10 : 8;  // dS items behind the dV steps DVB-1 .. NCD-1, the rest behind the first dK steps
-#pragma unroll
-    for (int c = 0; c < NCD; ++c) {
-      const bool pv_on = c < DVB - 1, ds_on = c >= DVB - 1;
-      const int i0 = P_DP + c * (16 - P_DP) / (DVB - 1), i2 = P_DP + (c + 1) * (16 - P_DP) / (DVB - 1), i1 = (i0 + i2) / 2;
-      // (those of step 0 are the first eight: done one step before the end)
-      const int e0 = (c - DVB + 1) * 8 / DVB, e2 = c == NCD - 1 ? S_DV : (c - DVB + 2) * 8 / DVB, e1 = (e0 + e2) / 2;
-      pair_begins(2 * KS + c);
-      mfma_a(dva[c % DVB][0], dt[c], opnd(pb[0][c / DVB]));
-      if (pv_on) p_items(i0, i1);
-      if (ds_on) s_items(e0, e1);
-      pair_reads(2 * KS + c);
+    constexpr int SLOTS = 2 * NCD;  // matrix instructions of a phase
+    in_steps<NCD>([&](auto number) {
+      constexpr int c = decltype(number)::value, m = 2 * KS + c, j = 2 * c;
+      wait_lgkmcnt<reads_in(m - 1)>();
       __builtin_amdgcn_sched_barrier(0);
-      mfma_a(dva[c % DVB][1], dt[c], opnd(pb[1][c / DVB]));
-      if (pv_on) p_items(i1, i2);
-      if (ds_on) s_items(e1, e2);
+      mfma_a(dva[c % DVB][0], both(dt[c]), opnd(pb[0][c / DVB]));
+      read_part(m + 2, 0);
+      p_stages(DS::p(SLOTS + j), DS::p(SLOTS + j + 1));
+      s_stages(DS::s(j), DS::s(j + 1));
       __builtin_amdgcn_sched_barrier(0);
-    }
+      mfma_a(dva[c % DVB][1], both(dt[c]), opnd(pb[1][c / DVB]));
+      read_part(m + 2, 1);
+      p_stages(DS::p(SLOTS + j + 1), DS::p(SLOTS + j + 2));
+      s_stages(DS::s(j + 1), DS::s(j + 2));
+      __builtin_amdgcn_sched_barrier(0);
+    });
     // ---- dK; the dO_f rows of this stage are done with: refill them (unit u + NST), then wait for the Q
     // rows of the next unit -- everything issued before this phase's copies but the dO_f, Q groups after them
 #pragma unroll
@@ -430,36 +482,29 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       next_off = unit_off(raws[NST - 1]);
     }
     const unsigned char* gd = dw + next_off;
-#pragma unroll
-    for (int c = 0; c < NCD; ++c) {
-      const bool ds_on = c < DVB - 1;
-      const int i0 = S_DV + c * (16 - S_DV) / (DVB - 1), i2 = S_DV + (c + 1) * (16 - S_DV) / (DVB - 1), i1 = (i0 + i2) / 2;
-      // copies of this step (they end DVB steps before the phase does)
-      const int g0 = c * NC / DVB, g2 = (c + 1) * NC / DVB, g1 = (g0 + g2) / 2;
-      auto copies = [&](int from, int to) {
-        if (STEADY && c < DVB)
-#pragma unroll
-          for (int e = from; e < to; ++e) copy_piece(gd, wbase + st_off + HALF, e);
-      };
-      pair_begins(2 * KS + NCD + c);
-      mfma_a(dka[c % DVB][0], qt[c], opnd(sb[0][c / DVB]));
-      if (ds_on) s_items(i0, i1);
-      copies(g0, g1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_a(dka[c % DVB][1], qt[c], opnd(sb[1][c / DVB]));
-      if (ds_on) s_items(i1, i2);
-      copies(g1, g2);
-      if (c == NCD - kAhead) {
+    in_steps<SLOTS>([&](auto number) {
+      constexpr int j = decltype(number)::value, c = j / 2, m = 2 * KS + NCD + c;
+      if (j % 2 == 0) {
+        wait_lgkmcnt<reads_in(m - 1)>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      constexpr int copy = DS::copy(j);  // (they end before the wait for the next unit's rows)
+      if (STEADY && copy >= 0) copy_aim(wbase + st_off + HALF, copy);
+      mfma_a(dka[c % DVB][j % 2], both(qt[c]), opnd(sb[j % 2][c / DVB]));
+      if (STEADY && copy >= 0) copy_piece(gd, wbase + st_off + HALF, copy, true);
+      if (j == 2 * (NCD - kAhead)) {
         // newer than the next unit's Q group: the dO_f and Q groups of the units after it requested so far
         const int left = nu - 1 - (u + 1);  // units after the next one
         if (STEADY) wait_vmcnt<(NST - 2) * G + NC>();
         else if (NST > 2 && left == 2) wait_vmcnt<2 * G>();
         else if (NST > 2 && left == 1) wait_vmcnt<G>();
         else wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
       }
-      pair_reads(2 * KS + NCD + c);
+      read_part(m + 2, j % 2);
+      s_stages(DS::s(SLOTS + j), DS::s(SLOTS + j + 1));
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
   int u = 0;
   for (; u + 2 * NST - 1 < nu; u += NST) {

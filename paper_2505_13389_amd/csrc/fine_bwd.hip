@@ -328,8 +328,10 @@ __device__ __forceinline__ void dq_block(
         if (b == 0 && D == 64) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
         if (b == 0 && D == 128 && m % 2 == 0) kt[G / 2 + m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, 1, m / 2);
         // the copy of V(u+2) (V(u) is in registers): d = 128 behind every other matrix instruction of both halves
-        if (D == 128 && m % 2 == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, b * (G / 2) + m / 2);
-        if (D == 64 && b == 1 && more2) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);
+        // (where the last units are near: all of it at once, one branch)
+        if (KIND == 1 && b == 1 && m == 0 && more2) copy.all(vb, un[2], lds0 + (2 + par) * HALF);
+        if (KIND == 2 && D == 128 && m % 2 == 1) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, b * (G / 2) + m / 2);
+        if (KIND == 2 && D == 64 && b == 1) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);
         with(m);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -359,9 +361,10 @@ __device__ __forceinline__ void dq_block(
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < G; ++m) {
-      if (more2 && m % kEvery == 0) copy.aim(lds0 + par * HALF, m / kEvery);
+      if (KIND == 2 && m % kEvery == 0) copy.aim(lds0 + par * HALF, m / kEvery);
       mfma_acc(acc[m % DVB][0], kt[m], __builtin_bit_cast(bf16x8, ds[0][m / DVB]));
-      if (more2 && m % kEvery == 0) copy.piece(kb, un[2], lds0 + par * HALF, m / kEvery, true);
+      if (KIND == 1 && m == 0 && more2) copy.all(kb, un[2], lds0 + par * HALF);
+      if (KIND == 2 && m % kEvery == 0) copy.piece(kb, un[2], lds0 + par * HALF, m / kEvery, true);
       if constexpr (D == 128) {
         if (m < 3) d_stages(0, 5 + m, m == 2 ? 9 : 6 + m);
         if (m >= 3) d_stages(1, m - 3, m - 2);
@@ -373,7 +376,7 @@ __device__ __forceinline__ void dq_block(
     }
     // ---- dQ of half 1 | the rest of its dS, the K operands of the next unit
     if (more1) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2)
-      if (more2) wait_vmcnt<NC + NC / kEvery>();
+      if (more2) wait_vmcnt<NC + (KIND == 2 ? NC / kEvery : NC)>();
       else wait_vmcnt<0>();
     }
     asm volatile("s_nop 1");
@@ -382,9 +385,9 @@ __device__ __forceinline__ void dq_block(
     for (int m = 0; m < G; ++m) {
       // (behind the last unit no operand reads lie between the last item of step 1 and the matrix instruction that reads it)
       if (!more1 && m == DVB) asm volatile("s_nop 1");
-      if (more2 && kEvery == 2 && m % 2 == 0) copy.aim(lds0 + par * HALF, (G + m) / 2);
+      if (KIND == 2 && kEvery == 2 && m % 2 == 0) copy.aim(lds0 + par * HALF, (G + m) / 2);
       mfma_acc(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
-      if (more2 && kEvery == 2 && m % 2 == 0) copy.piece(kb, un[2], lds0 + par * HALF, (G + m) / 2, true);
+      if (KIND == 2 && kEvery == 2 && m % 2 == 0) copy.piece(kb, un[2], lds0 + par * HALF, (G + m) / 2, true);
       if constexpr (D == 128) {
         if (m < 3) d_stages(1, 5 + m, m == 2 ? 9 : 6 + m);
       } else {

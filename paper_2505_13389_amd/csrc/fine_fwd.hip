@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int NPV = 2 * DVB;          // steps of the PV phase
   // LDS operands are waited for in pairs of steps, and read kAhead steps before the first of them is used
-  constexpr int kAhead = D == 128 ? 6 : 2;
+  constexpr int kAhead = D == 128 ? 4 : 2;
   constexpr int kEarly = FwdStages<D>::before_pv(16);  // of the 34 softmax stages of a unit, those behind the PV phase before it
   constexpr int OS = D;
   // per wavefront: K of two units, V of two units
@@ -508,18 +508,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     asm volatile("s_nop 1");  // (two wait states between the moves to pc and the first matrix instruction)
     in_steps<2 * NPV>([&](auto number) {
       constexpr int j = decltype(number)::value, i = j >> 1, q = j & 3;
-      if (more3 && q == 0 && j < kEvery * NC) copy.aim(lds0 + (1 - par) * HALF, j / kEvery);
+      if (KIND == 2 && q == 0 && j < kEvery * NC) copy.aim(lds0 + (1 - par) * HALF, j / kEvery);
       if (q == 0) {
         wait_lgkmcnt<reads_between(i, NPV, 4, 2)>();
         __builtin_amdgcn_sched_barrier(0);
       }
       mfma_o(o[i % DVB][j & 1], v_op(i), __builtin_bit_cast(bf16x8, pc[j & 1][i / DVB]));
       if (more1 && j == 2 * (NPV - kAhead)) {  // K(u+2) has landed; newer: V(u+1) and a part of K(u+3)
-        if (more3) wait_vmcnt<NC + kPart>();
+        if (more3) wait_vmcnt<NC + (KIND == 2 ? kPart : NC)>();
         else if (more2) wait_vmcnt<NC>();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (more3 && j % kEvery == 0 && j < kEvery * NC) copy.piece(kb, un[2], lds0 + (1 - par) * HALF, j / kEvery, q == 0);
+      if (KIND == 1 && j == 0 && more3) copy.all(kb, un[2], lds0 + (1 - par) * HALF);  // (one branch, not one per copy)
+      if (KIND == 2 && j % kEvery == 0 && j < kEvery * NC) copy.piece(kb, un[2], lds0 + (1 - par) * HALF, j / kEvery, q == 0);
       constexpr int to = i - i % 2 + kAhead;
       if constexpr (to < NPV) {
         read_v(to, q);

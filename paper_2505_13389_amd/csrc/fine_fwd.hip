@@ -712,10 +712,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 // launches of 288 to 8192 blocks in heads of 72 to 500, lists of 2 to 44 tiles; figures: time with the general kernel over that with
 // the one for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile.
 //   d = 128  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  The general one loses where its
-//            last generation is nearly empty -- 1056 blocks, 10 tiles 1.03, 26 1.04, 44 1.01; 1280, 26 1.01, 44 0.99; 2304, 12 1.05, 26
-//            1.01, 34 0.99; 2500, 8 1.00, 12 0.97; 2736, 16 1.02, 26 0.98; 2940, 4 1.01, 6 0.99; 3096, 12 1.03, 26 0.99; 4500, 4 1.03, 8 0.97 --
-//            and where the blocks are shared and nearly fill a generation of the other: 360, 4 1.00, 8 0.99; 384, 8 1.00, 16 0.98; 448, 12
-//            1.01, 20 0.98; 512, 16 1.00, 20 0.99.  Elsewhere it wins: 576, 4 0.98, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 4096, 12 0.91; 8192, 12 0.90.
+//            last generation is nearly empty -- 1056 blocks, 4 tiles 1.04, 16 1.01, 22 1.005, 26 0.99, 36 0.98; 1152, 8 1.01, 10 0.997; 1280, 8
+//            1.02, 12 1.00, 16 0.997, 44 0.95; 2112, 4 1.05, 12 1.01, 16 0.996; 2205, 6 1.02, 10 0.99; 2304, 4 1.03, 6 1.01, 8 0.99, 26 0.96; 2400, 4
+//            1.02, 6 1.00, 8 0.98; 2736, 2 1.03, 4 1.01, 6 0.98, 16 0.95; 2880, 4 1.01, 8 1.00; 2940, 3 1.01, 4 0.98; 3080, 4 1.05, 6 1.005, 8
+//            0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4 0.99 -- and where the blocks are shared and nearly fill a generation
+//            of the other: 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4 1.015, 6 1.00, 8 0.996; 512, 8 1.01, 10 0.99, 16 0.97.
+//            (449 to 512, 1025 to 1152, 2177 to 2304 and 2561 to 2815 blocks keep the lines drawn before the general kernel became
+//            faster, which tests/test_gpu_fwd_units.py holds: up to 4 % are left there.)
+//            Elsewhere it wins: 576, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 4096, 12 0.91; 8192, 12 0.90.
 //   d = 64   a generation of the general kernel is 1024 blocks: 384, 2 0.98; 560, 8 1.01, 16 1.01, 20 0.98; 1000, 4 0.96; 1056, 8 1.06, 20
 //            0.97; 1536, 12 1.08, 20 0.98; 2000, 4 0.99, 10 0.99; 2240, 8 1.04, 16 1.00; 2660, 8 1.02, 12 0.99; 3500, 6 1.00, 12 0.98; 4500, 2
 //            1.03, 6 1.00; 6144, 4 0.90.
@@ -729,12 +733,12 @@ inline bool fwd_short(int d, unsigned grid, int tiles) {
     if (grid <= 2560) return tiles <= 12;
     return tiles <= (grid < 2816 ? 9 : grid <= 4096 ? 6 : grid <= 5120 ? 2 : 0);
   }
-  if (grid <= 512) return tiles <= (grid > 448 ? 16 : grid > 368 ? 12 : 4);
+  if (grid <= 512) return tiles <= (grid > 448 ? 16 : 4);
   if (grid <= 1024) return false;
-  if (grid <= 1280) return tiles <= 44;
+  if (grid <= 1280) return tiles <= (grid <= 1152 ? 44 : 10);
   if (grid <= 2048) return false;
-  if (grid <= 3072) return tiles <= (grid <= 2304 ? 26 : grid <= 2560 ? 8 : grid < 2816 ? 18 : grid < 3072 ? 4 : 0);
-  return tiles <= (grid <= 3264 ? 20 : grid > 4096 && grid <= 4608 ? 4 : 0);
+  if (grid <= 3072) return tiles <= (grid <= 2176 ? 12 : grid <= 2304 ? 26 : grid <= 2560 ? 6 : grid < 2816 ? 18 : grid < 3072 ? 3 : 0);
+  return tiles <= (grid <= 3264 ? 6 : grid > 4096 && grid <= 4608 ? 3 : 0);
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
 // with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks

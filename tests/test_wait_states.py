@@ -227,6 +227,26 @@ def test_no_kernel_needs_private_memory(source, emitted):
     assert len(sizes) == len(re.findall(r"^\s*\.amdhsa_kernel ", text, re.M)) and not any(map(int, sizes)), sizes
 
 
+def transcendental_results_used_at_once(code):
+    return [(a.text, code[m].text) for a in code if re.match(r"v_(exp|log|rcp|rsq|sqrt)_", a.op)
+            for m in a.next if code[m].vector and code[m].reads & a.writes and not re.match(r"v_(exp|log|rcp|rsq|sqrt)_", code[m].op)]
+
+
+@pytest.mark.parametrize("source", FILES)
+def test_transcendental_results_have_a_wait_state(source, emitted):
+    """One instruction lies between an exponential and plain vector arithmetic on its result.  The compiler sees to that, but it counts
+    the empty assembly statements that hold the stages of the fine kernels in place as one."""
+    for name, code in kernels(emitted[source]):
+        found = transcendental_results_used_at_once(code)
+        assert not found, f"{name}: {len(found)}, the first: {found[0]}"
+
+
+def test_the_check_sees_a_result_used_at_once():
+    of = lambda *text: transcendental_results_used_at_once(parse(text + ("s_endpgm",)))
+    assert of("v_exp_f32_e32 v1, v2", "v_add_f32_e32 v3, v3, v1")
+    assert not of("v_exp_f32_e32 v1, v2", "s_nop 0", "v_add_f32_e32 v3, v3, v1") and not of("v_exp_f32_e32 v1, v2", "v_add_f32_e32 v3, v3, v4")
+
+
 def test_the_check_sees_a_copy_in_flight():
     def of(*text):
         code = parse(text + ("ds_write_b64 v9, v[2:3]", "s_endpgm"))

@@ -306,12 +306,14 @@ __device__ __forceinline__ void dq_block(
     // the share of `n` items that step m of the steps [lo, hi) of a group does: [from, to)
     auto share = [](int n, int m, int lo, int hi) { return m < lo ? 0 : (m >= hi ? n : n * (m - lo) / (hi - lo)); };
     __builtin_amdgcn_sched_barrier(0);
+    // LDS reads of the first G / 2 steps of S 0: a V operand each and, d = 128, behind every other one a K^T operand, which is two
+    constexpr int kNewer = G / 2 + (D == 128 ? 2 * (G / 4) : 0);
     // the groups of matrix instructions; `with(m)` is the rest of step m
     auto s_group = [&](int b, auto with) {
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         if (b == 0 && m == 0) wait_lgkmcnt<G / 2>();      // the first half of the K operands; newer: the second
-        if (b == 0 && m == G / 2) wait_lgkmcnt<D == 128 ? G / 2 + G / 4 : G / 2>();  // the second half; newer: the V, and K^T, operands read so far
+        if (b == 0 && m == G / 2) wait_lgkmcnt<kNewer>();  // the second half; newer: the V, and K^T, operands read so far
         S[b] = mfma32(ka[m], qreg[b][m], m == 0 ? zero16 : S[b]);
         if (b == 0) va[m] = TL::rowmajor_at(vc, lane_a, m);
         if (b == 0 && D == 128 && m % 2 == 1) kt[m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, m / 2 / DVB, m / 2 % DVB);

@@ -247,6 +247,56 @@ def test_the_check_sees_a_result_used_at_once():
     assert not of("v_exp_f32_e32 v1, v2", "s_nop 0", "v_add_f32_e32 v3, v3, v1") and not of("v_exp_f32_e32 v1, v2", "v_add_f32_e32 v3, v3, v4")
 
 
+def walks(code):
+    """Instructions of the loops that walk a list: without loops in them, a matrix instruction in 16 or more."""
+    loops = [range(t, n + 1) for n, i in enumerate(code) for t in i.next if t <= n]
+    for loop in loops:
+        matrix = sum(code[n].matrix for n in loop)
+        if matrix >= 16 and 16 * matrix >= len(loop) and not any(x != loop and x[0] >= loop[0] and x[-1] <= loop[-1] for x in loops):
+            yield loop
+
+
+def waits_for_later_operands(code, far=8):
+    """Waits for some, not all, of the LDS reads in flight that are for an operand which the next `far` matrix instructions
+    do not use: the reads are counted in issue order, so such a wait leaves fewer in flight than it could."""
+    found = []
+    for n in {n for loop in walks(code) for n in loop if code[n].op.startswith("ds_read")}:
+        read, behind, wait, matrix = code[n], 0, None, 0
+        for i in code[n + 1:]:
+            m = re.search(r"lgkmcnt\((\d+)\)", i.text) if i.op == "s_waitcnt" else None
+            if wait is None and m and int(m[1]) <= behind:
+                wait = i
+            behind += i.op.startswith(("ds_", "s_load"))
+            if (i.reads | i.writes) & read.writes or i.op == "s_branch":
+                if i.matrix and wait is not None and matrix >= far and "lgkmcnt(0)" not in wait.text:
+                    found.append(f"'{wait.text}' for '{read.text}', used {matrix} matrix instructions later")
+                break
+            matrix += i.matrix and wait is not None
+    return found
+
+
+@pytest.mark.parametrize("source", ["fine_fwd.hip", "fine_bwd.hip", "fine_bwd_dkv.hip"])
+def test_counted_waits_leave_later_operands_in_flight(source, emitted):
+    """A wait with the wrong number waits for too much where it is too small (too large, the compiler's own waits stand in)."""
+    seen = 0
+    for name, code in kernels(emitted[source]):
+        seen += sum(map(len, walks(code)))
+        found = waits_for_later_operands(code)
+        assert not found, f"{name}: {len(found)}, the first: {found[0]}"
+    assert seen
+
+
+def test_the_check_sees_a_wait_for_a_later_operand():
+    product = "v_mfma_f32_32x32x16_bf16 v[0:15], v[{}:{}], v[24:27], v[0:15]"
+    reads = [f"ds_read_b128 v[{r}:{r + 3}], v80" for r in (32, 36, 40)]
+    products = [product.format(r, r + 3) for r in [32] * 9 + [36, 40] + [32] * 7]
+
+    def of(count):
+        return waits_for_later_operands(parse([".LBB0_1:", *reads, f"s_waitcnt lgkmcnt({count})", *products, "s_cbranch_scc1 .LBB0_1", "s_endpgm"]))
+    assert of(1) and not of(2)
+    assert not of(0)  # (for all of them: ahead of a copy over their place)
+
+
 def test_the_check_sees_a_copy_in_flight():
     def of(*text):
         code = parse(text + ("ds_write_b64 v9, v[2:3]", "s_endpgm"))

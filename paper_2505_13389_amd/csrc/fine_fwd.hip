@@ -711,15 +711,20 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 // Which kernel, by the number of query blocks and of 64-key tiles in a list.  From whole forwards back to back, N(0,1) inputs, 79
 // launches of 288 to 8192 blocks in heads of 72 to 500, lists of 2 to 44 tiles; figures: time with the general kernel over that with
 // the one for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile.
-//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  The general one loses where its
-//            last generation is nearly empty -- 1056 blocks, 4 tiles 1.04, 16 1.01, 22 1.005, 26 0.99, 36 0.98; 1152, 8 1.01, 10 0.997; 1280, 8
-//            1.02, 12 1.00, 16 0.997, 44 0.95; 2112, 4 1.05, 12 1.01, 16 0.996; 2205, 6 1.02, 10 0.99; 2304, 4 1.03, 6 1.01, 8 0.99, 26 0.96; 2400, 4
-//            1.02, 6 1.00, 8 0.98; 2736, 2 1.03, 4 1.01, 6 0.98, 16 0.95; 2880, 4 1.01, 8 1.00; 2940, 3 1.01, 4 0.98; 3080, 4 1.05, 6 1.005, 8
-//            0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4 0.99 -- and where the blocks are shared and nearly fill a generation
-//            of the other: 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4 1.015, 6 1.00, 8 0.996; 512, 8 1.01, 10 0.99, 16 0.97.
-//            (449 to 512, 1025 to 1152, 2177 to 2304 and 2561 to 2815 blocks keep the lines drawn before the general kernel became
-//            faster, which tests/test_gpu_fwd_units.py holds: up to 4 % are left there.)
-//            Elsewhere it wins: 576, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 4096, 12 0.91; 8192, 12 0.90.
+//   d = 128  (133 launches more, both kernels in turn in one process, mean of two machines; a third had up to 0.03 more at 9 to 12
+//            tiles)  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  The general one loses where
+//            its last generation is nearly empty, for longer the emptier -- 1026 blocks, 8 tiles 1.025, 16 1.005, 24 0.99; 1056, 8 1.00, 16
+//            0.995, 20 0.995, 24 0.98; 1100, 6 1.01, 8 1.00, 16 0.99, 20 0.995, 24 0.98; 1152 in heads of 96, 4 1.035, 8 1.005, 12 1.00, 16
+//            0.995, 20 0.995, 26 0.98, of 288, 6 0.99, 10 0.985, 26 0.97; 1200, 8 1.01, 10 1.00, 12 0.995; 1280, 8 0.99, 16 0.98; 2112, 8
+//            0.995, 12 0.98, 16 0.97; 2200, 4 1.035, 6 1.00, 8 0.99, 12 0.98; 2205, 4 1.05, 6 0.995, 8 0.98; 2304 in heads of 96, 4 1.035, 8
+//            1.00, 10 0.985, 16 0.975, of 288, 4 1.03, 7 1.015, 8 1.005, 10 0.98, 16 0.96; 2400, 4 1.025, 5 0.985, 6 0.975; 2560, 4 1.01, 5
+//            0.985, 6 0.975; 2600, 3 1.06, 4 1.005, 5 0.98, 8 0.96; 2688, 3 1.055, 4 1.005, 5 0.985, 8 0.96, 18 0.94; 2736, 3 1.02, 4 1.00, 5
+//            0.975, 8 0.95; 2800, 3 1.045, 4 0.995, 5 0.98; 2880, 3 1.03, 4 0.955; 2940, 2 1.005, 3 0.995, 4 0.955; 3000, 3 1.01, 4 0.975 --
+//            and where the blocks are shared and nearly fill a generation of the other: 468, 6 1.01, 8 1.005, 10 0.98, 16 0.95; 480, 8 1.02,
+//            10 1.005, 12 0.99, 16 0.96; 504, 8 1.035, 10 1.005, 12 0.99; 512, 8 1.025, 10 1.01, 12 0.985, 16 0.98.  From the launches before
+//            (some of them 0.02 to 0.03 higher than these where they meet): 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4
+//            1.015, 6 1.00, 8 0.996; 2112, 12 1.01, 16 0.996; 3080, 4 1.05, 6 1.005, 8 0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4
+//            0.99. Elsewhere it wins: 576, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 3072, 4 0.97; 4096, 12 0.91; 8192, 12 0.90.
 //   d = 64   a generation of the general kernel is 1024 blocks: 384, 2 0.98; 560, 8 1.01, 16 1.01, 20 0.98; 1000, 4 0.96; 1056, 8 1.06, 20
 //            0.97; 1536, 12 1.08, 20 0.98; 2000, 4 0.99, 10 0.99; 2240, 8 1.04, 16 1.00; 2660, 8 1.02, 12 0.99; 3500, 6 1.00, 12 0.98; 4500, 2
 //            1.03, 6 1.00; 6144, 4 0.90.
@@ -733,11 +738,11 @@ inline bool fwd_short(int d, unsigned grid, int tiles) {
     if (grid <= 2560) return tiles <= 12;
     return tiles <= (grid < 2816 ? 9 : grid <= 4096 ? 6 : grid <= 5120 ? 2 : 0);
   }
-  if (grid <= 512) return tiles <= (grid > 448 ? 16 : 4);
+  if (grid <= 512) return tiles <= (grid > 448 ? 10 : 4);
   if (grid <= 1024) return false;
-  if (grid <= 1280) return tiles <= (grid <= 1152 ? 44 : 10);
+  if (grid <= 1280) return tiles <= (grid <= 1152 ? 20 : 10);
   if (grid <= 2048) return false;
-  if (grid <= 3072) return tiles <= (grid <= 2176 ? 12 : grid <= 2304 ? 26 : grid <= 2560 ? 6 : grid < 2816 ? 18 : grid < 3072 ? 3 : 0);
+  if (grid <= 3072) return tiles <= (grid <= 2304 ? 12 : grid < 2816 ? 4 : grid < 3072 ? 3 : 0);
   return tiles <= (grid <= 3264 ? 6 : grid > 4096 && grid <= 4608 ? 3 : 0);
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip

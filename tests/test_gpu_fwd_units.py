@@ -66,8 +66,10 @@ def test_walks_of_two_wavefronts(d, H, K):
 
 
 # d, heads of 96 query blocks, list length, kernel, whether workgroups take two blocks
-RULE = [(128, 5, 16, SHORT, False), (128, 5, 17, TWO, False), (128, 12, 44, SHORT, False), (128, 12, 45, TWO, True),
-        (128, 24, 26, SHORT, False), (128, 24, 27, TWO, True), (128, 28, 18, SHORT, False), (128, 28, 19, TWO, True),
+RULE = [(128, 5, 10, SHORT, False), (128, 5, 11, TWO, False), (128, 12, 20, SHORT, False), (128, 12, 21, TWO, True),
+        (128, 24, 12, SHORT, False), (128, 24, 13, TWO, True), (128, 28, 4, SHORT, False), (128, 28, 5, TWO, True),
+        (128, 5, 16, TWO, False), (128, 5, 17, TWO, False), (128, 12, 44, TWO, True), (128, 12, 45, TWO, True),
+        (128, 24, 26, TWO, True), (128, 24, 27, TWO, True), (128, 28, 18, TWO, True), (128, 28, 19, TWO, True),
         (64, 6, 16, SHORT, False), (64, 6, 17, FOUR, False), (64, 12, 14, SHORT, False), (64, 12, 15, FOUR, False),
         (64, 28, 9, SHORT, False), (64, 28, 10, TWO, False)]
 
@@ -80,13 +82,16 @@ def test_both_sides_of_the_short_list_rule(d, H, K, waves, paired):
     run_and_check(wl, tiled_bits(wl, seed=400 + K + d, pad_garbage=True), random_lists(wl, g, K), heads=[0, H // 2, H - 1])
 
 
-@pytest.mark.parametrize("d,H", [(64, 6), (128, 12), (128, 5)])  # 576, 1152 and 480 query blocks
-@pytest.mark.parametrize("K", [1, 2, 12, 13])
-def test_short_walks_of_larger_launches(K, d, H):
-    """The kernel for short lists."""
+# 576, 1152 and 480 query blocks: the kernel for short lists, and lists that it leaves to the general one
+SHORT_WALKS = ([(d, H, K, SHORT, False) for d, H in ((64, 6), (128, 12)) for K in (1, 2, 12, 13)] +
+               [(128, 5, K, SHORT, False) for K in (1, 2, 9)] + [(128, 5, K, TWO, False) for K in (12, 13)])
+
+
+@pytest.mark.parametrize("d,H,K,waves,paired", SHORT_WALKS)
+def test_short_walks_of_larger_launches(K, d, H, waves, paired):
     wl = Workload("fwd_short", 1, H, 7, 22, 30, d, K)
     g = grid_of(wl)
-    assert_kernel(wl, SHORT)
+    assert_kernel(wl, waves, paired)
     run_and_check(wl, tiled_bits(wl, seed=200 + K + d, pad_garbage=True), random_lists(wl, g, K))
 
 

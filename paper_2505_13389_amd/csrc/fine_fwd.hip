@@ -717,18 +717,28 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 //            0.995, 20 0.995, 24 0.98; 1100, 6 1.01, 8 1.00, 16 0.99, 20 0.995, 24 0.98; 1152 in heads of 96, 4 1.035, 8 1.005, 12 1.00, 16
 //            0.995, 20 0.995, 26 0.98, of 288, 6 0.99, 10 0.985, 26 0.97; 1200, 8 1.01, 10 1.00, 12 0.995; 1280, 8 0.99, 16 0.98; 2112, 8
 //            0.995, 12 0.98, 16 0.97; 2200, 4 1.035, 6 1.00, 8 0.99, 12 0.98; 2205, 4 1.05, 6 0.995, 8 0.98; 2304 in heads of 96, 4 1.035, 8
-//            1.00, 10 0.985, 16 0.975, of 288, 4 1.03, 7 1.015, 8 1.005, 10 0.98, 16 0.96; 2400, 4 1.025, 5 0.985, 6 0.975; 2560, 4 1.01, 5
-//            0.985, 6 0.975; 2600, 3 1.06, 4 1.005, 5 0.98, 8 0.96; 2688, 3 1.055, 4 1.005, 5 0.985, 8 0.96, 18 0.94; 2736, 3 1.02, 4 1.00, 5
-//            0.975, 8 0.95; 2800, 3 1.045, 4 0.995, 5 0.98; 2880, 3 1.03, 4 0.955; 2940, 2 1.005, 3 0.995, 4 0.955; 3000, 3 1.01, 4 0.975 --
-//            and where the blocks are shared and nearly fill a generation of the other: 468, 6 1.01, 8 1.005, 10 0.98, 16 0.95; 480, 8 1.02,
-//            10 1.005, 12 0.99, 16 0.96; 504, 8 1.035, 10 1.005, 12 0.99; 512, 8 1.025, 10 1.01, 12 0.985, 16 0.98.  From the launches before
-//            (some of them 0.02 to 0.03 higher than these where they meet): 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4
-//            1.015, 6 1.00, 8 0.996; 2112, 12 1.01, 16 0.996; 3080, 4 1.05, 6 1.005, 8 0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4
-//            0.99. Elsewhere it wins: 576, 12 0.97; 1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 3072, 4 0.97; 4096, 12 0.91; 8192, 12 0.90.
+//            1.00, 10 0.985, 16 0.975, of 288, 4 1.03, 7 1.015, 8 1.005, 10 0.98, 16 0.96; 2400 in heads of 96, 4 1.025, 5 0.985, 6 0.975, of
+//            400 to 600, 5 1.005, 6 0.99; 2560, of 256, 4 1.01, 5 0.985, 6 0.975, of 512 and 640, 5 1.015, 6 1.00; 2600, 3 1.06, 4 1.005, 5
+//            0.98, 8 0.96; 2688, 3 1.055, 4 1.005, 5 0.985, 8 0.96, 18 0.94; 2736, 3 1.02, 4 1.00, 5 0.975, 8 0.95; 2800, 3 1.045, 4 0.995, 5
+//            0.98; 2880, 3 1.03, 4 0.955; 2940, 2 1.005, 3 0.995, 4 0.955; 3000, 3 1.01, 4 0.975 -- and where the blocks are shared and
+//            nearly fill a generation of the other: 468, 6 1.01, 8 1.005, 10 0.98, 16 0.95; 480, 8 1.02, 10 1.005, 12 0.99, 16 0.96; 504, 8
+//            1.035, 10 1.005, 12 0.99; 512, 8 1.025, 10 1.01, 12 0.985, 16 0.98.  From the launches before (some of them 0.02 to 0.03 higher
+//            than these where they meet): 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4 1.015, 6 1.00, 8 0.996; 2112, 12 1.01,
+//            16 0.996; 3080, 4 1.05, 6 1.005, 8 0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4 0.99. Elsewhere it wins: 576, 12 0.97;
+//            1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 3072, 4 0.97; 4096, 12 0.91; 8192, 12 0.90.
 //   d = 64   a generation of the general kernel is 1024 blocks: 384, 2 0.98; 560, 8 1.01, 16 1.01, 20 0.98; 1000, 4 0.96; 1056, 8 1.06, 20
 //            0.97; 1536, 12 1.08, 20 0.98; 2000, 4 0.99, 10 0.99; 2240, 8 1.04, 16 1.00; 2660, 8 1.02, 12 0.99; 3500, 6 1.00, 12 0.98; 4500, 2
 //            1.03, 6 1.00; 6144, 4 0.90.
-inline bool fwd_short(int d, unsigned grid, int tiles) {
+//   Large heads (d = 128), whose K and V outgrow an L2 several times: a second wavefront per SIMD also hides the trips beyond it, so
+//            the lines lie further out. 22 to 64 MiB: 2200 blocks in 2 heads, 6 tiles 1.01, 12 0.985, 16 0.97; 2400 in 2 and 3, 5 1.025, 6
+//            1.01, 8 1.00 (in 4 to 6: 5 1.005, 6 0.99, 8 0.98); 2560 in 2, 8 1.01; 2640 and 2673, 5 1.01, 6 0.995, 12 0.965; 2880 in 2 and 3,
+//            4 1.01, in 4 0.985; 3000, 3 1.02, 4 1.00; 3200, 7 1.015, 8 1.005, 12 0.985; 4320 to 4400, 3 1.025, 4 1.015, 6 0.985. From 64
+//            MiB, where the general kernel's workgroups also wait for one another (gangs): 2112 to 2304, 8 1.05, 16 1.02, 20 1.005, 24 0.995;
+//            2400 and 2560, 8 1.04, 16 1.01, 20 1.005, 24 0.99; 2730, 8 1.02, 16 1.005, 20 0.985; 3072, 4 1.035, 8 1.02, 16 1.00; 4096, 4
+//            1.03, 8 1.02, 16 1.00; 4224 in 2, 8 1.03, 16 0.99.
+constexpr size_t kLargeHead = (size_t)22 << 20, kVastHead = (size_t)64 << 20;
+inline size_t kv_bytes(int Nc, int d) { return (size_t)Nc * kTile * d * 4; }
+inline bool fwd_short(int d, int Nc, unsigned grid, int tiles) {
   if (d == 64) {
     if (grid <= 512) return tiles <= 2;
     if (grid <= 768) return tiles <= 16;
@@ -742,8 +752,11 @@ inline bool fwd_short(int d, unsigned grid, int tiles) {
   if (grid <= 1024) return false;
   if (grid <= 1280) return tiles <= (grid <= 1152 ? 20 : 10);
   if (grid <= 2048) return false;
-  if (grid <= 3072) return tiles <= (grid <= 2304 ? 12 : grid < 2816 ? 4 : grid < 3072 ? 3 : 0);
-  return tiles <= (grid <= 3264 ? 6 : grid > 4096 && grid <= 4608 ? 3 : 0);
+  const size_t head = kv_bytes(Nc, d);
+  if (head >= kVastHead) return tiles <= (grid <= 2304 ? 20 : grid <= 4096 ? 16 : grid <= 4608 ? 8 : 0);
+  const bool large = head >= kLargeHead;
+  if (grid <= 3072) return tiles <= (grid <= 2304 ? 12 : grid <= 2560 ? (large ? 8 : 5) : grid < 2816 ? 4 + large : grid < 3072 ? 3 + large : 0);
+  return tiles <= (grid <= 3264 ? 6 + large : grid > 4096 && grid <= 4608 ? 3 + large : 0);
 }
 // The general kernel with four wavefronts per workgroup: half as long a walk counts where the launch does not fill the chip
 // with two-wavefront workgroups.  d = 64, 64 blocks, 8 tiles 10.0 against 12.0; 512 blocks, 33 tiles 27.6 / 37.2; 640 blocks
@@ -765,7 +778,7 @@ FineRoute fine_fwd_route(int BH, int Nc, int d, int K, int key_cubes_16, bool co
   const unsigned grid = (unsigned)(BH * Nc);
   const int tiles = fwd_tiles(K, key_cubes_16);
   if (coarse) return {4, 0};
-  if (fwd_short(d, grid, tiles)) return {0, 0};
+  if (fwd_short(d, Nc, grid, tiles)) return {0, 0};
   if (fwd_four_waves(d, grid, tiles)) return {4, 0};
   return {2, d == 128 ? paired_workgroups(grid, 512) : 0};
 }
@@ -790,9 +803,8 @@ hipError_t launch_fine_fwd(int BH, int Nc, int d, int K, float scale, const void
   // 2160 blocks (68 MiB), 2 heads, 180 2.72 / 2.62, 1.60 / 1.59, 4 heads 5.10 / 3.43, 3.17 / 3.20.  Elsewhere the waits
   // cost more than the hits return: 1440 blocks, 2 heads, 32 228 / 240 us; 624 blocks (19.5 MiB) 1.23 / 1.26 ms; d = 64,
   // 1440 blocks, 16 heads, 180 4.62 / 4.83, 4.55 / 4.72 ms, 2 heads, 24 105 / 123 us.
-  const size_t head = (size_t)Nc * kTile * d * 4;  // bytes of its K and V
-  const bool gangs = d == 128 && tiles < Nc &&
-                     ((head >= ((size_t)22 << 20) && grid >= 8192) || (head >= ((size_t)64 << 20) && grid >= 1024));
+  const size_t head = kv_bytes(Nc, d);
+  const bool gangs = d == 128 && tiles < Nc && ((head >= kLargeHead && grid >= 8192) || (head >= kVastHead && grid >= 1024));
   const unsigned every = gangs ? (unsigned)(127 / tiles + 1) : 1u;
   unsigned* arrived = gangs ? gang_scratch : nullptr;
   if (gangs) {

@@ -142,20 +142,24 @@ def test_routes(lib):
     assert lib.vsa_host_routes(ctypes.byref(vsa.Problem(*tiny).params()), None) == -1
 
 
-# d = 128: query blocks (as heads of so many), longest list in tiles that the forward's kernel for short lists takes
+# d = 128: query blocks, in so many heads, longest list in tiles that the forward's kernel for short lists takes; heads of less than 22
+# MiB of K and V, of less than 64, of more
 SHORT_LISTS = [(448, 4, 4), (450, 18, 10), (512, 4, 10), (513, 27, 0), (1024, 8, 0), (1025, 25, 20), (1152, 12, 20),
-               (1155, 33, 10), (1280, 5, 10), (1281, 21, 0), (2048, 8, 0), (2049, 3, 12), (2176, 17, 12), (2177, 7, 12), (2304, 24, 12), (2305, 5, 4),
-               (2560, 10, 4), (2561, 13, 4), (2688, 28, 4), (2815, 5, 4), (2816, 22, 3), (3071, 37, 3), (3072, 12, 0), (3073, 7, 6), (3264, 12, 6),
+               (1155, 33, 10), (1280, 5, 10), (1281, 21, 0), (2048, 8, 0), (2049, 3, 12), (2176, 17, 12), (2177, 7, 12), (2304, 24, 12), (2305, 5, 5),
+               (2560, 10, 5), (2561, 13, 4), (2688, 28, 4), (2815, 5, 4), (2816, 22, 3), (3071, 37, 3), (3072, 12, 0), (3073, 7, 6), (3264, 12, 6),
                (3265, 5, 0), (4096, 16, 0), (4097, 17, 3), (4608, 16, 3), (4609, 11, 0)]
+LARGE_HEADS = [(2112, 3, 12), (2304, 3, 12), (2400, 3, 8), (2400, 4, 5), (2560, 2, 8), (2684, 4, 4), (2674, 2, 5), (2816, 4, 4), (2814, 3, 5),
+               (3069, 3, 4), (3200, 4, 7), (4400, 4, 4), (4608, 3, 4)]
+VAST_HEADS = [(2048, 1, 0), (2049, 1, 20), (2304, 1, 20), (2305, 1, 16), (2560, 1, 16), (3071, 1, 16), (3265, 1, 16), (4096, 1, 16), (4096, 2, 16), (4224, 2, 8), (4608, 2, 8), (4610, 2, 0)]
 
 
-@pytest.mark.parametrize("blocks,H,longest", SHORT_LISTS)
+@pytest.mark.parametrize("blocks,H,longest", SHORT_LISTS + LARGE_HEADS + VAST_HEADS)
 def test_lines_of_the_short_list_rule(lib, blocks, H, longest):
     """Both sides of every line, in list length and in blocks, with lists of blocks and of key cubes of 16 tokens (four to a tile)."""
     import dataclasses
     Nc = blocks // H
     assert Nc * H == blocks
-    for flags, entries in ((0, 1), (vsa.VSA_FLAG_KEY_CUBES_16, 4)):
+    for flags, entries in ((0, 1), (vsa.VSA_FLAG_KEY_CUBES_16, 4))[:1 if Nc > 1024 else 2]:  # (at most 4096 key cubes)
         def short(K):
             pb = dataclasses.replace(vsa.Problem(1, H, 4 * Nc, 4, 4, 128, K), flags=flags)
             return vsa.vsa_host_routes(pb, indices_given=True)["fwd_waves"] == 0

@@ -250,6 +250,13 @@ def test_gangs_of_large_heads(d, K, shape):
         assert torch.equal(buf.out.view(torch.int16), eager.view(torch.int16)), f"replay {rep}"
 
 
+@pytest.mark.parametrize("K,waves", [(20, SHORT), (21, TWO)])
+def test_both_sides_of_the_line_of_large_heads(K, waves):
+    wl = Workload("fwd_gang", 1, *GANGS, 128, K)
+    assert_kernel(wl, waves, waves == TWO)
+    test_gangs_of_large_heads(128, K, GANGS)
+
+
 # d = 128, heads of 96 query blocks, list length, kernel, whether workgroups take two blocks: the lines of 369 to 448, 1153 to 1280, 2049 to
 # 2176, 2305 to 2560, 3073 to 3264 and 4097 to 4608 blocks
 LATER_LINES = [(4, 4, SHORT, False), (4, 5, TWO, False), (13, 10, SHORT, False), (13, 11, TWO, True), (22, 12, SHORT, False), (22, 13, TWO, True),

@@ -258,9 +258,10 @@ def test_both_sides_of_the_line_of_large_heads(K, waves):
 
 
 # d = 128, heads of 96 query blocks, list length, kernel, whether workgroups take two blocks: the lines of 369 to 448, 1153 to 1280, 2049 to
-# 2176, 2305 to 2560, 3073 to 3264 and 4097 to 4608 blocks
+# 2304, 2305 to 2560, 2816 to 3071, 3073 to 3264 and 4097 to 4608 blocks
 LATER_LINES = [(4, 4, SHORT, False), (4, 5, TWO, False), (13, 10, SHORT, False), (13, 11, TWO, True), (22, 12, SHORT, False), (22, 13, TWO, True),
-               (25, 7, TWO, True), (33, 6, SHORT, False), (33, 7, TWO, True), (47, 4, TWO, True)]
+               (25, 5, SHORT, False), (25, 6, TWO, True), (25, 7, TWO, True), (30, 3, SHORT, False), (30, 4, TWO, True),
+               (33, 6, SHORT, False), (33, 7, TWO, True), (47, 3, SHORT, False), (47, 4, TWO, True)]
 
 
 @pytest.mark.parametrize("H,K,waves,paired", LATER_LINES)

@@ -234,7 +234,7 @@ __device__ __forceinline__ void dq_block(
       if (w == 2) u4.z = x;
       if (w == 3) u4.w = x;
     };
-    // items 0..7 of a query half: two values each; the first four make up contraction step 0
+    // d = 64: items 0..7 of a query half, two values each; the first four make up contraction step 0
     auto p_items = [&](int b, int from, int to) {
 #pragma unroll
       for (int it = from; it < to; ++it) {
@@ -247,8 +247,7 @@ __device__ __forceinline__ void dq_block(
     auto d_items = [&](int b, int from, int to) {
 #pragma unroll
       for (int it = from; it < to; ++it) {
-        const float p0 = kDeltaInit ? P[b][2 * it] : P[b][2 * it] + ndelta[b];
-        const float p1 = kDeltaInit ? P[b][2 * it + 1] : P[b][2 * it + 1] + ndelta[b];
+        const float p0 = P[b][2 * it] + ndelta[b], p1 = P[b][2 * it + 1] + ndelta[b];
         const uint32_t x = pack_bf16(S[b][2 * it] * p0, S[b][2 * it + 1] * p1);
         put(ds[b][it >> 2], it & 3, x);
         asm volatile("" : : "v"(x));

@@ -24,12 +24,13 @@ namespace vsa {
 // matrix instruction reads an operand from either file).  d = 64: two wavefronts per SIMD, whose 256 registers do not
 // hold both halves' S and dP: there S 1 follows dP 0, and -Delta is added in vector arithmetic.
 //
-// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 200 others, all issued by one
-// wavefront, in 1930 cycles (d = 128; 2160 with the copies in two runs, one behind every matrix instruction of dP 1 and dQ 0, two
-// transposing reads behind one and items of P whose instructions waited for one another: costs of instructions in fine_fwd.hip),
-// at a clock that falls as the pipe fills (1.6 to 1.75 GHz at 39936 tokens).  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12
-// heads, d = 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of
-// the time.
+// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 208 others, 203 where all blocks are shared,
+// all issued by one wavefront, in 1930 cycles (d = 128; 2160 with the copies in two runs, one behind every matrix instruction of dP 1
+// and dQ 0, two transposing reads behind one and items of P whose instructions waited for one another: costs of instructions in
+// fine_fwd.hip, by which 80 to 145 cycles lie between two units, where list.get is, 75 to 90 and 50 at the seam of S 1 and dP 0, and 8
+// to 25 behind the matrix instructions of S 0 and the end of dQ 1), at a clock that falls as the pipe fills (1.6 to 1.75 GHz at 39936
+// tokens).  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12 heads, d =
+// 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of the time.
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
 // top-78 of 624: 1.61 -> 1.49 ms (1.23 PFLOP/s executed); 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
 // of 256, local lists: 2.83 -> 2.58 ms; d = 64, B = 2, 8 heads, top-32: 220 -> 210 us.
@@ -253,9 +254,10 @@ __device__ __forceinline__ void dq_block(
         asm volatile("" : : "v"(x));
       }
     };
-    // d = 128: the same in stages, dealt to the matrix instructions so that no result is used by the next instruction (see p_stages in
-    // fine_fwd.hip).  P: stage 0 the fma's of item 0 of 16, both halves'; 2g + 1 the first exponential of item g and the fma's of the
-    // next; 2g + 2 its second.  dS of half b: stage k the products of item k and the conversion of the item before.
+    // d = 128: the same in stages, dealt to the matrix instructions; inside a stage no result is used by the next instruction, the order
+    // of two stages in one place is the compiler's (see p_stages in fine_fwd.hip; here 10 pairs of exponentials a unit end up side by
+    // side).  P: stage 0 the fma's of item 0 of 16, both halves'; 2g + 1 the first exponential of item g and the fma's of the next; 2g + 2
+    // its second.  dS of half b: stage k the products of item k and the conversion of the item before.
     auto p_stages = [&](int from, int to) {
 #pragma unroll
       for (int n = from; n < to; ++n) {

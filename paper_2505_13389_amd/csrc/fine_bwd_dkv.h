@@ -49,12 +49,14 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // are per key cube.
 //
 // What bounds it: the clock, which falls as the matrix pipe fills (1.6 to 1.75 GHz at 39936 tokens), and the instructions of one
-// wavefront: a unit is 64 matrix instructions (2048 cycles of the pipe) and 280 others, in 2400 cycles at d = 128 (2590 with the
+// wavefront: a unit is 64 matrix instructions (2048 cycles of the pipe) and 276 others, in 2400 cycles at d = 128 (2590 with the
 // operand reads of two steps behind one matrix instruction, a wait for all of them two steps later and items whose instructions
-// waited for one another; costs of instructions in fine_fwd.hip), 32 and 240 in 1480 at d = 64 (1640 so); 3 us of start-up and 5 us of
-// merge and stores per workgroup, which the other workgroup of the CU overlaps.  d = 64 with two wavefronts per SIMD (256 registers
-// each, four to a workgroup; K and V in LDS) took 1700.  Before (32 keys x 32 queries per wavefront, 4
-// wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
+// waited for one another; costs of instructions in fine_fwd.hip), 32 and 212 in 1480 at d = 64 (1640 so), where 55 to 70 cycles
+// lie behind each matrix instruction of the dP phase and 4 to 20 behind those of S and the end of dK; 3 us of start-up and 5 us
+// of merge and stores per workgroup, which the other workgroup of the CU overlaps.  d = 64 with two wavefronts per SIMD (256
+// registers each, four to a workgroup; K and V in LDS) took 0.93 of the time of that earlier order (B = 2, 8 heads, top-32,
+// local lists: 317 -> 296 us) where the stages take 0.96 to 0.98 of it; with stages it has not been tried.
+// Before (32 keys x 32 queries per wavefront, 4 wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
 // 12 heads, d = 128, top-78 of 624: 2.68 -> 1.97 ms (1.22 PFLOP/s executed); 16384 tokens, top-32: 529 -> 370
 // us; d = 64, B = 2, 8 heads, top-32: 485 -> 288 us.  Four wavefronts (one workgroup
 // per CU, merging four partial results) instead of two: 2.20 ms, 426 us, 216 us, 349 us.
@@ -372,7 +374,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     }
     // ---- dP, with P = exp2(S' sl2) of both key halves behind it.  Item k of 16: one pair of values, first
     // those of contraction step 0 of the dV products (accumulator values 0..7), then those of step 1.  The items go through
-    // stages whose neighbours do not depend on one another (see fine_fwd.hip), dealt to the matrix instructions.  P: stage 0 the products of
+    // stages inside which neighbours do not depend on one another (see fine_fwd.hip), dealt to the matrix instructions.  P: stage 0 the products of
     // item 0; 2g + 1 the first exponential of item g and the products of the next; 2g + 2 its second, and the conversion of the
     // item before; 33 that of the last.  dS: stage k the products of item k and the conversion of the item before.
     uint4 pb[2][2], sb[2][2];

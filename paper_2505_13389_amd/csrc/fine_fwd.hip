@@ -22,14 +22,17 @@
 // multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
 // one.  d = 64 takes two wavefronts per SIMD.
 //
-// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 190 others (110 of softmax: fma,
-// exp2, sum, half a conversion per value; 24 LDS reads, 16 copies): 1490 cycles where the matrix pipe needs 1024, at a
+// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 210 others, 204 where all blocks
+// are shared (112 of softmax: fma, exp2, sum, half a conversion per value; 24 LDS reads, 16 copies, 33 to 38 scalar ones, most of them
+// of list.get): 1490 cycles where the matrix pipe needs 1024, at a
 // clock that falls as the chip fills (1.6 to 1.75 GHz; 2.1 while the last workgroups of a launch run).  What an instruction costs a
 // wavefront that is alone on its SIMD, measured behind matrix instructions: 5 cycles in vector arithmetic, 8 if the next one
 // needs its result, exp2 9, an LDS read 8, scalar ones and waits 4; five or six plain ones fit behind a matrix instruction,
 // and none is made up for by fewer behind the next.  So the softmax is a pipeline of stages without neighbours that depend on one another,
 // the stages, operand reads and copies are dealt to the 32 matrix instructions one by one, and what is rare (a moved
-// reference, pad keys, a new chunk of the list) lies out of the loop's line: 1730 -> 1490 cycles a unit (768 blocks, top-64
+// reference, pad keys, a new chunk of the list) lies out of the loop's line.  As emitted, by these costs, 20 to 50 cycles lie behind
+// most matrix instructions; more behind the two around list.get (60 to 75 and 115 to 130, a chain of dependent scalar instructions), the check
+// for a moved reference (105) and those the compiler gives two exponentials side by side (up to 75).  1730 -> 1490 cycles a unit (768 blocks, top-64
 // to 192), whole launches 8.5 % fewer at 39936 tokens, top-78, of which the clock leaves 3.8 % of the time: 1306 -> 1258 us for the
 // forward, 264 -> 259 at 16384 tokens, top-32 (two generations' start-up and end in it).  Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
@@ -311,10 +314,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (w == 3) u4.w = x;
   };
   // Softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0.  Its arithmetic goes
-  // through a pipeline of STAGES, one or two of them behind a matrix instruction, in which no result is used by the next
-  // instruction (that costs 8 cycles instead of 5) and exponentials (9) are apart: stage 0 the fma's of item 0; stage 2g + 1 the first
+  // through a pipeline of STAGES, one or two of them behind a matrix instruction, in each of which no result is used by the next
+  // instruction (that costs 8 cycles instead of 5): stage 0 the fma's of item 0; stage 2g + 1 the first
   // exponential of item g and the fma's of the next; stage 2g + 2 its second exponential, and the sums and the conversion of
-  // the item before; stage 33 those of the last item.
+  // the item before; stage 33 those of the last item.  The order of two stages in one place is the compiler's, which puts some of
+  // their exponentials (9 cycles) side by side (4 or 5 pairs a unit).
   float xf[2][2] = {}, xe[2][2] = {};  // arguments and exponentials of an item, by its parity
   auto p_fma = [&](const f32x16 (&S)[2], int it, const float* rf) {
     const int b = (it >> 2) & 1, e = 8 * (it >> 3) + 2 * (it & 3);
@@ -406,8 +410,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     bf16x8 ka[KS + kAhead];
     bf16x4 va[NPV + kAhead][2];
     auto v_half = [&](int i, int part) { return TL::transposed_half(vc, part ? lane_b1 : lane_b0, i / DVB, i % DVB); };
-    // The operand reads for the two steps kAhead further on, spread over the four matrix instructions of two steps (d = 64: over the
-    // first two): `k` reads a step's row-major operand, V operands are two reads.  q = 0 .. 3; `pv`: step of the PV phase.
+    // The operand reads for the two steps kAhead further on, spread over the four matrix instructions (q = 0 .. 3) of two steps, d = 64: over the
+    // first two.  A V operand is two reads: read_v issues the share of q of those of steps i and i + 1.  A K operand is one read: reads_row says
+    // whether that of the w-th of the two steps is issued at q.
     constexpr int kSpread = D == 128 ? 4 : 2;
     auto read_v = [&](int i, int q) {  // of steps i and i + 1
 #pragma unroll
@@ -420,7 +425,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       for (int t = s + 2; t < s + kAhead; t += 2) r += t < n ? now : next;
       return r;
     };
-    auto reads_row = [&](int q, int w) { return q == 2 * w * kSpread / 4; };  // the w-th of two row-major operands is read now
+    auto reads_row = [&](int q, int w) { return q == 2 * w * kSpread / 4; };
     auto v_op = [&](int i) { return __builtin_shufflevector(va[i][0], va[i][1], 0, 1, 2, 3, 4, 5, 6, 7); };
     if (more1) {
 #pragma unroll

@@ -26,35 +26,45 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // into UNITS of 32 query rows: wavefront w takes half w & 1 of the list entries w >> 1, (w >> 1) + NW/2, ...
 // and multiplies its units with ALL 64 keys:
 //   S [32 q x 64 k] = Q K^T,  dP = dO_f V^T,   P = exp2(S'),  dS = P dP',   dV += P^T dO_f,  dK += dS^T Q
-// so every operand it reads from LDS feeds two matrix instructions, and since nobody else reads its
+// so every operand it reads from LDS is multiplied with all of them, and since nobody else reads its
 // rows it copies them into stages of its own: the loop has no barrier, the wavefronts drift freely.
 // dK and dV [64 x d] are 2*d accumulation registers; K stays in registers (d/2 of them), and V of the first 32 keys (d/4);
 // V of the other 32 is in LDS, once for the workgroup.  S and dP (64 registers) become P and dS in place.  The NW partial
 // results are added once, through LDS, at the end.
 //
 // The order inside a unit is the dependency order, S | dP | dV | dK: P is formed while dP is multiplied,
-// dS while dV is, so the vector work hides behind matrix work without a second set of registers.  Each
-// phase is a run of STEPS, pinned by scheduling barriers: one step = one LDS operand multiplied with both
-// key halves (two matrix instructions, 64 cycles), the operand reads of the step kAhead later, and behind either
-// instruction a share of the copies and of the vector work (DkvStages).
+// dS while dV is, so the vector work hides behind matrix work without a second set of registers.
+//
+// d = 128 multiplies with 16x16x32 instructions (128 of 16 cycles), an operand with the four 16-key blocks one after the other;
+// behind each lies what DkvTicks deals to it, a read, a copy or two or three vector instructions, and P of the first 32 keys begins
+// while S of the others is multiplied.  d = 64 has 32x32x16 instructions (32 of 32 cycles) in STEPS: one step = one LDS
+// operand multiplied with both key halves, the operand reads of the step kAhead later, and behind either instruction a share of the
+// copies and of the vector work (DkvStages).
+// Why: under the power limit the chip gets 1.81 PFLOP/s out of the large instructions on N(0,1) operands and 2.05 to 2.19 out of the small ones,
+// but each costs 6 cycles of issue where a large one, for the work of two, costs 4.  With five vector instructions per 32 cycles of matrix work the
+// two are 4 % apart and with more of them the small ones lose: d = 128 has 4.2 others per 32 cycles here, d = 64 6.6.  (The forward,
+// with 6.5: 16384 tokens, top-32 254 -> 257 us, 39936 tokens, top-78 1232 -> 1302 us, so it keeps the large ones.)
 // The row terms enter through the accumulators' initial value: the preprocess kernel stores -lse*log2e/sl2
 // (then P = exp2(S' * sl2); -30000 on pad rows, whose P underflows to 0) and -Delta per row, and a lane
-// reads those of its 16 rows straight into the first matrix instruction's C operand.  Pad KEY rows need
+// reads those of its rows straight into the first matrix instruction's C operand.  Pad KEY rows need
 // no bias: a key's products only ever meet its own rows of dK and dV, which are stored as zeros.
 //
 // SUB: the lists name key cubes of 16 tokens (Sec. 3.2, the 64 x 16 row of the tile-size tables).  The
 // workgroup still owns a 64-row key block; its list is the union of the lists of the block's four key
-// cubes, and every entry says (bits 16..19) which of them the query block selected: one more matrix
-// instruction per key half subtracts a large number from S of the other keys.  The pooled-gradient terms
-// are per key cube.
+// cubes, and every entry says (bits 16..19) which of them the query block selected: a large number is
+// subtracted from S of the other keys (in the initial values; d = 64: by one more matrix instruction per key half).  The
+// pooled-gradient terms are per key cube.
 //
-// What bounds it: the clock, which falls as the matrix pipe fills (1.6 to 1.75 GHz at 39936 tokens), and the instructions of one
-// wavefront: a unit is 64 matrix instructions (2048 cycles of the pipe) and 276 others, in 2400 cycles at d = 128 (2590 with the
-// operand reads of two steps behind one matrix instruction, a wait for all of them two steps later and items whose instructions
-// waited for one another; costs of instructions in fine_fwd.hip), 32 and 212 in 1480 at d = 64 (1640 so), where 55 to 70 cycles
-// lie behind each matrix instruction of the dP phase and 4 to 20 behind those of S and the end of dK; 3 us of start-up and 5 us
+// What bounds it: the clock, which falls as the matrix pipe fills, and the instructions of one wavefront.  d = 128: a unit is 128
+// matrix instructions (2048 cycles of the pipe) and 267 others, 2520 cycles by the costs of fine_fwd.hip; a whole launch (39936 tokens, 12
+// heads, top-78) 3.21 M cycles at 1.66 GHz where the same order with 64 large instructions took 3.05 M at 1.53: a unit takes a fifth less
+// energy.  Steps of 16384 tokens, top-32 964 -> 942 us, 39936 tokens, top-78 4838 -> 4764, B = 2, 16 heads, top-128 of 256 7929 -> 7705, 256-token
+// cubes 933 -> 918, of which this pass is 35 to 40 %.  Two small instructions behind one another with the vector work of both behind
+// them: 21 % more cycles than the large ones, and slower; behind each a share of its own, but dealt by the count of instructions: 12 % more.
+// d = 64: 32 and 212 in 1480 cycles, where 55 to 70 cycles
+// lie behind each matrix instruction of the dP phase and 4 to 20 behind those of S and the end of dK.  3 us of start-up and 5 us
 // of merge and stores per workgroup, which the other workgroup of the CU overlaps.  d = 64 with two wavefronts per SIMD (256
-// registers each, four to a workgroup; K and V in LDS) took 0.93 of the time of that earlier order (B = 2, 8 heads, top-32,
+// registers each, four to a workgroup; K and V in LDS) took 0.93 of the time of an earlier order (B = 2, 8 heads, top-32,
 // local lists: 317 -> 296 us) where the stages take 0.96 to 0.98 of it; with stages it has not been tried.
 // Before (32 keys x 32 queries per wavefront, 4 wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,
 // 12 heads, d = 128, top-78 of 624: 2.68 -> 1.97 ms (1.22 PFLOP/s executed); 16384 tokens, top-32: 529 -> 370
@@ -67,28 +77,141 @@ struct DkvShape {
   static constexpr int NST = D == 128 ? 2 : 4;       // stages per wavefront
   static constexpr int LDS = HALF + NW * NST * STAGE;
 };
-// What lies behind which matrix instruction of a unit: the P stages ahead of instruction j of the dP phase and, behind those, of the dV
+// d = 64: what lies behind which matrix instruction of a unit: the P stages ahead of instruction j of the dP phase and, behind those, of the dV
 // phase; the dS stages ahead of instruction j of the dV and dK phases; the copy of dO_f rows behind instruction j of the dK phase (-1: none).
-template <int D>
 struct DkvStages {
   static constexpr int p_at(int j) {
-    constexpr int wide[32] = {1, 1, 2, 1, 2, 2, 1, 2, 1, 2, 1, 2, 1, 2, 1, 2, 2, 2, 2, 2, 1, 1}, narrow[16] = {3, 3, 3, 3, 3, 3, 3, 3, 4, 3, 3};
-    return D == 128 ? wide[j] : narrow[j];
+    constexpr int n[16] = {3, 3, 3, 3, 3, 3, 3, 3, 4, 3, 3};
+    return n[j];
   }
   static constexpr int s_at(int j) {
-    constexpr int wide[32] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, narrow[16] = {0, 0, 0, 2, 2, 2, 2, 2, 3, 2, 2};
-    return D == 128 ? wide[j] : narrow[j];
+    constexpr int n[16] = {0, 0, 0, 2, 2, 2, 2, 2, 3, 2, 2};
+    return n[j];
   }
   static constexpr int p(int j) { return j == 0 ? 0 : p(j - 1) + p_at(j - 1); }
   static constexpr int s(int j) { return j == 0 ? 0 : s(j - 1) + s_at(j - 1); }
-  static constexpr int copy(int j) {
-    constexpr int wide[16] = {-1, 0, -1, 1, -1, 2, -1, 3, 4, 5, 6, 7, -1, -1, -1, -1}, narrow[8] = {0, 1, 2, 3, -1, -1, -1, -1};
-    return D == 128 ? wide[j] : narrow[j];
-  }
+  static constexpr int copy(int j) { return j < 4 ? j : -1; }
 };
 // P of contraction step 0 (18 stages and its last conversion) ahead of dV, all of it ahead of step 1; dS likewise in dK
-static_assert(DkvStages<128>::p(16) > 18 && DkvStages<128>::p(23) == 34 && DkvStages<128>::s(16) > 8 && DkvStages<128>::s(23) == 17, "d = 128");
-static_assert(DkvStages<64>::p(8) > 18 && DkvStages<64>::p(11) == 34 && DkvStages<64>::s(8) > 8 && DkvStages<64>::s(11) == 17, "d = 64");
+static_assert(DkvStages::p(8) > 18 && DkvStages::p(11) == 34 && DkvStages::s(8) > 8 && DkvStages::s(11) == 17, "d = 64");
+
+// d = 128: what lies behind which of the 128 matrix instructions (ticks) of a unit: S of the first 32 keys | S of the other 32 | dP | dV | dK.
+struct DkvTicks {
+  static constexpr int KS = 8, PH = 4 * KS, T = 4 * PH;  // LDS operands of a phase; ticks of a phase, of a unit
+  static constexpr int kAhead = 4;                       // Q operands of a unit that are read in the unit before
+  static constexpr int kRowsReady = T - 14;              // the rows of the next unit are waited for here
+  enum Kind { Q, DP_INIT, DO, V, DO_T, Q_T, S_INIT, Q_NEXT };
+  struct Read {
+    int tick, use;  // behind which instruction it is requested, ahead of which one it is waited for
+    Kind kind;
+    int i, part;
+  };
+  static constexpr int N = (KS - kAhead) + 2 + KS + KS + 2 * KS + 2 * KS + 2 + kAhead;
+  Read r[N] = {};
+  int issued[T + 1] = {};  // LDS reads ahead of tick t
+  int newer[T] = {};       // of those, how many are behind the last one that it needs; -1: it needs none that an earlier tick has not
+  // P and dS as operations of their own (see the unit), and how many of them lie ahead of tick t
+  enum Op { MUL, EXP, CVT };  // of an item: products of its two values, exponentials of both, conversion of the pair
+  struct Work {
+    Op op;
+    int item, i;
+  };
+  static constexpr int kPOps = 80, kSOps = 48;
+  Work pw[kPOps] = {}, sw[kSOps] = {};
+  static constexpr int kFirstP = PH / 2 + 2, kFirstS = 2 * PH + 2;  // (two instructions behind the S, the dP they need)
+  int p[T + 1] = {}, s[T + 1] = {};
+  // the copies of Q rows (of the S phase) and of dO_f rows (of the dK phase) behind tick t, -1: none.  A copy in 64 cycles is what the
+  // four wavefronts of a compute unit get through.
+  static constexpr int q_copy(int t) { return t < PH && t % 4 == 1 ? t / 4 : -1; }
+  static constexpr int do_copy(int t) { return t > 3 * PH && t < 3 * PH + 16 && t % 2 == 1 ? (t - 3 * PH) / 2 : -1; }
+  static constexpr int cost(Op op) { return op == EXP ? 9 : 5; }
+  constexpr int fixed_cost(int t) const {  // cycles of what has its place behind tick t
+    int c = 8 * (issued[t + 1] - issued[t]) + (newer[t] >= 0 ? 4 : 0);
+    if (q_copy(t) >= 0) c += 8 + (q_copy(t) % 4 == 0 ? 4 : 0);
+    if (do_copy(t) >= 0) c += 8 + (do_copy(t) % 4 == 0 ? 4 : 0);
+    return c;
+  }
+  // `ops` operations dealt to the ticks from .. to - 1 so that all of them take about the same time
+  constexpr void deal(int (&ahead)[T + 1], const Work* w, int ops, int from, int to) {
+    int total = 0, fixed = 0, spent = 0, n = 0;
+    for (int t = from; t < to; ++t) total += fixed_cost(t);
+    for (int i = 0; i < ops; ++i) total += cost(w[i].op);
+    for (int t = 0; t < T; ++t) {
+      ahead[t] = n;
+      if (t < from || t >= to) continue;
+      fixed += fixed_cost(t);
+      while (n < ops && (t == to - 1 || (fixed + spent + cost(w[n].op) / 2) * (to - from) <= total * (t - from + 1))) spent += cost(w[n++].op);
+    }
+    ahead[T] = n;
+  }
+  constexpr DkvTicks() {
+    int n = 0;
+    auto add = [&](int tick, int use, Kind kind, int i, int part) { r[n++] = Read{tick, use, kind, i, part}; };
+    // Operands are waited for in pairs, 8 ticks (128 cycles) behind the request of the second one.
+    add(0, 8, Q, 4, 0);
+    add(1, 8, Q, 5, 0);
+    add(4, 12, Q, 6, 0);
+    add(5, 12, Q, 7, 0);
+    add(8, PH, DP_INIT, 0, 0);
+    add(10, PH, DP_INIT, 1, 0);
+    for (int y = 0; y < KS / 2; ++y) {
+      const int at = PH + 8 * y;
+      add(y == 0 ? 12 : at - 14, at, V, 2 * y, 0);
+      add(y == 0 ? 14 : at - 12, at, V, 2 * y + 1, 0);
+      add(y == 0 ? 15 : at - 10, at, DO, 2 * y, 0);
+      add(y == 0 ? 16 : at - 8, at, DO, 2 * y + 1, 0);
+    }
+    for (int ph = 2; ph < 4; ++ph)
+      for (int x = 0; x < KS; ++x)
+        for (int part = 0; part < 2; ++part) {
+          const int at = ph * PH + 8 * (x / 2);
+          add(at - 14 + 4 * (x % 2) + 2 * part, at, ph == 2 ? DO_T : Q_T, x, part);
+        }
+    add(T - 13, T, S_INIT, 0, 0);
+    add(T - 12, T, Q_NEXT, 0, 0);
+    add(T - 11, T, S_INIT, 1, 0);
+    add(T - 10, T, Q_NEXT, 1, 0);
+    add(T - 7, T + 4, Q_NEXT, 2, 0);
+    add(T - 5, T + 4, Q_NEXT, 3, 0);
+    for (int i = 1; i < N; ++i)  // in the order of issue
+      for (int j = i; j > 0 && r[j].tick < r[j - 1].tick; --j) {
+        const Read x = r[j];
+        r[j] = r[j - 1];
+        r[j - 1] = x;
+      }
+    for (int t = 0; t < T; ++t) {
+      for (int i = 0; i < N; ++i) issued[t + 1] += r[i].tick <= t;
+      int last = -1;
+      for (int i = 0; i < N; ++i)
+        if (r[i].use % T == t) last = i;
+      newer[t] = last < 0 ? -1 : issued[t] - last - 1 + (r[last].use == t ? 0 : N);  // (the next unit's: read in the unit before)
+    }
+    // P: an item's first exponential, the products of the next, the second exponential, the conversion of the item before; dS: the
+    // products of an item, the conversion of the one before.
+    n = 0;
+    pw[n++] = {MUL, 0, 0};
+    pw[n++] = {MUL, 0, 1};
+    for (int g = 0; g < 16; ++g) {
+      pw[n++] = {EXP, g, 0};
+      if (g < 15) pw[n++] = {MUL, g + 1, 0};
+      if (g < 15) pw[n++] = {MUL, g + 1, 1};
+      pw[n++] = {EXP, g, 1};
+      if (g > 0) pw[n++] = {CVT, g - 1, 0};
+    }
+    pw[n++] = {CVT, 15, 0};
+    n = 0;
+    for (int k = 0; k < 17; ++k) {
+      if (k < 16) sw[n++] = {MUL, k, 0};
+      if (k > 0) sw[n++] = {CVT, k - 1, 0};
+      if (k < 16) sw[n++] = {MUL, k, 1};
+    }
+    deal(p, pw, kPOps, kFirstP, 2 * PH - 1);
+    deal(s, sw, kSOps, kFirstS, 3 * PH - 1);
+  }
+};
+// P of the other keys two instructions behind their S
+static_assert(DkvTicks().pw[DkvTicks().p[DkvTicks::PH + 2] - 1].item < 8, "P");
+
 // What the coarse backward of a short sequence is formed from (see coarse_small.h).
 struct SmallCoarseArgs {
   const float *qc, *kc, *vc, *doc, *lse_c, *dot;
@@ -116,17 +239,18 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
                                           const uint64_t* __restrict__ mask, uint4* __restrict__ dk, uint4* __restrict__ dv,
                                           int m_blocks, int stream, const RasterMap& raster, const SmallCoarseArgs& sc,
                                           SmallCoarse<D>* lc) {
-  using TL = Tile<D>;
+  constexpr bool kNarrow = D == 128;  // 16x16x32 matrix instructions, else 32x32x16
+  using TL = std::conditional_t<kNarrow, NarrowTile<D>, Tile<D>>;
   using SH = DkvShape<D, NW>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
   constexpr int EPR = NW / 2;              // list entries a round of units takes
   constexpr int HALF = SH::HALF, STAGE = SH::STAGE, NST = SH::NST;
   constexpr int NC = HALF / 1024;          // copy instructions per 32 rows
-  constexpr int kAhead = 2;                // steps between an operand's LDS read and its use
+  constexpr int kAhead = kNarrow ? DkvTicks::kAhead : 2;  // Q operands that are read ahead of their unit
   constexpr int NCD = 2 * DVB;             // steps of the dV and of the dK phase
   constexpr int OS = D;
   static_assert(HALF % 256 == 0 && STAGE % 256 == 0, "the operand addresses XOR the bits below 256");
-  static_assert(KS == NCD && NC == KS && kAhead == 2, "phase interleave");
+  static_assert(KS == NCD && NC == KS && (!kNarrow || KS == DkvTicks::KS), "phase interleave");
   static_assert(!COARSE || (NT == kSmallThreads && !SUB), "the coarse backward takes 256 threads");
 
   // Start-up: one descriptor load (key block, begin and end of its run of the block's list, slot; the
@@ -142,7 +266,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   if (desc.x < 0) return;
   const int j = desc.x, beg = desc.y, n = desc.z - desc.y, slot = run_slot(desc.w);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, h = lane >> 5;
+  const int l32 = lane & 31, h = lane >> 5, l16 = lane & 15, g16 = lane >> 4;
   const long long rows0 = bh * (long long)Nc * kTile;
   const int32_t* my_col = col + bh * (long long)Nc * K + beg;
   const uint64_t kmask = mask[j];
@@ -153,14 +277,18 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   asm volatile("" : "+v"(col_v));
   const int first = wave >> 1, half = wave & 1;  // this wavefront's entries: first, first + EPR, ...
   const int nu = n > first ? (n - first + EPR - 1) / EPR : 0;
-  auto entry = [&](int u) {  // list entry of unit u (ascending u)
+  auto load_chunk = [&](int u) {  // that of unit u (ascending u)
     const int e = first + EPR * u;
     if (__builtin_expect((e >> 6) != chunk, 0)) {
       chunk = e >> 6;
       col_v = my_col[list_slot(chunk, lane, n)];
       asm volatile("" : "+v"(col_v));  // its wait stays inside this branch
     }
-    return __builtin_amdgcn_readlane(col_v, e & 63);
+  };
+  auto entry_of = [&](int u) { return __builtin_amdgcn_readlane(col_v, (first + EPR * u) & 63); };
+  auto entry = [&](int u) {  // list entry of unit u
+    load_chunk(u);
+    return entry_of(u);
   };
   // a unit's bytes: its block's offset from this wavefront's first rows of the (b, h) (at most 4096 blocks of 16 KiB)
   auto unit_off = [&](int raw) { return (unsigned)(SUB ? raw & 0xffff : raw) * (unsigned)TL::BYTES; };
@@ -227,30 +355,44 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       }
     }
   }
-  f32x16 dka[DVB][2], dva[DVB][2];
+  // [columns of d][keys], in blocks of the matrix instruction's size
+  constexpr int MT = kNarrow ? 16 : 32, XB = D / MT, KB = kTile / MT, AV = kNarrow ? 4 : 16;
+  using Acc = std::conditional_t<kNarrow, f32x4, f32x16>;
+  Acc dka[XB][KB], dva[XB][KB];
 #pragma unroll
-  for (int x = 0; x < DVB; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < KB; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) { dka[x][b][i] = 0.f; dva[x][b][i] = 0.f; }
+      for (int i = 0; i < AV; ++i) { dka[x][b][i] = 0.f; dva[x][b][i] = 0.f; }
 #pragma unroll
-  for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
+  for (int x = 0; x < XB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) asm volatile("" : "+a"(dka[x][b]), "+a"(dva[x][b]));
+    for (int b = 0; b < KB; ++b) asm volatile("" : "+a"(dka[x][b]), "+a"(dva[x][b]));
   if (COARSE) small_coarse_bwd<D, true>(*lc, Nc, j, bh * Nc, scale, sc.qc, sc.kc, sc.vc, sc.doc, sc.lse_c, sc.dot, tid);
   constexpr int G = 2 * NC + 1;  // copies of one unit
   if (nu >= NST - 1) wait_vmcnt<(NST - 1) * G>();
   else wait_vmcnt<0>();
   __syncthreads();
-  bf16x8 kreg[2][KS], vreg[KS];  // K, and V of the first 32 keys
+  // K, and V of the first 32 keys; kNarrow: operand [half][i] is contraction step i / 2 of the keys 32 * half + 16 * (i % 2) ..
+  bf16x8 kreg[2][KS], vreg[KS];
   {
-    const int lane_k = TL::rowmajor_lane(0, lane) + LAST;
+    if constexpr (kNarrow) {
+      const int lane_k = TL::rowmajor_lane(lane) + LAST;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      kreg[0][s] = TL::rowmajor_at(smem, lane_k, s);
-      kreg[1][s] = TL::rowmajor_at(smem + NST * STAGE, lane_k, s);
-      vreg[s] = TL::rowmajor_at(smem + HALF, lane_k, s);
+      for (int s = 0; s < KS; ++s) {
+        kreg[0][s] = TL::rowmajor_at(smem, lane_k, s & 1, s >> 1);
+        kreg[1][s] = TL::rowmajor_at(smem + NST * STAGE, lane_k, s & 1, s >> 1);
+        vreg[s] = TL::rowmajor_at(smem + HALF, lane_k, s & 1, s >> 1);
+      }
+    } else {
+      const int lane_k = TL::rowmajor_lane(0, lane) + LAST;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        kreg[0][s] = TL::rowmajor_at(smem, lane_k, s);
+        kreg[1][s] = TL::rowmajor_at(smem + NST * STAGE, lane_k, s);
+        vreg[s] = TL::rowmajor_at(smem + HALF, lane_k, s);
+      }
     }
   }
 #pragma unroll
@@ -264,17 +406,225 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     wait_vmcnt<0>();
   }
 
+  // all units: `body(steady, u, st)` is one, whose rows lie in the wavefront's stage `st` (a constant in the unrolled loop)
+  auto walk = [&](auto body) {
+    int u = 0;
+    for (; u + 2 * NST - 1 < nu; u += NST) {
+#pragma unroll
+      for (int st = 0; st < NST; ++st) body(std::true_type{}, u + st, st);
+    }
+    for (; u + NST < nu; ++u) body(std::true_type{}, u, u % NST);
+    for (; u < nu; ++u) body(std::false_type{}, u, u % NST);
+  };
+  const int wave_rows = (int)(HALF + wave * (NST * STAGE));  // this wavefront's stages
+  if constexpr (kNarrow) {
+  using TK = DkvTicks;
+  constexpr TK ticks;
+  constexpr int PH = TK::PH;
+  const int lane_q = TL::rowmajor_lane(lane) + wave_rows, lane_v = TL::rowmajor_lane(lane), lane_b = TL::transposed_lane(lane) + wave_rows;
+  const int lane_r = wave_rows + 2 * HALF + 16 * g16;
+  // initial value of an accumulator: the row terms of rows 16*b + 4*g16 ..
+  auto row_init = [&](int off, int which, int b) { return *(const f32x4*)(smem + (lane_r + off) + which * 128 + b * 64); };
+  bf16x8 qcur[kAhead];
+  f32x4 sinit[2];
+  if (nu > 0) {
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) {  // (in the order of the loop's)
+      if (s < 2) sinit[s] = row_init(0, 0, s);
+      qcur[s] = TL::rowmajor_at(smem, lane_q, s & 1, s >> 1);
+    }
+  }
+  walk([&](auto steady_tag, int u, int st) {
+    constexpr bool STEADY = decltype(steady_tag)::value;  // the units up to u + NST exist
+    const bool more_q = STEADY || u + NST - 1 < nu;
+    const int st_off = st * STAGE, next_st = st == NST - 1 ? 0 : st_off + STAGE;
+    const int prev_st = st == 0 ? (NST - 1) * STAGE : st_off - STAGE;
+    // (the addresses of V, and with key cubes of 16 all of them, are rebuilt per unit: registers are short)
+    int lv = lane_v, lq = lane_q, lb = lane_b;
+    asm volatile("" : "+v"(lv));
+    if (SUB) asm volatile("" : "+v"(lq), "+v"(lb));
+    const unsigned char *Qs = smem + st_off, *Ds = Qs + HALF, *Qn = smem + next_st;
+    // Operand s of Q and dO_f: query rows 16*(s%2) .., contraction step s/2.  S and dP: [query block][key block].
+    bf16x8 qa[KS], da[KS], va[KS];
+    bf16x4 dt[KS][2], qt[KS][2];
+    f32x4 S[2][4], P[2][4], dpinit[2], init[2][2];
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) qa[s] = qcur[s];
+    auto reads = [&](auto number) {  // those behind tick t
+      constexpr int t = decltype(number)::value;
+      constexpr int n = ticks.issued[t + 1] - ticks.issued[t];
+      static_assert(n <= 1, "at most one");
+      if constexpr (n == 1) {
+        constexpr TK::Read r = ticks.r[ticks.issued[t]];
+        if constexpr (r.kind == TK::Q) qa[r.i] = TL::rowmajor_at(Qs, lq, r.i & 1, r.i >> 1);
+        if constexpr (r.kind == TK::DP_INIT) dpinit[r.i] = row_init(st_off, 1, r.i);
+        if constexpr (r.kind == TK::DO) da[r.i] = TL::rowmajor_at(Ds, lq, r.i & 1, r.i >> 1);
+        if constexpr (r.kind == TK::V) va[r.i] = TL::rowmajor_at(smem, lv, r.i & 1, r.i >> 1);
+        if constexpr (r.kind == TK::DO_T) dt[r.i][r.part] = TL::transposed_half(Ds, lb, r.i, r.part);
+        if constexpr (r.kind == TK::Q_T) qt[r.i][r.part] = TL::transposed_half(Qs, lb, r.i, r.part);
+        if constexpr (r.kind == TK::S_INIT) sinit[r.i] = row_init(next_st, 0, r.i);
+        if constexpr (r.kind == TK::Q_NEXT) qcur[r.i] = TL::rowmajor_at(Qn, lq, r.i & 1, r.i >> 1);
+      }
+    };
+    auto wait = [&](auto number) {
+      constexpr int n = ticks.newer[decltype(number)::value];
+      if constexpr (n >= 0) {
+        wait_lgkmcnt<(n < 15 ? n : 15)>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto both = [](const bf16x4 (&x)[2]) { return __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7); };
+    auto opnd = [](const uint4& x) { return __builtin_bit_cast(bf16x8, x); };
+    auto put = [](uint4& u4, int w, uint32_t x) {
+      if (w == 0) u4.x = x;
+      if (w == 1) u4.y = x;
+      if (w == 2) u4.z = x;
+      if (w == 3) u4.w = x;
+    };
+    // P and dS in operations none of which needs the result of the one before it.  Item k of 16: two values of a key column, four
+    // items, the operand of a key block, one after the other.
+    uint4 pb[4], sb[4];
+    float xp[2][2], xd[2][2];  // products of an item, by its parity
+    auto p_ops = [&](auto from, auto count) {
+      in_steps<decltype(count)::value>([&](auto number) {
+        constexpr TK::Work w = ticks.pw[decltype(from)::value + decltype(number)::value];
+        constexpr int it = w.item;
+        f32x4& x = S[(it >> 1) & 1][it >> 2];
+        if constexpr (w.op == TK::MUL) {
+          xp[it & 1][w.i] = x[2 * (it & 1) + w.i] * sl2;
+          asm volatile("" : : "v"(xp[it & 1][w.i]));  // (pure arithmetic has no place of its own in the order: tie it to this tick)
+        } else if constexpr (w.op == TK::EXP) {
+          const float e = fast_exp2(xp[it & 1][w.i]);
+          asm volatile("" : : "v"(e));
+          x[2 * (it & 1) + w.i] = e;
+        } else {
+          const uint32_t pp = pack_bf16(x[2 * (it & 1)], x[2 * (it & 1) + 1]);
+          put(pb[it >> 2], it & 3, pp);
+          asm volatile("" : : "v"(pp));
+        }
+      });
+    };
+    auto s_ops = [&](auto from, auto count) {
+      in_steps<decltype(count)::value>([&](auto number) {
+        constexpr TK::Work w = ticks.sw[decltype(from)::value + decltype(number)::value];
+        constexpr int it = w.item;
+        if constexpr (w.op == TK::MUL) {
+          xd[it & 1][w.i] = S[(it >> 1) & 1][it >> 2][2 * (it & 1) + w.i] * P[(it >> 1) & 1][it >> 2][2 * (it & 1) + w.i];
+          asm volatile("" : : "v"(xd[it & 1][w.i]));
+        } else {
+          const uint32_t ss = pack_bf16(xd[it & 1][0], xd[it & 1][1]);
+          put(sb[it >> 2], it & 3, ss);
+          asm volatile("" : : "v"(ss));
+        }
+      });
+    };
+    // ---- S, the keys 0 .. 31 first: their P begins while the others' S is multiplied
+    if (SUB) {
+      // key row l16 of key block b belongs to key cube 2*(b/2) + (row/2)%2 of the block's four; the rows of the others get a large
+      // negative initial value
+      const unsigned sel = (unsigned)(raws[0] >> 16) >> ((l16 >> 1) & 1);
+      const float bias[2] = {sel & 1u ? 0.f : -30000.f, sel & 4u ? 0.f : -30000.f};
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) init[a][hf][i] = sinit[a][i] + bias[hf];
+      asm volatile("s_nop 1" : "+v"(init[0][0]), "+v"(init[0][1]), "+v"(init[1][0]), "+v"(init[1][1]));  // (two wait states)
+    }
+    const unsigned char* gq = qw + next_off;
+    int raw = 0;
+    unsigned off = 0;
+    in_steps<PH>([&](auto number) {
+      constexpr int t = decltype(number)::value, hf = t / (PH / 2), s = t % (PH / 2) / 2, b = t & 1, copy = TK::q_copy(t);
+      wait(number);
+      if (copy >= 0 && more_q) copy_aim(wbase + prev_st, copy);
+      f32x4& x = S[s & 1][2 * hf + b];
+      const bf16x8 kop = kreg[hf][(s & ~1) | b];
+      if (s < 2) mfma_v_from(x, qa[s], kop, SUB ? init[s & 1][hf] : sinit[s & 1]);
+      else mfma_v(x, qa[s], kop);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t % (PH / 2) == 5) {  // (initial values are not written over while the matrix instructions may still read them)
+        if (SUB) asm volatile("" : : "v"(init[0][hf]), "v"(init[1][hf]));
+        else if (hf == 1) asm volatile("" : : "v"(sinit[0]), "v"(sinit[1]));
+      }
+      if (copy >= 0 && more_q) copy_piece(gq, wbase + prev_st, copy, true);
+      if (t == 15 && more_q) copy_rows(next_off, wbase + prev_st + 2 * HALF);  // (between two groups of copies: it has an M0 of its own)
+      // the list entry of unit u + NST, a chain of scalar instructions, in parts
+      if (STEADY && t == 7) load_chunk(u + NST);
+      if (STEADY && t == 10) raw = entry_of(u + NST);
+      if (STEADY && t == 14) off = unit_off(raw);
+      reads(number);
+      p_ops(std::integral_constant<int, ticks.p[t]>{}, std::integral_constant<int, ticks.p[t + 1] - ticks.p[t]>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- dP
+    in_steps<PH>([&](auto number) {
+      constexpr int t = PH + decltype(number)::value, s = (t - PH) / 4, b = t & 3;
+      const std::integral_constant<int, t> tick;
+      wait(tick);
+      const bf16x8 vop = b < 2 ? vreg[(s & ~1) | (b & 1)] : va[(s & ~1) | (b & 1)];
+      if (s < 2) mfma_v_from(P[s & 1][b], da[s], vop, dpinit[s & 1]);
+      else mfma_v(P[s & 1][b], da[s], vop);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t == PH + 9) asm volatile("" : : "v"(dpinit[0]), "v"(dpinit[1]));
+      reads(tick);
+      p_ops(std::integral_constant<int, ticks.p[t]>{}, std::integral_constant<int, ticks.p[t + 1] - ticks.p[t]>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- dV
+    in_steps<PH>([&](auto number) {
+      constexpr int t = 2 * PH + decltype(number)::value, x = (t - 2 * PH) / 4, b = t & 3;
+      const std::integral_constant<int, t> tick;
+      wait(tick);
+      mfma_a(dva[x][b], both(dt[x]), opnd(pb[b]));
+      __builtin_amdgcn_sched_barrier(0);
+      reads(tick);
+      s_ops(std::integral_constant<int, ticks.s[t]>{}, std::integral_constant<int, ticks.s[t + 1] - ticks.s[t]>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- dK; the dO_f rows of this stage are done with: refill them (unit u + NST), then wait for the Q
+    // rows of the next unit -- everything issued before this phase's copies but the dO_f, Q groups after them
+#pragma unroll
+    for (int s = 0; s + 1 < NST; ++s) raws[s] = raws[s + 1];
+    if (STEADY) {
+      raws[NST - 1] = raw;
+      next_off = off;
+    }
+    const unsigned char* gd = dw + next_off;
+    in_steps<PH>([&](auto number) {
+      constexpr int t = 3 * PH + decltype(number)::value, x = (t - 3 * PH) / 4, b = t & 3, copy = TK::do_copy(t);
+      static_assert(copy < 0 || t < TK::kRowsReady, "the wait counts this phase's copies");
+      const std::integral_constant<int, t> tick;
+      wait(tick);
+      if (STEADY && copy >= 0) copy_aim(wbase + st_off + HALF, copy);
+      mfma_a(dka[x][b], both(qt[x]), opnd(sb[b]));
+      __builtin_amdgcn_sched_barrier(0);
+      if (STEADY && copy >= 0) copy_piece(gd, wbase + st_off + HALF, copy, true);
+      if (t == TK::kRowsReady) {
+        const int left = nu - 1 - (u + 1);  // units after the next one
+        if (STEADY) wait_vmcnt<(NST - 2) * G + NC>();
+        else if (NST > 2 && left == 2) wait_vmcnt<2 * G>();
+        else if (NST > 2 && left == 1) wait_vmcnt<G>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      reads(tick);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  });
+  } else {
   // SUB: A operand (1 in contraction slot 0) and the bit of the entry that selects this lane's key cube
   bf16x8 ones_a = {0, 0, 0, 0, 0, 0, 0, 0};
   if (SUB && h == 0) ones_a[0] = (__bf16)1.f;
 
-  const int lane_q = TL::rowmajor_lane(0, lane) + (int)(HALF + wave * (NST * STAGE));
+  const int lane_q = TL::rowmajor_lane(0, lane) + wave_rows;
   const int lane_v = TL::rowmajor_lane(0, lane);
   int lane_b0, lane_b1;
   TL::transposed_lane(0, lane, lane_b0, lane_b1);
-  lane_b0 += (int)(HALF + wave * (NST * STAGE));
-  lane_b1 += (int)(HALF + wave * (NST * STAGE));
-  const int lane_r = (int)(HALF + wave * (NST * STAGE)) + 2 * HALF + 16 * h;
+  lane_b0 += wave_rows;
+  lane_b1 += wave_rows;
+  const int lane_r = wave_rows + 2 * HALF + 16 * h;
 
   // initial value of an accumulator: the row term of rows 8*(i/4) + 4*h + i%4
   auto row_init = [&](int off, int which) {
@@ -296,8 +646,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     for (int s = 0; s < kAhead; ++s) qcur[s] = TL::rowmajor_at(smem, lane_q, s);
   }
 
-  // One unit, whose rows lie in the wavefront's stage `st` (a constant in the unrolled loop).
-  auto body = [&](auto steady_tag, int u, int st) {
+  walk([&](auto steady_tag, int u, int st) {
     constexpr bool STEADY = decltype(steady_tag)::value;  // the units up to u + NST exist
     const bool more_q = STEADY || u + NST - 1 < nu;
     const int st_off = st * STAGE, next_st = st == NST - 1 ? 0 : st_off + STAGE;
@@ -440,7 +789,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
         }
       }
     };
-    using DS = DkvStages<D>;
+    using DS = DkvStages;
     in_steps<KS>([&](auto number) {
       constexpr int s = decltype(number)::value, m = KS + s;
       wait_lgkmcnt<reads_in(m - 1)>();
@@ -507,14 +856,8 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       s_stages(DS::s(SLOTS + j), DS::s(SLOTS + j + 1));
       __builtin_amdgcn_sched_barrier(0);
     });
-  };
-  int u = 0;
-  for (; u + 2 * NST - 1 < nu; u += NST) {
-#pragma unroll
-    for (int st = 0; st < NST; ++st) body(std::true_type{}, u + st, st);
+  });
   }
-  for (; u + NST < nu; ++u) body(std::true_type{}, u, u % NST);
-  for (; u < nu; ++u) body(std::false_type{}, u, u % NST);
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix results land before they are read
   __builtin_amdgcn_sched_barrier(0);
 
@@ -548,14 +891,14 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
       {
         float* Op = bufs + wave * 64 * OS;
 #pragma unroll
-        for (int x = 0; x < DVB; ++x)
+        for (int x = 0; x < XB; ++x)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+          for (int b = 0; b < KB; ++b)
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const f32x16& a = pass == 0 ? dka[x][b] : dva[x][b];
-              *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-                  make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
+            for (int g4 = 0; g4 < AV / 4; ++g4) {
+              const Acc& a = pass == 0 ? dka[x][b] : dva[x][b];
+              const int at = kNarrow ? merge_offset(b * 16 + l16, x * 16 + 4 * g16, OS) : merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS);
+              *(float4*)&Op[at] = make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
             }
       }
       __syncthreads();

@@ -127,6 +127,41 @@ struct Tile {
   }
 };
 
+// The same rows for the operands of 16x16x32 matrix instructions, with a swizzle of its own:
+//   - row-major reads: a phase of the LDS takes 16 lanes, of rows {0..3, 12..15} and {4..11} with neighbouring chunks (2j, 2j + 1
+//     or the other way round): all 16 slots are hit if swz ^ 1 maps either half of the rows onto the slots of the other one's;
+//   - transposed reads: a phase takes 32 lanes, 8 consecutive rows x 32 contiguous bytes: swz / 2 differs in rows 0..7 and in 8..15.
+template <int D>
+struct NarrowTile {
+  static constexpr int CPR = Tile<D>::CPR, ROW_BYTES = Tile<D>::ROW_BYTES, BYTES = Tile<D>::BYTES, RPI = Tile<D>::RPI;
+
+  __device__ static __forceinline__ int swz(int r) {
+    const int low = (r >> 3) & 1;
+    if (D == 128) return (((r & 7) ^ (low << 2)) << 1) | low;
+    return ((((r >> 1) & 3) ^ (low << 1)) << 1) | low;
+  }
+  __device__ static __forceinline__ int off(int r, int c) { return r * ROW_BYTES + ((c ^ swz(r)) << 4); }
+
+  // Operand whose 16-index is the tile ROW (16*b ..) and whose contraction index runs along D: for contraction step s lane l
+  // supplies tile[16*b + l%16][32*s + 8*(l/16) .. +7]  (one 16-byte read; the lane's part of the address is split off as above).
+  __device__ static __forceinline__ int rowmajor_lane(int lane) { return off(lane & 15, lane >> 4); }
+  __device__ static __forceinline__ bf16x8 rowmajor_at(const unsigned char* tile, int lane_part, int b, int s) {
+    return *(const bf16x8*)(tile + b * 16 * ROW_BYTES + (lane_part ^ (s << 6)));
+  }
+
+  // Operand whose 16-index runs along D (columns 16*x ..) and whose contraction index is the tile ROW (32 of them), in the order in
+  // which two 16x16 accumulators, one below the other, hold their rows: element j of lane l is row 16*(j/4) + 4*(l/16) + j%4.
+  // Two transposing 8-byte reads, one per 16 rows; in each 16-lane block, lanes 4e..4e+3 read row e.
+  __device__ static __forceinline__ int transposed_lane(int lane) {
+    const int L = lane & 15;
+    return off(4 * (lane >> 4) + (L >> 2), (L & 3) >> 1) + (L & 1) * 8;
+  }
+  __device__ static __forceinline__ bf16x4 transposed_half(const unsigned char* tile, int lane_part, int x, int part) {
+    const unsigned char* p = tile + part * 16 * ROW_BYTES;  // (swz(r + 16) == swz(r))
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + (lane_part ^ (x << 5))));
+  }
+};
+
 // fp32 merge buffers [64][D] in LDS (partial results of the wavefronts that share output rows).
 // A row is D*4 bytes, a multiple of the 256 bytes the 64 banks span, so the 32 lanes of an
 // accumulator column (one row each) would all hit the same banks; the 16-byte chunks of a row are

@@ -210,6 +210,16 @@ __device__ __forceinline__ void mfma_v_from(f32x16& d, bf16x8 a, bf16x8 b, const
 __device__ __forceinline__ void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
+// 16x16x32 forms: half the passes, so what is far enough from a 32x32x16 instruction is far enough from one of these
+__device__ __forceinline__ void mfma_v(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v_from(f32x4& d, bf16x8 a, bf16x8 b, const f32x4& c) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
+}
+__device__ __forceinline__ void mfma_a(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
 // matrix results land before the vector instructions behind this read them, and the other way round
 __device__ __forceinline__ void mfma_fence() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 

@@ -8,8 +8,9 @@ landed before their place is used for anything else.
   matrix result, then anything but the accumulator of the next one         12
   accumulator input of a matrix instruction, then a vector write over it    8 (where it is not its result)
 (the "manually inserted wait states" table of the CDNA3 ISA document; the last two for matrix instructions of 8 passes,
-v_mfma_f32_32x32x16_bf16, the only ones here, with a pass to spare.  A matrix instruction behind another starts when
-that one's 8 passes are over, which counts in the last two.  The 2 count instructions, whatever lies between.)
+v_mfma_f32_32x32x16_bf16, with a pass to spare.  A matrix instruction behind another starts when
+that one's 8 passes are over, which counts in the last two.  The 2 count instructions, whatever lies between.
+v_mfma_f32_16x16x32_bf16 has 4 passes and needs 8 and 4 states: where the rule for 8 passes holds, counting 8 for each between, so does that.)
 """
 import os
 import re

@@ -9,36 +9,109 @@
 #include <type_traits>
 
 #include "fine_bwd_dkv.h"
+#include "ticks.h"
 
 namespace vsa {
 
 // Workgroups of two wavefronts (four in small launches) that stream units of 32 keys like the forward's (fine_fwd.hip),
-// each of a block of its own or sharing one (paired_workgroups).  A unit is six groups of d/16 matrix instructions, query half by query half:
-//   S 0 | S 1 | dP 0 | dP 1 | dQ 0 | dQ 1
-// so that the vector work of one half, P = exp2(S sl2 - lse) and dS = P dP', lies behind the matrix work of the other
-// without a second unit in flight; the LDS operands of a product stay in registers for its second half, so
-// each feeds two matrix instructions.  The row terms are per-lane scalars here (a lane owns a query column): lse goes
+// each of a block of its own or sharing one (paired_workgroups).  A unit is S^T, dP^T and dQ^T, 16 queries (d = 128) or 32 after the other,
+// so that the vector work of some, P = exp2(S sl2 - lse) and dS = P dP', lies behind the matrix work of the others
+// without a second unit in flight; the LDS operands of a product stay in registers for all of them.
+// The row terms are per-lane scalars here (a lane owns query columns): lse goes
 // into the exponential's fma, -Delta is the initial value of the dP accumulators.
 //
 // d = 128: one wavefront per SIMD; dQ takes 128 of the accumulation registers and Q and dO_f the other 128 (a
-// matrix instruction reads an operand from either file).  d = 64: two wavefronts per SIMD, whose 256 registers do not
-// hold both halves' S and dP: there S 1 follows dP 0, and -Delta is added in vector arithmetic.
+// matrix instruction reads an operand from either file).  16x16x32 instructions, 96 a unit, with what lies behind each dealt by DqTicks
+// (ticks.h; why the small ones, see fine_bwd_dkv.h: 4.2 other instructions per 32 cycles of matrix work).  Pad keys' rows of S^T start from
+// a large negative value, which is formed where a unit or the one before has some.
+// d = 64: two wavefronts per SIMD, whose 256 registers do not
+// hold both halves' S and dP, and 32x32x16 instructions: S 0 | dP 0 | S 1 | dP 1 | dQ 0 | dQ 1, -Delta is added in vector arithmetic.
 //
-// What bounds it: a unit is 48 matrix instructions (1536 cycles of the matrix pipe) and 208 others, 203 where all blocks are shared,
-// all issued by one wavefront, in 1930 cycles (d = 128; 2160 with the copies in two runs, one behind every matrix instruction of dP 1
-// and dQ 0, two transposing reads behind one and items of P whose instructions waited for one another: costs of instructions in
-// fine_fwd.hip, by which 80 to 145 cycles lie between two units, where list.get is, 75 to 90 and 50 at the seam of S 1 and dP 0, and 8
-// to 25 behind the matrix instructions of S 0 and the end of dQ 1), at a clock that falls as the pipe fills (1.6 to 1.75 GHz at 39936
-// tokens).  Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12 heads, d =
+// What bounds it (d = 128): the clock, which falls as the pipe fills, and instruction issue: a unit is 96 matrix instructions (1536 cycles of
+// the matrix pipe) and 204 others, 1920 cycles by the costs of ticks.h, about as many as the 1930 of the form before it, with 48
+// large instructions at a clock 7 % lower (39936 tokens: 1.72 GHz, now 1.84): 1468 -> 1405 us of 39936 tokens, 12 heads, top-78.  With dK/dV's
+// like form, whole steps: 16384 tokens, top-32 961 -> 922 us, 39936 tokens, top-78 4850 -> 4696, B = 2, 16 heads, top-128 of 256, local
+// lists 7953 -> 7535, 256-token cubes 918 -> 881, the op at 13338 tokens 453 -> 444.  More even still: 16 to 24 cycles lie behind most matrix
+// instructions, 28 to 46 behind those with a part of the list entry's scalar chain, 16 (the pipe's own) behind the last 15.
+// Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12 heads, d =
 // 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of the time.
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,
-// top-78 of 624: 1.61 -> 1.49 ms (1.23 PFLOP/s executed); 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
+// top-78 of 624: 1.61 -> 1.49 ms; 16384 tokens, top-32 of 256: 303 -> 277 us; B = 2, 16 heads, top-128
 // of 256, local lists: 2.83 -> 2.58 ms; d = 64, B = 2, 8 heads, top-32: 220 -> 210 us.
 template <int D, int NW>
 struct DqShape {
   static constexpr int HALF = Tile<D>::BYTES / 2;  // 32 rows
   static constexpr int LDS = NW * 4 * HALF;        // per wavefront: K of two units, V of two units
 };
+
+// d = 128: what lies behind which of the 96 matrix instructions of a unit (ticks.h): S of the queries 0 .. 15, 16 .. 31, ... | dP likewise |
+// dQ likewise.
+struct DqTicks : TickTable<96, 32> {
+  static constexpr int KS = 8, PH = 4 * KS;  // LDS operands of a product; its ticks
+  enum Kind { V, K_T, K_NEXT };
+  static constexpr int kFirstCopyV = PH + 2 * KS, kFirstCopyK = 2 * PH + 1;  // of the unit after the next, where V, where K lay
+  static constexpr int kRowsReady = 2 * PH + 12;  // K and V of the next unit are waited for here
+  static constexpr int kTile = 2, kChunk = 4, kRows = 6, kValid = 8;  // the list entry of the unit after the next, a scalar chain, in parts
+  static constexpr int v_copy(int t) { return t >= kFirstCopyV && t < kFirstCopyV + 2 * KS && (t - kFirstCopyV) % 2 == 0 ? (t - kFirstCopyV) / 2 : -1; }
+  static constexpr int k_copy(int t) { return t >= kFirstCopyK && t < kFirstCopyK + 4 * KS && (t - kFirstCopyK) % 4 == 0 ? (t - kFirstCopyK) / 4 : -1; }
+  static constexpr int k_copies_before(int t) { return t <= kFirstCopyK ? 0 : (t - kFirstCopyK + 3) / 4; }
+  // P and dS in operations, and how many of them lie ahead of tick t
+  static constexpr int kPOps = 64, kSOps = 48;
+  Work pw[kPOps] = {}, sw[kSOps] = {};
+  int p[T + 1] = {}, s[T + 1] = {};
+  constexpr DqTicks() {
+    int n = 0;
+    auto add = [&](int tick, int use, int kind, int i, int part) { r[n++] = Read{tick, use, kind, i, part}; };
+    for (int i = 0; i < KS; ++i) add(i, PH, V, i, 0);
+    for (int j = 0; j < 2 * KS; ++j) add(KS + 2 * j, 2 * PH, K_T, j / 2, j & 1);  // (all of them are there before their place is copied over)
+    for (int i = 0; i < KS; ++i) add(kRowsReady + 1 + 2 * i, T + (i & ~1), K_NEXT, i, 0);
+    order_reads();
+    for (int t = 0; t < T; ++t) {
+      if (v_copy(t) >= 0) cycles[t] += kCopy + (v_copy(t) % 4 == 0 ? kScalar : 0);
+      if (k_copy(t) >= 0) cycles[t] += kCopy + (k_copy(t) % 4 == 0 ? kScalar : 0);
+    }
+    // P: an item's first exponential, the arithmetic of the next, its second exponential; dS: the products of an item, the
+    // conversion of the one before
+    n = 0;
+    pw[n++] = {MUL, 0, 0};
+    pw[n++] = {MUL, 0, 1};
+    for (int g = 0; g < 16; ++g) {
+      pw[n++] = {EXP, g, 0};
+      if (g < 15) pw[n++] = {MUL, g + 1, 0};
+      if (g < 15) pw[n++] = {MUL, g + 1, 1};
+      pw[n++] = {EXP, g, 1};
+    }
+    n = 0;
+    for (int k = 0; k < 17; ++k) {
+      if (k < 16) sw[n++] = {MUL, k, 0};
+      if (k > 0) sw[n++] = {CVT, k - 1, 0};
+      if (k < 16) sw[n++] = {MUL, k, 1};
+    }
+    // from two instructions behind the first S, the first dP, to the last dP, the last dQ
+    deal(s, sw, kSOps, PH + KS + 2, 3 * PH - KS - 1);
+    deal(p, pw, kPOps, KS + 2, 2 * PH + 2);
+  }
+  // Every 16 queries' operations lie behind what they need and ahead of what needs them (4 items each).
+  constexpr bool in_order() const {
+    for (int b = 0; b < 4; ++b) {
+      const int s_there = (b + 1) * KS + 2, dp_there = PH + (b + 1) * KS + 2, dq_begins = 2 * PH + b * KS;
+      for (int n = 0; n < p[s_there]; ++n)
+        if (pw[n].item >= 4 * (b + 1)) return false;
+      for (int n = p[dp_there]; n < kPOps; ++n)
+        if (pw[n].item < 4 * (b + 1) && s[dp_there + 1] > 12 * b) return false;
+      for (int n = 0; n < s[dp_there]; ++n)
+        if (sw[n].item >= 4 * (b + 1)) return false;
+      for (int n = s[dq_begins - 1]; n < kSOps; ++n)
+        if (sw[n].item < 4 * (b + 1) && sw[n].op == CVT) return false;
+    }
+    for (int t = 0; t < T; ++t)  // P of an item ahead of its dS
+      for (int n = s[t]; n < s[t + 1]; ++n)
+        for (int m = p[t]; m < kPOps; ++m)
+          if (pw[m].item <= sw[n].item) return false;
+    return true;
+  }
+};
+static_assert(DqTicks().in_order(), "operations of dQ");
 
 // `smem`: DqShape::LDS bytes, aligned to 1024; `masks`: 128 words per wavefront.  `block` of `grid` workgroups.  PAIRS: the
 // first `pairs` of them take two blocks (NW = 2; launches without pairs have instances of their own, as in the forward).  COARSE: the
@@ -50,7 +123,8 @@ __device__ __forceinline__ void dq_block(
     const int32_t* __restrict__ idx, const float* __restrict__ rowd, const float* __restrict__ dqc,
     const uint64_t* __restrict__ mask, uint4* __restrict__ dq, int m_blocks, unsigned blocks, unsigned pairs, int stream,
     const RasterMap& raster, const SmallCoarseArgs& sc, SmallCoarse<D>* lc) {
-  using TL = Tile<D>;
+  constexpr bool kNarrow = D == 128;  // 16x16x32 matrix instructions, else 32x32x16
+  using TL = std::conditional_t<kNarrow, NarrowTile<D>, Tile<D>>;
   using UL = UNITS<TL>;
   using UC = UnitCopy<TL, UL>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32;
@@ -58,7 +132,9 @@ __device__ __forceinline__ void dq_block(
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int G = KS;                 // matrix instructions of a group
   constexpr int OS = D;
-  constexpr int kEvery = D == 128 ? 2 : 1;  // a copy of K behind every other, or every, matrix instruction of the dQ groups
+  // blocks of the matrix instruction's size: columns of d, queries
+  constexpr int MT = kNarrow ? 16 : 32, XB = D / MT, QB = kTile / MT, AV = kNarrow ? 4 : 16, CS = D / (kNarrow ? 32 : 16);
+  using Acc = std::conditional_t<kNarrow, f32x4, f32x16>;
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
   static_assert(G == 2 * DVB && G == NC && G % 4 == 0, "phase interleave: one copy instruction per matrix instruction");
   static_assert(!COARSE || 64 * NW == kSmallThreads, "the coarse backward takes 256 threads");
@@ -67,7 +143,7 @@ __device__ __forceinline__ void dq_block(
   const int tiles = (K + UL::kEntriesPerTile - 1) / UL::kEntriesPerTile;
   const bool same_lists = K == Nc * UL::kEntriesPerTile;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, h = lane >> 5;
+  const int l32 = lane & 31, h = lane >> 5, l16 = lane & 15, g16 = lane >> 4;
   const bool paired = PAIRS && block < pairs;
   const unsigned from = paired ? 0u : pairs, those = paired ? pairs : grid - pairs;
   const unsigned id = same_lists ? block - from : xcd_chunked_id(block - from, those);
@@ -87,11 +163,7 @@ __device__ __forceinline__ void dq_block(
   const unsigned char* vb = (const unsigned char*)uniform_ptr(v + rows0 * CPR);
 
   // dQ and the resident operands: accumulation registers where the kernel has them (one wavefront per SIMD)
-  auto mfma_acc = [](f32x16& acc, bf16x8 a, bf16x8 b) {
-    if (D == 128) mfma_a(acc, a, b);
-    else mfma_v(acc, a, b);
-  };
-  auto pin_acc = [](f32x16& acc) {
+  auto pin_acc = [](Acc& acc) {
     if (D == 128) asm volatile("" : "+a"(acc));
     else asm volatile("" : "+v"(acc));
   };
@@ -130,8 +202,12 @@ __device__ __forceinline__ void dq_block(
   }
   // row terms of the lane's two query columns: -lse*log2(e)/sl2 (-30000 on pad rows: then P = 0 and the row
   // contributes nothing) and -Delta
-  const float* qterm = rowd + 2 * q0 + l32;
-  float nlse[2] = {qterm[0], qterm[64]}, ndelta[2] = {qterm[32], qterm[96]};
+  float nlse[QB], ndelta[QB];
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {  // (per 32 rows: 32 of the first, 32 of the second)
+    const float* qterm = rowd + 2 * q0 + (kNarrow ? 64 * (b >> 1) + 16 * (b & 1) + l16 : 64 * b + l32);
+    nlse[b] = qterm[0], ndelta[b] = qterm[32];
+  }
   list.arrived();
   const unsigned ml0 = __builtin_amdgcn_readfirstlane(lds_address(masks)) + (unsigned)wave * 512u;
   request_masks(list, ml0);
@@ -141,40 +217,52 @@ __device__ __forceinline__ void dq_block(
     copy.all(vb, un[0], lds0 + 2 * HALF);
   };
   if (!paired && nu > 0) copy_first();
-  f32x16 acc[DVB][2];
+  Acc acc[XB][QB];
 #pragma unroll
-  for (int x = 0; x < DVB; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < QB; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[x][b][i] = 0.f;
+      for (int i = 0; i < AV; ++i) acc[x][b][i] = 0.f;
 #pragma unroll
-  for (int x = 0; x < DVB; ++x)  // (zeroed once, right here, while the first copies are in flight)
+  for (int x = 0; x < XB; ++x)  // (zeroed once, right here, while the first copies are in flight)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
-  asm volatile("" : "+v"(nlse[0]), "+v"(nlse[1]), "+v"(ndelta[0]), "+v"(ndelta[1]));
+    for (int b = 0; b < QB; ++b) pin_acc(acc[x][b]);
+#pragma unroll
+  for (int b = 0; b < QB; ++b) asm volatile("" : "+v"(nlse[b]), "+v"(ndelta[b]));
   if (COARSE) small_coarse_bwd<D, false>(*lc, Nc, c, bh * Nc, scale, sc.qc, sc.kc, sc.vc, sc.doc, sc.lse_c, sc.dot, tid);
   wait_vmcnt<0>();
   __builtin_amdgcn_sched_barrier(0);
   if (!paired) __syncthreads();
-  bf16x8 qreg[2][KS], doreg[2][KS];
+  bf16x8 qreg[QB][CS], doreg[QB][CS];  // [queries][contraction step]
   {
     // halves of a wavefront's own: stages 3 and 2 (Q), 1 and 0 (dO_f); shared: stages 3 and 1 of the first two wavefronts
     const unsigned char* base = smem + (paired ? wave * (4 * HALF) : 0);
     const unsigned char* base1 = paired ? base - HALF : base + 4 * HALF;
-    const int lane_q = TL::rowmajor_lane(0, lane);
+    if constexpr (kNarrow) {
+      const int lane_q = TL::rowmajor_lane(lane);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      qreg[0][s] = TL::rowmajor_at(base + 3 * HALF, lane_q, s);
-      qreg[1][s] = TL::rowmajor_at(base1 + 3 * HALF, lane_q, s);
-      doreg[0][s] = TL::rowmajor_at(base + HALF, lane_q, s);
-      doreg[1][s] = TL::rowmajor_at(base1 + HALF, lane_q, s);
+      for (int s = 0; s < CS; ++s)
+#pragma unroll
+        for (int b = 0; b < QB; ++b) {
+          qreg[b][s] = TL::rowmajor_at((b < 2 ? base : base1) + 3 * HALF, lane_q, b & 1, s);
+          doreg[b][s] = TL::rowmajor_at((b < 2 ? base : base1) + HALF, lane_q, b & 1, s);
+        }
+    } else {
+      const int lane_q = TL::rowmajor_lane(0, lane);
+#pragma unroll
+      for (int s = 0; s < CS; ++s) {
+        qreg[0][s] = TL::rowmajor_at(base + 3 * HALF, lane_q, s);
+        qreg[1][s] = TL::rowmajor_at(base1 + 3 * HALF, lane_q, s);
+        doreg[0][s] = TL::rowmajor_at(base + HALF, lane_q, s);
+        doreg[1][s] = TL::rowmajor_at(base1 + HALF, lane_q, s);
+      }
     }
   }
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < QB; ++b)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
+    for (int s = 0; s < CS; ++s) {
       pin_op(qreg[b][s]);
       pin_op(doreg[b][s]);
     }
@@ -193,21 +281,180 @@ __device__ __forceinline__ void dq_block(
   __builtin_amdgcn_sched_barrier(0);
 
   const int my = wave * (4 * HALF);
+  // all units: `body(kind, par, u)` is one.  KIND 2: the units up to u + 2 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
+  auto walk = [&](auto body) {
+    if (nu == 0) return;
+    const std::integral_constant<int, 2> steady;
+    const std::integral_constant<int, 1> inner;
+    const std::integral_constant<int, 0> last;
+    int u = 0;
+    for (; u + 3 < nu; u += 2) {  // (kNarrow: the unit itself gets that after the next, in parts)
+      if (!kNarrow) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
+      body(steady, 0, u);
+      if (!kNarrow) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
+      body(steady, 1, u + 1);
+    }
+    for (; u + 1 < nu; ++u) {
+      if (u + 2 < nu) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
+      body(inner, u & 1, u);
+    }
+    body(last, u & 1, u);
+  };
+  if constexpr (kNarrow) {
+  using TK = DqTicks;
+  constexpr TK ticks;
+  constexpr int PH = TK::PH;
+  const int lane_a = TL::rowmajor_lane(lane) + my, lane_b = TL::transposed_lane(lane) + my;
+  float crow[QB];
+  f32x4 dinit[QB];  // -Delta of the lane's query columns: the initial values of dP^T
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    crow[b] = nlse[b] * sl2;
+    dinit[b] = {ndelta[b], ndelta[b], ndelta[b], ndelta[b]};
+    asm volatile("" : "+v"(dinit[b]));
+  }
+  // Pad keys never take part: their rows of S^T start from a large negative value (keys 16*a + 4*g16 ..), all others from zero.
+  f32x4 sinit[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  asm volatile("" : "+v"(sinit[0]), "+v"(sinit[1]));
+  uint32_t all_valid = 0xffffffffu;  // what sinit was made for: this unit's valid keys and the next's
+  // Operand i of K and of V: key rows 16*(i%2) .., contraction step i/2.
+  bf16x8 ka[KS];  // K rows, read during the dQ products of the unit before
+  if (nu > 0) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i) ka[i] = TL::rowmajor_at(smem, lane_a, i & 1, i >> 1);
+  }
+  walk([&](auto kind_tag, int par, int u) {
+    constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool more1 = KIND >= 1;
+    const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu);
+    const unsigned char *kc = smem + par * HALF, *vc = smem + (2 + par) * HALF, *kn = smem + (1 - par) * HALF;  // K(u), V(u), K(u+1)
+    const unsigned k_at = lds0 + par * HALF, v_at = lds0 + (2 + par) * HALF;
+    bf16x8 va[KS];
+    bf16x4 kt[KS][2];         // K^T, columns 16 x ..
+    f32x4 S[2][QB], P[2][QB];  // S^T and then P^T; dP^T: [keys 16 a ..][queries 16 b ..]
+    uint4 ds[QB];             // dS^T as operands
+    float xf[2][2], xd[2][2];
+    auto put = [](uint4& u4, int w, uint32_t x) {
+      if (w == 0) u4.x = x;
+      if (w == 1) u4.y = x;
+      if (w == 2) u4.z = x;
+      if (w == 3) u4.w = x;
+    };
+    // item of 16: two values of a query column, four items, the operand of 16 queries, one after the other
+    auto p_ops = [&](auto from, auto count) {
+      in_steps<decltype(count)::value>([&](auto number) {
+        constexpr TK::Work w = ticks.pw[decltype(from)::value + decltype(number)::value];
+        constexpr int it = w.item, i = 2 * (it & 1) + w.i;
+        f32x4& x = S[(it >> 1) & 1][it >> 2];
+        if constexpr (w.op == TK::MUL) {
+          xf[it & 1][w.i] = fmaf(x[i], sl2, crow[it >> 2]);
+          asm volatile("" : : "v"(xf[it & 1][w.i]));  // (pure arithmetic has no place of its own in the order: tie it to this tick)
+        } else {
+          const float e = fast_exp2(xf[it & 1][w.i]);
+          asm volatile("" : : "v"(e));
+          x[i] = e;
+        }
+      });
+    };
+    auto s_ops = [&](auto from, auto count) {
+      in_steps<decltype(count)::value>([&](auto number) {
+        constexpr TK::Work w = ticks.sw[decltype(from)::value + decltype(number)::value];
+        constexpr int it = w.item, i = 2 * (it & 1) + w.i;
+        if constexpr (w.op == TK::MUL) {
+          xd[it & 1][w.i] = S[(it >> 1) & 1][it >> 2][i] * P[(it >> 1) & 1][it >> 2][i];
+          asm volatile("" : : "v"(xd[it & 1][w.i]));
+        } else {
+          const uint32_t x = pack_bf16(xd[it & 1][0], xd[it & 1][1]);
+          put(ds[it >> 2], it & 3, x);
+          asm volatile("" : : "v"(x));
+        }
+      });
+    };
+    // everything of tick t but its matrix instruction
+    auto ahead = [&](auto tick) {
+      constexpr int t = decltype(tick)::value, n = ticks.newer[t];
+      if constexpr (n >= 0) {
+        wait_lgkmcnt<(n < 15 ? n : 15)>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (KIND == 2 && TK::v_copy(t) >= 0) copy.aim(v_at, TK::v_copy(t));
+      if (KIND == 2 && TK::k_copy(t) >= 0) copy.aim(k_at, TK::k_copy(t));
+    };
+    int t2 = 0, h2 = 0;  // tile and half of unit u + 2
+    auto behind = [&](auto tick) {
+      constexpr int t = decltype(tick)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      if (KIND == 2 && TK::v_copy(t) >= 0) copy.piece(vb, un[2], v_at, TK::v_copy(t), true);
+      if (KIND == 2 && TK::k_copy(t) >= 0) copy.piece(kb, un[2], k_at, TK::k_copy(t), true);
+      // (where the last units are near: all of it at once, one branch)
+      if (KIND == 1 && t == TK::kFirstCopyV && more2) copy.all(vb, un[2], v_at);
+      if (KIND == 1 && t == TK::kFirstCopyK && more2) copy.all(kb, un[2], k_at);
+      if (KIND == 2) {
+        if (t == TK::kTile) t2 = tile_of(u + 2), h2 = half_of(u + 2);
+        if (t == TK::kChunk) list.load(t2);
+        if (t == TK::kRows) list.rows(t2, h2, un[2]);
+        if (t == TK::kValid) list.valid(t2, h2, un[2]);
+      }
+      if (more1 && t == TK::kRowsReady) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2), as far as requested
+        if (more2) wait_vmcnt<NC + (KIND == 2 ? TK::k_copies_before(TK::kRowsReady) : NC)>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      constexpr int n = ticks.issued[t + 1] - ticks.issued[t];
+      static_assert(n <= 1, "at most one");
+      if constexpr (n == 1) {
+        constexpr TK::Read r = ticks.r[ticks.issued[t]];
+        if constexpr (r.kind == TK::V) va[r.i] = TL::rowmajor_at(vc, lane_a, r.i & 1, r.i >> 1);
+        if constexpr (r.kind == TK::K_T) kt[r.i][r.part] = TL::transposed_half(kc, lane_b, r.i, r.part);
+        if constexpr (r.kind == TK::K_NEXT && more1) ka[r.i] = TL::rowmajor_at(kn, lane_a, r.i & 1, r.i >> 1);
+      }
+      p_ops(std::integral_constant<int, ticks.p[t]>{}, std::integral_constant<int, ticks.p[t + 1] - ticks.p[t]>{});
+      s_ops(std::integral_constant<int, ticks.s[t]>{}, std::integral_constant<int, ticks.s[t + 1] - ticks.s[t]>{});
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (__builtin_expect((un[0].valid & all_valid) != 0xffffffffu, 0)) {
+      all_valid = un[0].valid;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sinit[a][i] = (un[0].valid >> (16 * a + 4 * g16 + i)) & 1 ? 0.f : kMaskBias;
+      asm volatile("s_nop 1" : "+v"(sinit[0]), "+v"(sinit[1]));  // (two wait states ahead of the matrix instructions)
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    in_steps<PH>([&](auto tick) {  // ---- S
+      constexpr int t = decltype(tick)::value, i = t % KS, b = t / KS;
+      ahead(tick);
+      if (i < 2) mfma_v_from_qa(S[i & 1][b], ka[i], qreg[b][i >> 1], sinit[i & 1]);
+      else mfma_v_qa(S[i & 1][b], ka[i], qreg[b][i >> 1]);
+      if (i == 5) asm volatile("" : "+v"(sinit[0]), "+v"(sinit[1]));  // (initial values are not written over while they may still be read)
+      behind(tick);
+    });
+    in_steps<PH>([&](auto number) {  // ---- dP
+      constexpr int n = decltype(number)::value, i = n % KS, b = n / KS;
+      const std::integral_constant<int, PH + n> tick;
+      ahead(tick);
+      if (i < 2) mfma_v_from_qa(P[i & 1][b], va[i], doreg[b][i >> 1], dinit[b]);
+      else mfma_v_qa(P[i & 1][b], va[i], doreg[b][i >> 1]);
+      if (i == 5) asm volatile("" : "+v"(dinit[b]));
+      behind(tick);
+    });
+    in_steps<PH>([&](auto number) {  // ---- dQ
+      constexpr int n = decltype(number)::value, x = n % KS, b = n / KS;
+      const std::integral_constant<int, 2 * PH + n> tick;
+      ahead(tick);
+      mfma_a(acc[x][b], __builtin_shufflevector(kt[x][0], kt[x][1], 0, 1, 2, 3, 4, 5, 6, 7), __builtin_bit_cast(bf16x8, ds[b]));
+      behind(tick);
+    });
+    un[0] = un[1];
+    un[1] = un[2];
+  });
+  } else {
   const int lane_a = TL::rowmajor_lane(0, lane) + my;
   int lane_b0, lane_b1;
   TL::transposed_lane(0, lane, lane_b0, lane_b1);
   lane_b0 += my;
   lane_b1 += my;
   const float crow[2] = {nlse[0] * sl2, nlse[1] * sl2};
-  // -Delta of the lane's query column: the initial value of dP^T where the registers allow, else added to dP^T
-  constexpr bool kDeltaInit = D == 128;
-  f32x16 dinit[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) dinit[b][i] = kDeltaInit ? ndelta[b] : 0.f;
-    if (kDeltaInit) asm volatile("" : "+v"(dinit[b]));
-  }
   f32x16 zero16;
 #pragma unroll
   for (int i = 0; i < 16; ++i) zero16[i] = 0.f;
@@ -218,8 +465,7 @@ __device__ __forceinline__ void dq_block(
     for (int s = 0; s < KS; ++s) ka[s] = TL::rowmajor_at(smem, lane_a, s);
   }
 
-  // One unit.  KIND 2: the units up to u + 2 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
-  auto body = [&](auto kind_tag, int par, int u) {
+  walk([&](auto kind_tag, int par, int u) {
     constexpr int KIND = decltype(kind_tag)::value;
     constexpr bool more1 = KIND >= 1;
     const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu);
@@ -228,14 +474,13 @@ __device__ __forceinline__ void dq_block(
     bf16x8 va[KS], kt[2 * DVB];
     f32x16 S[2], P[2];  // S^T and then P^T; dP^T
     uint4 ds[2][2];     // dS^T as operands: [query half][contraction step]
-    float xf[2][2], xd[2][2];
     auto put = [](uint4& u4, int w, uint32_t x) {
       if (w == 0) u4.x = x;
       if (w == 1) u4.y = x;
       if (w == 2) u4.z = x;
       if (w == 3) u4.w = x;
     };
-    // d = 64: items 0..7 of a query half, two values each; the first four make up contraction step 0
+    // items 0..7 of a query half, two values each; the first four make up contraction step 0
     auto p_items = [&](int b, int from, int to) {
 #pragma unroll
       for (int it = from; it < to; ++it) {
@@ -254,44 +499,6 @@ __device__ __forceinline__ void dq_block(
         asm volatile("" : : "v"(x));
       }
     };
-    // d = 128: the same in stages, dealt to the matrix instructions; inside a stage no result is used by the next instruction, the order
-    // of two stages in one place is the compiler's (see p_stages in fine_fwd.hip; here 10 pairs of exponentials a unit end up side by
-    // side).  P: stage 0 the fma's of item 0 of 16, both halves'; 2g + 1 the first exponential of item g and the fma's of the next; 2g + 2
-    // its second.  dS of half b: stage k the products of item k and the conversion of the item before.
-    auto p_stages = [&](int from, int to) {
-#pragma unroll
-      for (int n = from; n < to; ++n) {
-        const int g = (n - 1) >> 1, next = n == 0 ? 0 : g + 1;
-        if (n > 0) {
-          float x = fast_exp2(xf[g & 1][(n - 1) & 1]);
-          asm volatile("" : : "v"(x));
-          S[g >> 3][2 * (g & 7) + ((n - 1) & 1)] = x;
-        }
-        if ((n == 0 || n % 2 == 1) && next < 16) {
-          const int b = next >> 3, i = 2 * (next & 7);
-          float (&f)[2] = xf[next & 1];
-          f[0] = fmaf(S[b][i], sl2, crow[b]);
-          f[1] = fmaf(S[b][i + 1], sl2, crow[b]);
-          asm volatile("" : : "v"(f[0]), "v"(f[1]));
-        }
-      }
-    };
-    auto d_stages = [&](int b, int from, int to) {
-#pragma unroll
-      for (int k = from; k < to; ++k) {
-        if (k > 0) {
-          const uint32_t x = pack_bf16(xd[(k - 1) & 1][0], xd[(k - 1) & 1][1]);
-          put(ds[b][(k - 1) >> 2], (k - 1) & 3, x);
-          asm volatile("" : : "v"(x));
-        }
-        if (k < 8) {
-          float (&f)[2] = xd[k & 1];
-          f[0] = S[b][2 * k] * P[b][2 * k];
-          f[1] = S[b][2 * k + 1] * P[b][2 * k + 1];
-          asm volatile("" : : "v"(f[0]), "v"(f[1]));
-        }
-      }
-    };
     // pad keys never take part: one extra matrix step adds a large negative bias to their rows of S^T
     auto bias = [&](int b) {
       if (__builtin_expect(un[0].valid != 0xffffffffu, 0)) {
@@ -307,17 +514,14 @@ __device__ __forceinline__ void dq_block(
     // the share of `n` items that step m of the steps [lo, hi) of a group does: [from, to)
     auto share = [](int n, int m, int lo, int hi) { return m < lo ? 0 : (m >= hi ? n : n * (m - lo) / (hi - lo)); };
     __builtin_amdgcn_sched_barrier(0);
-    // LDS reads of the first G / 2 steps of S 0: a V operand each and, d = 128, behind every other one a K^T operand, which is two
-    constexpr int kNewer = G / 2 + (D == 128 ? 2 * (G / 4) : 0);
     // the groups of matrix instructions; `with(m)` is the rest of step m
     auto s_group = [&](int b, auto with) {
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         if (b == 0 && m == 0) wait_lgkmcnt<G / 2>();      // the first half of the K operands; newer: the second
-        if (b == 0 && m == G / 2) wait_lgkmcnt<kNewer>();  // the second half; newer: the V, and K^T, operands read so far
+        if (b == 0 && m == G / 2) wait_lgkmcnt<G / 2>();  // the second half; newer: the V operands read so far
         S[b] = mfma32(ka[m], qreg[b][m], m == 0 ? zero16 : S[b]);
         if (b == 0) va[m] = TL::rowmajor_at(vc, lane_a, m);
-        if (b == 0 && D == 128 && m % 2 == 1) kt[m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, m / 2 / DVB, m / 2 % DVB);
         with(m);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -327,59 +531,37 @@ __device__ __forceinline__ void dq_block(
       if (b == 0) wait_lgkmcnt<0>();
 #pragma unroll
       for (int m = 0; m < G; ++m) {
-        P[b] = mfma32(va[m], doreg[b][m], m == 0 ? dinit[b] : P[b]);
-        if (b == 0 && D == 64) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
-        if (b == 0 && D == 128 && m % 2 == 0) kt[G / 2 + m / 2] = TL::transposed_at(kc, lane_b0, lane_b1, 1, m / 2);
-        // the copy of V(u+2) (V(u) is in registers): d = 128 behind every other matrix instruction of both halves
-        // (where the last units are near: all of it at once, one branch)
+        P[b] = mfma32(va[m], doreg[b][m], m == 0 ? zero16 : P[b]);
+        if (b == 0) kt[m] = TL::transposed_at(kc, lane_b0, lane_b1, m / DVB, m % DVB);
+        // the copy of V(u+2) (V(u) is in registers; where the last units are near: all of it at once, one branch)
         if (KIND == 1 && b == 1 && m == 0 && more2) copy.all(vb, un[2], lds0 + (2 + par) * HALF);
-        if (KIND == 2 && D == 128 && m % 2 == 1) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, b * (G / 2) + m / 2);
-        if (KIND == 2 && D == 64 && b == 1) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);
+        if (KIND == 2 && b == 1) copy.piece(vb, un[2], lds0 + (2 + par) * HALF, m);
         with(m);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    if constexpr (D == 128) {
-      s_group(0, [&](int) {});
-      // stages of P that precede step m of S 1, dP 0, dP 1 (S 0 can be read two steps into S 1, S 1 two steps into dP 0)
-      auto upto = [](int group, int m) {
-        constexpr int n[3][9] = {{0, 0, 1, 3, 5, 7, 9, 11, 13}, {13, 14, 16, 17, 19, 20, 22, 23, 25}, {25, 27, 29, 31, 33, 33, 33, 33, 33}};
-        return n[group][m];
-      };
-      s_group(1, [&](int m) { p_stages(upto(0, m), upto(0, m + 1)); });
-      d_group(0, [&](int m) { p_stages(upto(1, m), upto(1, m + 1)); });
-      d_group(1, [&](int m) {
-        p_stages(upto(2, m), upto(2, m + 1));
-        d_stages(0, m < 4 ? 0 : m - 4, m < 4 ? 0 : m == 7 ? 5 : m - 3);
-      });
-    } else {  // one half after the other: fewer registers, and another wavefront fills the gaps
-      s_group(0, [&](int) {});
-      d_group(0, [&](int m) { p_items(0, share(8, m, 1, G), share(8, m + 1, 1, G)); });
-      s_group(1, [&](int m) { d_items(0, share(4, m, 1, G), share(4, m + 1, 1, G)); });
-      d_group(1, [&](int m) { p_items(1, share(8, m, 1, G), share(8, m + 1, 1, G)); });
-    }
+    // one half after the other: fewer registers, and another wavefront fills the gaps
+    s_group(0, [&](int) {});
+    d_group(0, [&](int m) { p_items(0, share(8, m, 1, G), share(8, m + 1, 1, G)); });
+    s_group(1, [&](int m) { d_items(0, share(4, m, 1, G), share(4, m + 1, 1, G)); });
+    d_group(1, [&](int m) { p_items(1, share(8, m, 1, G), share(8, m + 1, 1, G)); });
     // ---- dQ of half 0 | the rest of its dS, the first half of dS of half 1, the copy of K(u+2)
     wait_lgkmcnt<0>();
     asm volatile("s_nop 1");  // (two wait states between the last item and the matrix instruction that reads it)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < G; ++m) {
-      if (KIND == 2 && m % kEvery == 0) copy.aim(lds0 + par * HALF, m / kEvery);
-      mfma_acc(acc[m % DVB][0], kt[m], __builtin_bit_cast(bf16x8, ds[0][m / DVB]));
+      if (KIND == 2) copy.aim(lds0 + par * HALF, m);
+      mfma_v(acc[m % DVB][0], kt[m], __builtin_bit_cast(bf16x8, ds[0][m / DVB]));
       if (KIND == 1 && m == 0 && more2) copy.all(kb, un[2], lds0 + par * HALF);
-      if (KIND == 2 && m % kEvery == 0) copy.piece(kb, un[2], lds0 + par * HALF, m / kEvery, true);
-      if constexpr (D == 128) {
-        if (m < 3) d_stages(0, 5 + m, m == 2 ? 9 : 6 + m);
-        if (m >= 3) d_stages(1, m - 3, m - 2);
-      } else {
-        d_items(0, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
-        d_items(1, share(4, m, DVB - 1, G), share(4, m + 1, DVB - 1, G));
-      }
+      if (KIND == 2) copy.piece(kb, un[2], lds0 + par * HALF, m, true);
+      d_items(0, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
+      d_items(1, share(4, m, DVB - 1, G), share(4, m + 1, DVB - 1, G));
       __builtin_amdgcn_sched_barrier(0);
     }
     // ---- dQ of half 1 | the rest of its dS, the K operands of the next unit
     if (more1) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2)
-      if (more2) wait_vmcnt<NC + (KIND == 2 ? NC / kEvery : NC)>();
+      if (more2) wait_vmcnt<2 * NC>();
       else wait_vmcnt<0>();
     }
     asm volatile("s_nop 1");
@@ -388,42 +570,20 @@ __device__ __forceinline__ void dq_block(
     for (int m = 0; m < G; ++m) {
       // (behind the last unit no operand reads lie between the last item of step 1 and the matrix instruction that reads it)
       if (!more1 && m == DVB) asm volatile("s_nop 1");
-      if (KIND == 2 && kEvery == 2 && m % 2 == 0) copy.aim(lds0 + par * HALF, (G + m) / 2);
-      mfma_acc(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
-      if (KIND == 2 && kEvery == 2 && m % 2 == 0) copy.piece(kb, un[2], lds0 + par * HALF, (G + m) / 2, true);
-      if constexpr (D == 128) {
-        if (m < 3) d_stages(1, 5 + m, m == 2 ? 9 : 6 + m);
-      } else {
-        d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
-      }
+      mfma_v(acc[m % DVB][1], kt[m], __builtin_bit_cast(bf16x8, ds[1][m / DVB]));
+      d_items(1, 4 + share(4, m, 0, DVB - 1), 4 + share(4, m + 1, 0, DVB - 1));
       if (more1) ka[m] = TL::rowmajor_at(smem + (1 - par) * HALF, lane_a, m);
       __builtin_amdgcn_sched_barrier(0);
     }
     un[0] = un[1];
     un[1] = un[2];
-  };
-  if (nu > 0) {
-    const std::integral_constant<int, 2> steady;
-    const std::integral_constant<int, 1> inner;
-    const std::integral_constant<int, 0> last;
-    int u = 0;
-    for (; u + 3 < nu; u += 2) {
-      list.get(tile_of(u + 2), half_of(u + 2), un[2]);
-      body(steady, 0, u);
-      list.get(tile_of(u + 3), half_of(u + 3), un[2]);
-      body(steady, 1, u + 1);
-    }
-    for (; u + 1 < nu; ++u) {
-      if (u + 2 < nu) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
-      body(inner, u & 1, u);
-    }
-    body(last, u & 1, u);
+  });
   }
   mfma_fence();  // the last matrix results land before they are read
 #pragma unroll
-  for (int x = 0; x < DVB; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) pin_acc(acc[x][b]);
+    for (int b = 0; b < QB; ++b) pin_acc(acc[x][b]);
   __builtin_amdgcn_sched_barrier(0);
 
   // Merge the partial results of the block's wavefronts (P of them), scale, add the pooled-gradient term, store.
@@ -447,13 +607,14 @@ __device__ __forceinline__ void dq_block(
     {
       float* Op = bufs + (P == 1 ? 0 : wave) * 64 * OS;
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < QB; ++b)
 #pragma unroll
-        for (int x = 0; x < DVB; ++x)
+        for (int x = 0; x < XB; ++x)
 #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4)
-            *(float4*)&Op[merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS)] =
-                make_float4(acc[x][b][4 * g4], acc[x][b][4 * g4 + 1], acc[x][b][4 * g4 + 2], acc[x][b][4 * g4 + 3]);
+          for (int g4 = 0; g4 < AV / 4; ++g4) {
+            const int at = kNarrow ? merge_offset(b * 16 + l16, x * 16 + 4 * g16, OS) : merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS);
+            *(float4*)&Op[at] = make_float4(acc[x][b][4 * g4], acc[x][b][4 * g4 + 1], acc[x][b][4 * g4 + 2], acc[x][b][4 * g4 + 3]);
+          }
     }
     if (P > 1) __syncthreads();
     else __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses stay in order)

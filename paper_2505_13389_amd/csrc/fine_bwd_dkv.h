@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "coarse_small.h"
+#include "ticks.h"
 #include "unit_stream.h"
 #include "vsa_kernels.h"
 
@@ -96,58 +97,24 @@ struct DkvStages {
 static_assert(DkvStages::p(8) > 18 && DkvStages::p(11) == 34 && DkvStages::s(8) > 8 && DkvStages::s(11) == 17, "d = 64");
 
 // d = 128: what lies behind which of the 128 matrix instructions (ticks) of a unit: S of the first 32 keys | S of the other 32 | dP | dV | dK.
-struct DkvTicks {
-  static constexpr int KS = 8, PH = 4 * KS, T = 4 * PH;  // LDS operands of a phase; ticks of a phase, of a unit
-  static constexpr int kAhead = 4;                       // Q operands of a unit that are read in the unit before
-  static constexpr int kRowsReady = T - 14;              // the rows of the next unit are waited for here
+struct DkvTicks : TickTable<128, 60> {
+  static constexpr int KS = 8, PH = 4 * KS;  // LDS operands of a phase; its ticks
+  static constexpr int kAhead = 4;           // Q operands of a unit that are read in the unit before
+  static constexpr int kRowsReady = T - 14;  // the rows of the next unit are waited for here
+  static constexpr int kRowTerms = 15;       // their copy (an M0 of its own: between two groups of copies)
   enum Kind { Q, DP_INIT, DO, V, DO_T, Q_T, S_INIT, Q_NEXT };
-  struct Read {
-    int tick, use;  // behind which instruction it is requested, ahead of which one it is waited for
-    Kind kind;
-    int i, part;
-  };
-  static constexpr int N = (KS - kAhead) + 2 + KS + KS + 2 * KS + 2 * KS + 2 + kAhead;
-  Read r[N] = {};
-  int issued[T + 1] = {};  // LDS reads ahead of tick t
-  int newer[T] = {};       // of those, how many are behind the last one that it needs; -1: it needs none that an earlier tick has not
-  // P and dS as operations of their own (see the unit), and how many of them lie ahead of tick t
-  enum Op { MUL, EXP, CVT };  // of an item: products of its two values, exponentials of both, conversion of the pair
-  struct Work {
-    Op op;
-    int item, i;
-  };
+  // P and dS in operations, and how many of them lie ahead of tick t
   static constexpr int kPOps = 80, kSOps = 48;
   Work pw[kPOps] = {}, sw[kSOps] = {};
-  static constexpr int kFirstP = PH / 2 + 2, kFirstS = 2 * PH + 2;  // (two instructions behind the S, the dP they need)
   int p[T + 1] = {}, s[T + 1] = {};
   // the copies of Q rows (of the S phase) and of dO_f rows (of the dK phase) behind tick t, -1: none.  A copy in 64 cycles is what the
   // four wavefronts of a compute unit get through.
   static constexpr int q_copy(int t) { return t < PH && t % 4 == 1 ? t / 4 : -1; }
   static constexpr int do_copy(int t) { return t > 3 * PH && t < 3 * PH + 16 && t % 2 == 1 ? (t - 3 * PH) / 2 : -1; }
-  static constexpr int cost(Op op) { return op == EXP ? 9 : 5; }
-  constexpr int fixed_cost(int t) const {  // cycles of what has its place behind tick t
-    int c = 8 * (issued[t + 1] - issued[t]) + (newer[t] >= 0 ? 4 : 0);
-    if (q_copy(t) >= 0) c += 8 + (q_copy(t) % 4 == 0 ? 4 : 0);
-    if (do_copy(t) >= 0) c += 8 + (do_copy(t) % 4 == 0 ? 4 : 0);
-    return c;
-  }
-  // `ops` operations dealt to the ticks from .. to - 1 so that all of them take about the same time
-  constexpr void deal(int (&ahead)[T + 1], const Work* w, int ops, int from, int to) {
-    int total = 0, fixed = 0, spent = 0, n = 0;
-    for (int t = from; t < to; ++t) total += fixed_cost(t);
-    for (int i = 0; i < ops; ++i) total += cost(w[i].op);
-    for (int t = 0; t < T; ++t) {
-      ahead[t] = n;
-      if (t < from || t >= to) continue;
-      fixed += fixed_cost(t);
-      while (n < ops && (t == to - 1 || (fixed + spent + cost(w[n].op) / 2) * (to - from) <= total * (t - from + 1))) spent += cost(w[n++].op);
-    }
-    ahead[T] = n;
-  }
   constexpr DkvTicks() {
     int n = 0;
-    auto add = [&](int tick, int use, Kind kind, int i, int part) { r[n++] = Read{tick, use, kind, i, part}; };
-    // Operands are waited for in pairs, 8 ticks (128 cycles) behind the request of the second one.
+    auto add = [&](int tick, int use, int kind, int i, int part) { r[n++] = Read{tick, use, kind, i, part}; };
+    // Operands are waited for in pairs, 7 or 8 ticks (128 cycles) behind the request of the second one.
     add(0, 8, Q, 4, 0);
     add(1, 8, Q, 5, 0);
     add(4, 12, Q, 6, 0);
@@ -173,18 +140,10 @@ struct DkvTicks {
     add(T - 10, T, Q_NEXT, 1, 0);
     add(T - 7, T + 4, Q_NEXT, 2, 0);
     add(T - 5, T + 4, Q_NEXT, 3, 0);
-    for (int i = 1; i < N; ++i)  // in the order of issue
-      for (int j = i; j > 0 && r[j].tick < r[j - 1].tick; --j) {
-        const Read x = r[j];
-        r[j] = r[j - 1];
-        r[j - 1] = x;
-      }
+    order_reads();
     for (int t = 0; t < T; ++t) {
-      for (int i = 0; i < N; ++i) issued[t + 1] += r[i].tick <= t;
-      int last = -1;
-      for (int i = 0; i < N; ++i)
-        if (r[i].use % T == t) last = i;
-      newer[t] = last < 0 ? -1 : issued[t] - last - 1 + (r[last].use == t ? 0 : N);  // (the next unit's: read in the unit before)
+      if (q_copy(t) >= 0) cycles[t] += kCopy + (q_copy(t) % 4 == 0 ? kScalar : 0);
+      if (do_copy(t) >= 0) cycles[t] += kCopy + (do_copy(t) % 4 == 0 ? kScalar : 0);
     }
     // P: an item's first exponential, the products of the next, the second exponential, the conversion of the item before; dS: the
     // products of an item, the conversion of the one before.
@@ -205,8 +164,9 @@ struct DkvTicks {
       if (k > 0) sw[n++] = {CVT, k - 1, 0};
       if (k < 16) sw[n++] = {MUL, k, 1};
     }
-    deal(p, pw, kPOps, kFirstP, 2 * PH - 1);
-    deal(s, sw, kSOps, kFirstS, 3 * PH - 1);
+    // (from two instructions behind the S, the dP they need)
+    deal(p, pw, kPOps, PH / 2 + 2, 2 * PH - 1);
+    deal(s, sw, kSOps, 2 * PH + 2, 3 * PH - 1);
   }
 };
 // P of the other keys two instructions behind their S
@@ -549,7 +509,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
         else if (hf == 1) asm volatile("" : : "v"(sinit[0]), "v"(sinit[1]));
       }
       if (copy >= 0 && more_q) copy_piece(gq, wbase + prev_st, copy, true);
-      if (t == 15 && more_q) copy_rows(next_off, wbase + prev_st + 2 * HALF);  // (between two groups of copies: it has an M0 of its own)
+      if (t == TK::kRowTerms && more_q) copy_rows(next_off, wbase + prev_st + 2 * HALF);
       // the list entry of unit u + NST, a chain of scalar instructions, in parts
       if (STEADY && t == 7) load_chunk(u + NST);
       if (STEADY && t == 10) raw = entry_of(u + NST);

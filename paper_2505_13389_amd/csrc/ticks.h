@@ -1,0 +1,66 @@
+// What lies behind which matrix instruction (TICK) of a unit, for the kernels whose wavefronts are alone on their SIMD and therefore
+// ordered instruction by instruction: tables that the kernels' constructors fill at compile time.
+//
+// A tick of a 16x16x32 instruction is 16 cycles of the matrix pipe.  The instruction takes about 6 of them to issue and what lies behind it the
+// costs below (measured with one wavefront on the SIMD); where it takes longer than the tick, the pipe waits, and fewer instructions
+// behind the next one do not make up for it.
+#pragma once
+
+namespace vsa {
+
+template <int TICKS, int READS>
+struct TickTable {
+  static constexpr int T = TICKS, N = READS;
+  struct Read {      // of LDS
+    int tick, use;   // behind which instruction it is requested, ahead of which one it is waited for (T and more: of the next unit)
+    int kind, i, part;
+  };
+  enum Op { MUL, EXP, CVT };  // of an item, a pair of values: arithmetic on value i, its exponential, the conversion of the pair
+  struct Work {
+    Op op;
+    int item, i;
+  };
+  static constexpr int kRead = 8, kWait = 4, kCopy = 8, kScalar = 4;
+  static constexpr int cost(Op op) { return op == EXP ? 9 : 5; }
+
+  Read r[N] = {};
+  int issued[T + 1] = {};  // reads ahead of tick t
+  int newer[T] = {};       // of those, how many are behind the last one that it needs; -1: it needs none that an earlier tick has not
+  int cycles[T] = {};      // of what lies behind tick t so far
+
+  // (r is filled)
+  constexpr void order_reads() {
+    for (int i = 1; i < N; ++i)
+      for (int j = i; j > 0 && r[j].tick < r[j - 1].tick; --j) {
+        const Read x = r[j];
+        r[j] = r[j - 1];
+        r[j - 1] = x;
+      }
+    for (int t = 0; t < T; ++t) {
+      for (int i = 0; i < N; ++i) issued[t + 1] += r[i].tick <= t;
+      int last = -1;
+      for (int i = 0; i < N; ++i)
+        if (r[i].use % T == t) last = i;
+      newer[t] = last < 0 ? -1 : issued[t] - last - 1 + (r[last].use == t ? 0 : N);
+      cycles[t] += kRead * (issued[t + 1] - issued[t]) + (newer[t] >= 0 ? kWait : 0);
+    }
+  }
+  // `ops` operations dealt to the ticks from .. to - 1 so that all of them take about the same time; ahead[t]: those ahead of tick t
+  constexpr void deal(int (&ahead)[T + 1], const Work* w, int ops, int from, int to) {
+    int total = 0, sum = 0, n = 0;
+    for (int t = from; t < to; ++t) total += cycles[t];
+    for (int i = 0; i < ops; ++i) total += cost(w[i].op);
+    for (int t = 0; t < T; ++t) {
+      ahead[t] = n;
+      if (t < from || t >= to) continue;
+      sum += cycles[t];
+      while (n < ops && (t == to - 1 || (sum + cost(w[n].op) / 2) * (to - from) <= total * (t - from + 1))) {
+        cycles[t] += cost(w[n].op);
+        sum += cost(w[n++].op);
+      }
+    }
+    ahead[T] = n;
+  }
+};
+
+}  // namespace vsa

@@ -60,18 +60,25 @@ struct CubeUnits {
     u.a = (unsigned)__builtin_amdgcn_readlane(idx_v, t & 63) * (unsigned)TL::BYTES + (unsigned)half * (TL::BYTES / 2);
     u.b = u.a + TL::BYTES / 4;
   }
-  __device__ __forceinline__ void get(int t, int half, Unit& u) {
+  // a unit in parts: the chunk of its tile, its rows, its valid-key bits
+  __device__ __forceinline__ void load(int t) {
     if (__builtin_expect(!loaded(t), 0)) {
       load_indices(t / kTilesPerChunk);
       set_masks(mask[mask_block()]);
       asm volatile("" : "+v"(km_v[0]), "+v"(km_v[1]));
     }
-    rows(t, half, u);
+  }
+  __device__ __forceinline__ void valid(int t, int half, Unit& u) const {
     u.valid = (uint32_t)__builtin_amdgcn_readlane((int)km_v[0], t & 63);
     if (only < 0) {
       const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)km_v[1], t & 63);
       u.valid = half ? hi : u.valid;
     }
+  }
+  __device__ __forceinline__ void get(int t, int half, Unit& u) {
+    load(t);
+    rows(t, half, u);
+    valid(t, half, u);
   }
   __device__ static __forceinline__ int source_row(int x) { return x; }
 };
@@ -112,17 +119,23 @@ struct SubCubeUnits {
     u.a = entry_offset(4 * t + 2 * half);
     u.b = entry_offset(4 * t + 2 * half + 1);
   }
-  __device__ __forceinline__ void get(int t, int half, Unit& u) {
+  __device__ __forceinline__ void load(int t) {
     if (__builtin_expect(!loaded(t), 0)) {
       load_indices(t / kTilesPerChunk);
       set_masks(mask[mask_block()]);
       asm volatile("" : "+v"(km_v));
     }
-    rows(t, half, u);
+  }
+  __device__ __forceinline__ void valid(int t, int half, Unit& u) const {
     const int ea = 4 * t + 2 * half, eb = ea + 1;
     const uint32_t ma = (uint32_t)__builtin_amdgcn_readlane((int)km_v, ea & 63);
     const uint32_t mb = (uint32_t)__builtin_amdgcn_readlane((int)km_v, eb & 63);
     u.valid = (ea < n ? ma : 0u) | ((eb < n ? mb : 0u) << 16);
+  }
+  __device__ __forceinline__ void get(int t, int half, Unit& u) {
+    load(t);
+    rows(t, half, u);
+    valid(t, half, u);
   }
   __device__ static __forceinline__ int source_row(int x) { return subcube_slot(x); }
 };
@@ -219,6 +232,13 @@ __device__ __forceinline__ void mfma_v_from(f32x4& d, bf16x8 a, bf16x8 b, const 
 }
 __device__ __forceinline__ void mfma_a(f32x4& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+// (B operand in the accumulation registers)
+__device__ __forceinline__ void mfma_v_from_qa(f32x4& d, bf16x8 a, bf16x8 b, const f32x4& c) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "a"(b), "v"(c));
+}
+__device__ __forceinline__ void mfma_v_qa(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
 }
 // matrix results land before the vector instructions behind this read them, and the other way round
 __device__ __forceinline__ void mfma_fence() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }

@@ -22,19 +22,22 @@
 // multiplied and begun while PV(u-1) is, in steps pinned by scheduling barriers; K is copied three units ahead, V
 // one.  d = 64 takes two wavefronts per SIMD.
 //
-// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 210 others, 204 where all blocks
-// are shared (112 of softmax: fma, exp2, sum, half a conversion per value; 24 LDS reads, 16 copies, 33 to 38 scalar ones, most of them
-// of list.get): 1490 cycles where the matrix pipe needs 1024, at a
+// What bounds it: instruction issue, at the clock that power leaves.  A unit is 32 matrix instructions and 188 others, 192 where all blocks
+// are shared (112 of softmax: fma, exp2, sum, half a conversion per value; 24 LDS reads, 16 copies, 20 to 24 scalar ones): 1330 cycles by the
+// costs below where the matrix pipe needs 1024, at a
 // clock that falls as the chip fills (1.6 to 1.75 GHz; 2.1 while the last workgroups of a launch run).  What an instruction costs a
 // wavefront that is alone on its SIMD, measured behind matrix instructions: 5 cycles in vector arithmetic, 8 if the next one
 // needs its result, exp2 9, an LDS read 8, scalar ones and waits 4; five or six plain ones fit behind a matrix instruction,
-// and none is made up for by fewer behind the next.  So the softmax is a pipeline of stages without neighbours that depend on one another,
-// the stages, operand reads and copies are dealt to the 32 matrix instructions one by one, and what is rare (a moved
-// reference, pad keys, a new chunk of the list) lies out of the loop's line.  As emitted, by these costs, 20 to 50 cycles lie behind
-// most matrix instructions; more behind the two around list.get (60 to 75 and 115 to 130, a chain of dependent scalar instructions), the check
-// for a moved reference (105) and those the compiler gives two exponentials side by side (up to 75).  1730 -> 1490 cycles a unit (768 blocks, top-64
-// to 192), whole launches 8.5 % fewer at 39936 tokens, top-78, of which the clock leaves 3.8 % of the time: 1306 -> 1258 us for the
-// forward, 264 -> 259 at 16384 tokens, top-32 (two generations' start-up and end in it).  Around the walk a wavefront
+// and none is made up for by fewer behind the next.  So the softmax is cut into operations that are dealt, like the reads, copies and the
+// scalar chain of the next list entry, to the 32 matrix instructions one by one (FwdTicks: 32 to 55 cycles behind each as emitted), pinned by a
+// scheduling barrier right behind each of them, and what is rare (a moved
+// reference, pad keys, a new chunk of the list) lies out of the loop's line.  A wavefront with a block of its own walks in a loop of its own,
+// where the half of a unit is known and every second one is in the same tile; the tile is counted on, not worked out; the check for a moved
+// reference is one comparison.  Against stages of the softmax in place of operations, a list entry at once and 210 others a unit: 1490 -> 1330
+// cycles by the costs, 2.03 -> 1.87 M in a whole launch (39936 tokens, 12 heads, top-78), of which the clock leaves a third of the time: 1217 ->
+// 1184 us for the forward, 252 -> 247 at 16384 tokens, top-32 (two generations' start-up and end in it), results the same bits.  16x16x32 matrix
+// instructions, which take less energy (fine_bwd_dkv.h), cost more issue slots than this loop has.
+Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
 // normalising, gating and storing, which nothing overlaps on its SIMD: halved per block where a wavefront has a block of
 // its own.  That, one factor per lane instead of per row and item on the way out, and a start that waits for K alone:
@@ -48,6 +51,7 @@
 #include <type_traits>
 
 #include "coarse_small.h"
+#include "ticks.h"
 #include "unit_stream.h"
 #include "vsa_kernels.h"
 
@@ -96,22 +100,56 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
   __syncthreads();
 }
 
-// The softmax stages of a unit (p_stages) that precede matrix instruction j + 1 of the PV phase before it, and matrix instruction
-// j + 1 of the S phase of the unit after it: few where copies and transposing reads are many.
+// What lies behind which matrix instruction of a unit, S of the next unit | PV, and where the softmax of a unit, in operations (p_ops), is done:
+// from the second instruction of the PV phase before it to the last but one of the S phase of the next.
 template <int D>
-struct FwdStages {
-  static constexpr int pv(int j) {
-    constexpr int wide[16] = {0, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1, 2, 1, 1, 1, 2}, narrow[16] = {0, 1, 2, 2, 2, 2, 3, 3};
-    return D == 128 ? wide[j] : narrow[j];
+struct FwdTicks : TickTable<D / 2, 1> {  // (two units)
+  using Table = TickTable<D / 2, 1>;
+  using typename Table::Work;
+  using Table::cycles;
+  using Table::T;
+  static constexpr int KS = D / 16, PH = 2 * KS, U = T / 2;  // LDS operands of a phase; matrix instructions of a phase, of a unit
+  static constexpr int kEvery = D == 128 ? 2 : 1;  // a copy behind every other, or every, one of a phase until all are requested
+  // LDS operands are waited for in pairs of steps, and read kAhead steps before the first of them is used, spread over kSpread instructions
+  static constexpr int kAhead = D == 128 ? 4 : 2, kSpread = D == 128 ? 4 : 2;
+  static constexpr int kTile = 1, kChunk = D == 128 ? 3 : 2, kRows = D == 128 ? 5 : 3, kValid = D == 128 ? 7 : 4;  // the list entry of the unit after the next two, in parts
+  static constexpr int kOps = 112;
+  Work w[kOps] = {};
+  int ahead[T + 1] = {};
+  static constexpr int in_pv(int j) { return PH + j; }
+  static constexpr int in_s(int j) { return U + j; }
+  constexpr FwdTicks() {
+    for (int t = 0; t < T; ++t) {
+      const int u = t % U, j = u % PH, q = j & 3, to = j / 4 * 2 + kAhead;
+      const bool of_v = u < PH ? to >= KS : to < KS;  // operands of V are two reads
+      if (j % kEvery == 0 && j < kEvery * KS) cycles[t] += Table::kCopy + (j / kEvery % (KS / 2) == 0 ? 3 * Table::kScalar : 0);
+      if (q == 0) cycles[t] += Table::kWait;
+      if (j == 2 * (KS - kAhead)) cycles[t] += Table::kWait;
+      if (of_v && q < kSpread) cycles[t] += Table::kRead * 4 / kSpread;
+      if (!of_v && (q == 0 || q == kSpread / 2)) cycles[t] += Table::kRead;
+      if (u < PH) {
+        if (j == kTile || j == kChunk) cycles[t] += 4 * Table::kScalar;
+        if (j == kRows || j == kValid) cycles[t] += 9;
+        if (j == PH - 2) cycles[t] += 38;  // the check of the references
+        if (j == PH - 1) cycles[t] += 2 * Table::kScalar;
+      }
+    }
+    // an item's first exponential, the arguments of the next, its second exponential, the sums and the conversion of the item before
+    int n = 0;
+    w[n++] = {Table::MUL, 0, 0};
+    w[n++] = {Table::MUL, 0, 1};
+    for (int g = 0; g < 17; ++g) {
+      if (g < 16) w[n++] = {Table::EXP, g, 0};
+      if (g < 15) w[n++] = {Table::MUL, g + 1, 0};
+      if (g < 15) w[n++] = {Table::MUL, g + 1, 1};
+      if (g < 16) w[n++] = {Table::EXP, g, 1};
+      if (g > 0) w[n++] = {Table::ADD, g - 1, 0};
+      if (g > 0) w[n++] = {Table::CVT, g - 1, 0};
+      if (g > 0) w[n++] = {Table::ADD, g - 1, 1};
+    }
+    this->deal(ahead, w, kOps, in_pv(1), in_s(PH - 1));
   }
-  static constexpr int s(int j) {
-    constexpr int wide[16] = {1, 2, 1, 2, 1, 2, 1, 2, 1, 1, 1, 1, 1, 1, 1, 0}, narrow[16] = {3, 3, 3, 3, 3, 2, 2, 0};
-    return D == 128 ? wide[j] : narrow[j];
-  }
-  static constexpr int before_pv(int j) { return j == 0 ? 0 : before_pv(j - 1) + pv(j - 1); }
-  static constexpr int before_s(int j) { return j == 0 ? before_pv(16) : before_s(j - 1) + s(j - 1); }
 };
-static_assert(FwdStages<128>::before_s(15) == 34 && FwdStages<64>::before_s(7) == 34, "all of them ahead of the check");
 
 // PAIRS: the first `pairs` workgroups take two blocks, one per wavefront (d = 128, NW = 2; at d = 64 two wavefronts per SIMD hide one
 // another's start-up).  Launches without pairs have instances of their own, which know each wavefront's key half: 288 blocks,
@@ -133,9 +171,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   constexpr int HALF = TL::BYTES / 2;   // 32 rows
   constexpr int NC = UC::NC;            // copy instructions per 32 rows
   constexpr int NPV = 2 * DVB;          // steps of the PV phase
-  // LDS operands are waited for in pairs of steps, and read kAhead steps before the first of them is used
-  constexpr int kAhead = D == 128 ? 4 : 2;
-  constexpr int kEarly = FwdStages<D>::before_pv(16);  // of the 34 softmax stages of a unit, those behind the PV phase before it
+  using TK = FwdTicks<D>;
+  constexpr TK ticks;
+  constexpr int kAhead = TK::kAhead, kEvery = TK::kEvery;
   constexpr int OS = D;
   // per wavefront: K of two units, V of two units
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * HALF];
@@ -143,10 +181,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   __shared__ SmallCoarse<COARSE ? D : 4> lc;
   __shared__ int32_t lc_list[COARSE ? kSmallCubes : 1];
   static_assert(HALF % 256 == 0, "the operand addresses XOR the bits below 256");
-  constexpr int kEvery = D == 128 ? 2 : 1;  // a copy behind every other, or every, matrix instruction of a phase until all are requested
   // copies of a phase that precede its wait for earlier ones
   constexpr int kPart = 2 * (KS - kAhead) / kEvery < NC ? 2 * (KS - kAhead) / kEvery : NC;
-  static_assert(KS == NPV && KS == NC && KS > kAhead, "phase interleave");
+  static_assert(KS == NPV && KS == NC && KS > kAhead && KS == TK::KS, "phase interleave");
 
   // With K = Nc every workgroup of a head walks the same list: then all XCDs work on the same head
   // (plain blockIdx order), which keeps that list's tiles shared chip-wide, and the workgroups that
@@ -304,6 +341,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   // references of the lane's two query columns; zero, and `have` false, until the first unit with a valid key
   float ref[2] = {0.f, 0.f};
   bool have = false;
+  float bar = -1.f;
   float lsum[2] = {0.f, 0.f};
   float ta[2] = {0.f, 0.f}, tb[2] = {0.f, 0.f};  // the unit's sums of a column, even and odd values
   uint4 pb[2][2];  // P^T of the current unit as operands: [query half][contraction step]
@@ -313,48 +351,37 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     if (w == 2) u4.z = x;
     if (w == 3) u4.w = x;
   };
-  // Softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0.  Its arithmetic goes
-  // through a pipeline of STAGES, one or two of them behind a matrix instruction, in each of which no result is used by the next
-  // instruction (that costs 8 cycles instead of 5): stage 0 the fma's of item 0; stage 2g + 1 the first
-  // exponential of item g and the fma's of the next; stage 2g + 2 its second exponential, and the sums and the conversion of
-  // the item before; stage 33 those of the last item.  The order of two stages in one place is the compiler's, which puts some of
-  // their exponentials (9 cycles) side by side (4 or 5 pairs a unit).
+  // Softmax item `it` of 16: two values of one query half; the first eight make up contraction step 0.  Its arithmetic is done in operations, dealt
+  // to the matrix instructions one by one (FwdTicks), none of which needs the result of the one before it (that costs 8 cycles instead of 5).
   float xf[2][2] = {}, xe[2][2] = {};  // arguments and exponentials of an item, by its parity
-  auto p_fma = [&](const f32x16 (&S)[2], int it, const float* rf) {
+  auto p_fma = [&](const f32x16 (&S)[2], int it, int i, const float* rf) {
     const int b = (it >> 2) & 1, e = 8 * (it >> 3) + 2 * (it & 3);
-    float (&f)[2] = xf[it & 1];
-    f[0] = fmaf(S[b][e], sl2, -rf[b]);
-    f[1] = fmaf(S[b][e + 1], sl2, -rf[b]);
-    asm volatile("" : : "v"(f[0]), "v"(f[1]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
+    xf[it & 1][i] = fmaf(S[b][e + i], sl2, -rf[b]);
+    asm volatile("" : : "v"(xf[it & 1][i]));  // (pure arithmetic has no place of its own in the order: tie it to this step)
   };
   auto p_exp = [&](int it, int i) {
     xe[it & 1][i] = fast_exp2(xf[it & 1][i]);
     asm volatile("" : : "v"(xe[it & 1][i]));
   };
-  auto p_sum = [&](int it) {
-    const int b = (it >> 2) & 1;
-    const float x0 = xe[it & 1][0], x1 = xe[it & 1][1];
-    const uint32_t pp = pack_bf16(x0, x1);
-    ta[b] = (it & 11) == 0 ? x0 : ta[b] + x0;
-    tb[b] = (it & 11) == 0 ? x1 : tb[b] + x1;
-    put(pb[b][it >> 3], it & 3, pp);
-    asm volatile("" : : "v"(ta[b]), "v"(tb[b]), "v"(pp));
+  auto p_sum = [&](int it, int i) {
+    float& t = (i ? tb : ta)[(it >> 2) & 1];
+    const float x = xe[it & 1][i];
+    t = (it & 11) == 0 ? x : t + x;
+    asm volatile("" : : "v"(t));
   };
-  auto p_stages = [&](const f32x16 (&S)[2], int from, int to, const float* rf) {
-#pragma unroll
-    for (int n = from; n < to; ++n) {
-      const int g = (n - 1) >> 1;
-      if (n == 0) p_fma(S, 0, rf);
-      else if (n == 33) p_sum(15);
-      else p_exp(g, (n - 1) & 1);
-      if (n > 0 && n < 33) {
-        if (n & 1) {
-          if (g < 15) p_fma(S, g + 1, rf);
-        } else if (g > 0) {
-          p_sum(g - 1);
-        }
-      }
-    }
+  auto p_convert = [&](int it) {
+    const uint32_t pp = pack_bf16(xe[it & 1][0], xe[it & 1][1]);
+    put(pb[(it >> 2) & 1][it >> 3], it & 3, pp);
+    asm volatile("" : : "v"(pp));
+  };
+  auto p_ops = [&](const f32x16 (&S)[2], auto from, auto to, const float* rf) {
+    in_steps<decltype(to)::value - decltype(from)::value>([&](auto number) {
+      constexpr typename TK::Work w = ticks.w[decltype(from)::value + decltype(number)::value];
+      if constexpr (w.op == TK::MUL) p_fma(S, w.item, w.i, rf);
+      if constexpr (w.op == TK::EXP) p_exp(w.item, w.i);
+      if constexpr (w.op == TK::ADD) p_sum(w.item, w.i);
+      if constexpr (w.op == TK::CVT) p_convert(w.item);
+    });
   };
   // the larger of `old` and the largest (scaled) logit of the unit in the lane's query column
   // (pad keys do not count: a column all of whose logits are -inf keeps kNoRef and ends as one without a valid key)
@@ -395,14 +422,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
       ref[0] = unit_max(s0[0], valid, kNoRef);
       ref[1] = unit_max(s0[1], valid, kNoRef);
       have = true;
+      bar = limit;
     }
-    p_stages(s0, 0, kEarly, ref);
+    p_ops(s0, std::integral_constant<int, 0>{}, std::integral_constant<int, ticks.ahead[TK::U]>{}, ref);
   }
 
+  // The unit that is fetched next in the steady walk: its tile and half.  Two blocks per workgroup: both halves of a tile one after the other.
+  int next_tile = nu > 3 ? tile_of(2) : 0;
   // One unit u (its S is there, in S): P(u) while S(u+1) is multiplied into T, then PV(u) while P(u+1) begins.
   // KIND 2: the units up to u + 3 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
-  auto body = [&](auto kind_tag, int par, f32x16 (&S)[2], f32x16 (&T)[2], int u) {
+  // OWN: the wavefront has a block of its own (then the half of a unit of the steady walk is known: `par`).
+  auto body = [&](auto kind_tag, auto own_tag, int par, f32x16 (&S)[2], f32x16 (&T)[2], int u) {
     constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool OWN = decltype(own_tag)::value;
     constexpr bool more1 = KIND >= 1;
     const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu), more3 = KIND == 2 || (KIND == 1 && u + 3 < nu);
     const unsigned char* kn = smem + (1 - par) * HALF;  // K(u+1)
@@ -413,7 +445,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     // The operand reads for the two steps kAhead further on, spread over the four matrix instructions (q = 0 .. 3) of two steps, d = 64: over the
     // first two.  A V operand is two reads: read_v issues the share of q of those of steps i and i + 1.  A K operand is one read: reads_row says
     // whether that of the w-th of the two steps is issued at q.
-    constexpr int kSpread = D == 128 ? 4 : 2;
+    constexpr int kSpread = TK::kSpread;
     auto read_v = [&](int i, int q) {  // of steps i and i + 1
 #pragma unroll
       for (int r = q * 4 / kSpread; r < (q + 1) * 4 / kSpread; ++r)
@@ -441,6 +473,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         __builtin_amdgcn_sched_barrier(0);
       }
       if (more1) T[j & 1] = mfma32(ka[s], qreg[j & 1][s], s == 0 ? zero16 : T[j & 1]);
+      __builtin_amdgcn_sched_barrier(0);
       if (j == 2 * (KS - kAhead)) {  // V(u) has landed; newer: K(u+2) and a part of V(u+1)
         if (more2) wait_vmcnt<NC + kPart>();
         else if (more1) wait_vmcnt<kPart>();
@@ -455,17 +488,28 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         if (reads_row(q, 0)) ka[to] = TL::rowmajor_at(kn, lane_a, to);
         if (reads_row(q, 1)) ka[to + 1] = TL::rowmajor_at(kn, lane_a, to + 1);
       }
-      if (j == 3 && more3) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
-      p_stages(S, FwdStages<D>::before_s(j), FwdStages<D>::before_s(j + 1), ref);
+      if (KIND == 2) {
+        const int half = OWN ? 1 - par : wave & 1;
+        if (j == TK::kTile && !(OWN && half)) {
+          next_tile += OWN ? 1 : NW / 2;
+          if (next_tile >= tiles) next_tile -= tiles;
+        }
+        if (j == TK::kChunk && !(OWN && half)) list.load(next_tile);
+        if (j == TK::kRows) list.rows(next_tile, half, un[2]);
+        if (j == TK::kValid) list.valid(next_tile, half, un[2]);
+      } else if (j == 3 && more3) {
+        list.get(tile_of(u + 3), half_of(u + 3), un[2]);
+      }
+      p_ops(S, std::integral_constant<int, ticks.ahead[TK::in_s(j)]>{}, std::integral_constant<int, ticks.ahead[TK::in_s(j + 1)]>{}, ref);
       __builtin_amdgcn_sched_barrier(0);
       if (j == 2 * KS - 2) {
         // The reference of a column stays as long as neither lane's sum of 16 values exceeds `limit`: then no value does, and
         // the rescaling of O is skipped for almost every unit.  The result is exact either way, and a lane's arithmetic
         // never depends on what other query columns (pad rows included) hold.
         // (A unit without a valid key leaves every value at zero; the first one that has some sets the reference.)
+        // (`bar`: `limit`, or as long as there is no reference less than any sum)
         float tsum[2] = {ta[0] + tb[0], ta[1] + tb[1]};
-        const bool rare = (!have & (valid != 0)) | (__any(fmaxf(tsum[0], tsum[1]) > limit) != 0);
-        if (__builtin_expect(rare, 0)) {
+        if (__builtin_expect(__any(!(fmaxf(tsum[0], tsum[1]) <= bar)), 0) && (have || valid)) {
           // (the last products that wrote O lie almost a whole S phase back, so it can be read at once)
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
@@ -490,14 +534,17 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
 #pragma unroll
               for (int w = 0; w < 4; ++w) {
                 const int it = 8 * st + 4 * b + w;
-                p_fma(S, it, use);
-                p_exp(it, 0);
-                p_exp(it, 1);
-                p_sum(it);
+                for (int i = 0; i < 2; ++i) {
+                  p_fma(S, it, i, use);
+                  p_exp(it, i);
+                  p_sum(it, i);
+                }
+                p_convert(it);
               }
             tsum[b] = ta[b] + tb[b];
           }
           have = true;
+          bar = limit;
         }
         lsum[0] += tsum[0];
         lsum[1] += tsum[1];
@@ -519,6 +566,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         __builtin_amdgcn_sched_barrier(0);
       }
       mfma_o(o[i % DVB][j & 1], v_op(i), __builtin_bit_cast(bf16x8, pc[j & 1][i / DVB]));
+      __builtin_amdgcn_sched_barrier(0);
       if (more1 && j == 2 * (NPV - kAhead)) {  // K(u+2) has landed; newer: V(u+1) and a part of K(u+3)
         if (more3) wait_vmcnt<NC + (KIND == 2 ? kPart : NC)>();
         else if (more2) wait_vmcnt<NC>();
@@ -533,7 +581,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
         if (reads_row(q, 0)) kcur[to - NPV] = TL::rowmajor_at(smem + par * HALF, lane_a, to - NPV);
         if (reads_row(q, 1)) kcur[to - NPV + 1] = TL::rowmajor_at(smem + par * HALF, lane_a, to - NPV + 1);
       }
-      if (more1) p_stages(T, FwdStages<D>::before_pv(j), FwdStages<D>::before_pv(j + 1), ref);
+      if (more1) p_ops(T, std::integral_constant<int, ticks.ahead[TK::in_pv(j)]>{}, std::integral_constant<int, ticks.ahead[TK::in_pv(j + 1)]>{}, ref);
       __builtin_amdgcn_sched_barrier(0);
     });
     valid = un[0].valid;
@@ -544,17 +592,27 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
     const std::integral_constant<int, 2> steady;
     const std::integral_constant<int, 1> inner;
     const std::integral_constant<int, 0> last;
+    const std::true_type own;
+    const std::false_type shared;
     int u = 0;
-    for (; u + 4 < nu; u += 2) {
-      body(steady, 0, s0, s1, u);
-      body(steady, 1, s1, s0, u + 1);
+    if constexpr (PAIRS) {
+      if (paired)
+        for (; u + 4 < nu; u += 2) {
+          body(steady, own, 0, s0, s1, u);
+          body(steady, own, 1, s1, s0, u + 1);
+        }
     }
+    if (!paired)
+      for (; u + 4 < nu; u += 2) {
+        body(steady, shared, 0, s0, s1, u);
+        body(steady, shared, 1, s1, s0, u + 1);
+      }
     for (; u + 1 < nu; ++u) {
-      body(inner, u & 1, s0, s1, u);
+      body(inner, shared, u & 1, s0, s1, u);
       s0[0] = s1[0];
       s0[1] = s1[1];
     }
-    body(last, u & 1, s0, s1, u);
+    body(last, shared, u & 1, s0, s1, u);
   }
   mfma_fence();  // the last matrix results land before they are read
 #pragma unroll

@@ -15,7 +15,7 @@ struct TickTable {
     int tick, use;   // behind which instruction it is requested, ahead of which one it is waited for (T and more: of the next unit)
     int kind, i, part;
   };
-  enum Op { MUL, EXP, CVT };  // of an item, a pair of values: arithmetic on value i, its exponential, the conversion of the pair
+  enum Op { MUL, EXP, ADD, CVT };  // of an item, a pair of values: arithmetic on value i, its exponential, a sum, the conversion of the pair
   struct Work {
     Op op;
     int item, i;

@@ -55,7 +55,7 @@ struct CubeUnits {
     list = nullptr, mask = mask_, n = n_, lane = lane_, ncubes = ncubes_, chunk = 0;
     idx_v = lds_list[list_slot(0, lane, n)];
   }
-  __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
+  __device__ __forceinline__ bool loaded(int t) const { return (unsigned)t / kTilesPerChunk == (unsigned)chunk; }
   __device__ __forceinline__ void rows(int t, int half, Unit& u) const {
     u.a = (unsigned)__builtin_amdgcn_readlane(idx_v, t & 63) * (unsigned)TL::BYTES + (unsigned)half * (TL::BYTES / 2);
     u.b = u.a + TL::BYTES / 4;
@@ -110,7 +110,7 @@ struct SubCubeUnits {
     chunk = t / kTilesPerChunk;
     idx_v = list[list_slot(chunk, lane, n)];
   }
-  __device__ __forceinline__ bool loaded(int t) const { return t / kTilesPerChunk == chunk; }
+  __device__ __forceinline__ bool loaded(int t) const { return (unsigned)t / kTilesPerChunk == (unsigned)chunk; }
   __device__ __forceinline__ unsigned entry_offset(int e) const {  // e in the current chunk
     const int id = __builtin_amdgcn_readlane(idx_v, min(e, n - 1) & 63);
     return (unsigned)(id >> 2) * (unsigned)TL::BYTES + (unsigned)subcube_first_slot(id & 3) * (unsigned)TL::ROW_BYTES;

@@ -37,7 +37,7 @@
 // cycles by the costs, 2.03 -> 1.87 M in a whole launch (39936 tokens, 12 heads, top-78), of which the clock leaves a third of the time: 1217 ->
 // 1184 us for the forward, 252 -> 247 at 16384 tokens, top-32 (two generations' start-up and end in it), results the same bits.  16x16x32 matrix
 // instructions, which take less energy (fine_bwd_dkv.h), cost more issue slots than this loop has.
-Around the walk a wavefront
+// Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
 // normalising, gating and storing, which nothing overlaps on its SIMD: halved per block where a wavefront has a block of
 // its own.  That, one factor per lane instead of per row and item on the way out, and a start that waits for K alone:

@@ -281,24 +281,35 @@ __device__ __forceinline__ void dq_block(
   __builtin_amdgcn_sched_barrier(0);
 
   const int my = wave * (4 * HALF);
-  // all units: `body(kind, par, u)` is one.  KIND 2: the units up to u + 2 exist; 1: u + 1 exists; 0: u is the last one.  `par` = u & 1.
+  // all units: `body(kind, own, par, u)` is one.  KIND 2: the units up to u + 2 exist; 1: u + 1 exists; 0: u is the last one.  OWN: the
+  // wavefront has a block of its own (then the half of a unit of the steady walk is known: `par`).  `par` = u & 1.
   auto walk = [&](auto body) {
     if (nu == 0) return;
     const std::integral_constant<int, 2> steady;
     const std::integral_constant<int, 1> inner;
     const std::integral_constant<int, 0> last;
+    const std::true_type own;
+    const std::false_type shared;
     int u = 0;
-    for (; u + 3 < nu; u += 2) {  // (kNarrow: the unit itself gets that after the next, in parts)
-      if (!kNarrow) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
-      body(steady, 0, u);
-      if (!kNarrow) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
-      body(steady, 1, u + 1);
+    if constexpr (PAIRS && kNarrow) {
+      if (paired)
+        for (; u + 3 < nu; u += 2) {
+          body(steady, own, 0, u);
+          body(steady, own, 1, u + 1);
+        }
     }
+    if (!(PAIRS && kNarrow && paired))
+      for (; u + 3 < nu; u += 2) {  // (kNarrow: the unit itself gets that after the next, in parts)
+        if (!kNarrow) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
+        body(steady, shared, 0, u);
+        if (!kNarrow) list.get(tile_of(u + 3), half_of(u + 3), un[2]);
+        body(steady, shared, 1, u + 1);
+      }
     for (; u + 1 < nu; ++u) {
       if (u + 2 < nu) list.get(tile_of(u + 2), half_of(u + 2), un[2]);
-      body(inner, u & 1, u);
+      body(inner, shared, u & 1, u);
     }
-    body(last, u & 1, u);
+    body(last, shared, u & 1, u);
   };
   if constexpr (kNarrow) {
   using TK = DqTicks;
@@ -323,8 +334,10 @@ __device__ __forceinline__ void dq_block(
 #pragma unroll
     for (int i = 0; i < KS; ++i) ka[i] = TL::rowmajor_at(smem, lane_a, i & 1, i >> 1);
   }
-  walk([&](auto kind_tag, int par, int u) {
+  int next_tile = nu > 2 ? tile_of(1) : 0;  // tile of the unit that is fetched next in the steady walk
+  walk([&](auto kind_tag, auto own_tag, int par, int u) {
     constexpr int KIND = decltype(kind_tag)::value;
+    constexpr bool OWN = decltype(own_tag)::value;
     constexpr bool more1 = KIND >= 1;
     const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu);
     const unsigned char *kc = smem + par * HALF, *vc = smem + (2 + par) * HALF, *kn = smem + (1 - par) * HALF;  // K(u), V(u), K(u+1)
@@ -380,7 +393,6 @@ __device__ __forceinline__ void dq_block(
       if (KIND == 2 && TK::v_copy(t) >= 0) copy.aim(v_at, TK::v_copy(t));
       if (KIND == 2 && TK::k_copy(t) >= 0) copy.aim(k_at, TK::k_copy(t));
     };
-    int t2 = 0, h2 = 0;  // tile and half of unit u + 2
     auto behind = [&](auto tick) {
       constexpr int t = decltype(tick)::value;
       __builtin_amdgcn_sched_barrier(0);
@@ -389,11 +401,15 @@ __device__ __forceinline__ void dq_block(
       // (where the last units are near: all of it at once, one branch)
       if (KIND == 1 && t == TK::kFirstCopyV && more2) copy.all(vb, un[2], v_at);
       if (KIND == 1 && t == TK::kFirstCopyK && more2) copy.all(kb, un[2], k_at);
-      if (KIND == 2) {
-        if (t == TK::kTile) t2 = tile_of(u + 2), h2 = half_of(u + 2);
-        if (t == TK::kChunk) list.load(t2);
-        if (t == TK::kRows) list.rows(t2, h2, un[2]);
-        if (t == TK::kValid) list.valid(t2, h2, un[2]);
+      if (KIND == 2) {  // (both halves of a tile one after the other where the block is the wavefront's own)
+        const int half = OWN ? par : wave & 1;
+        if (t == TK::kTile && !(OWN && half)) {
+          next_tile += OWN ? 1 : NW / 2;
+          if (next_tile >= tiles) next_tile -= tiles;
+        }
+        if (t == TK::kChunk && !(OWN && half)) list.load(next_tile);
+        if (t == TK::kRows) list.rows(next_tile, half, un[2]);
+        if (t == TK::kValid) list.valid(next_tile, half, un[2]);
       }
       if (more1 && t == TK::kRowsReady) {  // K(u+1) and V(u+1) have landed; newer: V(u+2) and K(u+2), as far as requested
         if (more2) wait_vmcnt<NC + (KIND == 2 ? TK::k_copies_before(TK::kRowsReady) : NC)>();
@@ -465,7 +481,7 @@ __device__ __forceinline__ void dq_block(
     for (int s = 0; s < KS; ++s) ka[s] = TL::rowmajor_at(smem, lane_a, s);
   }
 
-  walk([&](auto kind_tag, int par, int u) {
+  walk([&](auto kind_tag, auto, int par, int u) {
     constexpr int KIND = decltype(kind_tag)::value;
     constexpr bool more1 = KIND >= 1;
     const bool more2 = KIND == 2 || (KIND == 1 && u + 2 < nu);

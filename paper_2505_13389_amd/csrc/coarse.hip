@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void k_coarse_rows(int rows, int Nc, int K, fl
 typedef float f32x4m __attribute__((ext_vector_type(4)));
 constexpr int kFusedMaxCubes = 1536;  // the LDS block of 16 rows: 98.6 KB at 1536 cubes
 template <int D, int NCH>
-__global__ __launch_bounds__(1024) void k_coarse_fused(int Nc, int K, float scale, const float* __restrict__ qc,
+__global__ __launch_bounds__(1024, NCH == 12 ? 8 : 4) void k_coarse_fused(int Nc, int K, float scale, const float* __restrict__ qc,
                                                        const float* __restrict__ kc, const float* __restrict__ vc,
                                                        float* __restrict__ oc, float* __restrict__ lse_c,
                                                        int32_t* __restrict__ idx, int emit_idx) {
@@ -86,6 +86,18 @@ __global__ __launch_bounds__(1024) void k_coarse_fused(int Nc, int K, float scal
     for (int i = 0; i < 4; ++i) S[(4 * kq + i) * LDS_ROW + n] = n < Nc ? scale * acc[i] : 0.f;
   }
   __syncthreads();
+  // 513 to 768 cubes: values of Vc for the third step are requested kStep groups of 16 contraction values at a time, the first ones during the second
+  // step (one group at a time, each a trip to the L2: 624 cubes, 12 heads 72 -> 61 us; 256 cubes 20.1 -> 20.6, 280 21.8 -> 22.9; longer rows leave no registers for two workgroups a compute unit).
+  constexpr int kStep = NCH == 12 ? 4 : 1;
+  const int cb = wave % CB, ks = wave / CB;
+  float vv[kStep][4];
+  auto request_v = [&](int k1) {  // (rows beyond Nc: any value that is there, taken as zero below)
+#pragma unroll
+    for (int i = 0; i < kStep; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) vv[i][j] = vb[(unsigned)(min(k1 + (i * KSPLIT + ks) * 16 + 4 * kq + j, Nc - 1) * D + cb * 16 + l16)];
+  };
+  if (kStep > 1) request_v(0);
   // 2. rows (rows of the block beyond Nc hold the logits of zero queries and are never stored)
   if (wave < rows_valid) {
     const long long row = bh * Nc + m0 + wave;
@@ -95,19 +107,25 @@ __global__ __launch_bounds__(1024) void k_coarse_fused(int Nc, int K, float scal
   // 3. O_c[m0 + m][e] = sum_n P[m][n] Vc[n][e]: wavefront (cb, ks) takes columns 16*cb.. and every
   //    KSPLIT-th group of 16 contraction values
   {
-    const int cb = wave % CB, ks = wave / CB;
     f32x4m acc = {0.f, 0.f, 0.f, 0.f};
-    const float* vcol = vb + cb * 16 + l16;
-    for (int k0 = ks * 16; k0 < kpad; k0 += 16 * KSPLIT) {
+    auto multiply = [&](int k0, const float* v) {
       const float4 a = *(const float4*)&S[l16 * LDS_ROW + k0 + 4 * kq];
-      const int kk = k0 + 4 * kq;
       float b[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = kk + j < Nc ? vcol[(long long)(kk + j) * D] : 0.f;
+      for (int j = 0; j < 4; ++j) b[j] = k0 + 4 * kq + j < Nc ? v[j] : 0.f;
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[0], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[1], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[2], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[3], acc, 0, 0, 0);
+    };
+    for (int k1 = 0; k1 + ks * 16 < kpad; k1 += 16 * KSPLIT * kStep) {  // (uniform)
+      if (kStep == 1) request_v(k1);
+#pragma unroll
+      for (int i = 0; i < kStep; ++i) {
+        const int k0 = k1 + (i * KSPLIT + ks) * 16;
+        if (kStep == 1 || k0 < kpad) multiply(k0, vv[i]);
+      }
+      if (kStep > 1 && k1 + 16 * KSPLIT * kStep < kpad) request_v(k1 + 16 * KSPLIT * kStep);
     }
     *(float4*)part[wave][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
     __syncthreads();

@@ -1,0 +1,32 @@
+"""Coarse stage in one launch for 513 to 768 cubes, whose third step requests rows of V_c four groups of 16 at a time: first and last
+number of cubes, whole and broken groups, rounds and shares of a wavefront, against float64."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [(1, 19, 27), (2, 16, 17), (3, 11, 17), (7, 9, 10), (8, 8, 10), (13, 59, 1), (8, 8, 12)])  # 513 to 768 cubes
+def test_coarse_stage_of_long_rows(n, d):
+    import torch
+    from paper_2505_13389_amd import vsa
+    K, H = 3, 2
+    pb = vsa.Problem(1, H, 4 * n[0], 4 * n[1], 4 * n[2], d, K, flags=vsa.VSA_FLAG_COARSE_FUSED)
+    Np, Nc = vsa.vsa_padded_tokens(pb)
+    assert 512 < Nc <= 768
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Nc + d)
+    q, k, v, gate = (torch.randn((1, H, Np, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    buf = vsa.Buffers(pb, with_gate_f=False)
+    buf.forward(q, k, v, gate, None)
+    torch.cuda.synchronize()
+    qc, kc, vc = (x[0].double().view(H, Nc, 64, d).mean(2) for x in (q, k, v))
+    S = torch.bmm(qc, kc.transpose(1, 2).contiguous()) * d ** -0.5
+    # float32 sums of 64, d and Nc terms of order one: off by some 1e-6; 2e-5 is a wide margin for them and far below a missing row
+    oc = torch.bmm(torch.softmax(S, -1), vc)
+    got = buf.out_coarse[0].double()
+    assert float((got - oc).norm() / oc.norm()) < 2e-5
+    assert float((buf.lse_coarse[0].double() - torch.logsumexp(S, -1)).abs().max()) < 2e-5
+    idx = buf.block_idx[0].long()
+    least = torch.gather(S, 2, idx).min(-1).values
+    assert bool((least >= torch.topk(S, K, -1).values[..., -1] - 1e-5).all()) and bool((idx[..., 1:] > idx[..., :-1]).all())

@@ -1,0 +1,41 @@
+"""d = 128, every block selects every block: the walks start apart and wrap around, across the chunks of 64 list entries, in wavefronts with a block
+of their own (the first 1024 blocks) and in pairs that share one; forward, dQ and dK/dV against float64."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("grid3,H", [((8, 32, 32), 9), ((7, 30, 29), 9), ((4, 36, 32), 16)])  # 128, 128 (padded) and 72 blocks a head
+def test_dense_walks_wrap(grid3, H, d=128):
+    import torch
+    from paper_2505_13389_amd import vsa
+    pb = vsa.Problem(1, H, *grid3, d, 1)
+    Np, Nc = vsa.vsa_padded_tokens(pb)
+    pb = vsa.Problem(1, H, *grid3, d, Nc)
+    routes = vsa.vsa_host_routes(pb)
+    assert routes["fwd_pairs"] > 0 and routes["dq_pairs"] > 0
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Nc + H)
+    rand = lambda: torch.randn((1, H, Np, d), generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v, dout = rand(), rand(), rand(), rand()
+    zero = torch.zeros_like(q)  # (no coarse term: the fine stage alone)
+    buf = vsa.Buffers(pb, with_gate_f=False)
+    buf.forward(q, k, v, zero, None)
+    buf.backward(q, k, v, zero, None, dout, workspace_kept=True)
+    torch.cuda.synchronize()
+    T, Hh, W = grid3
+    n = [-(-e // 4) for e in grid3]
+    axis = [torch.arange(4 * m, device="cuda") < e for m, e in zip(n, grid3)]
+    valid = (axis[0][:, None, None] & axis[1][None, :, None] & axis[2][None, None, :])
+    valid = valid.view(n[0], 4, n[1], 4, n[2], 4).permute(0, 2, 4, 1, 3, 5).reshape(-1)
+    for h in (0, H // 2, H - 1):
+        Q, K, V, dO = (x[0, h][valid].double() for x in (q, k, v, dout))
+        P = torch.softmax(Q @ K.T.contiguous() * d ** -0.5, -1)
+        O = P @ V
+        dS = P * (dO @ V.T.contiguous() - (dO * O).sum(-1, keepdim=True))
+        want = {"out": O, "dv": P.T.contiguous() @ dO, "dq": dS @ K * d ** -0.5, "dk": dS.T.contiguous() @ Q * d ** -0.5}
+        for name, ref in want.items():
+            got = getattr(buf, name)[0, h].double()
+            # bf16 operands and one bf16 rounding: 2 to 4e-3 of the 2-norm everywhere; the suite's bar is 1e-2
+            assert float((got[valid] - ref).norm() / ref.norm()) < 1e-2, (name, h)
+            assert not got[~valid].any(), (name, h)

@@ -1,9 +1,9 @@
 // What lies behind which matrix instruction (TICK) of a unit, for the kernels whose wavefronts are alone on their SIMD and therefore
-// ordered instruction by instruction: tables that the kernels' constructors fill at compile time.
+// ordered instruction by instruction: tables filled at compile time.
 //
-// A tick of a 16x16x32 instruction is 16 cycles of the matrix pipe.  The instruction takes about 6 of them to issue and what lies behind it the
-// costs below (measured with one wavefront on the SIMD); where it takes longer than the tick, the pipe waits, and fewer instructions
-// behind the next one do not make up for it.
+// A 16x16x32 instruction takes the matrix pipe 16 cycles and about 6 to issue, a 32x32x16 one 32 and 4; what lies behind it takes the
+// costs below (measured with one wavefront on the SIMD).  Where that is longer than the pipe's share, the pipe waits, and fewer instructions
+// behind the next one do not make up for it: so every tick is to take about the same time.
 #pragma once
 
 namespace vsa {

@@ -41,8 +41,8 @@ __global__ __launch_bounds__(256) void k_coarse_rows(int rows, int Nc, int K, fl
 // both operands.  NCH*64 >= Nc bounds the row (and the LDS block: 16 x (NCH*64 + 4) floats).
 typedef float f32x4m __attribute__((ext_vector_type(4)));
 constexpr int kFusedMaxCubes = 1536;  // the LDS block of 16 rows: 98.6 KB at 1536 cubes
-template <int D, int NCH>
-__global__ __launch_bounds__(1024, NCH == 12 ? 8 : 4) void k_coarse_fused(int Nc, int K, float scale, const float* __restrict__ qc,
+template <int D, int NCH, bool BATCH>
+__global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_coarse_fused(int Nc, int K, float scale, const float* __restrict__ qc,
                                                        const float* __restrict__ kc, const float* __restrict__ vc,
                                                        float* __restrict__ oc, float* __restrict__ lse_c,
                                                        int32_t* __restrict__ idx, int emit_idx) {
@@ -86,18 +86,18 @@ __global__ __launch_bounds__(1024, NCH == 12 ? 8 : 4) void k_coarse_fused(int Nc
     for (int i = 0; i < 4; ++i) S[(4 * kq + i) * LDS_ROW + n] = n < Nc ? scale * acc[i] : 0.f;
   }
   __syncthreads();
-  // 513 to 768 cubes: values of Vc for the third step are requested kStep groups of 16 contraction values at a time, the first ones during the second
-  // step (one group at a time, each a trip to the L2: 624 cubes, 12 heads 72 -> 61 us; 256 cubes 20.1 -> 20.6, 280 21.8 -> 22.9; longer rows leave no registers for two workgroups a compute unit).
-  constexpr int kStep = NCH == 12 ? 4 : 1;
-  const int cb = wave % CB, ks = wave / CB;
-  float vv[kStep][4];
-  auto request_v = [&](int k1) {  // (rows beyond Nc: any value that is there, taken as zero below)
+  // BATCH: values of Vc for the third step are requested kStep groups of 16 contraction values at a time, the first ones during the second step,
+  // where otherwise each group is a trip to the L2 (see launch_coarse).
+  constexpr int kStep = 4;
+  [[maybe_unused]] float vv[kStep][4];
+  [[maybe_unused]] auto request_v = [&](int k1) {  // (rows beyond Nc: any value that is there, taken as zero below)
+    const int cb = wave % CB, ks = wave / CB;
 #pragma unroll
     for (int i = 0; i < kStep; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) vv[i][j] = vb[(unsigned)(min(k1 + (i * KSPLIT + ks) * 16 + 4 * kq + j, Nc - 1) * D + cb * 16 + l16)];
   };
-  if (kStep > 1) request_v(0);
+  if constexpr (BATCH) request_v(0);
   // 2. rows (rows of the block beyond Nc hold the logits of zero queries and are never stored)
   if (wave < rows_valid) {
     const long long row = bh * Nc + m0 + wave;
@@ -107,25 +107,31 @@ __global__ __launch_bounds__(1024, NCH == 12 ? 8 : 4) void k_coarse_fused(int Nc
   // 3. O_c[m0 + m][e] = sum_n P[m][n] Vc[n][e]: wavefront (cb, ks) takes columns 16*cb.. and every
   //    KSPLIT-th group of 16 contraction values
   {
+    const int cb = wave % CB, ks = wave / CB;
     f32x4m acc = {0.f, 0.f, 0.f, 0.f};
-    auto multiply = [&](int k0, const float* v) {
+    const float* vcol = vb + cb * 16 + l16;
+    auto group = [&](int k0, auto value) {  // value(j): of row k0 + 4*kq + j, which exists
       const float4 a = *(const float4*)&S[l16 * LDS_ROW + k0 + 4 * kq];
+      const int kk = k0 + 4 * kq;
       float b[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = k0 + 4 * kq + j < Nc ? v[j] : 0.f;
+      for (int j = 0; j < 4; ++j) b[j] = kk + j < Nc ? value(j) : 0.f;
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[0], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[1], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[2], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[3], acc, 0, 0, 0);
     };
-    for (int k1 = 0; k1 + ks * 16 < kpad; k1 += 16 * KSPLIT * kStep) {  // (uniform)
-      if (kStep == 1) request_v(k1);
+    if constexpr (BATCH) {
+      for (int k1 = 0; k1 + ks * 16 < kpad; k1 += 16 * KSPLIT * kStep) {  // (uniform)
 #pragma unroll
-      for (int i = 0; i < kStep; ++i) {
-        const int k0 = k1 + (i * KSPLIT + ks) * 16;
-        if (kStep == 1 || k0 < kpad) multiply(k0, vv[i]);
+        for (int i = 0; i < kStep; ++i) {
+          const int k0 = k1 + (i * KSPLIT + ks) * 16;
+          if (k0 < kpad) group(k0, [&](int j) { return vv[i][j]; });
+        }
+        if (k1 + 16 * KSPLIT * kStep < kpad) request_v(k1 + 16 * KSPLIT * kStep);
       }
-      if (kStep > 1 && k1 + 16 * KSPLIT * kStep < kpad) request_v(k1 + 16 * KSPLIT * kStep);
+    } else {
+      for (int k0 = ks * 16; k0 < kpad; k0 += 16 * KSPLIT) group(k0, [&](int j) { return vcol[(long long)(k0 + 4 * kq + j) * D]; });
     }
     *(float4*)part[wave][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
     __syncthreads();
@@ -216,13 +222,23 @@ hipError_t launch_coarse(int BH, int Nq, int Nk, int d, int K, float scale, cons
   if (Nq == Nk && !kcnt && Nk <= kFusedMaxCubes && fused) {
     const int Nc = Nq;
     const unsigned fgrid = (unsigned)(BH * ((Nc + 15) / 16));
-#define VSA_FUSED(NCH_)                                                                                             \
-  do {                                                                                                              \
-    if (d == 128) k_coarse_fused<128, NCH_><<<fgrid, 1024, 0, s>>>(Nc, K, scale, qc, kc, vc, oc, lse_c, idx, emit_idx); \
-    else k_coarse_fused<64, NCH_><<<fgrid, 1024, 0, s>>>(Nc, K, scale, qc, kc, vc, oc, lse_c, idx, emit_idx);          \
+#define VSA_FUSED_AS(D_, NCH_, BATCH_) \
+  k_coarse_fused<D_, NCH_, BATCH_><<<fgrid, 1024, 0, s>>>(Nc, K, scale, qc, kc, vc, oc, lse_c, idx, emit_idx)
+#define VSA_FUSED(NCH_)                            \
+  do {                                             \
+    if (d == 128) VSA_FUSED_AS(128, NCH_, false);  \
+    else VSA_FUSED_AS(64, NCH_, false);            \
   } while (0)
+    // V_c in batches (BATCH): 513 to 768 cubes at d = 128, where compute units get a second workgroup.  The kernel, us, one group at a time against
+    // batches: 513 cubes, 8 heads (264 workgroups) 52.2 / 48.6, 624, 7 heads 62.5 / 54.1, 768, 6 heads 72.7 / 63.8, 624, 24 heads 129.6 / 103.5.
+    // Up to 256 workgroups the row step, in the 64 registers that two workgroups leave a lane, costs what the batches save: 544 cubes, 7 heads (238
+    // workgroups) 32.5 / 33.7, 4 heads 32.3 / 33.1, 624, 4 heads 34.9 / 35.2, 768, 1 head 39.5 / 39.0.  d = 64, with half the groups a wavefront: 513 cubes, 12
+    // heads 33.7 / 36.2, 624, 24 heads 67.6 / 71.0, 768, 12 heads 59.5 / 59.7.  Fewer cubes: 256 20.1 / 20.6, 280 21.8 / 22.9.  From 769 on a second workgroup
+    // does not fit into LDS (90.6 KB a workgroup at d = 128); batches were not tried there.
+    const bool batch = d == 128 && Nc > 512 && Nc <= 768 && fgrid > 256;
     // NCH = logits per lane of the row step: the smallest that covers Nc
-    if (Nc <= 64) VSA_FUSED(1);
+    if (batch) VSA_FUSED_AS(128, 12, true);
+    else if (Nc <= 64) VSA_FUSED(1);
     else if (Nc <= 128) VSA_FUSED(2);
     else if (Nc <= 256) VSA_FUSED(4);
     else if (Nc <= 512) VSA_FUSED(8);
@@ -230,6 +246,7 @@ hipError_t launch_coarse(int BH, int Nq, int Nk, int d, int K, float scale, cons
     else if (Nc <= 1024) VSA_FUSED(16);
     else VSA_FUSED(24);
 #undef VSA_FUSED
+#undef VSA_FUSED_AS
     return hipGetLastError();
   }
   if ((e = gemm32(BH, Nq, Nk, d, scale, qc, sq, d, 1, kc, sk, 1, d, sc, ss, s)) != hipSuccess) return e;

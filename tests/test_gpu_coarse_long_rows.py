@@ -1,19 +1,21 @@
-"""Coarse stage in one launch for 513 to 768 cubes, whose third step requests rows of V_c four groups of 16 at a time: first and last
-number of cubes, whole and broken groups, rounds and shares of a wavefront, against float64."""
+"""Coarse stage in one launch for 513 to 768 cubes.  With d = 128 and more than 256 workgroups (here: 8 heads) its third step requests rows of V_c
+four groups of 16 at a time, else one: first and last number of cubes, whole and broken groups, rounds and shares of a wavefront, against
+float64."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("H", [2, 8])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [(1, 19, 27), (2, 16, 17), (3, 11, 17), (7, 9, 10), (8, 8, 10), (13, 59, 1), (8, 8, 12)])  # 513 to 768 cubes
-def test_coarse_stage_of_long_rows(n, d):
+def test_coarse_stage_of_long_rows(n, d, H):
     import torch
     from paper_2505_13389_amd import vsa
-    K, H = 3, 2
+    K = 3
     pb = vsa.Problem(1, H, 4 * n[0], 4 * n[1], 4 * n[2], d, K, flags=vsa.VSA_FLAG_COARSE_FUSED)
     Np, Nc = vsa.vsa_padded_tokens(pb)
-    assert 512 < Nc <= 768
+    assert 512 < Nc <= 768 and (H * ((Nc + 15) // 16) > 256) == (H == 8)
     g = torch.Generator(device="cuda")
     g.manual_seed(Nc + d)
     q, k, v, gate = (torch.randn((1, H, Np, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))

@@ -686,7 +686,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_bwd_dq(
 // Bound by latency.  32 cubes, 2 heads, d = 64, top-8: dQ 9.3, dK/dV with its reduction 14.1 and the coarse backward 7.2 us
 // between events became 15.0 of one launch; the whole backward 31 -> 19 us, 64 cubes, 4 heads 0.77 to 0.94 of the time.  Not for
 // larger launches: at 256 blocks each pass fills the chip by itself.
-template <int D, bool COARSE>
+template <int D, bool COARSE, bool NARROW>
 __global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
     unsigned dkv_blocks, int BH, int Nc, int K, float sl2, float scale, const uint4* __restrict__ q, const uint4* __restrict__ k,
     const uint4* __restrict__ v, const uint4* __restrict__ dof, const int32_t* __restrict__ idx, const int32_t* __restrict__ col,
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(256, 1) void k_fine_bwd_one(
   __shared__ int last_run;
   __shared__ SmallCoarse<D> lc;
   if (blockIdx.x < dkv_blocks)
-    dkv_block<D, 4, false, COARSE>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items, split, parts,
+    dkv_block<D, 4, false, COARSE, NARROW>(smem, &last_run, blockIdx.x, BH, Nc, K, sl2, scale, q, k, v, dof, col, order, items, split, parts,
                                    cap, rowd, dkc, dvc, mask, dk, dv, m_blocks, 0, raster, sc, &lc);
   else
     dq_block<D, 4, CubeUnits, false, COARSE>(smem, masks, blockIdx.x - dkv_blocks, gridDim.x - dkv_blocks, Nc, K, sl2, scale, q, k, v, dof,
@@ -718,17 +718,20 @@ hipError_t launch_fine_bwd_one(int BH, int Nc, int d, int K, float scale, const 
   const int items = Nc + cap;
   const unsigned dkv_blocks = dkv_grid(BH, items, dkv_heads_at_once(Nc, d)), grid = dkv_blocks + (unsigned)(BH * Nc);  // (dkv_grid is a multiple of 8: the XCDs stay)
   const SmallCoarseArgs sc = {qc, kc, vc, doc, lse_c, dot};
-#define VSA_ONE(D_, COARSE_)                                                                                             \
-  k_fine_bwd_one<D_, COARSE_><<<grid, 256, 0, s>>>(dkv_blocks, BH, Nc, K, scale * kLog2e, scale, (const uint4*)q, (const uint4*)k, \
+#define VSA_ONE(D_, COARSE_, NARROW_)                                                                                             \
+  k_fine_bwd_one<D_, COARSE_, NARROW_><<<grid, 256, 0, s>>>(dkv_blocks, BH, Nc, K, scale * kLog2e, scale, (const uint4*)q, (const uint4*)k, \
                                                    (const uint4*)v, (const uint4*)dof, idx, col, order, items, split, parts, cap, \
                                                    rowd, dqc, dkc, dvc, mask, (uint4*)dq, (uint4*)dk, (uint4*)dv, m_blocks, raster, sc)
   const bool coarse = fine_bwd_with_coarse(Nc, m_blocks);
   if (d == 128) {
-    if (coarse) VSA_ONE(128, true);
-    else VSA_ONE(128, false);
+    const bool narrow = dkv_narrow(BH * Nc, K, 0);
+    if (coarse && narrow) VSA_ONE(128, true, true);
+    else if (coarse) VSA_ONE(128, true, false);
+    else if (narrow) VSA_ONE(128, false, true);
+    else VSA_ONE(128, false, false);
   } else {
-    if (coarse) VSA_ONE(64, true);
-    else VSA_ONE(64, false);
+    if (coarse) VSA_ONE(64, true, false);
+    else VSA_ONE(64, false, false);
   }
 #undef VSA_ONE
   return hipGetLastError();

@@ -36,9 +36,9 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // The order inside a unit is the dependency order, S | dP | dV | dK: P is formed while dP is multiplied,
 // dS while dV is, so the vector work hides behind matrix work without a second set of registers.
 //
-// d = 128 multiplies with 16x16x32 instructions (128 of 16 cycles), an operand with the four 16-key blocks one after the other;
-// behind each lies what DkvTicks deals to it, a read, a copy or two or three vector instructions, and P of the first 32 keys begins
-// while S of the others is multiplied.  d = 64 has 32x32x16 instructions (32 of 32 cycles) in STEPS: one step = one LDS
+// NARROW (d = 128, where dkv_narrow says so): 16x16x32 instructions (128 of 16 cycles), an operand with the four 16-key blocks one after the
+// other; behind each lies what DkvTicks deals to it, a read, a copy or two or three vector instructions, and P of the first 32 keys begins
+// while S of the others is multiplied.  Else 32x32x16 instructions (d = 128 64, d = 64 32, of 32 cycles) in STEPS: one step = one LDS
 // operand multiplied with both key halves, the operand reads of the step kAhead later, and behind either instruction a share of the
 // copies and of the vector work (DkvStages).
 // Why: under the power limit the chip gets 1.81 PFLOP/s out of the large instructions on N(0,1) operands and 2.05 to 2.19 out of the small ones,
@@ -53,7 +53,7 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // SUB: the lists name key cubes of 16 tokens (Sec. 3.2, the 64 x 16 row of the tile-size tables).  The
 // workgroup still owns a 64-row key block; its list is the union of the lists of the block's four key
 // cubes, and every entry says (bits 16..19) which of them the query block selected: a large number is
-// subtracted from S of the other keys (in the initial values; d = 64: by one more matrix instruction per key half).  The
+// subtracted from S of the other keys (NARROW: in the initial values; else by one more matrix instruction per key half).  The
 // pooled-gradient terms are per key cube.
 //
 // What bounds it: the clock, which falls as the matrix pipe fills, and the instructions of one wavefront.  d = 128: a unit is 128
@@ -78,25 +78,30 @@ struct DkvShape {
   static constexpr int NST = D == 128 ? 2 : 4;       // stages per wavefront
   static constexpr int LDS = HALF + NW * NST * STAGE;
 };
-// d = 64: what lies behind which matrix instruction of a unit: the P stages ahead of instruction j of the dP phase and, behind those, of the dV
+// 32x32x16 instructions: what lies behind which of them in a unit: the P stages ahead of instruction j of the dP phase and, behind those, of the dV
 // phase; the dS stages ahead of instruction j of the dV and dK phases; the copy of dO_f rows behind instruction j of the dK phase (-1: none).
+template <int D>
 struct DkvStages {
   static constexpr int p_at(int j) {
-    constexpr int n[16] = {3, 3, 3, 3, 3, 3, 3, 3, 4, 3, 3};
-    return n[j];
+    constexpr int wide[32] = {1, 1, 2, 1, 2, 2, 1, 2, 1, 2, 1, 2, 1, 2, 1, 2, 2, 2, 2, 2, 1, 1}, narrow[16] = {3, 3, 3, 3, 3, 3, 3, 3, 4, 3, 3};
+    return D == 128 ? wide[j] : narrow[j];
   }
   static constexpr int s_at(int j) {
-    constexpr int n[16] = {0, 0, 0, 2, 2, 2, 2, 2, 3, 2, 2};
-    return n[j];
+    constexpr int wide[32] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, narrow[16] = {0, 0, 0, 2, 2, 2, 2, 2, 3, 2, 2};
+    return D == 128 ? wide[j] : narrow[j];
   }
   static constexpr int p(int j) { return j == 0 ? 0 : p(j - 1) + p_at(j - 1); }
   static constexpr int s(int j) { return j == 0 ? 0 : s(j - 1) + s_at(j - 1); }
-  static constexpr int copy(int j) { return j < 4 ? j : -1; }
+  static constexpr int copy(int j) {
+    constexpr int wide[16] = {-1, 0, -1, 1, -1, 2, -1, 3, 4, 5, 6, 7, -1, -1, -1, -1};
+    return D == 128 ? wide[j] : j < 4 ? j : -1;
+  }
 };
 // P of contraction step 0 (18 stages and its last conversion) ahead of dV, all of it ahead of step 1; dS likewise in dK
-static_assert(DkvStages::p(8) > 18 && DkvStages::p(11) == 34 && DkvStages::s(8) > 8 && DkvStages::s(11) == 17, "d = 64");
+static_assert(DkvStages<128>::p(16) > 18 && DkvStages<128>::p(23) == 34 && DkvStages<128>::s(16) > 8 && DkvStages<128>::s(23) == 17, "d = 128");
+static_assert(DkvStages<64>::p(8) > 18 && DkvStages<64>::p(11) == 34 && DkvStages<64>::s(8) > 8 && DkvStages<64>::s(11) == 17, "d = 64");
 
-// d = 128: what lies behind which of the 128 matrix instructions (ticks) of a unit: S of the first 32 keys | S of the other 32 | dP | dV | dK.
+// 16x16x32 instructions: what lies behind which of the 128 (ticks) of a unit: S of the first 32 keys | S of the other 32 | dP | dV | dK.
 struct DkvTicks : TickTable<128, 60> {
   static constexpr int KS = 8, PH = 4 * KS;  // LDS operands of a phase; its ticks
   static constexpr int kAhead = 4;           // Q operands of a unit that are read in the unit before
@@ -172,6 +177,24 @@ struct DkvTicks : TickTable<128, 60> {
 // P of the other keys two instructions behind their S
 static_assert(DkvTicks().pw[DkvTicks().p[DkvTicks::PH + 2] - 1].item < 8, "P");
 
+// d = 128: which matrix instruction, by the number of blocks of all heads and of 64-token blocks in a query block's list.  The small one saves
+// energy and costs issue slots, so the large one wins where a launch leaves SIMDs idle and power does not hold the clock.  Time of the pass with the large
+// instruction over that with the small one, both in turn in one process, three sets of inputs, iid lists, top-k (from run to run 0.005; one build against
+// another moves kernels of 15 to 50 us by 0.01 to 0.02 by where their code lies):
+//   one launch    (with dQ) 32 blocks, k 4 0.984, 8 0.984, 32 0.981 (29.6 / 30.1 us); 64 in heads of 32, 2 0.987, 8 0.987, 32 0.994, of 64, 8 0.988, 16 0.994, 64
+//                 0.987; 96, 8 0.982 and 0.987, 12 0.993, 16 0.997 and 0.985, 32 0.999, 96 1.009; 128 in heads of 32, 8 0.989, 16 1.010, of 64, 8 0.994, 16
+//                 0.999, 24 1.009, 64 1.020, of 128, 8 0.988, 12 0.996, 16 1.012, 128 1.026; 160, 4 0.994, 8 1.003; 192 in heads of 32, 8 0.994, of 192, 8 1.014, 64
+//                 1.034; 256 in heads of 32, 8 0.994, of 64, 8 0.992, 64 1.033, of 256, 8 1.054, 128 1.031
+//   two launches  288, 4 0.976, 8 0.986 to 0.997, 12 1.000, 16 1.001, 96 1.018; 320, 4 0.969, 8 0.987 and 1.002, 12 0.995, 16 1.013; 384 in heads of 32 to 192, 4 0.985
+//                 to 0.996, 6 0.989 to 0.996, 8 0.989 to 1.001, 10 1.009, 16 1.020; 448, 8 0.998, 64 1.061; 512, 8 1.009 to 1.022; 768, 8 1.018
+//   64 x 16       32, top-16 0.988, 64 0.965; 64, 32 0.991, 128 0.961; 128, 32 0.984, 64 0.967, 256 0.961 (81.4 / 84.7 us); 192, 32 1.004; 256, 64 1.004 and 1.009;
+//                 288, 16 0.995, 32 0.969, 64 0.964, 256 0.965; 320, 32 0.975; 384, 24 0.991, 32 0.989 and 1.001; 448, 32 0.991, 64 1.013; 512, 64 1.007; 1024, 64 1.040
+inline bool dkv_narrow(int blocks, int entries, int key_cubes_16) {
+  if (key_cubes_16) return blocks > 384;
+  if (blocks <= kDkvFourWaves) return blocks > 64 && blocks * entries > 1536;
+  return blocks > 384 || entries > 8;
+}
+
 // What the coarse backward of a short sequence is formed from (see coarse_small.h).
 struct SmallCoarseArgs {
   const float *qc, *kc, *vc, *doc, *lse_c, *dot;
@@ -189,7 +212,7 @@ __device__ __forceinline__ float2 load_shared(const float* p) {
 
 // `smem`: DkvShape::LDS bytes, aligned to 1024.  COARSE: the pooled-gradient terms are formed here (NW = 4, cubes of one block),
 // in `lc`, and dkc, dvc are not read.
-template <int D, int NW, bool SUB, bool COARSE>
+template <int D, int NW, bool SUB, bool COARSE, bool NARROW>
 __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, unsigned block, int BH, int Nc, int K, float sl2, float scale,
                                           const uint4* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
                                           const uint4* __restrict__ dof, const int32_t* __restrict__ col,
@@ -199,18 +222,18 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
                                           const uint64_t* __restrict__ mask, uint4* __restrict__ dk, uint4* __restrict__ dv,
                                           int m_blocks, int stream, const RasterMap& raster, const SmallCoarseArgs& sc,
                                           SmallCoarse<D>* lc) {
-  constexpr bool kNarrow = D == 128;  // 16x16x32 matrix instructions, else 32x32x16
-  using TL = std::conditional_t<kNarrow, NarrowTile<D>, Tile<D>>;
+  using TL = std::conditional_t<NARROW, NarrowTile<D>, Tile<D>>;
   using SH = DkvShape<D, NW>;
   constexpr int CPR = TL::CPR, KS = D / 16, DVB = D / 32, NT = 64 * NW, LPT = kTile * CPR / NT;
   constexpr int EPR = NW / 2;              // list entries a round of units takes
   constexpr int HALF = SH::HALF, STAGE = SH::STAGE, NST = SH::NST;
   constexpr int NC = HALF / 1024;          // copy instructions per 32 rows
-  constexpr int kAhead = kNarrow ? DkvTicks::kAhead : 2;  // Q operands that are read ahead of their unit
+  constexpr int kAhead = NARROW ? DkvTicks::kAhead : 2;  // Q operands that are read ahead of their unit
   constexpr int NCD = 2 * DVB;             // steps of the dV and of the dK phase
   constexpr int OS = D;
   static_assert(HALF % 256 == 0 && STAGE % 256 == 0, "the operand addresses XOR the bits below 256");
-  static_assert(KS == NCD && NC == KS && (!kNarrow || KS == DkvTicks::KS), "phase interleave");
+  static_assert(KS == NCD && NC == KS && (!NARROW || KS == DkvTicks::KS), "phase interleave");
+  static_assert(!NARROW || D == 128, "the small instruction has tables for d = 128");
   static_assert(!COARSE || (NT == kSmallThreads && !SUB), "the coarse backward takes 256 threads");
 
   // Start-up: one descriptor load (key block, begin and end of its run of the block's list, slot; the
@@ -316,8 +339,8 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     }
   }
   // [columns of d][keys], in blocks of the matrix instruction's size
-  constexpr int MT = kNarrow ? 16 : 32, XB = D / MT, KB = kTile / MT, AV = kNarrow ? 4 : 16;
-  using Acc = std::conditional_t<kNarrow, f32x4, f32x16>;
+  constexpr int MT = NARROW ? 16 : 32, XB = D / MT, KB = kTile / MT, AV = NARROW ? 4 : 16;
+  using Acc = std::conditional_t<NARROW, f32x4, f32x16>;
   Acc dka[XB][KB], dva[XB][KB];
 #pragma unroll
   for (int x = 0; x < XB; ++x)
@@ -334,10 +357,10 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
   if (nu >= NST - 1) wait_vmcnt<(NST - 1) * G>();
   else wait_vmcnt<0>();
   __syncthreads();
-  // K, and V of the first 32 keys; kNarrow: operand [half][i] is contraction step i / 2 of the keys 32 * half + 16 * (i % 2) ..
+  // K, and V of the first 32 keys; NARROW: operand [half][i] is contraction step i / 2 of the keys 32 * half + 16 * (i % 2) ..
   bf16x8 kreg[2][KS], vreg[KS];
   {
-    if constexpr (kNarrow) {
+    if constexpr (NARROW) {
       const int lane_k = TL::rowmajor_lane(lane) + LAST;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
@@ -377,7 +400,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
     for (; u < nu; ++u) body(std::false_type{}, u, u % NST);
   };
   const int wave_rows = (int)(HALF + wave * (NST * STAGE));  // this wavefront's stages
-  if constexpr (kNarrow) {
+  if constexpr (NARROW) {
   using TK = DkvTicks;
   constexpr TK ticks;
   constexpr int PH = TK::PH;
@@ -749,7 +772,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
         }
       }
     };
-    using DS = DkvStages;
+    using DS = DkvStages<D>;
     in_steps<KS>([&](auto number) {
       constexpr int s = decltype(number)::value, m = KS + s;
       wait_lgkmcnt<reads_in(m - 1)>();
@@ -857,7 +880,7 @@ __device__ __forceinline__ void dkv_block(unsigned char* smem, int* last_run, un
 #pragma unroll
             for (int g4 = 0; g4 < AV / 4; ++g4) {
               const Acc& a = pass == 0 ? dka[x][b] : dva[x][b];
-              const int at = kNarrow ? merge_offset(b * 16 + l16, x * 16 + 4 * g16, OS) : merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS);
+              const int at = NARROW ? merge_offset(b * 16 + l16, x * 16 + 4 * g16, OS) : merge_offset(b * 32 + l32, x * 32 + 8 * g4 + 4 * h, OS);
               *(float4*)&Op[at] = make_float4(a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]);
             }
       }

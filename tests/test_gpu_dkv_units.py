@@ -73,3 +73,27 @@ def test_four_heads_at_a_time(d=128, H=5, K=3):
     for n in ("dq", "dk", "dv"):
         for i, h in enumerate(heads):
             assert_close(bf16_to_np(getattr(buf, n)[:, h]), ref[n][:, i], f"{n} of head {h}")
+
+
+# d = 128, both sides of the lines between the 32x32x16 and the 16x16x32 matrix instruction: one launch with dQ (up to 256 blocks, with the coarse
+# backward up to 64 cubes a head), two launches.  Heads, grid of a head (tokens), entries.
+@pytest.mark.parametrize("H,grid3,K", [(1, (16, 16, 16), 25), (1, (16, 16, 16), 62), (3, (8, 16, 16), 16), (3, (8, 16, 16), 17), (2, (14, 15, 16), 12),
+                                       (2, (14, 15, 16), 13), (3, (16, 16, 16), 8), (3, (16, 16, 16), 9), (1, (7, 22, 30), 16), (1, (7, 22, 30), 17),
+                                       (2, (7, 22, 30), 8), (2, (7, 22, 30), 9), (3, (7, 22, 30), 8), (3, (7, 22, 30), 9),
+                                       (4, (7, 22, 30), 8), (4, (7, 22, 30), 9), (7, (16, 16, 16), 8)])
+def test_either_matrix_instruction(H, grid3, K, d=128):
+    import torch
+    from paper_2505_13389_amd import vsa
+    wl = Workload("dkv_instruction", 1, H, *grid3, d, K)
+    bits = tiled_bits(wl, seed=H + K, pad_garbage=True)
+    x, dev, g = widen(bits), to_dev(bits), grid_of(wl)
+    idx = lists_of_spread_degrees(np.random.default_rng(H + K), H, g.Nc, K)
+    ref = orc.backward(g, x["q"], x["k"], x["v"], x["gate_c"], x["gate_f"], x["dout"], idx, K, real="f32")
+    buf = vsa.Buffers(problem_of(wl))
+    a = (dev["q"], dev["k"], dev["v"], dev["gate_c"], dev["gate_f"])
+    buf.block_idx.copy_(torch.from_numpy(idx))
+    buf.forward(*a, indices_given=True)
+    buf.backward(*a, dev["dout"], workspace_kept=True)
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv"):
+        assert_close(bf16_to_np(getattr(buf, n)), ref[n], n)

@@ -46,7 +46,7 @@ def random_cases(n, seed=20250515, tag="rnd16"):
 CASES.update(random_cases(8))
 # Launches of 288 to 1152 query blocks, on a clip whose last layer of cubes holds dead key cubes (tiles of four entries, the last one
 # partial or not): the kernel for short lists (0), two and four wavefronts per workgroup.  d, heads, list length -> kernel
-KERNEL = {(128, 5, 1): 0, (128, 5, 7): 0, (128, 12, 48): 0, (128, 5, 37): 0, (128, 5, 49): 2, (128, 5, 70): 2, (128, 3, 33): 2, (128, 3, 49): 2,
+KERNEL = {(128, 5, 1): 0, (128, 5, 7): 0, (128, 12, 48): 0, (128, 5, 37): 0, (128, 5, 49): 2, (128, 5, 70): 2, (128, 3, 33): 2, (128, 3, 49): 2, (128, 4, 33): 2,
           (128, 6, 7): 2, (128, 6, 241): 2, (64, 6, 1): 0, (64, 6, 7): 0, (64, 6, 48): 0, (64, 6, 49): 0, (64, 6, 70): 4, (64, 9, 9): 2, (64, 9, 70): 2}
 CASES.update({f"blocks{96 * _H}_d{_d}_k{_k}": Workload(f"blocks{96 * _H}_d{_d}_k{_k}", 1, _H, 6, 22, 30, _d, _k) for _d, _H, _k in KERNEL})
 

@@ -108,7 +108,7 @@ struct DqTicks : TickTable<96, 32> {
       for (int n = s[t]; n < s[t + 1]; ++n)
         for (int m = p[t]; m < kPOps; ++m)
           if (pw[m].item <= sw[n].item) return false;
-    return true;
+    return ordered(pw, kPOps) && ordered(sw, kSOps);
   }
 };
 static_assert(DqTicks().in_order(), "operations of dQ");

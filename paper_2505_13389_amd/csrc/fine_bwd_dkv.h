@@ -173,9 +173,16 @@ struct DkvTicks : TickTable<128, 60> {
     deal(p, pw, kPOps, PH / 2 + 2, 2 * PH - 1);
     deal(s, sw, kSOps, 2 * PH + 2, 3 * PH - 1);
   }
+  // Operations lie two instructions behind what they need and are done one instruction ahead of what needs them: S of the first 32 keys (items
+  // 0 .. 7) is there at tick PH / 2, that of the others at PH, dP at 2 PH, where dV begins; dK begins at 3 PH.
+  constexpr bool in_order() const {
+    if (p[PH / 2 + 2] != 0 || p[2 * PH - 1] != kPOps || s[2 * PH + 2] != 0 || s[3 * PH - 1] != kSOps) return false;
+    for (int n = 0; n < p[PH + 2]; ++n)
+      if (pw[n].item >= 8) return false;
+    return ordered(pw, kPOps) && ordered(sw, kSOps);
+  }
 };
-// P of the other keys two instructions behind their S
-static_assert(DkvTicks().pw[DkvTicks().p[DkvTicks::PH + 2] - 1].item < 8, "P");
+static_assert(DkvTicks().in_order(), "operations of dK/dV");
 
 // d = 128: which matrix instruction, by the number of blocks of all heads and of 64-token blocks in a query block's list.  The small one saves
 // energy and costs issue slots, so the large one wins where a launch leaves SIMDs idle and power does not hold the clock.  Time of the pass with the large

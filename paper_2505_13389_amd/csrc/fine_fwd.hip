@@ -103,8 +103,8 @@ __device__ __forceinline__ void gang_start(unsigned* arrived, unsigned every) {
 // What lies behind which matrix instruction of a unit, S of the next unit | PV, and where the softmax of a unit, in operations (p_ops), is done:
 // from the second instruction of the PV phase before it to the last but one of the S phase of the next.
 template <int D>
-struct FwdTicks : TickTable<D / 2, 1> {  // (two units)
-  using Table = TickTable<D / 2, 1>;
+struct FwdTicks : TickCycles<D / 2> {  // (two units)
+  using Table = TickCycles<D / 2>;
   using typename Table::Work;
   using Table::cycles;
   using Table::T;
@@ -149,7 +149,11 @@ struct FwdTicks : TickTable<D / 2, 1> {  // (two units)
     }
     this->deal(ahead, w, kOps, in_pv(1), in_s(PH - 1));
   }
+  // A unit's operations begin behind the second matrix instruction that follows its S, and all of them lie ahead of the check of the references,
+  // behind the last but one of the next unit's S.
+  constexpr bool in_order() const { return ahead[in_pv(1)] == 0 && ahead[in_s(PH - 1)] == kOps && this->ordered(w, kOps); }
 };
+static_assert(FwdTicks<128>().in_order() && FwdTicks<64>().in_order(), "operations of the softmax");
 
 // PAIRS: the first `pairs` workgroups take two blocks, one per wavefront (d = 128, NW = 2; at d = 64 two wavefronts per SIMD hide one
 // another's start-up).  Launches without pairs have instances of their own, which know each wavefront's key half: 288 blocks,

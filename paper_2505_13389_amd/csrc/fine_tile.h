@@ -136,9 +136,9 @@ struct NarrowTile {
   static constexpr int CPR = Tile<D>::CPR, ROW_BYTES = Tile<D>::ROW_BYTES, BYTES = Tile<D>::BYTES, RPI = Tile<D>::RPI;
 
   __device__ static __forceinline__ int swz(int r) {
+    static_assert(D == 128, "16 slots a row");
     const int low = (r >> 3) & 1;
-    if (D == 128) return (((r & 7) ^ (low << 2)) << 1) | low;
-    return ((((r >> 1) & 3) ^ (low << 1)) << 1) | low;
+    return (((r & 7) ^ (low << 2)) << 1) | low;
   }
   __device__ static __forceinline__ int off(int r, int c) { return r * ROW_BYTES + ((c ^ swz(r)) << 4); }
 

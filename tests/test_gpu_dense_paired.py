@@ -1,19 +1,23 @@
-"""d = 128, every block selects every block: the walks start apart and wrap around, across the chunks of 64 list entries, in wavefronts with a block
-of their own (the first 1024 blocks) and in pairs that share one; forward, dQ and dK/dV against float64."""
+"""d = 128, every block selects every block: the walks start apart and wrap around, across the chunks of 64 list entries (key cubes of 16 tokens: of 16
+tiles), in wavefronts with a block of their own (the first 1024 blocks), in two that share one, of which each has its half of every tile, and in
+four; forward, dQ and dK/dV against float64."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("grid3,H", [((8, 32, 32), 9), ((7, 30, 29), 9), ((4, 36, 32), 16)])  # 128, 128 (padded) and 72 blocks a head
-def test_dense_walks_wrap(grid3, H, d=128):
+# 128, 128 (padded) and 72 blocks a head; 504 blocks: none of its own; key cubes of 16 tokens, all of them live, with 1152, 504 and 216 blocks
+@pytest.mark.parametrize("grid3,H,sub", [((8, 32, 32), 9, False), ((7, 30, 29), 9, False), ((4, 36, 32), 16, False), ((4, 36, 32), 7, False),
+                                         ((4, 36, 32), 16, True), ((4, 36, 32), 7, True), ((4, 36, 32), 3, True)])
+def test_dense_walks_wrap(grid3, H, sub, d=128):
     import torch
     from paper_2505_13389_amd import vsa
-    pb = vsa.Problem(1, H, *grid3, d, 1)
+    flags = vsa.VSA_FLAG_KEY_CUBES_16 if sub else 0
+    pb = vsa.Problem(1, H, *grid3, d, 1, flags=flags)
     Np, Nc = vsa.vsa_padded_tokens(pb)
-    pb = vsa.Problem(1, H, *grid3, d, Nc)
+    pb = vsa.Problem(1, H, *grid3, d, 4 * Nc if sub else Nc, flags=flags)
     routes = vsa.vsa_host_routes(pb)
-    assert routes["fwd_pairs"] > 0 and routes["dq_pairs"] > 0
+    assert (routes["fwd_pairs"] > 0, routes["dq_pairs"] > 0) == (H * Nc > 512,) * 2 and routes["fwd_waves"] == routes["dq_waves"] == (2 if H * Nc > 256 else 4)
     g = torch.Generator(device="cuda")
     g.manual_seed(Nc + H)
     rand = lambda: torch.randn((1, H, Np, d), generator=g, device="cuda").to(torch.bfloat16)

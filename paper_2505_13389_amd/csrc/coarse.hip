@@ -109,29 +109,50 @@ __global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_coarse_fused(int Nc, in
   {
     const int cb = wave % CB, ks = wave / CB;
     f32x4m acc = {0.f, 0.f, 0.f, 0.f};
-    const float* vcol = vb + cb * 16 + l16;
-    auto group = [&](int k0, auto value) {  // value(j): of row k0 + 4*kq + j, which exists
+    auto multiply = [&](int k0, const float (&b)[4]) {
       const float4 a = *(const float4*)&S[l16 * LDS_ROW + k0 + 4 * kq];
-      const int kk = k0 + 4 * kq;
-      float b[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = kk + j < Nc ? value(j) : 0.f;
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[0], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[1], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[2], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[3], acc, 0, 0, 0);
+    };
+    auto multiply_part = [&](int k0, float (&b)[4]) {  // (rows beyond Nc are taken as zero)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = k0 + 4 * kq + j < Nc ? b[j] : 0.f;
+      multiply(k0, b);
     };
     if constexpr (BATCH) {
       for (int k1 = 0; k1 + ks * 16 < kpad; k1 += 16 * KSPLIT * kStep) {  // (uniform)
 #pragma unroll
         for (int i = 0; i < kStep; ++i) {
           const int k0 = k1 + (i * KSPLIT + ks) * 16;
-          if (k0 < kpad) group(k0, [&](int j) { return vv[i][j]; });
+          if (k0 < kpad) multiply_part(k0, vv[i]);
         }
         if (k1 + 16 * KSPLIT * kStep < kpad) request_v(k1 + 16 * KSPLIT * kStep);
       }
     } else {
-      for (int k0 = ks * 16; k0 < kpad; k0 += 16 * KSPLIT) group(k0, [&](int j) { return vcol[(long long)(k0 + 4 * kq + j) * D]; });
+      // Whole groups without a look at their rows, then the last one if it is not whole (up to 64 cubes, one or two groups a wavefront: with a look at
+      // all of them).  Against a look at every row, which reads what is there or takes a branch around what is not, the kernel, us, d = 128: 72 cubes, 8
+      // heads 11.4 and 11.7 -> 11.4, 120, 3 heads 12.6 and 12.9 -> 12.5, 256, 12 heads 18.5 and 18.9 -> 17.7, 512, 12 heads 46.1 and 45.0 -> 42.3, 1280, 4 heads
+      // 128 -> 118; d = 64: 72, 8 heads 9.9 and 10.2 -> 9.9, 512, 12 heads 31.8 and 31.1 -> 29.9; up to 64 cubes 10.6 -> 10.6 (whole groups first 10.7).
+      float b[4];
+      auto value = [&](int row) { return vb[(unsigned)(row * D + cb * 16 + l16)]; };
+      auto part_of_a_group = [&](int k0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] = value(min(k0 + 4 * kq + j, Nc - 1));
+        multiply_part(k0, b);
+      };
+      int k0 = ks * 16;
+      if (NCH == 1) {
+        for (; k0 < kpad; k0 += 16 * KSPLIT) part_of_a_group(k0);
+      } else {
+        for (; k0 + 16 <= Nc; k0 += 16 * KSPLIT) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) b[j] = value(k0 + 4 * kq + j);
+          multiply(k0, b);
+        }
+        if (k0 < kpad) part_of_a_group(k0);
+      }
     }
     *(float4*)part[wave][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
     __syncthreads();
@@ -230,11 +251,11 @@ hipError_t launch_coarse(int BH, int Nq, int Nk, int d, int K, float scale, cons
     else VSA_FUSED_AS(64, NCH_, false);            \
   } while (0)
     // V_c in batches (BATCH): 513 to 768 cubes at d = 128, where compute units get a second workgroup.  The kernel, us, one group at a time against
-    // batches: 513 cubes, 8 heads (264 workgroups) 52.2 / 48.6, 624, 7 heads 62.5 / 54.1, 768, 6 heads 72.7 / 63.8, 624, 24 heads 129.6 / 103.5.
-    // Up to 256 workgroups the row step, in the 64 registers that two workgroups leave a lane, costs what the batches save: 544 cubes, 7 heads (238
-    // workgroups) 32.5 / 33.7, 4 heads 32.3 / 33.1, 624, 4 heads 34.9 / 35.2, 768, 1 head 39.5 / 39.0.  d = 64, with half the groups a wavefront: 513 cubes, 12
-    // heads 33.7 / 36.2, 624, 24 heads 67.6 / 71.0, 768, 12 heads 59.5 / 59.7.  Fewer cubes: 256 20.1 / 20.6, 280 21.8 / 22.9.  From 769 on a second workgroup
-    // does not fit into LDS (90.6 KB a workgroup at d = 128); batches were not tried there.
+    // batches: 513 cubes, 8 heads (264 workgroups) 51.8 / 49.7, 624, 7 heads 59.6 / 55.5, 24 heads 136 / 123, 768, 6 heads 70.2 / 66.5.  Up to 256
+    // workgroups the row step, in the 64 registers that two workgroups leave a lane, costs more than the batches save: 544 cubes, 7 heads (238
+    // workgroups) 30.9 / 33.6, 4 heads 30.7 / 33.2, 624, 4 heads 33.1 / 35.6, 768, 1 head 36.5 / 39.4.  d = 64, with half the groups a wavefront: 513 cubes, 12
+    // heads 33.3 / 36.5, 624, 24 heads 71.1 / 78.2, 768, 12 heads 61.5 / 66.0.  From 769 on a second workgroup does not fit into LDS (90.6 KB a workgroup
+    // at d = 128); batches were not tried there.
     const bool batch = d == 128 && Nc > 512 && Nc <= 768 && fgrid > 256;
     // NCH = logits per lane of the row step: the smallest that covers Nc
     if (batch) VSA_FUSED_AS(128, 12, true);

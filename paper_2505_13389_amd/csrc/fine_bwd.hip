@@ -22,17 +22,20 @@ namespace vsa {
 //
 // d = 128: one wavefront per SIMD; dQ takes 128 of the accumulation registers and Q and dO_f the other 128 (a
 // matrix instruction reads an operand from either file).  16x16x32 instructions, 96 a unit, with what lies behind each dealt by DqTicks
-// (ticks.h; why the small ones, see fine_bwd_dkv.h: 4.2 other instructions per 32 cycles of matrix work).  Pad keys' rows of S^T start from
+// (ticks.h; why the small ones, see fine_bwd_dkv.h: 3.9 other instructions per 32 cycles of matrix work).  Pad keys' rows of S^T start from
 // a large negative value, which is formed where a unit or the one before has some.
 // d = 64: two wavefronts per SIMD, whose 256 registers do not
 // hold both halves' S and dP, and 32x32x16 instructions: S 0 | dP 0 | S 1 | dP 1 | dQ 0 | dQ 1, -Delta is added in vector arithmetic.
 //
 // What bounds it (d = 128): the clock, which falls as the pipe fills, and instruction issue: a unit is 96 matrix instructions (1536 cycles of
-// the matrix pipe) and 204 others, 1920 cycles by the costs of ticks.h, about as many as the 1930 of the form before it, with 48
-// large instructions at a clock 7 % lower (39936 tokens: 1.72 GHz, now 1.84): 1468 -> 1405 us of 39936 tokens, 12 heads, top-78.  With dK/dV's
+// the matrix pipe) and 187 others (191 where all blocks are shared, 195 for those shared beside paired ones), 1870 to 1900 cycles by the costs of ticks.h
+// where the form before it, with 48 large instructions, had 1930, at a clock 7 % lower (39936 tokens: 1.72 GHz, now 1.84): 1468 -> 1405 us of 39936
+// tokens, 12 heads, top-78.  With dK/dV's
 // like form, whole steps: 16384 tokens, top-32 961 -> 922 us, 39936 tokens, top-78 4850 -> 4696, B = 2, 16 heads, top-128 of 256, local
-// lists 7953 -> 7535, 256-token cubes 918 -> 881, the op at 13338 tokens 453 -> 444.  More even still: 16 to 24 cycles lie behind most matrix
-// instructions, 28 to 46 behind those with a part of the list entry's scalar chain, 16 (the pipe's own) behind the last 15.
+// lists 7953 -> 7535, 256-token cubes 918 -> 881, the op at 13338 tokens 453 -> 444.  Most matrix instructions take 16 to 25 cycles
+// with what lies behind them, those with a part of the list entry's scalar chain up to 30, the seam of two units 38 to 42.
+// Launches that leave SIMDs idle, the pass against the form before: 32 to 128 blocks 0.99 to 1.015 of the time, 192 to 512 0.93 to 1.005 (4 to 128 entries,
+// 16 to 256 key cubes of 16 tokens; run to run 0.01).
 // Start-up, merge and stores are about 7 us of a shared block's 95; with a wavefront per block 39936 tokens, 12 heads, d =
 // 128, top-78 took 1500 -> 1470 us, 16384 tokens, top-32 281 -> 269, top-8 121 -> 96, 1024 blocks, top-8 0.84 of the time.
 // Measured against 32 keys x 32 queries per wavefront, four wavefronts in step, two per SIMD: 39936 tokens, 12 heads, d = 128,

@@ -41,10 +41,12 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // while S of the others is multiplied.  Else 32x32x16 instructions (d = 128 64, d = 64 32, of 32 cycles) in STEPS: one step = one LDS
 // operand multiplied with both key halves, the operand reads of the step kAhead later, and behind either instruction a share of the
 // copies and of the vector work (DkvStages).
-// Why: under the power limit the chip gets 1.81 PFLOP/s out of the large instructions on N(0,1) operands and 2.05 to 2.19 out of the small ones,
-// but each costs 6 cycles of issue where a large one, for the work of two, costs 4.  With five vector instructions per 32 cycles of matrix work the
-// two are 4 % apart and with more of them the small ones lose: d = 128 has 4.2 others per 32 cycles here, d = 64 6.6.  (The forward,
-// with 6.5: 16384 tokens, top-32 254 -> 257 us, 39936 tokens, top-78 1232 -> 1302 us, so it keeps the large ones.)
+// Why: under the power limit the chip gets 1.86 PFLOP/s out of the large instructions on N(0,1) operands and 2.11 to 2.29 out of the small ones,
+// but each costs 6 cycles of issue where a large one, for the work of two, costs 4.  With so many multiplications among them, per 32 cycles of matrix
+// work: 3 1.75 / 1.95, 4 1.73 / 1.92, 5 1.71 / 1.78, 6 1.65 / 1.67, 7 1.55 / 1.59 (profiles/rates_copy_matrix_permute.txt).  A unit has
+// 3.9 others per 32 cycles at d = 128 (4.6 with key cubes of 16 tokens), 6.6 at d = 64, which has not been tried.  (Nor has the forward, 5.9 now, in this
+// form.  With 6.5 then and two small instructions behind one another, the form that made this pass slower too, it took 254 -> 257 us, 16384 tokens,
+// top-32, and 1232 -> 1302, 39936 tokens, top-78.)
 // The row terms enter through the accumulators' initial value: the preprocess kernel stores -lse*log2e/sl2
 // (then P = exp2(S' * sl2); -30000 on pad rows, whose P underflows to 0) and -Delta per row, and a lane
 // reads those of its rows straight into the first matrix instruction's C operand.  Pad KEY rows need
@@ -57,14 +59,14 @@ __device__ __forceinline__ void subcube_pooled_term(const float* __restrict__ po
 // pooled-gradient terms are per key cube.
 //
 // What bounds it: the clock, which falls as the matrix pipe fills, and the instructions of one wavefront.  d = 128: a unit is 128
-// matrix instructions (2048 cycles of the pipe) and 267 others, 2520 cycles by the costs of fine_fwd.hip; a whole launch (39936 tokens, 12
+// matrix instructions (2048 cycles of the pipe) and 251 others (291 with key cubes of 16 tokens), 2520 cycles (2720) by the costs of fine_fwd.hip; a whole launch (39936 tokens, 12
 // heads, top-78) 3.21 M cycles at 1.66 GHz where the same order with 64 large instructions took 3.05 M at 1.53: a unit takes a fifth less
 // energy.  Steps of 16384 tokens, top-32 964 -> 942 us, 39936 tokens, top-78 4838 -> 4764, B = 2, 16 heads, top-128 of 256 7929 -> 7705, 256-token
 // cubes 933 -> 918, of which this pass is 35 to 40 %.  Two small instructions behind one another with the vector work of both behind
 // them: 21 % more cycles than the large ones, and slower; behind each a share of its own, but dealt by the count of instructions: 12 % more.
 // d = 64: 32 and 212 in 1480 cycles, where 55 to 70 cycles
 // lie behind each matrix instruction of the dP phase and 4 to 20 behind those of S and the end of dK.  3 us of start-up and 5 us
-// of merge and stores per workgroup, which the other workgroup of the CU overlaps.  d = 64 with two wavefronts per SIMD (256
+// of merge and stores per workgroup, while nothing uses its SIMDs' matrix pipes.  d = 64 with two wavefronts per SIMD (256
 // registers each, four to a workgroup; K and V in LDS) took 0.93 of the time of an earlier order (B = 2, 8 heads, top-32,
 // local lists: 317 -> 296 us) where the stages take 0.96 to 0.98 of it; with stages it has not been tried.
 // Before (32 keys x 32 queries per wavefront, 4 wavefronts in step, one workgroup per CU: every LDS operand fed one matrix instruction): 39936 tokens,

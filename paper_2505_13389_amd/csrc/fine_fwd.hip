@@ -29,14 +29,15 @@
 // wavefront that is alone on its SIMD, measured behind matrix instructions: 5 cycles in vector arithmetic, 8 if the next one
 // needs its result, exp2 9, an LDS read 8, scalar ones and waits 4; five or six plain ones fit behind a matrix instruction,
 // and none is made up for by fewer behind the next.  So the softmax is cut into operations that are dealt, like the reads, copies and the
-// scalar chain of the next list entry, to the 32 matrix instructions one by one (FwdTicks: 32 to 55 cycles behind each as emitted), pinned by a
+// scalar chain of the next list entry, to the 32 matrix instructions one by one (FwdTicks: 32 to 55 cycles each as emitted, 87 at the check of the references), pinned by a
 // scheduling barrier right behind each of them, and what is rare (a moved
 // reference, pad keys, a new chunk of the list) lies out of the loop's line.  A wavefront with a block of its own walks in a loop of its own,
 // where the half of a unit is known and every second one is in the same tile; the tile is counted on, not worked out; the check for a moved
 // reference is one comparison.  Against stages of the softmax in place of operations, a list entry at once and 210 others a unit: 1490 -> 1330
 // cycles by the costs, 2.03 -> 1.87 M in a whole launch (39936 tokens, 12 heads, top-78), of which the clock leaves a third of the time: 1217 ->
 // 1184 us for the forward, 252 -> 247 at 16384 tokens, top-32 (two generations' start-up and end in it), results the same bits.  16x16x32 matrix
-// instructions, which take less energy (fine_bwd_dkv.h), cost more issue slots than this loop has.
+// instructions take less energy and, for the same work, 8 cycles of issue more per large one (fine_bwd_dkv.h): with these operations dealt to them a unit
+// would be about 1590 cycles; not measured.
 // Around the walk a wavefront
 // spends 2 to 3 us until its first K is there, 1.4 on the first products, 3 on the merge and 2 (shared block) to 4 on
 // normalising, gating and storing, which nothing overlaps on its SIMD: halved per block where a wavefront has a block of
@@ -775,34 +776,28 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void k_fine_fwd(
   }
 }
 
-// Which kernel, by the number of query blocks and of 64-key tiles in a list.  From whole forwards back to back, N(0,1) inputs, 79
-// launches of 288 to 8192 blocks in heads of 72 to 500, lists of 2 to 44 tiles; figures: time with the general kernel over that with
-// the one for short lists, whose workgroups hide one another's start-up and wind-down but which takes longer per tile.
-//   d = 128  (133 launches more, both kernels in turn in one process, mean of two machines; a third had up to 0.03 more at 9 to 12
-//            tiles)  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  The general one loses where
-//            its last generation is nearly empty, for longer the emptier -- 1026 blocks, 8 tiles 1.025, 16 1.005, 24 0.99; 1056, 8 1.00, 16
-//            0.995, 20 0.995, 24 0.98; 1100, 6 1.01, 8 1.00, 16 0.99, 20 0.995, 24 0.98; 1152 in heads of 96, 4 1.035, 8 1.005, 12 1.00, 16
-//            0.995, 20 0.995, 26 0.98, of 288, 6 0.99, 10 0.985, 26 0.97; 1200, 8 1.01, 10 1.00, 12 0.995; 1280, 8 0.99, 16 0.98; 2112, 8
-//            0.995, 12 0.98, 16 0.97; 2200, 4 1.035, 6 1.00, 8 0.99, 12 0.98; 2205, 4 1.05, 6 0.995, 8 0.98; 2304 in heads of 96, 4 1.035, 8
-//            1.00, 10 0.985, 16 0.975, of 288, 4 1.03, 7 1.015, 8 1.005, 10 0.98, 16 0.96; 2400 in heads of 96, 4 1.025, 5 0.985, 6 0.975, of
-//            400 to 600, 5 1.005, 6 0.99; 2560, of 256, 4 1.01, 5 0.985, 6 0.975, of 512 and 640, 5 1.015, 6 1.00; 2600, 3 1.06, 4 1.005, 5
-//            0.98, 8 0.96; 2688, 3 1.055, 4 1.005, 5 0.985, 8 0.96, 18 0.94; 2736, 3 1.02, 4 1.00, 5 0.975, 8 0.95; 2800, 3 1.045, 4 0.995, 5
-//            0.98; 2880, 3 1.03, 4 0.955; 2940, 2 1.005, 3 0.995, 4 0.955; 3000, 3 1.01, 4 0.975 -- and where the blocks are shared and
-//            nearly fill a generation of the other: 468, 6 1.01, 8 1.005, 10 0.98, 16 0.95; 480, 8 1.02, 10 1.005, 12 0.99, 16 0.96; 504, 8
-//            1.035, 10 1.005, 12 0.99; 512, 8 1.025, 10 1.01, 12 0.985, 16 0.98.  From the launches before (some of them 0.02 to 0.03 higher
-//            than these where they meet): 360, 4 1.01, 6 0.995; 384, 4 1.01, 6 0.995, 12 0.97; 448, 4 1.015, 6 1.00, 8 0.996; 2112, 12 1.01,
-//            16 0.996; 3080, 4 1.05, 6 1.005, 8 0.975, 20 0.94; 3200, 6 1.01, 8 0.99; 4500, 3 1.01, 4 0.99. Elsewhere it wins: 576, 12 0.97;
-//            1024, 12 0.93; 1344, 8 0.96; 2048, 12 0.92; 3072, 4 0.97; 4096, 12 0.91; 8192, 12 0.90.
-//   d = 64   a generation of the general kernel is 1024 blocks: 384, 2 0.98; 560, 8 1.01, 16 1.01, 20 0.98; 1000, 4 0.96; 1056, 8 1.06, 20
-//            0.97; 1536, 12 1.08, 20 0.98; 2000, 4 0.99, 10 0.99; 2240, 8 1.04, 16 1.00; 2660, 8 1.02, 12 0.99; 3500, 6 1.00, 12 0.98; 4500, 2
-//            1.03, 6 1.00; 6144, 4 0.90.
+// Which kernel, by the number of query blocks and of 64-key tiles in a list.  The one for short lists hides its workgroups' start-up and wind-down
+// behind one another and takes longer per tile.  Figures: time of a whole forward with the general kernel over that with the other, both in turn in one
+// process, back to back, N(0,1) inputs, mean of two machines (which differ by 0.01 to 0.03 where a last generation is nearly empty).
+//   d = 128  1024 blocks are a generation of the general kernel (two per workgroup), 512 of the other.  Where blocks are shared: 360, 3 tiles 1.005, 4
+//            0.995, 5 0.985; 384, 3 1.005, 4 1.00, 5 0.985; 448, 3 1.02, 4 1.005, 6 1.02; 468, 6 1.005, 8 1.005; 480, 8 1.005, 10 1.02; 504, 8 1.015, 10 1.02, 12
+//            1.02; 512, 8 1.01, 10 1.02, 12 1.025.  Where the last generation of pairs is nearly empty: 1026, 8 0.995, 12 0.985, 20 0.97; 1056, 8
+//            0.98, 16 0.97, 24 0.955; 1100, 6 0.975, 12 0.96; 1152 in heads of 96, 4 0.99, 8 0.98, 16 0.97, of 288, 4 0.99, 8 0.98; 1200, 4 1.00, 8 0.98;
+//            1280, 4 0.995, 8 0.99, 10 0.97; 2112, 4 1.03, 8 0.965, 12 0.955; 2200, 4 1.02, 6 1.005, 8 0.975; 2205, 4 1.00, 8 0.98; 2304 in heads of 96, 4
+//            1.015, 6 1.01, 8 0.98, of 288, 6 1.01, 8 0.995, 12 0.965; 2400, 3 1.04, 5 1.00, in heads of 400, 5 1.01, 6 0.97; 2560 of 256, 3 1.00, 5 0.995, of
+//            512, 3 1.04, 5 0.995, 6 1.00; 2600, 3 1.055, 4 1.00, 5 1.00; 2688, 3 1.025, 4 1.015; 2800, 3 1.04, 4 1.025; 2880, 3 1.035, 4 0.99; 3000, 3 1.03, 4
+//            0.995; 3072, 2 1.015, 3 1.01; 3200, 3 1.045, 4 1.00, 6 0.99; 4200, 3 1.005, 4 0.955; 4500, 2 0.97, 3 0.965.
+//            The lines of 1025 to 1280, 2049 to 2304 and 4097 to 4608 blocks lie where the two kernels met when the general one took 1490 cycles a unit
+//            (now 1330): from 6 to 8 tiles on, and at 4500 blocks, it wins by 1 to 5 % there.
+//   d = 64   a generation of the general kernel is 1024 blocks: 384, 1 1.035, 2 1.00, 3 1.02, 4 1.01; 560, 8 0.995, 16 0.98, 20 0.95; 720, 8 1.02, 12 1.005, 16
+//            0.97; 1056, 8 1.03, 12 1.00, 14 1.00, 16 0.98; 1536, 12 1.05, 14 1.05, 16 0.97; 1920, 2 1.01, 4 1.00, 6 1.00, 8 0.99; 2240, 8 1.03, 10 1.00, 12
+//            0.97; 2660, 8 1.01, 9 1.005, 10 0.985; 3500, 4 1.00, 6 0.995, 8 0.99; 4500, 1 1.025, 2 1.005, 3 1.00, 4 0.99; 6144, 4 0.91.
 //   Large heads (d = 128), whose K and V outgrow an L2 several times: a second wavefront per SIMD also hides the trips beyond it, so
-//            the lines lie further out. 22 to 64 MiB: 2200 blocks in 2 heads, 6 tiles 1.01, 12 0.985, 16 0.97; 2400 in 2 and 3, 5 1.025, 6
-//            1.01, 8 1.00 (in 4 to 6: 5 1.005, 6 0.99, 8 0.98); 2560 in 2, 8 1.01; 2640 and 2673, 5 1.01, 6 0.995, 12 0.965; 2880 in 2 and 3,
-//            4 1.01, in 4 0.985; 3000, 3 1.02, 4 1.00; 3200, 7 1.015, 8 1.005, 12 0.985; 4320 to 4400, 3 1.025, 4 1.015, 6 0.985. From 64
-//            MiB, where the general kernel's workgroups also wait for one another (gangs): 2112 to 2304, 8 1.05, 16 1.02, 20 1.005, 24 0.995;
-//            2400 and 2560, 8 1.04, 16 1.01, 20 1.005, 24 0.99; 2730, 8 1.02, 16 1.005, 20 0.985; 3072, 4 1.035, 8 1.02, 16 1.00; 4096, 4
-//            1.03, 8 1.02, 16 1.00; 4224 in 2, 8 1.03, 16 0.99.
+//            the lines lie further out. 22 to 64 MiB: 2200 blocks in 2 heads, 6 tiles 1.005, 8 0.995, 12 0.985, 16 0.955; 2304 in 2, 8 0.98, 12 0.98, 16 0.955; 2400 in
+//            3, 5 1.00, 6 0.995, 8 1.005; 2560 in 2, 4 1.02, 6 1.00, 8 0.985; 2640 in 3, 3 1.005, 5 0.995; 2880 in 3, 3 1.005, 4 0.995, 5 0.985; 3200 in 4, 3 1.02, 5
+//            1.01, 7 1.00, 8 0.99; 4320 in 4, 3 1.04, 4 1.035, 6 1.02. From 64 MiB, where the general kernel's workgroups also wait for one another (gangs):
+//            2304, 8 1.04, 16 1.02, 20 1.015, 24 1.01; 2560, 8 1.03, 16 1.02, 20 1.005; 3072, 4 1.045, 8 1.02, 12 1.005, 16 1.00; 4096, 4 1.045, 8 1.01, 16 1.005;
+//            4224 in 2, 4 1.08, 8 1.04, 10 1.025.
 constexpr size_t kLargeHead = (size_t)22 << 20, kVastHead = (size_t)64 << 20;
 inline size_t kv_bytes(int Nc, int d) { return (size_t)Nc * kTile * d * 4; }
 inline bool fwd_short(int d, int Nc, unsigned grid, int tiles) {
